@@ -189,26 +189,16 @@ void fill_compress_args(CompressArgs& ca, const float* d_in, u64 n, float abs_eb
   ca.nonce = call_nonce();
 }
 
-// The launches of zc_compress / zc_compress_part over the tiles [first_tile, end_tile) of the stream.
-// `adopt`: the call continues one whose tag is in the control block (a later part).
+// The launch of zc_compress / zc_compress_part over the tiles [first_tile, end_tile) of the stream.
 void launch_compress(CompressArgs& ca, u32 first_tile, u32 end_tile, bool timed, hipStream_t stream) {
-  const u32 ntiles = u32(num_pack_tiles(ca.nb));
-  const u32 full_tiles = u32(ca.n / kPackValues);                       // tiles whose values all exist
-  const u32 end_full = end_tile < full_tiles ? end_tile : full_tiles;
   if (ca.nb == 0) {                                                     // the stream of no values
     EmptyStreamArgs ea{ca.ctl, ca.out, ca.out_cap, ca.eb_bits, ca.ix, ca.nonce};
     hipLaunchKernelGGL(empty_stream_kernel, dim3(1), dim3(64), 0, stream, ea);
     return;
   }
-  if (end_full > first_tile) {
-    if (timed)
-      launch_main(ZC_KERNEL_COMPRESS, compress_kernel<true>, dim3(end_full - first_tile), dim3(kPackThreads), stream, ca, first_tile, end_full);
-    else
-      hipLaunchKernelGGL(compress_kernel<true>, dim3(end_full - first_tile), dim3(kPackThreads), 0, stream, ca, first_tile, end_full);
-    ca.adopt = 1;
-  }
-  if (end_tile > full_tiles)                                            // the ragged last tile of the stream
-    hipLaunchKernelGGL(compress_kernel<false>, dim3(1), dim3(kPackThreads), 0, stream, ca, full_tiles, ntiles);
+  void (*kernel)(CompressArgs, u32, u32) = ca.ticketed ? compress_kernel<true> : compress_kernel<false>;
+  if (timed) launch_main(ZC_KERNEL_COMPRESS, kernel, dim3(end_tile - first_tile), dim3(kPackThreads), stream, ca, first_tile, end_tile);
+  else hipLaunchKernelGGL(kernel, dim3(end_tile - first_tile), dim3(kPackThreads), 0, stream, ca, first_tile, end_tile);
 }
 
 // Workspace of zc_compress_noalloc: a device array of the library itself, one copy per GPU,

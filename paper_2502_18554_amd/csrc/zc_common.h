@@ -267,8 +267,7 @@ __device__ inline u64 uniform64(u64 v) { return u64(uniform(u32(v))) | (u64(unif
 // that no earlier launch on the same workspace has had: the packet number of the dispatch in
 // its hardware queue (which a replay of a captured graph renews as well), the queue, a number
 // the host draws per call (its clock), and the workspace address, mixed.  A call of several
-// launches (a stream compressed in parts, the ragged last tile, the validation kernels of plain
-// streams) uses the tag of its first launch throughout: that launch leaves it in the control
+// launches (a stream produced in parts, the validation kernels of plain streams) uses the tag of its first launch throughout: that launch leaves it in the control
 // block, the later ones pick it up there (`adopt`).
 // ---------------------------------------------------------------------------------------
 extern "C" __device__ u64 zc_dispatch_id(void) __asm("llvm.amdgcn.dispatch.id");
@@ -339,6 +338,11 @@ __device__ inline float4 load_once(const float4* p) {
   const f32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p));
   return make_float4(t.x, t.y, t.z, t.w);
 }
+
+// Raw buffer accesses (the range check is the hardware's: what lies outside reads as zero): data format
+// word of the descriptor, and the cache policy of data that is touched once (non-temporal, see above).
+constexpr int kRawBuffer = 0x00020000;
+constexpr int kAccessOnce = 2;
 
 // A zero in a vector register that the compiler cannot see through.  An address that has it
 // added is not provably the same in every lane, so the access becomes a vector memory load.
@@ -429,7 +433,7 @@ constexpr int kDescStride = 16;            // in u64
 // device-coherent (sc1).  Nothing depends on that access being indivisible: torn halves fail
 // the tag check above.
 __device__ inline __amdgpu_buffer_rsrc_t desc_resource(const u64* desc) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(desc), 0, 0x7fffffff, 0x00020000);
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(desc), 0, 0x7fffffff, kRawBuffer);
 }
 constexpr int kCoherentAccess = 16;        // cache policy bits of the buffer builtins: sc1
 

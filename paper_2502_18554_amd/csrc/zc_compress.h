@@ -42,7 +42,7 @@ struct CompressArgs {
   u32 coherent;      // the look-back reads the tile's own chain with device-coherent loads too
   u32 ix;            // write an indexed stream (see index_bytes)
   u32 part_end;      // zc_compress_part: one past the last tile of this call; else 0
-  u32 adopt;         // this launch continues a call (a later part, the ragged last tile): its tag is in the control block
+  u32 adopt;         // this launch continues a call (a later part): its tag is in the control block
   u64 nonce;         // drawn by the host per call, goes into the tag (see launch_tag)
 };
 
@@ -98,32 +98,34 @@ __device__ inline int4 quantize4(const float4& x, const CompressArgs& a, bool ch
   return q;
 }
 
-// Raw input of one wave's share of a tile: 8 x 16 bytes per lane, every load in flight at once.
-template <bool FULL>
-__device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, float4 (&x)[8]) {
+// Values of a wave's share of a tile that exist: 2048 but for the wave at the end of the input and those behind it.
+constexpr u32 kWaveValues = u32(kWaveBlocks) * kBlockValues;
+__device__ inline u32 wave_values(const CompressArgs& a, u64 wblock0) {
   const u64 v0 = wblock0 * kBlockValues;
-  if (FULL) {
+  const u64 left = a.n > v0 ? a.n - v0 : 0;
+  return left < kWaveValues ? u32(left) : kWaveValues;
+}
+
+// Raw input of one wave's share of a tile: 8 x 16 bytes per lane, every load in flight at once.  They are
+// buffer loads whose range is the share's whole 16-byte pieces, so the ragged end of an input needs no branch
+// and no launch of its own: what lies beyond reads as zero without an access.  (The one to three values of an
+// incomplete last piece: see block_codes.)
+__device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u32 have, float4 (&x)[8]) {
+  const __amdgpu_buffer_rsrc_t share =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in + wblock0 * kBlockValues), 0, int(4u * (have & ~3u)), kRawBuffer);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = load_once(reinterpret_cast<const float4*>(a.in + v0 + u64(256 * i + 4 * lane)));
-    // Nothing moves across this line: left to itself the compiler puts the first use of the first value,
-    // and the wait for it, in front of the last four loads, which then go out a round trip late.
-    __builtin_amdgcn_sched_barrier(0);
-  } else {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const u64 idx = v0 + u64(256 * i + 4 * lane);
-      x[i].x = idx + 0 < a.n ? a.in[idx + 0] : 0.0f;
-      x[i].y = idx + 1 < a.n ? a.in[idx + 1] : 0.0f;
-      x[i].z = idx + 2 < a.n ? a.in[idx + 2] : 0.0f;
-      x[i].w = idx + 3 < a.n ? a.in[idx + 3] : 0.0f;
-    }
+  for (int i = 0; i < 8; ++i) {
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * (i & 3), 4096 * (i >> 2), kAccessOnce);
+    x[i] = make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
   }
+  // Nothing moves across this line: left to itself the compiler puts the first use of the first value,
+  // and the wait for it, in front of the last four loads, which then go out a round trip late.
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Quantise the wave's values where they landed and transpose the codes through LDS so that one
-// lane owns one block: q[j] = code j of the lane's block.
-template <bool FULL>
-__device__ inline void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, int lane, u32* wl,
+// lane owns one block: q[j] = code j of the lane's block.  have: see wave_values.
+__device__ inline void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                    i32 (&q)[32], u32& err) {
   // Some value of this wave outside the screened domain: the checked arithmetic for all of it.
   u32 flagged = 0;            // (no short-circuit: the four compares of a load are independent)
@@ -161,12 +163,22 @@ __device__ inline void block_codes(const CompressArgs& a, const float4 (&x)[8], 
     q[j] = i32(r[0]);
     q[16 + j] = i32(r[1]);
   }
-  if (!FULL) {
-    // the last block repeats its last code up to 32 values
-    const u64 b = wblock0 + u64(lane);
-    const u64 cnt = b < a.nb ? a.n - b * kBlockValues : 0;
+  if (have < kWaveValues) {
+    // uniform: the end of the input.  The values behind the last whole 16-byte piece first ...
+    const u32 whole = have & ~3u;
+    const float* const tail = a.in + wblock0 * kBlockValues + whole;
+#pragma nounroll
+    for (u32 t = 0; t < have - whole; ++t) {
+      const i32 code = quantize_value(tail[t], a, err);
+      const u32 at = whole + t;
 #pragma unroll
-    for (int j = 1; j < 32; ++j) q[j] = u64(j) < cnt ? q[j] : q[j - 1];
+      for (int j = 0; j < 32; ++j) q[j] = at == u32(kBlockValues) * u32(lane) + u32(j) ? code : q[j];
+    }
+    // ... then the last block repeats its last code up to 32 values
+    const u32 first = u32(kBlockValues) * u32(lane);
+    const u32 cnt = have > first ? have - first : 0u;
+#pragma unroll
+    for (int j = 1; j < 32; ++j) q[j] = u32(j) < cnt ? q[j] : q[j - 1];
   }
 }
 
@@ -179,11 +191,10 @@ struct BlockFields {
   i32 outlier;
 };
 
-template <bool FULL>
-__device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, int lane, u32* wl,
+__device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                     BlockFields& bf, u32& err) {
   i32 q[32];
-  block_codes<FULL>(a, x, wblock0, lane, wl, q, err);
+  block_codes(a, x, wblock0, have, lane, wl, q, err);
   bf.outlier = q[0];
   i32 top = 0, bottom = 0;              // largest and smallest delta (d0 = 0 is one of them)
 #pragma unroll
@@ -207,6 +218,7 @@ __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8],
 // codes in LDS; then 32 lanes take the 32 values of one block (two blocks per step), and a
 // plane word is simply the ballot of one bit of the magnitudes.  Slow, rare, and it needs
 // next to no registers, so it does not limit how many waves of the kernel fit a SIMD.
+// FULL: every value of the wave exists.
 template <bool FULL>
 __device__ inline void wide_tile(const CompressArgs& a, const PayloadSink& sink, const Placement& pl, u32 tile,
                                  u32 ntiles, u64 wblock0, u32* wl, u64* sh_base, int wave, int lane) {
@@ -226,14 +238,13 @@ __device__ inline void wide_tile(const CompressArgs& a, const PayloadSink& sink,
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const u64 idx = wblock0 * kBlockValues + u64(1024 * half + 256 * i + 4 * lane);
-      float4 x;
-      if (FULL) {
+      float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (FULL || idx + 4 <= a.n) {
         x = *reinterpret_cast<const float4*>(a.in + idx);
       } else {
         x.x = idx + 0 < a.n ? a.in[idx + 0] : 0.0f;
         x.y = idx + 1 < a.n ? a.in[idx + 1] : 0.0f;
         x.z = idx + 2 < a.n ? a.in[idx + 2] : 0.0f;
-        x.w = idx + 3 < a.n ? a.in[idx + 3] : 0.0f;
       }
       *reinterpret_cast<int4*>(wl + (8 * i + (lane >> 3)) * kStageRow + 4 * (lane & 7)) = quantize4(x, a, true, ignored);
     }
@@ -274,13 +285,16 @@ __device__ inline void wide_tile(const CompressArgs& a, const PayloadSink& sink,
   finish_stream(sink, pl, tile, ntiles, tb);
 }
 
-// One workgroup per tile.  FULL = the launch covers tiles whose 16384 values all exist
-// (pure 16-byte loads, no tail), tile = first_tile + workgroup id, or + a ticket (see
-// take_tile), over [first_tile, end_tile); the ragged last tile of an input runs as a launch
-// of its own, of one workgroup, with FULL = false on tile first_tile.  There is no set-up
-// launch: tile 0 writes the header, and nothing in the workspace needs clearing (see launch_tag).
-template <bool FULL>
-__global__ __launch_bounds__(kPackThreads, FULL ? 8 : 6) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
+// One workgroup per tile: tile = first_tile + workgroup id, or (TICKETS) + a ticket (see
+// take_tile), over [first_tile, end_tile).  There is no set-up launch: tile 0 writes the header,
+// and nothing in the workspace needs clearing (see launch_tag).  A workgroup that knows its tile
+// from its id asks for its values before anything else, so that the scalar work that opens a call
+// (tag, table positions: some 150 dependent instructions) runs while they are on their way: 512^3 field
+// 122.4 -> 121.7 us.  The ragged end is a tile like any other (see load_raw); as a launch of its own behind
+// the full tiles it cost 7 us per call on any input that is not a multiple of 16384 values (20 000 003
+// values, compress and decompress: 59.1 -> 52.2 us).
+template <bool TICKETS>
+__global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
   __shared__ __attribute__((aligned(16))) u32 lds[kPackWaves * kWaveStage];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kPackWaves];
@@ -288,7 +302,15 @@ __global__ __launch_bounds__(kPackThreads, FULL ? 8 : 6) void compress_kernel(Co
   __shared__ u64 sh_base;
 
   const int lane = lane_id();
-  const int wave = int(threadIdx.x) >> 6;
+  const int wave = wave_id();
+  u32 tile = first_tile + blockIdx.x;        // tiles in the order in which workgroups start
+  u32 have = 0;
+  float4 x[8];
+  if (!TICKETS) {
+    const u64 wblock0 = u64(tile) * kPackBlocks + u64(wave) * kWaveBlocks;
+    have = wave_values(a, wblock0);
+    load_raw(a, wblock0, lane, have, x);
+  }
   const u32 ntiles = u32(num_pack_tiles(a.nb));
   u32* const wl = lds + wave * kWaveStage;
   const bool tables_fit = a.out_cap >= tables_end(a.nb, a.ix);
@@ -296,19 +318,15 @@ __global__ __launch_bounds__(kPackThreads, FULL ? 8 : 6) void compress_kernel(Co
 
   const u64 ltag = launch_tag(a.nonce, a.ctl);
   const u64 tag = call_tag(a.ctl, ltag, a.adopt != 0);
-  u32 tile = first_tile;
-  if (FULL) {
-    tile = first_tile + blockIdx.x;          // tiles in the order in which workgroups start
-    if (a.ticketed) {                        // ... or handed out by tickets, see take_tile
-      if (threadIdx.x == 0) {
-        const u32 t = take_tile(a.ctl, ltag, end_tile - first_tile, ticket_shard());
-        sh_tile = t == kNoTile ? kNoTile : first_tile + t;
-      }
-      __syncthreads();
-      tile = uniform(sh_tile);
+  if (TICKETS) {                             // ... or handed out by tickets, see take_tile
+    if (threadIdx.x == 0) {
+      const u32 t = take_tile(a.ctl, ltag, end_tile - first_tile, ticket_shard());
+      sh_tile = t == kNoTile ? kNoTile : first_tile + t;
     }
-    if (tile >= end_tile) return;
+    __syncthreads();
+    tile = uniform(sh_tile);
   }
+  if (tile >= end_tile) return;
   // the first tile also writes the fixed header fields and the padding of the tables
   if (tile == 0 && threadIdx.x == 0) {
     if (tables_fit) write_stream_header(a.out, a.n, a.nb, a.eb_bits, 1u, a.ix != 0, false);
@@ -318,11 +336,13 @@ __global__ __launch_bounds__(kPackThreads, FULL ? 8 : 6) void compress_kernel(Co
     const u64 wblock0 = u64(tile) * kPackBlocks + u64(wave) * kWaveBlocks;
     const u64 b = wblock0 + u64(lane);
     const bool active = b < a.nb;
-    float4 x[8];
-    load_raw<FULL>(a, wblock0, lane, x);
+    if (TICKETS) {
+      have = wave_values(a, wblock0);
+      load_raw(a, wblock0, lane, have, x);
+    }
 
     BlockFields bf;
-    block_fields<FULL>(a, x, wblock0, lane, wl, bf, err);
+    block_fields(a, x, wblock0, have, lane, wl, bf, err);
     Placement pl;
     pl.w = (active && bf.any) ? 32u - u32(__builtin_clz(bf.any)) : 0u;
     pl.wmax = wave_max_u32(pl.w);
@@ -377,7 +397,8 @@ __global__ __launch_bounds__(kPackThreads, FULL ? 8 : 6) void compress_kernel(Co
         stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, pl, wl);
       });
     } else {
-      wide_tile<FULL>(a, sink, pl, tile, ntiles, wblock0, wl, &sh_base, wave, lane);
+      if (have == kWaveValues) wide_tile<true>(a, sink, pl, tile, ntiles, wblock0, wl, &sh_base, wave, lane);
+      else wide_tile<false>(a, sink, pl, tile, ntiles, wblock0, wl, &sh_base, wave, lane);
     }
     if (active && tables_fit) {
       a.out[widths_begin(a.nb, a.ix) + b] = u8(pl.w);

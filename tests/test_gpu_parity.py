@@ -726,6 +726,35 @@ def test_wide_block_in_the_ragged_last_tile(zcref, tail):
     assert st == zcref.compress(x, 1e-3)[0] and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
 
 
+@pytest.mark.parametrize("rest", [1, 2, 3, 4, 5, 29, 2046, 2049, 2 * TILE - 1])
+def test_compress_ragged_end_beside_full_tiles(zcref, rest):
+    """The values behind the last whole 16-byte piece of an input, in the launch of the full tiles: coded, padded and
+    checked like all others (poison lies behind the input)."""
+    u = _u()
+    n = 4 * TILE + rest
+    rng = np.random.default_rng(rest)
+    x = np.cumsum(rng.normal(0, 0.01, n)).astype(np.float32)
+    d_all = torch.full((n + 64,), float("nan"), device=u.DEV)
+
+    def run(x):
+        d_all[:n] = torch.from_numpy(x)
+        d_out = torch.zeros(zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
+        st, total = zc.zc_compress(d_all[:n], n, 1e-3, d_out, u.workspace(n))
+        return st, d_out[:total].cpu().numpy()
+
+    st, s = run(x)
+    ref = zcref.compress(x, 1e-3)[1]
+    assert st == ZC_OK and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+    for bad, status in ((np.nan, ZC_ERR_NONFINITE), (1e9, ZC_ERR_RANGE), (29518.893, ZC_ERR_BOUND)):     # (the last one misses the bound by its rounding)
+        y = x.copy()
+        y[n - 1] = bad
+        st, s = run(y)
+        st_ref, ref, _ = zcref.compress(y, 1e-3)
+        assert st == st_ref
+        if st == ZC_ERR_BOUND:
+            assert s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+
+
 # ---------------- the other aggregation functions: Max, Min (ring round) and Average (decompress) ----------------
 @pytest.mark.parametrize("n,rel", [(1, 1e-3), (33, 1e-3), (TILE, 1e-4), (5 * TILE + 77, 1e-3), (16 * TILE - 5, 1e-2)])
 def test_reduce_step_max_min_match_reference(zcref, n, rel):
