@@ -98,11 +98,11 @@ __device__ inline int4 quantize4(const float4& x, const CompressArgs& a, bool ch
   return q;
 }
 
-// Values of a wave's share of a tile that exist: 2048 but for the wave at the end of the input and those behind it.
+// Values of a wave's share of a tile (from value v0 on) that exist: 2048 but for the wave at the end of the
+// input and those behind it.
 constexpr u32 kWaveValues = u32(kWaveBlocks) * kBlockValues;
-__device__ inline u32 wave_values(const CompressArgs& a, u64 wblock0) {
-  const u64 v0 = wblock0 * kBlockValues;
-  const u64 left = a.n > v0 ? a.n - v0 : 0;
+__device__ inline u32 share_values(u64 n, u64 v0) {
+  const u64 left = n > v0 ? n - v0 : 0;
   return left < kWaveValues ? u32(left) : kWaveValues;
 }
 
@@ -124,7 +124,7 @@ __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u3
 }
 
 // Quantise the wave's values where they landed and transpose the codes through LDS so that one
-// lane owns one block: q[j] = code j of the lane's block.  have: see wave_values.
+// lane owns one block: q[j] = code j of the lane's block.  have: see share_values.
 __device__ inline void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                    i32 (&q)[32], u32& err) {
   // Some value of this wave outside the screened domain: the checked arithmetic for all of it.
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
   float4 x[8];
   if (!TICKETS) {
     const u64 wblock0 = u64(tile) * kPackBlocks + u64(wave) * kWaveBlocks;
-    have = wave_values(a, wblock0);
+    have = share_values(a.n, wblock0 * kBlockValues);
     load_raw(a, wblock0, lane, have, x);
   }
   const u32 ntiles = u32(num_pack_tiles(a.nb));
@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     const u64 b = wblock0 + u64(lane);
     const bool active = b < a.nb;
     if (TICKETS) {
-      have = wave_values(a, wblock0);
+      have = share_values(a.n, wblock0 * kBlockValues);
       load_raw(a, wblock0, lane, have, x);
     }
 

@@ -14,20 +14,20 @@
 //
 // Geometry: tiles of 256 blocks, one wave per 64 blocks.  A wave takes one of two paths.
 // The common one (one lane per block) serves waves whose received and produced blocks are at
-// most 15 bits wide, whose blocks are complete and whose sums lie inside the screened domain
-// of the quantiser: the received deltas stay packed as the bit-matrix transpose leaves them
-// (two 16-bit or four 8-bit fields per word), a single walk along the Lorenzo chain takes each
-// delta out of its field, forms the sum and the new code, and packs the new delta at once, so
-// that a block never occupies more than 16 + 16 registers; the local values arrive as coalesced
-// 16-byte loads, asked for before anything else, and pass through the wave's LDS area in two
-// halves (values 0..15 and 16..31 of every block) so that a lane finds its block's values in its
-// own row.  Whatever that path cannot take (a block wider than 15 bits on either side, the
-// ragged end of the buffer, a sum outside the screened domain, which is also where NaN and
-// infinity end up) is found out before anything is written and sends the whole wave through
-// the other path: 32 lanes per block, two blocks per step, the defining arithmetic with all
-// its checks, first to learn the new widths, and again, once the tile's place in the output
-// is known, to emit the plane words as ballots.  It is slow, rare, and needs next to no
-// registers, so it does not limit how many waves fit a SIMD.
+// most 15 bits wide and whose sums lie inside the screened domain of the quantiser: the
+// received deltas stay packed as the bit-matrix transpose leaves them (two 16-bit or four
+// 8-bit fields per word), a single walk along the Lorenzo chain takes each delta out of its
+// field, forms the sum and the new code, and packs the new delta at once, so that a block
+// never occupies more than 16 + 16 registers; the local values arrive as coalesced 16-byte
+// loads, asked for before anything else, and pass through the wave's LDS area in two halves
+// (values 0..15 and 16..31 of every block) so that a lane finds its block's values in its own
+// row.  Whatever that path cannot take (a block wider than 15 bits on either side, a sum
+// outside the screened domain, which is also where NaN and infinity end up) is found out
+// before anything is written and sends the whole wave through the other path: 32 lanes per
+// block, two blocks per step, the defining arithmetic with all its checks, first to learn the
+// new widths, and again, once the tile's place in the output is known, to emit the plane words
+// as ballots.  It is slow, rare, and needs next to no registers, so it does not limit how many
+// waves fit a SIMD.
 #pragma once
 
 #include "zc_bitmatrix.h"
@@ -140,6 +140,39 @@ __device__ inline void walk_half(const u32 (&fields)[NF], const u32* row, const 
     cs.bottom = min(cs.bottom, min(min(nd[0], nd[1]), min(nd[2], nd[3])));
     cs.upos = u32(max(i32(cs.upos), max(max(i32(yb[0]), i32(yb[1])), max(i32(yb[2]), i32(yb[3])))));
     cs.uneg = max(cs.uneg, max(max(yb[0], yb[1]), max(yb[2], yb[3])));
+  }
+}
+
+// The local values of a wave's share, 8 x 16 bytes per lane, as load_raw of the compression kernel asks for
+// them: buffer loads that end with the share's last whole 16-byte piece.
+__device__ inline void load_local(const float* local, u64 v0, u32 have, int lane, float4 (&x)[8]) {
+  const __amdgpu_buffer_rsrc_t share =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(local + v0), 0, int(4u * (have & ~3u)), kRawBuffer);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * (i & 3), 4096 * (i >> 2), kAccessOnce);
+    x[i] = make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
+  }
+}
+
+// The wave at the end of the buffer: everything behind its last value becomes a copy of that value.  The
+// received stream repeats the last code of its last block, so the results there repeat the last result:
+// their deltas are the zeros that the stream's padding wants, and they change neither width nor screen.
+// (The whole wave used to take the other path, 25 us longer than all others, on every call whose size is
+// not a multiple of 2048: a synchronous round of 262 177 values took 59.5 us and takes 33.9 now.)
+__device__ inline void pad_local(const float* local, u64 v0, u64 n, u32 have, int lane, float4 (&x)[8]) {
+  const u32 piece = have & ~3u;
+  float t[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const u64 at = v0 + piece + u32(c);
+    t[c] = local[at < n ? at : n - 1];
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const u32 e = 256u * u32(i) + 4u * u32(lane);
+    if (e == piece) x[i] = make_float4(t[0], t[1], t[2], t[3]);
+    if (e > piece) x[i] = make_float4(t[3], t[3], t[3], t[3]);
   }
 }
 
@@ -293,7 +326,6 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     const u32 seg = (a.first_tile + blockIdx.x) * kTileWaves + u32(wave);
     const u32 b = seg * kWaveBlocks + u32(lane);
     const u64 v0 = u64(seg) * kWaveBlocks * kBlockValues;
-    const bool whole = v0 + u64(kWaveBlocks) * kBlockValues <= a.n_local;
     // The segment's position and the width bytes first: loads return in the order in which they were asked
     // for, and the payload can be asked for as soon as these are there, while the local values still arrive.
     // None of these loads sits behind a branch (what must not be read is replaced by the stream's first
@@ -313,12 +345,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
       if (seg < 4 * a.index.tiles_cap) seg_parts = load_segment_offset(a.index, 0, seg, zero);
       if (u64(kHeaderBytes) + b < a.in.bytes) w = u32(*at_bytes(a.in.base, kHeaderBytes + b));
     }
-    const float4* const nothing = reinterpret_cast<const float4*>(a.in.base);      // (a ragged wave fetches its values later)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const u64 idx = v0 + u64(256 * i + 4 * lane);
-      x[i] = load_once(whole ? reinterpret_cast<const float4*>(a.local + idx) : nothing);
-    }
+    load_local(a.local, v0, share_values(a.n_local, v0), lane, x);
     // Nothing moves across this line: left to itself the compiler puts the wait for the header in front of
     // the last of these loads, which then goes out a round trip late.
     __builtin_amdgcn_sched_barrier(0);
@@ -374,14 +401,9 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   const u32 b = seg * kWaveBlocks + u32(lane);
   const bool active = b < h.nb;
   const u64 v0 = u64(seg) * kWaveBlocks * kBlockValues;
-  const bool whole = v0 + u64(kWaveBlocks) * kBlockValues <= h.n;     // every block of the wave exists, and is complete
+  const u32 have = share_values(h.n, v0);                             // values of the wave that exist
   if (!early) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const u64 idx = v0 + u64(256 * i + 4 * lane);
-      x[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      if (whole) x[i] = load_once(reinterpret_cast<const float4*>(a.local + idx));
-    }
+    load_local(a.local, v0, have, lane, x);
     if (IX) {
       if (seg_live) {
         seg_parts = load_segment_offset(a.index, 0, seg, 0, a.in.base);
@@ -422,10 +444,18 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   u32 nf[16];
 #pragma unroll
   for (int p = 0; p < 16; ++p) nf[p] = 0;
-  bool slow = wp.wmax > 15 || !whole;
+  bool slow = wp.wmax > 15;
   if (!slow) {
     u32 lo[16];
     pick_block_words(wp, seg_off, wl, lo);
+    if (have < kWaveValues) {                // uniform: the end of the buffer
+      pad_local(a.local, v0, h.n, have, lane, x);
+      const u32 first = u32(kBlockValues) * u32(lane);
+      const u32 cnt = have > first ? have - first : 0u;
+      const u32 exist = cnt < 32u ? (1u << cnt) - 1u : ~0u;      // (the deltas of the padding are zeros, whatever the stream says)
+#pragma unroll
+      for (int p = 0; p < 16; ++p) lo[p] &= exist;
+    }
     // Local values 0..15 of every block go to LDS first: each 16-byte load holds four values of one
     // block, and the lanes with (lane & 7) < 4 hold those of the first halves.  The other lanes'
     // registers hold the second halves, 8 KiB per wave in all, which wait for the first half of the

@@ -385,6 +385,36 @@ def test_reduce_step_stream_matches_reference(zcref, n, rel):
     assert s.tobytes() == s_ref.tobytes(), u.first_diff(s, s_ref)
 
 
+@pytest.mark.parametrize("rest", [1, 3, 4, 30, 33, 2045])
+@pytest.mark.parametrize("op", [0, 1, 2])
+def test_reduce_step_ragged_end(zcref, rest, op):
+    """The wave at the end of the buffer: poison behind the local values, and a received stream whose padding is not
+    the copies of the last code that a compressor writes (only the values count)."""
+    u = _u()
+    n = 2 * TILE + rest
+    rng = np.random.default_rng(rest)
+    q = np.cumsum(rng.integers(-60, 61, n)).astype(np.int32)
+    _, received, _ = zcref.encode_codes(q, 1e-3)
+    nb = (n + 31) // 32
+    w = zcref.inspect(received)[2]
+    if rest % 32 and w[nb - 1]:
+        received = received.copy()
+        received[-1] ^= 0x80                     # the top bit of the last block's last plane: a delta of the padding
+    local = torch.full((n + 64,), float("nan"), device=u.DEV)
+    y = (np.cumsum(rng.integers(-90, 91, n)) * 1e-3).astype(np.float32)
+    local[:n] = torch.from_numpy(y)
+    d_out = torch.zeros(zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
+    st, total = zc.zc_reduce_step_op(u.to_dev(received), received.size, local[:n], n, op, d_out, u.workspace(n))
+    st_ref, ref, _ = zcref.reduce_step(received, y, op=op)
+    assert st == st_ref == ZC_OK
+    s = d_out[:total].cpu().numpy()
+    assert s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+    y[n - 1] = np.inf
+    local[n - 1] = float("inf")
+    st, _ = zc.zc_reduce_step_op(u.to_dev(received), received.size, local[:n], n, op, d_out, u.workspace(n))
+    assert st == zcref.reduce_step(received, y, op=op)[0] == ZC_ERR_NONFINITE
+
+
 def test_reduce_step_chain_and_special_cases(zcref):
     """N rounds in a row on the GPU against N rounds of the reference; adding zeros keeps the
     stream, adding to zeros compresses the local chunk."""
