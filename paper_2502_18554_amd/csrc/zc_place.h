@@ -43,12 +43,13 @@ struct TileBase {
 // indexed stream marks its size when it holds a block wider than 15 bits.
 constexpr u32 kWaveWideMark = 1u << 31;
 
-__device__ inline void sum_wave_totals(const u32* sh_wave_total, int wave, bool ix, Placement& pl) {
+template <int WAVES>
+__device__ inline void sum_wave_totals(const u32 (&sh_wave_total)[WAVES], int wave, bool ix, Placement& pl) {
   pl.wave_off = 0;
   pl.tile_total = 0;
   u32 marks = 0;
 #pragma unroll
-  for (int i = 0; i < kTileWaves; ++i) {
+  for (int i = 0; i < WAVES; ++i) {
     u32 t = sh_wave_total[i];
     if (ix) {
       marks |= t;
@@ -255,35 +256,16 @@ __device__ inline void copy_staged_wave(const PayloadSink& s, const Placement& p
   wave_lds_sync();
 }
 
-// Back half of a tile whose size is published: look back for the base offset, then move the
-// payload out.  Called by every wave of the workgroup; one barrier.  `make_words()` runs while the
-// look-back's first poll is on its way and leaves the wave's words in its staging area (see
-// stage_wave_words): whatever turns the tile's codes into plane words belongs there.
-template <int NW, typename MakeWordsFn>
-__device__ inline void finish_staged_tile(const PayloadSink& s, const Placement& pl, u32 tile, u32 ntiles, u32* wl,
-                                          u64* sh_base, int wave, int lane, MakeWordsFn make_words) {
-  static_assert(64 * NW <= kWaveStage, "a wave of widest blocks must fit the staging area");
-  const TileBase tb = resolve_tile_base(s, pl, tile, sh_base, wave, lane, make_words);
-  if (lane == 0) write_index_entry(s, tile * (blockDim.x >> 6) + u32(wave), tb.words + pl.wave_off);
-  copy_staged_wave<NW>(s, pl, tb.words, wl, lane);
-  finish_stream(s, pl, tile, ntiles, tb);
-}
-
-// The same with the plane words in registers (`word(i)`: 0 = sign, 1 + p = plane p), for waves
-// whose payload need not fit the staging area at once.
-template <int NW, typename WordFn, typename MeanwhileFn>
-__device__ inline void finish_tile(const PayloadSink& s, WordFn word, const Placement& pl, u32 tile, u32 ntiles,
-                                   u32* wl, u64* sh_base, int wave, int lane, MeanwhileFn meanwhile) {
-  const TileBase tb = resolve_tile_base(s, pl, tile, sh_base, wave, lane, meanwhile);
-  if (lane == 0) write_index_entry(s, tile * (blockDim.x >> 6) + u32(wave), tb.words + pl.wave_off);
-  copy_wave_out<NW>(s, word, pl, tb.words, wl, lane);
-  finish_stream(s, pl, tile, ntiles, tb);
-}
-
+// Back half of a tile whose size is published, with the plane words in registers (`word(i)`: 0 = sign,
+// 1 + p = plane p): look back for the base offset, then move the payload out.  Called by every wave of
+// the workgroup; one barrier.
 template <int NW, typename WordFn>
 __device__ inline void finish_tile(const PayloadSink& s, WordFn word, const Placement& pl, u32 tile, u32 ntiles,
                                    u32* wl, u64* sh_base, int wave, int lane) {
-  finish_tile<NW>(s, word, pl, tile, ntiles, wl, sh_base, wave, lane, [] {});
+  const TileBase tb = resolve_tile_base(s, pl, tile, sh_base, wave, lane);
+  if (lane == 0) write_index_entry(s, tile * (blockDim.x >> 6) + u32(wave), tb.words + pl.wave_off);
+  copy_wave_out<NW>(s, word, pl, tb.words, wl, lane);
+  finish_stream(s, pl, tile, ntiles, tb);
 }
 
 }  // namespace zc

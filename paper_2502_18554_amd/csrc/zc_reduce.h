@@ -91,7 +91,7 @@ __device__ inline bool block_out_of_range(const u32 (&mag)[NP], u32 sign, i64 ou
 template <int NW, int NP, typename WordFn>
 __device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const u32 (&mag)[NP], u32 sign, u32 w,
                                  i64 outlier, bool active, u32 b, u32 tile, u32 ntiles, WordFn word, u32* wl,
-                                 u32* sh_wave_total, u64* sh_base, int wave, int lane, bool ix) {
+                                 u32 (&sh_wave_total)[kTileWaves], u64* sh_base, int wave, int lane, bool ix) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, ix);
   if (!active) w = 0;
@@ -136,7 +136,7 @@ constexpr int kWholeStage = 64 * 24;
 template <int NW, int NP, typename WordFn>
 __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c, const u32 (&mag)[NP], u32 sign, u32 w,
                                         i64 outlier, bool active, u32 b, u32 tile, u32 ntiles, WordFn word, u32* wl,
-                                        u32* sh_wave_total, u64* sh_base, int wave, int lane, bool ix) {
+                                        u32 (&sh_wave_total)[kTileWaves], u64* sh_base, int wave, int lane, bool ix) {
   static_assert(64 * NW <= kWholeStage, "a wave of widest blocks must fit the staging area");
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, ix);
@@ -447,7 +447,7 @@ __device__ inline int fresh_lane() {
 // operand 0 if the workgroup asked for them early (`early`).
 template <bool IX>
 __device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, OperandMeta meta,
-                                          bool early, u32* lds, u32* sh_wave_total, u64* sh_base) {
+                                          bool early, u32* lds, u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
   const ParsedHeader& h = c.h;
   const int wave = wave_id();
   const u64 tend = tables_end(h.nb, IX);
@@ -585,7 +585,7 @@ __device__ inline void magnitude_planes(u32 (&acc)[kAccPlanes], u32 s, u32 carry
 
 template <bool IX>
 __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, u32* lds,
-                                        u32* sh_wave_total, u64* sh_base) {
+                                        u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, IX);
   const int lane = lane_id();

@@ -31,7 +31,7 @@ __device__ inline i32 extreme(i32 a, i32 b) {
 // WIDE: blocks wider than 15 bits may come out (only if some operand had one).
 template <bool IX, bool WIDE>
 __device__ inline void place_codes(const ReduceArgs& a, const ReduceCall& c, i32 (&q)[32], bool active, u32 b, u32 tile,
-                                   u32 ntiles, u32* wl, u32* sh_wave_total, u64* sh_base, int wave, int lane, u32 err) {
+                                   u32 ntiles, u32* wl, u32 (&sh_wave_total)[kTileWaves], u64* sh_base, int wave, int lane, u32 err) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, IX);
   // range of the codes (operands of a valid stream are inside it, so is their extreme)
