@@ -2,8 +2,10 @@
  * hand-written for AMD MI355X (gfx950).  C ABI; every pointer named d_* is DEVICE memory,
  * everything else is host memory.  The library allocates no device memory and keeps no
  * settings: what varies between calls is said by each call's arguments (`flags`), and the
- * caller owns inputs, outputs and the workspace.  (The only thing that lives between calls is
- * the optional kernel timer of zc_profile_enable, a measurement aid.)
+ * caller owns inputs, outputs and the workspace.  (What lives between calls: the optional kernel
+ * timer of zc_profile_enable, a measurement aid, and 32 places of 552 bytes in pinned host memory
+ * through which synchronous calls, zc_finish and zc_quality get their result words, made by the
+ * first of them and held until the process ends; a call that finds them all taken goes without.)
  *
  * Method: ZCCL, arXiv 2502.18554.  fZ-light is described in Section 3.3 (block partition,
  * fused quantisation + 1D Lorenzo prediction, first value kept as a 4-byte outlier, sign
@@ -127,7 +129,7 @@ int zc_compress_ex(const float* d_in, size_t n, float abs_eb,
  * hipMalloc.  Same arguments, results and errors as zc_compress, without d_ws and ws_bytes: the
  * workspace is an array in the library's own device image (about 2.4 MB on every GPU the library
  * runs on, held until the process ends), sized for n <= ZC_NOALLOC_MAX_N; a larger n is
- * ZC_ERR_ARG.  The call allocates nothing, on the device or through any library.  The GPU of
+ * ZC_ERR_ARG.  The call allocates nothing, on the device, pinned, or through any library.  The GPU of
  * hip_stream must be the current device.  All calls on one GPU share that one array: calls that
  * overlap in time on one GPU (two host threads, two HIP streams) race on it and are not
  * allowed; calls one after the other on one stream are fine, nothing in the array needs clearing.

@@ -16,6 +16,7 @@
 #include "zc_decompress.h"
 #include "zc_reduce.h"
 #include "zc_reduce_op.h"
+#include "zc_report.h"
 #include "zc_scan.h"
 #include "zc_quality.h"
 #include "zc_step.h"
@@ -88,13 +89,21 @@ u64 blocks_bound(u64 bytes) { return bytes > kHeaderBytes ? (bytes - kHeaderByte
 // Workgroups of stream_index_kernel per stream: 16 tiles make a scan group.
 u32 index_grid(u64 tiles) { return u32(((tiles + 15) / 16 + kIndexGroups - 1) / kIndexGroups); }   // spans
 
-int finish(const void* d_ws, size_t* result, hipStream_t stream) {
-  struct { u64 status, call_tag, result; } host;
-  if (hipMemcpyAsync(&host, d_ws, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess) return ZC_ERR_HIP;
-  if (hipStreamSynchronize(stream) != hipSuccess) return ZC_ERR_HIP;
-  if (result) *result = size_t(host.result);
+ReportSlots g_reports;
+
+// Waits for the call and fetches its status and size; `more` further words (the streams' n) travel along.
+// may_pin: the caller has not ruled out allocations.
+int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = true, const u64* const* more = nullptr, u32 count = 0,
+           u64* more_out = nullptr) {
+  const Control* const ctl = static_cast<const Control*>(d_ws);
+  const u64* from[kReportWords] = {&ctl->status, &ctl->call_tag, &ctl->result};
+  u64 host[kReportWords];
+  for (u32 i = 0; i < count; ++i) from[3 + i] = more[i];
+  if (!report_words(g_reports, from, 3 + count, host, may_pin, stream)) return ZC_ERR_HIP;
+  if (result) *result = size_t(host[2]);
+  for (u32 i = 0; i < count; ++i) more_out[i] = host[3 + i];
   // status bits count only under the tag of the last call
-  return status_from_bits((host.status >> 32) == (host.call_tag >> 32) ? u32(host.status) : 0u);
+  return status_from_bits((host[0] >> 32) == (host[1] >> 32) ? u32(host[0]) : 0u);
 }
 
 // Validation and block positions of plain input streams, ahead of the kernel that reads them
@@ -259,9 +268,10 @@ const char* zc_strerror(int status) {
 }
 
 int zc_finish(const void* d_ws, size_t* result, void* hip_stream) {
+  const bool may_pin = d_ws != nullptr;
   if (!d_ws) d_ws = scratch_of_current_device();     // the call to complete was zc_compress_noalloc
   if (!d_ws) return ZC_ERR_HIP;
-  return finish(d_ws, result, static_cast<hipStream_t>(hip_stream));
+  return finish(d_ws, result, static_cast<hipStream_t>(hip_stream), may_pin);
 }
 
 int zc_compress_ex(const float* d_in, size_t n, float abs_eb, void* d_out, size_t out_cap, size_t* out_bytes,
@@ -292,7 +302,9 @@ int zc_compress_noalloc(const float* d_in, size_t n, float abs_eb, void* d_out, 
   if (!ws) return ZC_ERR_HIP;
   // nothing in a workspace needs clearing (every call tags what it shares), so what the
   // previous call left in the array does not matter
-  return zc_compress_ex(d_in, n, abs_eb, d_out, out_cap, out_bytes, ws, kScratchBytes, hip_stream, 0);
+  const int st = zc_compress_ex(d_in, n, abs_eb, d_out, out_cap, nullptr, ws, kScratchBytes, hip_stream, 0);
+  if (st != ZC_OK || !out_bytes) return st;
+  return finish(ws, out_bytes, static_cast<hipStream_t>(hip_stream), false);
 }
 
 int zc_compress_part(const float* d_in, size_t n, float abs_eb, size_t first_value, size_t count, void* d_out,
@@ -444,12 +456,10 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   if (!launch_ok()) return ZC_ERR_HIP;
   if (!n_out) return ZC_OK;
   // every header that passes validation holds its stream's n: fetch them along with the status
+  const u64* heads[ZC_MAX_K];
   u64 ns[ZC_MAX_K];
-  for (int i = 0; i < k; ++i)
-    if (hipMemcpyAsync(&ns[i], static_cast<const u8*>(d_chunks[i]) + 8, 8, hipMemcpyDeviceToHost, stream) != hipSuccess)
-      return ZC_ERR_HIP;
-  size_t total = 0;
-  const int st = finish(d_ws, &total, stream);
+  for (int i = 0; i < k; ++i) heads[i] = reinterpret_cast<const u64*>(static_cast<const u8*>(d_chunks[i]) + 8);
+  const int st = finish(d_ws, nullptr, stream, true, heads, u32(k), ns);
   if (st == ZC_ERR_HIP || st == ZC_ERR_ARG || st == ZC_ERR_FORMAT) return st;
   for (int i = 0; i < k; ++i) n_out[i] = size_t(ns[i]);
   return st;
@@ -670,13 +680,10 @@ int zc_quality(const float* d_ref, const float* d_test, size_t n, double* out4, 
   hipLaunchKernelGGL(quality_partial_kernel, dim3(u32(groups)), dim3(kQualityThreads), 0, stream, qa);
   hipLaunchKernelGGL(quality_final_kernel, dim3(1), dim3(kQualityThreads), 0, stream, qa, u32(groups));
   if (!launch_ok()) return ZC_ERR_HIP;
-  QualityPartial host;
-  if (hipMemcpyAsync(&host, qa.partials + groups, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess) return ZC_ERR_HIP;
-  if (hipStreamSynchronize(stream) != hipSuccess) return ZC_ERR_HIP;
-  out4[0] = host.worst;
-  out4[1] = host.sse;
-  out4[2] = host.lo;
-  out4[3] = host.hi;
+  const double* const sums = reinterpret_cast<const double*>(qa.partials + groups);      // worst, sse, lo, hi
+  const u64* from[4];
+  for (int i = 0; i < 4; ++i) from[i] = reinterpret_cast<const u64*>(sums + i);
+  if (!report_words(g_reports, from, 4, reinterpret_cast<u64*>(out4), true, stream)) return ZC_ERR_HIP;
   return ZC_OK;
 }
 

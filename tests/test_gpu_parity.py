@@ -1190,6 +1190,43 @@ def test_concurrent_calls_on_several_streams(zcref):
         torch.cuda.synchronize()
 
 
+def test_synchronous_calls_from_many_threads(zcref):
+    """Each waiting thread gets the size of its own call: more threads than there are places for answers, every thread
+    with a stream and a workspace of its own, sizes that all differ."""
+    import threading
+    u = _u()
+    rng = np.random.default_rng(150)
+    jobs = []
+    for i in range(40):
+        x = np.cumsum(rng.normal(0, 0.01, 700 + 331 * i)).astype(np.float32)
+        jobs.append((u.to_dev(x), zcref.compress(x, 1e-3)[1], u.workspace(x.size),
+                     torch.zeros(zc.zc_compress_bound(x.size), dtype=torch.uint8, device=u.DEV), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    failures = []
+    start = threading.Barrier(len(jobs))
+
+    def worker(i):
+        d_x, ref, ws, d_out, stream = jobs[i]
+        start.wait()
+        for _ in range(10):
+            st, total = zc.zc_compress(d_x, d_x.numel(), 1e-3, d_out, ws, stream=stream)
+            if st != ZC_OK or total != ref.size:
+                failures.append((i, st, total, ref.size))
+        st, n = zc.zc_finish(ws, stream=stream)
+        if st != ZC_OK or n != ref.size:
+            failures.append((i, "finish", st, n))
+
+    threads = [threading.Thread(target=worker, args=(i,)) for i in range(len(jobs))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures, failures[:5]
+    torch.cuda.synchronize()
+    for d_x, ref, ws, d_out, stream in jobs:
+        assert d_out[:ref.size].cpu().numpy().tobytes() == ref.tobytes()
+
+
 @pytest.mark.parametrize("short_by", ["all", "more than an index span"])
 def test_output_too_small_by_a_lot_is_capacity(zcref, short_by):
     """A stream that is in order and an output buffer that is much too small: CAPACITY and the stream's n,
