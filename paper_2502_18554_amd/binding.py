@@ -81,13 +81,17 @@ def lib():
     return _lib
 
 
+# Small calls are bound by what happens here (a chunk of a few thousand values runs for 5 us): addresses go to
+# ctypes as plain integers, the current stream's handle is read without building a Stream object around it, and
+# the result words exist only where a call waits for them.
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _p(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def zc_strerror(status):
@@ -103,13 +107,13 @@ def zc_workspace_bytes(n_max, k_max=1):
 
 
 def _size(t):
-    return t.numel() * t.element_size()
+    return t.nbytes
 
 
 def zc_compress(d_in, n, abs_eb, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
     """Returns (status, total_bytes); total_bytes is None in the asynchronous form.  flags 0 goes through
     zc_compress, anything else through zc_compress_ex."""
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     args = [_p(d_in), n, abs_eb, _p(d_out), cap, C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream)]
     st = lib().zc_compress_ex(*args, int(flags)) if flags else lib().zc_compress(*args)
@@ -121,7 +125,7 @@ ZC_NOALLOC_MAX_N = 1 << 27
 
 def zc_compress_noalloc(d_in, n, abs_eb, d_out, sync=True, stream=None, out_cap=None):
     """zc_compress on the library's own static workspace.  Returns (status, total_bytes)."""
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_compress_noalloc(_p(d_in), n, abs_eb, _p(d_out), cap, C.byref(nbytes) if sync else None,
                                    _stream(stream))
@@ -130,7 +134,7 @@ def zc_compress_noalloc(d_in, n, abs_eb, d_out, sync=True, stream=None, out_cap=
 
 def zc_compress_part(d_in, n, abs_eb, first_value, count, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
     """One part of a stream compressed in parts.  Returns (status, bytes of the stream final so far)."""
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_compress_part(_p(d_in), int(n), float(abs_eb), int(first_value), int(count), _p(d_out), cap,
                                 C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream), int(flags))
@@ -172,7 +176,7 @@ def zc_reduce_compressed(d_chunks, chunk_bytes, d_out, d_ws, sync=True, stream=N
     k = len(d_chunks)
     ptrs = (C.c_void_p * max(k, 1))(*[t.data_ptr() for t in d_chunks])
     sizes = (C.c_size_t * max(k, 1))(*[int(b) for b in chunk_bytes])
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     args = [ptrs, sizes, k, _p(d_out), cap, C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream)]
     st = lib().zc_reduce_compressed_ex(*args, int(flags)) if flags else lib().zc_reduce_compressed(*args)
@@ -184,7 +188,7 @@ def zc_reduce_compressed_op(d_chunks, chunk_bytes, op, d_out, d_ws, sync=True, s
     k = len(d_chunks)
     ptrs = (C.c_void_p * max(k, 1))(*[t.data_ptr() for t in d_chunks])
     sizes = (C.c_size_t * max(k, 1))(*[int(b) for b in chunk_bytes])
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_reduce_compressed_op(ptrs, sizes, k, int(op), _p(d_out), cap, C.byref(nbytes) if sync else None, _p(d_ws),
                                        _size(d_ws), _stream(stream), int(flags))
@@ -197,7 +201,7 @@ def zc_reduce_compressed_part(d_chunks, chunk_bytes, n, first_value, count, d_ou
     k = len(d_chunks)
     ptrs = (C.c_void_p * max(k, 1))(*[t.data_ptr() for t in d_chunks])
     sizes = (C.c_size_t * max(k, 1))(*[int(b) for b in chunk_bytes])
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_reduce_compressed_part(ptrs, sizes, k, int(n), int(first_value), int(count), _p(d_out), cap,
                                          C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream), int(flags))
@@ -207,7 +211,7 @@ def zc_reduce_compressed_part(d_chunks, chunk_bytes, n, first_value, count, d_ou
 def zc_reduce_step_part(d_chunk, chunk_bytes, d_local, n_local, op, first_value, count, d_out, d_ws, sync=True, stream=None,
                         out_cap=None, flags=0):
     """One part of a ring round done in parts.  Returns (status, bytes of the stream final so far)."""
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_reduce_step_part(_p(d_chunk), int(chunk_bytes), _p(d_local), int(n_local), int(op), int(first_value),
                                    int(count), _p(d_out), cap, C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws),
@@ -236,7 +240,7 @@ def zc_reduce_step(d_chunk, chunk_bytes, d_local, n_local, d_out, d_ws, sync=Tru
     flags 0 goes through zc_reduce_step, anything else through zc_reduce_step_op."""
     if flags:
         return zc_reduce_step_op(d_chunk, chunk_bytes, d_local, n_local, ZC_OP_SUM, d_out, d_ws, sync, stream, out_cap, flags)
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_reduce_step(_p(d_chunk), int(chunk_bytes), _p(d_local), int(n_local), _p(d_out), cap,
                               C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream))
@@ -246,7 +250,7 @@ def zc_reduce_step(d_chunk, chunk_bytes, d_local, n_local, d_out, d_ws, sync=Tru
 def zc_reduce_step_op(d_chunk, chunk_bytes, d_local, n_local, op, d_out, d_ws, sync=True, stream=None, out_cap=None,
                       flags=0):
     """zc_reduce_step for Sum, Max or Min.  Returns (status, total_bytes)."""
-    nbytes = C.c_size_t(0)
+    nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_reduce_step_op(_p(d_chunk), int(chunk_bytes), _p(d_local), int(n_local), int(op), _p(d_out), cap,
                                  C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream), int(flags))
