@@ -92,9 +92,21 @@ ZC_HD inline void twos_planes_to_magnitude(uint32_t (&r)[N]) {
     carry &= t;
   }
 }
-// The inverse is the same operation: negate the magnitudes where the sign is set.
+// The inverse is the same operation: negate the magnitudes where the sign is set.  A zero whose sign is set,
+// which no encoder here writes, is a zero all the same: the carry that runs through all its planes takes its
+// sign plane with it.
 template <int N>
-ZC_HD inline void magnitude_planes_to_twos(uint32_t (&r)[N]) { twos_planes_to_magnitude<N>(r); }
+ZC_HD inline void magnitude_planes_to_twos(uint32_t (&r)[N]) {
+  const uint32_t s = r[N - 1];
+  uint32_t carry = s;
+#pragma unroll
+  for (int p = 0; p < N - 1; ++p) {
+    const uint32_t t = r[p] ^ s;
+    r[p] = t ^ carry;
+    carry &= t;
+  }
+  r[N - 1] = s ^ carry;
+}
 
 // Low 16 bits of two values in one word / low 8 bits of four values in one word.
 ZC_HD inline uint32_t pack16(uint32_t lo, uint32_t hi) {

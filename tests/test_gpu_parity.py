@@ -1465,3 +1465,35 @@ def test_staging_corners_full_width_waves_off_the_grid(zcref, lead_width):
         sc = zcref.encode_codes(qc, eb)[1]
         st, y, m = u.gpu_decompress(sc, qc.size)
         assert st == ZC_OK and np.array_equal(y.view(np.uint32), zcref.decompress(sc)[1].view(np.uint32)), cut
+
+
+@pytest.mark.parametrize("top", [3, 60, 20000])
+def test_zero_deltas_with_their_sign_set(zcref, top):
+    """A received stream may have the sign of a zero delta set (a payload is not checked bit by bit): it is a
+    zero.  Blocks of up to 7 and of up to 15 bits, every consuming path."""
+    u = _u()
+    rng = np.random.default_rng(top)
+    n = 4 * TILE + 77
+    q = rng.integers(-top // 2, top // 2, n).astype(np.int32)
+    q[1::2] = q[0:-1:2]                                   # every other delta is zero
+    st, good, total = zcref.encode_codes(q, 1e-3)
+    assert st == ZC_OK
+    nb = (n + 31) // 32
+    w = u.widths_of(good, nb).astype(np.int64)
+    s = good.copy()
+    words = s[u.tables_end(nb):].view(np.uint32)
+    at = np.cumsum(np.where(w > 0, w + 1, 0)) - np.where(w > 0, w + 1, 0)
+    for b in range(0, nb, 3):
+        if w[b]:
+            words[at[b]] |= ~np.bitwise_or.reduce(words[at[b] + 1: at[b] + 1 + w[b]])
+    assert s.tobytes() != good.tobytes()
+    local = (rng.uniform(-1, 1, n) * 0.5).astype(np.float32)
+    y, y_ref = u.gpu_decompress(s, n), zcref.decompress(s)
+    assert y[0] == y_ref[0] == ZC_OK and np.array_equal(y[1].view(np.uint32), y_ref[1].view(np.uint32))
+    assert np.array_equal(y_ref[1].view(np.uint32), zcref.decompress(good)[1].view(np.uint32))
+    for op in (None, 1, 2):
+        r_ref = zcref.reduce([good, s]) if op is None else zcref.reduce([good, s], op=op)
+        r = u.gpu_reduce([good, s], n, op=op)
+        assert r[0] == r_ref[0] == ZC_OK and r[1].tobytes() == r_ref[1].tobytes()
+    r, r_ref = u.gpu_reduce_step(s, local), zcref.reduce_step(s, local)
+    assert r[0] == r_ref[0] == ZC_OK and r[1].tobytes() == r_ref[1].tobytes()

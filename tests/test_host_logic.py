@@ -141,6 +141,9 @@ def test_bit_matrix_transposes_match_packbits(bm, cls, maxw):
         d2 = np.zeros(32, np.int32)
         bm.bm_deltas_from_planes(out.ctypes.data_as(p32), 8 if cls == 816 else cls, d2.ctypes.data_as(pi32))
         assert np.array_equal(d2, d)
+        out[0] |= np.packbits((rng.integers(0, 2, 32) * (mag == 0)).astype(np.uint8), bitorder="little").view("<u4")[0]
+        bm.bm_deltas_from_planes(out.ctypes.data_as(p32), 8 if cls == 816 else cls, d2.ctypes.data_as(pi32))
+        assert np.array_equal(d2, d), "a zero with its sign set is a zero"
 
 
 def test_calls_from_two_threads_share_no_setting(libzc):
