@@ -356,6 +356,15 @@ __device__ inline u32 opaque_zero() {
   asm volatile("v_mov_b32 %0, 0" : "=v"(z));
   return z;
 }
+// The lane number, in a way that keeps the compiler from recognising two calls as the same value.
+// What a step of a kernel derives from the lane number is cheap to compute and is computed on
+// the spot: hoisted out of a loop over operands, or shared with a path that is hardly ever taken, it
+// would sit in registers that the step needs.
+__device__ inline int fresh_lane() {
+  int lane = lane_id();
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
 // Index of the calling wave in its workgroup, as a scalar.
 __device__ inline int wave_id() { return int(uniform(threadIdx.x >> 6)); }
 // base + byte offset, for a base that is the same in every lane: it stays in scalar registers

@@ -97,10 +97,11 @@ struct WavePayload {
   u32 off_in_wave;  // payload word offset of this lane's block inside the segment
   u32 wmax;         // the widest block of the wave (uniform)
   bool inside;      // the segment lies inside the payload and agrees with the index (uniform)
+  bool staged;      // its payload is in the staging area: always if no block is wider than 15 bits (uniform)
 };
 
 // First half of wave_block_words: scan of the widths, the checks, and the staged copy of the
-// segment's payload into `wl` when no block is wider than 15 bits.
+// segment's payload into `wl` if it has at most 64 x 16 words (with no block wider than 15 bits it has not more).
 __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload_words, u32 w, u64 seg_off, u32* wl, int lane,
                                                  bool ix, u32 seg_words, bool may_be_wide, u32& err, const uint4* safe) {
   const u32 mis = u32(seg_off) & 3u;
@@ -131,8 +132,9 @@ __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload
     err |= status_bit(ZC_ERR_FORMAT);
     wp.inside = false;
   }
-  if (wp.wmax <= 15 && !ix) {
-    span = wp.inside ? mis + wave_total : 0u;
+  wp.staged = wp.inside && wave_total <= 64u * 16u;
+  if (wp.staged && !ix) {
+    span = mis + wave_total;
     st = load_wave_stage(payload, payload_words, src0, span, lane, safe);
     store_wave_stage(st, payload, payload_words, src0, span, wl, lane);
   }

@@ -433,16 +433,6 @@ __device__ inline u32 sign_plane(const u32 (&acc)[kSumPlanes], u32 top) {
   }
 }
 
-// The lane number, in a way that keeps the compiler from recognising two calls as the same value.
-// What an operand step derives from the lane number is cheap to compute and is computed on
-// the spot: hoisted out of the loop over the operands it would sit in registers that the
-// adder needs.
-__device__ inline int fresh_lane() {
-  int lane = lane_id();
-  asm volatile("" : "+v"(lane));
-  return lane;
-}
-
 // One tile of a call whose operands have no block wider than 15 bits.  `meta`: the tables of
 // operand 0 if the workgroup asked for them early (`early`).
 template <bool IX>

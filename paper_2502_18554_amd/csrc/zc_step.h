@@ -23,11 +23,10 @@
 // (values 0..15 and 16..31 of every block) so that a lane finds its block's values in its own
 // row.  Whatever that path cannot take (a block wider than 15 bits on either side, a sum
 // outside the screened domain, which is also where NaN and infinity end up) is found out
-// before anything is written and sends the whole wave through the other path: 32 lanes per
-// block, two blocks per step, the defining arithmetic with all its checks, first to learn the
-// new widths, and again, once the tile's place in the output is known, to emit the plane words
-// as ballots.  It is slow, rare, and needs next to no registers, so it does not limit how many
-// waves fit a SIMD.
+// before anything is written and sends the block through the other path: 32 lanes per block, two
+// blocks per step, the defining arithmetic with all its checks, first to learn the new widths, and
+// again to form the plane words as ballots.  It needs next to no registers, so it does not
+// limit how many waves fit a SIMD, and the other blocks of the wave stay on the common path.
 #pragma once
 
 #include "zc_bitmatrix.h"
@@ -224,50 +223,80 @@ struct SlowInput {
   u32 outlier;          // its first code
 };
 
-// One pass over the wave's 64 blocks, two per step.  EMIT false: computes the new width and
-// first code of every block (returned one lane per block) and raises the errors of the
-// quantiser.  EMIT true: computes the same values again and stores the sign and plane words
-// of every block at its place: w_out, off_out (one lane per block) = its new width and its
-// word offset inside the wave's payload, which starts at payload word `dst_wave`.
-template <int OP, bool EMIT>
-__device__ inline void step_wave_slow(const StepArgs& a, const ParsedHeader& h, const CompressArgs& qa, u32 seg,
-                                      const SlowInput& in, u32& w_out, i32& outlier_out, u32 off_out, u64 dst_wave,
-                                      u64 cap_words, u32* payload_out, u32& err) {
-  const int lane = lane_id();
+// It is read again, so that none of it occupies a register on the common path.  inside: the segment is in order (its
+// blocks count as empty otherwise).
+template <bool IX>
+__device__ inline SlowInput load_slow_input(const StepArgs& a, const ParsedHeader& h, u32 seg, u32 seg_off, bool inside) {
+  const u32 b = seg * kWaveBlocks + u32(fresh_lane());
+  const bool active = b < h.nb;
+  SlowInput in;
+  in.payload = reinterpret_cast<const u32*>(a.in.base + tables_end(h.nb, IX));
+  in.w = active && inside ? u32(*at_bytes(a.in.base, u32(widths_begin(h.nb, IX)) + b)) : 0u;
+  in.outlier = active ? *reinterpret_cast<const u32*>(at_bytes(a.in.base, u32(outliers_begin(h.nb, IX)) + 4u * b)) : 0u;
+  if (in.w > 31) in.w = 0;                     // (cannot happen)
+  const u32 words = psize_words(in.w);
+  in.off = seg_off + wave_inclusive_sum(words) - words;
+  return in;
+}
+
+// One pass over the blocks in `mask` (bit l = the block of lane l), two per step.  kMeasure: computes the new
+// width and first code of every such block (returned in its lane) and raises the errors of the quantiser.
+// kStage, kStore: computes the same values again and stores the sign and plane words of every block at its
+// place in the wave's payload: w_out, off_out (one lane per block) = its new width and its word offset inside the
+// wave's payload, which starts at `to` and has room for `room` words.
+// (All 64 blocks of a wave used to go through here if one had to, 25 us per pass, in which a received block's words
+// were read one after the other; all tiles behind such a wave wait for it.  A round on 2^26 values of hard data,
+// where one wave in ten has such a block: 790 us, now 103.  Inlined as one lane per block in 32 bits, which is faster
+// for a wave of nothing but wide blocks, it cost every round 5 % in registers.)
+enum SlowPass { kMeasure, kStage, kStore };
+template <bool IX, int OP, SlowPass PASS>
+__device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h, const CompressArgs& qa, u32 seg, u64 mask,
+                                        u32 seg_off, bool inside, u32& w_out, i32& outlier_out, u32 off_out, u32* to, u64 room,
+                                        u32& err) {
+  const SlowInput in = load_slow_input<IX>(a, h, seg, seg_off, inside);
+  const int lane = fresh_lane();
   const u32 half = u32(lane) >> 5, j = u32(lane) & 31u;
-  u32 w_res = 0;
-  i32 outlier_res = 0;
+  u32 w_res = w_out;
+  i32 outlier_res = outlier_out;
 #pragma nounroll
-  for (u32 bp = 0; bp < 32; ++bp) {
-    const u32 blk_a = 2 * bp, blk_b = 2 * bp + 1;
-    // ---- the received deltas of the two blocks, one per lane ----
+  while (mask) {
+    const u32 blk_a = u32(__builtin_ctzll(mask));
+    mask &= mask - 1;
+    const u32 blk_b = mask ? u32(__builtin_ctzll(mask)) : blk_a;      // (an odd one out is done twice)
+    mask &= mask - 1;
+    const u64 b = u64(seg) * kWaveBlocks + (half ? blk_b : blk_a);
+    const u64 left = b < h.nb ? h.n - b * kBlockValues : 0;
+    const u32 cnt = left < 32 ? u32(left) : 32u;        // values of this block that exist
+    // ---- the received words of the two blocks, one per lane, and the local values ----
     const u32 wa = lane_value(in.w, int(blk_a)), wb = lane_value(in.w, int(blk_b));
     const u32 w_mine = half ? wb : wa;
     const u32 off_mine = half ? lane_value(in.off, int(blk_b)) : lane_value(in.off, int(blk_a));
     const u32 outl = half ? lane_value(in.outlier, int(blk_b)) : lane_value(in.outlier, int(blk_a));
+    const u32 word = w_mine && j <= w_mine ? in.payload[off_mine + j] : 0u;
+    const float local = j < cnt ? a.local[b * kBlockValues + j] : 0.0f;
+    // ---- the received deltas, one per lane: bit j of every word ----
     const u32 w_top = wa > wb ? wa : wb;
-    u32 mag = 0, neg = 0;
-    if (w_mine) neg = (in.payload[off_mine] >> j) & 1u;
+    const u32 sa = lane_value(word, 0), sb = lane_value(word, 32);
+    const u32 neg = ((half ? sb : sa) >> j) & 1u;
+    u32 mag = 0;
 #pragma nounroll
-    for (u32 p = 0; p < w_top; ++p)
-      if (p < w_mine) mag |= ((in.payload[off_mine + 1 + p] >> j) & 1u) << p;
+    for (u32 p = 0; p < w_top; ++p) {
+      const u32 pa = lane_value(word, int(1 + p)), pb = lane_value(word, int(33 + p));     // (p <= 30)
+      mag |= (((half ? pb : pa) >> j) & 1u) << p;
+    }
     const u32 d = neg ? 0u - mag : mag;
     const u32 code = outl + half_inclusive_sum(d);
-    // ---- the sum and its code ----
-    const u64 b = u64(seg) * kWaveBlocks + (half ? blk_b : blk_a);
-    const u64 left = b < h.nb ? h.n - b * kBlockValues : 0;
-    const u32 cnt = left < 32 ? u32(left) : 32u;        // values of this block that exist
-    const float local = j < cnt ? a.local[b * kBlockValues + j] : 0.0f;
+    // ---- the result and its code ----
     const float y = combine<OP>(float(__dmul_rn(double(i32(code)), qa.step)), local);
     u32 ignored = 0;
     i32 q = 0;
-    if (j < cnt) q = quantize_value(y, qa, EMIT ? ignored : err);
+    if (j < cnt) q = quantize_value(y, qa, PASS == kMeasure ? err : ignored);
     const i32 last = i32(from_lane(u32(q), 32u * half + (cnt ? cnt - 1u : 0u)));
     if (j >= cnt) q = cnt ? last : 0;                   // the last block repeats its last code
     const i32 before = i32(from_lane(u32(q), u32(lane) + 63u));                 // lane - 1 (lane 0 gets lane 63: unused)
     const i32 nd = j ? q - before : 0;
     const u32 nmag = u32(nd < 0 ? -nd : nd);
-    if (!EMIT) {
+    if constexpr (PASS == kMeasure) {
       const u32 m = half_max(nmag);
       const u32 wn = m ? 32u - u32(__builtin_clz(m)) : 0u;
       const u32 wn_a = lane_value(wn, 0), wn_b = lane_value(wn, 32);
@@ -277,18 +306,18 @@ __device__ inline void step_wave_slow(const StepArgs& a, const ParsedHeader& h, 
     } else {
       const u32 wo_a = lane_value(w_out, int(blk_a)), wo_b = lane_value(w_out, int(blk_b));
       const u32 wo_mine = half ? wo_b : wo_a;
-      const u64 dst = dst_wave + (half ? lane_value(off_out, int(blk_b)) : lane_value(off_out, int(blk_a)));
+      const u32 dst = half ? lane_value(off_out, int(blk_b)) : lane_value(off_out, int(blk_a));
       const u64 sign = __ballot(nd < 0);
-      if (j == 0 && wo_mine && dst < cap_words) payload_out[dst] = half ? u32(sign >> 32) : u32(sign);
+      if (j == 0 && wo_mine && dst < room) to[dst] = half ? u32(sign >> 32) : u32(sign);
       const u32 wo_top = wo_a > wo_b ? wo_a : wo_b;
 #pragma nounroll
       for (u32 p = 0; p < wo_top; ++p) {
         const u64 plane = __ballot(((nmag >> p) & 1u) != 0);
-        if (j == 0 && p < wo_mine && dst + 1 + p < cap_words) payload_out[dst + 1 + p] = half ? u32(plane >> 32) : u32(plane);
+        if (j == 0 && p < wo_mine && dst + 1 + p < room) to[dst + 1 + p] = half ? u32(plane >> 32) : u32(plane);
       }
     }
   }
-  if (!EMIT) {
+  if constexpr (PASS == kMeasure) {
     w_out = w_res;
     outlier_out = outlier_res;
   }
@@ -444,8 +473,13 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   u32 nf[16];
 #pragma unroll
   for (int p = 0; p < 16; ++p) nf[p] = 0;
-  bool slow = wp.wmax > 15;
-  if (!slow) {
+  // Blocks of the wave that the other path has to measure, and all that it has to produce (bit l = the block of
+  // lane l).  A received segment too large for the staging area has wide blocks throughout.
+  const u64 wide_in = __ballot(wp.w > 15);
+  u64 measure = 0, slow = 0;
+  if (wp.wmax > 15 && !wp.staged) {
+    measure = slow = __ballot(active);
+  } else {
     u32 lo[16];
     pick_block_words(wp, seg_off, wl, lo);
     if (have < kWaveValues) {                // uniform: the end of the buffer
@@ -508,15 +542,11 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     outlier = cs.outlier;
     // the largest magnitude among the sums: a NaN or an infinity has the largest bit pattern of all
     const u32 amax = max(i32(cs.upos) < 0 ? 0u : cs.upos, cs.uneg & 0x7fffffffu);
-    slow = __any(active && (needs_checks(__uint_as_float(amax), qa) || pl.w > 15));
+    measure = __ballot(active && (needs_checks(__uint_as_float(amax), qa))) | wide_in;
+    slow = measure | __ballot(pl.w > 15);          // (a wide result alone: its width is known)
   }
-  SlowInput si{payload_in, 0u, 0u, outlier_in};
-  if (slow) {
-    // (the segment is inside the payload, or its blocks count as empty)
-    si.w = wp.inside ? wp.w : 0u;
-    si.off = u32(seg_off) + wp.off_in_wave;
-    step_wave_slow<OP, false>(a, h, qa, seg, si, pl.w, outlier, 0u, 0, 0, nullptr, err);
-    if (!active) pl.w = 0;
+  if (measure) {
+    step_blocks_slow<IX, OP, kMeasure>(a, h, qa, seg, measure, u32(seg_off), wp.inside, pl.w, outlier, 0u, nullptr, 0, err);
   }
 
   // ---- width, tables, placement ----
@@ -536,7 +566,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   if (err) raise_status(a.ctl, tag, err);
   // ---- the new deltas as sign + plane words into the staging area, while the look-back is under way ----
   const TileBase tb = resolve_tile_base(sink, pl, tile, &sh_base, wave, lane, [&] {
-    if (slow) return;
+    if (pl.wave_total > u32(kStepStage)) return;       // uniform: out at once, when the base offset is known
     u32 pw[16];          // pw[0] = sign, pw[1 + p] = plane p
     if (pl.wmax <= 7) {
       // four 8-bit fields per word: word j = values j, j + 8 (word j of nf), j + 16, j + 24 (word j + 8)
@@ -556,19 +586,24 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
 #pragma unroll
       for (int p = 0; p < 15; ++p) pw[1 + p] = swap_middle_bytes(nf[p]);
     }
-    stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, pl, wl);
+    Placement here = pl;
+    if ((slow >> lane) & 1u) here.w = 0;
+    stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, here, wl);
+    u32 ignored = 0;
+    if (slow) step_blocks_slow<IX, OP, kStage>(a, h, qa, seg, slow, u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave, wl, kStepStage, ignored);
   });
   const u64 base = tb.words;
   if (lane == 0) write_index_entry(sink, seg, base + pl.wave_off);
 
   // ---- out ----
-  if (!slow) {
-    copy_staged_wave<16>(sink, pl, base, wl, lane);
+  if (pl.wave_total <= u32(kStepStage)) {
+    copy_staged_wave<kStepStage / 64>(sink, pl, base, wl, lane);
   } else {
     const u64 cap_words = a.out_cap > tend ? (a.out_cap - tend) / 4 : 0;
+    const u64 dst = base + pl.wave_off;
     u32 ignored = 0;
-    step_wave_slow<OP, true>(a, h, qa, seg, si, pl.w, outlier, pl.off_in_wave, base + pl.wave_off, cap_words,
-                             reinterpret_cast<u32*>(a.out + tend), ignored);
+    step_blocks_slow<IX, OP, kStore>(a, h, qa, seg, __ballot(active), u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave,
+                                     reinterpret_cast<u32*>(a.out + tend) + dst, cap_words > dst ? cap_words - dst : 0, ignored);
   }
   if (active && a.out_cap >= tend) {
     a.out[widths_begin(h.nb, IX) + b] = u8(pl.w);

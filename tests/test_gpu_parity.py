@@ -1497,3 +1497,37 @@ def test_zero_deltas_with_their_sign_set(zcref, top):
         assert r[0] == r_ref[0] == ZC_OK and r[1].tobytes() == r_ref[1].tobytes()
     r, r_ref = u.gpu_reduce_step(s, local), zcref.reduce_step(s, local)
     assert r[0] == r_ref[0] == ZC_OK and r[1].tobytes() == r_ref[1].tobytes()
+
+
+@pytest.mark.parametrize("count", [1, 2, 3, 40, 64])
+@pytest.mark.parametrize("kind", ["received", "result", "domain"])
+def test_reduce_step_some_blocks_of_a_wave_off_the_common_path(zcref, kind, count):
+    """`count` blocks of some waves (in an odd and an even number, up to all of them, which no longer fit the staging
+    area) arrive wide, come out wide, or leave the screened domain, beside narrow ones; the last wave is ragged."""
+    u = _u()
+    rng = np.random.default_rng(count)
+    eb = 2.0 ** -12
+    step = eb * 63 / 32
+    n = 2048 * 11 - 45
+    nb = (n + 31) // 32
+    q = rng.integers(-20, 20, n).astype(np.int64)
+    local = rng.integers(-20, 20, n) * step
+    for seg in (0, 2, 3, 10):
+        for b in rng.choice(64, count, replace=False) + 64 * seg:
+            if b >= nb:
+                continue
+            at = slice(32 * b, min(32 * b + 32, n))
+            m = at.stop - at.start
+            if kind == "received":
+                q[at] = rng.integers(-2 ** 22, 2 ** 22, m)
+                local[at] = -q[at] * step if b % 2 else 0.0    # some of them come out narrow
+            elif kind == "result":
+                local[at] = rng.integers(-2 ** 16, 2 ** 16, m) * step
+            else:
+                local[at] = 2.0 ** 18 * eb + rng.integers(-20, 20, m) * step
+    st, received, _ = zcref.encode_codes(q.astype(np.int32), eb)
+    assert st == ZC_OK
+    for op in (None, 1):
+        ref = zcref.reduce_step(received, local.astype(np.float32)) if op is None else zcref.reduce_step(received, local.astype(np.float32), op=op)
+        got = u.gpu_reduce_step(received, local.astype(np.float32), op=op)
+        assert got[0] == ref[0] and got[0] in (ZC_OK, ZC_ERR_BOUND) and got[1].tobytes() == ref[1].tobytes(), (op, u.first_diff(got[1], ref[1]))
