@@ -3,7 +3,7 @@
 //
 // One lane owns one block.  Plane word p has bit j = bit p of value j, so the plane words are
 // the transpose of the 32 x 32 bit matrix whose rows are the values.  A transpose by
-// recursive block swaps costs six simple operations per pair of words and stage, for all
+// recursive block swaps costs four simple operations per pair of words and stage, for all
 // planes at once, where gathering plane by plane costs one operation per value and plane.
 // Blocks are narrow most of the time, so the matrix is first folded:
 //   width <= 7  : four values per word (bytes), three stages on 8 words
@@ -26,11 +26,22 @@
 
 namespace zc {
 
-// Exchanges, between words a and b, the bit groups selected by mask m (in b) and m << s (in a).
+// The bits of x where m is set, those of y elsewhere.  One three-input operation on the GPU, spelled out: left
+// to itself the compiler pulls the masks of neighbouring stages together and needs more of them.
+ZC_HD inline uint32_t select_bits(uint32_t m, uint32_t x, uint32_t y) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_bitop3_b32(x, y, m, 0xE4);
+#else
+  return (x & m) | (y & ~m);
+#endif
+}
+
+// Exchanges, between words a and b, the bit groups selected by mask m (in b) and m << s (in a), where m << s is
+// what m leaves out: two shifts and two selections.
 ZC_HD inline void swap_bits(uint32_t& a, uint32_t& b, int s, uint32_t m) {
-  const uint32_t t = ((a >> s) ^ b) & m;
-  b ^= t;
-  a ^= t << s;
+  const uint32_t up = b << s, down = a >> s;
+  a = select_bits(m, a, up);
+  b = select_bits(m, down, b);
 }
 
 // Transposes the 16 x 16 bit matrix in the low halves of r[0..16) and, independently, the
@@ -79,18 +90,27 @@ ZC_HD inline void transpose8x8_quads(uint32_t (&r)[8]) {
 // ---- two's complement <-> sign + magnitude, on planes -------------------------------------
 // r[0..N-1) = planes of N-bit two's complement values (one bit of 32 values per word), r[N-1]
 // their sign plane.  Negating where the sign is set, with a ripple of carries over the planes,
-// turns them into magnitude planes and back: three operations per plane for 32 values, where
+// turns them into magnitude planes and back: two operations per plane for 32 values, where
 // the same conversion value by value costs five operations per value.
+// One plane of that ripple: plane ^ sign ^ carry, and the carry on, (plane ^ sign) & carry; two three-input
+// operations on the GPU, spelled out (see select_bits).
+ZC_HD inline void negate_plane(uint32_t& plane, uint32_t sign, uint32_t& carry) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t on = __builtin_amdgcn_bitop3_b32(plane, sign, carry, 0x28);
+  plane = __builtin_amdgcn_bitop3_b32(plane, sign, carry, 0x96);
+  carry = on;
+#else
+  const uint32_t t = plane ^ sign;
+  plane = t ^ carry;
+  carry &= t;
+#endif
+}
 template <int N>
 ZC_HD inline void twos_planes_to_magnitude(uint32_t (&r)[N]) {
   const uint32_t s = r[N - 1];
   uint32_t carry = s;                       // (bits ^ s) + s
 #pragma unroll
-  for (int p = 0; p < N - 1; ++p) {
-    const uint32_t t = r[p] ^ s;
-    r[p] = t ^ carry;
-    carry &= t;
-  }
+  for (int p = 0; p < N - 1; ++p) negate_plane(r[p], s, carry);
 }
 // The inverse is the same operation: negate the magnitudes where the sign is set.  A zero whose sign is set,
 // which no encoder here writes, is a zero all the same: the carry that runs through all its planes takes its
@@ -100,11 +120,7 @@ ZC_HD inline void magnitude_planes_to_twos(uint32_t (&r)[N]) {
   const uint32_t s = r[N - 1];
   uint32_t carry = s;
 #pragma unroll
-  for (int p = 0; p < N - 1; ++p) {
-    const uint32_t t = r[p] ^ s;
-    r[p] = t ^ carry;
-    carry &= t;
-  }
+  for (int p = 0; p < N - 1; ++p) negate_plane(r[p], s, carry);
   r[N - 1] = s ^ carry;
 }
 
