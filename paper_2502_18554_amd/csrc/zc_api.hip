@@ -535,17 +535,10 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   }
   if (op == ZC_OP_SUM) {
     launch_main(ZC_KERNEL_REDUCE, ix ? reduce_kernel<true> : reduce_kernel<false>, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
-    // plain streams with blocks wider than 15 bits have a kernel of their own, which returns at once otherwise
-    if (!ix) hipLaunchKernelGGL(reduce_wide_kernel, dim3(u32(tiles)), dim3(kTileThreads), 0, stream, ra);
   } else {
-    // Max and Min: a kernel for operands without blocks wider than 15 bits and one for the others;
-    // each returns at once when the operands are not its
-    void (*narrow)(ReduceArgs) = op == ZC_OP_MAX ? (ix ? reduce_op_kernel<true, ZC_OP_MAX> : reduce_op_kernel<false, ZC_OP_MAX>)
+    void (*kernel)(ReduceArgs) = op == ZC_OP_MAX ? (ix ? reduce_op_kernel<true, ZC_OP_MAX> : reduce_op_kernel<false, ZC_OP_MAX>)
                                                  : (ix ? reduce_op_kernel<true, ZC_OP_MIN> : reduce_op_kernel<false, ZC_OP_MIN>);
-    void (*wide)(ReduceArgs) = op == ZC_OP_MAX ? (ix ? reduce_op_wide_kernel<true, ZC_OP_MAX> : reduce_op_wide_kernel<false, ZC_OP_MAX>)
-                                               : (ix ? reduce_op_wide_kernel<true, ZC_OP_MIN> : reduce_op_wide_kernel<false, ZC_OP_MIN>);
-    launch_main(ZC_KERNEL_REDUCE, narrow, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
-    hipLaunchKernelGGL(wide, dim3(u32(tiles)), dim3(kTileThreads), 0, stream, ra);
+    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
   }
   if (!launch_ok()) return ZC_ERR_HIP;
   if (!out_bytes) return ZC_OK;

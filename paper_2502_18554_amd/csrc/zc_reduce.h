@@ -11,16 +11,15 @@
 // the end, and its highest non-zero plane gives the new code length.  Output placement is
 // the same ticketed look-back scan as in compression.
 //
-// Two kernels share this scheme.  reduce_kernel serves streams whose blocks are all at most
-// 15 bits wide (every stream of an input inside the guaranteed domain of a sensible bound):
-// a wave's payload of one operand is then at most 1024 words, is brought into LDS with
-// 16-byte loads, and the loads of the next operand fly while the current one is added; the
-// summed planes go to LDS in one pass and leave as coalesced stores.  Operand payloads are
-// read, and the output stream is written, with the non-temporal hint (see load_once).
-// The other path of the same kernel (reduce_wide_tile) takes any widths with per-lane loads,
-// a few planes at a time so that it needs no more registers than the common path.  Whether any
-// operand has a wider block is known when a workgroup starts (from the stream index of plain
-// streams, from the version words of indexed ones), so the whole call takes one path.
+// A tile takes one of two paths.  On the common one a wave brings its payload of one operand into
+// LDS with 16-byte loads, and the loads of the next operand fly while the current one is added;
+// the summed planes go to LDS in one pass and leave as coalesced stores.  Operand payloads are
+// read, and the output stream is written, with the non-temporal hint (see load_once).  Its
+// accumulator and its staging take all blocks of at most 15 bits, and most segments that have a
+// wider one (fits_common_path).  The other path (reduce_wide_tile) takes any widths with per-lane
+// loads, a few planes at a time.  Whether any operand has a wide block anywhere is known when a
+// workgroup starts (from the stream index of plain streams, from the version words of indexed
+// ones); only in such a call do the waves look where.
 // IX = the streams are indexed (see index_bytes): operands bring the positions of their
 // segments along, which every wave checks against the widths it reads, and the output gets
 // its own index as it is placed.
@@ -56,6 +55,7 @@ struct ReduceCall {
   u64 tag;           // the call's tag
   u64 ltag;          // this launch's tag (tile tickets)
   u64 nsum;          // sum of the operands' nsum
+  u64 wide_streams;  // bit s: operand s may have blocks wider than 15 bits
   u32 part_end;      // a reduce done in parts: one past the last tile of this part; else 0
 };
 
@@ -192,14 +192,14 @@ __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c
 }
 
 // ---------------------------------------------------------------------------------------
-// Streams without blocks wider than 15 bits.
+// The common path.
 // ---------------------------------------------------------------------------------------
 
 // The accumulator: 24 two's complement planes hold the sum of up to 64 deltas below 2^16 in
 // magnitude.  Planes [0, top) are valid, top a multiple of 4 and wave-uniform; plane top - 1
 // is a copy of the sign plane.
 constexpr int kSumPlanes = 24;
-static_assert(64 * kSumPlanes <= kWholeStage && kWholeStage >= kWaveStage, "staging area of reduce_kernel");
+static_assert(64 * kSumPlanes <= kWholeStage && kWholeStage >= kWaveStage, "staging area of reduce_kernel");   // (planes 0..22 and the sign: 24 words)
 constexpr int kSumChunk = 4;
 
 // What a wave needs to know about one operand's share, loaded two operands ahead: the values
@@ -216,7 +216,7 @@ struct OperandMeta {
 struct OperandPlace {
   u32 w;            // this lane's block width (0 if the block must be skipped)
   u32 pick;         // LDS word index of this lane's sign word
-  u32 wcap;         // uniform: 0 (nothing to add), 4, 8, 12 or 16: at least the widest block of the wave
+  u32 wcap;         // uniform: 0 (nothing to add), 4, 8, 12, 16 or 24: at least the widest block of a wave on the common path
   u32 span;         // uniform: words the wave stages, from the aligned start
   u32 src0;         // uniform: payload word index of the aligned start
   u32 room;         // uniform: words from src0 to the end of the caller's buffer
@@ -275,29 +275,30 @@ __device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, cons
 }
 
 // `err`: an indexed stream is checked as it is used: the widths of the segment must add up to
-// what the index says, and a stream that promised narrow blocks must have no other.
-__device__ inline OperandPlace place_operand(const OperandMeta& m, const ParsedHeader& h, bool ix, u32& err) {
+// what the index says, and no block may be wider than w_max (15 where the stream promised narrow
+// blocks, or where the caller has seen that there is no other).
+__device__ inline OperandPlace place_operand(const OperandMeta& m, const ParsedHeader& h, bool ix, u32& err, u32 w_max = 15) {
   OperandPlace p;
   // the same in every lane, and long since loaded: into scalar registers, 32-bit arithmetic
   const u64 seg_off64 = ix ? u64(uniform(m.seg_off.seg)) : uniform64(segment_offset(m.seg_off));
   const u32 seg_off = u32(seg_off64);
-  const u32 w = m.w > 15 ? 0u : m.w;           // plain streams: cannot happen here; keeps every LDS access in range
+  const u32 w = m.w > w_max ? 0u : m.w;        // plain streams: cannot happen here; keeps every LDS access in range
   const u32 words = psize_words(w);
   const u32 incl = wave_inclusive_sum(words);
   const u32 wave_total = lane_value(incl, 63);
   // true on a validated stream
   bool inside = (seg_off64 >> 32) == 0 && seg_off <= m.payload_room && wave_total <= m.payload_room - seg_off;
-  if (ix && (__any(m.w > 15) || uniform(m.seg_end) - seg_off != wave_total)) {
+  if (ix && (__any(m.w > w_max) || uniform(m.seg_end) - seg_off != wave_total)) {
     err |= status_bit(ZC_ERR_FORMAT);
     inside = false;
   }
   const u32 mis = seg_off & 3u;
   p.src0 = seg_off - mis;
   p.room = m.payload_room - p.src0;
-  p.span = inside ? mis + wave_total : 0u;     // <= 3 + 64 * 16
+  p.span = inside ? mis + wave_total : 0u;     // <= 3 + 64 * (1 + w_max)
   p.pick = mis + (incl - words);
   p.w = inside ? w : 0u;
-  p.wcap = __any(p.w > 12) ? 16u : __any(p.w > 8) ? 12u : __any(p.w > 4) ? 8u : __any(p.w != 0) ? 4u : 0u;
+  p.wcap = w_max > 15 && __any(p.w > 15) ? 24u : __any(p.w > 12) ? 16u : __any(p.w > 8) ? 12u : __any(p.w > 4) ? 8u : __any(p.w != 0) ? 4u : 0u;
   return p;
 }
 
@@ -379,7 +380,7 @@ __device__ inline void add_operand_chunks(u32 (&acc)[kSumPlanes], const u32* min
                                           u32 wcap, u32 top) {
   if constexpr (C * kSumChunk < kSumPlanes) {
     if (u32(C * kSumChunk) >= top) return;        // uniform
-    if (C * kSumChunk < 16 && u32(C * kSumChunk) < wcap) add_chunk<C, true>(acc, mine, keep, sgn, carry);
+    if (u32(C * kSumChunk) < wcap) add_chunk<C, true>(acc, mine, keep, sgn, carry);
     else add_chunk<C, false>(acc, mine, keep, sgn, carry);
     add_operand_chunks<C + 1>(acc, mine, keep, sgn, carry, wcap, top);
   }
@@ -433,21 +434,55 @@ __device__ inline u32 sign_plane(const u32 (&acc)[kSumPlanes], u32 top) {
   }
 }
 
-// One tile of a call whose operands have no block wider than 15 bits.  `meta`: the tables of
-// operand 0 if the workgroup asked for them early (`early`).
-template <bool IX>
-__device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, OperandMeta meta,
-                                          bool early, u32* lds, u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
+// What a wave knows about its share of a tile.
+struct ReduceShare {
+  u32 seg;                  // the segment (a stream has at most 2^26 blocks, so byte offsets into tables fit 32 bits)
+  bool live;                // it exists
+};
+
+// The widest block that stream s may have: 31, but 15 if it promised narrow blocks.
+__device__ inline u32 width_limit(const ReduceCall& c, int s) { return (c.wide_streams >> s) & 1u ? 31u : 15u; }
+
+// Words of an operand's payload that load_operand_payload and stage_to_lds can bring in.
+constexpr u32 kMostStaged = 256u * kStageLoads + 64u;
+static_assert(kMostStaged + kSumPlanes <= u32(kWholeStage), "payload staging, and the reads behind its last word, must fit the wave's area");
+
+// Whether the wave's blocks fit the common path: the sums its accumulator, every operand's payload the staging.
+// Without blocks wider than 15 bits they always do, and usually with some (a segment that has one is mostly
+// narrow blocks all the same: one or two spikes among 2048 values).  Only calls whose headers announce wide
+// blocks ask; the operands' width bytes are asked for together, which costs one round trip.
+__device__ inline bool fits_common_path(const ReduceArgs& a, const ReduceCall& c, u32 seg, bool ix) {
   const ParsedHeader& h = c.h;
-  const int wave = wave_id();
+  const u32 b = seg * kWaveBlocks + u32(fresh_lane());
+  const u32 at = u32(widths_begin(h.nb, ix)) + b;
+  bool unfit = false;
+  u32 reach = 0, words = 0;                    // bound on the sum of the lane's block (saturates by 2^23 a term); its largest payload
+  if (b < h.nb) {
+#pragma unroll 8
+    for (int s = 0; s < a.k; ++s) {
+      const u32 w = u32(*at_bytes(a.in[s].base, at));
+      unfit |= w > width_limit(c, s);          // (malformed: the other path says so)
+      reach += (1u << (w < u32(kSumPlanes) ? w : u32(kSumPlanes))) - 1u;      // k <= 64 terms of at most 2^24
+      words = max(words, psize_words(w));
+    }
+  }
+  // (64 x the largest possible width byte fits 32 bits; the sum over the lanes of the largest is at least any operand's)
+  return !__any(unfit || reach >= 1u << (kSumPlanes - 1)) && wave_sum_u32(words) + 3u <= kMostStaged;
+}
+
+// The sum of a wave's blocks as planes: acc = magnitudes, sgn = sign plane, w = code length, outlier = sum of the
+// first codes.  `meta`: the tables of operand 0 if the workgroup asked for them early (`early`).
+template <bool IX>
+__device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, OperandMeta meta,
+                                           bool early, u32* wl, u32 (&acc)[kSumPlanes], u32& sgn, u32& w, i64& outlier, u32& err) {
+  const ParsedHeader& h = c.h;
+  const u32 w_max = c.wide_streams ? 31u : 15u;
   const u64 tend = tables_end(h.nb, IX);
-  u32* const wl = lds + wave * kWholeStage;
-  const u32 seg = tile * kTileWaves + u32(wave);
-  const bool seg_live = seg < num_segments(h.nb);
+  const u32 seg = share.seg;
+  const bool seg_live = share.live;
   OperandPlace next;
   OperandStage stage;
   i32 outlier_next;        // the outlier of the operand in `stage`: travels with the payload
-  u32 err = 0;             // uniform
   {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
@@ -462,7 +497,7 @@ __device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall&
     } else {
       meta = load_operand_meta(a, 0, h, seg, b, active, seg_live, IX);
     }
-    next = place_operand(meta, h, IX, err);
+    next = place_operand(meta, h, IX, err, w_max);
     if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, seg_live, IX);
     stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
     outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
@@ -471,12 +506,11 @@ __device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall&
   if (IX && seg_live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
 
   // ---- add the k operands' blocks in plane form; loads run ahead of the adds ----
-  u32 acc[kSumPlanes];
 #pragma unroll
   for (int p = 0; p < kSumPlanes; ++p) acc[p] = 0;
   u32 top = 0;
-  u32 bound = 0;          // wave-uniform bound on |sum of deltas| so far (< 64 * 2^16)
-  i64 outlier = 0;
+  u32 bound = 0;          // wave-uniform bound on |sum of deltas| so far (the true sums are below 2^23: see fits_common_path)
+  outlier = 0;
   for (int s = 0; s < a.k; ++s) {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
@@ -486,7 +520,7 @@ __device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall&
     wave_lds_sync();
     outlier += i64(outlier_next);
     if (s + 1 < a.k) {
-      next = place_operand(meta, h, IX, err);
+      next = place_operand(meta, h, IX, err, w_max);
       if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, seg_live, IX);
       stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
       outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
@@ -494,7 +528,7 @@ __device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall&
     if (cur.wcap) {
       bound += (1u << cur.wcap) - 1u;
       u32 new_top = (32u - u32(__builtin_clz(bound)) + 1u + 3u) & ~3u;
-      if (new_top > u32(kSumPlanes)) new_top = kSumPlanes;      // cannot happen for k <= 64
+      if (new_top > u32(kSumPlanes)) new_top = kSumPlanes;
       grow_sum<0>(acc, top, new_top);
       top = new_top;
       const u32* mine = wl + cur.pick;
@@ -506,20 +540,11 @@ __device__ inline void reduce_narrow_tile(const ReduceArgs& a, const ReduceCall&
     wave_lds_sync();
   }
 
-  // ---- back to sign + magnitude planes; new code length; placement and copy-out ----
-  const u32 sgn = sign_plane<0>(acc, top);
-  u32 carry = sgn, w = 0;
+  // ---- back to sign + magnitude planes; new code length ----
+  sgn = sign_plane<0>(acc, top);
+  u32 carry = sgn;
+  w = 0;
   sum_to_magnitude<0>(acc, sgn, carry, w, top);
-  auto word = [&](auto i) {
-    constexpr int I = decltype(i)::value;        // 0: sign, 1 + p: plane p
-    if constexpr (I == 0) return sgn;
-    else return acc[I - 1];
-  };
-  const int lane = fresh_lane();
-  const u32 b = seg * kWaveBlocks + u32(lane);
-  if (IX && err && lane == 0) raise_status(a.ctl, c.tag, err);
-  place_sum_staged<kSumPlanes>(a, c, acc, sgn, w, outlier, b < h.nb, b, tile, ntiles, word, wl, sh_wave_total, sh_base,
-                               wave, lane, IX);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -578,7 +603,7 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
                                         u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, IX);
-  const int lane = lane_id();
+  const int lane = fresh_lane();
   const int wave = wave_id();
   u32* const wl = lds + wave * kWholeStage;
   const u32 seg = tile * kTileWaves + u32(wave);           // a stream has at most 2^26 blocks
@@ -618,7 +643,7 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
         fits = false;
       }
     } else if (seg_live) {
-      const u64 so = segment_offset(a.index, s, seg);
+      const u64 so = uniform64(segment_offset(a.index, s, seg));
       fits = so <= pw;
       seg_off = u32(so);
     }
@@ -648,17 +673,37 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
   place_sum<32>(a, c, acc, ext, w, outlier, active, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave, lane, IX);
 }
 
+// One tile on the common path.
+template <bool IX>
+__device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, const OperandMeta& meta,
+                                          bool early, u32* lds, u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
+  const int wave = wave_id();
+  u32* const wl = lds + wave * kWholeStage;
+  const u32 seg = tile * kTileWaves + u32(wave);
+  const ReduceShare share{seg, seg < num_segments(c.h.nb)};
+  u32 acc[kSumPlanes], sgn, w, err = 0;
+  i64 outlier;
+  sum_common<IX>(a, c, share, meta, early, wl, acc, sgn, w, outlier, err);
+  auto word = [&](auto i) {
+    constexpr int I = decltype(i)::value;        // 0: sign, 1 + p: plane p
+    if constexpr (I == 0) return sgn;
+    else return acc[I - 1];
+  };
+  const int lane = fresh_lane();
+  const u32 b = seg * kWaveBlocks + u32(lane);
+  if (IX && err && lane == 0) raise_status(a.ctl, c.tag, err);
+  place_sum_staged<kSumPlanes>(a, c, acc, sgn, w, outlier, b < c.h.nb, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave,
+                               lane, IX);
+}
+
 // What every workgroup of a reduce kernel does first: the call's verdict, tag and header, and its tile.
 // Returns false when the workgroup has nothing (more) to do.  Plain streams (IX false) have
 // been validated and indexed by the kernels of zc_scan.h, whose verdict and tag are in the
 // control block; indexed streams are judged here, by every workgroup alike, from their headers.
-// `meta`, `early`: see reduce_narrow_tile.  `for_wide`: the caller is the kernel that serves
-// streams with blocks wider than 15 bits (the narrow one returns at once on those, and
-// the other way round; either writes the header of its own calls); `split`: indexed streams
-// have such a pair of kernels as well (otherwise one kernel takes both kinds).
+// `meta`, `early`: see sum_common.
 template <bool IX>
-__device__ inline bool open_reduce(const ReduceArgs& a, bool for_wide, bool split, ReduceCall& c, bool& wide, OperandMeta& meta,
-                                   bool early, u32& tile, u32& ntiles, u32* sh_tile) {
+__device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMeta& meta, bool early, u32& tile, u32& ntiles,
+                                   u32* sh_tile) {
   c.ltag = launch_tag(a.nonce, a.ctl);
   // (with tickets the ticket is asked for first of all: its round trip runs beside the headers')
   u64 asked = 0;
@@ -683,15 +728,13 @@ __device__ inline bool open_reduce(const ReduceArgs& a, bool for_wide, bool spli
       meta.w = w_ok ? u32(*at_bytes(base, u32(widths_begin(nb_said, true)) + b + zero)) : 0u;
     }
     const StreamsVerdict v = judge_indexed_streams(a.in, a.k, true);
-    // (of a pair of kernels the narrow one is launched first and opens the call; a later part of a
-    //  reduce done in parts belongs to the call its first part opened)
-    const bool adopt = a.adopt != 0 || (split && for_wide);
-    c.tag = call_tag(a.ctl, c.ltag, adopt);
+    // (a later part of a reduce done in parts belongs to the call its first part opened)
+    c.tag = call_tag(a.ctl, c.ltag, a.adopt != 0);
     c.h = v.h0;
     c.nsum = v.nsum;
-    wide = v.wide;
+    c.wide_streams = v.wide;
     if (v.err) {
-      if (blockIdx.x == 0 && threadIdx.x == 0 && !(split && for_wide)) {
+      if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (!a.adopt) a.ctl->result = 0;
         raise_status(a.ctl, c.tag, v.err);
       }
@@ -701,7 +744,6 @@ __device__ inline bool open_reduce(const ReduceArgs& a, bool for_wide, bool spli
       if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, c.tag, status_bit(ZC_ERR_MISMATCH));
       return false;
     }
-    if (split && wide != for_wide) return false;
   } else {
     const u32 zero = opaque_zero();
     if (early) {
@@ -715,8 +757,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, bool for_wide, bool spli
     const Gate gate = parse_gate(gate_raw);
     c.tag = gate.tag;
     if (gate_failed(gate) || !c.h.ok) return false;
-    wide = gate_wide(gate);
-    if (wide != for_wide) return false;
+    c.wide_streams = gate_wide(gate) ? ~u64(0) : 0;
     c.nsum = 0;
   }
   ntiles = u32(num_tiles(c.h.nb));
@@ -744,17 +785,18 @@ __device__ inline bool open_reduce(const ReduceArgs& a, bool for_wide, bool spli
   return tile < end_tile;
 }
 
-// Indexed streams: one launch per call, whatever the widths.  Plain streams: the common case;
-// reduce_wide_kernel, launched behind it, takes the calls with wider blocks.
+// One launch per call, whatever the widths (plain streams: behind the two of zc_scan.h, and with a workgroup less
+// per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
+// but wide blocks, 4 x 4 194 301 values, 47 us with six and 43 with five; narrow ones, 8 x 2^24, 60.1 and 61.7.
+// The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
 template <bool IX>
-__global__ __launch_bounds__(kTileThreads, 6) void reduce_kernel(ReduceArgs a) {
+__global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];   // also holds an operand's payload
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base;
 
   ReduceCall c;
-  bool wide = false;
   OperandMeta meta{};
   // A workgroup that takes the tile of its own number asks for the first operand's tables
   // together with the control block and the header, before it knows the header: one memory
@@ -762,24 +804,25 @@ __global__ __launch_bounds__(kTileThreads, 6) void reduce_kernel(ReduceArgs a) {
   // indexed streams: where their width bytes are is only known with the header.)
   const bool early = !a.ticketed && (!IX || a.n_part != 0);
   u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, false, false, c, wide, meta, early, tile, ntiles, &sh_tile)) return;
-  if (IX && wide) reduce_wide_tile<true>(a, c, tile, ntiles, lds, sh_wave_total, &sh_base);
-  else reduce_narrow_tile<IX>(a, c, tile, ntiles, meta, early, lds, sh_wave_total, &sh_base);
-}
-
-// Plain streams with blocks wider than 15 bits.
-__global__ __launch_bounds__(kTileThreads) void reduce_wide_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base;
-
-  ReduceCall c;
-  bool wide = false;
-  OperandMeta meta{};
-  u32 tile = 0, ntiles = 0;
-  if (!open_reduce<false>(a, true, true, c, wide, meta, false, tile, ntiles, &sh_tile)) return;
-  reduce_wide_tile<false>(a, c, tile, ntiles, lds, sh_wave_total, &sh_base);
+  if (!open_reduce<IX>(a, c, meta, early, tile, ntiles, &sh_tile)) return;
+  // A tile leaves the common path only if one of its waves has to.  (A call with a block wider than 15 bits in
+  // some operand used to send every tile through reduce_wide_tile: 8 x 2^24 values of hard data 84 us, now 51;
+  // 4 x 4 194 301, two tiles per compute unit, 24.2 -> 18.9.  Calls without wide blocks,
+  // 8 x 2^26: 158.8 -> 159.9; with the mixed case as a function of its own, or as a second instance of the common
+  // path, they lost 2 and 4 % to another register allocation.)
+  bool common = true;
+  if (c.wide_streams) {                // (the same in every wave)
+    const bool fits = fits_common_path(a, c, tile * kTileWaves + u32(wave_id()), IX);
+    if (lane_id() == 0) sh_wave_total[wave_id()] = fits;
+    lds_barrier();
+    u32 all = 1;
+#pragma unroll
+    for (int i = 0; i < kTileWaves; ++i) all &= sh_wave_total[i];
+    common = uniform(all) != 0;
+    lds_barrier();                     // the words are used again
+  }
+  if (common) reduce_common_tile<IX>(a, c, tile, ntiles, meta, early, lds, sh_wave_total, &sh_base);
+  else reduce_wide_tile<IX>(a, c, tile, ntiles, lds, sh_wave_total, &sh_base);
 }
 
 }  // namespace zc

@@ -7,10 +7,20 @@
 // chain), the running extreme is kept per value in registers, and the result is encoded like a
 // compressed block (new deltas, width, planes, look-back placement).
 //
-// reduce_op_kernel serves operands without blocks wider than 15 bits; the deltas of an extreme
-// are bounded by the largest delta among the operands at the same place, so its output has
-// none either.  reduce_op_wide_kernel takes any widths with per-lane loads; both are launched
-// and each returns at once when the operands are not its.
+// What bounds it is arithmetic, and the registers that the running extremes occupy.  So the common
+// path never unpacks the codes: the transposes leave a block's deltas as 16 words of two 16-bit
+// fields, and chain, extreme and new deltas work on those words with packed 16-bit instructions,
+// two values at a time, 16 registers for the extremes of a block.  For that the codes are taken
+// relative to the lane's own base (its first code of the first operand, plus half the range), and
+// have to stay within [0, 2^15) there, which the sign bits of the fields show afterwards: a delta
+// is below 2^15 in magnitude, so a chain cannot leave that range and be back in it within one
+// step.  A wave that meets a code outside (16384 steps or more away from its block's first code), a
+// block wider than 15 bits or a code near the limits of the format starts over on the other path,
+// which keeps 32 codes of 32 bits per lane.  (Codes unpacked throughout took 145 registers, three
+// waves per SIMD, and a kernel of its own for wide blocks, launched with every call: 8 x 2^24
+// smooth values 79.5 us, now 66.3; 4 x 4 194 301 of hard data 27.8 and 21.8; 2 x 20 000 11.8 and
+// 9.3; nothing but wide blocks 36.3 both.  Five waves per SIMD instead of four: 61.9 on the smooth
+// data, but the other path spills: 46 where there are only wide blocks.)
 #pragma once
 
 #include "zc_bitmatrix.h"
@@ -27,39 +37,288 @@ __device__ inline i32 extreme(i32 a, i32 b) {
   return OP == ZC_OP_MAX ? max(a, b) : min(a, b);
 }
 
-// The extremes of a block (q[j], one lane per block) -> its place in the output stream.
-// WIDE: blocks wider than 15 bits may come out (only if some operand had one).
-template <bool IX, bool WIDE>
-__device__ inline void place_codes(const ReduceArgs& a, const ReduceCall& c, i32 (&q)[32], bool active, u32 b, u32 tile,
-                                   u32 ntiles, u32* wl, u32 (&sh_wave_total)[kTileWaves], u64* sh_base, int wave, int lane, u32 err) {
+// Two 16-bit values per word.
+typedef short i16x2_t __attribute__((ext_vector_type(2)));
+__device__ inline i16x2_t as_pair(u32 v) { return __builtin_bit_cast(i16x2_t, v); }
+__device__ inline u32 as_word(i16x2_t v) { return __builtin_bit_cast(u32, v); }
+__device__ inline u32 add_pairs(u32 a, u32 b) { return as_word(as_pair(a) + as_pair(b)); }
+__device__ inline u32 sub_pairs(u32 a, u32 b) { return as_word(as_pair(a) - as_pair(b)); }
+__device__ inline u32 max_pairs(u32 a, u32 b) { return as_word(__builtin_elementwise_max(as_pair(a), as_pair(b))); }
+__device__ inline u32 min_pairs(u32 a, u32 b) { return as_word(__builtin_elementwise_min(as_pair(a), as_pair(b))); }
+template <int OP>
+__device__ inline u32 extreme_pairs(u32 a, u32 b) {
+  return OP == ZC_OP_MAX ? max_pairs(a, b) : min_pairs(a, b);
+}
+
+// The extremes of a wave's blocks as the kernel keeps them until the tile's place is known: Lorenzo deltas
+// (d0 = 0), as 16 words of paired 16-bit fields (deltas j and j + 16) when the wave's blocks are at most 15 bits
+// wide, else one by one; the largest magnitude among a block's deltas; the first code.
+struct ExtremeBlock {
+  u32 d[32];
+  u32 any;
+  i32 outlier;
+};
+
+// The lane's sign and plane words out of its wave's staged payload: lo[0..15) = planes 0..14, lo[15] = sign
+// word (all reads at once and without conditions, what is not the block's own is dropped: see pick_block_words).
+__device__ inline void pick_operand_words(const OperandPlace& cur, const u32* wl, u32 (&lo)[16]) {
+  const u32* mine = wl + (cur.w ? cur.pick : 0u);
+  u32 t[16];
+#pragma unroll
+  for (int p = 0; p < 16; ++p) t[p] = mine[p];
+  const u32 keep = cur.w ? (1u << cur.w) - 1u : 0u;      // bit p: the block has plane p
+  lo[15] = cur.w ? t[0] : 0u;
+#pragma unroll
+  for (int p = 0; p < 15; ++p) lo[p] = t[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+}
+
+// Codes are kept as code - base + kCodeBias in the common path.
+constexpr i32 kCodeBias = 1 << 14;
+
+// The common path.  False (uniform) when some code left the range: nothing is known then.
+template <bool IX, int OP>
+__device__ __forceinline__ bool extreme_packed(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+                                      ExtremeBlock& out, u32& err) {
+  const u64 tend = tables_end(h.nb, IX);
+  const u32 seg = share.seg;
+  // operand s + 1 is on its way while operand s is decoded (as in sum_common)
+  OperandMeta meta;
+  OperandPlace next;
+  OperandStage stage;
+  i32 outlier_next;
+  {
+    const int lane = fresh_lane();
+    const u32 b = seg * kWaveBlocks + u32(lane);
+    const bool active = b < h.nb;
+    meta = load_operand_meta(a, 0, h, seg, b, active, share.live, IX);
+    next = place_operand(meta, h, IX, err);
+    if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, share.live, IX);
+    stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
+    outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
+  }
+
+  const i32 base = outlier_next;
+  // (codes of a block in range are then inside the format's limits as well: no check of the result is needed)
+  bool outside = base > kMaxCode - 2 * kCodeBias || base < 2 * kCodeBias - kMaxCode;
+  u32 acc[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) acc[j] = OP == ZC_OP_MAX ? 0u : 0x7fff7fffu;
+#pragma nounroll
+  for (int s = 0; s < a.k; ++s) {
+    const int lane = fresh_lane();
+    const u32 b = seg * kWaveBlocks + u32(lane);
+    const bool active = b < h.nb;
+    const OperandPlace cur = next;
+    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(a.in[s].base + tend), wl, lane);
+    wave_lds_sync();
+    const u32 first = u32(outlier_next) - u32(base) + u32(kCodeBias);
+    outside |= first >= u32(2 * kCodeBias);
+    if (s + 1 < a.k) {
+      next = place_operand(meta, h, IX, err);
+      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, share.live, IX);
+      stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
+      outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
+    }
+    if (cur.wcap == 0) {                       // nothing but constant blocks: every code is the block's first
+      const u32 both = first | (first << 16);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(acc[j], both);
+    } else {
+      u32 f[16];                               // word j: deltas j and j + 16, then the codes there
+      pick_operand_words(cur, wl, f);
+      if (!__any(cur.w > 7)) {                 // byte fields: word j = deltas j, j + 8, j + 16, j + 24
+        u32 r[8];
+#pragma unroll
+        for (int p = 0; p < 7; ++p) r[p] = f[p];
+        r[7] = f[15];
+        magnitude_planes_to_twos<8>(r);
+        transpose8x8_quads(r);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          f[j] = __builtin_amdgcn_perm(0u, r[j] << 8, 0x09030801u);       // (8, 9: the sign of bytes 1 and 3, eight times)
+          f[j + 8] = __builtin_amdgcn_perm(0u, r[j], 0x09030801u);
+        }
+      } else {
+        magnitude_planes_to_twos<16>(f);
+        transpose16x16_pairs(f);
+      }
+      // both halves of the block at once, the second one from zero; then it gets what the first one ends with
+      f[0] = add_pairs(f[0], first & 0xffffu);
+#pragma unroll
+      for (int j = 1; j < 16; ++j) f[j] = add_pairs(f[j], f[j - 1]);
+      const u32 half = f[15] << 16;
+      u32 seen = 0;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        f[j] += half;                          // (the low field of `half` is zero: no carry between the fields)
+        seen |= f[j];
+        acc[j] = extreme_pairs<OP>(acc[j], f[j]);
+      }
+      outside |= (seen & 0x80008000u) != 0;
+    }
+    wave_lds_sync();
+    if (__any(outside)) return false;
+  }
+  // the new deltas, in pairs; those of the second half's first value cross the halves
+  u32 top = 0, bottom = 0;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const u32 before = j ? acc[j - 1] : acc[15] << 16;
+    out.d[j] = j ? sub_pairs(acc[j], before) : sub_pairs(acc[j], before) & 0xffff0000u;
+    top = max_pairs(top, out.d[j]);
+    bottom = min_pairs(bottom, out.d[j]);
+  }
+  const i32 hi = max(i32(top) >> 16, i32(top << 16) >> 16), lo = min(i32(bottom) >> 16, i32(bottom << 16) >> 16);
+  out.any = u32(max(hi, -lo));
+  out.outlier = base + i32(acc[0] & 0xffffu) - kCodeBias;
+  return true;
+}
+
+// A segment whose payload is more than stage_to_lds brings in (all its blocks are wide then) comes in two parts,
+// the blocks of lanes 0..31 and those of lanes 32..63.
+static_assert(kMostStaged >= 3 + 32 * 32 && kMostStaged + 32 <= u32(kWaveStage), "half a segment of widest blocks, and the reads behind its last word, must fit the wave's area");
+
+__device__ inline u32 operand_parts(const OperandPlace& p) { return p.span > kMostStaged ? 2u : 1u; }     // uniform
+
+__device__ inline OperandPlace operand_part(const OperandPlace& p, u32 part, int lane) {
+  if (operand_parts(p) == 1) return p;
+  const u32 split = lane_value(p.pick, 32);                // where lane 32's words start
+  const u32 begin = part ? split & ~3u : 0u;
+  OperandPlace q = p;
+  q.src0 = p.src0 + begin;
+  q.room = p.room - begin;
+  q.span = (part ? p.span : split) - begin;
+  const bool mine = u32(lane >> 5) == part;
+  q.w = mine ? p.w : 0u;
+  q.pick = mine ? p.pick - begin : 0u;
+  return q;
+}
+
+// Any codes and widths.
+template <bool IX, int OP>
+__device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
+                                   ExtremeBlock& out, u32& err) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, IX);
+  i32 acc[32];
+#pragma unroll
+  for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
+  OperandMeta meta;
+  {
+    const u32 b = share.seg * kWaveBlocks + u32(fresh_lane());
+    meta = load_operand_meta(a, 0, h, share.seg, b, b < h.nb, share.live, IX);
+  }
+#pragma nounroll
+  for (int s = 0; s < a.k; ++s) {
+    const int lane = fresh_lane();
+    const u32 b = share.seg * kWaveBlocks + u32(lane);
+    const bool active = b < h.nb;
+    const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + tend);
+    const OperandPlace cur = place_operand(meta, h, IX, err, width_limit(c, s));
+    u32 code = u32(load_operand_outlier(a, s, h, b, active, IX));
+    if (!__any(cur.w > 15)) {
+      const OperandStage stage = load_operand_payload(payload, cur, lane);
+      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX);
+      stage_to_lds(stage, cur, payload, wl, lane);
+      wave_lds_sync();
+      u32 f[16];
+      pick_operand_words(cur, wl, f);
+      wave_lds_sync();
+      magnitude_planes_to_twos<16>(f);
+      transpose16x16_pairs(f);
+#pragma unroll
+      for (int j = 0; j < 32; ++j) {
+        code += u32(__builtin_amdgcn_sbfe(i32(f[j & 15]), u32(16 * (j >> 4)), 16u));
+        acc[j] = extreme<OP>(acc[j], i32(code));
+      }
+    } else {
+      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX);
+      u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
+#pragma unroll
+      for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
+#pragma nounroll
+      for (u32 part = 0; part < operand_parts(cur); ++part) {
+        const OperandPlace here = operand_part(cur, part, lane);
+        stage_to_lds(load_operand_payload(payload, here, lane), here, payload, wl, lane);
+        wave_lds_sync();
+        const u32* const mine = wl + (here.w ? here.pick : 0u);
+        const u32 keep = (1u << here.w) - 1u;  // bit p: the block has plane p
+#pragma unroll
+        for (int p = 0; p < 16; ++p) lo[p] |= mine[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+#pragma unroll
+        for (int p = 0; p < 15; ++p) hi[p] |= mine[17 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(16 + p), 1u));
+        hi[15] |= here.w ? mine[0] : 0u;
+        wave_lds_sync();
+      }
+      transpose16x16_pairs(lo);
+      transpose16x16_pairs(hi);
+#pragma unroll
+      for (int j = 0; j < 32; ++j) {
+        const u32 f = j < 16 ? (lo[j & 15] & 0xffffu) | (hi[j & 15] << 16) : (lo[j & 15] >> 16) | (hi[j & 15] & 0xffff0000u);
+        code += u32(delta_from_field<32>(f));
+        acc[j] = extreme<OP>(acc[j], i32(code));
+      }
+    }
+  }
+  const bool active = share.seg * kWaveBlocks + u32(fresh_lane()) < h.nb;
   // range of the codes (operands of a valid stream are inside it, so is their extreme)
-  i32 hi = q[0], lo = q[0];
+  i32 hi = acc[0], lo = acc[0];
 #pragma unroll
   for (int j = 1; j < 32; ++j) {
-    hi = max(hi, q[j]);
-    lo = min(lo, q[j]);
+    hi = max(hi, acc[j]);
+    lo = min(lo, acc[j]);
   }
   const bool out_of_range = active && (i64(hi) > kMaxCode || i64(lo) < -kMaxCode);
   if (out_of_range) err |= status_bit(ZC_ERR_RANGE);
-  const i32 outlier = q[0];
-  // codes -> Lorenzo deltas, in place, last first
+  out.outlier = acc[0];
+  // codes -> Lorenzo deltas, last first
   i32 top = 0, bottom = 0;
 #pragma unroll
   for (int j = 31; j >= 1; --j) {
-    q[j] = i32(u32(q[j]) - u32(q[j - 1]));
-    top = max(top, q[j]);
-    bottom = min(bottom, q[j]);
+    acc[j] = i32(u32(acc[j]) - u32(acc[j - 1]));
+    top = max(top, acc[j]);
+    bottom = min(bottom, acc[j]);
   }
-  q[0] = 0;
-  const u32 any = max(u32(top), u32(-bottom));
+  acc[0] = 0;
+  out.any = out_of_range ? 0u : max(u32(top), u32(-bottom));
+  if (__any(active && out.any > 0x7fffu)) {
+#pragma unroll
+    for (int j = 0; j < 32; ++j) out.d[j] = u32(acc[j]);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) out.d[j] = field16_pair(acc[j], acc[j + 16]);
+  }
+}
+
+template <bool IX, int OP>
+__global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[kTileWaves];
+  __shared__ u64 sh_base;
+
+  ReduceCall c;
+  OperandMeta meta{};
+  u32 tile = 0, ntiles = 0;
+  if (!open_reduce<IX>(a, c, meta, false, tile, ntiles, &sh_tile)) return;
+  const ParsedHeader& h = c.h;
+  const int wave = wave_id();
+  const u64 tend = tables_end(h.nb, IX);
+  u32* const wl = lds + wave * kWaveStage;
+  const u32 seg = tile * kTileWaves + u32(wave);
+  const ReduceShare share{seg, seg < num_segments(h.nb)};
+  u32 err = 0;
+  if (IX && share.live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
+
+  ExtremeBlock eb;
+  if (c.wide_streams || !extreme_packed<IX, OP>(a, h, share, wl, eb, err))
+    extreme_any<IX, OP>(a, c, share, wl, eb, err);
+
+  const int lane = fresh_lane();
+  const u32 b = seg * kWaveBlocks + u32(lane);
+  const bool active = b < h.nb;
   Placement pl;
-  pl.w = (active && any && !out_of_range) ? 32u - u32(__builtin_clz(any)) : 0u;
-  if (!WIDE && __any(pl.w > 15)) {          // cannot happen: |delta of an extreme| <= the operands' largest |delta|
-    err |= status_bit(ZC_ERR_HIP);
-    pl.w = 0;
-  }
+  pl.w = (active && eb.any) ? 32u - u32(__builtin_clz(eb.any)) : 0u;
   pl.wmax = wave_max_u32(pl.w);
   const u32 words = psize_words(pl.w);
   const u32 incl = wave_inclusive_sum(words);
@@ -72,23 +331,28 @@ __device__ inline void place_codes(const ReduceArgs& a, const ReduceCall& c, i32
   const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, IX, a.coherent != 0, 0u, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
-  const bool narrow = !WIDE || pl.wmax <= 15;
-  const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
+  const bool narrow = pl.wmax <= 15;         // uniform
+  const TileBase tb = resolve_tile_base(sink, pl, tile, &sh_base, wave, lane, [&] {
     if (!narrow) return;
     u32 pw[16];
-    planes_from_deltas16(q, pw);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) pw[j] = eb.d[j];
+    planes16_from_fields(pw);
     stage_wave_words<16>([&](auto i) {
       constexpr int I = decltype(i)::value;          // 0: sign, 1 + p: plane p
       if constexpr (I == 0) return pw[15];
       else return pw[I - 1];
     }, pl, wl);
   });
-  if (lane == 0) write_index_entry(sink, tile * kTileWaves + u32(wave), tb.words + pl.wave_off);
+  if (lane == 0) write_index_entry(sink, seg, tb.words + pl.wave_off);
   if (narrow) {
     copy_staged_wave<16>(sink, pl, tb.words, wl, lane);
   } else {
+    i32 d[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) d[j] = i32(eb.d[j]);
     u32 plo[16], phi[16];
-    planes_from_deltas32(q, plo, phi);
+    planes_from_deltas32(d, plo, phi);
     copy_wave_out<32>(sink, [&](auto i) {
       constexpr int I = decltype(i)::value;
       if constexpr (I == 0) return phi[15];
@@ -96,178 +360,11 @@ __device__ inline void place_codes(const ReduceArgs& a, const ReduceCall& c, i32
       else return phi[I - 17];
     }, pl, tb.words, wl, lane);
   }
-  if (active && a.out_cap >= tend) {     // (at the very end: see place_sum_staged)
+  if (active && a.out_cap >= tend) {     // (at the very end: a store under way is waited for by every poll of the look-back)
     __builtin_nontemporal_store(u8(pl.w), a.out + widths_begin(h.nb, IX) + b);
-    __builtin_nontemporal_store(outlier, reinterpret_cast<i32*>(a.out + outliers_begin(h.nb, IX)) + b);
+    __builtin_nontemporal_store(eb.outlier, reinterpret_cast<i32*>(a.out + outliers_begin(h.nb, IX)) + b);
   }
   finish_stream(sink, pl, tile, ntiles, tb);
-}
-
-template <bool IX, int OP>
-__global__ __launch_bounds__(kTileThreads, 3) void reduce_op_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base;
-
-  ReduceCall c;
-  bool wide = false;
-  OperandMeta meta{};
-  u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, false, true, c, wide, meta, false, tile, ntiles, &sh_tile)) return;
-  const ParsedHeader& h = c.h;
-  const int wave = wave_id();
-  const int lane = lane_id();
-  const u64 tend = tables_end(h.nb, IX);
-  u32* const wl = lds + wave * kWholeStage;
-  const u32 seg = tile * kTileWaves + u32(wave);
-  const bool seg_live = seg < num_segments(h.nb);
-  const u32 b = seg * kWaveBlocks + u32(lane);
-  const bool active = b < h.nb;
-  u32 err = 0;
-  if (IX && seg_live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
-
-  // operand s + 1 is on its way while operand s is decoded (as in reduce_narrow_tile)
-  meta = load_operand_meta(a, 0, h, seg, b, active, seg_live, IX);
-  OperandPlace next = place_operand(meta, h, IX, err);
-  if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, seg_live, IX);
-  OperandStage stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
-  i32 outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
-
-  i32 acc[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
-  for (int s = 0; s < a.k; ++s) {
-    const OperandPlace cur = next;
-    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(a.in[s].base + tend), wl, lane);
-    wave_lds_sync();
-    u32 code = u32(outlier_next);
-    if (s + 1 < a.k) {
-      next = place_operand(meta, h, IX, err);
-      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, seg_live, IX);
-      stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
-      outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
-    }
-    // the lane's sign and plane words out of the staged payload, then deltas by the bit-matrix transposes
-    // (all reads at once and without conditions, what is not the block's own is dropped: see pick_block_words)
-    u32 lo[16];
-    {
-      const u32* mine = wl + (cur.w ? cur.pick : 0u);
-      u32 t[16];
-#pragma unroll
-      for (int p = 0; p < 16; ++p) t[p] = mine[p];
-      const u32 keep = cur.w ? (1u << cur.w) - 1u : 0u;      // bit p: the block has plane p
-      lo[15] = cur.w ? t[0] : 0u;
-#pragma unroll
-      for (int p = 0; p < 15; ++p) lo[p] = t[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
-    }
-    wave_lds_sync();
-    if (cur.wcap == 0) {                       // nothing but constant blocks: every code is the block's first
-#pragma unroll
-      for (int j = 0; j < 32; ++j) acc[j] = extreme<OP>(acc[j], i32(code));
-    } else if (cur.wcap <= 4) {                // every block of the wave at most 4 bits wide: byte fields
-      u32 r[8];
-#pragma unroll
-      for (int p = 0; p < 7; ++p) r[p] = lo[p];
-      r[7] = lo[15];
-      magnitude_planes_to_twos<8>(r);
-      transpose8x8_quads(r);
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        code += u32(__builtin_amdgcn_sbfe(i32(r[j & 7]), u32(8 * (j >> 3)), 8u));
-        acc[j] = extreme<OP>(acc[j], i32(code));
-      }
-    } else {
-      magnitude_planes_to_twos<16>(lo);
-      transpose16x16_pairs(lo);
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        code += u32(__builtin_amdgcn_sbfe(i32(lo[j & 15]), u32(16 * (j >> 4)), 16u));
-        acc[j] = extreme<OP>(acc[j], i32(code));
-      }
-    }
-  }
-  place_codes<IX, false>(a, c, acc, active, b, tile, ntiles, wl, sh_wave_total, &sh_base, wave, lane, err);
-}
-
-template <bool IX, int OP>
-__global__ __launch_bounds__(kTileThreads) void reduce_op_wide_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base;
-
-  ReduceCall c;
-  bool wide = false;
-  OperandMeta meta{};
-  u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, true, true, c, wide, meta, false, tile, ntiles, &sh_tile)) return;
-  const ParsedHeader& h = c.h;
-  const int wave = wave_id();
-  const int lane = lane_id();
-  const u64 tend = tables_end(h.nb, IX);
-  u32* const wl = lds + wave * kWholeStage;
-  const u32 seg = tile * kTileWaves + u32(wave);
-  const bool seg_live = seg < num_segments(h.nb);
-  const u32 b = seg * kWaveBlocks + u32(lane);
-  const bool active = b < h.nb;
-  u32 err = 0;
-  if (IX && seg_live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
-
-  i32 acc[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
-#pragma nounroll
-  for (int s = 0; s < a.k; ++s) {
-    const u8* base = a.in[s].base;
-    const u64 total_s = reinterpret_cast<const u64*>(base)[3];
-    const u64 pw64 = total_s >= tend ? (total_s - tend) / 4 : 0;
-    const u32 pw = pw64 > 0xffffffffull ? 0xffffffffu : u32(pw64);
-    u32 w = active ? u32(*at_bytes(base, u32(widths_begin(h.nb, IX)) + b)) : 0u;
-    const bool bad_w = w > 31;                    // plain streams: cannot happen on a validated stream
-    if (bad_w) w = 0;
-    const u32 words = psize_words(w);
-    const u32 incl = wave_inclusive_sum(words);
-    u32 seg_off = 0;
-    bool fits = seg_live;
-    if (IX) {
-      const u32* index = reinterpret_cast<const u32*>(base + kHeaderBytes);
-      const u32 seg_end = seg_live ? index[seg + 1] : 0u;
-      seg_off = seg_live ? index[seg] : 0u;
-      const bool narrow_promised = (reinterpret_cast<const u32*>(base)[1] & 1u) == 0;
-      if (seg_end - seg_off != lane_value(incl, 63) || __any(bad_w) || (narrow_promised && __any(w > 15))) {
-        err |= status_bit(ZC_ERR_FORMAT);
-        fits = false;
-      }
-    } else if (seg_live) {
-      const u64 so = segment_offset(a.index, s, seg);
-      fits = so <= pw;
-      seg_off = u32(so);
-    }
-    if (!fits || seg_off > pw || lane_value(incl, 63) > pw - seg_off) w = 0;
-    u32 code = active ? u32(*reinterpret_cast<const i32*>(at_bytes(base, u32(outliers_begin(h.nb, IX)) + 4u * b))) : 0u;
-    u32 lo[16], hi[16];
-#pragma unroll
-    for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
-    if (w) {
-      const u32* mine = reinterpret_cast<const u32*>(base + tend) + seg_off + (incl - words);
-      hi[15] = mine[0];
-#pragma unroll
-      for (int p = 0; p < 16; ++p)
-        if (u32(p) < w) lo[p] = mine[1 + p];
-#pragma unroll
-      for (int p = 0; p < 15; ++p)
-        if (u32(16 + p) < w) hi[p] = mine[17 + p];
-    }
-    i32 d[32];
-    deltas_from_planes32(lo, hi, d);
-#pragma unroll
-    for (int j = 0; j < 32; ++j) {
-      code += u32(d[j]);
-      acc[j] = extreme<OP>(acc[j], i32(code));
-    }
-  }
-  place_codes<IX, true>(a, c, acc, active, b, tile, ntiles, wl, sh_wave_total, &sh_base, wave, lane, err);
 }
 
 }  // namespace zc

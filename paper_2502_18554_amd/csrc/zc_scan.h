@@ -324,7 +324,7 @@ struct StreamsVerdict {
   u32 err;              // status bits: FORMAT, MISMATCH (uniform)
   u64 nsum;             // sum of the nsum fields of the valid streams
   u64 sum_n;            // sum of their n fields
-  bool wide;            // some stream may hold blocks wider than 15 bits
+  u64 wide;             // bit s: stream s may hold blocks wider than 15 bits (uniform)
 };
 
 __device__ inline StreamsVerdict judge_indexed_streams(const StreamRef* streams, int k, bool check_match) {
@@ -353,7 +353,7 @@ __device__ inline StreamsVerdict judge_indexed_streams(const StreamRef* streams,
   if (__any(mine && !h.ok)) v.err |= status_bit(ZC_ERR_FORMAT);
   if (check_match && v.h0.ok && __any(mine && h.ok && (h.n != v.h0.n || h.eb_bits != v.h0.eb_bits)))
     v.err |= status_bit(ZC_ERR_MISMATCH);
-  v.wide = __any(mine && h.ok && h.wide);
+  v.wide = __ballot(mine && h.ok && h.wide);
   const u32 ns = mine && h.ok ? h.nsum : 0u;
   v.nsum = u64(wave_sum_u32(ns & 0xffffu)) + (u64(wave_sum_u32(ns >> 16)) << 16);
   const u64 nn = mine && h.ok ? h.n : 0;              // <= 2^31

@@ -1531,3 +1531,32 @@ def test_reduce_step_some_blocks_of_a_wave_off_the_common_path(zcref, kind, coun
         ref = zcref.reduce_step(received, local.astype(np.float32)) if op is None else zcref.reduce_step(received, local.astype(np.float32), op=op)
         got = u.gpu_reduce_step(received, local.astype(np.float32), op=op)
         assert got[0] == ref[0] and got[0] in (ZC_OK, ZC_ERR_BOUND) and got[1].tobytes() == ref[1].tobytes(), (op, u.first_diff(got[1], ref[1]))
+
+
+@pytest.mark.parametrize("k,width,count", [(2, 16, 1), (4, 17, 3), (2, 22, 2), (2, 23, 2), (7, 20, 1), (8, 20, 1), (9, 20, 2),
+                                           (3, 16, 62), (3, 16, 64), (2, 31, 1), (64, 16, 2)])
+def test_reduce_some_wide_blocks(zcref, k, width, count):
+    """Sum, Max and Min of operands with `count` blocks of `width` bits in some segments: either side of what the
+    Sum's common path takes (sums below 2^23, at most 1085 payload words a segment), beside narrow segments."""
+    u = _u()
+    rng = np.random.default_rng(100 * k + width)
+    eb = 1e-6
+    n = 2048 * 13 - 45
+    nb = (n + 31) // 32
+    streams = []
+    for s in range(k):
+        q = rng.integers(-900, 900, n).astype(np.int64)
+        for seg in (0, 5, 6, 12):
+            for b in rng.choice(64, count, replace=False) + 64 * seg:
+                if b >= nb or (b + s) % 3 == 0:
+                    continue
+                at = slice(32 * b, min(32 * b + 32, n))
+                top = min(2 ** (width - 1), 2 ** 30 // k)
+                q[at] = np.where(np.arange(at.stop - at.start) % 2 == 0, top - 1, -top // 2 - 5)
+        st, stream, _ = zcref.encode_codes(np.clip(q, -(2 ** 30) + 1, 2 ** 30 - 1).astype(np.int32), eb)
+        assert st == ZC_OK
+        streams.append(stream)
+    for op in (None, 1, 2):
+        ref = zcref.reduce(streams) if op is None else zcref.reduce(streams, op=op)
+        got = u.gpu_reduce(streams, n, op=op)
+        assert got[0] == ref[0] == ZC_OK and got[1].tobytes() == ref[1].tobytes(), (op, u.first_diff(got[1], ref[1]))
