@@ -109,13 +109,14 @@ __device__ inline u32 share_values(u64 n, u64 v0) {
 // Raw input of one wave's share of a tile: 8 x 16 bytes per lane, every load in flight at once.  They are
 // buffer loads whose range is the share's whole 16-byte pieces, so the ragged end of an input needs no branch
 // and no launch of its own: what lies beyond reads as zero without an access.  (The one to three values of an
-// incomplete last piece: see block_codes.)
+// incomplete last piece: see block_codes.)  The range check covers the vector offset and the instruction's own; a
+// scalar offset is not part of it, so there is none: the second four loads have a vector offset of their own.
 __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u32 have, float4 (&x)[8]) {
   const __amdgpu_buffer_rsrc_t share =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in + wblock0 * kBlockValues), 0, int(4u * (have & ~3u)), kRawBuffer);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * (i & 3), 4096 * (i >> 2), kAccessOnce);
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * i, 0, kAccessOnce);
     x[i] = make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
   }
   // Nothing moves across this line: left to itself the compiler puts the first use of the first value,

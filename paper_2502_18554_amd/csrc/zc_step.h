@@ -149,7 +149,7 @@ __device__ inline void load_local(const float* local, u64 v0, u32 have, int lane
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(local + v0), 0, int(4u * (have & ~3u)), kRawBuffer);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * (i & 3), 4096 * (i >> 2), kAccessOnce);
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * i, 0, kAccessOnce);
     x[i] = make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w));
   }
 }

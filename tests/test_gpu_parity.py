@@ -385,11 +385,12 @@ def test_reduce_step_stream_matches_reference(zcref, n, rel):
     assert s.tobytes() == s_ref.tobytes(), u.first_diff(s, s_ref)
 
 
-@pytest.mark.parametrize("rest", [1, 3, 4, 30, 33, 2045])
+@pytest.mark.parametrize("rest", [1, 3, 4, 30, 33, 1023, 1025, 2045, 2049])
 @pytest.mark.parametrize("op", [0, 1, 2])
 def test_reduce_step_ragged_end(zcref, rest, op):
-    """The wave at the end of the buffer: poison behind the local values, and a received stream whose padding is not
-    the copies of the last code that a compressor writes (only the values count)."""
+    """The waves at the end of the buffer, with less and with more than half their values: poison behind the local
+    values as far as a whole tile would reach, and a received stream whose padding is not the copies of the last code
+    that a compressor writes (only the values count)."""
     u = _u()
     n = 2 * TILE + rest
     rng = np.random.default_rng(rest)
@@ -400,7 +401,7 @@ def test_reduce_step_ragged_end(zcref, rest, op):
     if rest % 32 and w[nb - 1]:
         received = received.copy()
         received[-1] ^= 0x80                     # the top bit of the last block's last plane: a delta of the padding
-    local = torch.full((n + 64,), float("nan"), device=u.DEV)
+    local = torch.full((n + 2 * TILE,), float("nan"), device=u.DEV)
     y = (np.cumsum(rng.integers(-90, 91, n)) * 1e-3).astype(np.float32)
     local[:n] = torch.from_numpy(y)
     d_out = torch.zeros(zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
@@ -756,15 +757,16 @@ def test_wide_block_in_the_ragged_last_tile(zcref, tail):
     assert st == zcref.compress(x, 1e-3)[0] and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
 
 
-@pytest.mark.parametrize("rest", [1, 2, 3, 4, 5, 29, 2046, 2049, 2 * TILE - 1])
+@pytest.mark.parametrize("rest", [1, 2, 3, 4, 5, 29, 33, 1023, 1024, 1025, 2046, 2049, 2 * TILE - 1])
 def test_compress_ragged_end_beside_full_tiles(zcref, rest):
     """The values behind the last whole 16-byte piece of an input, in the launch of the full tiles: coded, padded and
-    checked like all others (poison lies behind the input)."""
+    checked like all others.  Poison lies behind the input for a whole tile, so that whatever a wave with less than
+    half its values, or a wave wholly behind the input, may ask for is poison if it arrives."""
     u = _u()
     n = 4 * TILE + rest
     rng = np.random.default_rng(rest)
     x = np.cumsum(rng.normal(0, 0.01, n)).astype(np.float32)
-    d_all = torch.full((n + 64,), float("nan"), device=u.DEV)
+    d_all = torch.full((n + 2 * TILE,), float("nan"), device=u.DEV)
 
     def run(x):
         d_all[:n] = torch.from_numpy(x)
