@@ -361,9 +361,7 @@ __device__ inline u32 opaque_zero() {
 // the spot: hoisted out of a loop over operands, or shared with a path that is hardly ever taken, it
 // would sit in registers that the step needs.
 __device__ inline int fresh_lane() {
-  int lane = lane_id();
-  asm volatile("" : "+v"(lane));
-  return lane;
+  return int(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, opaque_zero())));
 }
 // Index of the calling wave in its workgroup, as a scalar.
 __device__ inline int wave_id() { return int(uniform(threadIdx.x >> 6)); }

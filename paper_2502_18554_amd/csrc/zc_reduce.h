@@ -227,10 +227,10 @@ struct OperandPlace {
 // into the tables).  w_ok and seg_ok say which loads stay inside the stream and the index;
 // they need not be the exact "block exists" conditions (the caller drops what it must not
 // use), which lets a workgroup ask before it knows the header.
-__device__ inline OperandMeta load_operand_tables(const ReduceArgs& a, int s, u32 seg, u32 b, bool w_ok, bool seg_ok,
-                                                  u32 zero = 0) {
+__device__ inline OperandMeta load_operand_tables(const ReduceArgs& a, int s, const StreamRef& in, u32 seg, u32 b, bool w_ok,
+                                                  bool seg_ok, u32 zero = 0) {
   OperandMeta m;
-  const u8* base = a.in[s].base;
+  const u8* base = in.base;
   m.seg_off = SegmentOffsetParts{0, 0, 0};
   if (seg_ok) m.seg_off = load_segment_offset(a.index, s, seg, zero);
   m.seg_end = 0;
@@ -239,14 +239,17 @@ __device__ inline OperandMeta load_operand_tables(const ReduceArgs& a, int s, u3
   return m;
 }
 
-__device__ inline i32 load_operand_outlier(const ReduceArgs& a, int s, const ParsedHeader& h, u32 b, bool active, bool ix) {
-  const u8* base = a.in[s].base;
+__device__ inline i32 load_operand_outlier(const u8* base, const ParsedHeader& h, u32 b, bool active, bool ix) {
   return active ? *reinterpret_cast<const i32*>(at_bytes(base, u32(outliers_begin(h.nb, ix)) + 4u * b)) : 0;
 }
 
-__device__ inline u32 payload_room(const ReduceArgs& a, int s, const ParsedHeader& h, bool ix) {
+__device__ inline i32 load_operand_outlier(const ReduceArgs& a, int s, const ParsedHeader& h, u32 b, bool active, bool ix) {
+  return load_operand_outlier(a.in[s].base, h, b, active, ix);
+}
+
+__device__ inline u32 payload_room(u64 bytes, const ParsedHeader& h, bool ix) {
   const u64 tend = tables_end(h.nb, ix);
-  const u64 room = a.in[s].bytes > tend ? (a.in[s].bytes - tend) / 4 : 0;
+  const u64 room = bytes > tend ? (bytes - tend) / 4 : 0;
   return room > 0xffffffffull ? 0xffffffffu : u32(room);   // a stream's payload has at most 2^31 words
 }
 
@@ -255,23 +258,27 @@ __device__ inline u32 payload_room(const ReduceArgs& a, int s, const ParsedHeade
 // buffer; nothing reads those words).
 // An indexed stream (ix) has the segment's position in its own index, and its width bytes
 // behind that index (every stream of a validated call has the header's nb).
-__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const ParsedHeader& h, u32 seg, u32 b,
-                                                bool active, bool seg_live, bool ix) {
+__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const StreamRef& in, const ParsedHeader& h, u32 seg,
+                                                u32 b, bool active, bool seg_live, bool ix, u32 zero = 0) {
   OperandMeta m;
   if (ix) {
-    const u8* base = a.in[s].base;
+    const u8* base = in.base;
     m.seg_off = SegmentOffsetParts{0, 0, 0};
     m.seg_end = 0;
     if (seg_live) {
-      m.seg_off = load_segment_offset(a.index, s, seg, 0, base);
-      m.seg_end = load_segment_end(base, seg);
+      m.seg_off = load_segment_offset(a.index, s, seg, zero, base);
+      m.seg_end = load_segment_end(base, seg, zero);
     }
     m.w = active ? u32(*at_bytes(base, u32(widths_begin(h.nb, true)) + b)) : 0u;
   } else {
-    m = load_operand_tables(a, s, seg, b, active, seg_live);
+    m = load_operand_tables(a, s, in, seg, b, active, seg_live, zero);
   }
-  m.payload_room = payload_room(a, s, h, ix);
+  m.payload_room = payload_room(in.bytes, h, ix);
   return m;
+}
+__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const ParsedHeader& h, u32 seg, u32 b, bool active,
+                                                bool seg_live, bool ix, u32 zero = 0) {
+  return load_operand_meta(a, s, a.in[s], h, seg, b, active, seg_live, ix, zero);
 }
 
 // `err`: an indexed stream is checked as it is used: the widths of the segment must add up to
@@ -493,7 +500,7 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
         meta.seg_off = SegmentOffsetParts{0, 0, 0};
         meta.seg_end = 0;
       }
-      meta.payload_room = payload_room(a, 0, h, IX);
+      meta.payload_room = payload_room(a.in[0].bytes, h, IX);
     } else {
       meta = load_operand_meta(a, 0, h, seg, b, active, seg_live, IX);
     }
@@ -749,7 +756,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
     if (early) {
       const u32 seg = blockIdx.x * kTileWaves + u32(wave_id());     // < 2^22: the host launches at most 2^18 tiles
       const u32 b = seg * kWaveBlocks + u32(fresh_lane());
-      meta = load_operand_tables(a, 0, seg, b, u64(kHeaderBytes) + b < a.in[0].bytes, seg < 4 * a.index.tiles_cap, zero);
+      meta = load_operand_tables(a, 0, a.in[0], seg, b, u64(kHeaderBytes) + b < a.in[0].bytes, seg < 4 * a.index.tiles_cap, zero);
     }
     const uint4 gate_raw = load_gate(a.ctl, zero);
     const HeaderWords hw = load_header_words(a.in[0].base, zero);

@@ -10,17 +10,30 @@
 // What bounds it is arithmetic, and the registers that the running extremes occupy.  So the common
 // path never unpacks the codes: the transposes leave a block's deltas as 16 words of two 16-bit
 // fields, and chain, extreme and new deltas work on those words with packed 16-bit instructions,
-// two values at a time, 16 registers for the extremes of a block.  For that the codes are taken
-// relative to the lane's own base (its first code of the first operand, plus half the range), and
-// have to stay within [0, 2^15) there, which the sign bits of the fields show afterwards: a delta
-// is below 2^15 in magnitude, so a chain cannot leave that range and be back in it within one
-// step.  A wave that meets a code outside (16384 steps or more away from its block's first code), a
-// block wider than 15 bits or a code near the limits of the format starts over on the other path,
-// which keeps 32 codes of 32 bits per lane.  (Codes unpacked throughout took 145 registers, three
-// waves per SIMD, and a kernel of its own for wide blocks, launched with every call: 8 x 2^24
-// smooth values 79.5 us, now 66.3; 4 x 4 194 301 of hard data 27.8 and 21.8; 2 x 20 000 11.8 and
-// 9.3; nothing but wide blocks 36.3 both.  Five waves per SIMD instead of four: 61.9 on the smooth
-// data, but the other path spills: 46 where there are only wide blocks.)
+// two values at a time, 16 registers for the extremes of a block.  For that an operand's codes are
+// taken relative to the lane's base (the first code of its block in the first operand), or to
+// the operand's own first code where that is 2^13 or more away from the base: of two blocks that
+// far apart the one behind is shifted to the base of the other, and what leaves 16 bits by that has lost
+// (fold_far_codes).  Relative to whichever it is the codes have to stay within [0, 2^15) or
+// [-2^15, 0), which the sign bits of the fields show: a delta is below 2^15 in magnitude, so a
+// chain cannot leave that range and be back in it within one step.  A wave that meets a block with
+// a code 16384 or more away from its first (or a code near the limits of the format) goes on from
+// that operand with 32 codes of 32 bits per lane (extreme_rest).  A call with an operand that may have blocks wider
+// than 15 bits does so from the start, in all its waves (extreme_any).
+// Measured, 8 x 2^24 values unless said otherwise, first with codes unpacked throughout (145 registers, three waves
+// per SIMD, and a kernel of its own for wide blocks, launched with every call), then now:
+//   smooth field, bound 1e-4 of its range                     79.5   65.5 us
+//   the same at 1e-5 (first codes and excursions beyond 2^13) 90     82
+//   1e-4, each rank at a level of its own                     86     77
+//   white noise over 32000 codes (nothing fits 16 bits)       109    102
+//   16 x 2^20 at 1e-5                                         36.5   34.3
+//   hard data, 4 x 4 194 301                                  28.2   20.9
+//   2 x 20 000                                                11.7   9.1
+// (Starting over in 32 bits instead of going on there, without the next operand on its way, the second to fifth took 107,
+// 101, 120 and 43.5.)  128 registers, four waves per SIMD, and 52 bytes of scratch (68 on plain streams) that only the
+// wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
+// is computed where it is used: with both in registers across the loops these spilled 240 bytes, and every reload waits
+// for the loads under way.  Five waves per SIMD: 61.9 on the smooth field, but 46 against 36 where there are only wide blocks.
 #pragma once
 
 #include "zc_bitmatrix.h"
@@ -72,94 +85,154 @@ __device__ inline void pick_operand_words(const OperandPlace& cur, const u32* wl
   for (int p = 0; p < 15; ++p) lo[p] = t[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
 }
 
-// Codes are kept as code - base + kCodeBias in the common path.
-constexpr i32 kCodeBias = 1 << 14;
+// The deltas of the lane's block, fields as transpose16x16_pairs leaves them (word j: deltas j and j + 16), out of its
+// wave's staged payload.
+__device__ inline void operand_delta_pairs(const OperandPlace& cur, const u32* wl, u32 (&f)[16]) {
+  pick_operand_words(cur, wl, f);
+  if (!__any(cur.w > 7)) {                     // byte fields: word j = deltas j, j + 8, j + 16, j + 24
+    u32 r[8];
+#pragma unroll
+    for (int p = 0; p < 7; ++p) r[p] = f[p];
+    r[7] = f[15];
+    magnitude_planes_to_twos<8>(r);
+    transpose8x8_quads(r);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      f[j] = __builtin_amdgcn_perm(0u, r[j] << 8, 0x09030801u);       // (8, 9: the sign of bytes 1 and 3, eight times)
+      f[j + 8] = __builtin_amdgcn_perm(0u, r[j], 0x09030801u);
+    }
+  } else {
+    magnitude_planes_to_twos<16>(f);
+    transpose16x16_pairs(f);
+  }
+}
 
-// The common path.  False (uniform) when some code left the range: nothing is known then.
-template <bool IX, int OP>
-__device__ __forceinline__ bool extreme_packed(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
-                                      ExtremeBlock& out, u32& err) {
-  const u64 tend = tables_end(h.nb, IX);
-  const u32 seg = share.seg;
-  // operand s + 1 is on its way while operand s is decoded (as in sum_common)
+// The operands of a call without wide blocks one after the other: operand s + 1 is on its way while operand s is
+// decoded (as in sum_common).
+template <bool IX>
+struct OperandPipe {
   OperandMeta meta;
   OperandPlace next;
   OperandStage stage;
   i32 outlier_next;
-  {
+  OperandPlace cur;        // the operand whose payload is in the staging area
+  i32 first;               // ... and the first code of the lane's block there
+
+  __device__ __forceinline__ void open(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32& err) {
     const int lane = fresh_lane();
-    const u32 b = seg * kWaveBlocks + u32(lane);
+    const u32 b = share.seg * kWaveBlocks + u32(lane);
     const bool active = b < h.nb;
-    meta = load_operand_meta(a, 0, h, seg, b, active, share.live, IX);
+    meta = load_operand_meta(a, 0, h, share.seg, b, active, share.live, IX, opaque_zero());
     next = place_operand(meta, h, IX, err);
-    if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, share.live, IX);
-    stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
+    if (a.k > 1) meta = load_operand_meta(a, 1, h, share.seg, b, active, share.live, IX, opaque_zero());
+    stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tables_end(h.nb, IX)), next, lane);
     outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
   }
-
-  const i32 base = outlier_next;
-  // (codes of a block in range are then inside the format's limits as well: no check of the result is needed)
-  bool outside = base > kMaxCode - 2 * kCodeBias || base < 2 * kCodeBias - kMaxCode;
-  u32 acc[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) acc[j] = OP == ZC_OP_MAX ? 0u : 0x7fff7fffu;
-#pragma nounroll
-  for (int s = 0; s < a.k; ++s) {
+  // Operand s into the staging area.
+  __device__ __forceinline__ void take(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, int s, u32* wl, u32& err) {
+    // (where the next two operands are is asked for at once: one after the other, each behind a branch, these
+    // scalar loads are most of an operand's time in a call too small to fill the chip)
+    const StreamRef here = a.in[s], ahead1 = a.in[min(s + 1, a.k - 1)], ahead2 = a.in[min(s + 2, a.k - 1)];
+    const u64 tend = tables_end(h.nb, IX);
     const int lane = fresh_lane();
-    const u32 b = seg * kWaveBlocks + u32(lane);
+    const u32 b = share.seg * kWaveBlocks + u32(lane);
     const bool active = b < h.nb;
-    const OperandPlace cur = next;
-    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(a.in[s].base + tend), wl, lane);
+    cur = next;
+    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(here.base + tend), wl, lane);
     wave_lds_sync();
-    const u32 first = u32(outlier_next) - u32(base) + u32(kCodeBias);
-    outside |= first >= u32(2 * kCodeBias);
+    first = outlier_next;
     if (s + 1 < a.k) {
       next = place_operand(meta, h, IX, err);
-      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, share.live, IX);
-      stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
-      outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
+      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, ahead2, h, share.seg, b, active, share.live, IX, opaque_zero());
+      stage = load_operand_payload(reinterpret_cast<const u32*>(ahead1.base + tend), next, lane);
+      outlier_next = load_operand_outlier(ahead1.base, h, b, active, IX);
     }
-    if (cur.wcap == 0) {                       // nothing but constant blocks: every code is the block's first
-      const u32 both = first | (first << 16);
+  }
+};
+
+// The common path keeps codes as 16-bit code - base + bias, where base is the first code of one of the operands'
+// blocks and the codes must lie within kCodeReach of it: in [0, 2^15) for Max, in [-2^15, 0) for Min.
+constexpr i32 kCodeReach = 1 << 14;
+template <int OP>
+constexpr i32 kCodeBias = OP == ZC_OP_MAX ? kCodeReach : -kCodeReach;
+// An operand whose first code is within kNearFirst of the base is taken relative to the base in every lane of the
+// wave.  One that lies farther away in some lane is taken relative to its own first code (see fold_far_codes).
+constexpr i32 kNearFirst = 1 << 13;
+constexpr i32 kFirstLimit = i32(kMaxCode) - 2 * kCodeReach;
+
+// Folds an operand's codes f, which are relative to its own first code, into the extremes acc, whose base that first
+// code is `ahead` away from (positive: towards the extreme).  Whichever lies behind is shifted to the base of the
+// other.  A distance of more than 2^15 - 1 counts as that: what is shifted then ends at or behind the limit that the
+// other's codes do not pass, so the other's codes win, as they should.  No sum overflows: acc and f have the
+// same sign throughout (see kCodeReach), and a shift goes against it.
+template <int OP>
+__device__ inline void fold_far_codes(u32 (&acc)[16], const u32 (&f)[16], i32 ahead) {
+  const i32 shift = max(-0x7fff, min(ahead, 0x7fff));
+  const i32 toward = OP == ZC_OP_MAX ? shift : -shift;
+  const u32 acc_by = ahead > 0 ? u32(-toward) & 0xffffu : 0u, f_by = ahead > 0 ? 0u : u32(toward) & 0xffffu;
+  const u32 acc_pair = acc_by | (acc_by << 16), f_pair = f_by | (f_by << 16);
 #pragma unroll
-      for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(acc[j], both);
+  for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(add_pairs(acc[j], acc_pair), add_pairs(f[j], f_pair));
+}
+
+// The common path: the extremes of as many operands as it can take (returned, uniform).  If that is not all, the next
+// one is decoded: f = its codes modulo 2^16, `from` what the first of them starts from.
+template <bool IX, int OP>
+__device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+                                              OperandPipe<IX>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
+  base = pipe.outlier_next;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) acc[j] = OP == ZC_OP_MAX ? 0u : 0xffffffffu;
+#pragma nounroll
+  for (int s = 0; s < a.k; ++s) {
+    pipe.take(a, h, share, s, wl, err);
+    const i32 first = pipe.first;
+    // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits:
+    // no check of the result is needed)
+    bool outside = u32(first) + u32(kFirstLimit) > u32(2 * kFirstLimit);
+    const u32 apart = u32(first) - u32(base);
+    const bool near = !__any(apart + u32(kNearFirst) >= u32(2 * kNearFirst));      // uniform
+    const u32 start = ((near ? apart : 0u) + u32(kCodeBias<OP>)) & 0xffffu;
+    // f, word j: the deltas, and then the codes, j and j + 16
+    if (pipe.cur.wcap == 0) {                  // nothing but constant blocks: every code is the block's first
+      const u32 both = start | (start << 16);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) f[j] = both;
     } else {
-      u32 f[16];                               // word j: deltas j and j + 16, then the codes there
-      pick_operand_words(cur, wl, f);
-      if (!__any(cur.w > 7)) {                 // byte fields: word j = deltas j, j + 8, j + 16, j + 24
-        u32 r[8];
-#pragma unroll
-        for (int p = 0; p < 7; ++p) r[p] = f[p];
-        r[7] = f[15];
-        magnitude_planes_to_twos<8>(r);
-        transpose8x8_quads(r);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          f[j] = __builtin_amdgcn_perm(0u, r[j] << 8, 0x09030801u);       // (8, 9: the sign of bytes 1 and 3, eight times)
-          f[j + 8] = __builtin_amdgcn_perm(0u, r[j], 0x09030801u);
-        }
-      } else {
-        magnitude_planes_to_twos<16>(f);
-        transpose16x16_pairs(f);
-      }
+      operand_delta_pairs(pipe.cur, wl, f);
       // both halves of the block at once, the second one from zero; then it gets what the first one ends with
-      f[0] = add_pairs(f[0], first & 0xffffu);
+      f[0] = add_pairs(f[0], start);
 #pragma unroll
       for (int j = 1; j < 16; ++j) f[j] = add_pairs(f[j], f[j - 1]);
       const u32 half = f[15] << 16;
-      u32 seen = 0;
+      u32 seen = OP == ZC_OP_MAX ? 0u : ~0u;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         f[j] += half;                          // (the low field of `half` is zero: no carry between the fields)
-        seen |= f[j];
-        acc[j] = extreme_pairs<OP>(acc[j], f[j]);
+        seen = OP == ZC_OP_MAX ? seen | f[j] : seen & f[j];
       }
-      outside |= (seen & 0x80008000u) != 0;
+      outside |= ((OP == ZC_OP_MAX ? seen : ~seen) & 0x80008000u) != 0;
     }
     wave_lds_sync();
-    if (__any(outside)) return false;
+    if (__any(outside)) {
+      from = start;
+      return s;
+    }
+    if (near) {
+#pragma unroll
+      for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(acc[j], f[j]);
+    } else {
+      const i32 ahead = i32(OP == ZC_OP_MAX ? apart : 0u - apart);
+      fold_far_codes<OP>(acc, f, ahead);
+      if (ahead > 0) base = first;
+    }
   }
-  // the new deltas, in pairs; those of the second half's first value cross the halves
+  return a.k;
+}
+
+// The new deltas of packed extremes, in pairs; those of the second half's first value cross the halves.
+template <int OP>
+__device__ __forceinline__ void close_packed(const u32 (&acc)[16], i32 base, ExtremeBlock& out) {
   u32 top = 0, bottom = 0;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
@@ -170,8 +243,7 @@ __device__ __forceinline__ bool extreme_packed(const ReduceArgs& a, const Parsed
   }
   const i32 hi = max(i32(top) >> 16, i32(top << 16) >> 16), lo = min(i32(bottom) >> 16, i32(bottom << 16) >> 16);
   out.any = u32(max(hi, -lo));
-  out.outlier = base + i32(acc[0] & 0xffffu) - kCodeBias;
-  return true;
+  out.outlier = base + (i32(acc[0] << 16) >> 16) - kCodeBias<OP>;
 }
 
 // A segment whose payload is more than stage_to_lds brings in (all its blocks are wide then) comes in two parts,
@@ -194,73 +266,8 @@ __device__ inline OperandPlace operand_part(const OperandPlace& p, u32 part, int
   return q;
 }
 
-// Any codes and widths.
-template <bool IX, int OP>
-__device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
-                                   ExtremeBlock& out, u32& err) {
-  const ParsedHeader& h = c.h;
-  const u64 tend = tables_end(h.nb, IX);
-  i32 acc[32];
-#pragma unroll
-  for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
-  OperandMeta meta;
-  {
-    const u32 b = share.seg * kWaveBlocks + u32(fresh_lane());
-    meta = load_operand_meta(a, 0, h, share.seg, b, b < h.nb, share.live, IX);
-  }
-#pragma nounroll
-  for (int s = 0; s < a.k; ++s) {
-    const int lane = fresh_lane();
-    const u32 b = share.seg * kWaveBlocks + u32(lane);
-    const bool active = b < h.nb;
-    const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + tend);
-    const OperandPlace cur = place_operand(meta, h, IX, err, width_limit(c, s));
-    u32 code = u32(load_operand_outlier(a, s, h, b, active, IX));
-    if (!__any(cur.w > 15)) {
-      const OperandStage stage = load_operand_payload(payload, cur, lane);
-      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX);
-      stage_to_lds(stage, cur, payload, wl, lane);
-      wave_lds_sync();
-      u32 f[16];
-      pick_operand_words(cur, wl, f);
-      wave_lds_sync();
-      magnitude_planes_to_twos<16>(f);
-      transpose16x16_pairs(f);
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        code += u32(__builtin_amdgcn_sbfe(i32(f[j & 15]), u32(16 * (j >> 4)), 16u));
-        acc[j] = extreme<OP>(acc[j], i32(code));
-      }
-    } else {
-      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX);
-      u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
-#pragma unroll
-      for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
-#pragma nounroll
-      for (u32 part = 0; part < operand_parts(cur); ++part) {
-        const OperandPlace here = operand_part(cur, part, lane);
-        stage_to_lds(load_operand_payload(payload, here, lane), here, payload, wl, lane);
-        wave_lds_sync();
-        const u32* const mine = wl + (here.w ? here.pick : 0u);
-        const u32 keep = (1u << here.w) - 1u;  // bit p: the block has plane p
-#pragma unroll
-        for (int p = 0; p < 16; ++p) lo[p] |= mine[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
-#pragma unroll
-        for (int p = 0; p < 15; ++p) hi[p] |= mine[17 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(16 + p), 1u));
-        hi[15] |= here.w ? mine[0] : 0u;
-        wave_lds_sync();
-      }
-      transpose16x16_pairs(lo);
-      transpose16x16_pairs(hi);
-#pragma unroll
-      for (int j = 0; j < 32; ++j) {
-        const u32 f = j < 16 ? (lo[j & 15] & 0xffffu) | (hi[j & 15] << 16) : (lo[j & 15] >> 16) | (hi[j & 15] & 0xffff0000u);
-        code += u32(delta_from_field<32>(f));
-        acc[j] = extreme<OP>(acc[j], i32(code));
-      }
-    }
-  }
-  const bool active = share.seg * kWaveBlocks + u32(fresh_lane()) < h.nb;
+// The new deltas of extremes held in 32 bits.
+__device__ __forceinline__ void close_any(i32 (&acc)[32], bool active, ExtremeBlock& out, u32& err) {
   // range of the codes (operands of a valid stream are inside it, so is their extreme)
   i32 hi = acc[0], lo = acc[0];
 #pragma unroll
@@ -290,6 +297,119 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
   }
 }
 
+// The operands from s on, none of them with wide blocks, in 32 bits.  f: the deltas of operand s.
+template <bool IX, int OP>
+__device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+                                             OperandPipe<IX>& pipe, i32 (&acc)[32], u32 (&f)[16], int s, u32& err) {
+#pragma nounroll
+  for (;;) {
+    u32 code = u32(pipe.first);
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+      code += u32(__builtin_amdgcn_sbfe(i32(f[j & 15]), u32(16 * (j >> 4)), 16u));
+      acc[j] = extreme<OP>(acc[j], i32(code));
+    }
+    if (++s >= a.k) return;
+    pipe.take(a, h, share, s, wl, err);
+    operand_delta_pairs(pipe.cur, wl, f);
+    wave_lds_sync();
+  }
+}
+
+// Operands without wide blocks.  True: they are in `out` (the common path has taken them all), false: in acc.
+template <bool IX, int OP>
+__device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+                                               ExtremeBlock& out, i32 (&acc)[32], u32& err) {
+  OperandPipe<IX> pipe;
+  pipe.open(a, h, share, err);
+  u32 pairs[16], f[16], from = 0;
+  i32 base;
+  const int s = extreme_packed<IX, OP>(a, h, share, wl, pipe, pairs, f, from, base, err);
+  if (s == a.k) {
+    close_packed<OP>(pairs, base, out);
+    return true;
+  }
+  // its deltas again
+  from |= f[15] << 16;
+#pragma unroll
+  for (int j = 15; j >= 1; --j) f[j] = sub_pairs(f[j], f[j - 1]);
+  f[0] = sub_pairs(f[0], from);
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const i32 code = base + i32(i16x2_t(as_pair(pairs[j & 15]))[j >> 4]) - kCodeBias<OP>;
+    acc[j] = s ? code : OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
+  }
+  extreme_rest<IX, OP>(a, h, share, wl, pipe, acc, f, s, err);
+  return false;
+}
+
+// Any codes and widths.
+template <bool IX, int OP>
+__device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
+                                            i32 (&acc)[32], u32& err) {
+  const ParsedHeader& h = c.h;
+  const u64 tend = tables_end(h.nb, IX);
+#pragma unroll
+  for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
+  OperandMeta meta;
+  {
+    const u32 b = share.seg * kWaveBlocks + u32(fresh_lane());
+    meta = load_operand_meta(a, 0, h, share.seg, b, b < h.nb, share.live, IX, opaque_zero());
+  }
+#pragma nounroll
+  for (int s = 0; s < a.k; ++s) {
+    const int lane = fresh_lane();
+    const u32 b = share.seg * kWaveBlocks + u32(lane);
+    const bool active = b < h.nb;
+    const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + tend);
+    const OperandPlace cur = place_operand(meta, h, IX, err, width_limit(c, s));
+    u32 code = u32(load_operand_outlier(a, s, h, b, active, IX));
+    if (!__any(cur.w > 15)) {
+      const OperandStage stage = load_operand_payload(payload, cur, lane);
+      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX, opaque_zero());
+      stage_to_lds(stage, cur, payload, wl, lane);
+      wave_lds_sync();
+      u32 f[16];
+      pick_operand_words(cur, wl, f);
+      wave_lds_sync();
+      magnitude_planes_to_twos<16>(f);
+      transpose16x16_pairs(f);
+#pragma unroll
+      for (int j = 0; j < 32; ++j) {
+        code += u32(__builtin_amdgcn_sbfe(i32(f[j & 15]), u32(16 * (j >> 4)), 16u));
+        acc[j] = extreme<OP>(acc[j], i32(code));
+      }
+    } else {
+      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX, opaque_zero());
+      u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
+#pragma unroll
+      for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
+#pragma nounroll
+      for (u32 part = 0; part < operand_parts(cur); ++part) {
+        const OperandPlace here = operand_part(cur, part, lane);
+        stage_to_lds(load_operand_payload(payload, here, lane), here, payload, wl, lane);
+        wave_lds_sync();
+        const u32* const mine = wl + (here.w ? here.pick : 0u);
+        const u32 keep = (1u << here.w) - 1u;  // bit p: the block has plane p
+#pragma unroll
+        for (int p = 0; p < 16; ++p) lo[p] |= mine[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+#pragma unroll
+        for (int p = 0; p < 15; ++p) hi[p] |= mine[17 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(16 + p), 1u));
+        hi[15] |= here.w ? mine[0] : 0u;
+        wave_lds_sync();
+      }
+      transpose16x16_pairs(lo);
+      transpose16x16_pairs(hi);
+#pragma unroll
+      for (int j = 0; j < 32; ++j) {
+        const u32 f = j < 16 ? (lo[j & 15] & 0xffffu) | (hi[j & 15] << 16) : (lo[j & 15] >> 16) | (hi[j & 15] & 0xffff0000u);
+        code += u32(delta_from_field<32>(f));
+        acc[j] = extreme<OP>(acc[j], i32(code));
+      }
+    }
+  }
+}
+
 template <bool IX, int OP>
 __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
@@ -305,14 +425,17 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   const int wave = wave_id();
   const u64 tend = tables_end(h.nb, IX);
   u32* const wl = lds + wave * kWaveStage;
-  const u32 seg = tile * kTileWaves + u32(wave);
+  const u32 seg = uniform(tile * kTileWaves + u32(wave));
   const ReduceShare share{seg, seg < num_segments(h.nb)};
   u32 err = 0;
   if (IX && share.live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
 
   ExtremeBlock eb;
-  if (c.wide_streams || !extreme_packed<IX, OP>(a, h, share, wl, eb, err))
-    extreme_any<IX, OP>(a, c, share, wl, eb, err);
+  i32 codes[32];
+  bool closed = false;
+  if (c.wide_streams) extreme_any<IX, OP>(a, c, share, wl, codes, err);
+  else closed = extreme_narrow<IX, OP>(a, h, share, wl, eb, codes, err);
+  if (!closed) close_any(codes, share.seg * kWaveBlocks + u32(fresh_lane()) < h.nb, eb, err);
 
   const int lane = fresh_lane();
   const u32 b = seg * kWaveBlocks + u32(lane);

@@ -1562,3 +1562,45 @@ def test_reduce_some_wide_blocks(zcref, k, width, count):
         ref = zcref.reduce(streams) if op is None else zcref.reduce(streams, op=op)
         got = u.gpu_reduce(streams, n, op=op)
         assert got[0] == ref[0] == ZC_OK and got[1].tobytes() == ref[1].tobytes(), (op, u.first_diff(got[1], ref[1]))
+
+
+@pytest.mark.parametrize("seed", range(4))
+@pytest.mark.parametrize("k", [2, 3, 7])
+def test_extremes_of_operands_far_apart_and_at_the_edges_of_the_packed_codes(zcref, k, seed):
+    """Max and Min of operands without wide blocks.  Their common path holds codes in 16 bits: distances between the
+    operands' first codes on either side of every limit of that (2^13, 2^15, far beyond), codes just inside and just
+    outside the 2^14 that a block may span from its first code, at the ends of both halves of a block and at any
+    operand, segments of constant blocks only, of noise that no operand fits, and first codes at the limits of the
+    format."""
+    u = _u()
+    rng = np.random.default_rng(1000 * k + seed)
+    reach, top = 2 ** 14, 2 ** 30 - 1
+    nseg = 9
+    n = 2048 * nseg - 45
+    apart = np.array([0, 1, 8191, 8192, 8193, 16383, 16384, 32766, 32767, 32768, 49152, 65535, 65536, 10 ** 6, 2 ** 28])
+    streams = []
+    for s in range(k):
+        q = np.zeros((nseg, 64, 32), np.int64)
+        q += rng.integers(-2000, 2000, (nseg, 64, 1))
+        q[1:4] += (apart[rng.integers(0, apart.size, (3, 64))] * rng.choice([-1, 1], (3, 64)))[:, :, None]
+        q[2] += np.sort(rng.integers(0, 60000, (64, 1)), axis=0) * (s - 1)       # ranks at levels of their own
+        q[4] += 3 * 10 ** 6 * rng.integers(-1, 2, (64, 1))                       # constant blocks only
+        q[5] += (rng.choice([-1, 1]) * (top - 2 * reach - 2000 + rng.integers(-3, 4, (64, 1))))
+        q[6] += 9000 * s
+        q[[0, 1, 2, 3, 5, 6, 7], :, 1:] += rng.integers(-40, 41, (7, 64, 31))
+        for seg in (0, 1, 3, 7):                                 # codes at the reach, inside it throughout or not
+            for b in rng.choice(64, 12, replace=False):
+                j = rng.choice([1, 7, 15, 16, 17, 31])
+                over = 0 if seg != 7 or s != k - 1 else 1        # segment 7: out of reach at the last operand
+                q[seg, b, j] = q[seg, b, 0] + (reach - 1 + over if rng.integers(2) else -reach - over)
+        q[8] += rng.integers(-16000, 16001, (64, 32))            # nothing fits
+        if s == 1:
+            q[6, 5, 16] = q[6, 5, 0] + reach                     # ... and one at the second, behind it in reach again
+        q = np.clip(q.ravel()[:n], -top, top)
+        st, stream, _ = zcref.encode_codes(q.astype(np.int32), 1e-6)
+        assert st == ZC_OK and u.widths_of(stream, (n + 31) // 32).max() <= 15
+        streams.append(stream)
+    for op in (1, 2):
+        ref = zcref.reduce(streams, op=op)
+        got = u.gpu_reduce(streams, n, op=op)
+        assert got[0] == ref[0] == ZC_OK and got[1].tobytes() == ref[1].tobytes(), (op, u.first_diff(got[1], ref[1]))
