@@ -102,8 +102,11 @@ struct WavePayload {
 
 // First half of wave_block_words: scan of the widths, the checks, and the staged copy of the
 // segment's payload into `wl` if it has at most 64 x 16 words (with no block wider than 15 bits it has not more).
+// stage_wide: the caller uses the copy of a segment that has wider blocks, too; if not, such a segment of a plain stream,
+// whose widths are known ahead of the copy, is not copied.
 __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload_words, u32 w, u64 seg_off, u32* wl, int lane,
-                                                 bool ix, u32 seg_words, bool may_be_wide, u32& err, const uint4* safe) {
+                                                 bool ix, u32 seg_words, bool may_be_wide, u32& err, const uint4* safe,
+                                                 bool stage_wide) {
   const u32 mis = u32(seg_off) & 3u;
   const u64 src0 = seg_off - mis;                      // in words, multiple of 4
   WaveStage st;
@@ -132,7 +135,7 @@ __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload
     err |= status_bit(ZC_ERR_FORMAT);
     wp.inside = false;
   }
-  wp.staged = wp.inside && wave_total <= 64u * 16u;
+  wp.staged = wp.inside && wave_total <= 64u * 16u && (stage_wide || wp.wmax <= 15);
   if (wp.staged && !ix) {
     span = mis + wave_total;
     st = load_wave_stage(payload, payload_words, src0, span, lane, safe);
@@ -166,7 +169,8 @@ __device__ inline void pick_block_words(const WavePayload& wp, u64 seg_off, cons
 __device__ inline u32 wave_block_words(const u32* payload, u64 payload_words, u32 w, u64 seg_off, u32* wl, int lane,
                                        u32 (&lo)[16], u32 (&hi)[16], bool ix, u32 seg_words, bool may_be_wide,
                                        u32& err, const uint4* safe) {
-  const WavePayload wp = stage_wave_payload(payload, payload_words, w, seg_off, wl, lane, ix, seg_words, may_be_wide, err, safe);
+  const WavePayload wp = stage_wave_payload(payload, payload_words, w, seg_off, wl, lane, ix, seg_words, may_be_wide, err, safe,
+                                            false);
   if (wp.wmax <= 15) {
     pick_block_words(wp, seg_off, wl, lo);
   } else {

@@ -456,7 +456,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   u32 err = 0;
   const u64 seg_off = IX ? u64(uniform(seg_parts.seg)) : segment_offset(seg_parts);
   const WavePayload wp = stage_wave_payload(payload_in, (h.total - tend) / 4, w, seg_off, wl, lane, IX,
-                                            uniform(seg_end) - u32(seg_off), h.wide, err, reinterpret_cast<const uint4*>(a.in.base));
+                                            uniform(seg_end) - u32(seg_off), h.wide, err, reinterpret_cast<const uint4*>(a.in.base), true);
   if (IX && seg_live && !index_ends_ok(h, seg, u32(seg_off), uniform(seg_end))) err |= status_bit(ZC_ERR_FORMAT);
 
   CompressArgs qa;               // the quantiser's constants, from the stream's own bound
