@@ -1,0 +1,106 @@
+// The host side of zc_report.h: the places in pinned memory through which a synchronous call gets its result
+// words, and the wait for them.
+#pragma once
+
+#include <hip/hip_runtime_api.h>
+
+#include <atomic>
+#include <chrono>
+#include <cstdint>
+#include <mutex>
+
+#include "../../include/zc.h"
+
+namespace zc {
+
+constexpr int kReportWords = 4 + ZC_MAX_K;      // status, tag and size of a call (or the four quality sums), and k values of n
+
+// A request's place in pinned memory.
+struct ReportSlot {
+  uint64_t seq;                     // the request whose words these are
+  uint64_t words[kReportWords];
+};
+
+// The slots: a fixed number of them, taken for the length of one request and given back, so that threads and
+// streams never share one.  Pinned when the first is asked for, and until the process ends.
+class ReportSlots {
+ public:
+  // Null when all are taken or there is no pinned memory (`make`: pin it now if that has not been done yet).
+  ReportSlot* take(bool make) {
+    std::lock_guard<std::mutex> g(mu_);
+    if (!slots_) {
+      if (!make || refused_) return nullptr;
+      void* p = nullptr;
+      if (hipHostMalloc(&p, sizeof(ReportSlot) * kSlots, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        refused_ = true;
+        return nullptr;
+      }
+      slots_ = static_cast<ReportSlot*>(p);
+      for (int i = 0; i < kSlots; ++i) slots_[i].seq = 0;
+    }
+    for (int i = 0; i < kSlots; ++i) {
+      if (taken_ & (uint64_t(1) << i)) continue;
+      taken_ |= uint64_t(1) << i;
+      return slots_ + i;
+    }
+    return nullptr;
+  }
+  void give_back(ReportSlot* s) {
+    std::lock_guard<std::mutex> g(mu_);
+    taken_ &= ~(uint64_t(1) << (s - slots_));
+  }
+  uint64_t next_seq() { return seq_.fetch_add(1, std::memory_order_relaxed) + 1; }
+
+ private:
+  static constexpr int kSlots = 32;
+  std::mutex mu_;
+  ReportSlot* slots_ = nullptr;
+  uint64_t taken_ = 0;
+  bool refused_ = false;
+  std::atomic<uint64_t> seq_{0};
+};
+
+// The words at from[0 .. count) as they are when everything enqueued on `stream` so far has run.  `make`: see take.
+// launch(slot, seq): enqueues on `stream` what stores the words, and then seq, in the slot; false: nothing was enqueued.
+template <typename LaunchFn>
+inline bool report_words(ReportSlots& slots, const uint64_t* const* from, uint32_t count, uint64_t* to, bool make, hipStream_t stream,
+                         LaunchFn launch) {
+  // A stream that is being captured runs nothing, so there is no answer to wait for: the wait for the stream says so (and
+  // ends the capture, as it does in any synchronous call).
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(stream, &capture) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  if (known && capture != hipStreamCaptureStatusNone) {
+    (void)hipStreamSynchronize(stream);
+    return false;
+  }
+  ReportSlot* const slot = known ? slots.take(make) : nullptr;
+  if (!slot) {
+    for (uint32_t i = 0, run; i < count; i += run) {
+      for (run = 1; i + run < count && from[i + run] == from[i] + run;) ++run;
+      if (hipMemcpyAsync(to + i, from[i], run * sizeof(uint64_t), hipMemcpyDeviceToHost, stream) != hipSuccess) return false;
+    }
+    return hipStreamSynchronize(stream) == hipSuccess;
+  }
+  const uint64_t seq = slots.next_seq();
+  if (!launch(slot, seq)) {
+    slots.give_back(slot);
+    return false;
+  }
+  // Polled for the length of a large call, then left to the runtime, which also knows when no answer can come.
+  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(500);
+  auto answered = [&] { return __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq; };
+  bool there = false;
+  for (uint32_t polls = 1; !(there = answered()); ++polls) {
+    __builtin_ia32_pause();
+    if ((polls & 63u) == 0 && std::chrono::steady_clock::now() > until) break;
+  }
+  if (!there) there = hipStreamSynchronize(stream) == hipSuccess && answered();
+  if (!there) return false;      // (with its slot: what was enqueued may still write there, if the GPU comes to it)
+  for (uint32_t i = 0; i < count; ++i) to[i] = __atomic_load_n(&slot->words[i], __ATOMIC_RELAXED);
+  slots.give_back(slot);
+  return true;
+}
+
+}  // namespace zc

@@ -8,7 +8,7 @@ import torch
 import gpuutil
 from gpuutil import zc
 from paper_2502_18554_amd import synth
-from paper_2502_18554_amd.binding import (ZC_ERR_ARG, ZC_ERR_BOUND, ZC_ERR_CAPACITY, ZC_ERR_FORMAT,
+from paper_2502_18554_amd.binding import (ZC_ERR_ARG, ZC_ERR_BOUND, ZC_ERR_CAPACITY, ZC_ERR_FORMAT, ZC_ERR_HIP,
                                            ZC_ERR_MISMATCH, ZC_ERR_NONFINITE, ZC_ERR_RANGE, ZC_OK)
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("stream_variant")]
@@ -1227,6 +1227,30 @@ def test_synchronous_calls_from_many_threads(zcref):
     torch.cuda.synchronize()
     for d_x, ref, ws, d_out, stream in jobs:
         assert d_out[:ref.size].cpu().numpy().tobytes() == ref.tobytes()
+
+
+def test_synchronous_calls_on_a_stream_that_is_being_captured(zcref):
+    """They cannot wait for their result there: each ends with ZC_ERR_HIP (and ends the capture), and calls on other
+    streams are as good as any.  (The streams are the test's own: the runtime leaves them unusable.)"""
+    import ctypes
+    import types
+    u = _u()
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))
+    x = np.cumsum(np.random.default_rng(7).normal(0, 0.01, 5000)).astype(np.float32)
+    ref = zcref.compress(x, 1e-3)[1]
+    d_x, ws = u.to_dev(x), u.workspace(x.size)
+    d_out = torch.zeros(zc.zc_compress_bound(x.size), dtype=torch.uint8, device=u.DEV)
+    for call in (lambda s: zc.zc_compress(d_x, x.size, 1e-3, d_out, ws, stream=s), lambda s: zc.zc_finish(ws, stream=s)):
+        handle, graph = ctypes.c_void_p(), ctypes.c_void_p()
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(handle), 1) == 0
+        torch.cuda.synchronize()
+        assert hip.hipStreamBeginCapture(handle, 1) == 0           # (thread-local: other threads are not concerned)
+        st, _ = call(types.SimpleNamespace(cuda_stream=handle.value))
+        assert st == ZC_ERR_HIP
+        assert hip.hipStreamEndCapture(handle, ctypes.byref(graph)) != 0 and not graph.value
+        hip.hipGetLastError()
+        st, total = zc.zc_compress(d_x, x.size, 1e-3, d_out, ws)
+        assert st == ZC_OK and d_out[:total].cpu().numpy().tobytes() == ref.tobytes()
 
 
 @pytest.mark.parametrize("short_by", ["all", "more than an index span"])

@@ -146,6 +146,18 @@ def test_bit_matrix_transposes_match_packbits(bm, cls, maxw):
         assert np.array_equal(d2, d), "a zero with its sign set is a zero"
 
 
+def test_answers_of_synchronous_calls(tmp_path):
+    """The places through which synchronous calls get their result words, with the runtime's calls replaced: none is lost
+    by a launch that fails or by a call on a stream that is being captured, and whoever gets none goes by copies."""
+    src = os.path.join(ROOT, "tests", "host", "report_host.cpp")
+    exe = str(tmp_path / "report_host")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(rocm, "include"), src, "-o", exe],
+                   check=True)
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0, run.stdout
+
+
 def test_calls_from_two_threads_share_no_setting(libzc):
     """The library keeps no settings: two host threads that want different stream variants and tile
     hand-outs say so in their calls and never see each other's choice.  (Without a GPU only the
