@@ -5,7 +5,9 @@
  * caller owns inputs, outputs and the workspace.  (What lives between calls: the optional kernel
  * timer of zc_profile_enable, a measurement aid, and 32 places of 552 bytes in pinned host memory
  * through which synchronous calls, zc_finish and zc_quality get their result words, made by the
- * first of them and held until the process ends; a call that finds them all taken goes without.)
+ * first of them that is given the memory and held until the process ends.  A call that finds
+ * them all taken, or none made, goes without, by staged copies.  A place is lost only with an
+ * answer that never comes, i.e. when the GPU has failed.)
  *
  * Method: ZCCL, arXiv 2502.18554.  fZ-light is described in Section 3.3 (block partition,
  * fused quantisation + 1D Lorenzo prediction, first value kept as a 4-byte outlier, sign

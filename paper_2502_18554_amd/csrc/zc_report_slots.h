@@ -22,18 +22,19 @@ struct ReportSlot {
 };
 
 // The slots: a fixed number of them, taken for the length of one request and given back, so that threads and
-// streams never share one.  Pinned when the first is asked for, and until the process ends.
+// streams never share one.  Pinned when the first is asked for, and until the process ends.  Where that is refused (no
+// memory to be had at the moment, another thread capturing a graph in the mode that forbids allocations to all) the
+// request goes without and a later one asks again.
 class ReportSlots {
  public:
   // Null when all are taken or there is no pinned memory (`make`: pin it now if that has not been done yet).
   ReportSlot* take(bool make) {
     std::lock_guard<std::mutex> g(mu_);
     if (!slots_) {
-      if (!make || refused_) return nullptr;
+      if (!make) return nullptr;
       void* p = nullptr;
       if (hipHostMalloc(&p, sizeof(ReportSlot) * kSlots, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
         (void)hipGetLastError();
-        refused_ = true;
         return nullptr;
       }
       slots_ = static_cast<ReportSlot*>(p);
@@ -57,7 +58,6 @@ class ReportSlots {
   std::mutex mu_;
   ReportSlot* slots_ = nullptr;
   uint64_t taken_ = 0;
-  bool refused_ = false;
   std::atomic<uint64_t> seq_{0};
 };
 

@@ -88,6 +88,18 @@ int main() {
     slots.give_back(held[7]);
     CHECK(answered(slots));
   }
+  std::printf("pinned memory that was refused is asked for again\n");
+  {
+    zc::ReportSlots slots;
+    pins_to_refuse = 3;
+    const int before = launches;
+    for (int i = 0; i < 3; ++i) {
+      std::memset(to, 0, sizeof(to));
+      CHECK(zc::report_words(slots, from, 5, to, true, nullptr, runs) && to[0] == 11 && to[3] == 55);
+    }
+    CHECK(launches == before && pins_to_refuse == 0);
+    CHECK(answered(slots));
+  }
   std::printf("a caller who rules out allocations gets none\n");
   {
     zc::ReportSlots slots;
