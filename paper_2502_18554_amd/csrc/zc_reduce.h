@@ -502,10 +502,10 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
       }
       meta.payload_room = payload_room(a.in[0].bytes, h, IX);
     } else {
-      meta = load_operand_meta(a, 0, h, seg, b, active, seg_live, IX);
+      meta = load_operand_meta(a, 0, h, seg, b, active, seg_live, IX, opaque_zero());
     }
     next = place_operand(meta, h, IX, err, w_max);
-    if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, seg_live, IX);
+    if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, seg_live, IX, opaque_zero());
     stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
     outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
   }
@@ -528,7 +528,7 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
     outlier += i64(outlier_next);
     if (s + 1 < a.k) {
       next = place_operand(meta, h, IX, err, w_max);
-      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, seg_live, IX);
+      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, seg_live, IX, opaque_zero());
       stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
       outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
     }
@@ -794,7 +794,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
 
 // One launch per call, whatever the widths (plain streams: behind the two of zc_scan.h, and with a workgroup less
 // per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
-// but wide blocks, 4 x 4 194 301 values, 47 us with six and 43 with five; narrow ones, 8 x 2^24, 60.1 and 61.7.
+// but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
 template <bool IX>
 __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
@@ -812,11 +812,16 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   const bool early = !a.ticketed && (!IX || a.n_part != 0);
   u32 tile = 0, ntiles = 0;
   if (!open_reduce<IX>(a, c, meta, early, tile, ntiles, &sh_tile)) return;
+  // The segment number stays a scalar: in a vector register, with all the addresses that follow from it, it made the
+  // kernel spill in the operand loops.  (Plain streams of nothing but wide blocks, 4 x 4 194 301 values: 43.7 us, now
+  // 41.0; 16 x 100 003 hard values 33.6 and 32.2; 8 x 2^24 smooth ones 53.6 and 52.9.)  What the waves ask for two
+  // operands ahead is still asked for by vector loads (opaque_zero): scalar ones share their counter with the LDS reads.
+  tile = uniform(tile);
   // A tile leaves the common path only if one of its waves has to.  (A call with a block wider than 15 bits in
-  // some operand used to send every tile through reduce_wide_tile: 8 x 2^24 values of hard data 84 us, now 51;
-  // 4 x 4 194 301, two tiles per compute unit, 24.2 -> 18.9.  Calls without wide blocks,
-  // 8 x 2^26: 158.8 -> 159.9; with the mixed case as a function of its own, or as a second instance of the common
-  // path, they lost 2 and 4 % to another register allocation.)
+  // some operand used to send every tile through reduce_wide_tile: 8 x 2^24 values of hard data 84 us, now 50;
+  // 4 x 4 194 301, two tiles per compute unit, 24.2 -> 18.1.  Calls without wide blocks, 8 x 2^26: 159.5 and
+  // 158.8; with the mixed case as a function of its own, or as a second instance of the common path, they lost 2 and
+  // 4 % to another register allocation.)
   bool common = true;
   if (c.wide_streams) {                // (the same in every wave)
     const bool fits = fits_common_path(a, c, tile * kTileWaves + u32(wave_id()), IX);
