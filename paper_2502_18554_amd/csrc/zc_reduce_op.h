@@ -10,11 +10,11 @@
 // What bounds it is arithmetic, and the registers that the running extremes occupy.  So the common
 // path never unpacks the codes: the transposes leave a block's deltas as 16 words of two 16-bit
 // fields, and chain, extreme and new deltas work on those words with packed 16-bit instructions,
-// two values at a time, 16 registers for the extremes of a block.  For that an operand's codes are
+// two values at a time, 16 registers for the extremes of a block.  For that a block's codes are
 // taken relative to the lane's base (the first code of its block in the first operand), or to
-// the operand's own first code where that is 2^13 or more away from the base: of two blocks that
+// their own first code where that is 2^13 or more away from the base: of two blocks that
 // far apart the one behind is shifted to the base of the other, and what leaves 16 bits by that has lost
-// (fold_far_codes).  Relative to whichever it is the codes have to stay within [0, 2^15) or
+// (meet_far_codes).  Relative to whichever it is the codes have to stay within [0, 2^15) or
 // [-2^15, 0), which the sign bits of the fields show: a delta is below 2^15 in magnitude, so a
 // chain cannot leave that range and be back in it within one step.  A wave that meets a block with
 // a code 16384 or more away from its first (or a code near the limits of the format) goes on from
@@ -22,13 +22,14 @@
 // than 15 bits does so from the start, in all its waves (extreme_any).
 // Measured, 8 x 2^24 values unless said otherwise, first with codes unpacked throughout (145 registers, three waves
 // per SIMD, and a kernel of its own for wide blocks, launched with every call), then now:
-//   smooth field, bound 1e-4 of its range                     79.5   65.5 us
-//   the same at 1e-5 (first codes and excursions beyond 2^13) 90     82
+//   smooth field, bound 1e-4 of its range                     79.5   64.4 us
+//   the same at 1e-5 (first codes and excursions beyond 2^13) 90     83
 //   1e-4, each rank at a level of its own                     86     77
-//   white noise over 32000 codes (nothing fits 16 bits)       109    102
-//   16 x 2^20 at 1e-5                                         36.5   34.3
-//   hard data, 4 x 4 194 301                                  28.2   20.9
-//   2 x 20 000                                                11.7   9.1
+//   white noise over 32000 codes (nothing fits 16 bits)       109    101
+//   16 x 2^20 at 1e-5                                         36.5   34.7
+//   64 x 100 003 at 2e-4                                      109    111.5
+//   hard data, 4 x 4 194 301                                  28.2   21.0
+//   2 x 20 000                                                11.7   9.2
 // (Starting over in 32 bits instead of going on there, without the next operand on its way, the second to fifth took 107,
 // 101, 120 and 43.5.)  128 registers, four waves per SIMD, and 52 bytes of scratch (68 on plain streams) that only the
 // wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
@@ -117,8 +118,13 @@ struct OperandPipe {
   i32 outlier_next;
   OperandPlace cur;        // the operand whose payload is in the staging area
   i32 first;               // ... and the first code of the lane's block there
+  // Where operands s, s + 1 and s + 2 are, asked for a step before it is needed.
+  StreamRef at0, at1, at2;
 
   __device__ __forceinline__ void open(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32& err) {
+    at0 = a.in[0];
+    at1 = a.in[min(1, a.k - 1)];
+    at2 = a.in[min(2, a.k - 1)];
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
     const bool active = b < h.nb;
@@ -130,9 +136,10 @@ struct OperandPipe {
   }
   // Operand s into the staging area.
   __device__ __forceinline__ void take(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, int s, u32* wl, u32& err) {
-    // (where the next two operands are is asked for at once: one after the other, each behind a branch, these
-    // scalar loads are most of an operand's time in a call too small to fill the chip)
-    const StreamRef here = a.in[s], ahead1 = a.in[min(s + 1, a.k - 1)], ahead2 = a.in[min(s + 2, a.k - 1)];
+    const StreamRef here = at0, ahead1 = at1, ahead2 = at2;
+    at0 = at1;
+    at1 = at2;
+    at2 = a.in[min(s + 3, a.k - 1)];
     const u64 tend = tables_end(h.nb, IX);
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
@@ -155,24 +162,27 @@ struct OperandPipe {
 constexpr i32 kCodeReach = 1 << 14;
 template <int OP>
 constexpr i32 kCodeBias = OP == ZC_OP_MAX ? kCodeReach : -kCodeReach;
-// An operand whose first code is within kNearFirst of the base is taken relative to the base in every lane of the
-// wave.  One that lies farther away in some lane is taken relative to its own first code (see fold_far_codes).
+// A block whose first code is within kNearFirst of the base is taken relative to the base, one that lies farther away
+// relative to its own first code (see meet_far_codes).
 constexpr i32 kNearFirst = 1 << 13;
 constexpr i32 kFirstLimit = i32(kMaxCode) - 2 * kCodeReach;
 
-// Folds an operand's codes f, which are relative to its own first code, into the extremes acc, whose base that first
-// code is `ahead` away from (positive: towards the extreme).  Whichever lies behind is shifted to the base of the
-// other.  A distance of more than 2^15 - 1 counts as that: what is shifted then ends at or behind the limit that the
-// other's codes do not pass, so the other's codes win, as they should.  No sum overflows: acc and f have the
-// same sign throughout (see kCodeReach), and a shift goes against it.
+// Brings the extremes acc and an operand's codes f to one base, where f's is `ahead` of acc's (positive: towards the
+// extreme): whichever lies behind is shifted to the base of the other.  A distance of more than 2^15 - 1 counts as
+// that: what is shifted then ends at or behind the limit that the other's codes do not pass, so the other's codes win,
+// as they should.  No sum overflows: acc and f have the same sign throughout (see kCodeReach), and a shift goes
+// against it.
 template <int OP>
-__device__ inline void fold_far_codes(u32 (&acc)[16], const u32 (&f)[16], i32 ahead) {
+__device__ inline void meet_far_codes(u32 (&acc)[16], u32 (&f)[16], i32 ahead) {
   const i32 shift = max(-0x7fff, min(ahead, 0x7fff));
   const i32 toward = OP == ZC_OP_MAX ? shift : -shift;
   const u32 acc_by = ahead > 0 ? u32(-toward) & 0xffffu : 0u, f_by = ahead > 0 ? 0u : u32(toward) & 0xffffu;
   const u32 acc_pair = acc_by | (acc_by << 16), f_pair = f_by | (f_by << 16);
 #pragma unroll
-  for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(add_pairs(acc[j], acc_pair), add_pairs(f[j], f_pair));
+  for (int j = 0; j < 16; ++j) {
+    acc[j] = add_pairs(acc[j], acc_pair);
+    f[j] = add_pairs(f[j], f_pair);
+  }
 }
 
 // The common path: the extremes of as many operands as it can take (returned, uniform).  If that is not all, the next
@@ -181,18 +191,22 @@ template <bool IX, int OP>
 __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
                                               OperandPipe<IX>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
   base = pipe.outlier_next;
+  // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits: no
+  // check of the result is needed)
+  bool outside = u32(base) + u32(kFirstLimit) > u32(2 * kFirstLimit);
 #pragma unroll
   for (int j = 0; j < 16; ++j) acc[j] = OP == ZC_OP_MAX ? 0u : 0xffffffffu;
+  // The loop has one exit, told in a scalar that the compiler cannot see through, and one place where acc changes: with
+  // an exit from its middle the two exits are merged and acc is copied in every round (8 x 2^24 values 64.9 -> 64.4 us,
+  // 64 x 100 003, a chain of round trips, 115 -> 111.5).
+  int s = 0;
+  u32 going = 1;
 #pragma nounroll
-  for (int s = 0; s < a.k; ++s) {
+  while (going) {
     pipe.take(a, h, share, s, wl, err);
-    const i32 first = pipe.first;
-    // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits:
-    // no check of the result is needed)
-    bool outside = u32(first) + u32(kFirstLimit) > u32(2 * kFirstLimit);
-    const u32 apart = u32(first) - u32(base);
-    const bool near = !__any(apart + u32(kNearFirst) >= u32(2 * kNearFirst));      // uniform
-    const u32 start = ((near ? apart : 0u) + u32(kCodeBias<OP>)) & 0xffffu;
+    const u32 apart = u32(pipe.first) - u32(base);
+    const bool far = apart + u32(kNearFirst) >= u32(2 * kNearFirst);
+    const u32 start = ((far ? 0u : apart) + u32(kCodeBias<OP>)) & 0xffffu;
     // f, word j: the deltas, and then the codes, j and j + 16
     if (pipe.cur.wcap == 0) {                  // nothing but constant blocks: every code is the block's first
       const u32 both = start | (start << 16);
@@ -214,20 +228,25 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ParsedH
       outside |= ((OP == ZC_OP_MAX ? seen : ~seen) & 0x80008000u) != 0;
     }
     wave_lds_sync();
-    if (__any(outside)) {
-      from = start;
-      return s;
+    bool stop = false;
+    if (__any(outside || far)) {               // (one vote, one branch: in a small call these are time, too)
+      outside |= far && u32(pipe.first) + u32(kFirstLimit) > u32(2 * kFirstLimit);
+      stop = __any(outside);
+      if (!stop) {
+        const i32 ahead = far ? i32(OP == ZC_OP_MAX ? apart : 0u - apart) : 0;
+        meet_far_codes<OP>(acc, f, ahead);
+        if (ahead > 0) base = pipe.first;
+      }
     }
-    if (near) {
+    from = start;
+    if (!stop) {
 #pragma unroll
       for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(acc[j], f[j]);
-    } else {
-      const i32 ahead = i32(OP == ZC_OP_MAX ? apart : 0u - apart);
-      fold_far_codes<OP>(acc, f, ahead);
-      if (ahead > 0) base = first;
+      ++s;
     }
+    going = uniform(!stop && s < a.k ? 1u : 0u);
   }
-  return a.k;
+  return s;
 }
 
 // The new deltas of packed extremes, in pairs; those of the second half's first value cross the halves.
