@@ -82,13 +82,19 @@ __device__ inline i32 quantize_value(float x, const CompressArgs& a, u32& err) {
   return quantize_fast(x, a);
 }
 
+// FRESH: checked values are taken in a way that the compiler does not recognise.  Or the 32 compares of a wave's checked
+// values are made ahead of the branch, for every wave, and their results, 64 scalar registers, push others out into
+// vector registers.
+template <bool FRESH>
 __device__ inline int4 quantize4(const float4& x, const CompressArgs& a, bool checked, u32& err) {
   int4 q;
   if (__builtin_expect(checked, 0)) {
-    q.x = quantize_value(x.x, a, err);
-    q.y = quantize_value(x.y, a, err);
-    q.z = quantize_value(x.z, a, err);
-    q.w = quantize_value(x.w, a, err);
+    float4 y = x;
+    if (FRESH) asm volatile("" : "+v"(y.x), "+v"(y.y), "+v"(y.z), "+v"(y.w));
+    q.x = quantize_value(y.x, a, err);
+    q.y = quantize_value(y.y, a, err);
+    q.z = quantize_value(y.z, a, err);
+    q.w = quantize_value(y.w, a, err);
   } else {
     q.x = quantize_fast(x.x, a);
     q.y = quantize_fast(x.y, a);
@@ -126,6 +132,10 @@ __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u3
 
 // Quantise the wave's values where they landed and transpose the codes through LDS so that one
 // lane owns one block: q[j] = code j of the lane's block.  have: see share_values.
+// (quantize4 for fresh values in both halves: 27 scalar registers pushed out with tiles by ticket, 18 without, but then with
+// 20 bytes of scratch set aside, which zc_compress_noalloc is not to need; in the second half: 52 and 48; in none: 95 and
+// 92.  2^26 values by ticket 80.7 us with none, 80.0, 78.1 with both; without tickets 66.8, 65.6, 65.2.)
+template <bool TICKETS>
 __device__ __forceinline__ void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                    i32 (&q)[32], u32& err) {
   // Some value of this wave outside the screened domain: the checked arithmetic for all of it.
@@ -145,9 +155,10 @@ __device__ __forceinline__ void block_codes(const CompressArgs& a, const float4 
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<int4*>(wl + (8 * i + (lane >> 3)) * kStageRow + 4 * (lane & 7)) =
-          quantize4(x[4 * half + i], a, checked, err);
+    for (int i = 0; i < 4; ++i) {
+      int4* const at = reinterpret_cast<int4*>(wl + (8 * i + (lane >> 3)) * kStageRow + 4 * (lane & 7));
+      *at = half || TICKETS ? quantize4<true>(x[4 * half + i], a, checked, err) : quantize4<false>(x[4 * half + i], a, checked, err);
+    }
     wave_lds_sync();
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -192,10 +203,11 @@ struct BlockFields {
   i32 outlier;
 };
 
+template <bool TICKETS>
 __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                     BlockFields& bf, u32& err) {
   i32 q[32];
-  block_codes(a, x, wblock0, have, lane, wl, q, err);
+  block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, err);
   bf.outlier = q[0];
   i32 top = 0, bottom = 0;              // largest and smallest delta (d0 = 0 is one of them)
 #pragma unroll
@@ -219,6 +231,7 @@ __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8],
 // of the hard-data configuration 2 % of the waves, but 16 % of the tiles, hold such a block.  (A tile with one
 // used to store its blocks two at a time, a plane word being the ballot of one bit of 32 lanes; 2^28 hard
 // values, compressed and decompressed: 680 -> 464 us.)
+template <bool TICKETS>
 __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const PayloadSink& sink, const Placement& pl, u64 base,
                                                 u64 wblock0, u32 have, int lane, u32* wl) {
   asm volatile("" : "+v"(lane));               // (or the compiler keeps what it has loaded and quantised before, in scratch)
@@ -227,7 +240,7 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
     float4 x[8];
     u32 ignored = 0;                           // errors were raised on the first pass
     load_raw(a, wblock0, lane, have, x);
-    block_codes(a, x, wblock0, have, lane, wl, q, ignored);
+    block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, ignored);
   }
 #pragma unroll
   for (int j = 31; j >= 1; --j) q[j] -= q[j - 1];
@@ -298,7 +311,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     }
 
     BlockFields bf;
-    block_fields(a, x, wblock0, have, lane, wl, bf, err);
+    block_fields<TICKETS>(a, x, wblock0, have, lane, wl, bf, err);
     Placement pl;
     pl.w = (active && bf.any) ? 32u - u32(__builtin_clz(bf.any)) : 0u;
     pl.wmax = wave_max_u32(pl.w);
@@ -341,7 +354,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     });
     if (lane == 0) write_index_entry(sink, tile * u32(kPackWaves) + u32(wave), tb.words + pl.wave_off);
     if (narrow) copy_staged_wave<16>(sink, pl, tb.words, wl, lane);
-    else store_wide_wave(a, sink, pl, tb.words, wblock0, have, lane, wl);
+    else store_wide_wave<TICKETS>(a, sink, pl, tb.words, wblock0, have, lane, wl);
     finish_stream(sink, pl, tile, ntiles, tb);
     if (active && tables_fit) {
       a.out[widths_begin(a.nb, a.ix) + b] = u8(pl.w);
