@@ -326,8 +326,8 @@ int zc_debug_block_offsets(const void* d_in, size_t in_bytes, uint32_t* d_off_wo
  * zc_decompress_average, zc_decompress_many, zc_reduce_compressed, zc_reduce_step and
  * zc_reduce_step_op (and their _ex forms) hand a pair of HIP events to the launch of their
  * main kernel on the call's stream (hipExtLaunchKernelGGL), which stamps them with that
- * kernel's start and end (the compress kernel over the full tiles, the decompress, reduce or
- * step kernel; not the small kernels that run ahead of it for plain streams).
+ * kernel's start and end (the compress, decompress, reduce or step kernel; not the small
+ * kernels that run ahead of it for plain streams, nor the one that reports a synchronous call's result).
  * zc_profile_collect waits for the recorded pairs, stores up to cap elapsed times in
  * milliseconds in ms[] and the matching ZC_KERNEL_* ids in kernel[] (host arrays, either may
  * be NULL) in call order, forgets them, and returns how many it stored (a negative status on

@@ -267,8 +267,9 @@ __device__ inline u64 uniform64(u64 v) { return u64(uniform(u32(v))) | (u64(unif
 // that no earlier launch on the same workspace has had: the packet number of the dispatch in
 // its hardware queue (which a replay of a captured graph renews as well), the queue, a number
 // the host draws per call (its clock), and the workspace address, mixed.  A call of several
-// launches (a stream produced in parts, the validation kernels of plain streams) uses the tag of its first launch throughout: that launch leaves it in the control
-// block, the later ones pick it up there (`adopt`).
+// launches (a stream produced in parts, the validation kernels of plain streams) uses the tag of its
+// first launch throughout: that launch leaves it in the control block, the later ones pick it up
+// there (`adopt`).
 // ---------------------------------------------------------------------------------------
 extern "C" __device__ u64 zc_dispatch_id(void) __asm("llvm.amdgcn.dispatch.id");
 

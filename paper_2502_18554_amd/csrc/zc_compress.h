@@ -230,7 +230,7 @@ __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8],
 // again, turns them into sign and plane words and stores those.  Only that wave does, and no tile waits for it:
 // of the hard-data configuration 2 % of the waves, but 16 % of the tiles, hold such a block.  (A tile with one
 // used to store its blocks two at a time, a plane word being the ballot of one bit of 32 lanes; 2^28 hard
-// values, compressed and decompressed: 680 -> 464 us.)
+// values, compressed and decompressed: 674 us, now 455.)
 template <bool TICKETS>
 __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const PayloadSink& sink, const Placement& pl, u64 base,
                                                 u64 wblock0, u32 have, int lane, u32* wl) {
@@ -260,9 +260,9 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
 // and nothing in the workspace needs clearing (see launch_tag).  A workgroup that knows its tile
 // from its id asks for its values before anything else, so that the scalar work that opens a call
 // (tag, table positions: some 150 dependent instructions) runs while they are on their way: 512^3 field
-// 122.4 -> 121.7 us.  The ragged end is a tile like any other (see load_raw); as a launch of its own behind
-// the full tiles it cost 7 us per call on any input that is not a multiple of 16384 values (20 000 003
-// values, compress and decompress: 59.1 -> 52.2 us).
+// 122.4 -> 121.7 us when that was done, 116.4 now.  The ragged end is a tile like any other (see
+// load_raw); as a launch of its own behind the full tiles it cost 7 us per call on any input that is not
+// a multiple of 16384 values (20 000 003 values, compress and decompress: 59.0 us, now 51.9).
 template <bool TICKETS>
 __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
   __shared__ __attribute__((aligned(16))) u32 lds[kPackWaves * kWaveStage];

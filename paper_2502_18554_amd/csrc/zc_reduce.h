@@ -796,6 +796,8 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
 // per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
 // but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
+// 80 registers and 24 bytes of scratch (plain streams: 96 and 68), which the common path touches behind its
+// operand loop only: what the placement needs waits there.
 template <bool IX>
 __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];   // also holds an operand's payload

@@ -158,7 +158,7 @@ __device__ inline void load_local(const float* local, u64 v0, u32 have, int lane
 // received stream repeats the last code of its last block, so the results there repeat the last result:
 // their deltas are the zeros that the stream's padding wants, and they change neither width nor screen.
 // (The whole wave used to take the other path, 25 us longer than all others, on every call whose size is
-// not a multiple of 2048: a synchronous round of 262 177 values took 59.5 us and takes 33.9 now.)
+// not a multiple of 2048: a synchronous round of 262 177 values took 59.4 us and takes 18.2 now.)
 __device__ inline void pad_local(const float* local, u64 v0, u64 n, u32 have, int lane, float4 (&x)[8]) {
   const u32 piece = have & ~3u;
   float t[4];
@@ -246,7 +246,7 @@ __device__ inline SlowInput load_slow_input(const StepArgs& a, const ParsedHeade
 // wave's payload, which starts at `to` and has room for `room` words.
 // (All 64 blocks of a wave used to go through here if one had to, 25 us per pass, in which a received block's words
 // were read one after the other; all tiles behind such a wave wait for it.  A round on 2^26 values of hard data,
-// where one wave in ten has such a block: 790 us, now 103.  Inlined as one lane per block in 32 bits, which is faster
+// where one wave in ten has such a block: 790 us, now 98.  Inlined as one lane per block in 32 bits, which is faster
 // for a wave of nothing but wide blocks, it cost every round 5 % in registers.)
 enum SlowPass { kMeasure, kStage, kStore };
 template <bool IX, int OP, SlowPass PASS>

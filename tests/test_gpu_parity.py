@@ -1610,6 +1610,7 @@ def test_extremes_of_operands_far_apart_and_at_the_edges_of_the_packed_codes(zcr
         q[2] += np.sort(rng.integers(0, 60000, (64, 1)), axis=0) * (s - 1)       # ranks at levels of their own
         q[4] += 3 * 10 ** 6 * rng.integers(-1, 2, (64, 1))                       # constant blocks only
         q[5] += (rng.choice([-1, 1]) * (top - 2 * reach - 2000 + rng.integers(-3, 4, (64, 1))))
+        q[5, :4] = (top - 2 * reach + np.array([0, 1 if s == k - 1 else 0, 0, -1]))[:, None] * np.array([1, 1, -1, -1])[:, None]
         q[6] += 9000 * s
         q[[0, 1, 2, 3, 5, 6, 7], :, 1:] += rng.integers(-40, 41, (7, 64, 31))
         for seg in (0, 1, 3, 7):                                 # codes at the reach, inside it throughout or not
