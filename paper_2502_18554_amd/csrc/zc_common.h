@@ -559,14 +559,24 @@ __device__ inline bool own_chain_scalar(const u64* desc, u32 tile, u64 tag, u32&
   return true;
 }
 
-// Called by all 64 lanes of one wave.  Sum over the chains in `chains` (bit c = the chain of tile
-// - 1 - c, read by lane c) of the sizes of their tiles below `tile`, modulo 2^32 (a stream has
-// fewer payload words than that), with kDescWide set if one of those tiles has it set.
-__device__ inline u64 chains_lookback(const u64* desc, u32 tile, Control* ctl, u64 tag, u32 chains) {
-  const int lane = lane_id();
-  bool live = lane < kChains && ((chains >> lane) & 1u) != 0;
-  i64 head = i64(tile) - 1 - lane;            // the tile this lane inspects
-  live = live && head >= 0;                   // nothing before tile 0
+// Direct look-back: in a stream of few tiles every tile reads the size of every tile before it, one tile a lane, all
+// waves of the workgroup at once, and no chain sums are published.  That is one publication and (nearly always) one poll,
+// where a chain takes a scalar poll per two of its tiles, a second publication and a second poll: what bounds a call
+// whose tiles all run at once is that string of round trips.  The requests grow with the square of the number of tiles,
+// hence the limit.  Measured in us per call, chains and direct (sinusoids, bound 1e-4 of the range):
+//   compress   64 tiles 8.1  7.0 | 245: 10.2  7.9 | 732: 16.0 13.8 | 1024: 19.3 19.0 | 2048: 33.3, with a limit to match 36.8
+//   ring round 128 tiles 9.3  7.4 | 489: 12.6  9.9 | 1024: 17.1 14.9 | 1536: 21.3 21.0 | 4096: 46.1, 60.8
+//   Sum of 2   489 tiles 13.1 10.3 | 768: 14.8 11.7 | 1024: 16.2 13.9;  Max of 8   489: 22.9 20.7 | 1024: 31.7 30.8
+//   Sum of 8   489 tiles 19.8 17.6 | 768: 22.2 22.3 | 1024: 24.4 24.7; of power-law fields 25.2 25.8 and 28.2 31.0
+// The tiles of a Sum of many operands end further apart than others, and while they stream, a vector load takes three
+// times as long as the scalar loads of a chain: its limit (see sum_looks_direct) is lower.
+constexpr u32 kDirectTiles = 1024;
+
+// Called by all 64 lanes of a wave.  A lane inspects tile `head` (none if negative), and where that has published its size
+// but no chain sum, the tile `stride` before it, and so on: the sum over the lanes, modulo 2^32 (a stream has fewer
+// payload words than that), with kDescWide set if one of those tiles has it set.
+__device__ inline u64 walk_back(const u64* desc, i32 head, i32 stride, Control* ctl, u64 tag) {
+  bool live = head >= 0;
   u32 total = 0;
   bool wide = false;
   u32 spins = 0;
@@ -578,20 +588,27 @@ __device__ inline u64 chains_lookback(const u64* desc, u32 tile, Control* ctl, u
     if (live && there) {
       total += u32(d);
       wide = wide || (d & kDescWide) != 0;
-      head -= kChains;                         // a size: on to the tile before it in the chain
+      head -= stride;                          // a size: on to the tile before it in the chain
       live = state == 1 && head >= 0;
     }
     if (__ballot(live && !there)) {
       // give up after kSpinLimit polls, or as soon as another tile has given up
       const bool lost = (++spins & 1023u) == 0 && (status_bits(ctl, tag) & status_bit(ZC_ERR_HIP)) != 0;
       if (spins > kSpinLimit || lost) {
-        if (lane == 0) raise_status(ctl, tag, status_bit(ZC_ERR_HIP));
+        if (lane_id() == 0) raise_status(ctl, tag, status_bit(ZC_ERR_HIP));
         break;
       }
       __builtin_amdgcn_s_sleep(1);
     }
   }
   return u64(wave_sum_u32(total)) | (__ballot(wide) ? kDescWide : 0);
+}
+
+// The chains in `chains` (bit c = the chain of tile - 1 - c, read by lane c).
+__device__ inline u64 chains_lookback(const u64* desc, u32 tile, Control* ctl, u64 tag, u32 chains) {
+  const int lane = lane_id();
+  const bool mine = lane < kChains && ((chains >> lane) & 1u) != 0;
+  return walk_back(desc, mine ? i32(tile) - 1 - lane : -1, kChains, ctl, tag);
 }
 
 }  // namespace zc

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
   __shared__ __attribute__((aligned(16))) u32 lds[kPackWaves * kWaveStage];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kPackWaves];
-  __shared__ u64 sh_base;
+  __shared__ u64 sh_base[kPackWaves];
 
   const int lane = lane_id();
   const int wave = wave_id();
@@ -328,12 +328,12 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     lds_barrier();     // wave totals visible
     sum_wave_totals(sh_wave_total, wave, a.ix != 0, pl);
     // publish the tile's size as early as possible: the tiles after this one wait for it
-    const PayloadSink sink{a.out, a.out_cap, a.nb, a.ctl, a.desc, a.ix != 0, a.coherent != 0, a.part_end, tag};
+    const PayloadSink sink{a.out, a.out_cap, a.nb, a.ctl, a.desc, a.ix != 0, a.coherent != 0, ntiles <= kDirectTiles && !a.coherent, a.part_end, tag};
     if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
 
     // ---- fields -> sign + plane words, then the back half ----
     const bool narrow = pl.wmax <= 15;         // uniform
-    const TileBase tb = resolve_tile_base(sink, pl, tile, &sh_base, wave, lane, [&] {
+    const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
       if (!narrow) return;
       u32 pw[16];          // pw[0] = sign, pw[1 + p] = plane p
       if (pl.wmax <= 7) {

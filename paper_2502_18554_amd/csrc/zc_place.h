@@ -20,6 +20,7 @@ struct PayloadSink {
   u64* desc;        // look-back descriptors
   bool ix;          // the stream carries a segment index (see index_bytes)
   bool coherent;    // the look-back reads the tile's own chain with device-coherent loads (ZC_CHAINS_COHERENT)
+  bool direct;      // the look-back reads the sizes of all tiles before the tile (see kDirectTiles)
   u32 part_end;     // a stream produced in parts (zc_compress_part): one past the last tile of this part; else 0
   u64 tag;          // the call's tag (see launch_tag): descriptors and status bits carry it
 };
@@ -144,19 +145,28 @@ __device__ inline void publish_tile_size(const PayloadSink& s, u32 tile, u32 til
              (tile < u32(kChains) ? kDescChain : kDescAggregate) | (tile_wide ? kDescWide : 0) | u64(tile_total), s.tag);
 }
 
-// Base offset of the tile, in payload words: wave 0 looks back (see "Look-back by chains"),
-// everyone meets at one barrier.  The tile's size must have been published.  Called by every wave
+// Sum over groups of WAVES neighbouring lanes (4 or 8).
+template <int WAVES>
+__device__ inline u32 group_sum(u32 v) {
+  v += dpp_mov<kDppQuadSwap1>(v);
+  v += dpp_mov<kDppQuadSwap2>(v);
+  if (WAVES == 8) v += dpp_mov<kDppRowHalfMirror>(v);
+  return v;
+}
+
+// Base offset of the tile, in payload words: wave 0 looks back (see "Look-back by chains"), or all waves do (direct, see
+// kDirectTiles), everyone meets at one barrier.  The tile's size must have been published.  Called by every wave
 // of the workgroup.  `meanwhile()` runs in every wave: in the other waves while wave 0 looks back,
 // in wave 0 between the publication of its chain sum and its poll of the other chains, whose
 // tiles publish their chain sums at about the same time: a poll that goes out a little later
 // more often finds them and saves a second one (measured: 1 % over the whole kernel against
 // the poll ahead of `meanwhile()`).
-template <typename MeanwhileFn>
-__device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placement& pl, u32 tile, u64* sh_base, int wave,
+template <int WAVES, typename MeanwhileFn>
+__device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placement& pl, u32 tile, u64 (&sh_base)[WAVES], int wave,
                                              int lane, MeanwhileFn meanwhile) {
   u32 own = 0;              // sizes of the tile's chain before it
   u64 wide = pl.tile_wide ? kDescWide : 0;
-  if (wave == 0 && tile >= u32(kChains)) {
+  if (!s.direct && wave == 0 && tile >= u32(kChains)) {
     u64 own_wide = 0;
     if (s.coherent || !own_chain_scalar(s.desc, tile, s.tag, own, own_wide)) {
       const u64 v = chains_lookback(s.desc, tile, s.ctl, s.tag, kOwnChain);
@@ -167,17 +177,22 @@ __device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placeme
     if (lane == 0) desc_store(s.desc, tile, kDescChain | wide | u64(u32(own + pl.tile_total)), s.tag);
   }
   meanwhile();
-  if (wave == 0) {
-    // words of the tiles before this one, and kDescWide if one of them, or this one, is wide
-    const u64 others = chains_lookback(s.desc, tile, s.ctl, s.tag, kOtherChains);
-    if (lane == 0) *sh_base = u64(u32(own + u32(others))) | wide | (others & kDescWide);
+  if (wave == 0 || s.direct) {
+    // words of the tiles before this one (a wave's share of them), and kDescWide if one of them, or this one, is wide
+    const int l = fresh_lane();
+    const int first = s.direct ? l + 64 * wave : l < kChains - 1 ? l : int(tile);
+    const u64 others = walk_back(s.desc, i32(tile) - 1 - first, s.direct ? 64 * WAVES : kChains, s.ctl, s.tag);
+    if (lane == 0) sh_base[wave] = u64(u32(own + u32(others))) | wide | (others & kDescWide);
   }
   lds_barrier();                // only sh_base passes through it
-  const u64 before = *sh_base;
-  return TileBase{before & kDescValueMask, (before & kDescWide) != 0};
+  if (!s.direct) return TileBase{sh_base[0] & kDescValueMask, (sh_base[0] & kDescWide) != 0};
+  const u64 part = sh_base[lane_id() & (WAVES - 1)];      // (a lane per wave)
+  const u32 words = uniform(group_sum<WAVES>(u32(part)));
+  return TileBase{words, __any((part & kDescWide) != 0) || (wide & kDescWide) != 0};
 }
 
-__device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placement& pl, u32 tile, u64* sh_base, int wave,
+template <int WAVES>
+__device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placement& pl, u32 tile, u64 (&sh_base)[WAVES], int wave,
                                              int lane) {
   return resolve_tile_base(s, pl, tile, sh_base, wave, lane, [] {});
 }
@@ -259,9 +274,9 @@ __device__ inline void copy_staged_wave(const PayloadSink& s, const Placement& p
 // Back half of a tile whose size is published, with the plane words in registers (`word(i)`: 0 = sign,
 // 1 + p = plane p): look back for the base offset, then move the payload out.  Called by every wave of
 // the workgroup; one barrier.
-template <int NW, typename WordFn>
+template <int NW, int WAVES, typename WordFn>
 __device__ inline void finish_tile(const PayloadSink& s, WordFn word, const Placement& pl, u32 tile, u32 ntiles,
-                                   u32* wl, u64* sh_base, int wave, int lane) {
+                                   u32* wl, u64 (&sh_base)[WAVES], int wave, int lane) {
   const TileBase tb = resolve_tile_base(s, pl, tile, sh_base, wave, lane);
   if (lane == 0) write_index_entry(s, tile * (blockDim.x >> 6) + u32(wave), tb.words + pl.wave_off);
   copy_wave_out<NW>(s, word, pl, tb.words, wl, lane);

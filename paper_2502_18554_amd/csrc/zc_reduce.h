@@ -85,13 +85,18 @@ __device__ inline bool block_out_of_range(const u32 (&mag)[NP], u32 sign, i64 ou
   return bad;
 }
 
+// Whether the tiles of a Sum look back directly (see kDirectTiles, with the measurements).
+__device__ inline bool sum_looks_direct(const ReduceArgs& a, u32 ntiles) {
+  return !a.coherent && ntiles <= (a.k <= 3 ? kDirectTiles : kDirectTiles / 2);
+}
+
 // Range screen and placement of a summed block inside its wave and tile, then the shared
 // back half.  mag[0..NP) = magnitude planes, sign = sign word, w = highest non-zero plane + 1;
 // `word(i)` hands out the sign word (i = 0) and plane i - 1, for at most NW words.
 template <int NW, int NP, typename WordFn>
 __device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const u32 (&mag)[NP], u32 sign, u32 w,
                                  i64 outlier, bool active, u32 b, u32 tile, u32 ntiles, WordFn word, u32* wl,
-                                 u32 (&sh_wave_total)[kTileWaves], u64* sh_base, int wave, int lane, bool ix) {
+                                 u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], int wave, int lane, bool ix) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, ix);
   if (!active) w = 0;
@@ -121,7 +126,7 @@ __device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const
   }
   lds_barrier();                // the wave totals; the stores above stay in flight
   sum_wave_totals(sh_wave_total, wave, ix, pl);
-  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, ix, a.coherent != 0, c.part_end, c.tag};
+  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, ix, a.coherent != 0, sum_looks_direct(a, ntiles), c.part_end, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
   finish_tile<NW>(sink, word, pl, tile, ntiles, wl, sh_base, wave, lane);
@@ -136,7 +141,7 @@ constexpr int kWholeStage = 64 * 24;
 template <int NW, int NP, typename WordFn>
 __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c, const u32 (&mag)[NP], u32 sign, u32 w,
                                         i64 outlier, bool active, u32 b, u32 tile, u32 ntiles, WordFn word, u32* wl,
-                                        u32 (&sh_wave_total)[kTileWaves], u64* sh_base, int wave, int lane, bool ix) {
+                                        u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], int wave, int lane, bool ix) {
   static_assert(64 * NW <= kWholeStage, "a wave of widest blocks must fit the staging area");
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, ix);
@@ -171,7 +176,7 @@ __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c
   }
   lds_barrier();                // the wave totals (and the words above); the stores stay in flight
   sum_wave_totals(sh_wave_total, wave, ix, pl);
-  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, ix, a.coherent != 0, c.part_end, c.tag};
+  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, ix, a.coherent != 0, sum_looks_direct(a, ntiles), c.part_end, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
   const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane);
@@ -607,7 +612,7 @@ __device__ inline void magnitude_planes(u32 (&acc)[kAccPlanes], u32 s, u32 carry
 
 template <bool IX>
 __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, u32* lds,
-                                        u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
+                                        u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves]) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, IX);
   const int lane = fresh_lane();
@@ -683,7 +688,7 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
 // One tile on the common path.
 template <bool IX>
 __device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, const OperandMeta& meta,
-                                          bool early, u32* lds, u32 (&sh_wave_total)[kTileWaves], u64* sh_base) {
+                                          bool early, u32* lds, u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves]) {
   const int wave = wave_id();
   u32* const wl = lds + wave * kWholeStage;
   const u32 seg = tile * kTileWaves + u32(wave);
@@ -803,7 +808,7 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];   // also holds an operand's payload
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base;
+  __shared__ u64 sh_base[kTileWaves];
 
   ReduceCall c;
   OperandMeta meta{};
@@ -835,8 +840,8 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
     common = uniform(all) != 0;
     lds_barrier();                     // the words are used again
   }
-  if (common) reduce_common_tile<IX>(a, c, tile, ntiles, meta, early, lds, sh_wave_total, &sh_base);
-  else reduce_wide_tile<IX>(a, c, tile, ntiles, lds, sh_wave_total, &sh_base);
+  if (common) reduce_common_tile<IX>(a, c, tile, ntiles, meta, early, lds, sh_wave_total, sh_base);
+  else reduce_wide_tile<IX>(a, c, tile, ntiles, lds, sh_wave_total, sh_base);
 }
 
 }  // namespace zc

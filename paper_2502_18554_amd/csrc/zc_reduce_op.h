@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base;
+  __shared__ u64 sh_base[kTileWaves];
 
   ReduceCall c;
   OperandMeta meta{};
@@ -470,11 +470,11 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   if (lane == 0) sh_wave_total[wave] = pl.wave_total | (IX && pl.wmax > 15 ? kWaveWideMark : 0u);
   lds_barrier();
   sum_wave_totals(sh_wave_total, wave, IX, pl);
-  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, IX, a.coherent != 0, 0u, c.tag};
+  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, IX, a.coherent != 0, ntiles <= kDirectTiles && !a.coherent, 0u, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
   const bool narrow = pl.wmax <= 15;         // uniform
-  const TileBase tb = resolve_tile_base(sink, pl, tile, &sh_base, wave, lane, [&] {
+  const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
     if (!narrow) return;
     u32 pw[16];
 #pragma unroll

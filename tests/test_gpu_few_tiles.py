@@ -1,0 +1,47 @@
+"""Streams of few tiles take ways of their own through the kernels that write streams (all tiles run at once then, and
+round trips are what counts): sizes around the limits of those ways, against the reference codec."""
+import numpy as np
+import pytest
+import torch
+
+import gpuutil
+from paper_2502_18554_amd import synth
+from paper_2502_18554_amd.binding import ZC_OK
+
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("stream_variant")]
+
+TILE = 8192                                        # of the ring round and the reduces; the compressor's is twice that
+
+
+def _values(n, seed):
+    """Smooth values with a block wider than 15 bits near the start, so that the mark of such blocks has to travel."""
+    x = synth.sinusoids(n, seed=seed).numpy().copy()
+    x[37] = 900.0
+    return x
+
+
+# one lane, wave and round of lanes of the direct look-back more than the tile before needs (64, 256 and 512 tiles),
+# and both sides of its limits (512 and 1024 tiles)
+@pytest.mark.parametrize("tiles", [2, 8, 9, 64, 65, 256, 257, 512, 513, 1024, 1025])
+def test_streams_of_few_tiles(zcref, tiles):
+    u = gpuutil
+    n = tiles * TILE - 4097
+    xs = [_values(n, 40 + i) for i in range(4)]
+    eb = synth.abs_bound(torch.from_numpy(synth.sinusoids(n, seed=1).numpy()), 1e-3)
+    st_ref, ref = zcref.compress(xs[0], eb)[:2]
+    st, s, total = u.gpu_compress(xs[0], eb)
+    assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+    refs = [ref] + [zcref.compress(x, eb)[1] for x in xs[1:]]
+    for k, op in ((2, None), (4, None), (2, 1)):
+        st_ref, red_ref = zcref.reduce(refs[:k], op=op or 0)[:2]
+        st, red, _ = u.gpu_reduce(refs[:k], n, op=op)
+        assert st == st_ref == ZC_OK and red.tobytes() == red_ref.tobytes(), (k, op, u.first_diff(red, red_ref))
+    st_ref, step_ref = zcref.reduce_step(refs[0], xs[1])[:2]
+    st, step, _ = u.gpu_reduce_step(refs[0], xs[1])
+    assert st == st_ref and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
+    if tiles % 2 == 0:                             # the compressor's own tiles: as many again
+        n2 = 2 * tiles * TILE - 4097
+        x = _values(n2, 50)
+        st_ref, ref = zcref.compress(x, eb)[:2]
+        st, s, total = u.gpu_compress(x, eb)
+        assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
