@@ -106,13 +106,16 @@ int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = 
   return status_from_bits((host[0] >> 32) == (host[1] >> 32) ? u32(host[0]) : 0u);
 }
 
-// Validation and block positions of plain input streams, ahead of the kernel that reads them
-// (indexed streams bring their positions along and are judged by that kernel itself).
-// `tiles`: enough for the largest stream.  index_prep_kernel opens the call: the main kernel
-// adopts the tag it leaves in the control block.
-void launch_plain_index(ScanArgs& sa, u64 tiles, hipStream_t stream) {
-  hipLaunchKernelGGL(stream_index_kernel, dim3(index_grid(tiles), u32(sa.k)), dim3(256), 0, stream, sa);
-  hipLaunchKernelGGL(index_prep_kernel, dim3(1), dim3(256), 0, stream, sa);
+// Plain input streams of up to `tiles` tiles, most likely no more than `likely`: whether the main kernel is to sum their
+// width tables itself (see judge_plain_streams); if not, their positions are computed ahead of it.
+bool index_plain_streams(const StreamRef* streams, int k, u64 tiles, u64 likely, const WorkspaceLayout& l, hipStream_t stream) {
+  if (likely * u64(k) <= kSelfTiles) return true;
+  ScanArgs sa;
+  for (int i = 0; i < k; ++i) sa.streams[i] = streams[i];
+  sa.k = k;
+  sa.index = l.index;
+  hipLaunchKernelGGL(stream_index_kernel, dim3(index_grid(tiles), u32(k)), dim3(256), 0, stream, sa);
+  return false;
 }
 
 // Tiles that a stream of in_bytes bytes can have, as far as the workspace goes.
@@ -140,39 +143,40 @@ __global__ void quantize_kernel(QuantizeArgs a) {
 struct OffsetsArgs {
   StreamRef in;
   StreamIndex index;
+  u32 self;
   u32* off_words;
   u64 off_cap;
   Control* ctl;
   u64 nonce;
-  bool ix;
 };
 
-__global__ __launch_bounds__(256) void block_offsets_kernel(OffsetsArgs a) {
-  const ParsedHeader h = parse_header(a.in, a.ix);
-  u64 tag;
-  if (a.ix) {
-    tag = call_tag(a.ctl, launch_tag(a.nonce, a.ctl), false);
-    if (!h.ok) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_FORMAT));
-      return;
-    }
-  } else {
-    const Gate gate = parse_gate(load_gate(a.ctl, 0));
-    tag = gate.tag;
-    if (gate_failed(gate) || !h.ok) return;
+template <bool IX>
+__global__ __launch_bounds__(kTileThreads) void block_offsets_kernel(OffsetsArgs a) {
+  __shared__ PlainSurvey<1> survey;
+  const int wave = wave_id();
+  const u64 seg = u64(blockIdx.x) * kTileWaves + u64(wave);
+  StreamsVerdict v;
+  v.mine = parse_header(a.in, IX);
+  const ParsedHeader& h = v.mine;
+  v.err = h.ok ? 0u : status_bit(ZC_ERR_FORMAT);
+  const u64 tag = call_tag(a.ctl, launch_tag(a.nonce, a.ctl), false);
+  u32 seg_off = 0;
+  if (!IX) {
+    const SurveyLoads ask = ask_plain_streams<1>(&a.in, 1, a.index, a.self != 0, u32(seg), wave);
+    seg_off = lane_value(judge_plain_streams(&a.in, 1, a.index, a.self != 0, blockIdx.x, wave, ask, v, survey), 0);
   }
-  if (h.nb > a.off_cap) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_CAPACITY));
+  if (!v.err && h.nb > a.off_cap) v.err = status_bit(ZC_ERR_CAPACITY);
+  if (v.err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, v.err);
     return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->result = h.nb;
-  const u64 seg = u64(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  if (seg >= num_segments(h.nb) || (!a.ix && seg >= 4 * a.index.tiles_cap)) return;
+  if (seg >= num_segments(h.nb)) return;
   const u64 b = seg * kWaveBlocks + u64(lane_id());
-  const u32 w = b < h.nb ? u32(a.in.base[widths_begin(h.nb, a.ix) + b]) : 0u;
+  const u32 w = b < h.nb ? u32(a.in.base[widths_begin(h.nb, IX) + b]) : 0u;
   const u32 words = psize_words(w);
   const u32 incl = wave_inclusive_sum(words);
-  const u32 seg_off = a.ix ? reinterpret_cast<const u32*>(a.in.base + kHeaderBytes)[seg] : u32(segment_offset(a.index, 0, seg));
+  if (IX) seg_off = reinterpret_cast<const u32*>(a.in.base + kHeaderBytes)[seg];
   if (b < h.nb) a.off_words[b] = seg_off + incl - words;
 }
 
@@ -235,9 +239,14 @@ void* scratch_of_current_device() {
 
 namespace {
 template <int OP>
-void (*pick_step_kernel(bool ix, bool tickets))(StepArgs) {
-  if (ix) return tickets ? step_kernel<true, OP, true> : step_kernel<true, OP, false>;
-  return tickets ? step_kernel<false, OP, true> : step_kernel<false, OP, false>;
+void (*pick_step_kernel(bool ix, bool self, bool tickets))(StepArgs) {
+  if (ix) return tickets ? step_kernel<true, false, OP, true> : step_kernel<true, false, OP, false>;
+  if (self) return tickets ? step_kernel<false, true, OP, true> : step_kernel<false, true, OP, false>;
+  return tickets ? step_kernel<false, false, OP, true> : step_kernel<false, false, OP, false>;
+}
+template <bool AVERAGE>
+void (*pick_decompress_kernel(bool ix, bool self))(DecompressArgs) {
+  return ix ? decompress_kernel<true, false, AVERAGE> : self ? decompress_kernel<false, true, AVERAGE> : decompress_kernel<false, false, AVERAGE>;
 }
 }  // namespace
 
@@ -349,38 +358,31 @@ static int decompress_one(const void* d_in, size_t in_bytes, size_t first_value,
   u64 wanted = count < out_cap_elems ? count : out_cap_elems;
   const u64 stream_bound = blocks_bound(in_bytes) * kBlockValues;
   if (wanted > stream_bound) wanted = stream_bound;
-  u64 grid = (wanted + kTileValues - 1) / kTileValues;
+  // (a part need not start at a tile: the tiles that it touches)
+  u64 grid = (wanted + (ranged ? first_value % kTileValues : 0) + kTileValues - 1) / kTileValues;
   if (!ix && grid > l.tiles_cap) grid = l.tiles_cap;
   if (grid > kMaxTiles) grid = kMaxTiles;
   if (grid < 1) grid = 1;
-  const u64 nonce = call_nonce();
-  if (!ix) {
-    ScanArgs sa;
-    sa.streams[0].base = static_cast<const u8*>(d_in);
-    sa.streams[0].bytes = in_bytes;
-    sa.k = 1;
-    sa.check_match = 0;
-    sa.index = l.index;
-    sa.ctl = l.ctl;
-    sa.nonce = nonce;
-    launch_plain_index(sa, tiles_of_stream(in_bytes, l, false), stream);
-  }
   DecompressArgs da;
   da.in.base = static_cast<const u8*>(d_in);
   da.in.bytes = in_bytes;
+  bool self = false;
+  if (!ix) {
+    const u64 tiles = tiles_of_stream(in_bytes, l, false), most_out = num_tiles(num_blocks(out_cap_elems));
+    self = index_plain_streams(&da.in, 1, tiles, ranged || tiles < most_out ? tiles : most_out, l, stream);
+  }
   da.out = d_out;
   da.out_cap_elems = out_cap_elems;
   da.index = l.index;
   da.ctl = l.ctl;
   da.first_value = first_value;
   da.count = count;
-  da.nonce = nonce;
+  da.nonce = call_nonce();
   if (ranged) {
-    hipLaunchKernelGGL(ix ? decompress_range_kernel<true> : decompress_range_kernel<false>, dim3(u32(grid)),
-                       dim3(kTileThreads), 0, stream, da);
+    void (*kernel)(DecompressArgs) = ix ? decompress_range_kernel<true, false> : self ? decompress_range_kernel<false, true> : decompress_range_kernel<false, false>;
+    hipLaunchKernelGGL(kernel, dim3(u32(grid)), dim3(kTileThreads), 0, stream, da);
   } else {
-    void (*kernel)(DecompressArgs) = average ? (ix ? decompress_kernel<true, true> : decompress_kernel<false, true>)
-                                             : (ix ? decompress_kernel<true, false> : decompress_kernel<false, false>);
+    void (*kernel)(DecompressArgs) = average ? pick_decompress_kernel<true>(ix, self) : pick_decompress_kernel<false>(ix, self);
     launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(grid)), dim3(kTileThreads), stream, da);
   }
   if (!launch_ok()) return ZC_ERR_HIP;
@@ -423,13 +425,11 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   const bool ix = is_indexed(flags);
   const WorkspaceLayout l = workspace_layout(d_ws, ws_bytes, k);
   if (l.tiles_cap < 1) return ZC_ERR_ARG;
-  ScanArgs sa;
   DecompressManyArgs da;
   u64 tiles = 1, tiles_in = 1;
   for (int i = 0; i < k; ++i) {
-    sa.streams[i].base = static_cast<const u8*>(d_chunks[i]);
-    sa.streams[i].bytes = chunk_bytes[i];
-    da.in[i] = sa.streams[i];
+    da.in[i].base = static_cast<const u8*>(d_chunks[i]);
+    da.in[i].bytes = chunk_bytes[i];
     da.out[i] = d_outs[i];
     da.out_cap_elems[i] = out_cap_elems[i];
     const u64 t_in = tiles_of_stream(chunk_bytes[i], l, ix);
@@ -438,20 +438,12 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
     if (t > tiles) tiles = t;
     if (t_in > tiles_in) tiles_in = t_in;
   }
-  const u64 nonce = call_nonce();
-  if (!ix) {
-    sa.k = k;
-    sa.check_match = 0;
-    sa.index = l.index;
-    sa.ctl = l.ctl;
-    sa.nonce = nonce;
-    launch_plain_index(sa, tiles_in, stream);
-  }
   da.k = k;
   da.index = l.index;
+  const bool self = !ix && index_plain_streams(da.in, k, tiles_in, tiles, l, stream);
   da.ctl = l.ctl;
-  da.nonce = nonce;
-  void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true> : decompress_many_kernel<false>;
+  da.nonce = call_nonce();
+  void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false> : self ? decompress_many_kernel<false, true> : decompress_many_kernel<false, false>;
   launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(tiles), u32(k)), dim3(kTileThreads), stream, da);
   if (!launch_ok()) return ZC_ERR_HIP;
   if (!n_out) return ZC_OK;
@@ -491,31 +483,21 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   if (tiles > kMaxTiles) tiles = kMaxTiles;
   if (tiles < 1) tiles = 1;
   if (tiles_in > l.tiles_cap) tiles_in = l.tiles_cap;
-  ScanArgs sa;
   ReduceArgs ra;
   for (int i = 0; i < k; ++i) {
-    sa.streams[i].base = static_cast<const u8*>(d_chunks[i]);
-    sa.streams[i].bytes = chunk_bytes[i];
-    ra.in[i] = sa.streams[i];
-  }
-  const u64 nonce = call_nonce();
-  if (!ix) {
-    sa.k = k;
-    sa.check_match = 1;
-    sa.index = l.index;
-    sa.ctl = l.ctl;
-    sa.nonce = nonce;
-    launch_plain_index(sa, tiles_in, stream);
+    ra.in[i].base = static_cast<const u8*>(d_chunks[i]);
+    ra.in[i].bytes = chunk_bytes[i];
   }
   ra.k = k;
   ra.index = l.index;
+  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, tiles, l, stream);
   ra.out = static_cast<u8*>(d_out);
   ra.out_cap = out_cap;
   ra.ctl = l.ctl;
   ra.desc = l.desc;
   ra.ticketed = (flags & ZC_TILES_BY_TICKET) != 0;
   ra.coherent = (flags & ZC_CHAINS_COHERENT) != 0;
-  ra.nonce = nonce;
+  ra.nonce = call_nonce();
   ra.first_tile = ra.end_tile = ra.adopt = 0;
   ra.n_part = 0;
   if (ranged) {
@@ -592,20 +574,10 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   u64 tiles = num_tiles(num_blocks(n_local));
   if (l.tiles_cap < 1 || tiles > l.tiles_cap) return ZC_ERR_ARG;
   if (tiles < 1) tiles = 1;
-  const u64 nonce = call_nonce();
   StepArgs ta;
   ta.in.base = static_cast<const u8*>(d_chunk);
   ta.in.bytes = chunk_bytes;
-  if (!ix) {
-    ScanArgs sa;
-    sa.streams[0] = ta.in;
-    sa.k = 1;
-    sa.check_match = 0;
-    sa.index = l.index;
-    sa.ctl = l.ctl;
-    sa.nonce = nonce;
-    launch_plain_index(sa, tiles_of_stream(chunk_bytes, l, false), stream);
-  }
+  const bool self = !ix && index_plain_streams(&ta.in, 1, tiles_of_stream(chunk_bytes, l, false), tiles, l, stream);
   ta.local = d_local;
   ta.n_local = n_local;
   ta.index = l.index;
@@ -615,7 +587,7 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   ta.desc = l.desc;
   ta.ticketed = (flags & ZC_TILES_BY_TICKET) != 0;
   ta.coherent = (flags & ZC_CHAINS_COHERENT) != 0;
-  ta.nonce = nonce;
+  ta.nonce = call_nonce();
   ta.first_tile = ta.end_tile = ta.adopt = 0;
   if (ranged) {
     if (!ix || n_local == 0 || first_value % kTileValues != 0 || first_value >= n_local || count == 0 ||
@@ -630,9 +602,9 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   }
   void (*kernel)(StepArgs) = nullptr;
   const bool tickets = ta.ticketed != 0;
-  if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, tickets);
-  else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, tickets);
-  else kernel = pick_step_kernel<ZC_OP_MIN>(ix, tickets);
+  if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, self, tickets);
+  else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, self, tickets);
+  else kernel = pick_step_kernel<ZC_OP_MIN>(ix, self, tickets);
   launch_main(ZC_KERNEL_REDUCE_STEP, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ta);
   if (!launch_ok()) return ZC_ERR_HIP;
   if (!out_bytes) return ZC_OK;
@@ -764,28 +736,16 @@ int zc_debug_block_offsets(const void* d_in, size_t in_bytes, uint32_t* d_off_wo
   const WorkspaceLayout l = workspace_layout(d_ws, ws_bytes, 1);
   if (l.tiles_cap < 1) return ZC_ERR_ARG;
   const u64 tiles = tiles_of_stream(in_bytes, l, ix);
-  const u64 nonce = call_nonce();
-  if (!ix) {
-    ScanArgs sa;
-    sa.streams[0].base = static_cast<const u8*>(d_in);
-    sa.streams[0].bytes = in_bytes;
-    sa.k = 1;
-    sa.check_match = 0;
-    sa.index = l.index;
-    sa.ctl = l.ctl;
-    sa.nonce = nonce;
-    launch_plain_index(sa, tiles, stream);
-  }
   OffsetsArgs oa;
   oa.in.base = static_cast<const u8*>(d_in);
   oa.in.bytes = in_bytes;
   oa.index = l.index;
+  oa.self = ix ? 0u : index_plain_streams(&oa.in, 1, tiles, tiles, l, stream);
   oa.off_words = d_off_words;
   oa.off_cap = off_cap;
   oa.ctl = l.ctl;
-  oa.nonce = nonce;
-  oa.ix = ix;
-  hipLaunchKernelGGL(block_offsets_kernel, dim3(u32(tiles)), dim3(256), 0, stream, oa);
+  oa.nonce = call_nonce();
+  hipLaunchKernelGGL(ix ? block_offsets_kernel<true> : block_offsets_kernel<false>, dim3(u32(tiles)), dim3(256), 0, stream, oa);
   if (!launch_ok()) return ZC_ERR_HIP;
   return finish(d_ws, nullptr, stream);
 }

@@ -57,12 +57,6 @@ constexpr u32 kVersionIndexed = 2u | (5u << 16) | (6u << 24);   // | 1 when some
 // Device status word: bit i set <=> error code i was raised.
 __host__ __device__ constexpr u32 status_bit(int code) { return 1u << code; }
 
-// Errors that stop a call before it writes anything: bad arguments, malformed or mismatched
-// input streams.  Every workgroup of a main kernel takes the same decision on them, either
-// from the verdict the validation kernel of plain streams left (zc_scan.h) or from the same
-// header bytes (indexed streams).
-constexpr u32 kGateBits = status_bit(ZC_ERR_ARG) | status_bit(ZC_ERR_FORMAT) | status_bit(ZC_ERR_MISMATCH);
-
 // Control part of the caller's workspace.  Tile tickets, tile descriptors and segment-offset
 // tables follow.  Nothing in a workspace is ever cleared: whatever one call shares between its
 // workgroups or its launches carries the call's tag (below), and a word with another tag counts
@@ -70,11 +64,10 @@ constexpr u32 kGateBits = status_bit(ZC_ERR_ARG) | status_bit(ZC_ERR_FORMAT) | s
 constexpr int kTicketsPerXcd = 4;
 constexpr int kTicketShards = 8 * kTicketsPerXcd;
 struct Control {
-  u64 status;                  // bits 63..32: high half of the tag of the call that raised them; bits 31..0: OR of status_bit()s and kStatusWide
+  u64 status;                  // bits 63..32: high half of the tag of the call that raised them; bits 31..0: OR of status_bit()s
   u64 call_tag;                // tag of the last call's first launch; its later launches take it from here
   u64 result;                  // total_bytes, or n for decompress
-  u64 nsum;                    // sum of the input streams' nsum fields (plain streams: set by index_prep_kernel)
-  u32 pad[8];
+  u32 pad[10];
 };
 static_assert(sizeof(Control) == 64, "control block is 64 bytes");
 
@@ -90,30 +83,25 @@ __host__ __device__ inline u64* ticket_counter(Control* ctl, u32 shard) {
 
 // A segment is the 64 blocks owned by one wave; a tile is 4 segments.
 
-// Positions inside an existing stream are kept at three levels (see zc_scan.h): the offset of
-// every segment inside its scan group of 64 segments, the offset of every group inside its
-// index span of 8 groups (the share of one workgroup of the index kernel), and the offset of
-// every span.  A reader adds the three.
-constexpr int kScanGroupSegs = 64;
-constexpr int kScanGroupBlocks = kScanGroupSegs * kWaveBlocks;     // 4096 blocks
-constexpr int kIndexGroups = 8;                                    // scan groups per index span
-constexpr int kSpanSegs = kIndexGroups * kScanGroupSegs;           // 512 segments = 32768 blocks
-__host__ __device__ inline u64 num_scan_groups(u64 nb) { return (nb + kScanGroupBlocks - 1) / kScanGroupBlocks; }
-__host__ __device__ inline u64 num_spans(u64 nb) { return (num_scan_groups(nb) + kIndexGroups - 1) / kIndexGroups; }
+// Positions inside an existing plain stream are kept at two levels (see zc_scan.h): the offset of
+// every segment inside its index span of 512 segments (the share of one workgroup of the index kernel), and the size of
+// every span; the readers add up the sizes of the spans before theirs.
+constexpr int kIndexGroupBlocks = 4096;                            // a load of 16 width bytes by every thread of a workgroup
+constexpr int kIndexGroupSegs = kIndexGroupBlocks / kWaveBlocks;
+constexpr int kIndexGroups = 8;
+constexpr int kSpanSegs = kIndexGroups * kIndexGroupSegs;          // 512 segments
+constexpr int kSpanBlocks = kIndexGroups * kIndexGroupBlocks;      // 32768 blocks
+__host__ __device__ inline u64 num_spans(u64 nb) { return (nb + kSpanBlocks - 1) / kSpanBlocks; }
 
 struct StreamIndex {
-  u32* seg_off;     // [k][4 * tiles_cap]   payload word offset of each segment inside its scan group
-  u32* grp_off;     // [k][groups_cap]      payload word offset of each scan group inside its span
-  u32* span_off;    // [k][spans_cap]       payload word offset of each span (its size between the two index kernels)
-  u32* span_flags;  // [k][spans_cap]       what stream_index_kernel saw in each span
+  u32* seg_off;     // [k][4 * tiles_cap]   payload word offset of each segment inside its span
+  u32* spans;       // [k][spans_cap]       payload words of each span, and what stream_index_kernel saw in it (kSpanSize ...)
   u64 tiles_cap;
-  u64 groups_cap;
   u64 spans_cap;
 };
 
 // How a workspace of ws_bytes is carved up for calls with k input streams:
-//   Control | tickets | desc[tiles_cap] (128 B each) | seg_off[k][4 * tiles_cap] | grp_off[k][groups_cap] |
-//   span_off[k][spans_cap] | span_flags[k][spans_cap]
+//   Control | tickets | desc[tiles_cap] (128 B each) | seg_off[k][4 * tiles_cap] | spans[k][spans_cap]
 // tiles_cap follows from ws_bytes alone, so kernels can refuse streams that do not fit.
 struct WorkspaceLayout {
   u64 tiles_cap;
@@ -123,12 +111,12 @@ struct WorkspaceLayout {
 };
 
 constexpr u64 kDescBytes = 128;           // per tile, see kDescStride
-constexpr u64 kWsFixed = sizeof(Control) + kTicketBytes + 12 * ZC_MAX_K + 64;   // control, tickets, the +1 of every grp_off, span_off and span_flags row, padding
+constexpr u64 kWsFixed = sizeof(Control) + kTicketBytes + 12 * ZC_MAX_K + 64;   // control, tickets, the +1 of every row of spans, padding
 
 __host__ constexpr u64 workspace_bytes(u64 n_max, int k_max) {
   if (k_max < 1) k_max = 1;
   const u64 t = num_tiles(num_blocks(n_max)) + 16;
-  return kWsFixed + t * (kDescBytes + 17 * u64(k_max));      // 17 >= segment offsets (16) + the tile's share of the two coarser levels
+  return kWsFixed + t * (kDescBytes + 17 * u64(k_max));      // 17 >= segment offsets (16) + the tile's share of the spans
 }
 
 __host__ inline WorkspaceLayout workspace_layout(void* d_ws, u64 ws_bytes, int k) {
@@ -141,15 +129,10 @@ __host__ inline WorkspaceLayout workspace_layout(void* d_ws, u64 ws_bytes, int k
   l.desc = reinterpret_cast<u64*>(p);
   p += kDescBytes * l.tiles_cap;
   l.index.tiles_cap = l.tiles_cap;
-  l.index.groups_cap = l.tiles_cap / 16 + 1;        // 16 tiles = 64 segments = one scan group
-  l.index.spans_cap = l.tiles_cap / (16 * kIndexGroups) + 1;
+  l.index.spans_cap = l.tiles_cap / (kSpanBlocks / kTileBlocks) + 1;
   l.index.seg_off = reinterpret_cast<u32*>(p);
   p += pad16(16 * l.tiles_cap * u64(k));
-  l.index.grp_off = reinterpret_cast<u32*>(p);
-  p += 4 * l.index.groups_cap * u64(k);
-  l.index.span_off = reinterpret_cast<u32*>(p);
-  p += 4 * l.index.spans_cap * u64(k);
-  l.index.span_flags = reinterpret_cast<u32*>(p);
+  l.index.spans = reinterpret_cast<u32*>(p);
   return l;
 }
 
@@ -157,10 +140,6 @@ __host__ inline WorkspaceLayout workspace_layout(void* d_ws, u64 ws_bytes, int k
 // Wave-level primitives (64 lanes).
 // ---------------------------------------------------------------------------------------
 __device__ inline int lane_id() { return int(threadIdx.x) & 63; }
-
-// Not an error: the validation kernel of plain streams found a block wider than 15 bits (the
-// host ignores the bit).
-constexpr u32 kStatusWide = 1u << 16;
 
 // Tile hand-out.  A kernel that places its output by look-back needs every tile below a tile
 // in work to be in work too, or finished.  Two ways to get that:

@@ -209,104 +209,106 @@ __device__ inline void deltas_from_block_words(u32 wmax, u32 (&lo)[16], u32 (&hi
   }
 }
 
-// One tile (blockIdx.x) of stream `s` of the index, into `out`.  `many`: one of several streams
-// of a call (blockIdx.y); `others_ok`: the headers of the other streams are in order.
-// `ix`: the stream is indexed: no kernel has run ahead of this one, the header and the index
-// are judged here (see judge_indexed_streams, index_ends_ok), and the call's tag is this
-// launch's; its width bytes sit behind the index, whose size only the header tells, so they
-// are asked for together with the outlier and the payload.  A plain stream has been validated
-// and indexed by the kernels of zc_scan.h, whose verdict and tag are in the control block.
+// One tile (blockIdx.x) of stream `s` into `out`.
+// The header is judged here, by every workgroup alike (see judge_headers, judge_plain_streams, index_ends_ok).
+// `IX`: the stream is indexed; its width bytes sit behind the index, whose size only the header tells, so they
+// are asked for together with the outlier and the payload.  SELF: a plain stream whose width table the kernel sums itself
+// (a template parameter: as an argument it cost the streams that have an index 2 %).  K: room for that many streams in the survey of plain ones;
+// `streams`, `k`: all streams of the call.
 // `average`: the values are divided by the stream's nsum (the Average aggregation of Section
 // 3.2 on a stream of sums): x' = float((double(q) * s) * r), r = 1.0 / nsum.
 // first_value, count: only the values [first_value, first_value + count) of the stream, cut off
 // at its end, are produced, into out_values[0 ...] (a chunk handled on its own, Section 3.5.2);
 // first_value is a multiple of the 2048 values of a segment.  The whole stream: 0 and ~0.
-__device__ inline void decompress_tile(const StreamRef& in, float* out_values, u64 out_cap_elems, const StreamIndex& index,
-                                       int s, Control* ctl, u64 nonce, bool many, bool others_ok, u64 sum_n, u32* lds,
-                                       bool ix, bool average = false, u64 first_value = 0, u64 count = ~u64(0)) {
+template <bool IX, bool SELF, int K>
+__device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k, int s, float* out_values, u64 out_cap_elems,
+                                       const StreamIndex& index, Control* ctl, u64 nonce, u32* lds, PlainSurvey<K>* survey,
+                                       bool average = false, u64 first_value = 0, u64 count = ~u64(0)) {
+  const StreamRef in = streams[s];
   const DecompressArgs a{in, out_values, out_cap_elems, index, ctl, first_value, count, nonce};
+  constexpr bool many = K > 1;
 
-  // Everything that can be asked for before the header is known goes out at once: the control
-  // block, the header, the segment's position and the width bytes.  The loads are fenced in
-  // by sizes the host passed; what the header then rules out is dropped.
+  // Everything that can be asked for before the header is known goes out at once: the header, the segment's position and
+  // the width bytes.  The loads are fenced in by sizes the host passed; what the header then rules out is dropped.
   const int lane = lane_id();
   const int wave = wave_id();
-  const u32 seg = u32(first_value / (kWaveBlocks * kBlockValues)) + blockIdx.x * kTileWaves + u32(wave);   // < 2^22: the host launches at most 2^20 tiles
+  const u32 tile = u32(first_value / kTileValues) + blockIdx.x;
+  const u32 seg = tile * kTileWaves + u32(wave);       // < 2^22: the host launches at most 2^18 tiles
   const u32 wblock0 = seg * kWaveBlocks;
   const u32 b = wblock0 + u32(lane);                   // a stream has at most 2^26 blocks
   const u32 zero = opaque_zero();
   const bool first_group = blockIdx.x == 0 && blockIdx.y == 0;
-  uint4 gate_raw = make_uint4(0, 0, 0, 0);
-  if (!ix) gate_raw = load_gate(a.ctl, zero);
+  SurveyLoads ask{};
+  if (!IX) ask = ask_plain_streams<K>(streams, k, a.index, SELF, seg, wave);
   const HeaderWords hw = load_header_words(a.in.base, zero);
-  SegmentOffsetParts seg_parts{0, 0, 0};
-  u32 seg_end = 0, w = 0;
-  if (ix) {
+  u32 seg_begin = 0, seg_end = 0, w = 0;
+  if (IX) {
     if (u64(kHeaderBytes) + 4 * u64(seg) + 8 <= a.in.bytes) {
-      seg_parts = load_segment_offset(a.index, s, seg, zero, a.in.base);
+      seg_begin = load_segment_offset(a.in.base, seg, zero);
       seg_end = load_segment_end(a.in.base, seg, zero);
     }
   } else {
-    if (seg < 4 * a.index.tiles_cap) seg_parts = load_segment_offset(a.index, s, seg, zero);
     if (u64(kHeaderBytes) + b < a.in.bytes) w = u32(*at_bytes(a.in.base, kHeaderBytes + b));
   }
 
-  const ParsedHeader h = parse_header(hw, a.in.bytes, ix);
-  u64 tag;
-  if (ix) {
-    tag = call_tag(a.ctl, launch_tag(a.nonce, a.ctl), false);
-    if (!h.ok || !others_ok) {
-      if (first_group && threadIdx.x == 0) {
-        a.ctl->result = 0;
-        raise_status(a.ctl, tag, status_bit(ZC_ERR_FORMAT));
-      }
-      return;
-    }
-    // a stream without blocks: nobody looks at its index, which is one closing entry of 0
-    if (h.nb == 0 && blockIdx.x == 0 && threadIdx.x == 0 &&
-        (h.total != tables_end(0, true) || *reinterpret_cast<const u32*>(a.in.base + kHeaderBytes) != 0))
-      raise_status(a.ctl, tag, status_bit(ZC_ERR_FORMAT));
-  } else {
-    const Gate gate = parse_gate(gate_raw);
-    tag = gate.tag;
-    if (gate_failed(gate) || !h.ok) return;
+  // (the tag, some 100 dependent scalar instructions, while the loads are on their way)
+  u64 ltag = launch_tag(a.nonce, a.ctl);
+  asm volatile("" : "+s"(ltag));
+  StreamsVerdict v;
+  if constexpr (many) v = judge_headers<IX>(streams, k, false);      // any malformed stream stops the whole call
+  const ParsedHeader h = parse_header(hw, a.in.bytes, IX);
+  if constexpr (!many) {
+    v.mine = h;
+    v.err = h.ok ? 0u : status_bit(ZC_ERR_FORMAT);
   }
+  const u64 tag = call_tag(a.ctl, ltag, false);
+  if (!IX) {
+    const u32 off = judge_plain_streams(streams, k, a.index, SELF, tile, wave, ask, v, *survey);
+    seg_begin = lane_value(off, s);
+  }
+  if (v.err) {
+    if (first_group && threadIdx.x == 0) {
+      a.ctl->result = 0;
+      raise_status(a.ctl, tag, v.err);
+    }
+    return;
+  }
+  // a stream without blocks: nobody looks at its index, which is one closing entry of 0
+  if (IX && h.nb == 0 && blockIdx.x == 0 && threadIdx.x == 0 &&
+      (h.total != tables_end(0, true) || *reinterpret_cast<const u32*>(a.in.base + kHeaderBytes) != 0))
+    raise_status(a.ctl, tag, status_bit(ZC_ERR_FORMAT));
   if (first_value > h.n) {                            // the part lies beyond the stream
     if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_ARG));
     return;
   }
   const u64 end_value = count < h.n - first_value ? first_value + count : h.n;     // one past the last value wanted
   const u64 wanted = end_value - first_value;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    if (!many) a.ctl->result = wanted;
-    else if (ix) { if (blockIdx.y == 0) a.ctl->result = sum_n; }
-    else atomicAdd(reinterpret_cast<unsigned long long*>(&a.ctl->result), static_cast<unsigned long long>(wanted));
-  }
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.ctl->result = many ? v.sum_n : wanted;
   if (wanted > a.out_cap_elems) {
     if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_CAPACITY));
     return;
   }
-  if (!ix && u64(seg) >= 4 * a.index.tiles_cap) return;
 
   u32* const wl = lds + wave * kWaveStage;
-  if (seg >= num_segments(h.nb) || u64(seg) * kWaveBlocks * kBlockValues >= end_value) return;   // no barrier below: waves are independent
+  // (no barrier below: waves are independent)
+  if (seg >= num_segments(h.nb) || u64(seg) * (kWaveBlocks * kBlockValues) >= end_value || u64(seg) * (kWaveBlocks * kBlockValues) < first_value) return;
   const bool active = b < h.nb;
-  if (ix && active) w = u32(*at_bytes(a.in.base, u32(widths_begin(h.nb, true)) + b));
+  if (IX && active) w = u32(*at_bytes(a.in.base, u32(widths_begin(h.nb, true)) + b));
   if (!active) w = 0;
 
-  const i32* outliers = reinterpret_cast<const i32*>(a.in.base + outliers_begin(h.nb, ix));
-  const u32* payload = reinterpret_cast<const u32*>(a.in.base + tables_end(h.nb, ix));
-  const u64 payload_words = (h.total - tables_end(h.nb, ix)) / 4;
+  const i32* outliers = reinterpret_cast<const i32*>(a.in.base + outliers_begin(h.nb, IX));
+  const u32* payload = reinterpret_cast<const u32*>(a.in.base + tables_end(h.nb, IX));
+  const u64 payload_words = (h.total - tables_end(h.nb, IX)) / 4;
 
   u32 cur = active ? u32(outliers[b]) : 0u;
-  const u64 seg_off = ix ? u64(uniform(seg_parts.seg)) : segment_offset(seg_parts);
+  const u64 seg_off = u64(uniform(seg_begin));
   i32 d[32];
   {
     u32 lo[16], hi[16];
     u32 err = 0;
-    const u32 wmax = wave_block_words(payload, payload_words, w, seg_off, wl, lane, lo, hi, ix,
+    const u32 wmax = wave_block_words(payload, payload_words, w, seg_off, wl, lane, lo, hi, IX,
                                       uniform(seg_end) - u32(seg_off), h.wide, err, reinterpret_cast<const uint4*>(a.in.base));
-    if (ix && !index_ends_ok(h, seg, u32(seg_off), uniform(seg_end))) err |= status_bit(ZC_ERR_FORMAT);
+    if (IX && !index_ends_ok(h, seg, u32(seg_off), uniform(seg_end))) err |= status_bit(ZC_ERR_FORMAT);
     if (err && lane == 0) raise_status(a.ctl, tag, err);
     deltas_from_block_words(wmax, lo, hi, d);
   }
@@ -352,18 +354,20 @@ __device__ inline void decompress_tile(const StreamRef& in, float* out_values, u
   }
 }
 
-template <bool IX, bool AVERAGE>
+template <bool IX, bool SELF, bool AVERAGE>
 __global__ __launch_bounds__(kTileThreads, 5) void decompress_kernel(DecompressArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
-  decompress_tile(a.in, a.out, a.out_cap_elems, a.index, 0, a.ctl, a.nonce, false, true, 0, lds, IX, AVERAGE);
+  __shared__ PlainSurvey<1> survey;
+  decompress_tile<IX, SELF, 1>(&a.in, 1, 0, a.out, a.out_cap_elems, a.index, a.ctl, a.nonce, lds, &survey, AVERAGE);
 }
 
 // A part of a stream (see decompress_tile).
-template <bool IX>
+template <bool IX, bool SELF>
 __global__ __launch_bounds__(kTileThreads, 5) void decompress_range_kernel(DecompressArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
-  decompress_tile(a.in, a.out, a.out_cap_elems, a.index, 0, a.ctl, a.nonce, false, true, 0, lds, IX, false, a.first_value,
-                  a.count);
+  __shared__ PlainSurvey<1> survey;
+  decompress_tile<IX, SELF, 1>(&a.in, 1, 0, a.out, a.out_cap_elems, a.index, a.ctl, a.nonce, lds, &survey, false,
+                         a.first_value, a.count);
 }
 
 // k streams in one launch (the tail of the compressed Allgather, Section 3.5.1: every rank
@@ -378,18 +382,12 @@ struct DecompressManyArgs {
   u64 nonce;
 };
 
-template <bool IX>
+template <bool IX, bool SELF>
 __global__ __launch_bounds__(kTileThreads, 5) void decompress_many_kernel(DecompressManyArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
+  __shared__ PlainSurvey<ZC_MAX_K> survey;
   const int s = blockIdx.y;
-  bool all_ok = true;
-  u64 sum_n = 0;
-  if (IX) {                      // any malformed header stops the whole call
-    const StreamsVerdict v = judge_indexed_streams(a.in, a.k, false);
-    all_ok = v.err == 0;
-    sum_n = v.sum_n;
-  }
-  decompress_tile(a.in[s], a.out[s], a.out_cap_elems[s], a.index, s, a.ctl, a.nonce, true, all_ok, sum_n, lds, IX);
+  decompress_tile<IX, SELF, ZC_MAX_K>(a.in, a.k, s, a.out[s], a.out_cap_elems[s], a.index, a.ctl, a.nonce, lds, &survey);
 }
 
 }  // namespace zc

@@ -18,7 +18,7 @@
 // accumulator and its staging take all blocks of at most 15 bits, and most segments that have a
 // wider one (fits_common_path).  The other path (reduce_wide_tile) takes any widths with per-lane
 // loads, a few planes at a time.  Whether any operand has a wide block anywhere is known when a
-// workgroup starts (from the stream index of plain streams, from the version words of indexed
+// workgroup starts (from the width tables of plain streams, from the version words of indexed
 // ones); only in such a call do the waves look where.
 // IX = the streams are indexed (see index_bytes): operands bring the positions of their
 // segments along, which every wave checks against the widths it reads, and the output gets
@@ -35,6 +35,7 @@ struct ReduceArgs {
   StreamRef in[ZC_MAX_K];
   int k;
   StreamIndex index;
+  u32 self;          // plain streams: the kernel sums the width tables itself (see judge_plain_streams)
   u8* out;
   u64 out_cap;
   Control* ctl;
@@ -57,6 +58,7 @@ struct ReduceCall {
   u64 nsum;          // sum of the operands' nsum
   u64 wide_streams;  // bit s: operand s may have blocks wider than 15 bits
   u32 part_end;      // a reduce done in parts: one past the last tile of this part; else 0
+  u32 places;        // plain streams: lane s: payload word offset of the wave's segment in operand s
 };
 
 // Header fields and table padding of the output stream; one thread.
@@ -212,7 +214,7 @@ constexpr int kSumChunk = 4;
 // no load has to be waited for there.
 struct OperandMeta {
   u32 w;            // this lane's block width
-  SegmentOffsetParts seg_off;   // payload word offset of the wave's segment (uniform)
+  u32 seg_off;                  // payload word offset of the wave's segment (uniform)
   u32 seg_end;                  // indexed streams: the payload word offset at which the segment ends (uniform)
   u32 payload_room;             // words between the start of the payload and the end of the caller's buffer (saturated)
 };
@@ -226,23 +228,6 @@ struct OperandPlace {
   u32 src0;         // uniform: payload word index of the aligned start
   u32 room;         // uniform: words from src0 to the end of the caller's buffer
 };
-
-// The tables of operand s for the wave's segment (seg: the same in every lane; b: the lane's
-// block; both fit 32 bits because a stream has at most 2^26 blocks, and so do all byte offsets
-// into the tables).  w_ok and seg_ok say which loads stay inside the stream and the index;
-// they need not be the exact "block exists" conditions (the caller drops what it must not
-// use), which lets a workgroup ask before it knows the header.
-__device__ inline OperandMeta load_operand_tables(const ReduceArgs& a, int s, const StreamRef& in, u32 seg, u32 b, bool w_ok,
-                                                  bool seg_ok, u32 zero = 0) {
-  OperandMeta m;
-  const u8* base = in.base;
-  m.seg_off = SegmentOffsetParts{0, 0, 0};
-  if (seg_ok) m.seg_off = load_segment_offset(a.index, s, seg, zero);
-  m.seg_end = 0;
-  m.payload_room = 0;
-  m.w = w_ok ? u32(*at_bytes(base, kHeaderBytes + b)) : 0u;
-  return m;
-}
 
 __device__ inline i32 load_operand_outlier(const u8* base, const ParsedHeader& h, u32 b, bool active, bool ix) {
   return active ? *reinterpret_cast<const i32*>(at_bytes(base, u32(outliers_begin(h.nb, ix)) + 4u * b)) : 0;
@@ -258,32 +243,34 @@ __device__ inline u32 payload_room(u64 bytes, const ParsedHeader& h, bool ix) {
   return room > 0xffffffffull ? 0xffffffffu : u32(room);   // a stream's payload has at most 2^31 words
 }
 
+// The tables of operand s for the wave's segment (seg: the same in every lane; b: the lane's
+// block; both fit 32 bits because a stream has at most 2^26 blocks, and so do all byte offsets into the tables).
 // The payload is fenced in by the size of the caller's buffer, which a validated stream does
 // not exceed (a 16-byte load may run up to 12 bytes past the stream's own end, inside the
 // buffer; nothing reads those words).
 // An indexed stream (ix) has the segment's position in its own index, and its width bytes
-// behind that index (every stream of a validated call has the header's nb).
-__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const StreamRef& in, const ParsedHeader& h, u32 seg,
+// behind that index (every stream of a validated call has the header's nb); a plain one's is known since the workgroup
+// started (`places`).
+__device__ inline OperandMeta load_operand_meta(int s, const StreamRef& in, const ReduceCall& c, u32 seg,
                                                 u32 b, bool active, bool seg_live, bool ix, u32 zero = 0) {
   OperandMeta m;
+  const u8* base = in.base;
+  m.seg_off = m.seg_end = 0;
   if (ix) {
-    const u8* base = in.base;
-    m.seg_off = SegmentOffsetParts{0, 0, 0};
-    m.seg_end = 0;
     if (seg_live) {
-      m.seg_off = load_segment_offset(a.index, s, seg, zero, base);
+      m.seg_off = load_segment_offset(base, seg, zero);
       m.seg_end = load_segment_end(base, seg, zero);
     }
-    m.w = active ? u32(*at_bytes(base, u32(widths_begin(h.nb, true)) + b)) : 0u;
-  } else {
-    m = load_operand_tables(a, s, in, seg, b, active, seg_live, zero);
+  } else if (seg_live) {
+    m.seg_off = lane_value(c.places, s);
   }
-  m.payload_room = payload_room(in.bytes, h, ix);
+  m.w = active ? u32(*at_bytes(base, u32(widths_begin(c.h.nb, ix)) + b)) : 0u;
+  m.payload_room = payload_room(in.bytes, c.h, ix);
   return m;
 }
-__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const ParsedHeader& h, u32 seg, u32 b, bool active,
+__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const ReduceCall& c, u32 seg, u32 b, bool active,
                                                 bool seg_live, bool ix, u32 zero = 0) {
-  return load_operand_meta(a, s, a.in[s], h, seg, b, active, seg_live, ix, zero);
+  return load_operand_meta(s, a.in[s], c, seg, b, active, seg_live, ix, zero);
 }
 
 // `err`: an indexed stream is checked as it is used: the widths of the segment must add up to
@@ -292,14 +279,13 @@ __device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, cons
 __device__ inline OperandPlace place_operand(const OperandMeta& m, const ParsedHeader& h, bool ix, u32& err, u32 w_max = 15) {
   OperandPlace p;
   // the same in every lane, and long since loaded: into scalar registers, 32-bit arithmetic
-  const u64 seg_off64 = ix ? u64(uniform(m.seg_off.seg)) : uniform64(segment_offset(m.seg_off));
-  const u32 seg_off = u32(seg_off64);
+  const u32 seg_off = uniform(m.seg_off);
   const u32 w = m.w > w_max ? 0u : m.w;        // plain streams: cannot happen here; keeps every LDS access in range
   const u32 words = psize_words(w);
   const u32 incl = wave_inclusive_sum(words);
   const u32 wave_total = lane_value(incl, 63);
   // true on a validated stream
-  bool inside = (seg_off64 >> 32) == 0 && seg_off <= m.payload_room && wave_total <= m.payload_room - seg_off;
+  bool inside = seg_off <= m.payload_room && wave_total <= m.payload_room - seg_off;
   if (ix && (__any(m.w > w_max) || uniform(m.seg_end) - seg_off != wave_total)) {
     err |= status_bit(ZC_ERR_FORMAT);
     inside = false;
@@ -501,16 +487,16 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
     const bool active = b < h.nb;
     if (early) {
       if (!active) meta.w = 0;
+      if (!IX) meta.seg_off = lane_value(c.places, 0);
       if (!seg_live) {
-        meta.seg_off = SegmentOffsetParts{0, 0, 0};
-        meta.seg_end = 0;
+        meta.seg_off = meta.seg_end = 0;
       }
       meta.payload_room = payload_room(a.in[0].bytes, h, IX);
     } else {
-      meta = load_operand_meta(a, 0, h, seg, b, active, seg_live, IX, opaque_zero());
+      meta = load_operand_meta(a, 0, c, seg, b, active, seg_live, IX, opaque_zero());
     }
     next = place_operand(meta, h, IX, err, w_max);
-    if (a.k > 1) meta = load_operand_meta(a, 1, h, seg, b, active, seg_live, IX, opaque_zero());
+    if (a.k > 1) meta = load_operand_meta(a, 1, c, seg, b, active, seg_live, IX, opaque_zero());
     stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
     outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
   }
@@ -533,7 +519,7 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
     outlier += i64(outlier_next);
     if (s + 1 < a.k) {
       next = place_operand(meta, h, IX, err, w_max);
-      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, h, seg, b, active, seg_live, IX, opaque_zero());
+      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, c, seg, b, active, seg_live, IX, opaque_zero());
       stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
       outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
     }
@@ -655,9 +641,7 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
         fits = false;
       }
     } else if (seg_live) {
-      const u64 so = uniform64(segment_offset(a.index, s, seg));
-      fits = so <= pw;
-      seg_off = u32(so);
+      seg_off = lane_value(c.places, s);
     }
     // (cannot fail on a validated stream) the segment lies inside the payload
     if (!fits || seg_off > pw || lane_value(incl, 63) > pw - seg_off) w = 0;
@@ -709,83 +693,70 @@ __device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall&
 }
 
 // What every workgroup of a reduce kernel does first: the call's verdict, tag and header, and its tile.
-// Returns false when the workgroup has nothing (more) to do.  Plain streams (IX false) have
-// been validated and indexed by the kernels of zc_scan.h, whose verdict and tag are in the
-// control block; indexed streams are judged here, by every workgroup alike, from their headers.
+// Returns false when the workgroup has nothing (more) to do.  The headers, and the width tables of plain streams, are
+// judged here, by every workgroup alike.
 // `meta`, `early`: see sum_common.
 template <bool IX>
 __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMeta& meta, bool early, u32& tile, u32& ntiles,
-                                   u32* sh_tile) {
+                                   u32* sh_tile, PlainSurvey<IX ? 1 : ZC_MAX_K>* survey) {
   c.ltag = launch_tag(a.nonce, a.ctl);
   // (with tickets the ticket is asked for first of all: its round trip runs beside the headers')
   u64 asked = 0;
   if (a.ticketed && threadIdx.x == 0) asked = ask_ticket(ticket_counter(a.ctl, ticket_shard()));
-  if (IX) {
-    if (early) {
+  const int wave = wave_id();
+  tile = a.first_tile + blockIdx.x;          // tiles in the order in which workgroups start
+  SurveyLoads ask{};
+  if (!IX) ask = ask_plain_streams<ZC_MAX_K>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
+  if (early) {
+    const u32 seg = tile * kTileWaves + u32(wave);      // < 2^22: the host launches at most 2^18 tiles
+    const u32 b = seg * kWaveBlocks + u32(fresh_lane());
+    const u8* base = a.in[0].base;
+    const u32 zero = opaque_zero();
+    meta.seg_off = meta.seg_end = 0;
+    if (IX) {
       // the caller has said what n is (a reduce in parts): where the first operand's tables are follows from
       // that, and they are asked for together with the headers; a stream of another n ends the call below
       const u32 nb_said = u32(num_blocks(a.n_part));
-      const u32 seg = (a.first_tile + blockIdx.x) * kTileWaves + u32(wave_id());
-      const u32 b = seg * kWaveBlocks + u32(fresh_lane());
-      const u8* base = a.in[0].base;
-      const u32 zero = opaque_zero();
       const bool seg_ok = seg < num_segments(nb_said) && u64(kHeaderBytes) + 4ull * seg + 8 <= a.in[0].bytes;
       const bool w_ok = b < nb_said && widths_begin(nb_said, true) + b < a.in[0].bytes;
-      meta.seg_off = SegmentOffsetParts{0, 0, 0};
-      meta.seg_end = 0;
       if (seg_ok) {
-        meta.seg_off = load_segment_offset(a.index, 0, seg, zero, base);
+        meta.seg_off = load_segment_offset(base, seg, zero);
         meta.seg_end = load_segment_end(base, seg, zero);
       }
       meta.w = w_ok ? u32(*at_bytes(base, u32(widths_begin(nb_said, true)) + b + zero)) : 0u;
+    } else {
+      meta.w = u64(kHeaderBytes) + b < a.in[0].bytes ? u32(*at_bytes(base, kHeaderBytes + b)) : 0u;
     }
-    const StreamsVerdict v = judge_indexed_streams(a.in, a.k, true);
-    // (a later part of a reduce done in parts belongs to the call its first part opened)
-    c.tag = call_tag(a.ctl, c.ltag, a.adopt != 0);
-    c.h = v.h0;
-    c.nsum = v.nsum;
-    c.wide_streams = v.wide;
-    if (v.err) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (!a.adopt) a.ctl->result = 0;
-        raise_status(a.ctl, c.tag, v.err);
-      }
-      return false;
+  }
+  StreamsVerdict v = judge_headers<IX>(a.in, a.k, true);
+  // (a later part of a reduce done in parts belongs to the call its first part opened)
+  c.tag = call_tag(a.ctl, c.ltag, a.adopt != 0);
+  c.places = 0;
+  if (!IX) c.places = judge_plain_streams(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
+  c.h = v.h0;
+  c.nsum = v.nsum;
+  c.wide_streams = v.wide;
+  if (v.err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (!a.adopt) a.ctl->result = 0;
+      raise_status(a.ctl, c.tag, v.err);
     }
-    if (a.n_part && a.n_part != c.h.n) {      // the parts were laid out for another n
-      if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, c.tag, status_bit(ZC_ERR_MISMATCH));
-      return false;
-    }
-  } else {
-    const u32 zero = opaque_zero();
-    if (early) {
-      const u32 seg = blockIdx.x * kTileWaves + u32(wave_id());     // < 2^22: the host launches at most 2^18 tiles
-      const u32 b = seg * kWaveBlocks + u32(fresh_lane());
-      meta = load_operand_tables(a, 0, a.in[0], seg, b, u64(kHeaderBytes) + b < a.in[0].bytes, seg < 4 * a.index.tiles_cap, zero);
-    }
-    const uint4 gate_raw = load_gate(a.ctl, zero);
-    const HeaderWords hw = load_header_words(a.in[0].base, zero);
-    c.h = parse_header(hw, a.in[0].bytes, false);
-    const Gate gate = parse_gate(gate_raw);
-    c.tag = gate.tag;
-    if (gate_failed(gate) || !c.h.ok) return false;
-    c.wide_streams = gate_wide(gate) ? ~u64(0) : 0;
-    c.nsum = 0;
+    return false;
+  }
+  if (a.n_part && a.n_part != c.h.n) {      // the parts were laid out for another n
+    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, c.tag, status_bit(ZC_ERR_MISMATCH));
+    return false;
   }
   ntiles = u32(num_tiles(c.h.nb));
   const u32 end_tile = a.end_tile && a.end_tile < ntiles ? a.end_tile : ntiles;
   c.part_end = a.end_tile ? end_tile : 0u;
-  if (blockIdx.x == 0 && threadIdx.x == 0 && a.first_tile == 0) {
-    if (!IX) c.nsum = a.ctl->nsum;           // of all operands, summed by the validation kernel
-    write_reduce_header(a, c, ntiles, IX);
-  }
+  if (blockIdx.x == 0 && threadIdx.x == 0 && a.first_tile == 0) write_reduce_header(a, c, ntiles, IX);
   if (ntiles == 0) {                         // streams without blocks: their one index entry must say so
-    if (IX && blockIdx.x == 0 && wave_id() == 0 && !index_ends_consistent(a.in, a.k, c.h, 0) && lane_id() == 0)
+    if (IX && blockIdx.x == 0 && wave == 0 && !index_ends_consistent(a.in, a.k, c.h, 0) && lane_id() == 0)
       raise_status(a.ctl, c.tag, status_bit(ZC_ERR_FORMAT));
     return false;
   }
   if (a.first_tile >= end_tile) return false;
-  tile = a.first_tile + blockIdx.x;          // tiles in the order in which workgroups start
   if (a.ticketed) {                          // ... or handed out by tickets, see take_tile
     if (threadIdx.x == 0) {
       const u32 t = take_tile(a.ctl, c.ltag, end_tile - a.first_tile, ticket_shard(), asked);
@@ -793,15 +764,19 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
     }
     __syncthreads();
     tile = uniform(*sh_tile);
+    if (!IX && tile < end_tile) {            // (the verdict stands: once more, for the place of this tile)
+      ask = ask_plain_streams<ZC_MAX_K>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
+      c.places = judge_plain_streams(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
+    }
   }
   return tile < end_tile;
 }
 
-// One launch per call, whatever the widths (plain streams: behind the two of zc_scan.h, and with a workgroup less
+// One launch per call, whatever the widths (many plain streams: behind the one of zc_scan.h; plain ones with a workgroup less
 // per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
 // but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
-// 80 registers and 24 bytes of scratch (plain streams: 96 and 68), which the common path touches behind its
+// 80 registers and 24 bytes of scratch (plain streams: 96 and 28), which the common path touches behind its
 // operand loop only: what the placement needs waits there.
 template <bool IX>
 __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
@@ -809,6 +784,7 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
 
   ReduceCall c;
   OperandMeta meta{};
@@ -818,7 +794,7 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   // indexed streams: where their width bytes are is only known with the header.)
   const bool early = !a.ticketed && (!IX || a.n_part != 0);
   u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, c, meta, early, tile, ntiles, &sh_tile)) return;
+  if (!open_reduce<IX>(a, c, meta, early, tile, ntiles, &sh_tile, &survey)) return;
   // The segment number stays a scalar: in a vector register, with all the addresses that follow from it, it made the
   // kernel spill in the operand loops.  (Plain streams of nothing but wide blocks, 4 x 4 194 301 values: 43.7 us, now
   // 41.0; 16 x 100 003 hard values 33.6 and 32.2; 8 x 2^24 smooth ones 53.6 and 52.9.)  What the waves ask for two

@@ -121,21 +121,23 @@ struct OperandPipe {
   // Where operands s, s + 1 and s + 2 are, asked for a step before it is needed.
   StreamRef at0, at1, at2;
 
-  __device__ __forceinline__ void open(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32& err) {
+  __device__ __forceinline__ void open(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32& err) {
+    const ParsedHeader& h = c.h;
     at0 = a.in[0];
     at1 = a.in[min(1, a.k - 1)];
     at2 = a.in[min(2, a.k - 1)];
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
     const bool active = b < h.nb;
-    meta = load_operand_meta(a, 0, h, share.seg, b, active, share.live, IX, opaque_zero());
+    meta = load_operand_meta(a, 0, c, share.seg, b, active, share.live, IX, opaque_zero());
     next = place_operand(meta, h, IX, err);
-    if (a.k > 1) meta = load_operand_meta(a, 1, h, share.seg, b, active, share.live, IX, opaque_zero());
+    if (a.k > 1) meta = load_operand_meta(a, 1, c, share.seg, b, active, share.live, IX, opaque_zero());
     stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tables_end(h.nb, IX)), next, lane);
     outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
   }
   // Operand s into the staging area.
-  __device__ __forceinline__ void take(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, int s, u32* wl, u32& err) {
+  __device__ __forceinline__ void take(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32* wl, u32& err) {
+    const ParsedHeader& h = c.h;
     const StreamRef here = at0, ahead1 = at1, ahead2 = at2;
     at0 = at1;
     at1 = at2;
@@ -150,7 +152,7 @@ struct OperandPipe {
     first = outlier_next;
     if (s + 1 < a.k) {
       next = place_operand(meta, h, IX, err);
-      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, ahead2, h, share.seg, b, active, share.live, IX, opaque_zero());
+      if (s + 2 < a.k) meta = load_operand_meta(s + 2, ahead2, c, share.seg, b, active, share.live, IX, opaque_zero());
       stage = load_operand_payload(reinterpret_cast<const u32*>(ahead1.base + tend), next, lane);
       outlier_next = load_operand_outlier(ahead1.base, h, b, active, IX);
     }
@@ -188,7 +190,7 @@ __device__ inline void meet_far_codes(u32 (&acc)[16], u32 (&f)[16], i32 ahead) {
 // The common path: the extremes of as many operands as it can take (returned, uniform).  If that is not all, the next
 // one is decoded: f = its codes modulo 2^16, `from` what the first of them starts from.
 template <bool IX, int OP>
-__device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+__device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                               OperandPipe<IX>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
   base = pipe.outlier_next;
   // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits: no
@@ -203,7 +205,7 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ParsedH
   u32 going = 1;
 #pragma nounroll
   while (going) {
-    pipe.take(a, h, share, s, wl, err);
+    pipe.take(a, c, share, s, wl, err);
     const u32 apart = u32(pipe.first) - u32(base);
     const bool far = apart + u32(kNearFirst) >= u32(2 * kNearFirst);
     const u32 start = ((far ? 0u : apart) + u32(kCodeBias<OP>)) & 0xffffu;
@@ -318,7 +320,7 @@ __device__ __forceinline__ void close_any(i32 (&acc)[32], bool active, ExtremeBl
 
 // The operands from s on, none of them with wide blocks, in 32 bits.  f: the deltas of operand s.
 template <bool IX, int OP>
-__device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+__device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                              OperandPipe<IX>& pipe, i32 (&acc)[32], u32 (&f)[16], int s, u32& err) {
 #pragma nounroll
   for (;;) {
@@ -329,7 +331,7 @@ __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ParsedHe
       acc[j] = extreme<OP>(acc[j], i32(code));
     }
     if (++s >= a.k) return;
-    pipe.take(a, h, share, s, wl, err);
+    pipe.take(a, c, share, s, wl, err);
     operand_delta_pairs(pipe.cur, wl, f);
     wave_lds_sync();
   }
@@ -337,13 +339,13 @@ __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ParsedHe
 
 // Operands without wide blocks.  True: they are in `out` (the common path has taken them all), false: in acc.
 template <bool IX, int OP>
-__device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const ParsedHeader& h, const ReduceShare& share, u32* wl,
+__device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                                ExtremeBlock& out, i32 (&acc)[32], u32& err) {
   OperandPipe<IX> pipe;
-  pipe.open(a, h, share, err);
+  pipe.open(a, c, share, err);
   u32 pairs[16], f[16], from = 0;
   i32 base;
-  const int s = extreme_packed<IX, OP>(a, h, share, wl, pipe, pairs, f, from, base, err);
+  const int s = extreme_packed<IX, OP>(a, c, share, wl, pipe, pairs, f, from, base, err);
   if (s == a.k) {
     close_packed<OP>(pairs, base, out);
     return true;
@@ -358,7 +360,7 @@ __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const Parsed
     const i32 code = base + i32(i16x2_t(as_pair(pairs[j & 15]))[j >> 4]) - kCodeBias<OP>;
     acc[j] = s ? code : OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
   }
-  extreme_rest<IX, OP>(a, h, share, wl, pipe, acc, f, s, err);
+  extreme_rest<IX, OP>(a, c, share, wl, pipe, acc, f, s, err);
   return false;
 }
 
@@ -373,7 +375,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
   OperandMeta meta;
   {
     const u32 b = share.seg * kWaveBlocks + u32(fresh_lane());
-    meta = load_operand_meta(a, 0, h, share.seg, b, b < h.nb, share.live, IX, opaque_zero());
+    meta = load_operand_meta(a, 0, c, share.seg, b, b < h.nb, share.live, IX, opaque_zero());
   }
 #pragma nounroll
   for (int s = 0; s < a.k; ++s) {
@@ -385,7 +387,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
     u32 code = u32(load_operand_outlier(a, s, h, b, active, IX));
     if (!__any(cur.w > 15)) {
       const OperandStage stage = load_operand_payload(payload, cur, lane);
-      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX, opaque_zero());
+      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, c, share.seg, b, active, share.live, IX, opaque_zero());
       stage_to_lds(stage, cur, payload, wl, lane);
       wave_lds_sync();
       u32 f[16];
@@ -399,7 +401,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
         acc[j] = extreme<OP>(acc[j], i32(code));
       }
     } else {
-      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, h, share.seg, b, active, share.live, IX, opaque_zero());
+      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, c, share.seg, b, active, share.live, IX, opaque_zero());
       u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
@@ -435,11 +437,12 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
 
   ReduceCall c;
   OperandMeta meta{};
   u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, c, meta, false, tile, ntiles, &sh_tile)) return;
+  if (!open_reduce<IX>(a, c, meta, false, tile, ntiles, &sh_tile, &survey)) return;
   const ParsedHeader& h = c.h;
   const int wave = wave_id();
   const u64 tend = tables_end(h.nb, IX);
@@ -453,7 +456,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   i32 codes[32];
   bool closed = false;
   if (c.wide_streams) extreme_any<IX, OP>(a, c, share, wl, codes, err);
-  else closed = extreme_narrow<IX, OP>(a, h, share, wl, eb, codes, err);
+  else closed = extreme_narrow<IX, OP>(a, c, share, wl, eb, codes, err);
   if (!closed) close_any(codes, share.seg * kWaveBlocks + u32(fresh_lane()) < h.nb, eb, err);
 
   const int lane = fresh_lane();

@@ -1,16 +1,13 @@
 // Block positions of an existing stream: header validation and the exclusive prefix sum of
 // the block sizes implied by its width table (Section 3.3 stores one code length per block;
 // a block's position is the sum of the sizes before it), kept per segment of 64 blocks, the
-// share of one wave.  An indexed stream (Section 3.5.2) brings these positions along: neither
-// kernel of this file runs for it; the main kernels judge the headers themselves
-// (judge_indexed_streams) and every wave of a consumer checks that its own segment's entries
+// share of one wave.  An indexed stream (Section 3.5.2) brings these positions along: the main kernels judge the headers
+// (judge_headers) and every wave of a consumer checks that its own segment's entries
 // agree with its width bytes and with the ends of the index, which together is the whole index.
 //
-// stream_index_kernel records the offset of every segment inside its scan group, of every
-// group inside its index span and the size of every span, and validates header and width
-// bytes on the way; index_prep_kernel then turns the span sizes into offsets, compares the
-// header's total_bytes with the indexed payload and writes the control block.  No workgroup
-// waits for, or counts, another, and neither kernel needs anything cleared beforehand.
+// stream_index_kernel records the offset of every segment inside its index span and the size of
+// every span, with what it has seen in the width bytes; the main kernels add up the spans and judge header and widths (judge_plain_streams).  No workgroup
+// waits for, or counts, another, and nothing needs to be cleared beforehand.  Streams of few blocks go without it.
 #pragma once
 
 #include "zc_common.h"
@@ -63,9 +60,8 @@ __device__ inline ParsedHeader parse_header(const StreamRef& s, bool ix) {
   return parse_header_words(w, s.bytes, ix);
 }
 
-// The same for a main kernel's first instructions: the header (and with load_gate the control
-// block) is asked for with vector loads (see opaque_zero), so that it travels together with
-// whatever else the kernel can ask for before it knows the header.  The stream must have
+// The same for a main kernel's first instructions: the header is asked for with vector loads
+// (see opaque_zero), so that it travels together with whatever else the kernel can ask for before it knows the header.  The stream must have
 // at least kHeaderBytes bytes (the host checks that before it launches anything).
 struct HeaderWords {
   uint4 lo, hi;
@@ -84,79 +80,27 @@ __device__ inline ParsedHeader parse_header(const HeaderWords& hw, u64 bytes, bo
   return parse_header_words(w, bytes, ix);
 }
 
-// What a main kernel that reads plain streams finds in the control block: the call's tag and
-// the verdict of the validation kernel that ran ahead of it (final before the main kernel starts).
-struct Gate {
-  u64 tag;
-  u32 bits;
-};
-
-__device__ inline uint4 load_gate(const Control* ctl, u32 zero) {
-  return *reinterpret_cast<const uint4*>(at_bytes(reinterpret_cast<const u8*>(ctl), zero));
-}
-
-__device__ inline Gate parse_gate(uint4 raw) {
-  Gate g;
-  g.tag = u64(uniform(raw.z)) | (u64(uniform(raw.w)) << 32);
-  g.bits = uniform(raw.y) == u32(g.tag >> 32) ? uniform(raw.x) : 0u;
-  return g;
-}
-
-__device__ inline bool gate_failed(const Gate& g) { return (g.bits & kGateBits) != 0; }
-__device__ inline bool gate_wide(const Gate& g) { return (g.bits & kStatusWide) != 0; }
-
 struct ScanArgs {
   StreamRef streams[ZC_MAX_K];
   int k;
-  int check_match;   // reduce: every stream must have the n and eb_bits of stream 0
   StreamIndex index;
-  Control* ctl;
-  u64 nonce;         // drawn by the host per call, goes into the call's tag (see launch_tag)
 };
 
-constexpr u32 kSpanBadWidth = 1u;   // per-span flags left by stream_index_kernel: a width byte above 31
-constexpr u32 kSpanWide = 2u;       //                                               a width byte above 15
+// An entry of the list of spans: its payload words (less than 2^24), and whether it has a width byte above 31 and one
+// above 15.
+constexpr u32 kSpanSize = (1u << 30) - 1u;
+constexpr u32 kSpanBadWidth = 1u << 30;
+constexpr u32 kSpanWide = 1u << 31;
 
 // Whether the caller's workspace has room for the index of this stream.
 __device__ inline bool stream_fits(const ParsedHeader& h, const StreamIndex& ix) {
-  return num_tiles(h.nb) <= ix.tiles_cap && num_scan_groups(h.nb) <= ix.groups_cap && num_spans(h.nb) <= ix.spans_cap;
+  return num_tiles(h.nb) <= ix.tiles_cap && num_spans(h.nb) <= ix.spans_cap;
 }
 
-// Payload word offset of segment `seg` of stream `s`: the offset of its index span, plus its
-// group's offset in the span, plus its own offset in the group: three independent loads.
-// The parts are kept apart until the sum is needed.  Summing them where they are loaded makes
-// the compiler wait for two of the loads before it issues the third, which puts two memory
-// round trips where one will do.
-struct SegmentOffsetParts {
-  u32 span, grp, seg;
-};
-
-// `zero`: 0, or opaque_zero() to have vector loads whatever the compiler knows about seg.
-// An indexed stream has the sum in its own index (`base`: the stream): one load.
-__device__ inline SegmentOffsetParts load_segment_offset(const StreamIndex& ix, int s, u64 seg, u32 zero = 0,
-                                                         const u8* base = nullptr) {
-  SegmentOffsetParts p;
-  if (base) {
-    p.span = 0;
-    p.grp = 0;
-    p.seg = *reinterpret_cast<const u32*>(at_bytes(base, kHeaderBytes + 4u * u32(seg) + zero));
-    return p;
-  }
-  p.span = ix.span_off[u64(s) * ix.spans_cap + seg / kSpanSegs + zero];
-  p.grp = ix.grp_off[u64(s) * ix.groups_cap + seg / kScanGroupSegs + zero];
-  p.seg = ix.seg_off[u64(s) * 4 * ix.tiles_cap + seg + zero];
-  return p;
-}
-
-// The three loads above are in flight together when this is reached: nothing may use one of
-// the parts before all of them have been asked for.
-__device__ inline u64 segment_offset(SegmentOffsetParts p) {
-  asm volatile("" : "+v"(p.span), "+v"(p.grp), "+v"(p.seg));
-  return u64(p.span) + u64(p.grp) + u64(p.seg);
-}
-
-__device__ inline u64 segment_offset(const StreamIndex& ix, int s, u64 seg) {
-  return segment_offset(load_segment_offset(ix, s, seg));
+// Payload word offset of segment `seg` of an indexed stream, from its own index.  `zero`: 0, or opaque_zero() to have a
+// vector load whatever the compiler knows about seg.
+__device__ inline u32 load_segment_offset(const u8* base, u32 seg, u32 zero = 0) {
+  return *reinterpret_cast<const u32*>(at_bytes(base, kHeaderBytes + 4u * seg + zero));
 }
 
 // The entry after a segment's own in the index of an indexed stream: where the segment ends.
@@ -164,29 +108,44 @@ __device__ inline u32 load_segment_end(const u8* base, u32 seg, u32 zero = 0) {
   return *reinterpret_cast<const u32*>(at_bytes(base, kHeaderBytes + 4u + 4u * seg + zero));
 }
 
-// Payload words of the four blocks whose width bytes are packed in x, and whether any byte
-// exceeds 31 (bad) or 15 (wide).  Sum of (1 + w) over the non-zero bytes = byte sum + number of non-zero bytes.
-__device__ inline u32 psize_words4(u32 x, bool& bad, bool& wide) {
-  bad |= (x & 0xE0E0E0E0u) != 0;
-  wide |= (x & 0xF0F0F0F0u) != 0;
+// Payload words of the four blocks whose width bytes are packed in x, added to `sum`.  Sum of (1 + w) over the non-zero
+// bytes = byte sum + number of non-zero bytes.
+__device__ inline u32 psize_words4(u32 x, u32 sum) {
   const u32 nonzero = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;   // top bit of every non-zero byte
-  return __builtin_amdgcn_sad_u8(x, 0u, u32(__builtin_popcount(nonzero)));
+  return __builtin_amdgcn_sad_u8(x, 0u, sum + u32(__builtin_popcount(nonzero)));
 }
 
-// A workgroup covers one index span: kIndexGroups scan groups of 4096 blocks (64 segments)
-// of one stream.  Each thread takes 16 blocks of a group (one 16-byte load of the width
-// table), four threads make a segment; a scan over the workgroup gives every segment its
-// offset inside the group, every group its offset inside the span, and the span its size.
+// The same for 16 blocks from block b0 on of a table of nb (`seen`: OR of the width bytes; bytes behind nb do not count).
+__device__ inline u32 psize_words16(const uint4& v, u32 b0, u32 nb, u32& seen) {
+  u32 x[4] = {v.x, v.y, v.z, v.w};
+  if (b0 + 16 > nb) {
+    const u32 live = nb > b0 ? nb - b0 : 0u;           // 0..15 bytes exist
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[j] &= live >= 4u * j + 4 ? 0xFFFFFFFFu : (live > 4u * j ? (1u << (8 * (live - 4u * j))) - 1u : 0u);
+  }
+  u32 sum = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    seen |= x[j];
+    sum = psize_words4(x[j], sum);
+  }
+  return sum;
+}
+constexpr u32 kBadWidths = 0xE0E0E0E0u;                // bits of a width byte above 31 ...
+constexpr u32 kWideWidths = 0xF0F0F0F0u;               // ... and above 15
+
+// A workgroup covers one index span of one stream.  Each thread takes 16 blocks of a group of 4096 (one 16-byte load of
+// the width table), four threads make a segment; a scan over the workgroup gives every segment its offset inside the
+// group, the groups' totals the rest, and the span its size.
 __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
   __shared__ u32 sh_wave[kIndexGroups][4];
   __shared__ u32 sh_flags;
   const int s = blockIdx.y;
   const StreamRef st = a.streams[s];
   const ParsedHeader h = parse_header(st, false);
-  if (!h.ok || !stream_fits(h, a.index)) return;        // index_prep_kernel reports both
-  const u64 ngroups = num_scan_groups(h.nb);
+  if (!h.ok || !stream_fits(h, a.index)) return;        // judge_plain_streams reports both
   const u64 group0 = u64(blockIdx.x) * kIndexGroups;
-  if (group0 >= ngroups) return;
+  if (u64(blockIdx.x) >= num_spans(h.nb)) return;
 
   const int lane = lane_id();
   const int wave = int(threadIdx.x) >> 6;
@@ -197,32 +156,22 @@ __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
   uint4 v[kIndexGroups];
 #pragma unroll
   for (int i = 0; i < kIndexGroups; ++i) {
-    const u64 b0 = (group0 + u64(i)) * kScanGroupBlocks + u64(threadIdx.x) * 16;
+    const u64 b0 = (group0 + u64(i)) * kIndexGroupBlocks + u64(threadIdx.x) * 16;
     v[i] = make_uint4(0, 0, 0, 0);
     if (b0 < h.nb) v[i] = *reinterpret_cast<const uint4*>(widths + b0);
   }
   u32 sum[kIndexGroups], incl[kIndexGroups];
-  bool bad = false, wide = false;
+  u32 seen = 0;
 #pragma unroll
   for (int i = 0; i < kIndexGroups; ++i) {
-    const u64 b0 = (group0 + u64(i)) * kScanGroupBlocks + u64(threadIdx.x) * 16;
-    u32 x[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-    if (b0 < h.nb && b0 + 16 > h.nb) {
-      const u32 live = u32(h.nb - b0);                 // 1..15 bytes exist
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const u32 keep = live >= 4u * j + 4 ? 0xFFFFFFFFu : (live > 4u * j ? (1u << (8 * (live - 4u * j))) - 1u : 0u);
-        x[j] &= keep;
-      }
-    }
-    sum[i] = psize_words4(x[0], bad, wide) + psize_words4(x[1], bad, wide) + psize_words4(x[2], bad, wide) +
-             psize_words4(x[3], bad, wide);
+    const u64 b0 = (group0 + u64(i)) * kIndexGroupBlocks + u64(threadIdx.x) * 16;
+    sum[i] = psize_words16(v[i], u32(b0), u32(h.nb), seen);
     incl[i] = wave_inclusive_sum(sum[i]);
     if (lane == 63) sh_wave[i][wave] = incl[i];
   }
+  const bool bad = (seen & kBadWidths) != 0, wide = (seen & kWideWidths) != 0;
   __syncthreads();                                       // sh_flags cleared, wave sums visible
   if (bad || wide) atomicOr(&sh_flags, (bad ? kSpanBadWidth : 0u) | (wide ? kSpanWide : 0u));
-  u32* grp = a.index.grp_off + u64(s) * a.index.groups_cap;
   u32* seg_off = a.index.seg_off + u64(s) * 4 * a.index.tiles_cap;
   const u64 nsegs = num_segments(h.nb);
   u32 span_before = 0;                                   // payload words of the span's groups so far
@@ -235,82 +184,17 @@ __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
       if (j < wave) before += t;
       all += t;
     }
-    const u64 seg = (group0 + u64(i)) * kScanGroupSegs + (threadIdx.x >> 2);
-    if ((threadIdx.x & 3) == 0 && seg < nsegs) seg_off[seg] = before + incl[i] - sum[i];
-    if (threadIdx.x == 0 && group0 + u64(i) < ngroups) grp[group0 + u64(i)] = span_before;
+    const u64 seg = (group0 + u64(i)) * kIndexGroupSegs + (threadIdx.x >> 2);
+    if ((threadIdx.x & 3) == 0 && seg < nsegs) seg_off[seg] = span_before + before + incl[i] - sum[i];
     span_before += all;
   }
   __syncthreads();                                       // every thread's flags are in
-  if (threadIdx.x == 0) {
-    const u64 slot = u64(s) * a.index.spans_cap + blockIdx.x;
-    a.index.span_off[slot] = span_before;                // its size; index_prep_kernel makes it an offset
-    a.index.span_flags[slot] = sh_flags;
-  }
-}
-
-// Second step of the index of plain streams, and the first launch of the call as far as its
-// tag goes; one workgroup for all streams.  Each wave takes streams (wave, wave + 4, ...):
-// validates the header, turns the span sizes into exclusive offsets in place, collects the
-// spans' flags and checks that the header's total_bytes equals tables + payload.  Thread 0 then
-// writes the control block: the call's tag, the verdict under that tag, the operands' nsum.
-__global__ __launch_bounds__(256) void index_prep_kernel(ScanArgs a) {
-  __shared__ u32 sh_status[4], sh_wide[4];
-  __shared__ unsigned long long sh_nsum;        // sum of the valid streams' nsum, for the kernel that writes a stream
-  if (threadIdx.x == 0) sh_nsum = 0;
-  __syncthreads();
-  const u64 tag = launch_tag(a.nonce, a.ctl);
-  const int lane = lane_id();
-  const int wave = int(threadIdx.x) >> 6;
-  u32 status = 0, wide = 0;
-  ParsedHeader h0;
-  h0.ok = false;
-  if (a.check_match) h0 = parse_header(a.streams[0], false);
-  for (int s = wave; s < a.k; s += 4) {
-    const ParsedHeader h = parse_header(a.streams[s], false);
-    if (!h.ok) {
-      status |= status_bit(ZC_ERR_FORMAT);
-      continue;
-    }
-    if (!stream_fits(h, a.index)) {
-      status |= status_bit(ZC_ERR_ARG);
-      continue;
-    }
-    if (a.check_match && h0.ok && (h0.n != h.n || h0.eb_bits != h.eb_bits)) status |= status_bit(ZC_ERR_MISMATCH);
-    if (lane == 0) atomicAdd(&sh_nsum, static_cast<unsigned long long>(h.nsum));
-    const u64 nspans = num_spans(h.nb);
-    u32* spans = a.index.span_off + u64(s) * a.index.spans_cap;
-    const u32* flags = a.index.span_flags + u64(s) * a.index.spans_cap;
-    u64 carry = 0;
-    u32 seen = 0;
-    for (u64 start = 0; start < nspans; start += 64) {
-      const u64 i = start + u64(lane);
-      const u32 val = i < nspans ? spans[i] : 0u;
-      seen |= i < nspans ? flags[i] : 0u;
-      const u32 inc = wave_inclusive_sum(val);
-      if (i < nspans) spans[i] = u32(carry) + inc - val;
-      carry += lane_value(inc, 63);
-    }
-    if (__any((seen & kSpanBadWidth) != 0)) status |= status_bit(ZC_ERR_FORMAT);
-    if (__any((seen & kSpanWide) != 0)) wide = kStatusWide;
-    if (tables_end(h.nb, false) + 4 * carry != h.total) status |= status_bit(ZC_ERR_FORMAT);
-  }
-  if (lane == 0) {
-    sh_status[wave] = status;
-    sh_wide[wave] = wide;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const u32 bits = sh_status[0] | sh_status[1] | sh_status[2] | sh_status[3] | sh_wide[0] | sh_wide[1] | sh_wide[2] | sh_wide[3];
-    a.ctl->status = (tag & 0xffffffff00000000ull) | bits;
-    a.ctl->call_tag = tag;
-    a.ctl->result = 0;
-    a.ctl->nsum = sh_nsum;
-  }
+  if (threadIdx.x == 0) a.index.spans[u64(s) * a.index.spans_cap + blockIdx.x] = span_before | sh_flags;
 }
 
 // ---------------------------------------------------------------------------------------
-// Indexed streams need no launch ahead of the main kernel: every workgroup reads the headers
-// of all input streams itself and comes to the same verdict, and every wave checks the part
+// The main kernels read the headers of all input streams themselves, every workgroup, and come to the same verdict.
+// Indexed streams need no launch ahead of them: every wave checks the part
 // of the index it uses (the entries of its segment against its width bytes; the wave of the
 // first segment that entry 0 is 0, the wave of the last that the closing entry accounts for
 // total_bytes), which together is the whole index.
@@ -324,10 +208,12 @@ struct StreamsVerdict {
   u32 err;              // status bits: FORMAT, MISMATCH (uniform)
   u64 nsum;             // sum of the nsum fields of the valid streams
   u64 sum_n;            // sum of their n fields
-  u64 wide;             // bit s: stream s may hold blocks wider than 15 bits (uniform)
+  u64 wide;             // bit s: stream s may hold blocks wider than 15 bits (uniform; plain streams: see judge_plain_streams)
+  ParsedHeader mine;    // lane s: header of stream s
 };
 
-__device__ inline StreamsVerdict judge_indexed_streams(const StreamRef* streams, int k, bool check_match) {
+template <bool IX>
+__device__ inline StreamsVerdict judge_headers(const StreamRef* streams, int k, bool check_match) {
   const int lane = lane_id();
   const bool mine = lane < k;
   u32 w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -339,8 +225,9 @@ __device__ inline StreamsVerdict judge_indexed_streams(const StreamRef* streams,
     w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
     w[4] = hi.x; w[5] = hi.y; w[6] = hi.z; w[7] = hi.w;
   }
-  const ParsedHeader h = parse_header_words(w, bytes, true);
+  const ParsedHeader h = parse_header_words(w, bytes, IX);
   StreamsVerdict v;
+  v.mine = h;
   v.h0.n = u64(lane_value(u32(h.n), 0)) | (u64(lane_value(u32(h.n >> 32), 0)) << 32);
   v.h0.nb = num_blocks(v.h0.n);
   v.h0.total = u64(lane_value(u32(h.total), 0)) | (u64(lane_value(u32(h.total >> 32), 0)) << 32);
@@ -392,6 +279,184 @@ __device__ inline bool index_ends_consistent(const StreamRef* streams, int k, co
     }
   }
   return !__any(bad);
+}
+
+// ---------------------------------------------------------------------------------------
+// Plain streams store no positions, so their width tables have to be summed, whole: the sums say where a segment is,
+// whether every width is in order and whether total_bytes is.  Streams of few blocks are summed by every workgroup of the
+// main kernel for itself (`self`), with the table asked for together with the header; for others stream_index_kernel
+// runs ahead and a workgroup only adds up the sizes of the spans.  Either way all workgroups come to the same verdict before
+// anything is written.  What this saves is launches (a dependent one costs 3 to 4 us, however little it does): with two
+// ahead of the main kernel decompress took 10.4 us for a few thousand values (now 5.1) and 63.6 for 2^26 (61.5), a ring
+// round of 40 000 values 13.4 (7.7), the Sum of 8 x 2^20 23.8 (20.0), a round trip of 20 000 003 values 53.5 (50.3).
+// ---------------------------------------------------------------------------------------
+
+// What the waves of a workgroup tell each other about up to K streams, four words each: unit s * parts + p is part p of
+// stream s (see survey_parts).
+template <int K>
+struct PlainSurvey {
+  u32 before[4 * K];        // payload words before the workgroup's tile (self) or its span
+  u32 total[4 * K];         // payload words
+  u32 seen[4 * K];          // OR of the width bytes (of the spans' flags)
+  u32 in_tile[4 * K];       // self: per segment of the tile, payload words of the tile before it
+};
+
+// Tiles of all streams of a call together up to which every workgroup sums their tables itself: the work grows with the
+// square of the tiles, the launch it saves does not.  us per call, with the launch and without:
+//   decompress   1 tile 9.0 5.1 | 128: 9.6 6.2 | 489: 11.5 12.0 | 2048: 20.1 70
+//   8 buffers    8 x 33 tiles 12.3 11.0 | 8 x 128: 15.4 27;   Sum of 8   8 x 1 21.6 17.1 | 8 x 33 20.4 18.6 | 8 x 128 21.2 26.2
+constexpr u64 kSelfTiles = 512;
+
+// Waves that share a stream's table.
+__device__ inline u32 survey_parts(int k, bool self) { return !self ? 1u : k == 1 ? 4u : k == 2 ? 2u : 1u; }
+
+// Two loads of a width table by one wave, 1024 blocks each, `stride` blocks apart.  Fenced in by the caller's buffer (the
+// table is padded to 16 bytes, so a piece of it never reaches beyond): what the header rules out is dropped later.
+constexpr int kSurveyLoads = 2;
+typedef u32 u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+struct SurveyLoads {
+  uint4 v[kSurveyLoads];
+};
+__device__ inline SurveyLoads load_widths(const StreamRef& in, u32 b0, u32 stride) {
+  SurveyLoads l;
+#pragma unroll
+  for (int i = 0; i < kSurveyLoads; ++i) {
+    const u64 at = u64(kHeaderBytes) + b0 + u32(i) * stride + 16u * u32(lane_id());
+    l.v[i] = *reinterpret_cast<const uint4*>(at_bytes(in.base, at + 16 <= in.bytes ? u32(at) : 0u));
+  }
+  return l;
+}
+
+// Asked for before the headers are known.  self: the wave's first part of a table.  Else: [0] the first spans of stream
+// `wave` (of the only one: every wave), [1] in lane s where the wave's segment lies in its span of stream s (of both the
+// first word only; the workspace ends 64 bytes behind the last table, see workspace_bytes).  Two loads either way and
+// none behind a branch, so that a kernel that has asked for more behind them can wait for these alone; what must not be
+// read is replaced by the first stream's header.
+template <int K>
+__device__ __forceinline__ SurveyLoads ask_plain_streams(const StreamRef* streams, int k, const StreamIndex& index, bool self, u32 seg,
+                                                         int wave) {
+  const u32 parts = survey_parts(k, self);
+  const u32 lane = u32(lane_id());
+  const int s = K == 1 ? 0 : min(int(u32(wave) / parts), k - 1);
+  const u8* const safe = streams[0].base;
+  const u8* at[kSurveyLoads];
+  if (self) {
+#pragma unroll
+    for (int i = 0; i < kSurveyLoads; ++i) {
+      const u64 t = u64(kHeaderBytes) + 1024u * (u32(wave) % parts) + u32(i) * 1024u * parts + 16u * lane;
+      at[i] = t + 16 <= streams[s].bytes ? streams[s].base + t : safe;
+    }
+  } else {
+    const bool list = (k == 1 || wave < k) && lane < index.spans_cap, place = int(lane) < k && seg < 4 * index.tiles_cap;
+    at[0] = list ? reinterpret_cast<const u8*>(index.spans + u64(s) * index.spans_cap + lane) : safe;
+    at[1] = place ? reinterpret_cast<const u8*>(index.seg_off + (K == 1 ? 0 : u64(lane) * 4 * index.tiles_cap) + seg) : safe;
+  }
+  SurveyLoads l;
+#pragma unroll
+  for (int i = 0; i < kSurveyLoads; ++i) {
+    // (said to be global memory: the compiler no longer sees that through the choice above, and a load that may go to LDS
+    // as well makes every wait a wait for all)
+    typedef const __attribute__((address_space(1))) u32x4_a4 Global;
+    const u32x4_a4 v = *reinterpret_cast<Global*>(reinterpret_cast<uintptr_t>(at[i]));
+    l.v[i] = make_uint4(v.x, v.y, v.z, v.w);
+  }
+  return l;
+}
+
+// The spans of stream s (asked: the first 64 are in `ask`), one per lane and round: the lane's share of the payload words of
+// those before the tile's own span (`before`) and of all, and OR of their flags.
+__device__ inline void sum_spans(const StreamIndex& index, u32 s, u32 nb, u32 tile, bool asked, const SurveyLoads& ask, u32& before,
+                                 u32& total, u32& seen) {
+  const u32 nspans = u32(num_spans(nb)), span = tile / (kSpanSegs / kTileWaves);
+  const u32 lane = u32(lane_id());
+#pragma nounroll
+  for (u32 i0 = 0; i0 < nspans; i0 += 64) {
+    const u32 i = i0 + lane;
+    const bool have = asked && i0 == 0;
+    const u32 entry = i < nspans ? (have ? ask.v[0].x : index.spans[u64(s) * index.spans_cap + i]) : 0u;
+    seen |= entry;
+    total += entry & kSpanSize;
+    before += i < span ? entry & kSpanSize : 0u;
+  }
+}
+
+// Called by all waves of a workgroup of kTileWaves waves; at most one barrier.  `v`: the verdict on the headers, completed here (err,
+// wide).  Returns, in lane s, the payload word offset of the wave's segment, kTileWaves * tile + wave, in stream s.
+template <int K>
+__device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int k, const StreamIndex& index, bool self, u32 tile, int wave,
+                                          const SurveyLoads& ask, StreamsVerdict& v, PlainSurvey<K>& sh) {
+  const int lane = lane_id();
+  const u32 parts = survey_parts(k, self);
+  const bool mine = lane < k;
+  const bool fits = v.mine.ok && stream_fits(v.mine, index);
+  u32 off = 0, total = 0, seen = 0;            // lane s: of stream s
+  if (K == 1 && !self) {
+    // every wave for itself: no wave has to wait for another
+    sum_spans(index, 0, fits ? u32(v.mine.nb) : 0u, tile, true, ask, off, total, seen);
+    off = wave_sum_u32(off) + ask.v[1].x;
+    total = wave_sum_u32(total);
+    seen = (__any((seen & kSpanBadWidth) != 0) ? kSpanBadWidth : 0u) | (__any((seen & kSpanWide) != 0) ? kSpanWide : 0u);
+  } else {
+    SurveyLoads loads = ask;
+#pragma nounroll
+    for (u32 u = u32(wave); u < u32(k) * parts; u += kTileWaves) {
+      const u32 s = u / parts, p = u % parts;
+      const u32 nb = lane_value(u32(fits), int(s)) ? lane_value(u32(v.mine.nb), int(s)) : 0u;
+      u32 before = 0, total = 0, seen = 0;
+      if (self) {
+        const u32 first = tile * kTileBlocks, step = 1024u * parts;
+        if (u != u32(wave)) loads = load_widths(streams[s], 1024u * p, step);
+#pragma nounroll
+        for (u32 b0 = 1024u * p; b0 < nb; b0 += step * kSurveyLoads) {
+#pragma unroll
+          for (int i = 0; i < kSurveyLoads; ++i) {
+            const u32 c0 = b0 + step * u32(i);
+            if (c0 < nb) {                                 // uniform
+              const u32 b = c0 + 16u * u32(lane);
+              const u32 sum = psize_words16(loads.v[i], b, nb, seen);
+              total += sum;
+              before += b < first ? sum : 0u;
+              if (first - c0 < 1024u) {                    // uniform: the tile is one row of 16 lanes here
+                u32 incl = sum;
+                incl += dpp_row_shr_or_zero<1>(incl);
+                incl += dpp_row_shr_or_zero<2>(incl);
+                incl += dpp_row_shr_or_zero<4>(incl);
+                incl += dpp_row_shr_or_zero<8>(incl);
+                if (u32(lane) >> 4 == (first - c0) >> 8 && (lane & 3) == 0) sh.in_tile[4 * s + ((u32(lane) >> 2) & 3u)] = incl - sum;
+              }
+            }
+          }
+          if (b0 + step * kSurveyLoads < nb) loads = load_widths(streams[s], b0 + step * kSurveyLoads, step);
+        }
+      } else {
+        sum_spans(index, s, nb, tile, u == u32(wave), ask, before, total, seen);
+      }
+      before = wave_sum_u32(before);
+      total = wave_sum_u32(total);
+      if (self) seen = ((seen & kBadWidths) ? kSpanBadWidth : 0u) | ((seen & kWideWidths) ? kSpanWide : 0u);
+      const bool bad = __any((seen & kSpanBadWidth) != 0), wide = __any((seen & kSpanWide) != 0);
+      if (lane == 0) {
+        sh.before[u] = before;
+        sh.total[u] = total;
+        sh.seen[u] = (bad ? kSpanBadWidth : 0u) | (wide ? kSpanWide : 0u);
+      }
+    }
+    lds_barrier();
+    if (mine) {
+#pragma nounroll
+      for (u32 p = 0; p < parts; ++p) {
+        off += sh.before[u32(lane) * parts + p];
+        total += sh.total[u32(lane) * parts + p];
+        seen |= sh.seen[u32(lane) * parts + p];
+      }
+      off += self ? sh.in_tile[4 * lane + wave] : ask.v[1].x;
+    }
+  }
+  if (__any(mine && v.mine.ok && !fits)) v.err |= status_bit(ZC_ERR_ARG);
+  if (__any(mine && fits && ((seen & kSpanBadWidth) != 0 || tables_end(v.mine.nb, false) + 4 * u64(total) != v.mine.total)))
+    v.err |= status_bit(ZC_ERR_FORMAT);
+  v.wide = __any(mine && fits && (seen & kSpanWide) != 0) ? ~u64(0) : 0;
+  return off;
 }
 
 }  // namespace zc

@@ -177,7 +177,9 @@ __device__ inline void pad_local(const float* local, u64 v0, u64 n, u32 have, in
 
 // Local values 16..31 of every block into the wave's rows, once values 0..15 have been used (see
 // step_kernel: `later` holds them spread over all lanes).
-__device__ inline void stage_second_half(u32* wl, int lane, bool first_kind, const float4 (&later)[4]) {
+__device__ inline void stage_second_half(u32* wl, const float4 (&later)[4]) {
+  const int lane = fresh_lane();               // (or where each of these goes is kept in a register from the start)
+  const bool first_kind = (lane & 7) < 4;
   wave_lds_sync();
   // first kind: loads 4..7 of the partner (same rows, the partner's columns); second kind: its own loads 0..3
 #pragma unroll
@@ -325,13 +327,15 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
 
 // TICKETS: tiles are handed out by tickets (take_tile) instead of by workgroup id.  A template parameter,
 // not an argument: a workgroup that knows its tile from its id asks for everything at once, and the waits
-// for those loads can only be counted exactly when no other path joins them.
-template <bool IX, int OP, bool TICKETS>
+// for those loads can only be counted exactly when no other path joins them.  SELF: a plain stream whose width table the
+// kernel sums itself, one for the same reason (as an argument it cost 2^25 values with an index ahead 52.3 us, now 50.9).
+template <bool IX, bool SELF, int OP, bool TICKETS>
 __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<1> survey;
 
   const int lane = lane_id();
   const int wave = wave_id();
@@ -345,12 +349,10 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   // (with tickets the ticket is asked for first of all: its round trip runs beside the header's)
   u64 asked = 0;
   if (TICKETS && threadIdx.x == 0) asked = ask_ticket(ticket_counter(a.ctl, ticket_shard()));
-  uint4 gate_raw = make_uint4(0, 0, 0, 0);
-  if (!IX) gate_raw = load_gate(a.ctl, zero);
   const HeaderWords hw = load_header_words(a.in.base, zero);
   float4 x[8];
-  SegmentOffsetParts seg_parts{0, 0, 0};
-  u32 w = 0, seg_end = 0;
+  u32 w = 0, seg_begin = 0, seg_end = 0;
+  SurveyLoads ask{};
   if (early) {
     const u32 seg = (a.first_tile + blockIdx.x) * kTileWaves + u32(wave);
     const u32 b = seg * kWaveBlocks + u32(lane);
@@ -367,12 +369,14 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
       const u32 e1 = *reinterpret_cast<const u32*>(at_bytes(a.in.base, at + 4u + zero));
       const u64 w_at = widths_begin(num_blocks(a.n_local), true) + b;
       const u32 wb = u32(*at_bytes(a.in.base, w_at < a.in.bytes ? u32(w_at) : 0u));
-      seg_parts.seg = have ? e0 : 0u;
+      seg_begin = have ? e0 : 0u;
       seg_end = have ? e1 : 0u;
       w = w_at < a.in.bytes ? wb : 0u;
     } else {
-      if (seg < 4 * a.index.tiles_cap) seg_parts = load_segment_offset(a.index, 0, seg, zero);
-      if (u64(kHeaderBytes) + b < a.in.bytes) w = u32(*at_bytes(a.in.base, kHeaderBytes + b));
+      ask = ask_plain_streams<1>(&a.in, 1, a.index, SELF, seg, wave);
+      const u64 w_at = u64(kHeaderBytes) + b;
+      const u32 wb = u32(*at_bytes(a.in.base, w_at < a.in.bytes ? u32(w_at) : 0u));
+      w = w_at < a.in.bytes ? wb : 0u;
     }
     load_local(a.local, v0, share_values(a.n_local, v0), lane, x);
     // Nothing moves across this line: left to itself the compiler puts the wait for the header in front of
@@ -380,24 +384,24 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // Plain streams: validated and indexed by the kernels of zc_scan.h, whose verdict and tag are in
-  // the control block.  Indexed streams: judged here, by every workgroup alike.
+  // The header is judged here, by every workgroup alike; the width table of a plain stream too, once the tile is known.
+  // (the tag, some 100 dependent scalar instructions, while the loads are on their way)
+  u64 ltag = launch_tag(a.nonce, a.ctl);
+  asm volatile("" : "+s"(ltag));
   const ParsedHeader h = parse_header(hw, a.in.bytes, IX);
-  const u64 ltag = launch_tag(a.nonce, a.ctl);
-  u64 tag;
-  if (IX) {
-    tag = call_tag(a.ctl, ltag, a.adopt != 0);
-    if (!h.ok) {
-      if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (!a.adopt) a.ctl->result = 0;
-        raise_status(a.ctl, tag, status_bit(ZC_ERR_FORMAT));
-      }
-      return;
+  const u64 tag = call_tag(a.ctl, ltag, a.adopt != 0);
+  StreamsVerdict v;
+  v.mine = h;
+  v.err = h.ok ? 0u : status_bit(ZC_ERR_FORMAT);
+  u32 tile = a.first_tile + blockIdx.x;      // tiles in the order in which workgroups start
+  if (TICKETS && !IX) ask = ask_plain_streams<1>(&a.in, 1, a.index, SELF, tile * kTileWaves + u32(wave), wave);
+  if (!IX) seg_begin = lane_value(judge_plain_streams(&a.in, 1, a.index, SELF, tile, wave, ask, v, survey), 0);
+  if (v.err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (!a.adopt) a.ctl->result = 0;
+      raise_status(a.ctl, tag, v.err);
     }
-  } else {
-    const Gate gate = parse_gate(gate_raw);
-    tag = gate.tag;
-    if (gate_failed(gate) || !h.ok) return;
+    return;
   }
   if (a.n_local != h.n) {
     if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_MISMATCH));
@@ -414,7 +418,6 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   const u32 end_tile = a.end_tile && a.end_tile < ntiles ? a.end_tile : ntiles;
   if (a.first_tile >= end_tile) return;
 
-  u32 tile = a.first_tile + blockIdx.x;      // tiles in the order in which workgroups start
   if (TICKETS) {                             // ... or handed out by tickets, see take_tile
     if (threadIdx.x == 0) {
       const u32 t = take_tile(a.ctl, ltag, end_tile - a.first_tile, ticket_shard(), asked);
@@ -435,18 +438,20 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     load_local(a.local, v0, have, lane, x);
     if (IX) {
       if (seg_live) {
-        seg_parts = load_segment_offset(a.index, 0, seg, 0, a.in.base);
+        seg_begin = load_segment_offset(a.in.base, seg);
         seg_end = load_segment_end(a.in.base, seg);
       }
-    } else {
-      if (seg_live) seg_parts = load_segment_offset(a.index, 0, seg);
+    } else {                                 // (the verdict stands: once more, for the place of this tile)
+      lds_barrier();
+      ask = ask_plain_streams<1>(&a.in, 1, a.index, SELF, seg, wave);
+      seg_begin = lane_value(judge_plain_streams(&a.in, 1, a.index, SELF, tile, wave, ask, v, survey), 0);
       w = active ? u32(*at_bytes(a.in.base, kHeaderBytes + b)) : 0u;
     }
   }
   if (IX && !early && active) w = u32(*at_bytes(a.in.base, u32(widths_begin(h.nb, true)) + b));
   if (!active) w = 0;
   if (!seg_live) {
-    seg_parts = SegmentOffsetParts{0, 0, 0};
+    seg_begin = 0;
     seg_end = 0;
   }
   const u32 outlier_in = active ? u32(reinterpret_cast<const i32*>(a.in.base + outliers_begin(h.nb, IX))[b]) : 0u;
@@ -454,7 +459,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
   // ---- the received segment: scan of the widths, checks, payload into LDS ----
   const u32* const payload_in = reinterpret_cast<const u32*>(a.in.base + tend);
   u32 err = 0;
-  const u64 seg_off = IX ? u64(uniform(seg_parts.seg)) : segment_offset(seg_parts);
+  const u64 seg_off = u64(uniform(seg_begin));
   const WavePayload wp = stage_wave_payload(payload_in, (h.total - tend) / 4, w, seg_off, wl, lane, IX,
                                             uniform(seg_end) - u32(seg_off), h.wide, err, reinterpret_cast<const uint4*>(a.in.base), true);
   if (IX && seg_live && !index_ends_ok(h, seg, u32(seg_off), uniform(seg_end))) err |= status_bit(ZC_ERR_FORMAT);
@@ -525,7 +530,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
       magnitude_planes_to_twos<8>(r);
       transpose8x8_quads(r);
       walk_half<OP, 8, 0>(r, row, qa, cs, nf);
-      stage_second_half(wl, lane, first_kind, later);
+      stage_second_half(wl, later);
       walk_half<OP, 8, 1>(r, row, qa, cs, nf);
     } else {
 #pragma unroll
@@ -533,7 +538,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
       magnitude_planes_to_twos<16>(lo);
       transpose16x16_pairs(lo);
       walk_half<OP, 16, 0>(lo, row, qa, cs, nf);
-      stage_second_half(wl, lane, first_kind, later);
+      stage_second_half(wl, later);
       walk_half<OP, 16, 1>(lo, row, qa, cs, nf);
     }
     wave_lds_sync();

@@ -6,7 +6,7 @@ import torch
 
 import gpuutil
 from paper_2502_18554_amd import synth
-from paper_2502_18554_amd.binding import ZC_OK
+from paper_2502_18554_amd.binding import ZC_ERR_FORMAT, ZC_OK
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("stream_variant")]
 
@@ -45,3 +45,36 @@ def test_streams_of_few_tiles(zcref, tiles):
         st_ref, ref = zcref.compress(x, eb)[:2]
         st, s, total = u.gpu_compress(x, eb)
         assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+
+
+# the tables of plain streams are summed by every workgroup of the main kernel up to 512 tiles of all streams together, by
+# a kernel ahead of it from there on; parts of four waves (one stream), two and one, and a table of more than one round
+@pytest.mark.parametrize("tiles,k", [(4, 1), (5, 1), (17, 1), (512, 1), (513, 1), (3, 2), (256, 2), (257, 2), (5, 3), (170, 3), (171, 3),
+                                     (33, 5), (103, 5), (2, 64), (9, 64)])
+def test_decompress_of_few_tiles(zcref, stream_variant, tiles, k):
+    u = gpuutil
+    n = tiles * TILE - 2049
+    eb = 6e-3
+    base = _values(n, 60)
+    xs = [np.roll(base, 4096 * i) for i in range(k)]
+    refs = [zcref.compress(x, eb)[1] for x in xs]
+    want = [zcref.decompress(r)[1] for r in refs]
+    st, got, ns = u.gpu_decompress_many(refs, [n] * k)
+    assert st == ZC_OK and ns == [n] * k
+    for w, g in zip(want, got):
+        assert np.array_equal(w.view(np.uint32), g[:n].view(np.uint32))
+    st, y, got_n = u.gpu_decompress(refs[-1], n)
+    assert st == ZC_OK and got_n == n and np.array_equal(y.view(np.uint32), want[-1].view(np.uint32))
+    if stream_variant == "indexed":
+        return
+    # a table that does not add up, or holds a width above 31, far from every tile but its own: nothing is written
+    nb = (n + 31) // 32
+    for bad in (32, 7 + int(refs[-1][u.widths_begin(nb) + nb - 1])):
+        broken = refs[-1].copy()
+        broken[u.widths_begin(nb) + nb - 1] = bad
+        assert zcref.decompress(broken)[0] == ZC_ERR_FORMAT
+        d_out = torch.full((n,), 7.0, device=u.DEV)
+        st, _ = u.zc.zc_decompress(u.to_dev(broken), broken.size, d_out, u.workspace(n))
+        assert st == ZC_ERR_FORMAT and bool((d_out == 7.0).all())
+        st, outs, _ = u.gpu_decompress_many(refs[:-1] + [broken], [n] * k)
+        assert st == ZC_ERR_FORMAT and all(np.isnan(o).all() for o in outs)
