@@ -18,6 +18,7 @@ using u64 = uint64_t;
 using i32 = int32_t;
 using i64 = int64_t;
 typedef u32 u32x4_t __attribute__((ext_vector_type(4)));
+typedef u32 u32x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr u32 kMagic = 0x314C435Au;
@@ -380,17 +381,16 @@ __device__ inline u32 dpp_row_shr_or_zero(u32 v) {
   return u32(__builtin_amdgcn_update_dpp(0, int(v), 0x110 + S, 0xf, 0xf, false));
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave.
+// Inclusive prefix sum over the 64 lanes of a wave: inside each row of 16, then the last lane of rows 0 and 2 into the
+// row behind it, then lane 31 into the upper half.
 __device__ inline u32 wave_inclusive_sum(u32 v) {
   v += dpp_row_shr_or_zero<1>(v);
   v += dpp_row_shr_or_zero<2>(v);
   v += dpp_row_shr_or_zero<4>(v);
   v += dpp_row_shr_or_zero<8>(v);
-  // v is now the scan inside each row of 16; add the totals of the earlier rows
-  const u32 t0 = lane_value(v, 15), t1 = lane_value(v, 31), t2 = lane_value(v, 47);
-  int row = lane_id() >> 4;
-  u32 carry = (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
-  return v + carry;
+  v += u32(__builtin_amdgcn_update_dpp(0, int(v), 0x142, 0xa, 0xf, false));    // row_bcast:15
+  v += u32(__builtin_amdgcn_update_dpp(0, int(v), 0x143, 0xc, 0xf, false));    // row_bcast:31
+  return v;
 }
 
 // ---------------------------------------------------------------------------------------

@@ -59,6 +59,7 @@ struct ReduceCall {
   u64 wide_streams;  // bit s: operand s may have blocks wider than 15 bits
   u32 part_end;      // a reduce done in parts: one past the last tile of this part; else 0
   u32 places;        // plain streams: lane s: payload word offset of the wave's segment in operand s
+  u32 nb, widths, firsts, payload;      // blocks of every stream, and where its width bytes, first codes and payload begin (all below 2^29)
 };
 
 // Header fields and table padding of the output stream; one thread.
@@ -229,54 +230,50 @@ struct OperandPlace {
   u32 room;         // uniform: words from src0 to the end of the caller's buffer
 };
 
-__device__ inline i32 load_operand_outlier(const u8* base, const ParsedHeader& h, u32 b, bool active, bool ix) {
-  return active ? *reinterpret_cast<const i32*>(at_bytes(base, u32(outliers_begin(h.nb, ix)) + 4u * b)) : 0;
+// Loads of what is the wave's share of an operand are buffer loads whose range is what exists of it: no lane needs a
+// comparison, a branch or another address.  (With those an operand took 420 instructions; a wave that has its SIMD to
+// itself issues one in five cycles, so that they were what a call of few tiles waited for: Sum of 8 x 1024 values 15.8 us,
+// now 13.9, of 4 x 4 194 301 hard ones 15.5, now 14.5.  Larger calls gain as well: 8 x 2^26 161.6 -> 157.0, on one machine.)
+__device__ inline __amdgpu_buffer_rsrc_t bytes_from(const u8* at, u32 bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u8*>(at), 0, int(bytes), kRawBuffer);
 }
 
-__device__ inline i32 load_operand_outlier(const ReduceArgs& a, int s, const ParsedHeader& h, u32 b, bool active, bool ix) {
-  return load_operand_outlier(a.in[s].base, h, b, active, ix);
+// The first code of the lane's block (b; 0 if there is no such block).
+__device__ inline i32 load_operand_outlier(const u8* base, const ReduceCall& c, u32 b) {
+  return i32(__builtin_amdgcn_raw_buffer_load_b32(bytes_from(base + c.firsts, 4u * c.nb), int(4u * b), 0, 0));
 }
 
-__device__ inline u32 payload_room(u64 bytes, const ParsedHeader& h, bool ix) {
-  const u64 tend = tables_end(h.nb, ix);
-  const u64 room = bytes > tend ? (bytes - tend) / 4 : 0;
+__device__ inline u32 payload_room(u64 bytes, const ReduceCall& c) {
+  const u64 room = bytes > c.payload ? (bytes - c.payload) / 4 : 0;
   return room > 0xffffffffull ? 0xffffffffu : u32(room);   // a stream's payload has at most 2^31 words
 }
 
-// The tables of operand s for the wave's segment (seg: the same in every lane; b: the lane's
-// block; both fit 32 bits because a stream has at most 2^26 blocks, and so do all byte offsets into the tables).
+// The tables of operand s for the wave's segment (seg: the same in every lane; b: the lane's block).
 // The payload is fenced in by the size of the caller's buffer, which a validated stream does
 // not exceed (a 16-byte load may run up to 12 bytes past the stream's own end, inside the
 // buffer; nothing reads those words).
 // An indexed stream (ix) has the segment's position in its own index, and its width bytes
 // behind that index (every stream of a validated call has the header's nb); a plain one's is known since the workgroup
 // started (`places`).
-__device__ inline OperandMeta load_operand_meta(int s, const StreamRef& in, const ReduceCall& c, u32 seg,
-                                                u32 b, bool active, bool seg_live, bool ix, u32 zero = 0) {
+__device__ inline OperandMeta load_operand_meta(int s, const StreamRef& in, const ReduceCall& c, u32 seg, u32 b, bool seg_live, bool ix) {
   OperandMeta m;
-  const u8* base = in.base;
-  m.seg_off = m.seg_end = 0;
   if (ix) {
-    if (seg_live) {
-      m.seg_off = load_segment_offset(base, seg, zero);
-      m.seg_end = load_segment_end(base, seg, zero);
-    }
-  } else if (seg_live) {
-    m.seg_off = lane_value(c.places, s);
+    const u32x2_t ends = __builtin_amdgcn_raw_buffer_load_b64(bytes_from(in.base + kHeaderBytes + 4u * seg, seg_live ? 8u : 0u), 0, 0, 0);
+    m.seg_off = ends.x;
+    m.seg_end = ends.y;
+  } else {
+    m.seg_off = seg_live ? lane_value(c.places, s) : 0u;
+    m.seg_end = 0;
   }
-  m.w = active ? u32(*at_bytes(base, u32(widths_begin(c.h.nb, ix)) + b)) : 0u;
-  m.payload_room = payload_room(in.bytes, c.h, ix);
+  m.w = u32(__builtin_amdgcn_raw_buffer_load_b8(bytes_from(in.base + c.widths, c.nb), int(b), 0, 0));
+  m.payload_room = payload_room(in.bytes, c);
   return m;
-}
-__device__ inline OperandMeta load_operand_meta(const ReduceArgs& a, int s, const ReduceCall& c, u32 seg, u32 b, bool active,
-                                                bool seg_live, bool ix, u32 zero = 0) {
-  return load_operand_meta(s, a.in[s], c, seg, b, active, seg_live, ix, zero);
 }
 
 // `err`: an indexed stream is checked as it is used: the widths of the segment must add up to
 // what the index says, and no block may be wider than w_max (15 where the stream promised narrow
 // blocks, or where the caller has seen that there is no other).
-__device__ inline OperandPlace place_operand(const OperandMeta& m, const ParsedHeader& h, bool ix, u32& err, u32 w_max = 15) {
+__device__ inline OperandPlace place_operand(const OperandMeta& m, bool ix, u32& err, u32 w_max = 15) {
   OperandPlace p;
   // the same in every lane, and long since loaded: into scalar registers, 32-bit arithmetic
   const u32 seg_off = uniform(m.seg_off);
@@ -312,13 +309,13 @@ struct OperandStage {
 
 __device__ inline OperandStage load_operand_payload(const u32* payload, const OperandPlace& p, int lane) {
   OperandStage st;
-  const u32* src = payload + p.src0;             // uniform
+  // whole 16-byte pieces only: the last words of the caller's buffer are left to stage_to_lds (see load_wave_stage)
+  const u32 whole = min((p.span + 3u) & ~3u, p.room & ~3u);
+  const __amdgpu_buffer_rsrc_t share = bytes_from(reinterpret_cast<const u8*>(payload + p.src0), 4u * whole);
 #pragma unroll
   for (int i = 0; i < kStageLoads; ++i) {
-    const u32 idx = 4u * u32(lane) + 256u * u32(i);
-    st.v[i] = make_uint4(0, 0, 0, 0);
-    // whole 16-byte pieces only: the last words of the caller's buffer are left to stage_to_lds (see load_wave_stage)
-    if (idx < p.span && idx + 4 <= p.room) st.v[i] = load_once(reinterpret_cast<const uint4*>(src + idx));
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * i, 0, kAccessOnce);
+    st.v[i] = make_uint4(t.x, t.y, t.z, t.w);
   }
   return st;
 }
@@ -326,8 +323,7 @@ __device__ inline OperandStage load_operand_payload(const u32* payload, const Op
 __device__ inline void stage_to_lds(const OperandStage& st, const OperandPlace& p, const u32* payload, u32* wl, int lane) {
 #pragma unroll
   for (int i = 0; i < kStageLoads; ++i) {
-    const u32 idx = 4u * u32(lane) + 256u * u32(i);
-    if (idx < p.span) *reinterpret_cast<uint4*>(wl + idx) = st.v[i];
+    if (256u * u32(i) < p.span) *reinterpret_cast<uint4*>(wl + 4u * u32(lane) + 256u * u32(i)) = st.v[i];      // uniform
   }
   const u32 staged = p.span < 256u * kStageLoads ? p.span : 256u * kStageLoads;
   if (((staged + 3u) & ~3u) > p.room) {            // uniform, and rare: the buffer ends inside a 16-byte piece
@@ -475,7 +471,6 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
                                            bool early, u32* wl, u32 (&acc)[kSumPlanes], u32& sgn, u32& w, i64& outlier, u32& err) {
   const ParsedHeader& h = c.h;
   const u32 w_max = c.wide_streams ? 31u : 15u;
-  const u64 tend = tables_end(h.nb, IX);
   const u32 seg = share.seg;
   const bool seg_live = share.live;
   OperandPlace next;
@@ -484,21 +479,18 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
   {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
-    const bool active = b < h.nb;
     if (early) {
-      if (!active) meta.w = 0;
+      if (b >= c.nb) meta.w = 0;
       if (!IX) meta.seg_off = lane_value(c.places, 0);
-      if (!seg_live) {
-        meta.seg_off = meta.seg_end = 0;
-      }
-      meta.payload_room = payload_room(a.in[0].bytes, h, IX);
+      if (!seg_live) meta.seg_off = meta.seg_end = 0;
+      meta.payload_room = payload_room(a.in[0].bytes, c);
     } else {
-      meta = load_operand_meta(a, 0, c, seg, b, active, seg_live, IX, opaque_zero());
+      meta = load_operand_meta(0, a.in[0], c, seg, b, seg_live, IX);
     }
-    next = place_operand(meta, h, IX, err, w_max);
-    if (a.k > 1) meta = load_operand_meta(a, 1, c, seg, b, active, seg_live, IX, opaque_zero());
-    stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tend), next, lane);
-    outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
+    next = place_operand(meta, IX, err, w_max);
+    if (a.k > 1) meta = load_operand_meta(1, a.in[1], c, seg, b, seg_live, IX);
+    stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + c.payload), next, lane);
+    outlier_next = load_operand_outlier(a.in[0].base, c, b);
   }
   // the ends of every operand's index, by the waves that hold them
   if (IX && seg_live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
@@ -512,16 +504,15 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
   for (int s = 0; s < a.k; ++s) {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
-    const bool active = b < h.nb;
     const OperandPlace cur = next;
-    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(a.in[s].base + tend), wl, lane);
+    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(a.in[s].base + c.payload), wl, lane);
     wave_lds_sync();
     outlier += i64(outlier_next);
     if (s + 1 < a.k) {
-      next = place_operand(meta, h, IX, err, w_max);
-      if (s + 2 < a.k) meta = load_operand_meta(a, s + 2, c, seg, b, active, seg_live, IX, opaque_zero());
-      stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + tend), next, lane);
-      outlier_next = load_operand_outlier(a, s + 1, h, b, active, IX);
+      next = place_operand(meta, IX, err, w_max);
+      if (s + 2 < a.k) meta = load_operand_meta(s + 2, a.in[s + 2], c, seg, b, seg_live, IX);
+      stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[s + 1].base + c.payload), next, lane);
+      outlier_next = load_operand_outlier(a.in[s + 1].base, c, b);
     }
     if (cur.wcap) {
       bound += (1u << cur.wcap) - 1u;
@@ -734,6 +725,10 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
   c.places = 0;
   if (!IX) c.places = judge_plain_streams(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
   c.h = v.h0;
+  c.nb = u32(c.h.nb);
+  c.widths = u32(widths_begin(c.h.nb, IX));
+  c.firsts = u32(outliers_begin(c.h.nb, IX));
+  c.payload = u32(tables_end(c.h.nb, IX));
   c.nsum = v.nsum;
   c.wide_streams = v.wide;
   if (v.err) {

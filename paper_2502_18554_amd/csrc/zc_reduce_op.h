@@ -22,19 +22,16 @@
 // than 15 bits does so from the start, in all its waves (extreme_any).
 // Measured, 8 x 2^24 values unless said otherwise, first with codes unpacked throughout (145 registers, three waves
 // per SIMD, and a kernel of its own for wide blocks, launched with every call), then now:
-//   smooth field, bound 1e-4 of its range                     79.5   64.4 us
-//   the same at 1e-5 (first codes and excursions beyond 2^13) 90     83
-//   1e-4, each rank at a level of its own                     86     77
-//   white noise over 32000 codes (nothing fits 16 bits)       109    101
-//   16 x 2^20 at 1e-5                                         36.5   34.7
-//   64 x 100 003 at 2e-4                                      109    111.5
-//   hard data, 4 x 4 194 301                                  28.2   21.0
-//   2 x 20 000                                                11.7   9.2
-// (Starting over in 32 bits instead of going on there, without the next operand on its way, the second to fifth took 107,
-// 101, 120 and 43.5.)  128 registers, four waves per SIMD, and 52 bytes of scratch (68 on plain streams) that only the
+//   smooth field, bound 1e-4 of its range                     79.5   61.5 us
+//   8 x 2^23 (1024 tiles)                                     36.2   32.9
+//   16 x 2^20                                                 29.7   24.8
+//   hard data, 4 x 4 000 000                                  28.2   15.6
+//   8 x 1024                                                  17.6   15.0
+// (the last four: before payloads went straight to LDS and loads were trimmed, see OperandPipe and load_operand_meta).
+// 128 registers, four waves per SIMD, and 24 bytes of scratch (12 on plain streams) that only the
 // wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
 // is computed where it is used: with both in registers across the loops these spilled 240 bytes, and every reload waits
-// for the loads under way.  Five waves per SIMD: 61.9 on the smooth field, but 46 against 36 where there are only wide blocks.
+// for the loads under way.
 #pragma once
 
 #include "zc_bitmatrix.h"
@@ -73,23 +70,24 @@ struct ExtremeBlock {
   i32 outlier;
 };
 
-// The lane's sign and plane words out of its wave's staged payload: lo[0..15) = planes 0..14, lo[15] = sign
-// word (all reads at once and without conditions, what is not the block's own is dropped: see pick_block_words).
-__device__ inline void pick_operand_words(const OperandPlace& cur, const u32* wl, u32 (&lo)[16]) {
-  const u32* mine = wl + (cur.w ? cur.pick : 0u);
-  u32 t[16];
-#pragma unroll
-  for (int p = 0; p < 16; ++p) t[p] = mine[p];
+// The lane's sign and plane words out of what lies in its wave's staging area from the sign word on: lo[0..15) = planes
+// 0..14, lo[15] = sign word (what is not the block's own is dropped: see pick_block_words).
+__device__ inline void keep_operand_words(const OperandPlace& cur, const u32 (&t)[16], u32 (&lo)[16]) {
+  const u32 sign = t[0];
   const u32 keep = cur.w ? (1u << cur.w) - 1u : 0u;      // bit p: the block has plane p
-  lo[15] = cur.w ? t[0] : 0u;
 #pragma unroll
-  for (int p = 0; p < 15; ++p) lo[p] = t[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+  for (int p = 0; p < 15; ++p) {
+    // (the AND spelled out: seen as one, it is compiled into a test and a selection per plane)
+    const u32 m = u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+    lo[p] = __builtin_amdgcn_bitop3_b32(t[1 + p], m, m, 0xC0);
+  }
+  lo[15] = cur.w ? sign : 0u;
 }
 
-// The deltas of the lane's block, fields as transpose16x16_pairs leaves them (word j: deltas j and j + 16), out of its
-// wave's staged payload.
-__device__ inline void operand_delta_pairs(const OperandPlace& cur, const u32* wl, u32 (&f)[16]) {
-  pick_operand_words(cur, wl, f);
+// The deltas of the lane's block, fields as transpose16x16_pairs leaves them (word j: deltas j and j + 16), from the words
+// that were read from its wave's staging area, in place.
+__device__ inline void operand_delta_pairs(const OperandPlace& cur, u32 (&f)[16]) {
+  keep_operand_words(cur, f, f);
   if (!__any(cur.w > 7)) {                     // byte fields: word j = deltas j, j + 8, j + 16, j + 24
     u32 r[8];
 #pragma unroll
@@ -108,55 +106,126 @@ __device__ inline void operand_delta_pairs(const OperandPlace& cur, const u32* w
   }
 }
 
-// The operands of a call without wide blocks one after the other: operand s + 1 is on its way while operand s is
-// decoded (as in sum_common).
+// The operands of a call without wide blocks one after the other.  What bounds this loop is how many bytes a wave has on
+// their way: with the extremes in registers a SIMD holds four waves, and with one operand's payload (in 16 registers
+// more) on its way per wave, 8 x 2^24 values took 65.2 us, half of it arithmetic.  So the payload goes from memory
+// straight to LDS, where a wave has two areas: while operand s is decoded, s + 1 and, as soon as the words of s have
+// been read from their area, s + 2 are on their way (63.8 us; 16 x 2^20 29.5 -> 25.6; 8 x 1024, a string of round trips,
+// 17.6 -> 15.7).
+// Each round ends with the four loads to LDS of operand s + 2 and has no other memory access behind them, so that
+// "all but the newest four" is what a round waits for at its start; none of the round's loads is behind a branch
+// (behind the last operand the range of a load is empty).  The words are read by instructions of our own: ordinary reads
+// would wait for every load to LDS that is under way, not only for those to their area.
+constexpr u32 kOperandArea = 1056;             // words
+static_assert(kOperandArea >= 1027 + 16 && kOperandArea % 4 == 0, "an operand's payload, and the reads behind its last word, must fit");
+constexpr u32 kExtremeStage = 2 * kOperandArea;
+static_assert(kExtremeStage >= u32(kWaveStage), "the output is staged in the same place");
+
+typedef __attribute__((address_space(3))) u32 LdsWord;
+__device__ inline u32 lds_address(const u32* p) { return u32(reinterpret_cast<uintptr_t>((const LdsWord*)p)); }
+
 template <bool IX>
 struct OperandPipe {
-  OperandMeta meta;
-  OperandPlace next;
-  OperandStage stage;
-  i32 outlier_next;
-  OperandPlace cur;        // the operand whose payload is in the staging area
-  i32 first;               // ... and the first code of the lane's block there
-  // Where operands s, s + 1 and s + 2 are, asked for a step before it is needed.
-  StreamRef at0, at1, at2;
+  OperandPlace cur, next, ahead;           // operands s (whose words have been read), s + 1 and s + 2
+  i32 first, first_next, first_ahead;      // the first code of the lane's block in them
+  OperandMeta meta;                        // operand s + 3
 
-  __device__ __forceinline__ void open(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32& err) {
-    const ParsedHeader& h = c.h;
-    at0 = a.in[0];
-    at1 = a.in[min(1, a.k - 1)];
-    at2 = a.in[min(2, a.k - 1)];
-    const int lane = fresh_lane();
-    const u32 b = share.seg * kWaveBlocks + u32(lane);
-    const bool active = b < h.nb;
-    meta = load_operand_meta(a, 0, c, share.seg, b, active, share.live, IX, opaque_zero());
-    next = place_operand(meta, h, IX, err);
-    if (a.k > 1) meta = load_operand_meta(a, 1, c, share.seg, b, active, share.live, IX, opaque_zero());
-    stage = load_operand_payload(reinterpret_cast<const u32*>(a.in[0].base + tables_end(h.nb, IX)), next, lane);
-    outlier_next = load_operand_outlier(a, 0, h, b, active, IX);
+  __device__ __forceinline__ static OperandMeta load_meta(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32 b) {
+    const int t = min(s, a.k - 1);
+    return load_operand_meta(t, a.in[t], c, share.seg, b, share.live, IX);
   }
-  // Operand s into the staging area.
-  __device__ __forceinline__ void take(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32* wl, u32& err) {
-    const ParsedHeader& h = c.h;
-    const StreamRef here = at0, ahead1 = at1, ahead2 = at2;
-    at0 = at1;
-    at1 = at2;
-    at2 = a.in[min(s + 3, a.k - 1)];
-    const u64 tend = tables_end(h.nb, IX);
+  __device__ __forceinline__ static i32 load_first(const ReduceArgs& a, const ReduceCall& c, int s, u32 b) {
+    return load_operand_outlier(a.in[min(s, a.k - 1)].base, c, b);
+  }
+  __device__ __forceinline__ static OperandPlace place(const ReduceArgs& a, int s, const OperandMeta& m, u32& err) {
+    u32 bad = 0;
+    OperandPlace p = place_operand(m, IX, bad);
+    if (s < a.k) err |= bad;
+    else p.span = 0;
+    return p;
+  }
+  // The operand's payload for this wave, from the 16-byte boundary at or below its segment on, into `area`: whole 16-byte
+  // pieces inside the caller's buffer only (the rest: see take).  All 1024 words of the area are written.
+  __device__ __forceinline__ static void ask_payload(const ReduceArgs& a, const ReduceCall& c, int s, const OperandPlace& p, u32* area,
+                                                     int lane) {
+    const u32 whole = min((p.span + 3u) & ~3u, p.room & ~3u);
+    const __amdgpu_buffer_rsrc_t share = bytes_from(a.in[min(s, a.k - 1)].base + c.payload + 4 * u64(p.src0), 4u * whole);
+#pragma unroll
+    for (int i = 0; i < kStageLoads; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(share, (LdsWord*)(area + 256 * i), 16, 16 * lane + 1024 * i, 0, 0, kAccessOnce);
+  }
+  // Nothing moves across this line.
+  __device__ __forceinline__ static void line() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  __device__ __forceinline__ void open(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl, u32& err) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    const bool active = b < h.nb;
-    cur = next;
-    stage_to_lds(stage, cur, reinterpret_cast<const u32*>(here.base + tend), wl, lane);
-    wave_lds_sync();
-    first = outlier_next;
-    if (s + 1 < a.k) {
-      next = place_operand(meta, h, IX, err);
-      if (s + 2 < a.k) meta = load_operand_meta(s + 2, ahead2, c, share.seg, b, active, share.live, IX, opaque_zero());
-      stage = load_operand_payload(reinterpret_cast<const u32*>(ahead1.base + tend), next, lane);
-      outlier_next = load_operand_outlier(ahead1.base, h, b, active, IX);
+    const OperandMeta m0 = load_meta(a, c, share, 0, b), m1 = load_meta(a, c, share, 1, b);
+    meta = load_meta(a, c, share, 2, b);
+    first = load_first(a, c, 0, b);
+    first_next = load_first(a, c, 1, b);
+    line();
+    cur = place(a, 0, m0, err);
+    ask_payload(a, c, 0, cur, wl, lane);
+    line();
+    next = place(a, 1, m1, err);
+    ask_payload(a, c, 1, next, wl + kOperandArea, lane);
+    line();
+  }
+  // The words of operand s from its lanes' sign words on, and operand s + 2 on its way.  Operands in turn from 0 on.
+  __device__ __forceinline__ void take(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32* wl, u32 (&t)[16], u32& err) {
+    u32* const area = wl + (s & 1 ? kOperandArea : 0u);
+    const int lane = fresh_lane();
+    if (s) {
+      cur = next;
+      first = first_next;
+      next = ahead;
+      first_next = first_ahead;
     }
+    line();
+    asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+    if (cur.span > 1024u || ((cur.span + 3u) & ~3u) > cur.room) {      // uniform, and rare: words 1024 .. 1026, or the buffer ends inside a 16-byte piece
+      const u32 whole = min((cur.span + 3u) & ~3u, min(cur.room & ~3u, 1024u));
+      const u32 i = whole + u32(lane);
+      if (i < min(cur.span, cur.room))
+        area[i] = reinterpret_cast<const u32*>(a.in[s].base + c.payload)[cur.src0 + i];
+      wave_lds_sync();
+    }
+    const u32 at = lds_address(area) + 4u * (cur.w ? cur.pick : 0u);
+    u64 v[8];
+    asm volatile(
+        "s_waitcnt lgkmcnt(0)\n\t"
+        "ds_read2_b32 %0, %8 offset0:0 offset1:1\n\t"
+        "ds_read2_b32 %1, %8 offset0:2 offset1:3\n\t"
+        "ds_read2_b32 %2, %8 offset0:4 offset1:5\n\t"
+        "ds_read2_b32 %3, %8 offset0:6 offset1:7\n\t"
+        "ds_read2_b32 %4, %8 offset0:8 offset1:9\n\t"
+        "ds_read2_b32 %5, %8 offset0:10 offset1:11\n\t"
+        "ds_read2_b32 %6, %8 offset0:12 offset1:13\n\t"
+        "ds_read2_b32 %7, %8 offset0:14 offset1:15\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+        : "v"(at)
+        : "memory");
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      t[2 * i] = u32(v[i]);
+      t[2 * i + 1] = u32(v[i] >> 32);
+    }
+    // operand s + 2, in the place of operand s
+    ahead = place(a, s + 2, meta, err);
+    const u32 b = share.seg * kWaveBlocks + u32(lane);
+    first_ahead = load_first(a, c, s + 2, b);
+    meta = load_meta(a, c, share, s + 3, b);
+    line();
+    ask_payload(a, c, s + 2, ahead, area, lane);
+    line();
   }
+  // Behind the last operand: what is still on its way (empty ranges, which leave zeros) has landed.
+  __device__ __forceinline__ void close() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 };
 
 // The common path keeps codes as 16-bit code - base + bias, where base is the first code of one of the operands'
@@ -192,7 +261,7 @@ __device__ inline void meet_far_codes(u32 (&acc)[16], u32 (&f)[16], i32 ahead) {
 template <bool IX, int OP>
 __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                               OperandPipe<IX>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
-  base = pipe.outlier_next;
+  base = pipe.first;
   // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits: no
   // check of the result is needed)
   bool outside = u32(base) + u32(kFirstLimit) > u32(2 * kFirstLimit);
@@ -205,7 +274,7 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceC
   u32 going = 1;
 #pragma nounroll
   while (going) {
-    pipe.take(a, c, share, s, wl, err);
+    pipe.take(a, c, share, s, wl, f, err);
     const u32 apart = u32(pipe.first) - u32(base);
     const bool far = apart + u32(kNearFirst) >= u32(2 * kNearFirst);
     const u32 start = ((far ? 0u : apart) + u32(kCodeBias<OP>)) & 0xffffu;
@@ -215,7 +284,7 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceC
 #pragma unroll
       for (int j = 0; j < 16; ++j) f[j] = both;
     } else {
-      operand_delta_pairs(pipe.cur, wl, f);
+      operand_delta_pairs(pipe.cur, f);
       // both halves of the block at once, the second one from zero; then it gets what the first one ends with
       f[0] = add_pairs(f[0], start);
 #pragma unroll
@@ -229,7 +298,6 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceC
       }
       outside |= ((OP == ZC_OP_MAX ? seen : ~seen) & 0x80008000u) != 0;
     }
-    wave_lds_sync();
     bool stop = false;
     if (__any(outside || far)) {               // (one vote, one branch: in a small call these are time, too)
       outside |= far && u32(pipe.first) + u32(kFirstLimit) > u32(2 * kFirstLimit);
@@ -269,7 +337,7 @@ __device__ __forceinline__ void close_packed(const u32 (&acc)[16], i32 base, Ext
 
 // A segment whose payload is more than stage_to_lds brings in (all its blocks are wide then) comes in two parts,
 // the blocks of lanes 0..31 and those of lanes 32..63.
-static_assert(kMostStaged >= 3 + 32 * 32 && kMostStaged + 32 <= u32(kWaveStage), "half a segment of widest blocks, and the reads behind its last word, must fit the wave's area");
+static_assert(kMostStaged >= 3 + 32 * 32 && kMostStaged + 32 <= kExtremeStage, "half a segment of widest blocks, and the reads behind its last word, must fit the wave's area");
 
 __device__ inline u32 operand_parts(const OperandPlace& p) { return p.span > kMostStaged ? 2u : 1u; }     // uniform
 
@@ -331,9 +399,8 @@ __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCa
       acc[j] = extreme<OP>(acc[j], i32(code));
     }
     if (++s >= a.k) return;
-    pipe.take(a, c, share, s, wl, err);
-    operand_delta_pairs(pipe.cur, wl, f);
-    wave_lds_sync();
+    pipe.take(a, c, share, s, wl, f, err);
+    operand_delta_pairs(pipe.cur, f);
   }
 }
 
@@ -342,11 +409,12 @@ template <bool IX, int OP>
 __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                                ExtremeBlock& out, i32 (&acc)[32], u32& err) {
   OperandPipe<IX> pipe;
-  pipe.open(a, c, share, err);
+  pipe.open(a, c, share, wl, err);
   u32 pairs[16], f[16], from = 0;
   i32 base;
   const int s = extreme_packed<IX, OP>(a, c, share, wl, pipe, pairs, f, from, base, err);
   if (s == a.k) {
+    pipe.close();
     close_packed<OP>(pairs, base, out);
     return true;
   }
@@ -361,6 +429,7 @@ __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const Reduce
     acc[j] = s ? code : OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
   }
   extreme_rest<IX, OP>(a, c, share, wl, pipe, acc, f, s, err);
+  pipe.close();
   return false;
 }
 
@@ -368,30 +437,29 @@ __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const Reduce
 template <bool IX, int OP>
 __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                             i32 (&acc)[32], u32& err) {
-  const ParsedHeader& h = c.h;
-  const u64 tend = tables_end(h.nb, IX);
 #pragma unroll
   for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
   OperandMeta meta;
   {
-    const u32 b = share.seg * kWaveBlocks + u32(fresh_lane());
-    meta = load_operand_meta(a, 0, c, share.seg, b, b < h.nb, share.live, IX, opaque_zero());
+    meta = load_operand_meta(0, a.in[0], c, share.seg, share.seg * kWaveBlocks + u32(fresh_lane()), share.live, IX);
   }
 #pragma nounroll
   for (int s = 0; s < a.k; ++s) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    const bool active = b < h.nb;
-    const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + tend);
-    const OperandPlace cur = place_operand(meta, h, IX, err, width_limit(c, s));
-    u32 code = u32(load_operand_outlier(a, s, h, b, active, IX));
+    const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + c.payload);
+    const OperandPlace cur = place_operand(meta, IX, err, width_limit(c, s));
+    u32 code = u32(load_operand_outlier(a.in[s].base, c, b));
     if (!__any(cur.w > 15)) {
       const OperandStage stage = load_operand_payload(payload, cur, lane);
-      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, c, share.seg, b, active, share.live, IX, opaque_zero());
+      if (s + 1 < a.k) meta = load_operand_meta(s + 1, a.in[s + 1], c, share.seg, b, share.live, IX);
       stage_to_lds(stage, cur, payload, wl, lane);
       wave_lds_sync();
       u32 f[16];
-      pick_operand_words(cur, wl, f);
+      const u32* const mine = wl + (cur.w ? cur.pick : 0u);
+#pragma unroll
+      for (int p = 0; p < 16; ++p) f[p] = mine[p];
+      keep_operand_words(cur, f, f);
       wave_lds_sync();
       magnitude_planes_to_twos<16>(f);
       transpose16x16_pairs(f);
@@ -401,7 +469,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
         acc[j] = extreme<OP>(acc[j], i32(code));
       }
     } else {
-      if (s + 1 < a.k) meta = load_operand_meta(a, s + 1, c, share.seg, b, active, share.live, IX, opaque_zero());
+      if (s + 1 < a.k) meta = load_operand_meta(s + 1, a.in[s + 1], c, share.seg, b, share.live, IX);
       u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
@@ -433,7 +501,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
 
 template <bool IX, int OP>
 __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kExtremeStage];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
@@ -446,7 +514,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   const ParsedHeader& h = c.h;
   const int wave = wave_id();
   const u64 tend = tables_end(h.nb, IX);
-  u32* const wl = lds + wave * kWaveStage;
+  u32* const wl = lds + wave * kExtremeStage;
   const u32 seg = uniform(tile * kTileWaves + u32(wave));
   const ReduceShare share{seg, seg < num_segments(h.nb)};
   u32 err = 0;
