@@ -325,6 +325,14 @@ __device__ inline float4 load_once(const float4* p) {
 constexpr int kRawBuffer = 0x00020000;
 constexpr int kAccessOnce = 2;
 
+// A buffer of `bytes` bytes.  What is a wave's share of something is loaded and stored with this and an offset per lane: the
+// range is what exists of it, so that no lane needs a comparison, a branch or an address of its own.  A wave that has its
+// SIMD to itself issues one instruction in some five cycles, so that in a call of few tiles such instructions are what
+// everything else waits for; in larger ones they take the place of others.
+__device__ inline __amdgpu_buffer_rsrc_t bytes_from(const void* at, u32 bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(at), 0, int(bytes), kRawBuffer);
+}
+
 // A zero in a vector register that the compiler cannot see through.  An address that has it
 // added is not provably the same in every lane, so the access becomes a vector memory load.
 // Vector loads return in order and have a counter of their own: several independent loads

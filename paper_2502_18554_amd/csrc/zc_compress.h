@@ -303,8 +303,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
   }
   {
     const u64 wblock0 = u64(tile) * kPackBlocks + u64(wave) * kWaveBlocks;
-    const u64 b = wblock0 + u64(lane);
-    const bool active = b < a.nb;
+    const bool active = u32(wblock0) + u32(lane) < u32(a.nb);      // (a stream has at most 2^26 blocks)
     if (TICKETS) {
       have = share_values(a.n, wblock0 * kBlockValues);
       load_raw(a, wblock0, lane, have, x);
@@ -356,10 +355,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     if (narrow) copy_staged_wave<16>(sink, pl, tb.words, wl, lane);
     else store_wide_wave<TICKETS>(a, sink, pl, tb.words, wblock0, have, lane, wl);
     finish_stream(sink, pl, tile, ntiles, tb);
-    if (active && tables_fit) {
-      a.out[widths_begin(a.nb, a.ix) + b] = u8(pl.w);
-      reinterpret_cast<i32*>(a.out + outliers_begin(a.nb, a.ix))[b] = bf.outlier;
-    }
+    store_tables<0>(sink, u32(wblock0) + u32(fresh_lane()), pl.w, bf.outlier);
   }
   if (err) raise_status(a.ctl, tag, err);
 }

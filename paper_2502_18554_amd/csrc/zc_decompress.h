@@ -50,19 +50,22 @@ struct WaveStage {
 // Four loads cover 1024 words; only whole 16-byte pieces are asked for here: the up to three
 // words beyond (a wave whose 64 blocks are all 15 bits wide, off the 16-byte grid) and the
 // last words of a stream that do not fill a piece are fetched by store_wave_stage.  The loads
-// are written without any branch: a lane with nothing to fetch reads the 16 bytes at `safe`
-// (the stream's header) instead.  (With a branch around a load and a zero on its other side,
-// or with the stream's last words fetched into single components of the same registers, the
-// compiler copied a component after every 16-byte load and waited for the load to do so: the
+// are written without any branch: a lane with nothing to fetch is outside the buffer's range.  (With a branch around a
+// load and a zero on its other side, or with the stream's last words fetched into single components of the same
+// registers, the compiler copied a component after every 16-byte load and waited for the load to do so: the
 // loads went out one round trip after the other.)
-__device__ inline WaveStage load_wave_stage(const u32* payload, u64 payload_words, u64 src0, u32 span, int lane,
-                                            const uint4* safe) {
+__device__ inline u32 whole_pieces(u64 payload_words, u64 src0, u32 span) {
+  const u64 room = payload_words > src0 ? (payload_words - src0) & ~u64(3) : 0;
+  const u32 wanted = min((span + 3u) & ~3u, 256u * kWaveStageLoads);
+  return room < wanted ? u32(room) : wanted;
+}
+__device__ inline WaveStage load_wave_stage(const u32* payload, u64 payload_words, u64 src0, u32 span, int lane) {
   WaveStage st;
+  const __amdgpu_buffer_rsrc_t share = bytes_from(payload + src0, 4u * whole_pieces(payload_words, src0, span));
 #pragma unroll
   for (int i = 0; i < kWaveStageLoads; ++i) {
-    const u32 idx = 4u * u32(lane) + 256u * u32(i);
-    const bool piece = idx < span && src0 + idx + 4 <= payload_words;
-    st.v[i] = *(piece ? reinterpret_cast<const uint4*>(payload + src0 + idx) : safe);
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * i, 0, 0);
+    st.v[i] = make_uint4(t.x, t.y, t.z, t.w);
   }
   return st;
 }
@@ -70,23 +73,11 @@ __device__ inline WaveStage load_wave_stage(const u32* payload, u64 payload_word
 __device__ inline void store_wave_stage(const WaveStage& st, const u32* payload, u64 payload_words, u64 src0, u32 span,
                                         u32* wl, int lane) {
 #pragma unroll
-  for (int i = 0; i < kWaveStageLoads; ++i) {
-    const u32 idx = 4u * u32(lane) + 256u * u32(i);
-    if (idx < span) *reinterpret_cast<uint4*>(wl + idx) = st.v[i];
-  }
-  const u32 staged = span < 256u * kWaveStageLoads ? span : 256u * kWaveStageLoads;
-  if (src0 + ((u64(staged) + 3) & ~u64(3)) > payload_words) {    // uniform: the wave that holds the end of the stream
-#pragma unroll
-    for (int i = 0; i < kWaveStageLoads; ++i) {
-      const u32 idx = 4u * u32(lane) + 256u * u32(i);
-      if (idx < span && src0 + idx + 4 > payload_words) {
-        for (u32 j = 0; j < 3; ++j)
-          if (src0 + idx + j < payload_words) wl[idx + j] = payload[src0 + idx + j];
-      }
-    }
-  }
-  if (span > 256u * kWaveStageLoads) {                           // uniform, and rare: words 1024 .. 1026
-    const u32 idx = 256u * kWaveStageLoads + u32(lane);
+  for (int i = 0; i < kWaveStageLoads; ++i)
+    if (256u * u32(i) < span) *reinterpret_cast<uint4*>(wl + 4u * u32(lane) + 256u * u32(i)) = st.v[i];      // uniform
+  const u32 whole = whole_pieces(payload_words, src0, span);
+  if (whole < span) {                                  // uniform, and rare: at most three words, or the end of the stream
+    const u32 idx = whole + u32(lane);
     if (idx < span && src0 + idx < payload_words) wl[idx] = payload[src0 + idx];
   }
 }
@@ -105,8 +96,7 @@ struct WavePayload {
 // stage_wide: the caller uses the copy of a segment that has wider blocks, too; if not, such a segment of a plain stream,
 // whose widths are known ahead of the copy, is not copied.
 __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload_words, u32 w, u64 seg_off, u32* wl, int lane,
-                                                 bool ix, u32 seg_words, bool may_be_wide, u32& err, const uint4* safe,
-                                                 bool stage_wide) {
+                                                 bool ix, u32 seg_words, bool may_be_wide, u32& err, bool stage_wide) {
   const u32 mis = u32(seg_off) & 3u;
   const u64 src0 = seg_off - mis;                      // in words, multiple of 4
   WaveStage st;
@@ -114,7 +104,7 @@ __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload
   if (ix) {
     // at most 64 * 16 words when no block is wider than 15 bits
     if (seg_words <= 64u * 16u && seg_off + seg_words <= payload_words) span = mis + seg_words;
-    st = load_wave_stage(payload, payload_words, src0, span, lane, safe);
+    st = load_wave_stage(payload, payload_words, src0, span, lane);
     store_wave_stage(st, payload, payload_words, src0, span, wl, lane);   // at once: the registers are free for what follows
   }
   bool unfit = false;
@@ -138,7 +128,7 @@ __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload
   wp.staged = wp.inside && wave_total <= 64u * 16u && (stage_wide || wp.wmax <= 15);
   if (wp.staged && !ix) {
     span = mis + wave_total;
-    st = load_wave_stage(payload, payload_words, src0, span, lane, safe);
+    st = load_wave_stage(payload, payload_words, src0, span, lane);
     store_wave_stage(st, payload, payload_words, src0, span, wl, lane);
   }
   return wp;
@@ -168,9 +158,8 @@ __device__ inline void pick_block_words(const WavePayload& wp, u64 seg_off, cons
 
 __device__ inline u32 wave_block_words(const u32* payload, u64 payload_words, u32 w, u64 seg_off, u32* wl, int lane,
                                        u32 (&lo)[16], u32 (&hi)[16], bool ix, u32 seg_words, bool may_be_wide,
-                                       u32& err, const uint4* safe) {
-  const WavePayload wp = stage_wave_payload(payload, payload_words, w, seg_off, wl, lane, ix, seg_words, may_be_wide, err, safe,
-                                            false);
+                                       u32& err) {
+  const WavePayload wp = stage_wave_payload(payload, payload_words, w, seg_off, wl, lane, ix, seg_words, may_be_wide, err, false);
   if (wp.wmax <= 15) {
     pick_block_words(wp, seg_off, wl, lo);
   } else {
@@ -293,21 +282,20 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
   // (no barrier below: waves are independent)
   if (seg >= num_segments(h.nb) || u64(seg) * (kWaveBlocks * kBlockValues) >= end_value || u64(seg) * (kWaveBlocks * kBlockValues) < first_value) return;
   const bool active = b < h.nb;
-  if (IX && active) w = u32(*at_bytes(a.in.base, u32(widths_begin(h.nb, true)) + b));
+  if (IX) w = u32(__builtin_amdgcn_raw_buffer_load_b8(bytes_from(a.in.base + widths_begin(h.nb, true), u32(h.nb)), int(b), 0, 0));
   if (!active) w = 0;
 
-  const i32* outliers = reinterpret_cast<const i32*>(a.in.base + outliers_begin(h.nb, IX));
   const u32* payload = reinterpret_cast<const u32*>(a.in.base + tables_end(h.nb, IX));
   const u64 payload_words = (h.total - tables_end(h.nb, IX)) / 4;
 
-  u32 cur = active ? u32(outliers[b]) : 0u;
+  u32 cur = __builtin_amdgcn_raw_buffer_load_b32(bytes_from(a.in.base + outliers_begin(h.nb, IX), 4u * u32(h.nb)), int(4u * b), 0, 0);
   const u64 seg_off = u64(uniform(seg_begin));
   i32 d[32];
   {
     u32 lo[16], hi[16];
     u32 err = 0;
     const u32 wmax = wave_block_words(payload, payload_words, w, seg_off, wl, lane, lo, hi, IX,
-                                      uniform(seg_end) - u32(seg_off), h.wide, err, reinterpret_cast<const uint4*>(a.in.base));
+                                      uniform(seg_end) - u32(seg_off), h.wide, err);
     if (IX && !index_ends_ok(h, seg, u32(seg_off), uniform(seg_end))) err |= status_bit(ZC_ERR_FORMAT);
     if (err && lane == 0) raise_status(a.ctl, tag, err);
     deltas_from_block_words(wmax, lo, hi, d);
@@ -326,8 +314,11 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
 
   // ---- transpose through LDS (two halves of 32 blocks), 16-byte coalesced stores ----
   const u64 v0 = u64(wblock0) * kBlockValues;
-  const bool full = v0 + u64(kWaveBlocks) * kBlockValues <= end_value;
-  float* const out = a.out - first_value;           // indexed by the value's number in the stream
+  float* const out = a.out + (v0 - first_value);
+  const u64 left = end_value - v0;
+  const u32 have = left < u32(kWaveBlocks * kBlockValues) ? u32(left) : u32(kWaveBlocks * kBlockValues);     // values of the wave
+  const u32 whole = have & ~3u;
+  const __amdgpu_buffer_rsrc_t to = bytes_from(out, 4u * whole);      // (whole 16-byte pieces)
 #pragma unroll
   for (int hh = 0; hh < 2; ++hh) {
     if ((lane >> 5) == hh) {
@@ -339,16 +330,12 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
     wave_lds_sync();
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const u64 idx = v0 + u64(1024 * hh + 256 * i + 4 * lane);
-      const float4 v = *reinterpret_cast<const float4*>(wl + (8 * i + (lane >> 3)) * kStageRow + 4 * (lane & 7));
-      if (full) {
-        store_once(reinterpret_cast<float4*>(out + idx), v);
-      } else {
-        if (idx + 0 < end_value) out[idx + 0] = v.x;
-        if (idx + 1 < end_value) out[idx + 1] = v.y;
-        if (idx + 2 < end_value) out[idx + 2] = v.z;
-        if (idx + 3 < end_value) out[idx + 3] = v.w;
-      }
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(wl + (8 * i + (lane >> 3)) * kStageRow + 4 * (lane & 7));
+      __builtin_amdgcn_raw_buffer_store_b128(v, to, 16 * lane + 4096 * hh + 1024 * i, 0, kAccessOnce);
+    }
+    if (have != whole && int(whole >> 10) == hh) {     // uniform: the values behind the last piece
+      const u32 at = whole + u32(lane);
+      if (at < have) reinterpret_cast<u32*>(out)[at] = wl[((at & 1023u) >> 5) * kStageRow + (at & 31u)];
     }
     wave_lds_sync();
   }

@@ -97,25 +97,48 @@ __device__ inline void write_stream_header(u8* out, u64 n, u64 nb, u32 eb_bits, 
 // line boundary, so a line is written by one instruction and not by the tail of one and the head of
 // the next.  The stores bypass the caches: a stream is on its way to another device, or to a later
 // call, and keeping it in cache lines would only push the write-back into the kernels that follow.
-// ROUNDS * 64 >= limit + 31.
+// A round is a read and a store (with a comparison, a selection and a 64-bit address for each, and the like in the tables'
+// stores and in the loads of the received stream, a ring round of 2^26 values took 93 us, now 89.5; Sum of 8 x 2^24 49.8, 48.7).
+// ROUNDS * 64 >= limit + 31.  The last group of rounds may read LDS behind the wave's words, up to kCopyOver words behind
+// 64 * (ROUNDS - 1) of them, which nothing comes of.
+constexpr int kCopyOver = 64;
 template <int ROUNDS>
 __device__ inline void copy_staged_words(const u32* wl, u32* dst, u32 limit, int lane) {
   const u32 lead = uniform(u32(reinterpret_cast<uintptr_t>(dst) >> 2) & 31u);   // words of dst's line before dst
-  const u32 end = uniform(limit) + lead;
-  // four rounds at a time: their LDS reads are all under way before the first store needs its word
+  limit = uniform(limit);
+  // the first round, without the lanes ahead of dst ...
+  {
+    const u32 i = u32(lane) - lead;            // (wraps for those)
+    const u32 v = wl[i < limit ? i : 0u];
+    if (i < limit) store_once(dst + i, v);
+  }
+  // ... and the others, in which every lane has its place and only the last one ends early; four at a time: their LDS
+  // reads are all under way before the first store needs its word
+  const u32 first = 64u - lead;
+  if (limit <= first) return;                  // uniform
+  const u32 rest = limit - first;
+  const __amdgpu_buffer_rsrc_t to = bytes_from(dst + first, 4u * rest);
+  const u32* const from = wl + first + u32(lane);
 #pragma unroll
-  for (int r0 = 0; r0 < ROUNDS; r0 += 4) {
-    if (64u * u32(r0) >= end) break;           // uniform
-    u32 i[4], v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      i[k] = u32(lane) + 64u * u32(r0 + k) - lead;   // wraps for the lanes ahead of dst: they sit out
-      v[k] = wl[i[k] < limit ? i[k] : 0u];
-    }
+  for (int r0 = 0; r0 < ROUNDS - 1; r0 += 4) {
+    if (64u * u32(r0) >= rest) break;          // uniform
+    u32 v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      if (r0 + k < ROUNDS && i[k] < limit) store_once(dst + i[k], v[k]);
+      if (r0 + k < ROUNDS - 1) v[k] = from[64 * (r0 + k)];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (r0 + k < ROUNDS - 1) __builtin_amdgcn_raw_buffer_store_b32(v[k], to, 4 * lane + 256 * (r0 + k), 0, kAccessOnce);
   }
+}
+
+// Width byte and first code of the lane's block b (nothing for a block that does not exist, or where the tables do not
+// fit the caller's buffer).  AUX: the cache policy of the stores.
+template <int AUX>
+__device__ inline void store_tables(const PayloadSink& s, u32 b, u32 w, i32 outlier) {
+  const u32 nb = s.out_cap >= tables_end(s.nb, s.ix) ? u32(s.nb) : 0u;
+  __builtin_amdgcn_raw_buffer_store_b8(u8(w), bytes_from(s.out + widths_begin(s.nb, s.ix), nb), int(b), 0, AUX);
+  __builtin_amdgcn_raw_buffer_store_b32(u32(outlier), bytes_from(s.out + outliers_begin(s.nb, s.ix), 4u * nb), int(4u * b), 0, AUX);
 }
 
 // Writes the payload words of the lanes of one half-wave to the wave's staging area and copies

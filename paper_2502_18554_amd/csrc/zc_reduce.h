@@ -191,11 +191,7 @@ __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c
   const u32 limit = u64(pl.wave_total) < room ? pl.wave_total : u32(room);
   copy_staged_words<NW + 1>(wl, dst, limit, lane);
   wave_lds_sync();
-  if (active && a.out_cap >= tend) {
-    // (the whole output stream is written with the non-temporal hint, see store_once)
-    __builtin_nontemporal_store(u8(w), a.out + widths_begin(h.nb, ix) + b);
-    __builtin_nontemporal_store(i32(outlier), reinterpret_cast<i32*>(a.out + outliers_begin(h.nb, ix)) + b);
-  }
+  store_tables<kAccessOnce>(sink, b, w, i32(outlier));     // (the whole output stream is written with the non-temporal hint, see store_once)
   finish_stream(sink, pl, tile, ntiles, tb);
 }
 
@@ -230,14 +226,9 @@ struct OperandPlace {
   u32 room;         // uniform: words from src0 to the end of the caller's buffer
 };
 
-// Loads of what is the wave's share of an operand are buffer loads whose range is what exists of it: no lane needs a
-// comparison, a branch or another address.  (With those an operand took 420 instructions; a wave that has its SIMD to
-// itself issues one in five cycles, so that they were what a call of few tiles waited for: Sum of 8 x 1024 values 15.8 us,
-// now 13.9, of 4 x 4 194 301 hard ones 15.5, now 14.5.  Larger calls gain as well: 8 x 2^26 161.6 -> 157.0, on one machine.)
-__device__ inline __amdgpu_buffer_rsrc_t bytes_from(const u8* at, u32 bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u8*>(at), 0, int(bytes), kRawBuffer);
-}
-
+// (A wave's loads of its share of an operand are buffer loads, see bytes_from.  With conditions and addresses per lane an
+// operand took 420 instructions: Sum of 8 x 1024 values 15.8 us, now 13.9, of 4 x 4 194 301 hard ones 15.5, now 14.5,
+// of 8 x 2^26 161.6, now 157.0.)
 // The first code of the lane's block (b; 0 if there is no such block).
 __device__ inline i32 load_operand_outlier(const u8* base, const ReduceCall& c, u32 b) {
   return i32(__builtin_amdgcn_raw_buffer_load_b32(bytes_from(base + c.firsts, 4u * c.nb), int(4u * b), 0, 0));
@@ -325,20 +316,10 @@ __device__ inline void stage_to_lds(const OperandStage& st, const OperandPlace& 
   for (int i = 0; i < kStageLoads; ++i) {
     if (256u * u32(i) < p.span) *reinterpret_cast<uint4*>(wl + 4u * u32(lane) + 256u * u32(i)) = st.v[i];      // uniform
   }
-  const u32 staged = p.span < 256u * kStageLoads ? p.span : 256u * kStageLoads;
-  if (((staged + 3u) & ~3u) > p.room) {            // uniform, and rare: the buffer ends inside a 16-byte piece
-#pragma unroll
-    for (int i = 0; i < kStageLoads; ++i) {
-      const u32 idx = 4u * u32(lane) + 256u * u32(i);
-      if (idx < p.span && idx + 4 > p.room) {
-        for (u32 j = 0; j < 3; ++j)
-          if (idx + j < p.room) wl[idx + j] = payload[p.src0 + idx + j];
-      }
-    }
-  }
-  if (p.span > 256u * kStageLoads) {               // uniform, and rare: words 1024 .. 1026
-    const u32 idx = 256u * kStageLoads + u32(lane);
-    if (idx < p.span) wl[idx] = payload[p.src0 + idx];
+  if (p.span > 256u * kStageLoads || ((p.span + 3u) & ~3u) > p.room) {      // uniform, and rare: more than four loads, or the buffer ends inside a 16-byte piece
+    const u32 whole = min(min((p.span + 3u) & ~3u, p.room & ~3u), 256u * kStageLoads);
+    const u32 idx = whole + u32(lane);
+    if (idx < min(p.span, p.room)) wl[idx] = payload[p.src0 + idx];
   }
 }
 
@@ -775,7 +756,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
 // operand loop only: what the placement needs waits there.
 template <bool IX>
 __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage];   // also holds an operand's payload
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage + kCopyOver];   // also holds an operand's payload
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];

@@ -513,7 +513,6 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   if (!open_reduce<IX>(a, c, meta, false, tile, ntiles, &sh_tile, &survey)) return;
   const ParsedHeader& h = c.h;
   const int wave = wave_id();
-  const u64 tend = tables_end(h.nb, IX);
   u32* const wl = lds + wave * kExtremeStage;
   const u32 seg = uniform(tile * kTileWaves + u32(wave));
   const ReduceShare share{seg, seg < num_segments(h.nb)};
@@ -573,10 +572,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
       else return phi[I - 17];
     }, pl, tb.words, wl, lane);
   }
-  if (active && a.out_cap >= tend) {     // (at the very end: a store under way is waited for by every poll of the look-back)
-    __builtin_nontemporal_store(u8(pl.w), a.out + widths_begin(h.nb, IX) + b);
-    __builtin_nontemporal_store(eb.outlier, reinterpret_cast<i32*>(a.out + outliers_begin(h.nb, IX)) + b);
-  }
+  store_tables<kAccessOnce>(sink, b, pl.w, eb.outlier);     // (at the very end: a store under way is waited for by every poll of the look-back)
   finish_stream(sink, pl, tile, ntiles, tb);
 }
 

@@ -331,7 +331,7 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
 // kernel sums itself, one for the same reason (as an argument it cost 2^25 values with an index ahead 52.3 us, now 50.9).
 template <bool IX, bool SELF, int OP, bool TICKETS>
 __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage];
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage + kCopyOver];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
@@ -454,14 +454,14 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     seg_begin = 0;
     seg_end = 0;
   }
-  const u32 outlier_in = active ? u32(reinterpret_cast<const i32*>(a.in.base + outliers_begin(h.nb, IX))[b]) : 0u;
+  const u32 outlier_in = __builtin_amdgcn_raw_buffer_load_b32(bytes_from(a.in.base + outliers_begin(h.nb, IX), 4u * u32(h.nb)), int(4u * b), 0, 0);
 
   // ---- the received segment: scan of the widths, checks, payload into LDS ----
   const u32* const payload_in = reinterpret_cast<const u32*>(a.in.base + tend);
   u32 err = 0;
   const u64 seg_off = u64(uniform(seg_begin));
   const WavePayload wp = stage_wave_payload(payload_in, (h.total - tend) / 4, w, seg_off, wl, lane, IX,
-                                            uniform(seg_end) - u32(seg_off), h.wide, err, reinterpret_cast<const uint4*>(a.in.base), true);
+                                            uniform(seg_end) - u32(seg_off), h.wide, err, true);
   if (IX && seg_live && !index_ends_ok(h, seg, u32(seg_off), uniform(seg_end))) err |= status_bit(ZC_ERR_FORMAT);
 
   CompressArgs qa;               // the quantiser's constants, from the stream's own bound
@@ -610,10 +610,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     step_blocks_slow<IX, OP, kStore>(a, h, qa, seg, __ballot(active), u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave,
                                      reinterpret_cast<u32*>(a.out + tend) + dst, cap_words > dst ? cap_words - dst : 0, ignored);
   }
-  if (active && a.out_cap >= tend) {
-    a.out[widths_begin(h.nb, IX) + b] = u8(pl.w);
-    reinterpret_cast<i32*>(a.out + outliers_begin(h.nb, IX))[b] = outlier;
-  }
+  store_tables<0>(sink, b, pl.w, outlier);
   finish_stream(sink, pl, tile, ntiles, tb);
 }
 
