@@ -37,7 +37,7 @@ __host__ __device__ constexpr u64 num_blocks(u64 n) { return (n + kBlockValues -
 __host__ __device__ constexpr u64 num_tiles(u64 nb) { return (nb + kTileBlocks - 1) / kTileBlocks; }
 // No stream has more tiles than this (n <= ZC_MAX_N), so block and segment numbers fit 32 bits.
 constexpr u64 kMaxTiles = (ZC_MAX_N / kBlockValues + kTileBlocks - 1) / kTileBlocks;
-__host__ __device__ inline u32 psize_words(u32 w) { return w ? 1 + w : 0; }
+__host__ __device__ inline u32 psize_words(u32 w) { return w + (w < 1u ? w : 1u); }      // 1 + w, but 0 for w = 0
 
 // Stream layout.  The plain stream (version 1) is header, width table, outlier table,
 // payload.  The indexed stream (Section 3.5.2 keeps the compressed size of every chunk in

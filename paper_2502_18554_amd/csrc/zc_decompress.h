@@ -77,6 +77,7 @@ __device__ inline void store_wave_stage(const WaveStage& st, const u32* payload,
     if (256u * u32(i) < span) *reinterpret_cast<uint4*>(wl + 4u * u32(lane) + 256u * u32(i)) = st.v[i];      // uniform
   const u32 whole = whole_pieces(payload_words, src0, span);
   if (whole < span) {                                  // uniform, and rare: at most three words, or the end of the stream
+    asm volatile("");                                  // (keeps the branch: merged with the condition below, all of this runs every time)
     const u32 idx = whole + u32(lane);
     if (idx < span && src0 + idx < payload_words) wl[idx] = payload[src0 + idx];
   }

@@ -130,12 +130,12 @@ struct OperandPipe {
   i32 first, first_next, first_ahead;      // the first code of the lane's block in them
   OperandMeta meta;                        // operand s + 3
 
-  __device__ __forceinline__ static OperandMeta load_meta(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32 b) {
-    const int t = min(s, a.k - 1);
-    return load_operand_meta(t, a.in[t], c, share.seg, b, share.live, IX);
-  }
-  __device__ __forceinline__ static i32 load_first(const ReduceArgs& a, const ReduceCall& c, int s, u32 b) {
-    return load_operand_outlier(a.in[min(s, a.k - 1)].base, c, b);
+  // Where operands s ... s + 3 are, asked for a step before it is needed (behind the last operand: the last one).
+  StreamRef at0, at1, at2, at3;
+
+  __device__ __forceinline__ static OperandMeta load_meta(const ReduceArgs& a, const StreamRef& in, const ReduceCall& c, const ReduceShare& share,
+                                                          int s, u32 b) {
+    return load_operand_meta(min(s, a.k - 1), in, c, share.seg, b, share.live, IX);
   }
   __device__ __forceinline__ static OperandPlace place(const ReduceArgs& a, int s, const OperandMeta& m, u32& err) {
     u32 bad = 0;
@@ -146,10 +146,9 @@ struct OperandPipe {
   }
   // The operand's payload for this wave, from the 16-byte boundary at or below its segment on, into `area`: whole 16-byte
   // pieces inside the caller's buffer only (the rest: see take).  All 1024 words of the area are written.
-  __device__ __forceinline__ static void ask_payload(const ReduceArgs& a, const ReduceCall& c, int s, const OperandPlace& p, u32* area,
-                                                     int lane) {
+  __device__ __forceinline__ static void ask_payload(const StreamRef& in, const ReduceCall& c, const OperandPlace& p, u32* area, int lane) {
     const u32 whole = min((p.span + 3u) & ~3u, p.room & ~3u);
-    const __amdgpu_buffer_rsrc_t share = bytes_from(a.in[min(s, a.k - 1)].base + c.payload + 4 * u64(p.src0), 4u * whole);
+    const __amdgpu_buffer_rsrc_t share = bytes_from(in.base + c.payload + 4 * u64(p.src0), 4u * whole);
 #pragma unroll
     for (int i = 0; i < kStageLoads; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(share, (LdsWord*)(area + 256 * i), 16, 16 * lane + 1024 * i, 0, 0, kAccessOnce);
@@ -163,16 +162,20 @@ struct OperandPipe {
   __device__ __forceinline__ void open(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl, u32& err) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    const OperandMeta m0 = load_meta(a, c, share, 0, b), m1 = load_meta(a, c, share, 1, b);
-    meta = load_meta(a, c, share, 2, b);
-    first = load_first(a, c, 0, b);
-    first_next = load_first(a, c, 1, b);
+    at0 = a.in[0];
+    at1 = a.in[min(1, a.k - 1)];
+    at2 = a.in[min(2, a.k - 1)];
+    at3 = a.in[min(3, a.k - 1)];
+    const OperandMeta m0 = load_meta(a, at0, c, share, 0, b), m1 = load_meta(a, at1, c, share, 1, b);
+    meta = load_meta(a, at2, c, share, 2, b);
+    first = load_operand_outlier(at0.base, c, b);
+    first_next = load_operand_outlier(at1.base, c, b);
     line();
     cur = place(a, 0, m0, err);
-    ask_payload(a, c, 0, cur, wl, lane);
+    ask_payload(at0, c, cur, wl, lane);
     line();
     next = place(a, 1, m1, err);
-    ask_payload(a, c, 1, next, wl + kOperandArea, lane);
+    ask_payload(at1, c, next, wl + kOperandArea, lane);
     line();
   }
   // The words of operand s from its lanes' sign words on, and operand s + 2 on its way.  Operands in turn from 0 on.
@@ -184,14 +187,19 @@ struct OperandPipe {
       first = first_next;
       next = ahead;
       first_next = first_ahead;
+      at0 = at1;
+      at1 = at2;
+      at2 = at3;
+      at3 = a.in[min(s + 3, a.k - 1)];
     }
     line();
     asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
     if (cur.span > 1024u || ((cur.span + 3u) & ~3u) > cur.room) {      // uniform, and rare: words 1024 .. 1026, or the buffer ends inside a 16-byte piece
+      asm volatile("");                        // (keeps the branch)
       const u32 whole = min((cur.span + 3u) & ~3u, min(cur.room & ~3u, 1024u));
       const u32 i = whole + u32(lane);
       if (i < min(cur.span, cur.room))
-        area[i] = reinterpret_cast<const u32*>(a.in[s].base + c.payload)[cur.src0 + i];
+        area[i] = reinterpret_cast<const u32*>(at0.base + c.payload)[cur.src0 + i];
       wave_lds_sync();
     }
     const u32 at = lds_address(area) + 4u * (cur.w ? cur.pick : 0u);
@@ -218,10 +226,10 @@ struct OperandPipe {
     // operand s + 2, in the place of operand s
     ahead = place(a, s + 2, meta, err);
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    first_ahead = load_first(a, c, s + 2, b);
-    meta = load_meta(a, c, share, s + 3, b);
+    first_ahead = load_operand_outlier(at2.base, c, b);
+    meta = load_meta(a, at3, c, share, s + 3, b);
     line();
-    ask_payload(a, c, s + 2, ahead, area, lane);
+    ask_payload(at2, c, ahead, area, lane);
     line();
   }
   // Behind the last operand: what is still on its way (empty ranges, which leave zeros) has landed.
