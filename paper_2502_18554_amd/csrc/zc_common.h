@@ -557,7 +557,12 @@ __device__ inline bool own_chain_scalar(const u64* desc, u32 tile, u64 tag, u32&
 //   Sum of 8   489 tiles 19.8 17.6 | 768: 22.2 22.3 | 1024: 24.4 24.7; of power-law fields 25.2 25.8 and 28.2 31.0
 // The tiles of a Sum of many operands end further apart than others, and while they stream, a vector load takes three
 // times as long as the scalar loads of a chain: its limit (see sum_looks_direct) is lower.
+// Not for a stream produced in parts: a part may follow one that was given with ZC_CHAINS_COHERENT, whose tiles have
+// published chain sums in the place of their sizes.
 constexpr u32 kDirectTiles = 1024;
+__device__ inline bool looks_direct(u32 ntiles, u32 limit, bool coherent, u32 part_end) {
+  return ntiles <= limit && !coherent && part_end == 0;
+}
 
 // Called by all 64 lanes of a wave.  A lane inspects tile `head` (none if negative), and where that has published its size
 // but no chain sum, the tile `stride` before it, and so on: the sum over the lanes, modulo 2^32 (a stream has fewer

@@ -327,7 +327,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     lds_barrier();     // wave totals visible
     sum_wave_totals(sh_wave_total, wave, a.ix != 0, pl);
     // publish the tile's size as early as possible: the tiles after this one wait for it
-    const PayloadSink sink{a.out, a.out_cap, a.nb, a.ctl, a.desc, a.ix != 0, a.coherent != 0, ntiles <= kDirectTiles && !a.coherent, a.part_end, tag};
+    const PayloadSink sink{a.out, a.out_cap, a.nb, a.ctl, a.desc, a.ix != 0, a.coherent != 0, looks_direct(ntiles, kDirectTiles, a.coherent != 0, a.part_end), a.part_end, tag};
     if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
 
     // ---- fields -> sign + plane words, then the back half ----

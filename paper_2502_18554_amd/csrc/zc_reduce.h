@@ -90,7 +90,7 @@ __device__ inline bool block_out_of_range(const u32 (&mag)[NP], u32 sign, i64 ou
 
 // Whether the tiles of a Sum look back directly (see kDirectTiles, with the measurements).
 __device__ inline bool sum_looks_direct(const ReduceArgs& a, u32 ntiles) {
-  return !a.coherent && ntiles <= (a.k <= 3 ? kDirectTiles : kDirectTiles / 2);
+  return looks_direct(ntiles, a.k <= 3 ? kDirectTiles : kDirectTiles / 2, a.coherent != 0, a.end_tile);
 }
 
 // Range screen and placement of a summed block inside its wave and tile, then the shared

@@ -78,3 +78,34 @@ def test_decompress_of_few_tiles(zcref, stream_variant, tiles, k):
         assert st == ZC_ERR_FORMAT and bool((d_out == 7.0).all())
         st, outs, _ = u.gpu_decompress_many(refs[:-1] + [broken], [n] * k)
         assert st == ZC_ERR_FORMAT and all(np.isnan(o).all() for o in outs)
+
+
+@pytest.mark.parametrize("tiles", [12, 40])
+def test_parts_that_look_back_in_different_ways(zcref, stream_variant, tiles):
+    """A part may be given with ZC_CHAINS_COHERENT and the next without, or the other way round: the tiles of a part read
+    what those of the parts before it have published, however they looked back themselves."""
+    if stream_variant == "plain":
+        return
+    u, zc = gpuutil, gpuutil.zc
+    n = 2 * tiles * TILE - 4097
+    xs = [_values(n, 70 + i) for i in range(2)]
+    eb = synth.abs_bound(torch.from_numpy(xs[0]), 1e-3)
+    refs = [zcref.compress(x, eb)[1] for x in xs]
+    d_xs, d_refs, sizes = [u.to_dev(x) for x in xs], [u.to_dev(r) for r in refs], [r.size for r in refs]
+    wanted = [refs[0], zcref.reduce(refs)[1], zcref.reduce_step(refs[0], xs[1])[1]]
+    cut = tiles // 2 * 2 * TILE
+    d_out, ws = torch.empty(zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV), u.workspace(n, 2)
+    calls = [lambda *part: zc.zc_compress_part(d_xs[0], n, eb, *part, d_out, ws),
+             lambda *part: zc.zc_reduce_compressed_part(d_refs, sizes, n, *part, d_out, ws),
+             lambda *part: zc.zc_reduce_step_part(d_refs[0], sizes[0], d_xs[1], n, 0, *part, d_out, ws)]
+    try:
+        for want, call in zip(wanted, calls):
+            for first_coherent in (True, False):
+                u.set_coherent(first_coherent)
+                assert call(0, cut)[0] == ZC_OK
+                u.set_coherent(not first_coherent)
+                st, total = call(cut, n - cut)
+                got = d_out[:total].cpu().numpy()
+                assert st == ZC_OK and got.tobytes() == want.tobytes(), u.first_diff(got, want)
+    finally:
+        u.set_coherent(False)
