@@ -124,6 +124,29 @@ ZC_HD inline void magnitude_planes_to_twos(uint32_t (&r)[N]) {
   r[N - 1] = s ^ carry;
 }
 
+// Planes 0..14 in r[0..15), of which those from w (<= 15) on may hold anything, and a sign word in r[15] -> the deltas as
+// transpose16x16_pairs leaves fields, in place (w = 0: zeros, whatever r holds).  Dropping the planes that are not the
+// block's own and negating is done on the fields, where it takes three operations per two values: on the planes it is a mask, an AND
+// and two operations of the ripple for each of fifteen planes, one behind the other (magnitude_planes_to_twos).
+// Max of 8 x 2^24 values, bound by arithmetic: 59.2 -> 58.5 us.
+ZC_HD inline void deltas_from_raw_planes16(uint32_t (&r)[16], uint32_t w) {
+  transpose16x16_pairs(r);
+  const uint32_t own = ((1u << w) - 1u) * 0x10001u;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef short pair_t __attribute__((ext_vector_type(2)));
+    const pair_t sign = __builtin_bit_cast(pair_t, r[j]) >> short(15);
+    const uint32_t t = __builtin_amdgcn_bitop3_b32(r[j], own, __builtin_bit_cast(uint32_t, sign), 0x6A);      // (field & own) ^ sign
+    r[j] = __builtin_bit_cast(uint32_t, pair_t(__builtin_bit_cast(pair_t, t) - sign));
+#else
+    const uint32_t ones = ((r[j] >> 15) & 0x10001u) * 0xFFFFu;
+    const uint32_t t = (r[j] & own) ^ ones;
+    r[j] = (((t & 0xFFFFu) + (ones & 1u)) & 0xFFFFu) | ((t & 0xFFFF0000u) + (ones & 0x10000u));
+#endif
+  }
+}
+
 // Low 16 bits of two values in one word / low 8 bits of four values in one word.
 ZC_HD inline uint32_t pack16(uint32_t lo, uint32_t hi) {
 #if defined(__HIP_DEVICE_COMPILE__)

@@ -22,13 +22,13 @@
 // than 15 bits does so from the start, in all its waves (extreme_any).
 // Measured, 8 x 2^24 values unless said otherwise, first with codes unpacked throughout (145 registers, three waves
 // per SIMD, and a kernel of its own for wide blocks, launched with every call), then now:
-//   smooth field, bound 1e-4 of its range                     79.5   61.5 us
+//   smooth field, bound 1e-4 of its range                     79.5   58.5 us
 //   8 x 2^23 (1024 tiles)                                     36.2   32.9
 //   16 x 2^20                                                 29.7   24.8
 //   hard data, 4 x 4 000 000                                  28.2   15.6
-//   8 x 1024                                                  17.6   15.0
+//   8 x 1024                                                  17.6   14.3
 // (the last four: before payloads went straight to LDS and loads were trimmed, see OperandPipe and load_operand_meta).
-// 128 registers, four waves per SIMD, and 24 bytes of scratch (12 on plain streams) that only the
+// 122 registers, four waves per SIMD, and 12 bytes of scratch that only the
 // wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
 // is computed where it is used: with both in registers across the loops these spilled 240 bytes, and every reload waits
 // for the loads under way.
@@ -87,8 +87,8 @@ __device__ inline void keep_operand_words(const OperandPlace& cur, const u32 (&t
 // The deltas of the lane's block, fields as transpose16x16_pairs leaves them (word j: deltas j and j + 16), from the words
 // that were read from its wave's staging area, in place.
 __device__ inline void operand_delta_pairs(const OperandPlace& cur, u32 (&f)[16]) {
-  keep_operand_words(cur, f, f);
   if (!__any(cur.w > 7)) {                     // byte fields: word j = deltas j, j + 8, j + 16, j + 24
+    keep_operand_words(cur, f, f);
     u32 r[8];
 #pragma unroll
     for (int p = 0; p < 7; ++p) r[p] = f[p];
@@ -101,8 +101,11 @@ __device__ inline void operand_delta_pairs(const OperandPlace& cur, u32 (&f)[16]
       f[j + 8] = __builtin_amdgcn_perm(0u, r[j], 0x09030801u);
     }
   } else {
-    magnitude_planes_to_twos<16>(f);
-    transpose16x16_pairs(f);
+    const u32 sign = f[0];
+#pragma unroll
+    for (int p = 0; p < 15; ++p) f[p] = f[p + 1];
+    f[15] = sign;
+    deltas_from_raw_planes16(f, cur.w);
   }
 }
 

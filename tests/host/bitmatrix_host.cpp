@@ -56,4 +56,16 @@ void bm_deltas_from_planes(const uint32_t* in, int cls, int32_t* dout) {
   for (int j = 0; j < 32; ++j) dout[j] = d[j];
 }
 
+// in: sign word, then planes 0..14, of which those from w on hold anything.
+void bm_deltas_from_raw_planes(const uint32_t* in, uint32_t w, int32_t* d) {
+  uint32_t r[16];
+  r[15] = in[0];
+  for (int p = 0; p < 15; ++p) r[p] = in[1 + p];
+  zc::deltas_from_raw_planes16(r, w);
+  for (int j = 0; j < 16; ++j) {
+    d[j] = int16_t(r[j] & 0xffffu);
+    d[j + 16] = int16_t(r[j] >> 16);
+  }
+}
+
 }  // extern "C"

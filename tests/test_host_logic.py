@@ -120,6 +120,22 @@ def bm():
     return C.CDLL(lib)
 
 
+@pytest.mark.parametrize("w", range(16))
+def test_deltas_from_planes_that_are_followed_by_others(bm, w):
+    """The planes behind a block's own, and the sign of a block without payload, may hold anything."""
+    rng = np.random.default_rng(w)
+    for trial in range(40):
+        words = rng.integers(0, 1 << 32, 16, dtype=np.uint64).astype(np.uint32)
+        if trial < 4:
+            words[:1 + w] = [0, 0xffffffff][trial & 1]
+            words[1 + w:] = [0, 0xffffffff][trial >> 1]
+        bits = np.unpackbits(words.view(np.uint8), bitorder="little").reshape(16, 32).astype(np.int64)
+        mag = sum((bits[1 + p] << p for p in range(w)), np.zeros(32, np.int64))
+        d = np.zeros(32, np.int32)
+        bm.bm_deltas_from_raw_planes(words.ctypes.data_as(C.POINTER(C.c_uint32)), w, d.ctypes.data_as(C.POINTER(C.c_int32)))
+        assert np.array_equal(d, np.where(bits[0] == 1, -mag, mag))
+
+
 @pytest.mark.parametrize("cls,maxw", [(8, 7), (816, 7), (16, 15), (32, 31)])
 def test_bit_matrix_transposes_match_packbits(bm, cls, maxw):
     rng = np.random.default_rng(cls)
