@@ -239,7 +239,13 @@ void* scratch_of_current_device() {
 
 namespace {
 template <int OP>
-void (*pick_step_kernel(bool ix, bool self, bool tickets))(StepArgs) {
+void (*pick_step_kernel(bool ix, bool self, bool tickets, u64 tiles))(StepArgs) {
+  if constexpr (OP == ZC_OP_SUM) {
+    if (tiles > kStepAtOnce) {               // (more than a call of plain streams sums itself)
+      if (ix) return tickets ? step_kernel<true, false, OP, true, 6> : step_kernel<true, false, OP, false, 6>;
+      if (!self) return tickets ? step_kernel<false, false, OP, true, 6> : step_kernel<false, false, OP, false, 6>;
+    }
+  }
   if (ix) return tickets ? step_kernel<true, false, OP, true> : step_kernel<true, false, OP, false>;
   if (self) return tickets ? step_kernel<false, true, OP, true> : step_kernel<false, true, OP, false>;
   return tickets ? step_kernel<false, false, OP, true> : step_kernel<false, false, OP, false>;
@@ -602,9 +608,9 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   }
   void (*kernel)(StepArgs) = nullptr;
   const bool tickets = ta.ticketed != 0;
-  if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, self, tickets);
-  else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, self, tickets);
-  else kernel = pick_step_kernel<ZC_OP_MIN>(ix, self, tickets);
+  if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, self, tickets, tiles);
+  else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, self, tickets, tiles);
+  else kernel = pick_step_kernel<ZC_OP_MIN>(ix, self, tickets, tiles);
   launch_main(ZC_KERNEL_REDUCE_STEP, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ta);
   if (!launch_ok()) return ZC_ERR_HIP;
   if (!out_bytes) return ZC_OK;

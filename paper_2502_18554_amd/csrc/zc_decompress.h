@@ -142,19 +142,31 @@ __device__ inline WavePayload stage_wave_payload(const u32* payload, u64 payload
 // afterwards; the area is large enough for 15 words behind any staged word).  A loop that
 // stops at the wave's widest block costs far more than the reads it saves: it is compiled as
 // a loop, with a wait after every read.
-__device__ inline void pick_block_words(const WavePayload& wp, u64 seg_off, const u32* wl, u32 (&lo)[16]) {
+// In two parts: the words as they come, and without what is not the block's own (`w`: its width, 0 if it has no payload).
+__device__ inline u32 own_width(const WavePayload& wp) { return wp.inside ? wp.w : 0u; }
+__device__ inline void pick_raw_words(const WavePayload& wp, u64 seg_off, const u32* wl, u32 (&lo)[16]) {
   static_assert(kWaveStage >= 1027 + 16, "reads behind the last staged word stay inside the staging area");
   wave_lds_sync();
-  const bool have = wp.w && wp.inside;
-  const u32* mine = wl + (have ? (u32(seg_off) & 3u) + wp.off_in_wave : 0u);
-  u32 t[16];
+  const u32* mine = wl + (own_width(wp) ? (u32(seg_off) & 3u) + wp.off_in_wave : 0u);
+  lo[15] = mine[0];
 #pragma unroll
-  for (int p = 0; p < 16; ++p) t[p] = mine[p];
-  const u32 keep = have ? (1u << wp.w) - 1u : 0u;      // bit p: the block has plane p
-  lo[15] = have ? t[0] : 0u;
-#pragma unroll
-  for (int p = 0; p < 15; ++p) lo[p] = t[1 + p] & u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+  for (int p = 0; p < 15; ++p) lo[p] = mine[1 + p];
   wave_lds_sync();
+}
+template <int PLANES>
+__device__ inline void keep_block_words(u32 w, u32 (&lo)[16]) {
+  const u32 keep = (1u << w) - 1u;                     // bit p: the block has plane p
+  lo[15] = w ? lo[15] : 0u;
+#pragma unroll
+  for (int p = 0; p < PLANES; ++p) {
+    // (the AND spelled out: seen as one, it is compiled into a test and a selection per plane)
+    const u32 m = u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
+    lo[p] = __builtin_amdgcn_bitop3_b32(lo[p], m, m, 0xC0);
+  }
+}
+__device__ inline void pick_block_words(const WavePayload& wp, u64 seg_off, const u32* wl, u32 (&lo)[16]) {
+  pick_raw_words(wp, seg_off, wl, lo);
+  keep_block_words<15>(own_width(wp), lo);
 }
 
 __device__ inline u32 wave_block_words(const u32* payload, u64 payload_words, u32 w, u64 seg_off, u32* wl, int lane,

@@ -96,8 +96,7 @@ struct ChainState {
   u32 cur;          // the received code of the value before
   i32 prev;         // the new code of the value before
   i32 top, bottom;  // largest and smallest new delta so far (d0 = 0 is one of them)
-  u32 upos, uneg;   // largest bit pattern of a sum as a signed and as an unsigned number: the
-                    // largest positive and the largest negative magnitude, NaN and infinity on top
+  float most;       // largest magnitude of a sum, or NaN if one of them is NaN
   i32 outlier;      // the new code of value 0
 };
 
@@ -107,6 +106,12 @@ struct ChainState {
 // 8 + (j & 7) those of its second half, so the walk below is done with eight words when it has
 // done half the block, and has filled eight words of new deltas.
 __device__ inline u32 swap_middle_bytes(u32 v) { return __builtin_amdgcn_perm(v, v, 0x03010200u); }
+
+// The largest magnitude of three (the first is not negative), NaN if there is one.  (One instruction, which takes magnitudes
+// by itself; integer maxima of the bit patterns need a signed and an unsigned one.)
+__device__ inline float most_of(float so_far, float b, float c) {
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(so_far, __builtin_fabsf(b)), __builtin_fabsf(c));
+}
 
 // Values 16 HALF .. 16 HALF + 15 of the lane's block.  BITS: width of the fields the received
 // deltas are packed in (16: word (j & 7) + 8 HALF holds values j and j + 8, see above; 8: word
@@ -119,7 +124,7 @@ __device__ inline void walk_half(const u32 (&fields)[NF], const u32* row, const 
     const float4 l4 = *reinterpret_cast<const float4*>(row + 4 * t);
     const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
     i32 nd[4];
-    u32 yb[4];
+    float ys[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int j = 16 * HALF + 4 * t + u;
@@ -127,7 +132,7 @@ __device__ inline void walk_half(const u32 (&fields)[NF], const u32* row, const 
       const int at = BITS == 16 ? 16 * ((j >> 3) & 1) : 8 * (j >> 3);
       cs.cur += u32(__builtin_amdgcn_sbfe(i32(f), u32(at), u32(BITS)));
       const float y = combine<OP>(float(__dmul_rn(double(i32(cs.cur)), qa.step)), lv[u]);
-      yb[u] = __float_as_uint(y);
+      ys[u] = y;
       const i32 q = quantize_fast(y, qa);
       if (j == 0) cs.outlier = q;
       nd[u] = j ? q - cs.prev : 0;
@@ -137,8 +142,9 @@ __device__ inline void walk_half(const u32 (&fields)[NF], const u32* row, const 
     }
     cs.top = max(cs.top, max(max(nd[0], nd[1]), max(nd[2], nd[3])));
     cs.bottom = min(cs.bottom, min(min(nd[0], nd[1]), min(nd[2], nd[3])));
-    cs.upos = u32(max(i32(cs.upos), max(max(i32(yb[0]), i32(yb[1])), max(i32(yb[2]), i32(yb[3])))));
-    cs.uneg = max(cs.uneg, max(max(yb[0], yb[1]), max(yb[2], yb[3])));
+    cs.most = most_of(most_of(cs.most, ys[0], ys[1]), ys[2], ys[3]);
+    // (four values at a time: left to itself the compiler mixes in the next ones and needs 93 registers instead of 82)
+    asm volatile("" : "+v"(cs.most));
   }
 }
 
@@ -329,8 +335,13 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
 // not an argument: a workgroup that knows its tile from its id asks for everything at once, and the waits
 // for those loads can only be counted exactly when no other path joins them.  SELF: a plain stream whose width table the
 // kernel sums itself, one for the same reason (as an argument it cost 2^25 values with an index ahead 52.3 us, now 50.9).
-template <bool IX, bool SELF, int OP, bool TICKETS>
-__global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
+// GROUPS: workgroups per compute unit the registers are to allow.  Five for calls that five per compute unit can take at
+// once, and for Max and Min.  A Sum of more runs with six, in 80 registers and (of indexed streams) one more in scratch: 2^26 values
+// 90.4 us with five and integer maxima in the walk, now 87.3.  In a call of few tiles there is nothing to gain from that, and the
+// scratch has its price: 262 177 values 6.7 us with five, 7.0 with six.  Max and Min would keep two to three registers in scratch.
+constexpr u32 kStepAtOnce = 5 * 256;      // workgroups
+template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5>
+__global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage + kCopyOver];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
@@ -486,7 +497,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     measure = slow = __ballot(active);
   } else {
     u32 lo[16];
-    pick_block_words(wp, seg_off, wl, lo);
+    pick_raw_words(wp, seg_off, wl, lo);
     if (have < kWaveValues) {                // uniform: the end of the buffer
       pad_local(a.local, v0, h.n, have, lane, x);
       const u32 first = u32(kBlockValues) * u32(lane);
@@ -520,9 +531,10 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
       later[i].w = first_kind ? uw : x[i].w;
     }
     wave_lds_sync();
-    ChainState cs{outlier_in, 0, 0, 0, 0u, 0u, 0};
+    ChainState cs{outlier_in, 0, 0, 0, 0.0f, 0};
     const u32* const row = wl + lane * kStepRow;
     if (wp.wmax <= 7) {
+      keep_block_words<7>(own_width(wp), lo);
       u32 r[8];
 #pragma unroll
       for (int p = 0; p < 7; ++p) r[p] = lo[p];
@@ -535,8 +547,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     } else {
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = swap_middle_bytes(lo[p]);
-      magnitude_planes_to_twos<16>(lo);
-      transpose16x16_pairs(lo);
+      deltas_from_raw_planes16(lo, own_width(wp));
       walk_half<OP, 16, 0>(lo, row, qa, cs, nf);
       stage_second_half(wl, later);
       walk_half<OP, 16, 1>(lo, row, qa, cs, nf);
@@ -545,9 +556,7 @@ __global__ __launch_bounds__(kTileThreads, 5) void step_kernel(StepArgs a) {
     const u32 any = max(u32(cs.top), u32(-cs.bottom));
     pl.w = (active && any) ? 32u - u32(__builtin_clz(any)) : 0u;
     outlier = cs.outlier;
-    // the largest magnitude among the sums: a NaN or an infinity has the largest bit pattern of all
-    const u32 amax = max(i32(cs.upos) < 0 ? 0u : cs.upos, cs.uneg & 0x7fffffffu);
-    measure = __ballot(active && (needs_checks(__uint_as_float(amax), qa))) | wide_in;
+    measure = __ballot(active && needs_checks(cs.most, qa)) | wide_in;
     slow = measure | __ballot(pl.w > 15);          // (a wide result alone: its width is known)
   }
   if (measure) {

@@ -47,6 +47,19 @@ def test_streams_of_few_tiles(zcref, tiles):
         assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
 
 
+# calls that five workgroups per compute unit can take at once, and the Sum of the first that they cannot
+@pytest.mark.parametrize("tiles", [1280, 1281])
+def test_ring_rounds_of_as_many_tiles_as_run_at_once(zcref, tiles):
+    u = gpuutil
+    n = tiles * TILE - 4097
+    xs = [_values(n, 80 + i) for i in range(2)]
+    ref = zcref.compress(xs[0], 1e-3)[1]
+    for op in (0, 1):
+        st_ref, step_ref = zcref.reduce_step(ref, xs[1], op=op)[:2]
+        st, step, _ = u.gpu_reduce_step(ref, xs[1], op=op)
+        assert st == st_ref and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
+
+
 # the tables of plain streams are summed by every workgroup of the main kernel up to 512 tiles of all streams together, by
 # a kernel ahead of it from there on; parts of four waves (one stream), two and one, and a table of more than one round
 @pytest.mark.parametrize("tiles,k", [(4, 1), (5, 1), (17, 1), (512, 1), (513, 1), (3, 2), (256, 2), (257, 2), (5, 3), (170, 3), (171, 3),
