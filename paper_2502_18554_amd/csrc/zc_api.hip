@@ -240,12 +240,7 @@ void* scratch_of_current_device() {
 namespace {
 template <int OP>
 void (*pick_step_kernel(bool ix, bool self, bool tickets, u64 tiles))(StepArgs) {
-  if constexpr (OP == ZC_OP_SUM) {
-    if (tiles > kStepAtOnce) {               // (more than a call of plain streams sums itself)
-      if (ix) return tickets ? step_kernel<true, false, OP, true, 6> : step_kernel<true, false, OP, false, 6>;
-      if (!self) return tickets ? step_kernel<false, false, OP, true, 6> : step_kernel<false, false, OP, false, 6>;
-    }
-  }
+  if (ix && tiles >= kStepMany) return tickets ? step_kernel<true, false, OP, true, 6> : step_kernel<true, false, OP, false, 6>;
   if (ix) return tickets ? step_kernel<true, false, OP, true> : step_kernel<true, false, OP, false>;
   if (self) return tickets ? step_kernel<false, true, OP, true> : step_kernel<false, true, OP, false>;
   return tickets ? step_kernel<false, false, OP, true> : step_kernel<false, false, OP, false>;

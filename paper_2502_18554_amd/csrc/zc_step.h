@@ -335,11 +335,13 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
 // not an argument: a workgroup that knows its tile from its id asks for everything at once, and the waits
 // for those loads can only be counted exactly when no other path joins them.  SELF: a plain stream whose width table the
 // kernel sums itself, one for the same reason (as an argument it cost 2^25 values with an index ahead 52.3 us, now 50.9).
-// GROUPS: workgroups per compute unit the registers are to allow.  Five for calls that five per compute unit can take at
-// once, and for Max and Min.  A Sum of more runs with six, in 80 registers and (of indexed streams) one more in scratch: 2^26 values
-// 90.4 us with five and integer maxima in the walk, now 87.3.  In a call of few tiles there is nothing to gain from that, and the
-// scratch has its price: 262 177 values 6.7 us with five, 7.0 with six.  Max and Min would keep two to three registers in scratch.
-constexpr u32 kStepAtOnce = 5 * 256;      // workgroups
+// GROUPS: workgroups per compute unit the registers are to allow.  Calls of indexed streams of fewer than eight
+// tiles per compute unit are made for five (82 registers), others for six, in 80 registers and two to three more in scratch (plain streams
+// need 80 at most either way): 2^26 values of a power-law field 90.4 us with five and integer maxima in the walk, now 87.3; of
+// sinusoids 50.9, now 49.9 (Max 51.7, 50.6); 2048 tiles 16.92, 16.83.  In calls of fewer tiles there is nothing to gain from the
+// sixth, and the scratch has its price: 33 tiles 6.7 us with five, 7.0 with six; 1343 tiles 12.76 and
+// 12.98; 1587 tiles 14.02 and 14.22.
+constexpr u32 kStepMany = 8 * 256;        // tiles
 template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5>
 __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage + kCopyOver];

@@ -47,9 +47,9 @@ def test_streams_of_few_tiles(zcref, tiles):
         assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
 
 
-# calls that five workgroups per compute unit can take at once, and the Sum of the first that they cannot
-@pytest.mark.parametrize("tiles", [1280, 1281])
-def test_ring_rounds_of_as_many_tiles_as_run_at_once(zcref, tiles):
+# both sides of the size from which ring rounds run with more workgroups per compute unit
+@pytest.mark.parametrize("tiles", [2047, 2048])
+def test_ring_rounds_of_many_tiles(zcref, tiles):
     u = gpuutil
     n = tiles * TILE - 4097
     xs = [_values(n, 80 + i) for i in range(2)]
