@@ -167,7 +167,10 @@ __global__ __launch_bounds__(kTileThreads) void block_offsets_kernel(OffsetsArgs
   }
   if (!v.err && h.nb > a.off_cap) v.err = status_bit(ZC_ERR_CAPACITY);
   if (v.err) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, v.err);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      a.ctl->result = 0;
+      raise_status(a.ctl, tag, v.err);
+    }
     return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl->result = h.nb;

@@ -280,7 +280,10 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
       (h.total != tables_end(0, true) || *reinterpret_cast<const u32*>(a.in.base + kHeaderBytes) != 0))
     raise_status(a.ctl, tag, status_bit(ZC_ERR_FORMAT));
   if (first_value > h.n) {                            // the part lies beyond the stream
-    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_ARG));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      a.ctl->result = 0;
+      raise_status(a.ctl, tag, status_bit(ZC_ERR_ARG));
+    }
     return;
   }
   const u64 end_value = count < h.n - first_value ? first_value + count : h.n;     // one past the last value wanted

@@ -730,7 +730,10 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
     return false;
   }
   if (a.n_part && a.n_part != c.h.n) {      // the parts were laid out for another n
-    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, c.tag, status_bit(ZC_ERR_MISMATCH));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (!a.adopt) a.ctl->result = 0;
+      raise_status(a.ctl, c.tag, status_bit(ZC_ERR_MISMATCH));
+    }
     return false;
   }
   ntiles = u32(num_tiles(c.h.nb));

@@ -417,7 +417,10 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
     return;
   }
   if (a.n_local != h.n) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) raise_status(a.ctl, tag, status_bit(ZC_ERR_MISMATCH));
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (!a.adopt) a.ctl->result = 0;
+      raise_status(a.ctl, tag, status_bit(ZC_ERR_MISMATCH));
+    }
     return;
   }
   const u64 tend = tables_end(h.nb, IX);

@@ -6,7 +6,7 @@ import torch
 
 import gpuutil
 from paper_2502_18554_amd import synth
-from paper_2502_18554_amd.binding import ZC_ERR_FORMAT, ZC_OK
+from paper_2502_18554_amd.binding import ZC_ERR_ARG, ZC_ERR_CAPACITY, ZC_ERR_FORMAT, ZC_ERR_MISMATCH, ZC_OK
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("stream_variant")]
 
@@ -122,3 +122,25 @@ def test_parts_that_look_back_in_different_ways(zcref, stream_variant, tiles):
                 assert st == ZC_OK and got.tobytes() == want.tobytes(), u.first_diff(got, want)
     finally:
         u.set_coherent(False)
+
+
+@pytest.mark.parametrize("tiles", [3, 600])          # plain streams: one launch, and two
+def test_a_refused_call_reports_a_size_of_nothing(zcref, stream_variant, tiles):
+    """Whatever the workspace held before."""
+    u, zc = gpuutil, gpuutil.zc
+    n = tiles * TILE - 2049
+    x = _values(n, 90)
+    ref = zcref.compress(x, 1e-3)[1]
+    d_ref, d_x = u.to_dev(ref), u.to_dev(x)
+    d_out = torch.empty(zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
+    d_y = torch.empty(n, device=u.DEV)
+    offsets = torch.empty(8, dtype=torch.int32, device=u.DEV)
+    ws = u.workspace(n)
+    for call, want in ((lambda: zc.zc_reduce_step(d_ref, ref.size, d_x, n - 1, d_out, ws), ZC_ERR_MISMATCH),
+                       (lambda: zc.zc_decompress_range(d_ref, ref.size, tiles * TILE, 5, d_y, ws), ZC_ERR_ARG),
+                       (lambda: (zc.zc_debug_block_offsets(d_ref, ref.size, offsets, ws), u.zc.zc_finish(ws)[1]), ZC_ERR_CAPACITY)):
+        ws.fill_(0x5A)
+        assert call() == (want, 0)
+    if stream_variant == "indexed":                  # (parts are of indexed streams)
+        ws.fill_(0x5A)
+        assert zc.zc_reduce_compressed_part([d_ref], [ref.size], n - 1, 0, TILE, d_out, ws) == (ZC_ERR_MISMATCH, 0)
