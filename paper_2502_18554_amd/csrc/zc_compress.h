@@ -132,9 +132,10 @@ __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u3
 
 // Quantise the wave's values where they landed and transpose the codes through LDS so that one
 // lane owns one block: q[j] = code j of the lane's block.  have: see share_values.
-// (quantize4 for fresh values in both halves: 27 scalar registers pushed out with tiles by ticket, 18 without, but then with
-// 20 bytes of scratch set aside, which zc_compress_noalloc is not to need; in the second half: 52 and 48; in none: 95 and
-// 92.  2^26 values by ticket 80.7 us with none, 80.0, 78.1 with both; without tickets 66.8, 65.6, 65.2.)
+// (quantize4 for fresh values in both halves with tiles by ticket, in the second half without: 38 and 52 scalar registers
+// pushed out.  In both halves without tickets it needs fewer, but then has 20 bytes of scratch set aside, which
+// zc_compress_noalloc is not to need; in none it needs twice as many.  2^26 values by ticket 80.7 us with none, 80.0 with one,
+// 78.1 with both; without tickets 66.8, 65.6, 65.2.)
 template <bool TICKETS>
 __device__ __forceinline__ void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                    i32 (&q)[32], u32& err) {
@@ -247,7 +248,7 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
   q[0] = 0;
   u32 lo[16], hi[16];
   planes_from_deltas32(q, lo, hi);
-  copy_wave_out<32>(sink, [&](auto i) {
+  copy_wave_out<32, false>(sink, [&](auto i) {
     constexpr int I = decltype(i)::value;      // 0: sign, 1 + p: plane p
     if constexpr (I == 0) return hi[15];
     else if constexpr (I <= 16) return lo[I - 1];
@@ -352,10 +353,14 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
       stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, pl, wl);
     });
     if (lane == 0) write_index_entry(sink, tile * u32(kPackWaves) + u32(wave), tb.words + pl.wave_off);
-    if (narrow) copy_staged_wave<16>(sink, pl, tb.words, wl, lane);
+    if (narrow) copy_staged_wave<16, false>(sink, pl, tb.words, wl, lane);
     else store_wide_wave<TICKETS>(a, sink, pl, tb.words, wblock0, have, lane, wl);
     finish_stream(sink, pl, tile, ntiles, tb);
-    store_tables<0>(sink, u32(wblock0) + u32(fresh_lane()), pl.w, bf.outlier);
+    if (active && tables_fit) {                // (not store_tables: see copy_staged_words)
+      const u64 b = wblock0 + u64(lane);
+      a.out[widths_begin(a.nb, a.ix) + b] = u8(pl.w);
+      reinterpret_cast<i32*>(a.out + outliers_begin(a.nb, a.ix))[b] = bf.outlier;
+    }
   }
   if (err) raise_status(a.ctl, tag, err);
 }

@@ -97,14 +97,36 @@ __device__ inline void write_stream_header(u8* out, u64 n, u64 nb, u32 eb_bits, 
 // line boundary, so a line is written by one instruction and not by the tail of one and the head of
 // the next.  The stores bypass the caches: a stream is on its way to another device, or to a later
 // call, and keeping it in cache lines would only push the write-back into the kernels that follow.
-// A round is a read and a store (with a comparison, a selection and a 64-bit address for each, and the like in the tables'
-// stores and in the loads of the received stream, a ring round of 2^26 values took 93 us, now 89.5; Sum of 8 x 2^24 49.8, 48.7).
-// ROUNDS * 64 >= limit + 31.  The last group of rounds may read LDS behind the wave's words, up to kCopyOver words behind
-// 64 * (ROUNDS - 1) of them, which nothing comes of.
+// ROUNDS * 64 >= limit + 31.
+// BY_RANGE: a round is a read and a store, and the range of the store says which lanes have a word (with a comparison, a
+// selection and a 64-bit address for each, and the like in the tables' stores and in the loads of the received stream, a
+// ring round of 2^26 values took 93 us, now 89.5; Sum of 8 x 2^24 49.8, 48.7).  The last group of rounds may read LDS behind
+// the wave's words, up to kCopyOver words behind 64 * (ROUNDS - 1) of them, which nothing comes of.
+// Not for the compression, whose scalar registers are spoken for and whose waves often have few words: 20 000 003 values by
+// ranges 23.4 us (a smooth field at 1e-4 of its range), 25.3 (hard data) and 22.0 (sinusoids at 1e-2), by conditions
+// 23.0, 24.6 and 21.1; 1000 sinusoid values 6.1 and 5.9.
 constexpr int kCopyOver = 64;
-template <int ROUNDS>
+template <int ROUNDS, bool BY_RANGE>
 __device__ inline void copy_staged_words(const u32* wl, u32* dst, u32 limit, int lane) {
   const u32 lead = uniform(u32(reinterpret_cast<uintptr_t>(dst) >> 2) & 31u);   // words of dst's line before dst
+  if constexpr (!BY_RANGE) {
+    const u32 end = uniform(limit) + lead;
+    // four rounds at a time: their LDS reads are all under way before the first store needs its word
+#pragma unroll
+    for (int r0 = 0; r0 < ROUNDS; r0 += 4) {
+      if (64u * u32(r0) >= end) break;         // uniform
+      u32 i[4], v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        i[k] = u32(lane) + 64u * u32(r0 + k) - lead;   // wraps for the lanes ahead of dst: they sit out
+        v[k] = wl[i[k] < limit ? i[k] : 0u];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (r0 + k < ROUNDS && i[k] < limit) store_once(dst + i[k], v[k]);
+    }
+    return;
+  }
   limit = uniform(limit);
   // the first round, without the lanes ahead of dst ...
   {
@@ -145,7 +167,7 @@ __device__ inline void store_tables(const PayloadSink& s, u32 b, u32 w, i32 outl
 // them out with coalesced stores.  Word 0 is the sign word, word 1 + p is plane p; `word(i)`
 // yields word i from registers and is only ever called with compile-time constants.
 // half_total <= 32 * NW.
-template <int NW, typename WordFn>
+template <int NW, bool BY_RANGE, typename WordFn>
 __device__ inline void stage_and_copy_half(WordFn word, u32 w, bool in_half, u32 off_in_half, u32 half_total,
                                            u32* wl, u32* dst, u64 dst_room, int lane) {
   if (in_half && w) {
@@ -156,7 +178,7 @@ __device__ inline void stage_and_copy_half(WordFn word, u32 w, bool in_half, u32
   }
   wave_lds_sync();
   const u32 limit = u64(half_total) < dst_room ? half_total : u32(dst_room);
-  copy_staged_words<NW / 2 + 1>(wl, dst, limit, lane);
+  copy_staged_words<NW / 2 + 1, BY_RANGE>(wl, dst, limit, lane);
   wave_lds_sync();
 }
 
@@ -250,7 +272,7 @@ __device__ inline void finish_stream(const PayloadSink& s, const Placement& pl, 
 
 // Moves a wave's payload out once the tile's base offset is known: through LDS, one half-wave
 // of blocks at a time (the staging area `wl` of a wave holds kWaveStage words).
-template <int NW, typename WordFn>
+template <int NW, bool BY_RANGE, typename WordFn>
 __device__ inline void copy_wave_out(const PayloadSink& s, WordFn word, const Placement& pl, u64 base, u32* wl, int lane) {
   static_assert(32 * NW <= kWaveStage, "a half-wave of widest blocks must fit the staging area");
   const u64 tend = tables_end(s.nb, s.ix);
@@ -262,7 +284,7 @@ __device__ inline void copy_wave_out(const PayloadSink& s, WordFn word, const Pl
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const u64 d0 = dst0 + half_base[h];
-    stage_and_copy_half<NW>(word, pl.w, (lane >> 5) == h, pl.off_in_wave - half_base[h], half_total[h], wl,
+    stage_and_copy_half<NW, BY_RANGE>(word, pl.w, (lane >> 5) == h, pl.off_in_wave - half_base[h], half_total[h], wl,
                             payload + d0, cap_words > d0 ? cap_words - d0 : 0, lane);
   }
 }
@@ -281,7 +303,7 @@ __device__ inline void stage_wave_words(WordFn word, const Placement& pl, u32* w
 }
 
 // Then the copy-out is a plain LDS-to-memory copy of the wave's words.
-template <int NW>
+template <int NW, bool BY_RANGE>
 __device__ inline void copy_staged_wave(const PayloadSink& s, const Placement& pl, u64 base, u32* wl, int lane) {
   wave_lds_sync();
   const u64 tend = tables_end(s.nb, s.ix);
@@ -290,7 +312,7 @@ __device__ inline void copy_staged_wave(const PayloadSink& s, const Placement& p
   u32* const dst = reinterpret_cast<u32*>(s.out + tend) + d0;
   const u64 room = cap_words > d0 ? cap_words - d0 : 0;
   const u32 limit = u64(pl.wave_total) < room ? pl.wave_total : u32(room);
-  copy_staged_words<NW + 1>(wl, dst, limit, lane);
+  copy_staged_words<NW + 1, BY_RANGE>(wl, dst, limit, lane);
   wave_lds_sync();
 }
 
@@ -302,7 +324,7 @@ __device__ inline void finish_tile(const PayloadSink& s, WordFn word, const Plac
                                    u32* wl, u64 (&sh_base)[WAVES], int wave, int lane) {
   const TileBase tb = resolve_tile_base(s, pl, tile, sh_base, wave, lane);
   if (lane == 0) write_index_entry(s, tile * (blockDim.x >> 6) + u32(wave), tb.words + pl.wave_off);
-  copy_wave_out<NW>(s, word, pl, tb.words, wl, lane);
+  copy_wave_out<NW, true>(s, word, pl, tb.words, wl, lane);
   finish_stream(s, pl, tile, ntiles, tb);
 }
 

@@ -189,7 +189,7 @@ __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c
   u32* const dst = reinterpret_cast<u32*>(a.out + tend) + d0;
   const u64 room = cap_words > d0 ? cap_words - d0 : 0;
   const u32 limit = u64(pl.wave_total) < room ? pl.wave_total : u32(room);
-  copy_staged_words<NW + 1>(wl, dst, limit, lane);
+  copy_staged_words<NW + 1, true>(wl, dst, limit, lane);
   wave_lds_sync();
   store_tables<kAccessOnce>(sink, b, w, i32(outlier));     // (the whole output stream is written with the non-temporal hint, see store_once)
   finish_stream(sink, pl, tile, ntiles, tb);

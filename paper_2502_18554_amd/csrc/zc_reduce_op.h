@@ -569,14 +569,14 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   });
   if (lane == 0) write_index_entry(sink, seg, tb.words + pl.wave_off);
   if (narrow) {
-    copy_staged_wave<16>(sink, pl, tb.words, wl, lane);
+    copy_staged_wave<16, true>(sink, pl, tb.words, wl, lane);
   } else {
     i32 d[32];
 #pragma unroll
     for (int j = 0; j < 32; ++j) d[j] = i32(eb.d[j]);
     u32 plo[16], phi[16];
     planes_from_deltas32(d, plo, phi);
-    copy_wave_out<32>(sink, [&](auto i) {
+    copy_wave_out<32, true>(sink, [&](auto i) {
       constexpr int I = decltype(i)::value;
       if constexpr (I == 0) return phi[15];
       else if constexpr (I <= 16) return plo[I - 1];

@@ -616,7 +616,7 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
 
   // ---- out ----
   if (pl.wave_total <= u32(kStepStage)) {
-    copy_staged_wave<kStepStage / 64>(sink, pl, base, wl, lane);
+    copy_staged_wave<kStepStage / 64, true>(sink, pl, base, wl, lane);
   } else {
     const u64 cap_words = a.out_cap > tend ? (a.out_cap - tend) / 4 : 0;
     const u64 dst = base + pl.wave_off;
