@@ -117,7 +117,9 @@ __device__ inline float most_of(float so_far, float b, float c) {
 // deltas are packed in (16: word (j & 7) + 8 HALF holds values j and j + 8, see above; 8: word
 // j & 7 holds values j, j + 8, j + 16, j + 24).  `row`: the lane's 16 local values of this half.
 // The new deltas go into nf as 16-bit fields paired the same way.
-template <int OP, int BITS, int HALF, int NF>
+// FOURS: four values at a time.  Left to itself the compiler mixes in the next ones, which takes ten registers more and gives a
+// wave that is alone on its SIMD something to issue while a binary64 result is on its way.
+template <int OP, int BITS, int HALF, bool FOURS, int NF>
 __device__ inline void walk_half(const u32 (&fields)[NF], const u32* row, const CompressArgs& qa, ChainState& cs, u32 (&nf)[16]) {
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
@@ -143,8 +145,7 @@ __device__ inline void walk_half(const u32 (&fields)[NF], const u32* row, const 
     cs.top = max(cs.top, max(max(nd[0], nd[1]), max(nd[2], nd[3])));
     cs.bottom = min(cs.bottom, min(min(nd[0], nd[1]), min(nd[2], nd[3])));
     cs.most = most_of(most_of(cs.most, ys[0], ys[1]), ys[2], ys[3]);
-    // (four values at a time: left to itself the compiler mixes in the next ones and needs 93 registers instead of 82)
-    asm volatile("" : "+v"(cs.most));
+    if constexpr (FOURS) asm volatile("" : "+v"(cs.most));
   }
 }
 
@@ -336,11 +337,14 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
 // for those loads can only be counted exactly when no other path joins them.  SELF: a plain stream whose width table the
 // kernel sums itself, one for the same reason (as an argument it cost 2^25 values with an index ahead 52.3 us, now 50.9).
 // GROUPS: workgroups per compute unit the registers are to allow.  Calls of indexed streams of fewer than eight
-// tiles per compute unit are made for five (82 registers), others for six, in 80 registers and two to three more in scratch (plain streams
-// need 80 at most either way): 2^26 values of a power-law field 90.4 us with five and integer maxima in the walk, now 87.3; of
+// tiles per compute unit are made for five (93 registers at most), others for six, in 80 registers and two to three more in scratch (plain
+// streams that are indexed ahead need 80 for five): 2^26 values of a power-law field 90.4 us with five and integer maxima in the walk, now 87.3; of
 // sinusoids 50.9, now 49.9 (Max 51.7, 50.6); 2048 tiles 16.92, 16.83.  In calls of fewer tiles there is nothing to gain from the
 // sixth, and the scratch has its price: 33 tiles 6.7 us with five, 7.0 with six; 1343 tiles 12.76 and
 // 12.98; 1587 tiles 14.02 and 14.22.
+// FOURS (see walk_half) is for the kernel of six, for plain streams of many tiles, and with tickets, where the registers
+// would not hold the other form: a round of 1000 values 6.73 us with it, 6.59 without, 100 003 sinusoids 6.69 and 6.54, 2^22 hard values
+// 13.50 and 13.29; but 2^24 values of a plain stream 32.2 and 33.1.
 constexpr u32 kStepMany = 8 * 256;        // tiles
 template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5>
 __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) {
@@ -349,6 +353,7 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
   __shared__ PlainSurvey<1> survey;
+  constexpr bool FOURS = TICKETS || GROUPS > 5 || !(IX || SELF);
 
   const int lane = lane_id();
   const int wave = wave_id();
@@ -546,16 +551,16 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
       r[7] = lo[15];
       magnitude_planes_to_twos<8>(r);
       transpose8x8_quads(r);
-      walk_half<OP, 8, 0>(r, row, qa, cs, nf);
+      walk_half<OP, 8, 0, FOURS>(r, row, qa, cs, nf);
       stage_second_half(wl, later);
-      walk_half<OP, 8, 1>(r, row, qa, cs, nf);
+      walk_half<OP, 8, 1, FOURS>(r, row, qa, cs, nf);
     } else {
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = swap_middle_bytes(lo[p]);
       deltas_from_raw_planes16(lo, own_width(wp));
-      walk_half<OP, 16, 0>(lo, row, qa, cs, nf);
+      walk_half<OP, 16, 0, FOURS>(lo, row, qa, cs, nf);
       stage_second_half(wl, later);
-      walk_half<OP, 16, 1>(lo, row, qa, cs, nf);
+      walk_half<OP, 16, 1, FOURS>(lo, row, qa, cs, nf);
     }
     wave_lds_sync();
     const u32 any = max(u32(cs.top), u32(-cs.bottom));
