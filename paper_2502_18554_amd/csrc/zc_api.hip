@@ -162,8 +162,8 @@ __global__ __launch_bounds__(kTileThreads) void block_offsets_kernel(OffsetsArgs
   const u64 tag = call_tag(a.ctl, launch_tag(a.nonce, a.ctl), false);
   u32 seg_off = 0;
   if (!IX) {
-    const SurveyLoads ask = ask_plain_streams<1>(&a.in, 1, a.index, a.self != 0, u32(seg), wave);
-    seg_off = lane_value(judge_plain_streams(&a.in, 1, a.index, a.self != 0, blockIdx.x, wave, ask, v, survey), 0);
+    const SurveyLoads ask = ask_plain_streams<1, false>(&a.in, 1, a.index, a.self != 0, u32(seg), wave);
+    seg_off = lane_value(judge_plain_streams<1, false>(&a.in, 1, a.index, a.self != 0, blockIdx.x, wave, ask, v, survey), 0);
   }
   if (!v.err && h.nb > a.off_cap) v.err = status_bit(ZC_ERR_CAPACITY);
   if (v.err) {
@@ -447,7 +447,8 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   const bool self = !ix && index_plain_streams(da.in, k, tiles_in, tiles, l, stream);
   da.ctl = l.ctl;
   da.nonce = call_nonce();
-  void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false> : self ? decompress_many_kernel<false, true> : decompress_many_kernel<false, false>;
+  void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false, false> : self ? decompress_many_kernel<false, true, false>
+                                         : k > kManyByWave ? decompress_many_kernel<false, false, true> : decompress_many_kernel<false, false, false>;
   launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(tiles), u32(k)), dim3(kTileThreads), stream, da);
   if (!launch_ok()) return ZC_ERR_HIP;
   if (!n_out) return ZC_OK;

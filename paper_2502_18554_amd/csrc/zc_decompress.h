@@ -215,14 +215,14 @@ __device__ inline void deltas_from_block_words(u32 wmax, u32 (&lo)[16], u32 (&hi
 // The header is judged here, by every workgroup alike (see judge_headers, judge_plain_streams, index_ends_ok).
 // `IX`: the stream is indexed; its width bytes sit behind the index, whose size only the header tells, so they
 // are asked for together with the outlier and the payload.  SELF: a plain stream whose width table the kernel sums itself
-// (a template parameter: as an argument it cost the streams that have an index 2 %).  K: room for that many streams in the survey of plain ones;
-// `streams`, `k`: all streams of the call.
+// (a template parameter: as an argument it cost the streams that have an index 2 %).  K: room for that many streams in the survey of plain ones (ROWS: see
+// kManyByWave); `streams`, `k`: all streams of the call.
 // `average`: the values are divided by the stream's nsum (the Average aggregation of Section
 // 3.2 on a stream of sums): x' = float((double(q) * s) * r), r = 1.0 / nsum.
 // first_value, count: only the values [first_value, first_value + count) of the stream, cut off
 // at its end, are produced, into out_values[0 ...] (a chunk handled on its own, Section 3.5.2);
 // first_value is a multiple of the 2048 values of a segment.  The whole stream: 0 and ~0.
-template <bool IX, bool SELF, int K>
+template <bool IX, bool SELF, int K, bool ROWS = false>
 __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k, int s, float* out_values, u64 out_cap_elems,
                                        const StreamIndex& index, Control* ctl, u64 nonce, u32* lds, PlainSurvey<K>* survey,
                                        bool average = false, u64 first_value = 0, u64 count = ~u64(0)) {
@@ -241,7 +241,7 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
   const u32 zero = opaque_zero();
   const bool first_group = blockIdx.x == 0 && blockIdx.y == 0;
   SurveyLoads ask{};
-  if (!IX) ask = ask_plain_streams<K>(streams, k, a.index, SELF, seg, wave);
+  if (!IX) ask = ask_plain_streams<K, ROWS>(streams, k, a.index, SELF, seg, wave);
   const HeaderWords hw = load_header_words(a.in.base, zero);
   u32 seg_begin = 0, seg_end = 0, w = 0;
   if (IX) {
@@ -265,7 +265,7 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
   }
   const u64 tag = call_tag(a.ctl, ltag, false);
   if (!IX) {
-    const u32 off = judge_plain_streams(streams, k, a.index, SELF, tile, wave, ask, v, *survey);
+    const u32 off = judge_plain_streams<K, ROWS>(streams, k, a.index, SELF, tile, wave, ask, v, *survey);
     seg_begin = lane_value(off, s);
   }
   if (v.err) {
@@ -385,12 +385,12 @@ struct DecompressManyArgs {
   u64 nonce;
 };
 
-template <bool IX, bool SELF>
+template <bool IX, bool SELF, bool ROWS>
 __global__ __launch_bounds__(kTileThreads, 5) void decompress_many_kernel(DecompressManyArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
   __shared__ PlainSurvey<ZC_MAX_K> survey;
   const int s = blockIdx.y;
-  decompress_tile<IX, SELF, ZC_MAX_K>(a.in, a.k, s, a.out[s], a.out_cap_elems[s], a.index, a.ctl, a.nonce, lds, &survey);
+  decompress_tile<IX, SELF, ZC_MAX_K, ROWS>(a.in, a.k, s, a.out[s], a.out_cap_elems[s], a.index, a.ctl, a.nonce, lds, &survey);
 }
 
 }  // namespace zc

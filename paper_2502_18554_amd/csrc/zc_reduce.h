@@ -688,7 +688,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
   const int wave = wave_id();
   tile = a.first_tile + blockIdx.x;          // tiles in the order in which workgroups start
   SurveyLoads ask{};
-  if (!IX) ask = ask_plain_streams<ZC_MAX_K>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
+  if (!IX) ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
   if (early) {
     const u32 seg = tile * kTileWaves + u32(wave);      // < 2^22: the host launches at most 2^18 tiles
     const u32 b = seg * kWaveBlocks + u32(fresh_lane());
@@ -714,7 +714,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
   // (a later part of a reduce done in parts belongs to the call its first part opened)
   c.tag = call_tag(a.ctl, c.ltag, a.adopt != 0);
   c.places = 0;
-  if (!IX) c.places = judge_plain_streams(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
+  if (!IX) c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
   c.h = v.h0;
   c.nb = u32(c.h.nb);
   c.widths = u32(widths_begin(c.h.nb, IX));
@@ -754,8 +754,8 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
     __syncthreads();
     tile = uniform(*sh_tile);
     if (!IX && tile < end_tile) {            // (the verdict stands: once more, for the place of this tile)
-      ask = ask_plain_streams<ZC_MAX_K>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
-      c.places = judge_plain_streams(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
+      ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
+      c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
     }
   }
   return tile < end_tile;

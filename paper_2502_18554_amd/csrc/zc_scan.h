@@ -206,8 +206,8 @@ __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
 struct StreamsVerdict {
   ParsedHeader h0;      // header of stream 0 (uniform)
   u32 err;              // status bits: FORMAT, MISMATCH (uniform)
-  u64 nsum;             // sum of the nsum fields of the valid streams
-  u64 sum_n;            // sum of their n fields
+  u64 nsum;             // sum of the nsum fields of the valid streams (of a reduce, in its first workgroup only)
+  u64 sum_n;            // sum of their n fields (the same)
   u64 wide;             // bit s: stream s may hold blocks wider than 15 bits (uniform; plain streams: see judge_plain_streams)
   ParsedHeader mine;    // lane s: header of stream s
 };
@@ -241,10 +241,13 @@ __device__ inline StreamsVerdict judge_headers(const StreamRef* streams, int k, 
   if (check_match && v.h0.ok && __any(mine && h.ok && (h.n != v.h0.n || h.eb_bits != v.h0.eb_bits)))
     v.err |= status_bit(ZC_ERR_MISMATCH);
   v.wide = __ballot(mine && h.ok && h.wide);
-  const u32 ns = mine && h.ok ? h.nsum : 0u;
-  v.nsum = u64(wave_sum_u32(ns & 0xffffu)) + (u64(wave_sum_u32(ns >> 16)) << 16);
-  const u64 nn = mine && h.ok ? h.n : 0;              // <= 2^31
-  v.sum_n = u64(wave_sum_u32(u32(nn) & 0xffffu)) + (u64(wave_sum_u32(u32(nn >> 16))) << 16);
+  v.nsum = v.sum_n = 0;
+  if (!check_match || blockIdx.x == 0) {
+    const u32 ns = mine && h.ok ? h.nsum : 0u;
+    v.nsum = u64(wave_sum_u32(ns & 0xffffu)) + (u64(wave_sum_u32(ns >> 16)) << 16);
+    const u64 nn = mine && h.ok ? h.n : 0;            // <= 2^31
+    v.sum_n = u64(wave_sum_u32(u32(nn) & 0xffffu)) + (u64(wave_sum_u32(u32(nn >> 16))) << 16);
+  }
   return v;
 }
 
@@ -307,6 +310,18 @@ struct PlainSurvey {
 //   8 buffers    8 x 33 tiles 12.3 11.0 | 8 x 128: 15.4 27;   Sum of 8   8 x 1 21.6 17.1 | 8 x 33 20.4 18.6 | 8 x 128 21.2 26.2
 constexpr u64 kSelfTiles = 512;
 
+// How the lists of spans of a call of several streams are added up: by whole waves, one stream after the other, or in rows (ROWS)
+// of 16 lanes, a stream each, four a wave at once.  The reduces have rows throughout, and with four streams or fewer every wave
+// adds all of them up for itself, without a barrier; the decompression of many from 17 streams on, with fewer it runs into
+// itself where every tile does nothing but read and write.  us per call, by waves and in rows:
+//   Sum of 2 x 2 000 003 13.6 13.2, 2 x 2^26 81.5 80.2 | 5 x 2^26 106.6 104.3 | 16 x 2^24 62.9 59.5 | 64 x 2^20 70.7 65.8
+//   17 buffers of 2^20 21.8 21.4 | 32 x 2^20 37.8 30.8 | 64 x 2^20 89.2 57.7;   12 x 2^24 141 152
+// (A kernel of one workgroup that added them up for all before the main kernel started took 78.2 for the Sum of 2 x 2^26, but
+// 104.2 for that of 5, 19.2 for 2 x 2 000 003 and 74.8 for the 64 buffers.)
+constexpr int kManyByWave = 16;
+// The first stream of the lane's row.
+__device__ inline u32 row_stream(int k, int wave) { return (k <= 4 ? 0u : 4u * u32(wave)) + (u32(lane_id()) >> 4); }
+
 // Waves that share a stream's table.
 __device__ inline u32 survey_parts(int k, bool self) { return !self ? 1u : k == 1 ? 4u : k == 2 ? 2u : 1u; }
 
@@ -328,11 +343,11 @@ __device__ inline SurveyLoads load_widths(const StreamRef& in, u32 b0, u32 strid
 }
 
 // Asked for before the headers are known.  self: the wave's first part of a table.  Else: [0] the first spans of stream
-// `wave` (of the only one: every wave), [1] in lane s where the wave's segment lies in its span of stream s (of both the
-// first word only; the workspace ends 64 bytes behind the last table, see workspace_bytes).  Two loads either way and
+// `wave` (of the only one: every wave; in rows: of the rows' streams, four a lane), [1] in lane s where the wave's segment lies in its span of stream s (of
+// both the first word only, but in rows; the workspace ends 64 bytes behind the last table, see workspace_bytes).  Two loads either way and
 // none behind a branch, so that a kernel that has asked for more behind them can wait for these alone; what must not be
 // read is replaced by the first stream's header.
-template <int K>
+template <int K, bool ROWS>
 __device__ __forceinline__ SurveyLoads ask_plain_streams(const StreamRef* streams, int k, const StreamIndex& index, bool self, u32 seg,
                                                          int wave) {
   const u32 parts = survey_parts(k, self);
@@ -347,8 +362,9 @@ __device__ __forceinline__ SurveyLoads ask_plain_streams(const StreamRef* stream
       at[i] = t + 16 <= streams[s].bytes ? streams[s].base + t : safe;
     }
   } else {
-    const bool list = (k == 1 || wave < k) && lane < index.spans_cap, place = int(lane) < k && seg < 4 * index.tiles_cap;
-    at[0] = list ? reinterpret_cast<const u8*>(index.spans + u64(s) * index.spans_cap + lane) : safe;
+    const u32 of = ROWS ? row_stream(k, wave) : u32(s), i = ROWS ? 4u * (lane & 15u) : lane;
+    const bool list = (ROWS ? int(of) < k : k == 1 || wave < k) && i < index.spans_cap, place = int(lane) < k && seg < 4 * index.tiles_cap;
+    at[0] = list ? reinterpret_cast<const u8*>(index.spans + u64(of) * index.spans_cap + i) : safe;
     at[1] = place ? reinterpret_cast<const u8*>(index.seg_off + (K == 1 ? 0 : u64(lane) * 4 * index.tiles_cap) + seg) : safe;
   }
   SurveyLoads l;
@@ -380,9 +396,88 @@ __device__ inline void sum_spans(const StreamIndex& index, u32 s, u32 nb, u32 ti
   }
 }
 
+// Sum over the 16 lanes of a row, in all of them.
+__device__ inline u32 row_sum(u32 v) {
+  v += dpp_mov<kDppQuadSwap1>(v);
+  v += dpp_mov<kDppQuadSwap2>(v);
+  v += dpp_mov<kDppRowHalfMirror>(v);
+  v += dpp_mov<kDppRowMirror>(v);
+  return v;
+}
+
+// The spans of the stream `s` of the lane's row (nspans of them, 64 at a time, four a lane): payload words of those before the
+// tile's own, of all, and OR of their flags, in every lane of the row.  first: entries 4 at ... 4 at + 3 (at: the lane's
+// place in its row).
+struct RowOfSpans {
+  u32 before, total, seen;
+};
+__device__ inline uint4 load_spans(const StreamIndex& index, u32 s, u32 nspans, u32 i) {
+  const u32x4_a4 v = *reinterpret_cast<const u32x4_a4*>(index.spans + (i < nspans ? u64(s) * index.spans_cap + i : 0));
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ inline RowOfSpans sum_row_of_spans(const StreamIndex& index, u32 s, u32 nspans, u32 tile, const uint4& first) {
+  const u32 lane = u32(lane_id());
+  const u32 span = tile / (kSpanSegs / kTileWaves);
+  uint4 e = first;
+  u32 before = 0, total = 0, seen = 0;
+  u32 i = 4u * (lane & 15u);
+#pragma nounroll
+  for (;;) {
+    const u32 x[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+    for (u32 j = 0; j < 4; ++j) {
+      const u32 entry = i + j < nspans ? x[j] : 0u;
+      seen |= entry;
+      total += entry & kSpanSize;
+      before += i + j < span ? entry & kSpanSize : 0u;
+    }
+    i += 64;
+    if (!__any(i < nspans)) break;
+    e = load_spans(index, s, nspans, i);
+  }
+  const u64 bad = __ballot((seen & kSpanBadWidth) != 0), wide = __ballot((seen & kSpanWide) != 0);
+  const u32 row = lane & 48u;
+  return {row_sum(before), row_sum(total), (u32(bad >> row) & 0xffffu ? kSpanBadWidth : 0u) | (u32(wide >> row) & 0xffffu ? kSpanWide : 0u)};
+}
+
+// Lane r holds what is in row r (r < 4), and the other way round.
+__device__ inline u32 rows_to_lanes(u32 v) {
+  const u32 a = lane_value(v, 0), b = lane_value(v, 16), c = lane_value(v, 32), d = lane_value(v, 48);
+  const int lane = lane_id();
+  return lane == 0 ? a : lane == 1 ? b : lane == 2 ? c : d;
+}
+__device__ inline u32 lanes_to_rows(u32 v) {
+  const u32 a = lane_value(v, 0), b = lane_value(v, 1), c = lane_value(v, 2), d = lane_value(v, 3);
+  const int row = lane_id() >> 4;
+  return row == 0 ? a : row == 1 ? b : row == 2 ? c : d;
+}
+
+// The lists of spans of a call in rows, for `sh`: four streams a wave and round.  blocks: lane s: of stream s (none from stream k on).
+template <int K>
+__device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 blocks, u32 tile, int wave, const SurveyLoads& ask, PlainSurvey<K>& sh) {
+  const u32 lane = u32(lane_id());
+  uint4 next = ask.v[0];
+  u32 s = row_stream(k, wave);
+  u32 nspans = (u32(__builtin_amdgcn_ds_bpermute(int(4u * s), int(blocks))) + kSpanBlocks - 1) / kSpanBlocks;
+#pragma nounroll
+  for (u32 s0 = 4u * u32(wave); s0 < u32(k); s0 += 4u * kTileWaves) {
+    const uint4 first = next;
+    const u32 here = s, spans_here = nspans;
+    s = (s + 4u * kTileWaves) & 63u;           // (asked for ahead of time; beyond the last stream nothing comes of it)
+    nspans = (u32(__builtin_amdgcn_ds_bpermute(int(4u * s), int(blocks))) + kSpanBlocks - 1) / kSpanBlocks;
+    next = load_spans(index, s, nspans, 4u * (lane & 15u));
+    const RowOfSpans r = sum_row_of_spans(index, here, spans_here, tile, first);
+    if ((lane & 15u) == 0 && here < u32(k)) {
+      sh.before[here] = r.before;
+      sh.total[here] = r.total;
+      sh.seen[here] = r.seen;
+    }
+  }
+}
+
 // Called by all waves of a workgroup of kTileWaves waves; at most one barrier.  `v`: the verdict on the headers, completed here (err,
 // wide).  Returns, in lane s, the payload word offset of the wave's segment, kTileWaves * tile + wave, in stream s.
-template <int K>
+template <int K, bool ROWS>
 __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int k, const StreamIndex& index, bool self, u32 tile, int wave,
                                           const SurveyLoads& ask, StreamsVerdict& v, PlainSurvey<K>& sh) {
   const int lane = lane_id();
@@ -396,10 +491,19 @@ __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int
     off = wave_sum_u32(off) + ask.v[1].x;
     total = wave_sum_u32(total);
     seen = (__any((seen & kSpanBadWidth) != 0) ? kSpanBadWidth : 0u) | (__any((seen & kSpanWide) != 0) ? kSpanWide : 0u);
+  } else if (ROWS && !self && k <= 4) {
+    // and so with four streams, a row each
+    const u32 nspans = (lanes_to_rows(fits ? u32(v.mine.nb) : 0u) + kSpanBlocks - 1) / kSpanBlocks;
+    const RowOfSpans r = sum_row_of_spans(index, row_stream(k, wave), nspans, tile, ask.v[0]);
+    off = rows_to_lanes(r.before) + ask.v[1].x;
+    total = rows_to_lanes(r.total);
+    seen = rows_to_lanes(r.seen);
   } else {
     SurveyLoads loads = ask;
+    const bool rows = ROWS && !self;
+    if (rows) sum_spans_by_rows(index, k, fits ? u32(v.mine.nb) : 0u, tile, wave, ask, sh);
 #pragma nounroll
-    for (u32 u = u32(wave); u < u32(k) * parts; u += kTileWaves) {
+    for (u32 u = u32(wave); !rows && u < u32(k) * parts; u += kTileWaves) {
       const u32 s = u / parts, p = u % parts;
       const u32 nb = lane_value(u32(fits), int(s)) ? lane_value(u32(v.mine.nb), int(s)) : 0u;
       u32 before = 0, total = 0, seen = 0;

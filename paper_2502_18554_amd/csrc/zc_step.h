@@ -391,7 +391,7 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
       seg_end = have ? e1 : 0u;
       w = w_at < a.in.bytes ? wb : 0u;
     } else {
-      ask = ask_plain_streams<1>(&a.in, 1, a.index, SELF, seg, wave);
+      ask = ask_plain_streams<1, false>(&a.in, 1, a.index, SELF, seg, wave);
       const u64 w_at = u64(kHeaderBytes) + b;
       const u32 wb = u32(*at_bytes(a.in.base, w_at < a.in.bytes ? u32(w_at) : 0u));
       w = w_at < a.in.bytes ? wb : 0u;
@@ -412,8 +412,8 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
   v.mine = h;
   v.err = h.ok ? 0u : status_bit(ZC_ERR_FORMAT);
   u32 tile = a.first_tile + blockIdx.x;      // tiles in the order in which workgroups start
-  if (TICKETS && !IX) ask = ask_plain_streams<1>(&a.in, 1, a.index, SELF, tile * kTileWaves + u32(wave), wave);
-  if (!IX) seg_begin = lane_value(judge_plain_streams(&a.in, 1, a.index, SELF, tile, wave, ask, v, survey), 0);
+  if (TICKETS && !IX) ask = ask_plain_streams<1, false>(&a.in, 1, a.index, SELF, tile * kTileWaves + u32(wave), wave);
+  if (!IX) seg_begin = lane_value(judge_plain_streams<1, false>(&a.in, 1, a.index, SELF, tile, wave, ask, v, survey), 0);
   if (v.err) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       if (!a.adopt) a.ctl->result = 0;
@@ -464,8 +464,8 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
       }
     } else {                                 // (the verdict stands: once more, for the place of this tile)
       lds_barrier();
-      ask = ask_plain_streams<1>(&a.in, 1, a.index, SELF, seg, wave);
-      seg_begin = lane_value(judge_plain_streams(&a.in, 1, a.index, SELF, tile, wave, ask, v, survey), 0);
+      ask = ask_plain_streams<1, false>(&a.in, 1, a.index, SELF, seg, wave);
+      seg_begin = lane_value(judge_plain_streams<1, false>(&a.in, 1, a.index, SELF, tile, wave, ask, v, survey), 0);
       w = active ? u32(*at_bytes(a.in.base, kHeaderBytes + b)) : 0u;
     }
   }

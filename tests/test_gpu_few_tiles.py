@@ -6,7 +6,7 @@ import torch
 
 import gpuutil
 from paper_2502_18554_amd import synth
-from paper_2502_18554_amd.binding import ZC_ERR_ARG, ZC_ERR_CAPACITY, ZC_ERR_FORMAT, ZC_ERR_MISMATCH, ZC_OK
+from paper_2502_18554_amd.binding import ZC_ERR_ARG, ZC_ERR_CAPACITY, ZC_ERR_FORMAT, ZC_ERR_MISMATCH, ZC_OK, ZC_STREAM_PLAIN
 
 pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("stream_variant")]
 
@@ -91,6 +91,79 @@ def test_decompress_of_few_tiles(zcref, stream_variant, tiles, k):
         assert st == ZC_ERR_FORMAT and bool((d_out == 7.0).all())
         st, outs, _ = u.gpu_decompress_many(refs[:-1] + [broken], [n] * k)
         assert st == ZC_ERR_FORMAT and all(np.isnan(o).all() for o in outs)
+
+
+# the lists of spans (128 tiles each) of plain streams that a kernel ahead has indexed, which are added up in rows of lanes: by
+# every wave for itself up to four streams, four streams a wave and round above; one span and several
+@pytest.mark.parametrize("k,tiles", [(1, 600), (2, 300), (3, 257), (4, 129), (5, 128), (15, 40), (16, 33), (17, 129), (33, 16), (64, 9)])
+def test_plain_streams_indexed_ahead(zcref, stream_variant, k, tiles):
+    if stream_variant == "indexed":
+        return
+    u = gpuutil
+    n = tiles * TILE - 2049
+    base = _values(n, 61)
+    refs = [zcref.compress(np.roll(base, 4096 * i), 6e-3)[1] for i in range(k)]
+    for tickets in (False, True):
+        u.set_tickets(tickets)
+        try:
+            for op in (None, 1, 2):
+                st_ref, want = zcref.reduce(refs, op=op or 0)[:2]
+                st, got, _ = u.gpu_reduce(refs, n, op=op)
+                assert st == st_ref == ZC_OK and got.tobytes() == want.tobytes(), (op, u.first_diff(got, want))
+        finally:
+            u.set_tickets(False)
+    want = [zcref.decompress(r)[1] for r in refs]
+    st, got, ns = u.gpu_decompress_many(refs, [n] * k)
+    assert st == ZC_OK and ns == [n] * k
+    for w, g in zip(want, got):
+        assert np.array_equal(w.view(np.uint32), g[:n].view(np.uint32))
+    # one stream whose table does not add up, or holds a width above 31, in its last block or its first: every tile must know
+    nb = (n + 31) // 32
+    for s in sorted({0, k // 2, k - 1}):
+        for at, bad in ((nb - 1, 32), (0, 1 + int(refs[s][u.widths_begin(nb)]) % 15)):
+            broken = refs[s].copy()
+            broken[u.widths_begin(nb) + at] = bad
+            assert zcref.decompress(broken)[0] == ZC_ERR_FORMAT
+            streams = refs[:s] + [broken] + refs[s + 1:]
+            assert u.gpu_reduce(streams, n)[0] == ZC_ERR_FORMAT and u.gpu_reduce(streams, n, op=1)[0] == ZC_ERR_FORMAT
+            st, outs, _ = u.gpu_decompress_many(streams, [n] * k)
+            assert st == ZC_ERR_FORMAT and all(np.isnan(o).all() for o in outs)
+
+
+@pytest.mark.parametrize("k", [2, 17])
+def test_plain_streams_of_more_spans_than_a_row_reads_at_once(stream_variant, k):
+    """65 spans: against the indexed streams of the same values, whose positions come from their index."""
+    if stream_variant == "indexed":
+        return
+    u, lib = gpuutil, gpuutil._zc
+    n = 64 * 128 * TILE + 5000
+    xs = [synth.sinusoids(n, seed=5 + i, device=u.DEV) for i in range(2)]
+    ws = u.workspace(n, k)
+    results, made = [], []
+    for flags in (ZC_STREAM_PLAIN, 0):
+        room = torch.empty(lib.zc_compress_bound(n, flags), dtype=torch.uint8, device=u.DEV)
+        streams = []
+        for x in xs:
+            st, size = lib.zc_compress(x, n, 1e-2, room, ws, flags=flags)
+            assert st == ZC_OK
+            streams.append(room[:size].clone())
+        made.append(streams)
+        operands = (streams * k)[:k]
+        for op in (0, 1):
+            st, size = lib.zc_reduce_compressed_op(operands, [s.numel() for s in operands], op, room, ws, flags=flags)
+            assert st == ZC_OK
+            begin = 32 + (0 if flags else (4 * ((n + 2047) // 2048 + 1) + 15) // 16 * 16)
+            results.append(room[begin:size].clone())         # width table, first codes and payload
+    assert torch.equal(results[0], results[2]) and torch.equal(results[1], results[3])
+    del xs, results
+    operands = (made[0] * k)[:k]
+    outs = [torch.empty(n, device=u.DEV) for _ in range(k)]
+    st, ns = lib.zc_decompress_many(operands, [s.numel() for s in operands], outs, ws, flags=ZC_STREAM_PLAIN)
+    assert st == ZC_OK and ns == [n] * k
+    for i in range(2):
+        y = torch.empty(n, device=u.DEV)
+        assert lib.zc_decompress(made[1][i], made[1][i].numel(), y, ws)[0] == ZC_OK
+        assert all(torch.equal(y.view(torch.int32), o.view(torch.int32)) for o in outs[i::2])
 
 
 @pytest.mark.parametrize("tiles", [12, 40])
