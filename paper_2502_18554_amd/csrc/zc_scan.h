@@ -206,8 +206,8 @@ __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
 struct StreamsVerdict {
   ParsedHeader h0;      // header of stream 0 (uniform)
   u32 err;              // status bits: FORMAT, MISMATCH (uniform)
-  u64 nsum;             // sum of the nsum fields of the valid streams (of a reduce, in its first workgroup only)
-  u64 sum_n;            // sum of their n fields (the same)
+  u64 nsum;             // sum of the nsum fields of the valid streams
+  u64 sum_n;            // sum of their n fields
   u64 wide;             // bit s: stream s may hold blocks wider than 15 bits (uniform; plain streams: see judge_plain_streams)
   ParsedHeader mine;    // lane s: header of stream s
 };
@@ -241,13 +241,11 @@ __device__ inline StreamsVerdict judge_headers(const StreamRef* streams, int k, 
   if (check_match && v.h0.ok && __any(mine && h.ok && (h.n != v.h0.n || h.eb_bits != v.h0.eb_bits)))
     v.err |= status_bit(ZC_ERR_MISMATCH);
   v.wide = __ballot(mine && h.ok && h.wide);
-  v.nsum = v.sum_n = 0;
-  if (!check_match || blockIdx.x == 0) {
-    const u32 ns = mine && h.ok ? h.nsum : 0u;
-    v.nsum = u64(wave_sum_u32(ns & 0xffffu)) + (u64(wave_sum_u32(ns >> 16)) << 16);
-    const u64 nn = mine && h.ok ? h.n : 0;            // <= 2^31
-    v.sum_n = u64(wave_sum_u32(u32(nn) & 0xffffu)) + (u64(wave_sum_u32(u32(nn >> 16))) << 16);
-  }
+  // (in every workgroup: behind a branch for the first one, the Sum of 8 x 1000 values of plain streams took 13.4 us, without 13.1)
+  const u32 ns = mine && h.ok ? h.nsum : 0u;
+  v.nsum = u64(wave_sum_u32(ns & 0xffffu)) + (u64(wave_sum_u32(ns >> 16)) << 16);
+  const u64 nn = mine && h.ok ? h.n : 0;              // <= 2^31
+  v.sum_n = u64(wave_sum_u32(u32(nn) & 0xffffu)) + (u64(wave_sum_u32(u32(nn >> 16))) << 16);
   return v;
 }
 
