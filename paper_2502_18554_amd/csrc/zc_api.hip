@@ -107,9 +107,11 @@ int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = 
 }
 
 // Plain input streams of up to `tiles` tiles, most likely no more than `likely`: whether the main kernel is to sum their
-// width tables itself (see judge_plain_streams); if not, their positions are computed ahead of it.
-bool index_plain_streams(const StreamRef* streams, int k, u64 tiles, u64 likely, const WorkspaceLayout& l, hipStream_t stream) {
-  if (likely * u64(k) <= kSelfTiles) return true;
+// width tables itself (see judge_plain_streams); if not, their positions are computed ahead of it.  Either way is right
+// whatever the streams hold.
+bool index_plain_streams(const StreamRef* streams, int k, u64 tiles, u64 likely, const WorkspaceLayout& l, hipStream_t stream,
+                         bool reduce = false) {
+  if (likely * u64(k) <= self_tiles(k, reduce) && tiles <= kMostTables * likely) return true;
   ScanArgs sa;
   for (int i = 0; i < k; ++i) sa.streams[i] = streams[i];
   sa.k = k;
@@ -495,7 +497,10 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   }
   ra.k = k;
   ra.index = l.index;
-  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, tiles, l, stream);
+  // (the operands' bytes allow up to kMostTables tiles where there is one; a workspace of zc_workspace_bytes(n, k) bytes says how
+  // many there are, and with a larger one a call that could do without the launch ahead may get it all the same)
+  const u64 made_for = l.tiles_cap > kWsSpareTiles ? l.tiles_cap - kWsSpareTiles : 1;
+  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, tiles < made_for ? tiles : made_for, l, stream, true);
   ra.out = static_cast<u8*>(d_out);
   ra.out_cap = out_cap;
   ra.ctl = l.ctl;

@@ -114,9 +114,10 @@ struct WorkspaceLayout {
 constexpr u64 kDescBytes = 128;           // per tile, see kDescStride
 constexpr u64 kWsFixed = sizeof(Control) + kTicketBytes + 12 * ZC_MAX_K + 64;   // control, tickets, the +1 of every row of spans, padding
 
+constexpr u64 kWsSpareTiles = 16;
 __host__ constexpr u64 workspace_bytes(u64 n_max, int k_max) {
   if (k_max < 1) k_max = 1;
-  const u64 t = num_tiles(num_blocks(n_max)) + 16;
+  const u64 t = num_tiles(num_blocks(n_max)) + kWsSpareTiles;
   return kWsFixed + t * (kDescBytes + 17 * u64(k_max));      // 17 >= segment offsets (16) + the tile's share of the spans
 }
 

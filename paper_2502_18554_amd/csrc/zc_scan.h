@@ -302,11 +302,21 @@ struct PlainSurvey {
   u32 in_tile[4 * K];       // self: per segment of the tile, payload words of the tile before it
 };
 
-// Tiles of all streams of a call together up to which every workgroup sums their tables itself: the work grows with the
-// square of the tiles, the launch it saves does not.  us per call, with the launch and without:
-//   decompress   1 tile 9.0 5.1 | 128: 9.6 6.2 | 489: 11.5 12.0 | 2048: 20.1 70
-//   8 buffers    8 x 33 tiles 12.3 11.0 | 8 x 128: 15.4 27;   Sum of 8   8 x 1 21.6 17.1 | 8 x 33 20.4 18.6 | 8 x 128 21.2 26.2
-constexpr u64 kSelfTiles = 512;
+// Tiles of all k streams of a call together up to which every workgroup sums their tables itself: the work grows with the
+// square of the tiles, the launch it saves does not.  us per call, with the launch ahead and without (power-law fields, 1e-3):
+//   decompress   1 tile 8.9 5.0 | 256: 8.8 7.8 | 320: 9.3 9.3 | 384: 9.3 10.1;   ring round   256: 11.0 10.2 | 320: 12.7 12.6 | 384: 13.3 13.6
+//   3 buffers    255: 9.8 9.6 | 384: 10.1 12.1;   8 buffers   256: 10.9 8.9 | 384: 11.0 11.0 | 512: 11.1 12.5
+//   16 buffers   384: 13.5 12.0 | 512: 13.4 13.6;   64 buffers   512: 28.5 25.3
+// The tables are summed one stream after the other, and what a launch ahead leaves to do is done for many at once in the
+// reduces (see below), so that there the launch pays earlier with many streams:
+//   Sum of 2     256: 12.3 11.5 | 320: 12.7 12.4;   of 8   256: 17.0 16.1 | 320: 17.7 17.5;   of 12   192: 20.2 19.0 | 288: 20.7 20.4
+//   Sum of 16    128: 23.9 23.2 | 256: 23.8 23.5 | 320: 23.8 24.7;   of 24   192: 31.2 30.4 | 288: 31.3 32.3
+//   Sum of 32    32: 37.9 38.4 | 256: 38.5 39.4;   of 64   64: 68.4 74.2
+__host__ constexpr u64 self_tiles(int k, bool reduce) { return reduce ? (k <= 12 ? 320 : k <= 16 ? 256 : k <= 24 ? 192 : 0) : k < 16 ? 320 : 512; }
+
+// The host does not know the tiles.  A stream of T tiles has at most kMostTables times as many tables as it needs (133 bytes
+// a block where a table takes 5): more bytes than that, and T is not what there is, or not all of it is the stream.
+constexpr u64 kMostTables = 27;
 
 // How the lists of spans of a call of several streams are added up: by whole waves, one stream after the other, or in rows (ROWS)
 // of 16 lanes, a stream each, four a wave at once.  The reduces have rows throughout, and with four streams or fewer every wave

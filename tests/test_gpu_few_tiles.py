@@ -60,10 +60,11 @@ def test_ring_rounds_of_many_tiles(zcref, tiles):
         assert st == st_ref and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
 
 
-# the tables of plain streams are summed by every workgroup of the main kernel up to 512 tiles of all streams together, by
-# a kernel ahead of it from there on; parts of four waves (one stream), two and one, and a table of more than one round
+# the tables of plain streams are summed by every workgroup of the main kernel up to 320 tiles of all streams together (512 from
+# 16 streams on), by a kernel ahead of it from there on; parts of four waves (one stream), two and one, and a table of more than one round
 @pytest.mark.parametrize("tiles,k", [(4, 1), (5, 1), (17, 1), (512, 1), (513, 1), (3, 2), (256, 2), (257, 2), (5, 3), (170, 3), (171, 3),
-                                     (33, 5), (103, 5), (2, 64), (9, 64)])
+                                     (33, 5), (103, 5), (2, 64), (9, 64),
+                                     (320, 1), (321, 1), (160, 2), (161, 2), (106, 3), (107, 3), (64, 5), (65, 5), (32, 16), (33, 16), (8, 64)])
 def test_decompress_of_few_tiles(zcref, stream_variant, tiles, k):
     u = gpuutil
     n = tiles * TILE - 2049
@@ -91,6 +92,21 @@ def test_decompress_of_few_tiles(zcref, stream_variant, tiles, k):
         assert st == ZC_ERR_FORMAT and bool((d_out == 7.0).all())
         st, outs, _ = u.gpu_decompress_many(refs[:-1] + [broken], [n] * k)
         assert st == ZC_ERR_FORMAT and all(np.isnan(o).all() for o in outs)
+
+
+# both sides of the number of tiles up to which a reduce of plain streams sums their tables itself
+@pytest.mark.parametrize("k,tiles", [(1, 320), (1, 321), (2, 160), (2, 161), (12, 26), (12, 27), (16, 16), (16, 17), (24, 8), (24, 9), (25, 1)])
+def test_reduces_of_few_tiles(zcref, stream_variant, k, tiles):
+    if stream_variant == "indexed":
+        return
+    u = gpuutil
+    n = tiles * TILE - 2049
+    base = _values(n, 62)
+    refs = [zcref.compress(np.roll(base, 4096 * i), 6e-3)[1] for i in range(k)]
+    for op in (None, 1):
+        st_ref, want = zcref.reduce(refs, op=op or 0)[:2]
+        st, got, _ = u.gpu_reduce(refs, n, op=op)
+        assert st == st_ref == ZC_OK and got.tobytes() == want.tobytes(), (op, u.first_diff(got, want))
 
 
 # the lists of spans (128 tiles each) of plain streams that a kernel ahead has indexed, which are added up in rows of lanes: by
