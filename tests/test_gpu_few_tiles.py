@@ -39,25 +39,40 @@ def test_streams_of_few_tiles(zcref, tiles):
     st_ref, step_ref = zcref.reduce_step(refs[0], xs[1])[:2]
     st, step, _ = u.gpu_reduce_step(refs[0], xs[1])
     assert st == st_ref and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
-    if tiles % 2 == 0:                             # the compressor's own tiles: as many again
-        n2 = 2 * tiles * TILE - 4097
-        x = _values(n2, 50)
-        st_ref, ref = zcref.compress(x, eb)[:2]
-        st, s, total = u.gpu_compress(x, eb)
-        assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+    n2 = 2 * tiles * TILE - 4097                   # the compressor's own tiles: as many
+    x = _values(n2, 50)
+    st_ref, ref = zcref.compress(x, eb)[:2]
+    st, s, total = u.gpu_compress(x, eb)
+    assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
 
 
-# both sides of the size from which ring rounds run with more workgroups per compute unit
+# the same with tiles handed out by tickets, on both sides of both limits
+@pytest.mark.parametrize("tiles", [9, 512, 513, 1024, 1025])
+def test_streams_of_few_tiles_by_ticket(zcref, tiles):
+    gpuutil.set_tickets(True)
+    try:
+        test_streams_of_few_tiles(zcref, tiles)
+    finally:
+        gpuutil.set_tickets(False)
+
+
+# both sides of the size from which ring rounds of indexed streams run with more workgroups per compute unit, and plain ones
+# that are indexed ahead
+@pytest.mark.parametrize("tickets", [False, True])
 @pytest.mark.parametrize("tiles", [2047, 2048])
-def test_ring_rounds_of_many_tiles(zcref, tiles):
+def test_ring_rounds_of_many_tiles(zcref, tiles, tickets):
     u = gpuutil
     n = tiles * TILE - 4097
     xs = [_values(n, 80 + i) for i in range(2)]
     ref = zcref.compress(xs[0], 1e-3)[1]
-    for op in (0, 1):
-        st_ref, step_ref = zcref.reduce_step(ref, xs[1], op=op)[:2]
-        st, step, _ = u.gpu_reduce_step(ref, xs[1], op=op)
-        assert st == st_ref and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
+    u.set_tickets(tickets)
+    try:
+        for op in (0, 1, 2):
+            st_ref, step_ref = zcref.reduce_step(ref, xs[1], op=op)[:2]
+            st, step, _ = u.gpu_reduce_step(ref, xs[1], op=op)
+            assert st == st_ref and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
+    finally:
+        u.set_tickets(False)
 
 
 # the tables of plain streams are summed by every workgroup of the main kernel up to 320 tiles of all streams together (512 from
