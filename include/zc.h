@@ -43,8 +43,8 @@
  * flags (an OR of the flag bits below; 0 = the defaults):
  *   ZC_STREAM_PLAIN     every stream of this call, read or written, is a plain stream.  A
  *                       stream of the other variant is ZC_ERR_FORMAT.  Consumers of plain
- *                       streams run two small kernels ahead of their main kernel to sum the
- *                       width table.
+ *                       streams have to sum the width tables first: the main kernel does it for
+ *                       small streams, a small kernel ahead of it for others.
  *   ZC_TILES_BY_TICKET  (calls that write a stream) tiles of 256 or 512 blocks are claimed by
  *                       workgroups with atomic tickets instead of being taken by workgroup id.
  *                       The single-pass placement of the output (a device-wide exclusive sum of
@@ -327,7 +327,7 @@ int zc_debug_block_offsets(const void* d_in, size_t in_bytes, uint32_t* d_off_wo
  * zc_reduce_step_op (and their _ex forms) hand a pair of HIP events to the launch of their
  * main kernel on the call's stream (hipExtLaunchKernelGGL), which stamps them with that
  * kernel's start and end (the compress, decompress, reduce or step kernel; not the small
- * kernels that run ahead of it for plain streams, nor the one that reports a synchronous call's result).
+ * kernel that may run ahead of it for plain streams, nor the one that reports a synchronous call's result).
  * zc_profile_collect waits for the recorded pairs, stores up to cap elapsed times in
  * milliseconds in ms[] and the matching ZC_KERNEL_* ids in kernel[] (host arrays, either may
  * be NULL) in call order, forgets them, and returns how many it stored (a negative status on

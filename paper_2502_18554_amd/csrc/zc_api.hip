@@ -111,7 +111,7 @@ int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = 
 // whatever the streams hold.
 bool index_plain_streams(const StreamRef* streams, int k, u64 tiles, u64 likely, const WorkspaceLayout& l, hipStream_t stream,
                          bool reduce = false) {
-  if (likely * u64(k) <= self_tiles(k, reduce) && tiles <= kMostTables * likely) return true;
+  if (likely * u64(k) <= self_tiles(k, reduce) && tiles * u64(k) <= kMostTables * self_tiles(k, reduce)) return true;
   ScanArgs sa;
   for (int i = 0; i < k; ++i) sa.streams[i] = streams[i];
   sa.k = k;

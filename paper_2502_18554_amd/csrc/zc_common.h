@@ -75,7 +75,7 @@ static_assert(sizeof(Control) == 64, "control block is 64 bytes");
 // Tile hand-out counters, four per XCD (see take_tile), follow the control block.  Each sits
 // in a 128-byte line of its own, and none shares the line of the control block: accesses to
 // one line retire one after the other even when they address different words of it, and every
-// workgroup reads the control block when it starts.
+// workgroup of a later part of a call reads the control block when it starts.
 constexpr int kTicketStride = 16;            // in u64
 constexpr u64 kTicketBytes = u64(kTicketShards + 1) * kTicketStride * 8;
 __host__ __device__ inline u64* ticket_counter(Control* ctl, u32 shard) {
@@ -248,7 +248,7 @@ __device__ inline u64 uniform64(u64 v) { return u64(uniform(u32(v))) | (u64(unif
 // that no earlier launch on the same workspace has had: the packet number of the dispatch in
 // its hardware queue (which a replay of a captured graph renews as well), the queue, a number
 // the host draws per call (its clock), and the workspace address, mixed.  A call of several
-// launches (a stream produced in parts, the validation kernels of plain streams) uses the tag of its
+// launches that write (a stream produced in parts) uses the tag of its
 // first launch throughout: that launch leaves it in the control block, the later ones pick it up
 // there (`adopt`).
 // ---------------------------------------------------------------------------------------
@@ -310,10 +310,6 @@ __device__ inline u32 status_bits(const Control* ctl, u64 tag) {
 __device__ inline uint4 load_once(const uint4* p) {
   const u32x4_t t = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
   return make_uint4(t.x, t.y, t.z, t.w);
-}
-__device__ inline void store_once(float4* p, const float4& v) {
-  const f32x4_t t = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(t, reinterpret_cast<f32x4_t*>(p));
 }
 __device__ inline void store_once(u32* p, u32 v) { __builtin_nontemporal_store(v, p); }
 __device__ inline float4 load_once(const float4* p) {
@@ -492,7 +488,6 @@ constexpr int kChains = 8;
 static_assert(kTicketShards % kChains == 0, "tickets hand out the tiles of a chain on one XCD");
 constexpr u32 kLocalPolls = 16;
 constexpr u32 kOwnChain = 1u << (kChains - 1);               // lane 7: the chain of tile - 8, the tile's own
-constexpr u32 kOtherChains = kOwnChain - 1u;                 // lanes 0..6: the chains of tile - 1 .. tile - 7
 
 // state | wide mark | value of a descriptor as loaded (four 32-bit words); 0 (empty) unless it is of this call.
 __device__ inline u64 desc_decode(const u32x4_t& w, u64 tag) {

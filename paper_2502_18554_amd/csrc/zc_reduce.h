@@ -778,7 +778,7 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   ReduceCall c;
   OperandMeta meta{};
   // A workgroup that takes the tile of its own number asks for the first operand's tables
-  // together with the control block and the header, before it knows the header: one memory
+  // together with the headers, before it knows them: one memory
   // round trip instead of two.  The loads are fenced in by sizes the host passed.  (Not for
   // indexed streams: where their width bytes are is only known with the header.)
   const bool early = !a.ticketed && (!IX || a.n_part != 0);

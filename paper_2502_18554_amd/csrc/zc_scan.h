@@ -314,8 +314,9 @@ struct PlainSurvey {
 //   Sum of 32    32: 37.9 38.4 | 256: 38.5 39.4;   of 64   64: 68.4 74.2
 __host__ constexpr u64 self_tiles(int k, bool reduce) { return reduce ? (k <= 12 ? 320 : k <= 16 ? 256 : k <= 24 ? 192 : 0) : k < 16 ? 320 : 512; }
 
-// The host does not know the tiles.  A stream of T tiles has at most kMostTables times as many tables as it needs (133 bytes
-// a block where a table takes 5): more bytes than that, and T is not what there is, or not all of it is the stream.
+// The host does not know the tiles, only what the output or the workspace has room for and the bytes, which are at most
+// kMostTables times what the tables of so many tiles need (133 bytes a block where its tables take 5).  With more bytes than
+// the largest such streams have there may be tables that take every workgroup long to read, if only to find that the call fails.
 constexpr u64 kMostTables = 27;
 
 // How the lists of spans of a call of several streams are added up: by whole waves, one stream after the other, or in rows (ROWS)
