@@ -132,7 +132,7 @@ __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u3
 
 // Quantise the wave's values where they landed and transpose the codes through LDS so that one
 // lane owns one block: q[j] = code j of the lane's block.  have: see share_values.
-// (quantize4 for fresh values in both halves with tiles by ticket, in the second half without: 38 and 52 scalar registers
+// (quantize4 for fresh values in both halves with tiles by ticket, in the second half without: 38 and 54 scalar registers
 // pushed out.  In both halves without tickets it needs fewer, but then has 20 bytes of scratch set aside, which
 // zc_compress_noalloc is not to need; in none it needs twice as many.  2^26 values by ticket 80.7 us with none, 80.0 with one,
 // 78.1 with both; without tickets 66.8, 65.6, 65.2.)

@@ -26,7 +26,7 @@
 //   8 x 2^23 (1024 tiles)                                     36.2   32.9
 //   16 x 2^20                                                 29.7   24.8
 //   hard data, 4 x 4 000 000                                  28.2   15.6
-//   8 x 1024                                                  17.6   14.3
+//   8 x 1000                                                  18.7   14.9
 // (the last four: before payloads went straight to LDS and loads were trimmed, see OperandPipe and load_operand_meta).
 // 122 registers, four waves per SIMD, and 12 bytes of scratch that only the
 // wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
