@@ -15,6 +15,7 @@
 #include "zc_compress.h"
 #include "zc_decompress.h"
 #include "zc_reduce.h"
+#include "zc_reduce_few.h"
 #include "zc_reduce_op.h"
 #include "zc_report.h"
 #include "zc_scan.h"
@@ -500,7 +501,8 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   // (the operands' bytes allow up to kMostTables tiles where there is one; a workspace of zc_workspace_bytes(n, k) bytes says how
   // many there are, and with a larger one a call that could do without the launch ahead may get it all the same)
   const u64 made_for = l.tiles_cap > kWsSpareTiles ? l.tiles_cap - kWsSpareTiles : 1;
-  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, tiles < made_for ? tiles : made_for, l, stream, true);
+  const u64 likely = tiles < made_for ? tiles : made_for;
+  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, likely, l, stream, true);
   ra.out = static_cast<u8*>(d_out);
   ra.out_cap = out_cap;
   ra.ctl = l.ctl;
@@ -526,7 +528,14 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     tiles = ra.end_tile - ra.first_tile;
   }
   if (op == ZC_OP_SUM) {
-    launch_main(ZC_KERNEL_REDUCE, ix ? reduce_kernel<true> : reduce_kernel<false>, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
+    const int segs = ranged || ra.ticketed ? 0 : few_segments(k, likely);
+    void (*kernel)(ReduceArgs) = ix ? reduce_kernel<true> : reduce_kernel<false>;
+    if (segs == 1) kernel = ix ? reduce_few_kernel<true, 1, 4> : reduce_few_kernel<false, 1, 4>;
+    else if (segs == 2) kernel = ix ? reduce_few_kernel<true, 2, 4> : reduce_few_kernel<false, 2, 4>;
+    else if (segs == 4 && likely <= kFewTiles) kernel = ix ? reduce_few_kernel<true, 4, 4> : reduce_few_kernel<false, 4, 4>;
+    else if (segs == 4 && ix) kernel = reduce_few_kernel<true, 4, 2>;
+    if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
+    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
   } else {
     void (*kernel)(ReduceArgs) = op == ZC_OP_MAX ? (ix ? reduce_op_kernel<true, ZC_OP_MAX> : reduce_op_kernel<false, ZC_OP_MAX>)
                                                  : (ix ? reduce_op_kernel<true, ZC_OP_MIN> : reduce_op_kernel<false, ZC_OP_MIN>);

@@ -419,6 +419,9 @@ constexpr u64 kDescTagMask = ((u64(1) << 29) - 1) << 32;
 // Descriptors are polled by every tile in flight, so neighbours must not share a memory
 // line (polls of one line queue up behind each other): one descriptor per 128 bytes.
 constexpr int kDescStride = 16;            // in u64
+// A call whose tiles are of fewer segments (see zc_reduce_few.h) has up to four times as many in the same place.  Its tiles look
+// back directly, 64 neighbouring descriptors a load.
+constexpr u32 kDescApart = kDescStride * 8, kDescApartFine = kDescApart / 4;      // bytes
 
 // Both words travel in one 16-byte access (a hot line serves its requests one after the other,
 // so a second access per poll or publication would double the time the look-back chain takes),
@@ -430,10 +433,10 @@ __device__ inline __amdgpu_buffer_rsrc_t desc_resource(const u64* desc) {
 constexpr int kCoherentAccess = 16;        // cache policy bits of the buffer builtins: sc1
 
 // v = state | wide mark | value.
-__device__ inline void desc_store(u64* desc, u32 tile, u64 v, u64 tag) {
+__device__ inline void desc_store(u64* desc, u32 tile, u64 v, u64 tag, u32 apart) {
   const u64 a = v | ((tag << 32) & kDescTagMask);
   const u32x4_t words = {u32(a), u32(a >> 32), u32(tag), u32(tag >> 32)};
-  __builtin_amdgcn_raw_buffer_store_b128(words, desc_resource(desc), tile * u32(kDescStride * 8), 0, kCoherentAccess);
+  __builtin_amdgcn_raw_buffer_store_b128(words, desc_resource(desc), tile * apart, 0, kCoherentAccess);
 }
 
 // LDS of one wave: 32 rows (blocks) of 32 codes + 4 words of padding, which keeps the 128-bit
@@ -495,23 +498,23 @@ __device__ inline u64 desc_decode(const u32x4_t& w, u64 tag) {
   const u64 t = u64(w.z) | (u64(w.w) << 32);
   return (t == tag && (v & kDescTagMask) == ((tag << 32) & kDescTagMask)) ? (v & ~kDescTagMask) : 0ull;
 }
-__device__ inline u64 desc_load(const u64* desc, u32 tile, u64 tag) {
-  return desc_decode(__builtin_amdgcn_raw_buffer_load_b128(desc_resource(desc), tile * u32(kDescStride * 8), 0, kCoherentAccess), tag);
+__device__ inline u64 desc_load(const u64* desc, u32 tile, u64 tag, u32 apart) {
+  return desc_decode(__builtin_amdgcn_raw_buffer_load_b128(desc_resource(desc), tile * apart, 0, kCoherentAccess), tag);
 }
 
 // Exclusive sum of the chain of `tile` (tile >= kChains) by scalar loads, two descriptors a round
 // (both loads and the wait for them in one statement: the compiler does not track what inline
 // assembly has in flight).  False when kLocalPolls rounds in a row found nothing new.
 // Uniform values throughout.
-__device__ inline bool own_chain_scalar(const u64* desc, u32 tile, u64 tag, u32& sum, u64& wide) {
+__device__ inline bool own_chain_scalar(const u64* desc, u32 tile, u64 tag, u32 apart, u32& sum, u64& wide) {
   i64 look = i64(tile) - kChains;
   u32 idle = 0;
   sum = 0;
   wide = 0;
   while (look >= 0) {
     const i64 next = look - kChains;
-    const u64 a0 = uniform64(reinterpret_cast<u64>(desc + u64(look) * kDescStride));
-    const u64 a1 = uniform64(reinterpret_cast<u64>(desc + u64(next >= 0 ? next : look) * kDescStride));
+    const u64 a0 = uniform64(reinterpret_cast<u64>(desc) + u64(look) * apart);
+    const u64 a1 = uniform64(reinterpret_cast<u64>(desc) + u64(next >= 0 ? next : look) * apart);
     u32x4_t w0, w1;
     asm volatile(
         "s_load_dwordx4 %0, %2, 0x0 glc\n\t"
@@ -563,14 +566,14 @@ __device__ inline bool looks_direct(u32 ntiles, u32 limit, bool coherent, u32 pa
 // Called by all 64 lanes of a wave.  A lane inspects tile `head` (none if negative), and where that has published its size
 // but no chain sum, the tile `stride` before it, and so on: the sum over the lanes, modulo 2^32 (a stream has fewer
 // payload words than that), with kDescWide set if one of those tiles has it set.
-__device__ inline u64 walk_back(const u64* desc, i32 head, i32 stride, Control* ctl, u64 tag) {
+__device__ inline u64 walk_back(const u64* desc, i32 head, i32 stride, Control* ctl, u64 tag, u32 apart) {
   bool live = head >= 0;
   u32 total = 0;
   bool wide = false;
   u32 spins = 0;
   while (__ballot(live)) {
     u64 d = 0;
-    if (live) d = desc_load(desc, u32(head), tag);
+    if (live) d = desc_load(desc, u32(head), tag, apart);
     const u32 state = u32(d >> 62);
     const bool there = state == 1 || state == 2;
     if (live && there) {
@@ -593,10 +596,10 @@ __device__ inline u64 walk_back(const u64* desc, i32 head, i32 stride, Control* 
 }
 
 // The chains in `chains` (bit c = the chain of tile - 1 - c, read by lane c).
-__device__ inline u64 chains_lookback(const u64* desc, u32 tile, Control* ctl, u64 tag, u32 chains) {
+__device__ inline u64 chains_lookback(const u64* desc, u32 tile, Control* ctl, u64 tag, u32 apart, u32 chains) {
   const int lane = lane_id();
   const bool mine = lane < kChains && ((chains >> lane) & 1u) != 0;
-  return walk_back(desc, mine ? i32(tile) - 1 - lane : -1, kChains, ctl, tag);
+  return walk_back(desc, mine ? i32(tile) - 1 - lane : -1, kChains, ctl, tag, apart);
 }
 
 }  // namespace zc

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     if (lane == 0) write_index_entry(sink, tile * u32(kPackWaves) + u32(wave), tb.words + pl.wave_off);
     if (narrow) copy_staged_wave<16, false>(sink, pl, tb.words, wl, lane);
     else store_wide_wave<TICKETS>(a, sink, pl, tb.words, wblock0, have, lane, wl);
-    finish_stream(sink, pl, tile, ntiles, tb);
+    finish_stream<kPackWaves>(sink, pl, tile, ntiles, tb);
     if (active && tables_fit) {                // (not store_tables: see copy_staged_words)
       const u64 b = wblock0 + u64(lane);
       a.out[widths_begin(a.nb, a.ix) + b] = u8(pl.w);

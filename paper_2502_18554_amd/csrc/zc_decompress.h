@@ -257,7 +257,7 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
   u64 ltag = launch_tag(a.nonce, a.ctl);
   asm volatile("" : "+s"(ltag));
   StreamsVerdict v;
-  if constexpr (many) v = judge_headers<IX>(streams, k, false);      // any malformed stream stops the whole call
+  if constexpr (many) v = judge_headers<IX>(read_headers(streams, k), k, false);      // any malformed stream stops the whole call
   const ParsedHeader h = parse_header(hw, a.in.bytes, IX);
   if constexpr (!many) {
     v.mine = h;

@@ -23,6 +23,7 @@ struct PayloadSink {
   bool direct;      // the look-back reads the sizes of all tiles before the tile (see kDirectTiles)
   u32 part_end;     // a stream produced in parts (zc_compress_part): one past the last tile of this part; else 0
   u64 tag;          // the call's tag (see launch_tag): descriptors and status bits carry it
+  u32 apart = kDescApart;      // bytes from one tile's descriptor to the next
 };
 
 // Per-wave view of where its payload goes.
@@ -187,7 +188,7 @@ __device__ inline void stage_and_copy_half(WordFn word, u32 w, bool in_half, u32
 __device__ inline void publish_tile_size(const PayloadSink& s, u32 tile, u32 tile_total, bool tile_wide) {
   // (the first tile of a chain has nothing before it in the chain: its size is its chain sum)
   desc_store(s.desc, tile,
-             (tile < u32(kChains) ? kDescChain : kDescAggregate) | (tile_wide ? kDescWide : 0) | u64(tile_total), s.tag);
+             (tile < u32(kChains) ? kDescChain : kDescAggregate) | (tile_wide ? kDescWide : 0) | u64(tile_total), s.tag, s.apart);
 }
 
 // Sum over groups of WAVES neighbouring lanes (4 or 8).
@@ -213,13 +214,13 @@ __device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placeme
   u64 wide = pl.tile_wide ? kDescWide : 0;
   if (!s.direct && wave == 0 && tile >= u32(kChains)) {
     u64 own_wide = 0;
-    if (s.coherent || !own_chain_scalar(s.desc, tile, s.tag, own, own_wide)) {
-      const u64 v = chains_lookback(s.desc, tile, s.ctl, s.tag, kOwnChain);
+    if (s.coherent || !own_chain_scalar(s.desc, tile, s.tag, s.apart, own, own_wide)) {
+      const u64 v = chains_lookback(s.desc, tile, s.ctl, s.tag, s.apart, kOwnChain);
       own = u32(v);
       own_wide = v & kDescWide;
     }
     wide |= own_wide;
-    if (lane == 0) desc_store(s.desc, tile, kDescChain | wide | u64(u32(own + pl.tile_total)), s.tag);
+    if (lane == 0) desc_store(s.desc, tile, kDescChain | wide | u64(u32(own + pl.tile_total)), s.tag, s.apart);
   }
   meanwhile();
   // Nothing is before the first tile, and nobody waits at the barrier for its waves: 1000 sinusoid values compressed 5.9 us,
@@ -230,7 +231,7 @@ __device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placeme
     // words of the tiles before this one (a wave's share of them), and kDescWide if one of them, or this one, is wide
     const int l = fresh_lane();
     const int first = s.direct ? l + 64 * wave : l < kChains - 1 ? l : int(tile);
-    const u64 others = walk_back(s.desc, i32(tile) - 1 - first, s.direct ? 64 * WAVES : kChains, s.ctl, s.tag);
+    const u64 others = walk_back(s.desc, i32(tile) - 1 - first, s.direct ? 64 * WAVES : kChains, s.ctl, s.tag, s.apart);
     if (lane == 0) sh_base[wave] = u64(u32(own + u32(others))) | wide | (others & kDescWide);
   }
   lds_barrier();                // only sh_base passes through it
@@ -238,6 +239,18 @@ __device__ inline TileBase resolve_tile_base(const PayloadSink& s, const Placeme
   const u64 part = sh_base[lane_id() & (WAVES - 1)];      // (a lane per wave)
   const u32 words = uniform(group_sum<WAVES>(u32(part)));
   return TileBase{words, __any((part & kDescWide) != 0) || (wide & kDescWide) != 0};
+}
+
+// The same for a wave of the workgroup that has no segment to place: it takes its share of a direct look-back.
+template <int WAVES>
+__device__ inline void help_look_back(const PayloadSink& s, u32 tile, u64 (&sh_base)[WAVES], int wave) {
+  if (uniform(tile) == 0) return;
+  if (s.direct) {
+    const int l = fresh_lane();
+    const u64 others = walk_back(s.desc, i32(tile) - 1 - l - 64 * wave, 64 * WAVES, s.ctl, s.tag, s.apart);
+    if (l == 0) sh_base[wave] = others;
+  }
+  lds_barrier();
 }
 
 template <int WAVES>
@@ -255,6 +268,8 @@ __device__ inline void write_index_entry(const PayloadSink& s, u32 seg, u64 seg_
 // The last tile knows the size of the stream, and of an indexed one whether it holds wide blocks.
 // The last tile of a part of a stream that is produced in parts writes the same for the stream
 // so far: what has been produced is then a stream that can be read up to there.
+// WAVES: segments of a tile.
+template <int WAVES>
 __device__ inline void finish_stream(const PayloadSink& s, const Placement& pl, u32 tile, u32 ntiles, const TileBase& tb) {
   if ((tile == ntiles - 1 || tile + 1 == s.part_end) && threadIdx.x == 0) {
     const u64 words = tb.words + pl.tile_total;
@@ -268,7 +283,7 @@ __device__ inline void finish_stream(const PayloadSink& s, const Placement& pl, 
       hw[kHeaderBytes / 4 + num_segments(s.nb)] = u32(words);      // the closing entry of the index
       // the end of a part is where the next part's first segment will start: its entry, ahead of time,
       // lets the last segment of this part be checked and read before the next part exists
-      const u64 next_seg = u64(tile + 1) * (blockDim.x >> 6);
+      const u64 next_seg = u64(tile + 1) * WAVES;
       if (next_seg < num_segments(s.nb)) hw[kHeaderBytes / 4 + next_seg] = u32(words);
     }
   }
@@ -323,13 +338,14 @@ __device__ inline void copy_staged_wave(const PayloadSink& s, const Placement& p
 // Back half of a tile whose size is published, with the plane words in registers (`word(i)`: 0 = sign,
 // 1 + p = plane p): look back for the base offset, then move the payload out.  Called by every wave of
 // the workgroup; one barrier.
-template <int NW, int WAVES, typename WordFn>
+// SEGS: segments of a tile.
+template <int NW, int SEGS, int WAVES, typename WordFn>
 __device__ inline void finish_tile(const PayloadSink& s, WordFn word, const Placement& pl, u32 tile, u32 ntiles,
                                    u32* wl, u64 (&sh_base)[WAVES], int wave, int lane) {
   const TileBase tb = resolve_tile_base(s, pl, tile, sh_base, wave, lane);
-  if (lane == 0) write_index_entry(s, tile * (blockDim.x >> 6) + u32(wave), tb.words + pl.wave_off);
+  if (lane == 0) write_index_entry(s, tile * u32(SEGS) + u32(wave), tb.words + pl.wave_off);
   copy_wave_out<NW, true>(s, word, pl, tb.words, wl, lane);
-  finish_stream(s, pl, tile, ntiles, tb);
+  finish_stream<SEGS>(s, pl, tile, ntiles, tb);
 }
 
 }  // namespace zc

@@ -58,7 +58,9 @@ struct ReduceCall {
   u64 nsum;          // sum of the operands' nsum
   u64 wide_streams;  // bit s: operand s may have blocks wider than 15 bits
   u32 part_end;      // a reduce done in parts: one past the last tile of this part; else 0
-  u32 places;        // plain streams: lane s: payload word offset of the wave's segment in operand s
+  u32 places, ends;  // lane s: payload word offset of the wave's segment in operand s (0 if there is no such segment), and where it ends (indexed streams)
+  u64 base, bytes;   // lane s: where operand s is, and its buffer's size
+  bool ends_bad;     // indexed streams: the wave holds an end of the index, which some operand contradicts
   u32 nb, widths, firsts, payload;      // blocks of every stream, and where its width bytes, first codes and payload begin (all below 2^29)
 };
 
@@ -93,14 +95,20 @@ __device__ inline bool sum_looks_direct(const ReduceArgs& a, u32 ntiles) {
   return looks_direct(ntiles, a.k <= 3 ? kDirectTiles : kDirectTiles / 2, a.coherent != 0, a.end_tile);
 }
 
+__device__ inline PayloadSink sum_sink(const ReduceArgs& a, const ReduceCall& c, u32 ntiles, bool ix) {
+  return {a.out, a.out_cap, c.h.nb, a.ctl, a.desc, ix, a.coherent != 0, sum_looks_direct(a, ntiles), c.part_end, c.tag};
+}
+
 // Range screen and placement of a summed block inside its wave and tile, then the shared
 // back half.  mag[0..NP) = magnitude planes, sign = sign word, w = highest non-zero plane + 1;
 // `word(i)` hands out the sign word (i = 0) and plane i - 1, for at most NW words.
-template <int NW, int NP, typename WordFn>
-__device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const u32 (&mag)[NP], u32 sign, u32 w,
+// SEGS: segments of a tile; LOOK: waves that look back.
+template <int NW, int NP, int SEGS, int LOOK, typename WordFn>
+__device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const PayloadSink& sink, const u32 (&mag)[NP], u32 sign, u32 w,
                                  i64 outlier, bool active, u32 b, u32 tile, u32 ntiles, WordFn word, u32* wl,
-                                 u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], int wave, int lane, bool ix) {
+                                 u32 (&sh_wave_total)[SEGS], u64 (&sh_base)[LOOK], int wave, int lane) {
   const ParsedHeader& h = c.h;
+  const bool ix = sink.ix;
   const u64 tend = tables_end(h.nb, ix);
   if (!active) w = 0;
   u32 err = 0;
@@ -129,10 +137,9 @@ __device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const
   }
   lds_barrier();                // the wave totals; the stores above stay in flight
   sum_wave_totals(sh_wave_total, wave, ix, pl);
-  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, ix, a.coherent != 0, sum_looks_direct(a, ntiles), c.part_end, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
-  finish_tile<NW>(sink, word, pl, tile, ntiles, wl, sh_base, wave, lane);
+  finish_tile<NW, SEGS>(sink, word, pl, tile, ntiles, wl, sh_base, wave, lane);
 }
 
 // The same for a wave whose whole payload fits its staging area (kWholeStage words per wave):
@@ -141,10 +148,11 @@ __device__ inline void place_sum(const ReduceArgs& a, const ReduceCall& c, const
 // copy of the wave's words.
 constexpr int kWholeStage = 64 * 24;
 
-template <int NW, int NP, typename WordFn>
-__device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c, const u32 (&mag)[NP], u32 sign, u32 w,
+template <int NW, int NP, int SEGS, int LOOK, typename WordFn>
+__device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c, const PayloadSink& sink, const u32 (&mag)[NP], u32 sign, u32 w,
                                         i64 outlier, bool active, u32 b, u32 tile, u32 ntiles, WordFn word, u32* wl,
-                                        u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], int wave, int lane, bool ix) {
+                                        u32 (&sh_wave_total)[SEGS], u64 (&sh_base)[LOOK], int wave, int lane) {
+  const bool ix = sink.ix;
   static_assert(64 * NW <= kWholeStage, "a wave of widest blocks must fit the staging area");
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, ix);
@@ -179,20 +187,19 @@ __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c
   }
   lds_barrier();                // the wave totals (and the words above); the stores stay in flight
   sum_wave_totals(sh_wave_total, wave, ix, pl);
-  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, ix, a.coherent != 0, sum_looks_direct(a, ntiles), c.part_end, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
   const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane);
   const u64 cap_words = a.out_cap > tend ? (a.out_cap - tend) / 4 : 0;
   const u64 d0 = tb.words + pl.wave_off;
-  if (lane == 0) write_index_entry(sink, tile * kTileWaves + u32(wave), d0);
+  if (lane == 0) write_index_entry(sink, tile * u32(SEGS) + u32(wave), d0);
   u32* const dst = reinterpret_cast<u32*>(a.out + tend) + d0;
   const u64 room = cap_words > d0 ? cap_words - d0 : 0;
   const u32 limit = u64(pl.wave_total) < room ? pl.wave_total : u32(room);
   copy_staged_words<NW + 1, true>(wl, dst, limit, lane);
   wave_lds_sync();
   store_tables<kAccessOnce>(sink, b, w, i32(outlier));     // (the whole output stream is written with the non-temporal hint, see store_once)
-  finish_stream(sink, pl, tile, ntiles, tb);
+  finish_stream<SEGS>(sink, pl, tile, ntiles, tb);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -206,17 +213,7 @@ constexpr int kSumPlanes = 24;
 static_assert(64 * kSumPlanes <= kWholeStage && kWholeStage >= kWaveStage, "staging area of reduce_kernel");   // (planes 0..22 and the sign: 24 words)
 constexpr int kSumChunk = 4;
 
-// What a wave needs to know about one operand's share, loaded two operands ahead: the values
-// as they come from memory.  Nothing is computed from them where they are loaded, so that
-// no load has to be waited for there.
-struct OperandMeta {
-  u32 w;            // this lane's block width
-  u32 seg_off;                  // payload word offset of the wave's segment (uniform)
-  u32 seg_end;                  // indexed streams: the payload word offset at which the segment ends (uniform)
-  u32 payload_room;             // words between the start of the payload and the end of the caller's buffer (saturated)
-};
-
-// ... and after the scan of the widths: one operand ahead.
+// What a wave needs to know about one operand's share.
 struct OperandPlace {
   u32 w;            // this lane's block width (0 if the block must be skipped)
   u32 pick;         // LDS word index of this lane's sign word
@@ -234,60 +231,65 @@ __device__ inline i32 load_operand_outlier(const u8* base, const ReduceCall& c, 
   return i32(__builtin_amdgcn_raw_buffer_load_b32(bytes_from(base + c.firsts, 4u * c.nb), int(4u * b), 0, 0));
 }
 
+// The width of the lane's block (0 if there is no such block).
+__device__ inline u32 load_operand_width(const u8* base, const ReduceCall& c, u32 b) {
+  return u32(__builtin_amdgcn_raw_buffer_load_b8(bytes_from(base + c.widths, c.nb), int(b), 0, 0));
+}
+
 // Words between the start of the payload and the end of the caller's buffer, of a stream whose header is in order (saturated:
-// a stream's payload has at most 2^31 words).
+// a stream's payload has at most 2^31 words).  The payload is fenced in by that, which a validated stream does
+// not exceed (a 16-byte load may run up to 12 bytes past the stream's own end, inside the
+// buffer; nothing reads those words).
 __device__ inline u32 payload_room(u64 bytes, const ReduceCall& c) {
   const u64 room = (bytes - c.payload) >> 2;
   return u32(room >> 32) ? 0xffffffffu : u32(room);
 }
 
-// The tables of operand s for the wave's segment (seg: the same in every lane; b: the lane's block).
-// The payload is fenced in by the size of the caller's buffer, which a validated stream does
-// not exceed (a 16-byte load may run up to 12 bytes past the stream's own end, inside the
-// buffer; nothing reads those words).
-// An indexed stream (ix) has the segment's position in its own index, and its width bytes
-// behind that index (every stream of a validated call has the header's nb); a plain one's is known since the workgroup
-// started (`places`).
-__device__ inline OperandMeta load_operand_meta(int s, const StreamRef& in, const ReduceCall& c, u32 seg, u32 b, bool seg_live, bool ix) {
-  OperandMeta m;
+// Words of an operand's payload that load_operand_payload and stage_to_lds can bring in.
+constexpr int kStageLoads = 4;
+constexpr u32 kMostStaged = 256u * kStageLoads + 64u;
+
+// Where operand s has the wave's segment.  An indexed stream (ix) says so by itself, and how long the segment is, so that its
+// payload can be asked for before its widths are there; of a plain one only the start is known.  Everything here is the same in every lane.
+__device__ inline OperandPlace open_operand(int s, u64 bytes, const ReduceCall& c, bool ix, u32 most = kMostStaged) {
+  OperandPlace p;
+  const u32 seg_off = lane_value(c.places, s), room = payload_room(bytes, c);
+  const u32 mis = seg_off & 3u;
+  p.src0 = seg_off - mis;
+  p.room = seg_off <= room ? room - p.src0 : 0u;         // (the start is inside on a validated stream)
+  p.span = 0;
   if (ix) {
-    const u32x2_t ends = __builtin_amdgcn_raw_buffer_load_b64(bytes_from(in.base + kHeaderBytes + 4u * seg, seg_live ? 8u : 0u), 0, 0, 0);
-    m.seg_off = ends.x;
-    m.seg_end = ends.y;
-  } else {
-    m.seg_off = seg_live ? lane_value(c.places, s) : 0u;
-    m.seg_end = 0;
+    const u32 words = lane_value(c.ends, s) - seg_off;
+    if (mis <= p.room && words <= p.room - mis && words <= most - 3u) p.span = mis + words;      // (else place_operand finds that the widths say something else)
   }
-  m.w = u32(__builtin_amdgcn_raw_buffer_load_b8(bytes_from(in.base + c.widths, c.nb), int(b), 0, 0));
-  m.payload_room = payload_room(in.bytes, c);
-  return m;
+  p.w = p.pick = p.wcap = 0;
+  return p;
 }
 
+// ... and once the lane's block width is there.
 // `err`: an indexed stream is checked as it is used: the widths of the segment must add up to
 // what the index says, and no block may be wider than w_max (15 where the stream promised narrow
 // blocks, or where the caller has seen that there is no other).
-__device__ inline OperandPlace place_operand(const OperandMeta& m, bool ix, u32& err, u32 w_max = 15) {
-  OperandPlace p;
-  // the same in every lane, and long since loaded: into scalar registers, 32-bit arithmetic
-  const u32 seg_off = uniform(m.seg_off);
-  const u32 w = m.w > w_max ? 0u : m.w;        // plain streams: cannot happen here; keeps every LDS access in range
+__device__ inline void place_operand(OperandPlace& p, int s, u32 width, const ReduceCall& c, bool ix, u32& err, u32 w_max = 15) {
+  const u32 w = width > w_max ? 0u : width;    // plain streams: cannot happen here; keeps every LDS access in range
   const u32 words = psize_words(w);
   const u32 incl = wave_inclusive_sum(words);
   const u32 wave_total = lane_value(incl, 63);
-  // true on a validated stream
-  bool inside = seg_off <= m.payload_room && wave_total <= m.payload_room - seg_off;
-  if (ix && (__any(m.w > w_max) || uniform(m.seg_end) - seg_off != wave_total)) {
-    err |= status_bit(ZC_ERR_FORMAT);
-    inside = false;
-  }
+  const u32 seg_off = lane_value(c.places, s);
   const u32 mis = seg_off & 3u;
-  p.src0 = seg_off - mis;
-  p.room = m.payload_room - p.src0;
+  // true on a validated stream
+  bool inside = mis <= p.room && wave_total <= p.room - mis;
+  if (ix) {
+    inside = p.span == mis + wave_total;
+    if (__any(width > w_max) || lane_value(c.ends, s) - seg_off != wave_total) {
+      err |= status_bit(ZC_ERR_FORMAT);
+      inside = false;
+    }
+  }
   p.span = inside ? mis + wave_total : 0u;     // <= 3 + 64 * (1 + w_max)
   p.pick = mis + (incl - words);
   p.w = inside ? w : 0u;
   p.wcap = w_max > 15 && __any(p.w > 15) ? 24u : __any(p.w > 12) ? 16u : __any(p.w > 8) ? 12u : __any(p.w > 4) ? 8u : __any(p.w != 0) ? 4u : 0u;
-  return p;
 }
 
 // The operand's payload for this wave: 16 bytes per lane and load, all in flight together.
@@ -295,7 +297,6 @@ __device__ inline OperandPlace place_operand(const OperandMeta& m, bool ix, u32&
 // 16-byte aligned) and keeps that misalignment in LDS.  Four loads cover 1024 words; a wave
 // whose 64 blocks are all 15 bits wide can need up to three more words, which stage_to_lds
 // fetches on the spot.
-constexpr int kStageLoads = 4;
 struct OperandStage {
   uint4 v[kStageLoads];
 };
@@ -379,6 +380,12 @@ __device__ inline void grow_sum(u32 (&acc)[kSumPlanes], u32 top, u32 new_top) {
   }
 }
 
+// Planes that hold sums of a magnitude of at most `bound`, as many chunks as it takes.
+__device__ inline u32 planes_for(u32 bound) {
+  const u32 top = bound ? (32u - u32(__builtin_clz(bound)) + 1u + 3u) & ~3u : 0u;
+  return top > u32(kSumPlanes) ? u32(kSumPlanes) : top;
+}
+
 // Two's complement planes -> magnitude planes (in place), given the sign plane; tracks the width.
 template <int C>
 __device__ inline void sum_to_magnitude(u32 (&acc)[kSumPlanes], u32 sgn, u32& carry, u32& width, u32 top) {
@@ -421,8 +428,6 @@ struct ReduceShare {
 // The widest block that stream s may have: 31, but 15 if it promised narrow blocks.
 __device__ inline u32 width_limit(const ReduceCall& c, int s) { return (c.wide_streams >> s) & 1u ? 31u : 15u; }
 
-// Words of an operand's payload that load_operand_payload and stage_to_lds can bring in.
-constexpr u32 kMostStaged = 256u * kStageLoads + 64u;
 static_assert(kMostStaged + kSumPlanes <= u32(kWholeStage), "payload staging, and the reads behind its last word, must fit the wave's area");
 
 // Whether the wave's blocks fit the common path: the sums its accumulator, every operand's payload the staging.
@@ -448,50 +453,51 @@ __device__ inline bool fits_common_path(const ReduceArgs& a, const ReduceCall& c
   return !__any(unfit || reach >= 1u << (kSumPlanes - 1)) && wave_sum_u32(words) + 3u <= kMostStaged;
 }
 
-// The sum of a wave's blocks as planes: acc = magnitudes, sgn = sign plane, w = code length, outlier = sum of the
-// first codes.  `meta`: the tables of operand 0 if the workgroup asked for them early (`early`).
+// The sum of a wave's blocks as planes: acc = two's complement, `top` of them, outlier = sum of the first codes.
+// `width0`: the widths of operand 0 if the workgroup asked for them early (`early`).
 template <bool IX>
-__device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, OperandMeta meta,
-                                           bool early, u32* wl, u32 (&acc)[kSumPlanes], u32& sgn, u32& w, i64& outlier, u32& err) {
-  const ParsedHeader& h = c.h;
+__device__ __forceinline__ void sum_operands(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32 width0,
+                                             bool early, u32* wl, u32 (&acc)[kSumPlanes], u32& top, i64& outlier, u32& err) {
   const u32 w_max = c.wide_streams ? 31u : 15u;
   const u32 seg = share.seg;
-  const bool seg_live = share.live;
+  // What travels together: an operand's payload and first codes, and of an indexed one, whose segment is found without them,
+  // the widths; a plain one's widths a step ahead of the others.
   OperandPlace next;
   OperandStage stage;
-  i32 outlier_next;        // the outlier of the operand in `stage`: travels with the payload
+  i32 outlier_next;
+  u32 width_next = 0;
   // Where operands s, s + 1 and s + 2 are, asked for a step before it is needed (a scalar load on the spot is waited for,
   // with all LDS reads under way, three times an operand: Sum of 8 x 1024 values 12.4 us, now 12.0).
   StreamRef at0 = a.in[0], at1 = a.in[min(1, a.k - 1)], at2 = a.in[min(2, a.k - 1)];
   {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
-    if (early) {
-      if (b >= c.nb) meta.w = 0;
-      if (!IX) meta.seg_off = lane_value(c.places, 0);
-      if (!seg_live) meta.seg_off = meta.seg_end = 0;
-      meta.payload_room = payload_room(at0.bytes, c);
+    next = open_operand(0, at0.bytes, c, IX);
+    if (IX) {
+      width_next = load_operand_width(at0.base, c, b);
     } else {
-      meta = load_operand_meta(0, at0, c, seg, b, seg_live, IX);
+      u32 width = early ? width0 : load_operand_width(at0.base, c, b);
+      if (b >= c.nb) width = 0;
+      place_operand(next, 0, width, c, IX, err, w_max);
+      if (a.k > 1) width_next = load_operand_width(at1.base, c, b);
     }
-    next = place_operand(meta, IX, err, w_max);
-    if (a.k > 1) meta = load_operand_meta(1, at1, c, seg, b, seg_live, IX);
     stage = load_operand_payload(reinterpret_cast<const u32*>(at0.base + c.payload), next, lane);
     outlier_next = load_operand_outlier(at0.base, c, b);
   }
   // the ends of every operand's index, by the waves that hold them
-  if (IX && seg_live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
+  if (c.ends_bad) err |= status_bit(ZC_ERR_FORMAT);
 
   // ---- add the k operands' blocks in plane form; loads run ahead of the adds ----
 #pragma unroll
   for (int p = 0; p < kSumPlanes; ++p) acc[p] = 0;
-  u32 top = 0;
+  top = 0;
   u32 bound = 0;          // wave-uniform bound on |sum of deltas| so far (the true sums are below 2^23: see fits_common_path)
   outlier = 0;
   for (int s = 0; s < a.k; ++s) {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
-    const OperandPlace cur = next;
+    OperandPlace cur = next;
+    const u32 width = width_next;
     const StreamRef here = at0, ahead1 = at1, ahead2 = at2;
     at0 = at1;
     at1 = at2;
@@ -499,16 +505,21 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
     stage_to_lds(stage, cur, reinterpret_cast<const u32*>(here.base + c.payload), wl, lane);
     wave_lds_sync();
     outlier += i64(outlier_next);
+    if (IX) place_operand(cur, s, width, c, IX, err, w_max);
     if (s + 1 < a.k) {
-      next = place_operand(meta, IX, err, w_max);
-      if (s + 2 < a.k) meta = load_operand_meta(s + 2, ahead2, c, seg, b, seg_live, IX);
+      next = open_operand(s + 1, ahead1.bytes, c, IX);
+      if (IX) {
+        width_next = load_operand_width(ahead1.base, c, b);
+      } else {
+        place_operand(next, s + 1, width, c, IX, err, w_max);
+        if (s + 2 < a.k) width_next = load_operand_width(ahead2.base, c, b);
+      }
       stage = load_operand_payload(reinterpret_cast<const u32*>(ahead1.base + c.payload), next, lane);
       outlier_next = load_operand_outlier(ahead1.base, c, b);
     }
     if (cur.wcap) {
       bound += (1u << cur.wcap) - 1u;
-      u32 new_top = (32u - u32(__builtin_clz(bound)) + 1u + 3u) & ~3u;
-      if (new_top > u32(kSumPlanes)) new_top = kSumPlanes;
+      const u32 new_top = planes_for(bound);
       grow_sum<0>(acc, top, new_top);
       top = new_top;
       const u32* mine = wl + cur.pick;
@@ -519,8 +530,10 @@ __device__ __forceinline__ void sum_common(const ReduceArgs& a, const ReduceCall
     }
     wave_lds_sync();
   }
+}
 
-  // ---- back to sign + magnitude planes; new code length ----
+// Back to sign + magnitude planes; new code length.
+__device__ __forceinline__ void close_sum(u32 (&acc)[kSumPlanes], u32 top, u32& sgn, u32& w) {
   sgn = sign_plane<0>(acc, top);
   u32 carry = sgn;
   w = 0;
@@ -578,20 +591,19 @@ __device__ inline void magnitude_planes(u32 (&acc)[kAccPlanes], u32 s, u32 carry
   }
 }
 
-template <bool IX>
-__device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, u32* lds,
-                                        u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves]) {
+// One wave per segment of the tile; wl: its LDS.
+template <bool IX, int SEGS, int LOOK>
+__device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c, const PayloadSink& sink, u32 tile, u32 ntiles, u32* wl,
+                                        u32 (&sh_wave_total)[SEGS], u64 (&sh_base)[LOOK]) {
   const ParsedHeader& h = c.h;
   const u64 tend = tables_end(h.nb, IX);
   const int lane = fresh_lane();
   const int wave = wave_id();
-  u32* const wl = lds + wave * kWholeStage;
-  const u32 seg = tile * kTileWaves + u32(wave);           // a stream has at most 2^26 blocks
+  const u32 seg = tile * u32(SEGS) + u32(wave);            // a stream has at most 2^26 blocks
   const bool seg_live = seg < num_segments(h.nb);
   const u32 b = seg * kWaveBlocks + u32(lane);
   const bool active = b < h.nb;
-  if (IX && seg_live && !index_ends_consistent(a.in, a.k, h, seg) && lane == 0)
-    raise_status(a.ctl, c.tag, status_bit(ZC_ERR_FORMAT));
+  if (c.ends_bad && lane == 0) raise_status(a.ctl, c.tag, status_bit(ZC_ERR_FORMAT));
 
   u32 acc[kAccPlanes];
 #pragma unroll
@@ -610,20 +622,14 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
     if (bad_w) w = 0;
     const u32 words = psize_words(w);
     const u32 incl = wave_inclusive_sum(words);
-    u32 seg_off = 0;
+    const u32 seg_off = lane_value(c.places, s);
     bool fits = seg_live;
-    if (IX) {
-      // the segment's place by the stream's own index, which must agree with the widths
-      const u32* index = reinterpret_cast<const u32*>(base + kHeaderBytes);
-      const u32 seg_end = seg_live ? index[seg + 1] : 0u;
-      seg_off = seg_live ? index[seg] : 0u;
+    if (IX) {                                     // the stream's own index must agree with the widths
       const bool narrow_promised = (reinterpret_cast<const u32*>(base)[1] & 1u) == 0;
-      if (seg_end - seg_off != lane_value(incl, 63) || __any(bad_w) || (narrow_promised && __any(w > 15))) {
+      if (lane_value(c.ends, s) - seg_off != lane_value(incl, 63) || __any(bad_w) || (narrow_promised && __any(w > 15))) {
         if (lane == 0) raise_status(a.ctl, c.tag, status_bit(ZC_ERR_FORMAT));
         fits = false;
       }
-    } else if (seg_live) {
-      seg_off = lane_value(c.places, s);
     }
     // (cannot fail on a validated stream) the segment lies inside the payload
     if (!fits || seg_off > pw || lane_value(incl, 63) > pw - seg_off) w = 0;
@@ -648,20 +654,21 @@ __device__ inline void reduce_wide_tile(const ReduceArgs& a, const ReduceCall& c
     if constexpr (I == 0) return ext;
     else return acc[I - 1];
   };
-  place_sum<32>(a, c, acc, ext, w, outlier, active, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave, lane, IX);
+  place_sum<32>(a, c, sink, acc, ext, w, outlier, active, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave, lane);
 }
 
 // One tile on the common path.
 template <bool IX>
-__device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, const OperandMeta& meta,
-                                          bool early, u32* lds, u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves]) {
+__device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall& c, u32 tile, u32 ntiles, u32 width0, bool early, u32* lds,
+                                          u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves]) {
   const int wave = wave_id();
   u32* const wl = lds + wave * kWholeStage;
   const u32 seg = tile * kTileWaves + u32(wave);
   const ReduceShare share{seg, seg < num_segments(c.h.nb)};
-  u32 acc[kSumPlanes], sgn, w, err = 0;
+  u32 acc[kSumPlanes], top, sgn, w, err = 0;
   i64 outlier;
-  sum_common<IX>(a, c, share, meta, early, wl, acc, sgn, w, outlier, err);
+  sum_operands<IX>(a, c, share, width0, early, wl, acc, top, outlier, err);
+  close_sum(acc, top, sgn, w);
   auto word = [&](auto i) {
     constexpr int I = decltype(i)::value;        // 0: sign, 1 + p: plane p
     if constexpr (I == 0) return sgn;
@@ -670,51 +677,44 @@ __device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall&
   const int lane = fresh_lane();
   const u32 b = seg * kWaveBlocks + u32(lane);
   if (IX && err && lane == 0) raise_status(a.ctl, c.tag, err);
-  place_sum_staged<kSumPlanes>(a, c, acc, sgn, w, outlier, b < c.h.nb, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave,
-                               lane, IX);
+  place_sum_staged<kSumPlanes>(a, c, sum_sink(a, c, ntiles, IX), acc, sgn, w, outlier, b < c.h.nb, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave,
+                               lane);
 }
 
 // What every workgroup of a reduce kernel does first: the call's verdict, tag and header, and its tile.
 // Returns false when the workgroup has nothing (more) to do.  The headers, and the width tables of plain streams, are
 // judged here, by every workgroup alike.
-// `meta`, `early`: see sum_common.
-template <bool IX>
-__device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMeta& meta, bool early, u32& tile, u32& ntiles,
+// The segments' places in all operands are found here too.  `width0`, `early`: see sum_common.
+// SEGS: segments of a tile, wave i of the workgroup on segment i % SEGS of its tile; TICKETS: tiles may be handed out by tickets.
+template <bool IX, int SEGS = kTileWaves, bool TICKETS = true>
+__device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& width0, bool early, u32& tile, u32& ntiles,
                                    u32* sh_tile, PlainSurvey<IX ? 1 : ZC_MAX_K>* survey) {
-  c.ltag = launch_tag(a.nonce, a.ctl);
+  const StreamRef any = lane_stream(a.in);   // (before the other arguments are there)
+  __builtin_amdgcn_sched_barrier(0);
   // (with tickets the ticket is asked for first of all: its round trip runs beside the headers')
   u64 asked = 0;
-  if (a.ticketed && threadIdx.x == 0) asked = ask_ticket(ticket_counter(a.ctl, ticket_shard()));
+  if (TICKETS && a.ticketed && threadIdx.x == 0) asked = ask_ticket(ticket_counter(a.ctl, ticket_shard()));
   const int wave = wave_id();
   tile = a.first_tile + blockIdx.x;          // tiles in the order in which workgroups start
+  u32 seg = tile * u32(SEGS) + u32(wave % SEGS);     // < 2^22: the host launches at most 2^18 tiles of four
   SurveyLoads ask{};
-  if (!IX) ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
+  if (!IX) ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg, wave);
   if (early) {
-    const u32 seg = tile * kTileWaves + u32(wave);      // < 2^22: the host launches at most 2^18 tiles
     const u32 b = seg * kWaveBlocks + u32(fresh_lane());
-    const u8* base = a.in[0].base;
-    const u32 zero = opaque_zero();
-    meta.seg_off = meta.seg_end = 0;
-    if (IX) {
-      // the caller has said what n is (a reduce in parts): where the first operand's tables are follows from
-      // that, and they are asked for together with the headers; a stream of another n ends the call below
-      const u32 nb_said = u32(num_blocks(a.n_part));
-      const bool seg_ok = seg < num_segments(nb_said) && u64(kHeaderBytes) + 4ull * seg + 8 <= a.in[0].bytes;
-      const bool w_ok = b < nb_said && widths_begin(nb_said, true) + b < a.in[0].bytes;
-      if (seg_ok) {
-        meta.seg_off = load_segment_offset(base, seg, zero);
-        meta.seg_end = load_segment_end(base, seg, zero);
-      }
-      meta.w = w_ok ? u32(*at_bytes(base, u32(widths_begin(nb_said, true)) + b + zero)) : 0u;
-    } else {
-      meta.w = u64(kHeaderBytes) + b < a.in[0].bytes ? u32(*at_bytes(base, kHeaderBytes + b)) : 0u;
-    }
+    const StreamRef first = a.in[0];
+    width0 = u64(kHeaderBytes) + b < first.bytes ? u32(*at_bytes(first.base, kHeaderBytes + b)) : 0u;
   }
-  StreamsVerdict v = judge_headers<IX>(a.in, a.k, true);
+  LaneStream in = ask_headers<IX>(any, a.k, seg);
+  // (the tag, some 100 dependent scalar instructions, while the loads are on their way)
+  c.ltag = launch_tag(a.nonce, a.ctl);
+  asm volatile("" : "+s"(c.ltag));
+  StreamsVerdict v = judge_headers<IX>(in, a.k, true);
   // (a later part of a reduce done in parts belongs to the call its first part opened)
   c.tag = call_tag(a.ctl, c.ltag, a.adopt != 0);
   c.places = 0;
-  if (!IX) c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
+  if (!IX) c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg / kTileWaves, wave, ask, v, *survey, kTileWaves, int(seg % kTileWaves));
+  c.base = in.base;
+  c.bytes = in.bytes;
   c.h = v.h0;
   c.nb = u32(c.h.nb);
   c.widths = u32(widths_begin(c.h.nb, IX));
@@ -736,7 +736,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
     }
     return false;
   }
-  ntiles = u32(num_tiles(c.h.nb));
+  ntiles = (u32(num_segments(c.h.nb)) + u32(SEGS) - 1) / u32(SEGS);
   const u32 end_tile = a.end_tile && a.end_tile < ntiles ? a.end_tile : ntiles;
   c.part_end = a.end_tile ? end_tile : 0u;
   if (blockIdx.x == 0 && threadIdx.x == 0 && a.first_tile == 0) write_reduce_header(a, c, ntiles, IX);
@@ -746,17 +746,32 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, OperandMe
     return false;
   }
   if (a.first_tile >= end_tile) return false;
-  if (a.ticketed) {                          // ... or handed out by tickets, see take_tile
+  if (TICKETS && a.ticketed) {                          // ... or handed out by tickets, see take_tile
     if (threadIdx.x == 0) {
       const u32 t = take_tile(a.ctl, c.ltag, end_tile - a.first_tile, ticket_shard(), asked);
       *sh_tile = t == kNoTile ? kNoTile : a.first_tile + t;
     }
     __syncthreads();
     tile = uniform(*sh_tile);
+    seg = tile * u32(SEGS) + u32(wave % SEGS);
     if (!IX && tile < end_tile) {            // (the verdict stands: once more, for the place of this tile)
-      ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile * kTileWaves + u32(wave), wave);
-      c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, tile, wave, ask, v, *survey);
+      ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg, wave);
+      c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg / kTileWaves, wave, ask, v, *survey, kTileWaves, int(seg % kTileWaves));
     }
+    if (IX) in = ask_headers<IX>(any, a.k, tile < end_tile ? seg : 0u);
+  }
+  const u32 nseg = u32(num_segments(c.h.nb));
+  const bool live = seg < nseg;
+  if (IX) {
+    const int lane = lane_id();
+    c.places = live ? in.begin : 0u;
+    c.ends = live ? in.end : 0u;
+    // the ends of every operand's index, by the waves that hold them (see index_ends_ok)
+    c.ends_bad = __any(lane < a.k && ((seg == 0 && c.places != 0) || (seg + 1 == nseg && u64(c.payload) + 4 * u64(c.ends) != v.mine.total)));
+  } else {
+    if (!live) c.places = 0;
+    c.ends = 0;
+    c.ends_bad = false;
   }
   return tile < end_tile;
 }
@@ -776,14 +791,15 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
 
   ReduceCall c;
-  OperandMeta meta{};
-  // A workgroup that takes the tile of its own number asks for the first operand's tables
+  u32 width0 = 0;
+  // A workgroup that takes the tile of its own number asks for the first operand's widths
   // together with the headers, before it knows them: one memory
   // round trip instead of two.  The loads are fenced in by sizes the host passed.  (Not for
-  // indexed streams: where their width bytes are is only known with the header.)
-  const bool early = !a.ticketed && (!IX || a.n_part != 0);
+  // indexed streams: where their width bytes are is only known with the header.  But where their segments are is, see
+  // ask_segment_ends, and with that the widths and the payload are asked for together.)
+  const bool early = !a.ticketed && !IX;
   u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, c, meta, early, tile, ntiles, &sh_tile, &survey)) return;
+  if (!open_reduce<IX>(a, c, width0, early, tile, ntiles, &sh_tile, &survey)) return;
   // The segment number stays a scalar: in a vector register, with all the addresses that follow from it, it made the
   // kernel spill in the operand loops.  (Plain streams of nothing but wide blocks, 4 x 4 194 301 values: 43.7 us, now
   // 41.0; 16 x 100 003 hard values 33.6 and 32.2; 8 x 2^24 smooth ones 53.6 and 52.9.)  What the waves ask for two
@@ -805,8 +821,8 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
     common = uniform(all) != 0;
     lds_barrier();                     // the words are used again
   }
-  if (common) reduce_common_tile<IX>(a, c, tile, ntiles, meta, early, lds, sh_wave_total, sh_base);
-  else reduce_wide_tile<IX>(a, c, tile, ntiles, lds, sh_wave_total, sh_base);
+  if (common) reduce_common_tile<IX>(a, c, tile, ntiles, width0, early, lds, sh_wave_total, sh_base);
+  else reduce_wide_tile<IX>(a, c, sum_sink(a, c, ntiles, IX), tile, ntiles, lds + wave_id() * kWholeStage, sh_wave_total, sh_base);
 }
 
 }  // namespace zc

@@ -22,11 +22,11 @@
 // than 15 bits does so from the start, in all its waves (extreme_any).
 // Measured, 8 x 2^24 values unless said otherwise, first with codes unpacked throughout (145 registers, three waves
 // per SIMD, and a kernel of its own for wide blocks, launched with every call), then now:
-//   smooth field, bound 1e-4 of its range                     79.5   58.5 us
+//   smooth field, bound 1e-4 of its range                     79.5   56.0 us
 //   8 x 2^23 (1024 tiles)                                     36.2   32.9
-//   16 x 2^20                                                 29.7   24.8
+//   16 x 2^20                                                 29.7   24.4
 //   hard data, 4 x 4 000 000                                  28.2   15.6
-//   8 x 1000                                                  18.7   14.9
+//   8 x 1000                                                  18.7   12.8
 // (the last four: before payloads went straight to LDS and loads were trimmed, see OperandPipe and load_operand_meta).
 // 122 registers, four waves per SIMD, and 12 bytes of scratch that only the
 // wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
@@ -37,6 +37,7 @@
 #include "zc_bitmatrix.h"
 #include "zc_common.h"
 #include "zc_decompress.h"
+#include "zc_lds_words.h"
 #include "zc_place.h"
 #include "zc_reduce.h"
 #include "zc_scan.h"
@@ -72,23 +73,23 @@ struct ExtremeBlock {
 
 // The lane's sign and plane words out of what lies in its wave's staging area from the sign word on: lo[0..15) = planes
 // 0..14, lo[15] = sign word (what is not the block's own is dropped: see pick_block_words).
-__device__ inline void keep_operand_words(const OperandPlace& cur, const u32 (&t)[16], u32 (&lo)[16]) {
+__device__ inline void keep_operand_words(u32 w, const u32 (&t)[16], u32 (&lo)[16]) {
   const u32 sign = t[0];
-  const u32 keep = cur.w ? (1u << cur.w) - 1u : 0u;      // bit p: the block has plane p
+  const u32 keep = w ? (1u << w) - 1u : 0u;      // bit p: the block has plane p
 #pragma unroll
   for (int p = 0; p < 15; ++p) {
     // (the AND spelled out: seen as one, it is compiled into a test and a selection per plane)
     const u32 m = u32(__builtin_amdgcn_sbfe(i32(keep), u32(p), 1u));
     lo[p] = __builtin_amdgcn_bitop3_b32(t[1 + p], m, m, 0xC0);
   }
-  lo[15] = cur.w ? sign : 0u;
+  lo[15] = w ? sign : 0u;
 }
 
 // The deltas of the lane's block, fields as transpose16x16_pairs leaves them (word j: deltas j and j + 16), from the words
 // that were read from its wave's staging area, in place.
-__device__ inline void operand_delta_pairs(const OperandPlace& cur, u32 (&f)[16]) {
-  if (!__any(cur.w > 7)) {                     // byte fields: word j = deltas j, j + 8, j + 16, j + 24
-    keep_operand_words(cur, f, f);
+__device__ inline void operand_delta_pairs(u32 w, u32 (&f)[16]) {
+  if (!__any(w > 7)) {                     // byte fields: word j = deltas j, j + 8, j + 16, j + 24
+    keep_operand_words(w, f, f);
     u32 r[8];
 #pragma unroll
     for (int p = 0; p < 7; ++p) r[p] = f[p];
@@ -105,7 +106,7 @@ __device__ inline void operand_delta_pairs(const OperandPlace& cur, u32 (&f)[16]
 #pragma unroll
     for (int p = 0; p < 15; ++p) f[p] = f[p + 1];
     f[15] = sign;
-    deltas_from_raw_planes16(f, cur.w);
+    deltas_from_raw_planes16(f, w);
   }
 }
 
@@ -115,6 +116,8 @@ __device__ inline void operand_delta_pairs(const OperandPlace& cur, u32 (&f)[16]
 // straight to LDS, where a wave has two areas: while operand s is decoded, s + 1 and, as soon as the words of s have
 // been read from their area, s + 2 are on their way (63.8 us; 16 x 2^20 29.5 -> 25.6; 8 x 1024, a string of round trips,
 // 17.6 -> 15.7).
+// What a round needs to ask for an operand's share comes from lane s of values worked out for all operands at once (LaneOperands), and an indexed
+// stream's payload is asked for by its index alone, with the widths and first codes: 8 x 2^24 values 58.7 -> 56.0, 16 x 1000 23.6 -> 20.9.
 // Each round ends with the four loads to LDS of operand s + 2 and has no other memory access behind them, so that
 // "all but the newest four" is what a round waits for at its start; none of the round's loads is behind a branch
 // (behind the last operand the range of a load is empty).  The words are read by instructions of our own: ordinary reads
@@ -124,62 +127,72 @@ static_assert(kOperandArea >= 1027 + 16 && kOperandArea % 4 == 0, "an operand's 
 constexpr u32 kExtremeStage = 2 * kOperandArea;
 static_assert(kExtremeStage >= u32(kWaveStage), "the output is staged in the same place");
 
-typedef __attribute__((address_space(3))) u32 LdsWord;
-__device__ inline u32 lds_address(const u32* p) { return u32(reinterpret_cast<uintptr_t>((const LdsWord*)p)); }
+// What a wave knows about an operand's blocks once their widths are there.
+struct PipeOperand {
+  u32 w, pick;              // the lane's block: its width, and where its sign word lies in the operand's area
+  u32 bytes, span;          // uniform: what is asked for, and the words that the segment takes
+  bool tail;                // uniform: the one leaves out some of the other
+};
 
 template <bool IX>
 struct OperandPipe {
-  OperandPlace cur, next, ahead;           // operands s (whose words have been read), s + 1 and s + 2
+  LaneOperands o;
+  PipeOperand cur, next, ahead;            // operands s (whose words have been read), s + 1 and s + 2
   i32 first, first_next, first_ahead;      // the first code of the lane's block in them
-  OperandMeta meta;                        // operand s + 3
+  // The width of the lane's block: in operands s, s + 1 and s + 2 (indexed streams, whose segments are found without it), or in s + 3
+  u32 width, width_next, width_ahead;
 
-  // Where operands s ... s + 3 are, asked for a step before it is needed (behind the last operand: the last one).
-  StreamRef at0, at1, at2, at3;
-
-  __device__ __forceinline__ static OperandMeta load_meta(const ReduceArgs& a, const StreamRef& in, const ReduceCall& c, const ReduceShare& share,
-                                                          int s, u32 b) {
-    return load_operand_meta(min(s, a.k - 1), in, c, share.seg, b, share.live, IX);
+  // What to ask for of operand s (nothing behind the last one); of a plain stream its widths have to be there.
+  __device__ __forceinline__ void open_ahead(PipeOperand& p, int k, int s, u32 blocks_width, u32& err) {
+    const int of = min(s, k - 1);
+    if (IX) {
+      p.bytes = lane_value(o.bytes, of);
+    } else {
+      place(p, of, blocks_width, err);
+      const u32 room = lane_value(o.room, of), pieces = (p.span + 3u) & ~3u, whole = min(pieces, room & ~3u);
+      p.bytes = 4u * whole;
+      p.tail = pieces != whole || p.span > 256u * kStageLoads;
+    }
+    if (s >= k) p.bytes = 0;
   }
-  __device__ __forceinline__ static OperandPlace place(const ReduceArgs& a, int s, const OperandMeta& m, u32& err) {
-    u32 bad = 0;
-    OperandPlace p = place_operand(m, IX, bad);
-    if (s < a.k) err |= bad;
-    else p.span = 0;
-    return p;
-  }
-  // The operand's payload for this wave, from the 16-byte boundary at or below its segment on, into `area`: whole 16-byte
-  // pieces inside the caller's buffer only (the rest: see take).  All 1024 words of the area are written.
-  __device__ __forceinline__ static void ask_payload(const StreamRef& in, const ReduceCall& c, const OperandPlace& p, u32* area, int lane) {
-    const u32 whole = min((p.span + 3u) & ~3u, p.room & ~3u);
-    const __amdgpu_buffer_rsrc_t share = bytes_from(in.base + c.payload + 4 * u64(p.src0), 4u * whole);
-#pragma unroll
-    for (int i = 0; i < kStageLoads; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(share, (LdsWord*)(area + 256 * i), 16, 16 * lane + 1024 * i, 0, 0, kAccessOnce);
-  }
-  // Nothing moves across this line.
-  __device__ __forceinline__ static void line() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
+  // See place_operand.
+  __device__ __forceinline__ void place(PipeOperand& p, int s, u32 blocks_width, u32& err) {
+    const u32 words = psize_words(blocks_width), incl = wave_inclusive_sum(words), total = lane_value(incl, 63);     // (at most 64 x 256)
+    const u32 shape = lane_value(o.shape, s);
+    p.span = (shape & 3u) + total;
+    p.pick = (shape & 3u) + incl - words;
+    p.w = blocks_width;
+    if (IX) p.tail = ((o.tails >> s) & 1u) != 0;
+    if (__any(blocks_width > 15) || (IX ? total != shape >> 2 : p.span > lane_value(o.room, s))) {      // uniform
+      if (IX) err |= status_bit(ZC_ERR_FORMAT);
+      p.w = p.span = 0;
+      p.tail = false;
+    }
   }
 
   __device__ __forceinline__ void open(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl, u32& err) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    at0 = a.in[0];
-    at1 = a.in[min(1, a.k - 1)];
-    at2 = a.in[min(2, a.k - 1)];
-    at3 = a.in[min(3, a.k - 1)];
-    const OperandMeta m0 = load_meta(a, at0, c, share, 0, b), m1 = load_meta(a, at1, c, share, 1, b);
-    meta = load_meta(a, at2, c, share, 2, b);
-    first = load_operand_outlier(at0.base, c, b);
-    first_next = load_operand_outlier(at1.base, c, b);
-    line();
-    cur = place(a, 0, m0, err);
-    ask_payload(at0, c, cur, wl, lane);
-    line();
-    next = place(a, 1, m1, err);
-    ask_payload(at1, c, next, wl + kOperandArea, lane);
-    line();
+    o = lane_operands<IX>(c);
+    width = load_width(a, c, 0, b);
+    width_next = load_width(a, c, 1, b);
+    if (!IX) width_ahead = load_width(a, c, 2, b);
+    first = load_first(a, c, 0, b);
+    first_next = load_first(a, c, 1, b);
+    lds_words_line();
+    open_ahead(cur, a.k, 0, width, err);
+    ask_payload_to_lds(o, 0, cur.bytes, wl, lane);
+    lds_words_line();
+    u32 bad = 0;
+    open_ahead(next, a.k, 1, width_next, bad);
+    ask_payload_to_lds(o, min(1, a.k - 1), next.bytes, wl + kOperandArea, lane);
+    lds_words_line();
+  }
+  __device__ __forceinline__ u32 load_width(const ReduceArgs& a, const ReduceCall& c, int s, u32 b) const {
+    return u32(__builtin_amdgcn_raw_buffer_load_b8(widths_buffer(o, c, min(s, a.k - 1), true), int(b), 0, 0));
+  }
+  __device__ __forceinline__ i32 load_first(const ReduceArgs& a, const ReduceCall& c, int s, u32 b) const {
+    return i32(__builtin_amdgcn_raw_buffer_load_b32(outliers_buffer(o, c, min(s, a.k - 1), true), int(4u * b), 0, 0));
   }
   // The words of operand s from its lanes' sign words on, and operand s + 2 on its way.  Operands in turn from 0 on.
   __device__ __forceinline__ void take(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32* wl, u32 (&t)[16], u32& err) {
@@ -190,53 +203,32 @@ struct OperandPipe {
       first = first_next;
       next = ahead;
       first_next = first_ahead;
-      at0 = at1;
-      at1 = at2;
-      at2 = at3;
-      at3 = a.in[min(s + 3, a.k - 1)];
+      if (IX) {
+        width = width_next;
+        width_next = width_ahead;
+      }
     }
-    line();
-    asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    if (cur.span > 1024u || ((cur.span + 3u) & ~3u) > cur.room) {      // uniform, and rare: words 1024 .. 1026, or the buffer ends inside a 16-byte piece
-      asm volatile("");                        // (keeps the branch)
-      const u32 whole = min((cur.span + 3u) & ~3u, min(cur.room & ~3u, 1024u));
-      const u32 i = whole + u32(lane);
-      if (i < min(cur.span, cur.room))
-        area[i] = reinterpret_cast<const u32*>(at0.base + c.payload)[cur.src0 + i];
+    lds_words_line();
+    wait_all_but<kStageLoads>();
+    if (IX) place(cur, s, width, err);
+    if (cur.tail) {                            // uniform, and rare
+      fetch_payload_end(o, s, cur.bytes, cur.span, area, lane);
       wave_lds_sync();
     }
     const u32 at = lds_address(area) + 4u * (cur.w ? cur.pick : 0u);
-    u64 v[8];
-    asm volatile(
-        "s_waitcnt lgkmcnt(0)\n\t"
-        "ds_read2_b32 %0, %8 offset0:0 offset1:1\n\t"
-        "ds_read2_b32 %1, %8 offset0:2 offset1:3\n\t"
-        "ds_read2_b32 %2, %8 offset0:4 offset1:5\n\t"
-        "ds_read2_b32 %3, %8 offset0:6 offset1:7\n\t"
-        "ds_read2_b32 %4, %8 offset0:8 offset1:9\n\t"
-        "ds_read2_b32 %5, %8 offset0:10 offset1:11\n\t"
-        "ds_read2_b32 %6, %8 offset0:12 offset1:13\n\t"
-        "ds_read2_b32 %7, %8 offset0:14 offset1:15\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(at)
-        : "memory");
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      t[2 * i] = u32(v[i]);
-      t[2 * i + 1] = u32(v[i] >> 32);
-    }
+    read_lds_words<0>(at, t);
+    read_lds_words<8>(at, t);
     // operand s + 2, in the place of operand s
-    ahead = place(a, s + 2, meta, err);
+    open_ahead(ahead, a.k, s + 2, width_ahead, err);
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    first_ahead = load_operand_outlier(at2.base, c, b);
-    meta = load_meta(a, at3, c, share, s + 3, b);
-    line();
-    ask_payload(at2, c, ahead, area, lane);
-    line();
+    first_ahead = load_first(a, c, s + 2, b);
+    width_ahead = load_width(a, c, s + (IX ? 2 : 3), b);
+    lds_words_line();
+    ask_payload_to_lds(o, min(s + 2, a.k - 1), ahead.bytes, area, lane);
+    lds_words_line();
   }
   // Behind the last operand: what is still on its way (empty ranges, which leave zeros) has landed.
-  __device__ __forceinline__ void close() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+  __device__ __forceinline__ void close() { wait_all_but<0>(); }
 };
 
 // The common path keeps codes as 16-bit code - base + bias, where base is the first code of one of the operands'
@@ -290,12 +282,12 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceC
     const bool far = apart + u32(kNearFirst) >= u32(2 * kNearFirst);
     const u32 start = ((far ? 0u : apart) + u32(kCodeBias<OP>)) & 0xffffu;
     // f, word j: the deltas, and then the codes, j and j + 16
-    if (pipe.cur.wcap == 0) {                  // nothing but constant blocks: every code is the block's first
+    if (!__any(pipe.cur.w != 0)) {                  // nothing but constant blocks: every code is the block's first
       const u32 both = start | (start << 16);
 #pragma unroll
       for (int j = 0; j < 16; ++j) f[j] = both;
     } else {
-      operand_delta_pairs(pipe.cur, f);
+      operand_delta_pairs(pipe.cur.w, f);
       // both halves of the block at once, the second one from zero; then it gets what the first one ends with
       f[0] = add_pairs(f[0], start);
 #pragma unroll
@@ -411,7 +403,7 @@ __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCa
     }
     if (++s >= a.k) return;
     pipe.take(a, c, share, s, wl, f, err);
-    operand_delta_pairs(pipe.cur, f);
+    operand_delta_pairs(pipe.cur.w, f);
   }
 }
 
@@ -450,27 +442,25 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
                                             i32 (&acc)[32], u32& err) {
 #pragma unroll
   for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
-  OperandMeta meta;
-  {
-    meta = load_operand_meta(0, a.in[0], c, share.seg, share.seg * kWaveBlocks + u32(fresh_lane()), share.live, IX);
-  }
+  u32 width = load_operand_width(a.in[0].base, c, share.seg * kWaveBlocks + u32(fresh_lane()));
 #pragma nounroll
   for (int s = 0; s < a.k; ++s) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
     const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + c.payload);
-    const OperandPlace cur = place_operand(meta, IX, err, width_limit(c, s));
+    OperandPlace cur = open_operand(s, a.in[s].bytes, c, IX, 3 + 64 * 32);
+    place_operand(cur, s, width, c, IX, err, width_limit(c, s));
     u32 code = u32(load_operand_outlier(a.in[s].base, c, b));
     if (!__any(cur.w > 15)) {
       const OperandStage stage = load_operand_payload(payload, cur, lane);
-      if (s + 1 < a.k) meta = load_operand_meta(s + 1, a.in[s + 1], c, share.seg, b, share.live, IX);
+      if (s + 1 < a.k) width = load_operand_width(a.in[s + 1].base, c, b);
       stage_to_lds(stage, cur, payload, wl, lane);
       wave_lds_sync();
       u32 f[16];
       const u32* const mine = wl + (cur.w ? cur.pick : 0u);
 #pragma unroll
       for (int p = 0; p < 16; ++p) f[p] = mine[p];
-      keep_operand_words(cur, f, f);
+      keep_operand_words(cur.w, f, f);
       wave_lds_sync();
       magnitude_planes_to_twos<16>(f);
       transpose16x16_pairs(f);
@@ -480,7 +470,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
         acc[j] = extreme<OP>(acc[j], i32(code));
       }
     } else {
-      if (s + 1 < a.k) meta = load_operand_meta(s + 1, a.in[s + 1], c, share.seg, b, share.live, IX);
+      if (s + 1 < a.k) width = load_operand_width(a.in[s + 1].base, c, b);
       u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
@@ -519,16 +509,15 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
 
   ReduceCall c;
-  OperandMeta meta{};
-  u32 tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, c, meta, false, tile, ntiles, &sh_tile, &survey)) return;
+  u32 width0 = 0, tile = 0, ntiles = 0;
+  if (!open_reduce<IX>(a, c, width0, false, tile, ntiles, &sh_tile, &survey)) return;
   const ParsedHeader& h = c.h;
   const int wave = wave_id();
   u32* const wl = lds + wave * kExtremeStage;
   const u32 seg = uniform(tile * kTileWaves + u32(wave));
   const ReduceShare share{seg, seg < num_segments(h.nb)};
   u32 err = 0;
-  if (IX && share.live && !index_ends_consistent(a.in, a.k, h, seg)) err |= status_bit(ZC_ERR_FORMAT);
+  if (c.ends_bad) err |= status_bit(ZC_ERR_FORMAT);
 
   ExtremeBlock eb;
   i32 codes[32];
@@ -584,7 +573,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
     }, pl, tb.words, wl, lane);
   }
   store_tables<kAccessOnce>(sink, b, pl.w, eb.outlier);     // (at the very end: a store under way is waited for by every poll of the look-back)
-  finish_stream(sink, pl, tile, ntiles, tb);
+  finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
 }
 
 }  // namespace zc

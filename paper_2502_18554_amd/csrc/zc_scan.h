@@ -201,7 +201,7 @@ __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
 // ---------------------------------------------------------------------------------------
 
 // Verdict on the k <= 64 input streams of a call, from their headers alone.  Lane s of the
-// calling wave reads and judges the header of stream s, so that all headers are in flight at
+// calling wave reads (ask_headers) and judges the header of stream s, so that all headers are in flight at
 // once; every wave of every workgroup comes to the same verdict.
 struct StreamsVerdict {
   ParsedHeader h0;      // header of stream 0 (uniform)
@@ -212,20 +212,67 @@ struct StreamsVerdict {
   ParsedHeader mine;    // lane s: header of stream s
 };
 
+// What a wave asks for before it knows anything about the streams: in lane s stream s itself (the arguments have room for ZC_MAX_K
+// of them, so that this does not wait for k, which is in the arguments too), then its header and, of an indexed one, where the wave's
+// segment lies in its payload, as its own index says: the entries sit right behind the header, whatever n is.  Lanes from k on ask for
+// stream 0 once more, and for entries outside the caller's buffer comes the header: no load is behind a branch, and nothing that is asked
+// for later may go ahead of them.
+__device__ inline StreamRef lane_stream(const StreamRef* streams) { return streams[lane_id()]; }
+struct LaneStream {
+  uint4 lo, hi;         // the header
+  u64 base, bytes;      // (at least kHeaderBytes: the host has checked)
+  u32 begin, end;       // the segment's two entries
+};
 template <bool IX>
-__device__ inline StreamsVerdict judge_headers(const StreamRef* streams, int k, bool check_match) {
+__device__ inline LaneStream ask_headers(const StreamRef& any, int k, u32 seg) {      // any = lane_stream(streams)
+  const int lane = lane_id();
+  const uint64_t base = reinterpret_cast<uint64_t>(any.base);
+  const u64 base0 = u64(lane_value(u32(base), 0)) | (u64(lane_value(u32(base >> 32), 0)) << 32);
+  const u64 bytes0 = u64(lane_value(u32(any.bytes), 0)) | (u64(lane_value(u32(any.bytes >> 32), 0)) << 32);
+  const u64 from = lane < k ? base : base0;
+  LaneStream l;
+  l.base = from;
+  l.bytes = lane < k ? any.bytes : bytes0;
+  // (said to be global memory, see ask_plain_streams)
+  typedef const __attribute__((address_space(1))) u32x4_t Global;
+  const u32x4_t lo = reinterpret_cast<Global*>(from)[0], hi = reinterpret_cast<Global*>(from)[1];
+  l.lo = make_uint4(lo.x, lo.y, lo.z, lo.w);
+  l.hi = make_uint4(hi.x, hi.y, hi.z, hi.w);
+  l.begin = l.end = 0;
+  if (IX) {
+    typedef const __attribute__((address_space(1))) u32 GlobalWord;
+    const u64 at = u64(kHeaderBytes) + 4 * u64(seg);
+    GlobalWord* const p = reinterpret_cast<GlobalWord*>(from + (at + 8 <= l.bytes ? at : 0));
+    l.begin = p[0];
+    l.end = p[1];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  return l;
+}
+
+// The headers alone, where they are judged.  (The decompression of several streams asks for its own stream's header and segment
+// first: with these headers ahead of that 8 x 2^26 values took 469 us, behind it 457.)
+__device__ inline LaneStream read_headers(const StreamRef* streams, int k) {
+  LaneStream l{};
+  const int lane = lane_id();
+  if (lane < k) {
+    l.bytes = streams[lane].bytes;
+    const uint4* src = reinterpret_cast<const uint4*>(streams[lane].base);
+    l.lo = src[0];
+    l.hi = src[1];
+  }
+  return l;
+}
+
+template <bool IX>
+__device__ inline StreamsVerdict judge_headers(const LaneStream& asked, int k, bool check_match) {
   const int lane = lane_id();
   const bool mine = lane < k;
-  u32 w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  u64 bytes = 0;
-  if (mine) {
-    bytes = streams[lane].bytes;                       // >= kHeaderBytes: the host has checked
-    const uint4* src = reinterpret_cast<const uint4*>(streams[lane].base);
-    const uint4 lo = src[0], hi = src[1];
-    w[0] = lo.x; w[1] = lo.y; w[2] = lo.z; w[3] = lo.w;
-    w[4] = hi.x; w[5] = hi.y; w[6] = hi.z; w[7] = hi.w;
-  }
-  const ParsedHeader h = parse_header_words(w, bytes, IX);
+  const u64 bytes = asked.bytes;
+  const u32 w[8] = {asked.lo.x, asked.lo.y, asked.lo.z, asked.lo.w, asked.hi.x, asked.hi.y, asked.hi.z, asked.hi.w};
+  ParsedHeader h = parse_header_words(w, bytes, IX);
+  h.ok = mine && h.ok;
+  if (!mine) h.nb = 0;
   StreamsVerdict v;
   v.mine = h;
   v.h0.n = u64(lane_value(u32(h.n), 0)) | (u64(lane_value(u32(h.n >> 32), 0)) << 32);
@@ -463,16 +510,16 @@ __device__ inline u32 lanes_to_rows(u32 v) {
 
 // The lists of spans of a call in rows, for `sh`: four streams a wave and round.  blocks: lane s: of stream s (none from stream k on).
 template <int K>
-__device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 blocks, u32 tile, int wave, const SurveyLoads& ask, PlainSurvey<K>& sh) {
+__device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 blocks, u32 tile, int wave, u32 waves, const SurveyLoads& ask, PlainSurvey<K>& sh) {
   const u32 lane = u32(lane_id());
   uint4 next = ask.v[0];
   u32 s = row_stream(k, wave);
   u32 nspans = (u32(__builtin_amdgcn_ds_bpermute(int(4u * s), int(blocks))) + kSpanBlocks - 1) / kSpanBlocks;
 #pragma nounroll
-  for (u32 s0 = 4u * u32(wave); s0 < u32(k); s0 += 4u * kTileWaves) {
+  for (u32 s0 = 4u * u32(wave); s0 < u32(k); s0 += 4u * waves) {
     const uint4 first = next;
     const u32 here = s, spans_here = nspans;
-    s = (s + 4u * kTileWaves) & 63u;           // (asked for ahead of time; beyond the last stream nothing comes of it)
+    s = (s + 4u * waves) & 63u;           // (asked for ahead of time; beyond the last stream nothing comes of it)
     nspans = (u32(__builtin_amdgcn_ds_bpermute(int(4u * s), int(blocks))) + kSpanBlocks - 1) / kSpanBlocks;
     next = load_spans(index, s, nspans, 4u * (lane & 15u));
     const RowOfSpans r = sum_row_of_spans(index, here, spans_here, tile, first);
@@ -484,11 +531,11 @@ __device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 bl
   }
 }
 
-// Called by all waves of a workgroup of kTileWaves waves; at most one barrier.  `v`: the verdict on the headers, completed here (err,
-// wide).  Returns, in lane s, the payload word offset of the wave's segment, kTileWaves * tile + wave, in stream s.
+// Called by all `waves` waves of a workgroup; at most one barrier.  `v`: the verdict on the headers, completed here (err,
+// wide).  Returns, in lane s, the payload word offset of the wave's segment, kTileWaves * tile + in_tile, in stream s.
 template <int K, bool ROWS>
 __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int k, const StreamIndex& index, bool self, u32 tile, int wave,
-                                          const SurveyLoads& ask, StreamsVerdict& v, PlainSurvey<K>& sh) {
+                                          const SurveyLoads& ask, StreamsVerdict& v, PlainSurvey<K>& sh, u32 waves = kTileWaves, int in_tile = wave_id() % kTileWaves) {
   const int lane = lane_id();
   const u32 parts = survey_parts(k, self);
   const bool mine = lane < k;
@@ -510,9 +557,9 @@ __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int
   } else {
     SurveyLoads loads = ask;
     const bool rows = ROWS && !self;
-    if (rows) sum_spans_by_rows(index, k, fits ? u32(v.mine.nb) : 0u, tile, wave, ask, sh);
+    if (rows) sum_spans_by_rows(index, k, fits ? u32(v.mine.nb) : 0u, tile, wave, waves, ask, sh);
 #pragma nounroll
-    for (u32 u = u32(wave); !rows && u < u32(k) * parts; u += kTileWaves) {
+    for (u32 u = u32(wave); !rows && u < u32(k) * parts; u += waves) {
       const u32 s = u / parts, p = u % parts;
       const u32 nb = lane_value(u32(fits), int(s)) ? lane_value(u32(v.mine.nb), int(s)) : 0u;
       u32 before = 0, total = 0, seen = 0;
@@ -562,7 +609,7 @@ __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int
         total += sh.total[u32(lane) * parts + p];
         seen |= sh.seen[u32(lane) * parts + p];
       }
-      off += self ? sh.in_tile[4 * lane + wave] : ask.v[1].x;
+      off += self ? sh.in_tile[4 * lane + in_tile] : ask.v[1].x;
     }
   }
   if (__any(mine && v.mine.ok && !fits)) v.err |= status_bit(ZC_ERR_ARG);

@@ -630,7 +630,7 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
                                      reinterpret_cast<u32*>(a.out + tend) + dst, cap_words > dst ? cap_words - dst : 0, ignored);
   }
   store_tables<0>(sink, b, pl.w, outlier);
-  finish_stream(sink, pl, tile, ntiles, tb);
+  finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
 }
 
 }  // namespace zc
