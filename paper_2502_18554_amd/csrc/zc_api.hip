@@ -92,6 +92,14 @@ u32 index_grid(u64 tiles) { return u32(((tiles + 15) / 16 + kIndexGroups - 1) / 
 
 ReportSlots g_reports;
 
+// Status, tag and size of a call, and `count` further words.
+int read_answer(const u64* host, size_t* result, u32 count, u64* more_out) {
+  if (result) *result = size_t(host[2]);
+  for (u32 i = 0; i < count; ++i) more_out[i] = host[3 + i];
+  // status bits count only under the tag of the last call
+  return status_from_bits((host[0] >> 32) == (host[1] >> 32) ? u32(host[0]) : 0u);
+}
+
 // Waits for the call and fetches its status and size; `more` further words (the streams' n) travel along.
 // may_pin: the caller has not ruled out allocations.
 int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = true, const u64* const* more = nullptr, u32 count = 0,
@@ -101,11 +109,37 @@ int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = 
   u64 host[kReportWords];
   for (u32 i = 0; i < count; ++i) from[3 + i] = more[i];
   if (!report_words(g_reports, from, 3 + count, host, may_pin, stream)) return ZC_ERR_HIP;
-  if (result) *result = size_t(host[2]);
-  for (u32 i = 0; i < count; ++i) more_out[i] = host[3 + i];
-  // status bits count only under the tag of the last call
-  return status_from_bits((host[0] >> 32) == (host[1] >> 32) ? u32(host[0]) : 0u);
+  return read_answer(host, result, count, more_out);
 }
+
+// The answer to a call whose main kernel gives it itself, if it may: somebody waits, the launch is one workgroup and the stream runs.
+// (With an error of an earlier call still to be told, a failed launch could not be told from it, and the slot not be given back.)
+class CallAnswer {
+ public:
+  CallAnswer(bool wanted, u64 groups, hipStream_t stream, bool may_pin = true) {
+    if (!wanted || groups != 1 || hipPeekAtLastError() != hipSuccess || !stream_runs(stream)) return;
+    slot_ = g_reports.take(may_pin);
+    if (slot_) seq_ = g_reports.next_seq();
+  }
+  Answer arg() const { return {slot_, seq_}; }
+  // The launches are enqueued (or not).  See finish.
+  int collect(bool launched, const void* d_ws, size_t* result, hipStream_t stream, bool wanted, bool may_pin = true, const u64* const* more = nullptr,
+              u32 count = 0, u64* more_out = nullptr) {
+    if (!launched) {
+      if (slot_) g_reports.give_back(slot_);
+      return ZC_ERR_HIP;
+    }
+    if (!wanted) return ZC_OK;
+    if (!slot_) return finish(d_ws, result, stream, may_pin, more, count, more_out);
+    u64 host[kReportWords];
+    if (!await_words(g_reports, slot_, seq_, 3 + count, host, stream)) return ZC_ERR_HIP;
+    return read_answer(host, result, count, more_out);
+  }
+
+ private:
+  ReportSlot* slot_ = nullptr;
+  u64 seq_ = 0;
+};
 
 // Plain input streams of up to `tiles` tiles, most likely no more than `likely`: whether the main kernel is to sum their
 // width tables itself (see judge_plain_streams); if not, their positions are computed ahead of it.  Either way is right
@@ -206,6 +240,7 @@ void fill_compress_args(CompressArgs& ca, const float* d_in, u64 n, float abs_eb
   ca.part_end = 0;
   ca.adopt = 0;
   ca.nonce = call_nonce();
+  ca.answer = {};
 }
 
 // The launch of zc_compress / zc_compress_part over the tiles [first_tile, end_tile) of the stream.
@@ -290,8 +325,8 @@ int zc_finish(const void* d_ws, size_t* result, void* hip_stream) {
   return finish(d_ws, result, static_cast<hipStream_t>(hip_stream), may_pin);
 }
 
-int zc_compress_ex(const float* d_in, size_t n, float abs_eb, void* d_out, size_t out_cap, size_t* out_bytes,
-                   void* d_ws, size_t ws_bytes, void* hip_stream, unsigned flags) {
+static int compress_impl(const float* d_in, size_t n, float abs_eb, void* d_out, size_t out_cap, size_t* out_bytes, void* d_ws,
+                         size_t ws_bytes, void* hip_stream, unsigned flags, bool may_pin) {
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   if (!flags_valid(flags) || !eb_valid(abs_eb) || n > ZC_MAX_N || (n && !d_in) || !d_out || !d_ws) return ZC_ERR_ARG;
   if (!aligned16(d_in) || !aligned16(d_out) || !aligned16(d_ws)) return ZC_ERR_ARG;
@@ -300,10 +335,16 @@ int zc_compress_ex(const float* d_in, size_t n, float abs_eb, void* d_out, size_
   if (l.tiles_cap < 1 || num_tiles(nb) > l.tiles_cap) return ZC_ERR_ARG;
   CompressArgs ca;
   fill_compress_args(ca, d_in, n, abs_eb, d_out, out_cap, l, flags);
-  launch_compress(ca, 0, u32(num_pack_tiles(nb)), true, stream);
-  if (!launch_ok()) return ZC_ERR_HIP;
-  if (!out_bytes) return ZC_OK;
-  return finish(d_ws, out_bytes, stream);
+  const u64 tiles = num_pack_tiles(nb);
+  CallAnswer answer(out_bytes != nullptr, tiles, stream, may_pin);
+  ca.answer = answer.arg();
+  launch_compress(ca, 0, u32(tiles), true, stream);
+  return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr, may_pin);
+}
+
+int zc_compress_ex(const float* d_in, size_t n, float abs_eb, void* d_out, size_t out_cap, size_t* out_bytes,
+                   void* d_ws, size_t ws_bytes, void* hip_stream, unsigned flags) {
+  return compress_impl(d_in, n, abs_eb, d_out, out_cap, out_bytes, d_ws, ws_bytes, hip_stream, flags, true);
 }
 
 int zc_compress(const float* d_in, size_t n, float abs_eb, void* d_out, size_t out_cap, size_t* out_bytes,
@@ -318,9 +359,7 @@ int zc_compress_noalloc(const float* d_in, size_t n, float abs_eb, void* d_out, 
   if (!ws) return ZC_ERR_HIP;
   // nothing in a workspace needs clearing (every call tags what it shares), so what the
   // previous call left in the array does not matter
-  const int st = zc_compress_ex(d_in, n, abs_eb, d_out, out_cap, nullptr, ws, kScratchBytes, hip_stream, 0);
-  if (st != ZC_OK || !out_bytes) return st;
-  return finish(ws, out_bytes, static_cast<hipStream_t>(hip_stream), false);
+  return compress_impl(d_in, n, abs_eb, d_out, out_cap, out_bytes, ws, kScratchBytes, hip_stream, 0, false);
 }
 
 int zc_compress_part(const float* d_in, size_t n, float abs_eb, size_t first_value, size_t count, void* d_out,
@@ -385,6 +424,8 @@ static int decompress_one(const void* d_in, size_t in_bytes, size_t first_value,
   da.first_value = first_value;
   da.count = count;
   da.nonce = call_nonce();
+  CallAnswer answer(n_out && !ranged, grid, stream);
+  da.answer = answer.arg();
   if (ranged) {
     void (*kernel)(DecompressArgs) = ix ? decompress_range_kernel<true, false> : self ? decompress_range_kernel<false, true> : decompress_range_kernel<false, false>;
     hipLaunchKernelGGL(kernel, dim3(u32(grid)), dim3(kTileThreads), 0, stream, da);
@@ -392,9 +433,7 @@ static int decompress_one(const void* d_in, size_t in_bytes, size_t first_value,
     void (*kernel)(DecompressArgs) = average ? pick_decompress_kernel<true>(ix, self) : pick_decompress_kernel<false>(ix, self);
     launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(grid)), dim3(kTileThreads), stream, da);
   }
-  if (!launch_ok()) return ZC_ERR_HIP;
-  if (!n_out) return ZC_OK;
-  return finish(d_ws, n_out, stream);
+  return answer.collect(launch_ok(), d_ws, n_out, stream, n_out != nullptr);
 }
 
 int zc_decompress_ex(const void* d_in, size_t in_bytes, float* d_out, size_t out_cap_elems, size_t* n_out,
@@ -452,14 +491,15 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   da.nonce = call_nonce();
   void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false, false> : self ? decompress_many_kernel<false, true, false>
                                          : k > kManyByWave ? decompress_many_kernel<false, false, true> : decompress_many_kernel<false, false, false>;
+  CallAnswer answer(n_out != nullptr, tiles * u64(k), stream);
+  da.answer = answer.arg();
   launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(tiles), u32(k)), dim3(kTileThreads), stream, da);
-  if (!launch_ok()) return ZC_ERR_HIP;
-  if (!n_out) return ZC_OK;
   // every header that passes validation holds its stream's n: fetch them along with the status
   const u64* heads[ZC_MAX_K];
   u64 ns[ZC_MAX_K];
   for (int i = 0; i < k; ++i) heads[i] = reinterpret_cast<const u64*>(static_cast<const u8*>(d_chunks[i]) + 8);
-  const int st = finish(d_ws, nullptr, stream, true, heads, u32(k), ns);
+  const int st = answer.collect(launch_ok(), d_ws, nullptr, stream, n_out != nullptr, true, heads, u32(k), ns);
+  if (!n_out) return st;
   if (st == ZC_ERR_HIP || st == ZC_ERR_ARG || st == ZC_ERR_FORMAT) return st;
   for (int i = 0; i < k; ++i) n_out[i] = size_t(ns[i]);
   return st;
@@ -527,23 +567,22 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     ra.n_part = n;
     tiles = ra.end_tile - ra.first_tile;
   }
+  void (*kernel)(ReduceArgs) = ix ? reduce_kernel<true> : reduce_kernel<false>;
   if (op == ZC_OP_SUM) {
     const int segs = ranged || ra.ticketed ? 0 : few_segments(k, likely);
-    void (*kernel)(ReduceArgs) = ix ? reduce_kernel<true> : reduce_kernel<false>;
     if (segs == 1) kernel = ix ? reduce_few_kernel<true, 1, 4> : reduce_few_kernel<false, 1, 4>;
     else if (segs == 2) kernel = ix ? reduce_few_kernel<true, 2, 4> : reduce_few_kernel<false, 2, 4>;
     else if (segs == 4 && likely <= kFewTiles) kernel = ix ? reduce_few_kernel<true, 4, 4> : reduce_few_kernel<false, 4, 4>;
     else if (segs == 4 && ix) kernel = reduce_few_kernel<true, 4, 2>;
     if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
-    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
   } else {
-    void (*kernel)(ReduceArgs) = op == ZC_OP_MAX ? (ix ? reduce_op_kernel<true, ZC_OP_MAX> : reduce_op_kernel<false, ZC_OP_MAX>)
-                                                 : (ix ? reduce_op_kernel<true, ZC_OP_MIN> : reduce_op_kernel<false, ZC_OP_MIN>);
-    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
+    kernel = op == ZC_OP_MAX ? (ix ? reduce_op_kernel<true, ZC_OP_MAX> : reduce_op_kernel<false, ZC_OP_MAX>)
+                             : (ix ? reduce_op_kernel<true, ZC_OP_MIN> : reduce_op_kernel<false, ZC_OP_MIN>);
   }
-  if (!launch_ok()) return ZC_ERR_HIP;
-  if (!out_bytes) return ZC_OK;
-  return finish(d_ws, out_bytes, stream);
+  CallAnswer answer(out_bytes && !ranged, tiles, stream);
+  ra.answer = answer.arg();
+  launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
+  return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr);
 }
 
 int zc_reduce_compressed_op(const void* const* d_chunks, const size_t* chunk_bytes, int k, int op, void* d_out, size_t out_cap,
@@ -624,10 +663,10 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, self, tickets, tiles);
   else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, self, tickets, tiles);
   else kernel = pick_step_kernel<ZC_OP_MIN>(ix, self, tickets, tiles);
+  CallAnswer answer(out_bytes && !ranged, tiles, stream);
+  ta.answer = answer.arg();
   launch_main(ZC_KERNEL_REDUCE_STEP, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ta);
-  if (!launch_ok()) return ZC_ERR_HIP;
-  if (!out_bytes) return ZC_OK;
-  return finish(d_ws, out_bytes, stream);
+  return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr);
 }
 
 int zc_reduce_step_op(const void* d_chunk, size_t chunk_bytes, const float* d_local, size_t n_local, int op, void* d_out,

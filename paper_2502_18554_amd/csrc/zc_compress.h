@@ -13,6 +13,7 @@
 #include "zc_bitmatrix.h"
 #include "zc_common.h"
 #include "zc_place.h"
+#include "zc_report.h"
 
 namespace zc {
 
@@ -44,6 +45,7 @@ struct CompressArgs {
   u32 part_end;      // zc_compress_part: one past the last tile of this call; else 0
   u32 adopt;         // this launch continues a call (a later part): its tag is in the control block
   u64 nonce;         // drawn by the host per call, goes into the tag (see launch_tag)
+  Answer answer;
 };
 
 // Round-to-nearest-even of r for |r| < 2^31 as the low word of r + 1.5 * 2^52.
@@ -265,12 +267,8 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
 // load_raw); as a launch of its own behind the full tiles it cost 7 us per call on any input that is not
 // a multiple of 16384 values (20 000 003 values, compress and decompress: 59.0 us, now 51.9).
 template <bool TICKETS>
-__global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kPackWaves * kWaveStage];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kPackWaves];
-  __shared__ u64 sh_base[kPackWaves];
-
+__device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_tile, u32 end_tile, u32 (&lds)[kPackWaves * kWaveStage], u32& sh_tile,
+                                             u32 (&sh_wave_total)[kPackWaves], u64 (&sh_base)[kPackWaves]) {
   const int lane = lane_id();
   const int wave = wave_id();
   u32 tile = first_tile + blockIdx.x;        // tiles in the order in which workgroups start
@@ -363,6 +361,16 @@ __global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs 
     }
   }
   if (err) raise_status(a.ctl, tag, err);
+}
+
+template <bool TICKETS>
+__global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kPackWaves * kWaveStage];
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[kPackWaves];
+  __shared__ u64 sh_base[kPackWaves];
+  compress_tile<TICKETS>(a, first_tile, end_tile, lds, sh_tile, sh_wave_total, sh_base);
+  give_answer(a.answer, a.ctl);
 }
 
 // The stream of no values: a header (and the one closing entry of an indexed stream's index).

@@ -27,6 +27,7 @@
 
 #include "zc_common.h"
 #include "zc_place.h"
+#include "zc_report.h"
 #include "zc_scan.h"
 
 namespace zc {
@@ -47,6 +48,7 @@ struct ReduceArgs {
   // [first_tile, end_tile) of the output, end_tile = 0 meaning all of them; a later part
   // (adopt) belongs to the call whose tag the first part left in the control block.
   u32 first_tile, end_tile, adopt;
+  Answer answer;
   u64 n_part;        // a reduce done in parts: the n the caller laid the parts out for (the streams must have it); else 0
 };
 
@@ -783,14 +785,8 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
 // 80 registers and 24 bytes of scratch (plain streams: 96 and 28), which the common path touches behind its
 // operand loop only: what the placement needs waits there.
 template <bool IX>
-__global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage + kCopyOver];   // also holds an operand's payload
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base[kTileWaves];
-  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
-
-  ReduceCall c;
+__device__ __forceinline__ void reduce_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kTileWaves * kWholeStage + kCopyOver], u32& sh_tile,
+                                            u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
   u32 width0 = 0;
   // A workgroup that takes the tile of its own number asks for the first operand's widths
   // together with the headers, before it knows them: one memory
@@ -823,6 +819,18 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   }
   if (common) reduce_common_tile<IX>(a, c, tile, ntiles, width0, early, lds, sh_wave_total, sh_base);
   else reduce_wide_tile<IX>(a, c, sum_sink(a, c, ntiles, IX), tile, ntiles, lds + wave_id() * kWholeStage, sh_wave_total, sh_base);
+}
+
+template <bool IX>
+__global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage + kCopyOver];   // also holds an operand's payload
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[kTileWaves];
+  __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
+  ReduceCall c;
+  reduce_tile<IX>(a, c, lds, sh_tile, sh_wave_total, sh_base, survey);
+  give_answer(a.answer, a.ctl);
 }
 
 }  // namespace zc

@@ -501,14 +501,8 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
 }
 
 template <bool IX, int OP>
-__global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kExtremeStage];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base[kTileWaves];
-  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
-
-  ReduceCall c;
+__device__ __forceinline__ void reduce_op_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kTileWaves * kExtremeStage], u32& sh_tile,
+                                               u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
   u32 width0 = 0, tile = 0, ntiles = 0;
   if (!open_reduce<IX>(a, c, width0, false, tile, ntiles, &sh_tile, &survey)) return;
   const ParsedHeader& h = c.h;
@@ -574,6 +568,18 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   }
   store_tables<kAccessOnce>(sink, b, pl.w, eb.outlier);     // (at the very end: a store under way is waited for by every poll of the look-back)
   finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
+}
+
+template <bool IX, int OP>
+__global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kExtremeStage];
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[kTileWaves];
+  __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
+  ReduceCall c;
+  reduce_op_tile<IX, OP>(a, c, lds, sh_tile, sh_wave_total, sh_base, survey);
+  give_answer(a.answer, a.ctl);
 }
 
 }  // namespace zc

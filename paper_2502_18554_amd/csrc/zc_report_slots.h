@@ -61,6 +61,31 @@ class ReportSlots {
   std::atomic<uint64_t> seq_{0};
 };
 
+// Whether `stream` can be told to be running what is enqueued on it (not while it is being captured).
+inline bool stream_runs(hipStream_t stream) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(stream, &capture) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  return known && capture == hipStreamCaptureStatusNone;
+}
+
+// Waits for the answer to request `seq`, which something enqueued on `stream` stores in `slot`, and gives the slot back.
+inline bool await_words(ReportSlots& slots, ReportSlot* slot, uint64_t seq, uint32_t count, uint64_t* to, hipStream_t stream) {
+  // Polled for the length of a large call, then left to the runtime, which also knows when no answer can come.
+  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(500);
+  auto answered = [&] { return __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq; };
+  bool there = false;
+  for (uint32_t polls = 1; !(there = answered()); ++polls) {
+    __builtin_ia32_pause();
+    if ((polls & 63u) == 0 && std::chrono::steady_clock::now() > until) break;
+  }
+  if (!there) there = hipStreamSynchronize(stream) == hipSuccess && answered();
+  if (!there) return false;      // (with its slot: what was enqueued may still write there, if the GPU comes to it)
+  for (uint32_t i = 0; i < count; ++i) to[i] = __atomic_load_n(&slot->words[i], __ATOMIC_RELAXED);
+  slots.give_back(slot);
+  return true;
+}
+
 // The words at from[0 .. count) as they are when everything enqueued on `stream` so far has run.  `make`: see take.
 // launch(slot, seq): enqueues on `stream` what stores the words, and then seq, in the slot; false: nothing was enqueued.
 template <typename LaunchFn>
@@ -88,19 +113,7 @@ inline bool report_words(ReportSlots& slots, const uint64_t* const* from, uint32
     slots.give_back(slot);
     return false;
   }
-  // Polled for the length of a large call, then left to the runtime, which also knows when no answer can come.
-  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(500);
-  auto answered = [&] { return __atomic_load_n(&slot->seq, __ATOMIC_ACQUIRE) == seq; };
-  bool there = false;
-  for (uint32_t polls = 1; !(there = answered()); ++polls) {
-    __builtin_ia32_pause();
-    if ((polls & 63u) == 0 && std::chrono::steady_clock::now() > until) break;
-  }
-  if (!there) there = hipStreamSynchronize(stream) == hipSuccess && answered();
-  if (!there) return false;      // (with its slot: what was enqueued may still write there, if the GPU comes to it)
-  for (uint32_t i = 0; i < count; ++i) to[i] = __atomic_load_n(&slot->words[i], __ATOMIC_RELAXED);
-  slots.give_back(slot);
-  return true;
+  return await_words(slots, slot, seq, count, to, stream);
 }
 
 }  // namespace zc

@@ -54,6 +54,7 @@ struct StepArgs {
   // of the output, end_tile = 0 meaning all of them; a later part (adopt) belongs to the call whose
   // tag the first part left in the control block.
   u32 first_tile, end_tile, adopt;
+  Answer answer;
 };
 
 // LDS of one wave: 64 rows (blocks) of 16 local values + 4 words of padding (an odd number of
@@ -346,13 +347,9 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
 // would not hold the other form: a round of 1000 values 6.73 us with it, 6.59 without, 100 003 sinusoids 6.69 and 6.54, 2^22 hard values
 // 13.50 and 13.29; but 2^24 values of a plain stream 32.2 and 33.1.
 constexpr u32 kStepMany = 8 * 256;        // tiles
-template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5>
-__global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage + kCopyOver];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base[kTileWaves];
-  __shared__ PlainSurvey<1> survey;
+template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS>
+__device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWaves * kStepStage + kCopyOver], u32& sh_tile, u32 (&sh_wave_total)[kTileWaves],
+                                         u64 (&sh_base)[kTileWaves], PlainSurvey<1>& survey) {
   constexpr bool FOURS = TICKETS || GROUPS > 5 || !(IX || SELF);
 
   const int lane = lane_id();
@@ -631,6 +628,17 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) 
   }
   store_tables<0>(sink, b, pl.w, outlier);
   finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
+}
+
+template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5>
+__global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage + kCopyOver];
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[kTileWaves];
+  __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<1> survey;
+  step_tile<IX, SELF, OP, TICKETS, GROUPS>(a, lds, sh_tile, sh_wave_total, sh_base, survey);
+  give_answer(a.answer, a.ctl);
 }
 
 }  // namespace zc

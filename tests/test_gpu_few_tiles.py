@@ -278,3 +278,31 @@ def test_sums_of_few_tiles(zcref, stream_variant, k, tiles, wide):
         broken[u.widths_begin(nb) + at] = (int(broken[u.widths_begin(nb) + at]) + 1) % 31
     assert zcref.reduce(refs[:-1] + [broken])[0] == ZC_ERR_FORMAT
     assert u.gpu_reduce(refs[:-1] + [broken], n)[0] == ZC_ERR_FORMAT
+
+
+# calls of one workgroup that somebody waits for: the main kernel itself gives the answer, also to a call that fails
+@pytest.mark.parametrize("n", [1, 31, 2049, 8192])
+def test_calls_of_one_workgroup_answer_themselves(zcref, n):
+    u = gpuutil
+    x = synth.sinusoids(n, seed=3).numpy()
+    st_ref, ref = zcref.compress(x, 1e-3)[:2]
+    for _ in range(3):                               # (the slots of the answers before hold their words)
+        st, s, total = u.gpu_compress(x, 1e-3)
+        assert st == st_ref == ZC_OK and total == ref.size and s.tobytes() == ref.tobytes()
+        assert u.gpu_compress(x, 1e-3, out_cap=ref.size - 4)[0] == ZC_ERR_CAPACITY
+        want = zcref.decompress(ref)[1]
+        st, y, got = u.gpu_decompress(ref, n)
+        assert st == ZC_OK and got == n and np.array_equal(y.view(np.uint32), want.view(np.uint32))
+        st, ys, ns = u.gpu_decompress_many([ref], [n])
+        assert st == ZC_OK and ns == [n] and np.array_equal(ys[0][:n].view(np.uint32), want.view(np.uint32))
+        assert u.gpu_decompress(ref, n, in_bytes=ref.size - 1)[0] == ZC_ERR_FORMAT
+        want = zcref.reduce_step(ref, x)[1]
+        st, s, total = u.gpu_reduce_step(ref, x)
+        assert st == ZC_OK and total == want.size and s.tobytes() == want.tobytes()
+        bad = x.copy()
+        bad[n // 2] = np.nan
+        assert u.gpu_reduce_step(ref, bad)[0] == zcref.reduce_step(ref, bad)[0] == u.gpu_compress(bad, 1e-3)[0]
+        for op in (None, 1):
+            want = zcref.reduce([ref], op=op or 0)[1]
+            st, s, total = u.gpu_reduce([ref], n, op=op)
+            assert st == ZC_OK and total == want.size and s.tobytes() == want.tobytes()
