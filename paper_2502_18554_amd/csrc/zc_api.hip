@@ -286,6 +286,12 @@ void (*pick_step_kernel(bool ix, bool self, bool tickets, u64 tiles))(StepArgs) 
   if (self) return tickets ? step_kernel<false, true, OP, true> : step_kernel<false, true, OP, false>;
   return tickets ? step_kernel<false, false, OP, true> : step_kernel<false, false, OP, false>;
 }
+template <int OP>
+void (*pick_op_kernel(bool ix, int segs))(ReduceArgs) {
+  if (segs == 1) return ix ? reduce_op_kernel<true, OP, 1> : reduce_op_kernel<false, OP, 1>;
+  if (segs == 2) return ix ? reduce_op_kernel<true, OP, 2> : reduce_op_kernel<false, OP, 2>;
+  return ix ? reduce_op_kernel<true, OP> : reduce_op_kernel<false, OP>;
+}
 template <bool AVERAGE>
 void (*pick_decompress_kernel(bool ix, bool self))(DecompressArgs) {
   return ix ? decompress_kernel<true, false, AVERAGE> : self ? decompress_kernel<false, true, AVERAGE> : decompress_kernel<false, false, AVERAGE>;
@@ -576,8 +582,9 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     else if (segs == 4 && ix) kernel = reduce_few_kernel<true, 4, 2>;
     if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
   } else {
-    kernel = op == ZC_OP_MAX ? (ix ? reduce_op_kernel<true, ZC_OP_MAX> : reduce_op_kernel<false, ZC_OP_MAX>)
-                             : (ix ? reduce_op_kernel<true, ZC_OP_MIN> : reduce_op_kernel<false, ZC_OP_MIN>);
+    const int segs = ranged || ra.ticketed ? 4 : few_op_segments(k, likely);
+    kernel = op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs) : pick_op_kernel<ZC_OP_MIN>(ix, segs);
+    tiles = tiles * u64(kTileWaves) / u64(segs);
   }
   CallAnswer answer(out_bytes && !ranged, tiles, stream);
   ra.answer = answer.arg();

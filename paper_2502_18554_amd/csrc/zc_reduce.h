@@ -425,6 +425,7 @@ __device__ inline u32 sign_plane(const u32 (&acc)[kSumPlanes], u32 top) {
 struct ReduceShare {
   u32 seg;                  // the segment (a stream has at most 2^26 blocks, so byte offsets into tables fit 32 bits)
   bool live;                // it exists
+  int first = 0, count = 0; // Max and Min, whose waves may share a segment's operands (see reduce_op_kernel): the wave's first one, and how many
 };
 
 // The widest block that stream s may have: 31, but 15 if it promised narrow blocks.

@@ -125,7 +125,7 @@ __device__ inline void operand_delta_pairs(u32 w, u32 (&f)[16]) {
 constexpr u32 kOperandArea = 1056;             // words
 static_assert(kOperandArea >= 1027 + 16 && kOperandArea % 4 == 0, "an operand's payload, and the reads behind its last word, must fit");
 constexpr u32 kExtremeStage = 2 * kOperandArea;
-static_assert(kExtremeStage >= u32(kWaveStage), "the output is staged in the same place");
+static_assert(kExtremeStage >= u32(kWaveStage) && kExtremeStage >= 64 * 32, "the output is staged in the same place, and a wave's extremes");
 
 // What a wave knows about an operand's blocks once their widths are there.
 struct PipeOperand {
@@ -134,7 +134,8 @@ struct PipeOperand {
   bool tail;                // uniform: the one leaves out some of the other
 };
 
-template <bool IX>
+// PARTS: the wave's operands are `share.count` of the call's, PARTS apart (s counts those).
+template <bool IX, int PARTS>
 struct OperandPipe {
   LaneOperands o;
   PipeOperand cur, next, ahead;            // operands s (whose words have been read), s + 1 and s + 2
@@ -142,9 +143,12 @@ struct OperandPipe {
   // The width of the lane's block: in operands s, s + 1 and s + 2 (indexed streams, whose segments are found without it), or in s + 3
   u32 width, width_next, width_ahead;
 
+  // Which of the call's operands is the wave's s-th (behind the last one: the last one).
+  __device__ __forceinline__ static int which(const ReduceShare& share, int s) { return share.first + PARTS * min(s, share.count - 1); }
+
   // What to ask for of operand s (nothing behind the last one); of a plain stream its widths have to be there.
-  __device__ __forceinline__ void open_ahead(PipeOperand& p, int k, int s, u32 blocks_width, u32& err) {
-    const int of = min(s, k - 1);
+  __device__ __forceinline__ void open_ahead(PipeOperand& p, const ReduceShare& share, int s, u32 blocks_width, u32& err) {
+    const int of = which(share, s);
     if (IX) {
       p.bytes = lane_value(o.bytes, of);
     } else {
@@ -153,9 +157,9 @@ struct OperandPipe {
       p.bytes = 4u * whole;
       p.tail = pieces != whole || p.span > 256u * kStageLoads;
     }
-    if (s >= k) p.bytes = 0;
+    if (s >= share.count) p.bytes = 0;
   }
-  // See place_operand.
+  // See place_operand (s: one of the call's operands).
   __device__ __forceinline__ void place(PipeOperand& p, int s, u32 blocks_width, u32& err) {
     const u32 words = psize_words(blocks_width), incl = wave_inclusive_sum(words), total = lane_value(incl, 63);     // (at most 64 x 256)
     const u32 shape = lane_value(o.shape, s);
@@ -170,32 +174,32 @@ struct OperandPipe {
     }
   }
 
-  __device__ __forceinline__ void open(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl, u32& err) {
+  __device__ __forceinline__ void open(const ReduceCall& c, const ReduceShare& share, u32* wl, u32& err) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
     o = lane_operands<IX>(c);
-    width = load_width(a, c, 0, b);
-    width_next = load_width(a, c, 1, b);
-    if (!IX) width_ahead = load_width(a, c, 2, b);
-    first = load_first(a, c, 0, b);
-    first_next = load_first(a, c, 1, b);
+    width = load_width(c, share, 0, b);
+    width_next = load_width(c, share, 1, b);
+    if (!IX) width_ahead = load_width(c, share, 2, b);
+    first = load_first(c, share, 0, b);
+    first_next = load_first(c, share, 1, b);
     lds_words_line();
-    open_ahead(cur, a.k, 0, width, err);
-    ask_payload_to_lds(o, 0, cur.bytes, wl, lane);
+    open_ahead(cur, share, 0, width, err);
+    ask_payload_to_lds(o, which(share, 0), cur.bytes, wl, lane);
     lds_words_line();
     u32 bad = 0;
-    open_ahead(next, a.k, 1, width_next, bad);
-    ask_payload_to_lds(o, min(1, a.k - 1), next.bytes, wl + kOperandArea, lane);
+    open_ahead(next, share, 1, width_next, bad);
+    ask_payload_to_lds(o, which(share, 1), next.bytes, wl + kOperandArea, lane);
     lds_words_line();
   }
-  __device__ __forceinline__ u32 load_width(const ReduceArgs& a, const ReduceCall& c, int s, u32 b) const {
-    return u32(__builtin_amdgcn_raw_buffer_load_b8(widths_buffer(o, c, min(s, a.k - 1), true), int(b), 0, 0));
+  __device__ __forceinline__ u32 load_width(const ReduceCall& c, const ReduceShare& share, int s, u32 b) const {
+    return u32(__builtin_amdgcn_raw_buffer_load_b8(widths_buffer(o, c, which(share, s), true), int(b), 0, 0));
   }
-  __device__ __forceinline__ i32 load_first(const ReduceArgs& a, const ReduceCall& c, int s, u32 b) const {
-    return i32(__builtin_amdgcn_raw_buffer_load_b32(outliers_buffer(o, c, min(s, a.k - 1), true), int(4u * b), 0, 0));
+  __device__ __forceinline__ i32 load_first(const ReduceCall& c, const ReduceShare& share, int s, u32 b) const {
+    return i32(__builtin_amdgcn_raw_buffer_load_b32(outliers_buffer(o, c, which(share, s), true), int(4u * b), 0, 0));
   }
   // The words of operand s from its lanes' sign words on, and operand s + 2 on its way.  Operands in turn from 0 on.
-  __device__ __forceinline__ void take(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, int s, u32* wl, u32 (&t)[16], u32& err) {
+  __device__ __forceinline__ void take(const ReduceCall& c, const ReduceShare& share, int s, u32* wl, u32 (&t)[16], u32& err) {
     u32* const area = wl + (s & 1 ? kOperandArea : 0u);
     const int lane = fresh_lane();
     if (s) {
@@ -210,21 +214,21 @@ struct OperandPipe {
     }
     lds_words_line();
     wait_all_but<kStageLoads>();
-    if (IX) place(cur, s, width, err);
+    if (IX) place(cur, which(share, s), width, err);
     if (cur.tail) {                            // uniform, and rare
-      fetch_payload_end(o, s, cur.bytes, cur.span, area, lane);
+      fetch_payload_end(o, which(share, s), cur.bytes, cur.span, area, lane);
       wave_lds_sync();
     }
     const u32 at = lds_address(area) + 4u * (cur.w ? cur.pick : 0u);
     read_lds_words<0>(at, t);
     read_lds_words<8>(at, t);
     // operand s + 2, in the place of operand s
-    open_ahead(ahead, a.k, s + 2, width_ahead, err);
+    open_ahead(ahead, share, s + 2, width_ahead, err);
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    first_ahead = load_first(a, c, s + 2, b);
-    width_ahead = load_width(a, c, s + (IX ? 2 : 3), b);
+    first_ahead = load_first(c, share, s + 2, b);
+    width_ahead = load_width(c, share, s + (IX ? 2 : 3), b);
     lds_words_line();
-    ask_payload_to_lds(o, min(s + 2, a.k - 1), ahead.bytes, area, lane);
+    ask_payload_to_lds(o, which(share, s + 2), ahead.bytes, area, lane);
     lds_words_line();
   }
   // Behind the last operand: what is still on its way (empty ranges, which leave zeros) has landed.
@@ -261,9 +265,9 @@ __device__ inline void meet_far_codes(u32 (&acc)[16], u32 (&f)[16], i32 ahead) {
 
 // The common path: the extremes of as many operands as it can take (returned, uniform).  If that is not all, the next
 // one is decoded: f = its codes modulo 2^16, `from` what the first of them starts from.
-template <bool IX, int OP>
+template <bool IX, int OP, int PARTS>
 __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
-                                              OperandPipe<IX>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
+                                              OperandPipe<IX, PARTS>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
   base = pipe.first;
   // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits: no
   // check of the result is needed)
@@ -277,7 +281,7 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceC
   u32 going = 1;
 #pragma nounroll
   while (going) {
-    pipe.take(a, c, share, s, wl, f, err);
+    pipe.take(c, share, s, wl, f, err);
     const u32 apart = u32(pipe.first) - u32(base);
     const bool far = apart + u32(kNearFirst) >= u32(2 * kNearFirst);
     const u32 start = ((far ? 0u : apart) + u32(kCodeBias<OP>)) & 0xffffu;
@@ -317,7 +321,7 @@ __device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceC
       for (int j = 0; j < 16; ++j) acc[j] = extreme_pairs<OP>(acc[j], f[j]);
       ++s;
     }
-    going = uniform(!stop && s < a.k ? 1u : 0u);
+    going = uniform(!stop && s < share.count ? 1u : 0u);
   }
   return s;
 }
@@ -390,9 +394,9 @@ __device__ __forceinline__ void close_any(i32 (&acc)[32], bool active, ExtremeBl
 }
 
 // The operands from s on, none of them with wide blocks, in 32 bits.  f: the deltas of operand s.
-template <bool IX, int OP>
+template <bool IX, int OP, int PARTS>
 __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
-                                             OperandPipe<IX>& pipe, i32 (&acc)[32], u32 (&f)[16], int s, u32& err) {
+                                             OperandPipe<IX, PARTS>& pipe, i32 (&acc)[32], u32 (&f)[16], int s, u32& err) {
 #pragma nounroll
   for (;;) {
     u32 code = u32(pipe.first);
@@ -401,25 +405,30 @@ __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCa
       code += u32(__builtin_amdgcn_sbfe(i32(f[j & 15]), u32(16 * (j >> 4)), 16u));
       acc[j] = extreme<OP>(acc[j], i32(code));
     }
-    if (++s >= a.k) return;
-    pipe.take(a, c, share, s, wl, f, err);
+    if (++s >= share.count) return;
+    pipe.take(c, share, s, wl, f, err);
     operand_delta_pairs(pipe.cur.w, f);
   }
 }
 
 // Operands without wide blocks.  True: they are in `out` (the common path has taken them all), false: in acc.
-template <bool IX, int OP>
+template <bool IX, int OP, int PARTS>
 __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                                ExtremeBlock& out, i32 (&acc)[32], u32& err) {
-  OperandPipe<IX> pipe;
-  pipe.open(a, c, share, wl, err);
+  OperandPipe<IX, PARTS> pipe;
+  pipe.open(c, share, wl, err);
   u32 pairs[16], f[16], from = 0;
   i32 base;
-  const int s = extreme_packed<IX, OP>(a, c, share, wl, pipe, pairs, f, from, base, err);
-  if (s == a.k) {
+  const int s = extreme_packed<IX, OP, PARTS>(a, c, share, wl, pipe, pairs, f, from, base, err);
+  if (s == share.count) {
     pipe.close();
-    close_packed<OP>(pairs, base, out);
-    return true;
+    if constexpr (PARTS == 1) {
+      close_packed<OP>(pairs, base, out);
+      return true;
+    }
+#pragma unroll
+    for (int j = 0; j < 32; ++j) acc[j] = base + i32(i16x2_t(as_pair(pairs[j & 15]))[j >> 4]) - kCodeBias<OP>;
+    return false;
   }
   // its deltas again
   from |= f[15] << 16;
@@ -431,20 +440,20 @@ __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const Reduce
     const i32 code = base + i32(i16x2_t(as_pair(pairs[j & 15]))[j >> 4]) - kCodeBias<OP>;
     acc[j] = s ? code : OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
   }
-  extreme_rest<IX, OP>(a, c, share, wl, pipe, acc, f, s, err);
+  extreme_rest<IX, OP, PARTS>(a, c, share, wl, pipe, acc, f, s, err);
   pipe.close();
   return false;
 }
 
 // Any codes and widths.
-template <bool IX, int OP>
+template <bool IX, int OP, int PARTS>
 __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
                                             i32 (&acc)[32], u32& err) {
 #pragma unroll
   for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
-  u32 width = load_operand_width(a.in[0].base, c, share.seg * kWaveBlocks + u32(fresh_lane()));
+  u32 width = load_operand_width(a.in[share.first].base, c, share.seg * kWaveBlocks + u32(fresh_lane()));
 #pragma nounroll
-  for (int s = 0; s < a.k; ++s) {
+  for (int s = share.first; s < a.k; s += PARTS) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
     const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + c.payload);
@@ -453,7 +462,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
     u32 code = u32(load_operand_outlier(a.in[s].base, c, b));
     if (!__any(cur.w > 15)) {
       const OperandStage stage = load_operand_payload(payload, cur, lane);
-      if (s + 1 < a.k) width = load_operand_width(a.in[s + 1].base, c, b);
+      if (s + PARTS < a.k) width = load_operand_width(a.in[s + PARTS].base, c, b);
       stage_to_lds(stage, cur, payload, wl, lane);
       wave_lds_sync();
       u32 f[16];
@@ -470,7 +479,7 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
         acc[j] = extreme<OP>(acc[j], i32(code));
       }
     } else {
-      if (s + 1 < a.k) width = load_operand_width(a.in[s + 1].base, c, b);
+      if (s + PARTS < a.k) width = load_operand_width(a.in[s + PARTS].base, c, b);
       u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
@@ -500,24 +509,62 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
   }
 }
 
-template <bool IX, int OP>
+// Segments per tile for k operands of so many tiles of four: with fewer, their operands are divided among more waves, and there are more
+// workgroups, of which four fit a compute unit.  us per call, tiles of four, two and one (Max of power-law fields at 1e-4 of their range | of hard data):
+//            1 tile             49                  128                 245                 384             512
+//    2 x   7.8  7.1           9.1  8.4            9.5  9.2           10.0 10.7           11.2 12.1       11.6 14.0
+//    4 x   9.4  8.0  7.3     11.1  9.4  9.0      11.5 10.0 10.6      11.8 11.9 13.2      14.1 14.2       14.5 16.2
+//    8 x  13.5  9.8  8.1     15.4 11.4 10.0      15.8 12.0 12.2      16.1 15.2 15.6      19.7 18.0 26.4  20.2 20.9 30.9
+//   16 x  21.8 13.7 10.3     23.9 15.6 12.0      25.2 16.5 15.2      24.1 20.2 20.4      31.7 25.2 32.5  31.9 30.1 39.1
+//    8 x  18.8 12.7 10.1     17.8 12.5 10.5      18.3 13.4 12.1      18.5 15.6 16.3      22.2 18.9 26.4  22.6 22.2 31.0
+__host__ constexpr int few_op_segments(int k, u64 tiles) {
+  if (k < 2) return 4;
+  if (tiles <= 128) return k >= (tiles <= 64 ? 4 : 8) ? 1 : 2;
+  return (tiles <= 256 ? k >= 8 : tiles <= 512 && k >= 12) ? 2 : 4;
+}
+
+// SEGS: segments of a tile.  Their operands are divided among PARTS = 4 / SEGS waves each, whose extremes meet in LDS: see zc_reduce_few.h.
+template <bool IX, int OP, int SEGS>
 __device__ __forceinline__ void reduce_op_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kTileWaves * kExtremeStage], u32& sh_tile,
-                                               u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
+                                               u32 (&sh_wave_total)[SEGS], u64 (&sh_base)[kTileWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
+  constexpr int PARTS = kTileWaves / SEGS;
   u32 width0 = 0, tile = 0, ntiles = 0;
-  if (!open_reduce<IX>(a, c, width0, false, tile, ntiles, &sh_tile, &survey)) return;
+  if (!open_reduce<IX, SEGS, PARTS == 1>(a, c, width0, false, tile, ntiles, &sh_tile, &survey)) return;
   const ParsedHeader& h = c.h;
-  const int wave = wave_id();
-  u32* const wl = lds + wave * kExtremeStage;
-  const u32 seg = uniform(tile * kTileWaves + u32(wave));
-  const ReduceShare share{seg, seg < num_segments(h.nb)};
+  const int wave = wave_id() % SEGS, part = PARTS > 1 ? wave_id() / SEGS : 0;
+  u32* const wl = lds + wave_id() * kExtremeStage;
+  const u32 seg = uniform(tile * u32(SEGS) + u32(wave));
+  const ReduceShare share{seg, seg < num_segments(h.nb), part, (a.k - part + PARTS - 1) / PARTS};
   u32 err = 0;
   if (c.ends_bad) err |= status_bit(ZC_ERR_FORMAT);
 
   ExtremeBlock eb;
   i32 codes[32];
   bool closed = false;
-  if (c.wide_streams) extreme_any<IX, OP>(a, c, share, wl, codes, err);
-  else closed = extreme_narrow<IX, OP>(a, c, share, wl, eb, codes, err);
+  if (c.wide_streams) extreme_any<IX, OP, PARTS>(a, c, share, wl, codes, err);
+  else closed = extreme_narrow<IX, OP, PARTS>(a, c, share, wl, eb, codes, err);
+  PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, IX, a.coherent != 0, looks_direct(ntiles, kDirectTiles, a.coherent != 0, 0u), 0u, c.tag};
+  if constexpr (PARTS > 1) {
+    sink.apart = kDescApartFine;
+    if (part) {
+      u32* const mine = wl + fresh_lane();
+#pragma unroll
+      for (int j = 0; j < 32; ++j) mine[64 * j] = u32(codes[j]);
+      if (err) raise_status(a.ctl, c.tag, err);
+    }
+    lds_barrier();
+    if (part) {
+      lds_barrier();
+      help_look_back(sink, tile, sh_base, wave_id());
+      return;
+    }
+#pragma unroll
+    for (int p = 1; p < PARTS; ++p) {
+      const u32* const theirs = lds + (p * SEGS + wave) * kExtremeStage + fresh_lane();
+#pragma unroll
+      for (int j = 0; j < 32; ++j) codes[j] = extreme<OP>(codes[j], i32(theirs[64 * j]));
+    }
+  }
   if (!closed) close_any(codes, share.seg * kWaveBlocks + u32(fresh_lane()) < h.nb, eb, err);
 
   const int lane = fresh_lane();
@@ -534,7 +581,6 @@ __device__ __forceinline__ void reduce_op_tile(const ReduceArgs& a, ReduceCall& 
   if (lane == 0) sh_wave_total[wave] = pl.wave_total | (IX && pl.wmax > 15 ? kWaveWideMark : 0u);
   lds_barrier();
   sum_wave_totals(sh_wave_total, wave, IX, pl);
-  const PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, IX, a.coherent != 0, looks_direct(ntiles, kDirectTiles, a.coherent != 0, 0u), 0u, c.tag};
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
   if (err) raise_status(a.ctl, c.tag, err);
   const bool narrow = pl.wmax <= 15;         // uniform
@@ -567,18 +613,18 @@ __device__ __forceinline__ void reduce_op_tile(const ReduceArgs& a, ReduceCall& 
     }, pl, tb.words, wl, lane);
   }
   store_tables<kAccessOnce>(sink, b, pl.w, eb.outlier);     // (at the very end: a store under way is waited for by every poll of the look-back)
-  finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
+  finish_stream<SEGS>(sink, pl, tile, ntiles, tb);
 }
 
-template <bool IX, int OP>
+template <bool IX, int OP, int SEGS = kTileWaves>
 __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kExtremeStage];
   __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
+  __shared__ u32 sh_wave_total[SEGS];
   __shared__ u64 sh_base[kTileWaves];
   __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
   ReduceCall c;
-  reduce_op_tile<IX, OP>(a, c, lds, sh_tile, sh_wave_total, sh_base, survey);
+  reduce_op_tile<IX, OP, SEGS>(a, c, lds, sh_tile, sh_wave_total, sh_base, survey);
   give_answer(a.answer, a.ctl);
 }
 

@@ -252,11 +252,12 @@ def test_a_refused_call_reports_a_size_of_nothing(zcref, stream_variant, tiles):
 
 # Sums of few tiles: four segments of a tile by a wave each, two by two and one by four that share its operands; a wave's last batch of
 # operands of every size, several batches, one side of every limit and the other; blocks of all classes of widths, and (wide) so many
-# wide blocks that they do not fit a wave's place for them; a segment count that is no multiple of a tile's
+# wide blocks that they do not fit a wave's place for them; a segment count that is no multiple of a tile's.  Max and Min the same way.
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("k,tiles", [(2, 1), (3, 2), (4, 9), (5, 3), (6, 129), (7, 17), (8, 256), (8, 257), (9, 1), (11, 5), (12, 128), (12, 129),
-                                     (13, 2), (16, 16), (17, 3), (64, 2), (4, 512), (4, 513), (2, 1024), (2, 1025), (5, 513)])
-def test_sums_of_few_tiles(zcref, stream_variant, k, tiles, wide):
+                                     (13, 2), (16, 16), (17, 3), (64, 2), (4, 512), (4, 513), (2, 1024), (2, 1025), (5, 513),
+                                     (4, 64), (4, 65), (7, 128), (8, 129), (12, 512), (12, 513)])
+def test_reduces_by_waves_that_share_operands(zcref, stream_variant, k, tiles, wide):
     u = gpuutil
     n = tiles * TILE - 2049 - 31
     g = np.random.default_rng(7 * k + tiles)
@@ -265,9 +266,10 @@ def test_sums_of_few_tiles(zcref, stream_variant, k, tiles, wide):
     base += rough * g.standard_normal(n).astype(np.float32)
     refs = [zcref.compress(np.roll(base, 4096 * i), 6e-3)[1] for i in range(min(k, 4))]
     refs = (refs * 16)[:k]
-    st_ref, want = zcref.reduce(refs)[:2]
-    st, got, _ = u.gpu_reduce(refs, n)
-    assert st == st_ref == ZC_OK and got.tobytes() == want.tobytes(), u.first_diff(got, want)
+    for op in (None, 1, 2) if tiles <= 513 else (None,):
+        st_ref, want = zcref.reduce(refs, op=op or 0)[:2]
+        st, got, _ = u.gpu_reduce(refs, n, op=op)
+        assert st == st_ref == ZC_OK and got.tobytes() == want.tobytes(), (op, u.first_diff(got, want))
     # one operand whose index says something else than its widths, or whose widths say something else than its size
     nb, at = (n + 31) // 32, int(g.integers(0, (n + 31) // 32))
     broken = refs[-1].copy()
@@ -277,7 +279,8 @@ def test_sums_of_few_tiles(zcref, stream_variant, k, tiles, wide):
     else:
         broken[u.widths_begin(nb) + at] = (int(broken[u.widths_begin(nb) + at]) + 1) % 31
     assert zcref.reduce(refs[:-1] + [broken])[0] == ZC_ERR_FORMAT
-    assert u.gpu_reduce(refs[:-1] + [broken], n)[0] == ZC_ERR_FORMAT
+    for op in (None, 1):
+        assert u.gpu_reduce(refs[:-1] + [broken], n, op=op)[0] == ZC_ERR_FORMAT
 
 
 # calls of one workgroup that somebody waits for: the main kernel itself gives the answer, also to a call that fails
