@@ -243,7 +243,7 @@ void fill_compress_args(CompressArgs& ca, const float* d_in, u64 n, float abs_eb
   ca.answer = {};
 }
 
-// The launch of zc_compress / zc_compress_part over the tiles [first_tile, end_tile) of the stream.
+// The launch of zc_compress (timed) / zc_compress_part over the tiles [first_tile, end_tile) of the stream.
 void launch_compress(CompressArgs& ca, u32 first_tile, u32 end_tile, bool timed, hipStream_t stream) {
   if (ca.nb == 0) {                                                     // the stream of no values
     EmptyStreamArgs ea{ca.ctl, ca.out, ca.out_cap, ca.eb_bits, ca.ix, ca.nonce};
@@ -251,7 +251,8 @@ void launch_compress(CompressArgs& ca, u32 first_tile, u32 end_tile, bool timed,
     return;
   }
   void (*kernel)(CompressArgs, u32, u32) = ca.ticketed ? compress_kernel<true> : compress_kernel<false>;
-  if (timed) launch_main(ZC_KERNEL_COMPRESS, kernel, dim3(end_tile - first_tile), dim3(kPackThreads), stream, ca, first_tile, end_tile);
+  if (timed && packs_small_tiles(ca)) launch_main(ZC_KERNEL_COMPRESS, compress_kernel<false, kTileWaves>, dim3(end_tile), dim3(kTileThreads), stream, ca, first_tile, end_tile);
+  else if (timed) launch_main(ZC_KERNEL_COMPRESS, kernel, dim3(end_tile - first_tile), dim3(kPackThreads), stream, ca, first_tile, end_tile);
   else hipLaunchKernelGGL(kernel, dim3(end_tile - first_tile), dim3(kPackThreads), 0, stream, ca, first_tile, end_tile);
 }
 
@@ -341,7 +342,7 @@ static int compress_impl(const float* d_in, size_t n, float abs_eb, void* d_out,
   if (l.tiles_cap < 1 || num_tiles(nb) > l.tiles_cap) return ZC_ERR_ARG;
   CompressArgs ca;
   fill_compress_args(ca, d_in, n, abs_eb, d_out, out_cap, l, flags);
-  const u64 tiles = num_pack_tiles(nb);
+  const u64 tiles = packs_small_tiles(ca) ? num_tiles(nb) : num_pack_tiles(nb);
   CallAnswer answer(out_bytes != nullptr, tiles, stream, may_pin);
   ca.answer = answer.arg();
   launch_compress(ca, 0, u32(tiles), true, stream);

@@ -54,6 +54,12 @@ __device__ inline i32 rint_small(double r) {
   return i32(__double2loint(t));
 }
 
+// The largest magnitude of three (the first is not negative), NaN if there is one.  (One instruction, which takes magnitudes
+// by itself; integer maxima of the bit patterns need a signed and an unsigned one.)
+__device__ inline float most_of(float so_far, float b, float c) {
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(so_far, __builtin_fabsf(b)), __builtin_fabsf(c));
+}
+
 // Codes of one value that failed the cheap screen: the defining arithmetic, with its checks.
 __device__ inline i32 quantize_checked(float x, const CompressArgs& a, u32& err) {
   if (!(__builtin_fabsf(x) <= 3.4028234663852886e38f)) {   // NaN or Inf
@@ -138,16 +144,26 @@ __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u3
 // pushed out.  In both halves without tickets it needs fewer, but then has 20 bytes of scratch set aside, which
 // zc_compress_noalloc is not to need; in none it needs twice as many.  2^26 values by ticket 80.7 us with none, 80.0 with one,
 // 78.1 with both; without tickets 66.8, 65.6, 65.2.)
-template <bool TICKETS>
+// FEW: see compress_kernel.
+template <bool TICKETS, bool FEW>
 __device__ __forceinline__ void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                    i32 (&q)[32], u32& err) {
   // Some value of this wave outside the screened domain: the checked arithmetic for all of it.
-  u32 flagged = 0;            // (no short-circuit: the four compares of a load are independent)
+  bool outside;
+  if constexpr (FEW) {
+    float most = 0.0f;
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    flagged |= u32(needs_checks(x[i].x, a)) | u32(needs_checks(x[i].y, a)) | u32(needs_checks(x[i].z, a)) |
-               u32(needs_checks(x[i].w, a));
-  const bool checked = __any(flagged != 0);
+    for (int i = 0; i < 8; ++i) most = most_of(most_of(most, x[i].x, x[i].y), x[i].z, x[i].w);
+    outside = needs_checks(most, a);
+  } else {
+    u32 flagged = 0;            // (no short-circuit: the four compares of a load are independent)
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      flagged |= u32(needs_checks(x[i].x, a)) | u32(needs_checks(x[i].y, a)) | u32(needs_checks(x[i].z, a)) |
+                 u32(needs_checks(x[i].w, a));
+    outside = flagged != 0;
+  }
+  const bool checked = __any(outside);
 
   // Loads 0..3 hold blocks 0..31, loads 4..7 blocks 32..63.  Either half goes through LDS as 32 rows
   // of 32 codes, and every lane takes half a row: lane l and lane l + 32 the first and the second 16
@@ -206,11 +222,11 @@ struct BlockFields {
   i32 outlier;
 };
 
-template <bool TICKETS>
+template <bool TICKETS, bool FEW>
 __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                     BlockFields& bf, u32& err) {
   i32 q[32];
-  block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, err);
+  block_codes<TICKETS, FEW>(a, x, wblock0, have, lane, wl, q, err);
   bf.outlier = q[0];
   i32 top = 0, bottom = 0;              // largest and smallest delta (d0 = 0 is one of them)
 #pragma unroll
@@ -234,7 +250,7 @@ __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8],
 // of the hard-data configuration 2 % of the waves, but 16 % of the tiles, hold such a block.  (A tile with one
 // used to store its blocks two at a time, a plane word being the ballot of one bit of 32 lanes; 2^28 hard
 // values, compressed and decompressed: 674 us, now 455.)
-template <bool TICKETS>
+template <bool TICKETS, bool FEW>
 __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const PayloadSink& sink, const Placement& pl, u64 base,
                                                 u64 wblock0, u32 have, int lane, u32* wl) {
   asm volatile("" : "+v"(lane));               // (or the compiler keeps what it has loaded and quantised before, in scratch)
@@ -243,7 +259,7 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
     float4 x[8];
     u32 ignored = 0;                           // errors were raised on the first pass
     load_raw(a, wblock0, lane, have, x);
-    block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, ignored);
+    block_codes<TICKETS, FEW>(a, x, wblock0, have, lane, wl, q, ignored);
   }
 #pragma unroll
   for (int j = 31; j >= 1; --j) q[j] -= q[j - 1];
@@ -266,20 +282,34 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
 // 122.4 -> 121.7 us when that was done, 116.4 now.  The ragged end is a tile like any other (see
 // load_raw); as a launch of its own behind the full tiles it cost 7 us per call on any input that is not
 // a multiple of 16384 values (20 000 003 values, compress and decompress: 59.0 us, now 51.9).
-template <bool TICKETS>
-__device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_tile, u32 end_tile, u32 (&lds)[kPackWaves * kWaveStage], u32& sh_tile,
-                                             u32 (&sh_wave_total)[kPackWaves], u64 (&sh_base)[kPackWaves]) {
+// WAVES: kPackWaves, or kTileWaves where that shortens the call (packs_small_tiles): with few tiles two waves of a workgroup of eight
+// share a SIMD, which one alone keeps busy, while other compute units have nothing to do, and between one and one and a half workgroups of eight per compute unit
+// three of four waves share it more evenly.  There it is the instructions that count, so these kernels also screen with maxima (16 instructions for 64),
+// copy out by ranges and stage narrow blocks without conditions (stage_words_downward).  us, tiles of eight waves and of four:
+//   sinusoids at 1e-4   1000 values 5.6 5.1 | 2^20: 6.6 5.4 | 2 000 003: 7.0 6.3 | 3 000 000: 7.1 6.8 | 5 000 000: 9.4 8.2 | 6 500 000: 9.5 9.7
+//   a field at 1e-4     1000 values 6.0 5.3 | 2^20: 6.8 5.8 | 2 000 003: 7.2 6.5 | 3 400 000: 7.6 7.8 | 5 000 000: 10.3 9.0 | 6 500 000: 10.5 10.7
+//   hard data           1000 values 5.7 4.6 | 2^20: 8.8 7.4 | 2 000 003: 9.1 7.7 | 3 000 000: 9.2 9.0 | 5 000 000: 11.7 10.2 | 8 000 000: 13.2 12.9
+__host__ inline bool packs_small_tiles(const CompressArgs& a) {
+  const u64 tiles = num_tiles(a.nb);
+  return !a.ticketed && (tiles <= 256 || (tiles > 512 && tiles <= 768));
+}
+
+template <bool TICKETS, int WAVES>
+__device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_tile, u32 end_tile, u32 (&lds)[WAVES * kWaveStage], u32& sh_tile,
+                                             u32 (&sh_wave_total)[WAVES], u64 (&sh_base)[WAVES]) {
+  constexpr int kBlocks = WAVES * kWaveBlocks;
+  constexpr bool FEW = WAVES != kPackWaves;
   const int lane = lane_id();
   const int wave = wave_id();
   u32 tile = first_tile + blockIdx.x;        // tiles in the order in which workgroups start
   u32 have = 0;
   float4 x[8];
   if (!TICKETS) {
-    const u64 wblock0 = u64(tile) * kPackBlocks + u64(wave) * kWaveBlocks;
+    const u64 wblock0 = u64(tile) * kBlocks + u64(wave) * kWaveBlocks;
     have = share_values(a.n, wblock0 * kBlockValues);
     load_raw(a, wblock0, lane, have, x);
   }
-  const u32 ntiles = u32(num_pack_tiles(a.nb));
+  const u32 ntiles = (u32(a.nb) + kBlocks - 1) / kBlocks;
   u32* const wl = lds + wave * kWaveStage;
   const bool tables_fit = a.out_cap >= tables_end(a.nb, a.ix);
   u32 err = 0;
@@ -301,7 +331,7 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
     else raise_status(a.ctl, tag, status_bit(ZC_ERR_CAPACITY));
   }
   {
-    const u64 wblock0 = u64(tile) * kPackBlocks + u64(wave) * kWaveBlocks;
+    const u64 wblock0 = u64(tile) * kBlocks + u64(wave) * kWaveBlocks;
     const bool active = u32(wblock0) + u32(lane) < u32(a.nb);      // (a stream has at most 2^26 blocks)
     if (TICKETS) {
       have = share_values(a.n, wblock0 * kBlockValues);
@@ -309,7 +339,7 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
     }
 
     BlockFields bf;
-    block_fields<TICKETS>(a, x, wblock0, have, lane, wl, bf, err);
+    block_fields<TICKETS, FEW>(a, x, wblock0, have, lane, wl, bf, err);
     Placement pl;
     pl.w = (active && bf.any) ? 32u - u32(__builtin_clz(bf.any)) : 0u;
     pl.wmax = wave_max_u32(pl.w);
@@ -333,6 +363,8 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
     const bool narrow = pl.wmax <= 15;         // uniform
     const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
       if (!narrow) return;
+      constexpr u32 kAside = 64 * 16 + 16;
+      static_assert(kAside + 16 <= u32(kWaveStage));
       u32 pw[16];          // pw[0] = sign, pw[1 + p] = plane p
       if (pl.wmax <= 7) {
         u32 r[8];
@@ -340,6 +372,10 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
         pw[0] = r[7];
 #pragma unroll
         for (int p = 0; p < 7; ++p) pw[1 + p] = r[p];
+        if constexpr (FEW) {
+          stage_words_downward<8>([&](auto i) { return pw[decltype(i)::value]; }, pl.w, pl.off_in_wave, wl, kAside);
+          return;
+        }
 #pragma unroll
         for (int p = 8; p < 16; ++p) pw[p] = 0;
       } else {
@@ -350,10 +386,10 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
       }
       stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, pl, wl);
     });
-    if (lane == 0) write_index_entry(sink, tile * u32(kPackWaves) + u32(wave), tb.words + pl.wave_off);
-    if (narrow) copy_staged_wave<16, false>(sink, pl, tb.words, wl, lane);
-    else store_wide_wave<TICKETS>(a, sink, pl, tb.words, wblock0, have, lane, wl);
-    finish_stream<kPackWaves>(sink, pl, tile, ntiles, tb);
+    if (lane == 0) write_index_entry(sink, tile * u32(WAVES) + u32(wave), tb.words + pl.wave_off);
+    if (narrow) copy_staged_wave<16, FEW>(sink, pl, tb.words, wl, lane);
+    else store_wide_wave<TICKETS, FEW>(a, sink, pl, tb.words, wblock0, have, lane, wl);
+    finish_stream<WAVES>(sink, pl, tile, ntiles, tb);
     if (active && tables_fit) {                // (not store_tables: see copy_staged_words)
       const u64 b = wblock0 + u64(lane);
       a.out[widths_begin(a.nb, a.ix) + b] = u8(pl.w);
@@ -363,13 +399,13 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
   if (err) raise_status(a.ctl, tag, err);
 }
 
-template <bool TICKETS>
-__global__ __launch_bounds__(kPackThreads, 8) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kPackWaves * kWaveStage];
+template <bool TICKETS, int WAVES = kPackWaves>
+__global__ __launch_bounds__(64 * WAVES, WAVES == kPackWaves ? 8 : 4) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
+  __shared__ __attribute__((aligned(16))) u32 lds[WAVES * kWaveStage];
   __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kPackWaves];
-  __shared__ u64 sh_base[kPackWaves];
-  compress_tile<TICKETS>(a, first_tile, end_tile, lds, sh_tile, sh_wave_total, sh_base);
+  __shared__ u32 sh_wave_total[WAVES];
+  __shared__ u64 sh_base[WAVES];
+  compress_tile<TICKETS, WAVES>(a, first_tile, end_tile, lds, sh_tile, sh_wave_total, sh_base);
   give_answer(a.answer, a.ctl);
 }
 

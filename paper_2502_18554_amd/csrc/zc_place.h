@@ -321,6 +321,22 @@ __device__ inline void stage_wave_words(WordFn word, const Placement& pl, u32* w
   }
 }
 
+// The same with one store a word and no condition, for a wave whose blocks have at most NW words each, where the instructions count (ring rounds of
+// 2^24 values with blocks of at most 7 bits 25.9 -> 24.7 us; compression of 2^20 such values by small tiles 5.9 -> 5.4).  With 16 words, of which a block has ten, the
+// stores themselves take longer than the conditions (compression of 2^20: this part of a tile 0.52 -> 0.84 us), and so they do in the kernels that are bound by memory (compression of 512^3
+// values 118.0 -> 120.2, Sum of 4 x 2^24 28.4 -> 28.8).  The words go from the last plane down
+// to the sign word: what a block of fewer planes writes behind its own words is another block's place, in which that block has a plane of a
+// lower number (its place begins no sooner than this one's ends), and so is overwritten later (a wave's LDS accesses are carried
+// out in their order; volatile keeps the compiler's hands off it).  A block without words, whose place is that of the next one, writes to
+// `aside`, which has room for NW words, as there must be behind the wave's last word.
+template <int NW, typename WordFn>
+__device__ inline void stage_words_downward(WordFn word, u32 w, u32 off, u32* wl, u32 aside) {
+  volatile u32* const at = wl + (w ? off : aside);
+  [&]<int... I>(std::integer_sequence<int, I...>) {
+    ((at[NW - 1 - I] = word(std::integral_constant<int, NW - 1 - I>{})), ...);
+  }(std::make_integer_sequence<int, NW>{});
+}
+
 // Then the copy-out is a plain LDS-to-memory copy of the wave's words.
 template <int NW, bool BY_RANGE>
 __device__ inline void copy_staged_wave(const PayloadSink& s, const Placement& pl, u64 base, u32* wl, int lane) {

@@ -181,12 +181,7 @@ __device__ inline void place_sum_staged(const ReduceArgs& a, const ReduceCall& c
   if (lane == 0) sh_wave_total[wave] = pl.wave_total | (ix && pl.wmax > 15 ? kWaveWideMark : 0u);
   // (width and outlier go to their tables at the very end: a store that is under way is waited for by
   // every poll of the look-back)
-  if (w) {
-    wl[pl.off_in_wave] = word(std::integral_constant<int, 0>{});
-    [&]<int... P>(std::integer_sequence<int, P...>) {
-      ((u32(P) < w ? void(wl[pl.off_in_wave + 1 + P] = word(std::integral_constant<int, 1 + P>{})) : void()), ...);
-    }(std::make_integer_sequence<int, NW - 1>{});
-  }
+  stage_wave_words<NW>(word, pl, wl);
   lds_barrier();                // the wave totals (and the words above); the stores stay in flight
   sum_wave_totals(sh_wave_total, wave, ix, pl);
   if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);

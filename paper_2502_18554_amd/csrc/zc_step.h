@@ -108,12 +108,6 @@ struct ChainState {
 // done half the block, and has filled eight words of new deltas.
 __device__ inline u32 swap_middle_bytes(u32 v) { return __builtin_amdgcn_perm(v, v, 0x03010200u); }
 
-// The largest magnitude of three (the first is not negative), NaN if there is one.  (One instruction, which takes magnitudes
-// by itself; integer maxima of the bit patterns need a signed and an unsigned one.)
-__device__ inline float most_of(float so_far, float b, float c) {
-  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(so_far, __builtin_fabsf(b)), __builtin_fabsf(c));
-}
-
 // Values 16 HALF .. 16 HALF + 15 of the lane's block.  BITS: width of the fields the received
 // deltas are packed in (16: word (j & 7) + 8 HALF holds values j and j + 8, see above; 8: word
 // j & 7 holds values j, j + 8, j + 16, j + 24).  `row`: the lane's 16 local values of this half.
@@ -588,7 +582,10 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
   // ---- the new deltas as sign + plane words into the staging area, while the look-back is under way ----
   const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
     if (pl.wave_total > u32(kStepStage)) return;       // uniform: out at once, when the base offset is known
+    constexpr u32 kAside = 64 * 16 + 16;
+    static_assert(kAside + 16 <= u32(kStepStage));
     u32 pw[16];          // pw[0] = sign, pw[1 + p] = plane p
+    auto word = [&](auto i) { return pw[decltype(i)::value]; };
     if (pl.wmax <= 7) {
       // four 8-bit fields per word: word j = values j, j + 8 (word j of nf), j + 16, j + 24 (word j + 8)
       u32 r[8];
@@ -599,17 +596,25 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
       pw[0] = r[7];
 #pragma unroll
       for (int p = 0; p < 7; ++p) pw[1 + p] = r[p];
-#pragma unroll
-      for (int p = 8; p < 16; ++p) pw[p] = 0;
     } else {
       planes16_from_fields(nf);
       pw[0] = swap_middle_bytes(nf[15]);
 #pragma unroll
       for (int p = 0; p < 15; ++p) pw[1 + p] = swap_middle_bytes(nf[p]);
     }
-    Placement here = pl;
-    if ((slow >> lane) & 1u) here.w = 0;
-    stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, here, wl);
+    if (slow) {                                // uniform: places of up to 32 words among them
+      Placement here = pl;
+      if ((slow >> lane) & 1u) here.w = 0;
+      if (pl.wmax <= 7) {
+#pragma unroll
+        for (int p = 8; p < 16; ++p) pw[p] = 0;
+      }
+      stage_wave_words<16>(word, here, wl);
+    } else if (pl.wmax <= 7) {
+      stage_words_downward<8>(word, pl.w, pl.off_in_wave, wl, kAside);
+    } else {
+      stage_wave_words<16>(word, pl, wl);
+    }
     u32 ignored = 0;
     if (slow) step_blocks_slow<IX, OP, kStage>(a, h, qa, seg, slow, u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave, wl, kStepStage, ignored);
   });

@@ -309,3 +309,15 @@ def test_calls_of_one_workgroup_answer_themselves(zcref, n):
             want = zcref.reduce([ref], op=op or 0)[1]
             st, s, total = u.gpu_reduce([ref], n, op=op)
             assert st == ZC_OK and total == want.size and s.tobytes() == want.tobytes()
+
+
+# both sides of the sizes between which the compressor's tiles are of four waves, with narrow and with wider blocks
+@pytest.mark.parametrize("tiles", [1, 2, 255, 256, 257, 512, 513, 768, 769])
+def test_compression_by_small_tiles(zcref, tiles):
+    u = gpuutil
+    for n in (tiles * TILE, tiles * TILE - 4097):
+        for eb in (2e-2, 1e-5):                      # blocks of at most 7 bits (but for one), and of more
+            x = _values(n, 30)
+            st_ref, ref = zcref.compress(x, eb)[:2]
+            st, s, total = u.gpu_compress(x, eb)
+            assert st == st_ref and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
