@@ -252,14 +252,42 @@ __device__ inline SlowInput load_slow_input(const StepArgs& a, const ParsedHeade
 // were read one after the other; all tiles behind such a wave wait for it.  A round on 2^26 values of hard data,
 // where one wave in ten has such a block: 790 us, now 98.  Inlined as one lane per block in 32 bits, which is faster
 // for a wave of nothing but wide blocks, it cost every round 5 % in registers.)
+// KEEP: the last pass over the first two blocks need not be computed again: `kept` holds their new deltas from the first pass on (mostly there
+// are no others, and a call of few tiles waits for the wave that has them: a Max round of 2^20 hard values 10.8 us, now 9.5, a Sum round of 40 000 9.9 and 8.9).
+struct KeptDeltas {
+  u64 blocks = 0;           // which two (or one)
+  i32 nd = 0;               // lane j, 32 + j: delta j of the one, of the other
+};
 enum SlowPass { kMeasure, kStage, kStore };
-template <bool IX, int OP, SlowPass PASS>
+template <bool IX, int OP, SlowPass PASS, bool KEEP>
 __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h, const CompressArgs& qa, u32 seg, u64 mask,
                                         u32 seg_off, bool inside, u32& w_out, i32& outlier_out, u32 off_out, u32* to, u64 room,
-                                        u32& err) {
-  const SlowInput in = load_slow_input<IX>(a, h, seg, seg_off, inside);
+                                        u32& err, KeptDeltas& kept) {
   const int lane = fresh_lane();
   const u32 half = u32(lane) >> 5, j = u32(lane) & 31u;
+  // sign and plane words of two blocks, one per half of the wave, as ballots of their deltas
+  auto store_block = [&](i32 nd, u32 blk_a, u32 blk_b) {
+    const u32 nmag = u32(nd < 0 ? -nd : nd);
+    const u32 wo_a = lane_value(w_out, int(blk_a)), wo_b = lane_value(w_out, int(blk_b));
+    const u32 wo_mine = half ? wo_b : wo_a;
+    const u32 dst = half ? lane_value(off_out, int(blk_b)) : lane_value(off_out, int(blk_a));
+    const u64 sign = __ballot(nd < 0);
+    if (j == 0 && wo_mine && dst < room) to[dst] = half ? u32(sign >> 32) : u32(sign);
+    const u32 wo_top = wo_a > wo_b ? wo_a : wo_b;
+#pragma nounroll
+    for (u32 p = 0; p < wo_top; ++p) {
+      const u64 plane = __ballot(((nmag >> p) & 1u) != 0);
+      if (j == 0 && p < wo_mine && dst + 1 + p < room) to[dst + 1 + p] = half ? u32(plane >> 32) : u32(plane);
+    }
+  };
+  if constexpr (KEEP && PASS != kMeasure) {
+    if (kept.blocks) {                         // uniform
+      store_block(kept.nd, u32(__builtin_ctzll(kept.blocks)), 63u - u32(__builtin_clzll(kept.blocks)));
+      mask &= ~kept.blocks;
+      if (!mask) return;
+    }
+  }
+  const SlowInput in = load_slow_input<IX>(a, h, seg, seg_off, inside);
   u32 w_res = w_out;
   i32 outlier_res = outlier_out;
 #pragma nounroll
@@ -299,8 +327,12 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
     if (j >= cnt) q = cnt ? last : 0;                   // the last block repeats its last code
     const i32 before = i32(from_lane(u32(q), u32(lane) + 63u));                 // lane - 1 (lane 0 gets lane 63: unused)
     const i32 nd = j ? q - before : 0;
-    const u32 nmag = u32(nd < 0 ? -nd : nd);
     if constexpr (PASS == kMeasure) {
+      if (KEEP && !kept.blocks) {
+        kept.blocks = (u64(1) << blk_a) | (u64(1) << blk_b);
+        kept.nd = nd;
+      }
+      const u32 nmag = u32(nd < 0 ? -nd : nd);
       const u32 m = half_max(nmag);
       const u32 wn = m ? 32u - u32(__builtin_clz(m)) : 0u;
       const u32 wn_a = lane_value(wn, 0), wn_b = lane_value(wn, 32);
@@ -308,17 +340,7 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
       if (u32(lane) == blk_a) { w_res = wn_a; outlier_res = i32(q0_a); }
       if (u32(lane) == blk_b) { w_res = wn_b; outlier_res = i32(q0_b); }
     } else {
-      const u32 wo_a = lane_value(w_out, int(blk_a)), wo_b = lane_value(w_out, int(blk_b));
-      const u32 wo_mine = half ? wo_b : wo_a;
-      const u32 dst = half ? lane_value(off_out, int(blk_b)) : lane_value(off_out, int(blk_a));
-      const u64 sign = __ballot(nd < 0);
-      if (j == 0 && wo_mine && dst < room) to[dst] = half ? u32(sign >> 32) : u32(sign);
-      const u32 wo_top = wo_a > wo_b ? wo_a : wo_b;
-#pragma nounroll
-      for (u32 p = 0; p < wo_top; ++p) {
-        const u64 plane = __ballot(((nmag >> p) & 1u) != 0);
-        if (j == 0 && p < wo_mine && dst + 1 + p < room) to[dst + 1 + p] = half ? u32(plane >> 32) : u32(plane);
-      }
+      store_block(nd, blk_a, blk_b);
     }
   }
   if constexpr (PASS == kMeasure) {
@@ -345,6 +367,7 @@ template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS>
 __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWaves * kStepStage + kCopyOver], u32& sh_tile, u32 (&sh_wave_total)[kTileWaves],
                                          u64 (&sh_base)[kTileWaves], PlainSurvey<1>& survey) {
   constexpr bool FOURS = TICKETS || GROUPS > 5 || !(IX || SELF);
+  constexpr bool KEEP = !FOURS;             // (where a register more is to be had)
 
   const int lane = lane_id();
   const int wave = wave_id();
@@ -494,6 +517,7 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
   // lane l).  A received segment too large for the staging area has wide blocks throughout.
   const u64 wide_in = __ballot(wp.w > 15);
   u64 measure = 0, slow = 0;
+  KeptDeltas kept;
   if (wp.wmax > 15 && !wp.staged) {
     measure = slow = __ballot(active);
   } else {
@@ -561,7 +585,10 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
     slow = measure | __ballot(pl.w > 15);          // (a wide result alone: its width is known)
   }
   if (measure) {
-    step_blocks_slow<IX, OP, kMeasure>(a, h, qa, seg, measure, u32(seg_off), wp.inside, pl.w, outlier, 0u, nullptr, 0, err);
+    // (two at a time: an odd one out takes one along that is to be produced too, whose deltas are then there as well)
+    const u64 also = slow & ~measure;
+    if (KEEP && (__builtin_popcountll(measure) & 1) && also) measure |= also & (0 - also);
+    step_blocks_slow<IX, OP, kMeasure, KEEP>(a, h, qa, seg, measure, u32(seg_off), wp.inside, pl.w, outlier, 0u, nullptr, 0, err, kept);
   }
 
   // ---- width, tables, placement ----
@@ -602,21 +629,19 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
 #pragma unroll
       for (int p = 0; p < 15; ++p) pw[1 + p] = swap_middle_bytes(nf[p]);
     }
-    if (slow) {                                // uniform: places of up to 32 words among them
-      Placement here = pl;
-      if ((slow >> lane) & 1u) here.w = 0;
+    if (GROUPS > 5 && pl.wmax <= 7 && !slow) {      // uniform (slow: places of up to 32 words among them)
+      stage_words_downward<8>(word, pl.w, pl.off_in_wave, wl, kAside);
+    } else {
       if (pl.wmax <= 7) {
 #pragma unroll
         for (int p = 8; p < 16; ++p) pw[p] = 0;
       }
+      Placement here = pl;
+      if ((slow >> lane) & 1u) here.w = 0;
       stage_wave_words<16>(word, here, wl);
-    } else if (pl.wmax <= 7) {
-      stage_words_downward<8>(word, pl.w, pl.off_in_wave, wl, kAside);
-    } else {
-      stage_wave_words<16>(word, pl, wl);
     }
     u32 ignored = 0;
-    if (slow) step_blocks_slow<IX, OP, kStage>(a, h, qa, seg, slow, u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave, wl, kStepStage, ignored);
+    if (slow) step_blocks_slow<IX, OP, kStage, KEEP>(a, h, qa, seg, slow, u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave, wl, kStepStage, ignored, kept);
   });
   const u64 base = tb.words;
   if (lane == 0) write_index_entry(sink, seg, base + pl.wave_off);
@@ -628,8 +653,8 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
     const u64 cap_words = a.out_cap > tend ? (a.out_cap - tend) / 4 : 0;
     const u64 dst = base + pl.wave_off;
     u32 ignored = 0;
-    step_blocks_slow<IX, OP, kStore>(a, h, qa, seg, __ballot(active), u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave,
-                                     reinterpret_cast<u32*>(a.out + tend) + dst, cap_words > dst ? cap_words - dst : 0, ignored);
+    step_blocks_slow<IX, OP, kStore, KEEP>(a, h, qa, seg, __ballot(active), u32(seg_off), wp.inside, pl.w, outlier, pl.off_in_wave,
+                                     reinterpret_cast<u32*>(a.out + tend) + dst, cap_words > dst ? cap_words - dst : 0, ignored, kept);
   }
   store_tables<0>(sink, b, pl.w, outlier);
   finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
