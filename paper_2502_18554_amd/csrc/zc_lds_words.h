@@ -29,8 +29,9 @@ struct LaneOperands {
 };
 constexpr u32 kNoWords = 0x3fffffffu;     // more than any widths add up to
 
+// most: words of the longest segment, and three.
 template <bool IX>
-__device__ __forceinline__ LaneOperands lane_operands(const ReduceCall& c) {
+__device__ __forceinline__ LaneOperands lane_operands(const ReduceCall& c, u32 most = kMostStaged) {
   LaneOperands o;
   const u64 widths = c.base + c.widths;
   o.widths_lo = u32(widths);
@@ -41,7 +42,7 @@ __device__ __forceinline__ LaneOperands lane_operands(const ReduceCall& c) {
   o.share_hi = u32(share >> 32);
   o.room = c.places <= room ? room - src0 : 0u;
   const u32 words = c.ends - c.places;
-  const bool inside = IX && mis <= o.room && words <= o.room - mis && words <= kMostStaged - 3u;
+  const bool inside = IX && mis <= o.room && words <= o.room - mis && words <= most - 3u;
   o.shape = mis | (inside ? words : kNoWords) << 2;
   const u32 pieces = inside ? (mis + words + 3u) & ~3u : 0u, whole = min(pieces, o.room & ~3u);
   o.bytes = 4u * whole;
@@ -49,6 +50,9 @@ __device__ __forceinline__ LaneOperands lane_operands(const ReduceCall& c) {
   return o;
 }
 
+__device__ __forceinline__ const u32* lane_share(const LaneOperands& o, int s) {
+  return reinterpret_cast<const u32*>(u64(lane_value(o.share_lo, s)) | (u64(lane_value(o.share_hi, s)) << 32));
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t lane_buffer(u32 lo, u32 hi, int s, u32 behind, u32 bytes) {
   const u64 at = (u64(lane_value(lo, s)) | (u64(lane_value(hi, s)) << 32)) + behind;
   return bytes_from(reinterpret_cast<const void*>(at), bytes);
@@ -73,7 +77,7 @@ __device__ __forceinline__ void ask_payload_to_lds(const LaneOperands& o, int s,
 __device__ __forceinline__ void fetch_payload_end(const LaneOperands& o, int s, u32 bytes, u32 span, u32* area, int lane) {
   const u32 from = min(bytes / 4u, 256u * kStageLoads) + u32(lane);
   if (from < min(span, lane_value(o.room, s)))
-    area[from] = reinterpret_cast<const u32*>(u64(lane_value(o.share_lo, s)) | (u64(lane_value(o.share_hi, s)) << 32))[from];
+    area[from] = lane_share(o, s)[from];
 }
 
 // All vector memory accesses of the wave but the newest N are done.

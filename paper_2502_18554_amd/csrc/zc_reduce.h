@@ -248,7 +248,7 @@ constexpr u32 kMostStaged = 256u * kStageLoads + 64u;
 
 // Where operand s has the wave's segment.  An indexed stream (ix) says so by itself, and how long the segment is, so that its
 // payload can be asked for before its widths are there; of a plain one only the start is known.  Everything here is the same in every lane.
-__device__ inline OperandPlace open_operand(int s, u64 bytes, const ReduceCall& c, bool ix, u32 most = kMostStaged) {
+__device__ inline OperandPlace open_operand(int s, u64 bytes, const ReduceCall& c, bool ix) {
   OperandPlace p;
   const u32 seg_off = lane_value(c.places, s), room = payload_room(bytes, c);
   const u32 mis = seg_off & 3u;
@@ -257,7 +257,7 @@ __device__ inline OperandPlace open_operand(int s, u64 bytes, const ReduceCall& 
   p.span = 0;
   if (ix) {
     const u32 words = lane_value(c.ends, s) - seg_off;
-    if (mis <= p.room && words <= p.room - mis && words <= most - 3u) p.span = mis + words;      // (else place_operand finds that the widths say something else)
+    if (mis <= p.room && words <= p.room - mis && words <= kMostStaged - 3u) p.span = mis + words;      // (else place_operand finds that the widths say something else)
   }
   p.w = p.pick = p.wcap = 0;
   return p;

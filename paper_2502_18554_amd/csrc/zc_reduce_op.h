@@ -451,35 +451,47 @@ __device__ __forceinline__ void extreme_any(const ReduceArgs& a, const ReduceCal
                                             i32 (&acc)[32], u32& err) {
 #pragma unroll
   for (int j = 0; j < 32; ++j) acc[j] = OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
-  u32 width = load_operand_width(a.in[share.first].base, c, share.seg * kWaveBlocks + u32(fresh_lane()));
+  const LaneOperands o = lane_operands<IX>(c, 3 + 64 * 32);
+  u32 width = u32(__builtin_amdgcn_raw_buffer_load_b8(widths_buffer(o, c, share.first, true), int(share.seg * kWaveBlocks + u32(fresh_lane())), 0, 0));
 #pragma nounroll
   for (int s = share.first; s < a.k; s += PARTS) {
     const int lane = fresh_lane();
     const u32 b = share.seg * kWaveBlocks + u32(lane);
-    const u32* const payload = reinterpret_cast<const u32*>(a.in[s].base + c.payload);
-    OperandPlace cur = open_operand(s, a.in[s].bytes, c, IX, 3 + 64 * 32);
-    place_operand(cur, s, width, c, IX, err, width_limit(c, s));
-    u32 code = u32(load_operand_outlier(a.in[s].base, c, b));
+    const u32* const payload = lane_share(o, s);
+    OperandPlace cur;
+    {
+      const u32 words = psize_words(width), incl = wave_inclusive_sum(words), total = lane_value(incl, 63);     // (at most 64 x 256)
+      const u32 shape = lane_value(o.shape, s);
+      cur.src0 = 0;
+      cur.room = lane_value(o.room, s);
+      cur.span = (shape & 3u) + total;
+      cur.pick = (shape & 3u) + incl - words;
+      cur.w = width;
+      if (__any(width > width_limit(c, s)) || (IX ? total != shape >> 2 : cur.span > cur.room)) {      // uniform; see place_operand
+        if (IX) err |= status_bit(ZC_ERR_FORMAT);
+        cur.w = cur.span = 0;
+      }
+    }
+    u32 code = u32(__builtin_amdgcn_raw_buffer_load_b32(outliers_buffer(o, c, s, true), int(4u * b), 0, 0));
     if (!__any(cur.w > 15)) {
       const OperandStage stage = load_operand_payload(payload, cur, lane);
-      if (s + PARTS < a.k) width = load_operand_width(a.in[s + PARTS].base, c, b);
+      if (s + PARTS < a.k) width = u32(__builtin_amdgcn_raw_buffer_load_b8(widths_buffer(o, c, s + PARTS, true), int(b), 0, 0));
       stage_to_lds(stage, cur, payload, wl, lane);
       wave_lds_sync();
       u32 f[16];
       const u32* const mine = wl + (cur.w ? cur.pick : 0u);
 #pragma unroll
-      for (int p = 0; p < 16; ++p) f[p] = mine[p];
-      keep_operand_words(cur.w, f, f);
+      for (int p = 0; p < 15; ++p) f[p] = mine[1 + p];
+      f[15] = mine[0];
       wave_lds_sync();
-      magnitude_planes_to_twos<16>(f);
-      transpose16x16_pairs(f);
+      deltas_from_raw_planes16(f, cur.w);
 #pragma unroll
       for (int j = 0; j < 32; ++j) {
         code += u32(__builtin_amdgcn_sbfe(i32(f[j & 15]), u32(16 * (j >> 4)), 16u));
         acc[j] = extreme<OP>(acc[j], i32(code));
       }
     } else {
-      if (s + PARTS < a.k) width = load_operand_width(a.in[s + PARTS].base, c, b);
+      if (s + PARTS < a.k) width = u32(__builtin_amdgcn_raw_buffer_load_b8(widths_buffer(o, c, s + PARTS, true), int(b), 0, 0));
       u32 lo[16], hi[16];                       // planes 0..15; planes 16..30 and the sign word
 #pragma unroll
       for (int p = 0; p < 16; ++p) lo[p] = hi[p] = 0;
