@@ -2,7 +2,7 @@
 // sign + plane packing, single-pass placement of the variable-size blocks.
 //
 // Work split.  A tile is 512 blocks (16384 values, 64 KiB of input) handled by a workgroup of
-// 8 waves.  Each wave loads 2048 consecutive values with 16-byte loads,
+// 8 waves (256 and 4 where that shortens the call, see packs_small_tiles).  Each wave loads 2048 consecutive values with 16-byte loads,
 // quantises them where they land, and transposes the integer codes through LDS so that one
 // lane owns one block.  Deltas (kept as 16 words of paired 16-bit fields), width and the
 // bit-matrix transpose that yields the plane words are then in-lane; the packed words wait

@@ -682,7 +682,7 @@ __device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall&
 // What every workgroup of a reduce kernel does first: the call's verdict, tag and header, and its tile.
 // Returns false when the workgroup has nothing (more) to do.  The headers, and the width tables of plain streams, are
 // judged here, by every workgroup alike.
-// The segments' places in all operands are found here too.  `width0`, `early`: see sum_common.
+// The segments' places in all operands are found here too.  `width0`, `early`: see sum_operands.
 // SEGS: segments of a tile, wave i of the workgroup on segment i % SEGS of its tile; TICKETS: tiles may be handed out by tickets.
 template <bool IX, int SEGS = kTileWaves, bool TICKETS = true>
 __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& width0, bool early, u32& tile, u32& ntiles,
@@ -778,7 +778,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
 // per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
 // but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
-// 80 registers and 24 bytes of scratch (plain streams: 96 and 28), which the common path touches behind its
+// 80 registers and 28 bytes of scratch (plain streams: 96 and 36), which the common path touches behind its
 // operand loop only: what the placement needs waits there.
 template <bool IX>
 __device__ __forceinline__ void reduce_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kTileWaves * kWholeStage + kCopyOver], u32& sh_tile,
@@ -788,7 +788,7 @@ __device__ __forceinline__ void reduce_tile(const ReduceArgs& a, ReduceCall& c, 
   // together with the headers, before it knows them: one memory
   // round trip instead of two.  The loads are fenced in by sizes the host passed.  (Not for
   // indexed streams: where their width bytes are is only known with the header.  But where their segments are is, see
-  // ask_segment_ends, and with that the widths and the payload are asked for together.)
+  // ask_headers, and with that the widths and the payload are asked for together.)
   const bool early = !a.ticketed && !IX;
   u32 tile = 0, ntiles = 0;
   if (!open_reduce<IX>(a, c, width0, early, tile, ntiles, &sh_tile, &survey)) return;

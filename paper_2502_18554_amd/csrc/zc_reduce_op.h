@@ -22,13 +22,13 @@
 // than 15 bits does so from the start, in all its waves (extreme_any).
 // Measured, 8 x 2^24 values unless said otherwise, first with codes unpacked throughout (145 registers, three waves
 // per SIMD, and a kernel of its own for wide blocks, launched with every call), then now:
-//   smooth field, bound 1e-4 of its range                     79.5   56.0 us
+//   smooth field, bound 1e-4 of its range                     79.5   55.5 us
 //   8 x 2^23 (1024 tiles)                                     36.2   32.9
-//   16 x 2^20                                                 29.7   24.4
-//   hard data, 4 x 4 000 000                                  28.2   15.6
-//   8 x 1000                                                  18.7   12.8
-// (the last four: before payloads went straight to LDS and loads were trimmed, see OperandPipe and load_operand_meta).
-// 122 registers, four waves per SIMD, and 12 bytes of scratch that only the
+//   16 x 2^20                                                 29.7   15.2
+//   hard data, 4 x 4 194 304                                  28.2   15.5
+//   8 x 1000                                                  18.7    7.6
+// (before: those ahead of payloads that go straight to LDS and of trimmed loads, see OperandPipe; the last three are tiles of fewer segments now, see few_op_segments).
+// 128 registers, four waves per SIMD, and 12 bytes of scratch that only the
 // wide blocks' loop and the ends of the others touch.  It pays that the segment number is a scalar and the lane number
 // is computed where it is used: with both in registers across the loops these spilled 240 bytes, and every reload waits
 // for the loads under way.
