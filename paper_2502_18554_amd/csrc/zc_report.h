@@ -70,7 +70,10 @@ inline bool report_words(ReportSlots& slots, const u64* const* from, u32 count, 
 // heads, k: the streams whose n (the second word of a header) follow the call's own words.
 __device__ __forceinline__ void give_answer(const Answer& an, const Control* ctl, const StreamRef* heads = nullptr, int k = 0) {
   if (!an.to) return;       // uniform
-  __syncthreads();          // every wave's stores are done
+  // Every wave waits for its own stores and atomics first: a barrier orders LDS, and whether the compiler puts a wait for memory in front
+  // of it differs from kernel to kernel; the words read below, and the output that the caller may read next, need it.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
   if (wave_id() != 0) return;
   const int lane = lane_id();
   const u64* const own = lane == 0 ? &ctl->status : lane == 1 ? &ctl->call_tag : &ctl->result;
