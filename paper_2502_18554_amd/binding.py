@@ -95,18 +95,20 @@ def _p(t):
     return t.data_ptr() if t is not None else None
 
 
-# The lists of a call with k streams, one behind the other in memory: the words and their address, k of them (8 * k bytes) a list.  (16 buffers of
-# a few thousand values decompressed 11.5 us with a ctypes array for each list, now 9.0.)
+# The lists of a call with k streams (any sequences of whole numbers, arrays and tensors among them), one behind the other in memory: the
+# words and their address, k of them (8 * k bytes) a list.  (16 buffers of a few thousand values decompressed 11.5 us with a ctypes array for
+# each list, now 9.0.)
 def _lists(k, *lists):
     flat = []
     for values in lists:
         if not hasattr(values, "__len__"):
             values = [*values]
-        if len(values) != k:                     # more than k are an error; what is missing is zeros, which the calls refuse
-            if len(values) > k:
-                raise IndexError("more entries than streams")
-            values = [*values] + [0] * (k - len(values))
-        flat += values
+        missing = k - len(values)
+        if missing < 0:
+            raise IndexError("more entries than streams")
+        flat.extend(values)                      # (not +=, by which an array is added to the entries)
+        if missing:
+            flat.extend([0] * missing)           # which the calls refuse
     try:
         words = array("Q", flat)
     except (TypeError, OverflowError):

@@ -207,3 +207,21 @@ def test_calls_from_two_threads_share_no_setting(libzc):
     for t in threads:
         t.join()
     assert not failures, failures[:5]
+
+
+@pytest.mark.parametrize("k", [1, 2, 5, 64])
+def test_lists_of_a_call_with_k_streams(k):
+    """Sizes and capacities may come in any kind of sequence; each list is k words, in the order given."""
+    import torch
+    from paper_2502_18554_amd.binding import _lists
+    a = [0x7F0000000000 + 16 * i for i in range(k)]
+    b = [1000 + 7 * i for i in range(k)]
+    for make in (list, tuple, iter, np.array, lambda v: np.array(v, dtype=np.uint64), lambda v: np.array(v, dtype=np.float64), torch.tensor,
+                 lambda v: [np.int64(x) for x in v], lambda v: [float(x) for x in v], lambda v: dict.fromkeys(v).keys()):
+        words, at = _lists(k, a, make(b), make(b))
+        assert words.tolist() == a + b + b and at == words.buffer_info()[0]
+    assert _lists(k, a, [-1] * k)[0].tolist() == a + [2**64 - 1] * k          # as a size_t takes it
+    assert _lists(k, a, b[:-1], b)[0].tolist() == a + b[:-1] + [0] + b        # what is missing is zeros
+    for more in (b + [1], np.array(b + [1])):
+        with pytest.raises(IndexError):
+            _lists(k, a, more)
