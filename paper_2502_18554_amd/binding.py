@@ -99,11 +99,12 @@ def _p(t):
 # words and their address, k of them (8 * k bytes) a list.  (16 buffers of a few thousand values decompressed 11.5 us with a ctypes array for
 # each list, now 9.0.)
 def _lists(k, *lists):
+    room = k if k > 1 else 1                     # (no streams are for the call to refuse)
     flat = []
     for values in lists:
         if not hasattr(values, "__len__"):
             values = [*values]
-        missing = k - len(values)
+        missing = room - len(values)
         if missing < 0:
             raise IndexError("more entries than streams")
         flat.extend(values)                      # (not +=, by which an array is added to the entries)

@@ -225,3 +225,14 @@ def test_lists_of_a_call_with_k_streams(k):
     for more in (b + [1], np.array(b + [1])):
         with pytest.raises(IndexError):
             _lists(k, a, more)
+
+
+def test_a_call_of_no_streams_is_refused(libzc):
+    import types
+    from paper_2502_18554_amd import binding
+    buf = types.SimpleNamespace(data_ptr=lambda: 0x3000, nbytes=1 << 20, numel=lambda: 1 << 18)
+    stream = types.SimpleNamespace(cuda_stream=0)
+    for sizes in ([], [100], np.array([100])):
+        assert binding.zc_reduce_compressed([], sizes, buf, buf, stream=stream) == (binding.ZC_ERR_ARG, 0)
+        assert binding.zc_reduce_compressed_op([], sizes, 1, buf, buf, stream=stream) == (binding.ZC_ERR_ARG, 0)
+        assert binding.zc_decompress_many([], sizes, [], buf, stream=stream)[0] == binding.ZC_ERR_ARG
