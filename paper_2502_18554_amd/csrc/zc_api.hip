@@ -558,7 +558,8 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   ra.coherent = (flags & ZC_CHAINS_COHERENT) != 0;
   ra.nonce = call_nonce();
   ra.first_tile = ra.end_tile = ra.adopt = 0;
-  ra.n_part = 0;
+  ra.n_least = 0;
+  ra.n_most = (l.tiles_cap < kMaxTiles ? l.tiles_cap : kMaxTiles) * u64(kTileValues);
   if (ranged) {
     // parts are laid out in tiles of the reduce kernel; only indexed streams can be taken up in parts
     if (!ix || op != ZC_OP_SUM || n > ZC_MAX_N || n == 0 || first_value % kTileValues != 0 || first_value >= n ||
@@ -571,7 +572,7 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     ra.first_tile = u32(first_value / kTileValues);
     ra.end_tile = to_the_end ? u32(all_tiles) : u32((first_value + count) / kTileValues);
     ra.adopt = first_value != 0;
-    ra.n_part = n;
+    ra.n_least = ra.n_most = n;
     tiles = ra.end_tile - ra.first_tile;
   }
   void (*kernel)(ReduceArgs) = ix ? reduce_kernel<true> : reduce_kernel<false>;

@@ -49,7 +49,9 @@ struct ReduceArgs {
   // (adopt) belongs to the call whose tag the first part left in the control block.
   u32 first_tile, end_tile, adopt;
   Answer answer;
-  u64 n_part;        // a reduce done in parts: the n the caller laid the parts out for (the streams must have it); else 0
+  // The n that the call takes: of a reduce done in parts the one that the parts were laid out for; else any that has a descriptor in the
+  // workspace for each of its tiles.
+  u64 n_least, n_most;
 };
 
 // What a workgroup knows about the call once the headers are judged.
@@ -727,10 +729,10 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
     }
     return false;
   }
-  if (a.n_part && a.n_part != c.h.n) {      // the parts were laid out for another n
+  if (c.h.n < a.n_least || c.h.n > a.n_most) {
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       if (!a.adopt) a.ctl->result = 0;
-      raise_status(a.ctl, c.tag, status_bit(ZC_ERR_MISMATCH));
+      raise_status(a.ctl, c.tag, status_bit(a.n_least ? ZC_ERR_MISMATCH : ZC_ERR_ARG));
     }
     return false;
   }

@@ -250,6 +250,31 @@ def test_a_refused_call_reports_a_size_of_nothing(zcref, stream_variant, tiles):
         assert zc.zc_reduce_compressed_part([d_ref], [ref.size], n - 1, 0, TILE, d_out, ws) == (ZC_ERR_MISMATCH, 0)
 
 
+
+@pytest.mark.parametrize("tickets", [False, True])
+@pytest.mark.parametrize("k", [1, 2, 5, 12])
+def test_a_reduce_in_too_small_a_workspace_is_refused(zcref, k, tickets):
+    """n is only known on the GPU, from the streams: every tile of the result needs a place in the workspace."""
+    u = gpuutil
+    n = 40 * TILE - 2049
+    ref = zcref.compress(_values(n, 91), 1e-3)[1]
+    d_refs, sizes = [u.to_dev(ref)] * k, [ref.size] * k
+    d_out = torch.empty(u.zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
+    u.set_tickets(tickets)
+    try:
+        for small in (1, 16 * TILE, 23 * TILE):
+            ws = u.workspace(small, k)
+            for op in (0, 1, 2):
+                ws.fill_(0x5A)
+                assert u.zc.zc_reduce_compressed_op(d_refs, sizes, op, d_out, ws) == (ZC_ERR_ARG, 0), (small, op)
+        for op in (0, 1, 2):
+            want = zcref.reduce([ref] * k, op=op)[1]
+            st, total = u.zc.zc_reduce_compressed_op(d_refs, sizes, op, d_out, u.workspace(n, k))
+            assert st == ZC_OK and d_out[:total].cpu().numpy().tobytes() == want.tobytes(), op
+    finally:
+        u.set_tickets(False)
+
+
 # Sums of few tiles: four segments of a tile by a wave each, two by two and one by four that share its operands; a wave's last batch of
 # operands of every size, several batches, one side of every limit and the other; blocks of all classes of widths, and (wide) so many
 # wide blocks that they do not fit a wave's place for them; a segment count that is no multiple of a tile's.  Max and Min the same way.
