@@ -121,6 +121,7 @@ class CallAnswer {
     slot_ = g_reports.take(may_pin);
     if (slot_) seq_ = g_reports.next_seq();
   }
+  bool by_kernel() const { return slot_ != nullptr; }
   Answer arg() const { return {slot_, seq_}; }
   // The launches are enqueued (or not).  See finish.
   int collect(bool launched, const void* d_ws, size_t* result, hipStream_t stream, bool wanted, bool may_pin = true, const u64* const* more = nullptr,
@@ -292,6 +293,28 @@ void (*pick_op_kernel(bool ix, int segs))(ReduceArgs) {
   if (segs == 1) return ix ? reduce_op_kernel<true, OP, 1> : reduce_op_kernel<false, OP, 1>;
   if (segs == 2) return ix ? reduce_op_kernel<true, OP, 2> : reduce_op_kernel<false, OP, 2>;
   return ix ? reduce_op_kernel<true, OP> : reduce_op_kernel<false, OP>;
+}
+// segs: 0: not by reduce_few_kernel.
+void (*pick_sum_kernel(bool ix, int segs, u64 likely))(ReduceArgs) {
+  if (segs == 1) return ix ? reduce_few_kernel<true, 1, 4> : reduce_few_kernel<false, 1, 4>;
+  if (segs == 2) return ix ? reduce_few_kernel<true, 2, 4> : reduce_few_kernel<false, 2, 4>;
+  if (segs && likely <= kFewTiles) return ix ? reduce_few_kernel<true, 4, 4> : reduce_few_kernel<false, 4, 4>;
+  if (segs) return reduce_few_kernel<true, 4, 2>;
+  return ix ? reduce_kernel<true> : reduce_kernel<false>;
+}
+// The same for calls of one workgroup that answer themselves.  (That is one tile of four segments: no tickets, and none of the Sums, Maxima and Minima whose
+// tiles have fewer.)
+template <int OP>
+void (*answering_step_kernel(bool ix))(StepArgs, Answer) {
+  return ix ? step_kernel<true, false, OP, false, 5, Answer> : step_kernel<false, true, OP, false, 5, Answer>;
+}
+template <int OP>
+void (*answering_op_kernel(bool ix))(ReduceArgs, Answer) {
+  return ix ? reduce_op_kernel<true, OP, kTileWaves, Answer> : reduce_op_kernel<false, OP, kTileWaves, Answer>;
+}
+void (*answering_sum_kernel(bool ix, int segs))(ReduceArgs, Answer) {
+  if (segs) return ix ? reduce_few_kernel<true, 4, 4, Answer> : reduce_few_kernel<false, 4, 4, Answer>;
+  return ix ? reduce_kernel<true, Answer> : reduce_kernel<false, Answer>;
 }
 template <bool AVERAGE>
 void (*pick_decompress_kernel(bool ix, bool self))(DecompressArgs) {
@@ -554,7 +577,7 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   ra.out_cap = out_cap;
   ra.ctl = l.ctl;
   ra.desc = l.desc;
-  ra.ticketed = (flags & ZC_TILES_BY_TICKET) != 0;
+  ra.ticketed = (flags & ZC_TILES_BY_TICKET) != 0 && (ranged || tiles > 1);      // (one tile has no other to wait for)
   ra.coherent = (flags & ZC_CHAINS_COHERENT) != 0;
   ra.nonce = call_nonce();
   ra.first_tile = ra.end_tile = ra.adopt = 0;
@@ -575,22 +598,19 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     ra.n_least = ra.n_most = n;
     tiles = ra.end_tile - ra.first_tile;
   }
-  void (*kernel)(ReduceArgs) = ix ? reduce_kernel<true> : reduce_kernel<false>;
-  if (op == ZC_OP_SUM) {
-    const int segs = ranged || ra.ticketed ? 0 : few_segments(k, likely);
-    if (segs == 1) kernel = ix ? reduce_few_kernel<true, 1, 4> : reduce_few_kernel<false, 1, 4>;
-    else if (segs == 2) kernel = ix ? reduce_few_kernel<true, 2, 4> : reduce_few_kernel<false, 2, 4>;
-    else if (segs == 4 && likely <= kFewTiles) kernel = ix ? reduce_few_kernel<true, 4, 4> : reduce_few_kernel<false, 4, 4>;
-    else if (segs == 4 && ix) kernel = reduce_few_kernel<true, 4, 2>;
-    if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
-  } else {
-    const int segs = ranged || ra.ticketed ? 4 : few_op_segments(k, likely);
-    kernel = op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs) : pick_op_kernel<ZC_OP_MIN>(ix, segs);
-    tiles = tiles * u64(kTileWaves) / u64(segs);
-  }
+  int segs = 0;
+  if (op != ZC_OP_SUM) segs = ranged || ra.ticketed ? kTileWaves : few_op_segments(k, likely);
+  else if (!ranged && !ra.ticketed) segs = few_segments(k, likely);
+  if (op == ZC_OP_SUM && likely > kFewTiles && !ix) segs = 0;
+  if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
   CallAnswer answer(out_bytes && !ranged, tiles, stream);
-  ra.answer = answer.arg();
-  launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
+  if (answer.by_kernel()) {
+    void (*kernel)(ReduceArgs, Answer) = op == ZC_OP_SUM ? answering_sum_kernel(ix, segs) : op == ZC_OP_MAX ? answering_op_kernel<ZC_OP_MAX>(ix) : answering_op_kernel<ZC_OP_MIN>(ix);
+    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(1), dim3(kTileThreads), stream, ra, answer.arg());
+  } else {
+    void (*kernel)(ReduceArgs) = op == ZC_OP_SUM ? pick_sum_kernel(ix, segs, likely) : op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs) : pick_op_kernel<ZC_OP_MIN>(ix, segs);
+    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
+  }
   return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr);
 }
 
@@ -652,7 +672,7 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   ta.out_cap = out_cap;
   ta.ctl = l.ctl;
   ta.desc = l.desc;
-  ta.ticketed = (flags & ZC_TILES_BY_TICKET) != 0;
+  ta.ticketed = (flags & ZC_TILES_BY_TICKET) != 0 && (ranged || tiles > 1);      // (one tile has no other to wait for)
   ta.coherent = (flags & ZC_CHAINS_COHERENT) != 0;
   ta.nonce = call_nonce();
   ta.first_tile = ta.end_tile = ta.adopt = 0;
@@ -667,14 +687,18 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
     ta.adopt = first_value != 0;
     tiles = ta.end_tile - ta.first_tile;
   }
-  void (*kernel)(StepArgs) = nullptr;
-  const bool tickets = ta.ticketed != 0;
-  if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, self, tickets, tiles);
-  else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, self, tickets, tiles);
-  else kernel = pick_step_kernel<ZC_OP_MIN>(ix, self, tickets, tiles);
-  CallAnswer answer(out_bytes && !ranged, tiles, stream);
-  ta.answer = answer.arg();
-  launch_main(ZC_KERNEL_REDUCE_STEP, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ta);
+  CallAnswer answer(out_bytes && !ranged && (ix || self), tiles, stream);
+  if (answer.by_kernel()) {
+    void (*kernel)(StepArgs, Answer) = op == ZC_OP_SUM ? answering_step_kernel<ZC_OP_SUM>(ix) : op == ZC_OP_MAX ? answering_step_kernel<ZC_OP_MAX>(ix) : answering_step_kernel<ZC_OP_MIN>(ix);
+    launch_main(ZC_KERNEL_REDUCE_STEP, kernel, dim3(1), dim3(kTileThreads), stream, ta, answer.arg());
+  } else {
+    void (*kernel)(StepArgs) = nullptr;
+    const bool tickets = ta.ticketed != 0;
+    if (op == ZC_OP_SUM) kernel = pick_step_kernel<ZC_OP_SUM>(ix, self, tickets, tiles);
+    else if (op == ZC_OP_MAX) kernel = pick_step_kernel<ZC_OP_MAX>(ix, self, tickets, tiles);
+    else kernel = pick_step_kernel<ZC_OP_MIN>(ix, self, tickets, tiles);
+    launch_main(ZC_KERNEL_REDUCE_STEP, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ta);
+  }
   return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr);
 }
 

@@ -48,7 +48,6 @@ struct ReduceArgs {
   // [first_tile, end_tile) of the output, end_tile = 0 meaning all of them; a later part
   // (adopt) belongs to the call whose tag the first part left in the control block.
   u32 first_tile, end_tile, adopt;
-  Answer answer;
   // The n that the call takes: of a reduce done in parts the one that the parts were laid out for; else any that has a descriptor in the
   // workspace for each of its tiles.
   u64 n_least, n_most;
@@ -782,9 +781,16 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
 // 80 registers and 28 bytes of scratch (plain streams: 96 and 36), which the common path touches behind its
 // operand loop only: what the placement needs waits there.
-template <bool IX>
-__device__ __forceinline__ void reduce_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kTileWaves * kWholeStage + kCopyOver], u32& sh_tile,
-                                            u32 (&sh_wave_total)[kTileWaves], u64 (&sh_base)[kTileWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
+template <bool IX, typename... A>
+__global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a, A... answer) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage + kCopyOver];   // also holds an operand's payload
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[kTileWaves];
+  __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
+  const AnswerAtEnd<ReduceArgs, A...> at_end(a, answer...);
+
+  ReduceCall c;
   u32 width0 = 0;
   // A workgroup that takes the tile of its own number asks for the first operand's widths
   // together with the headers, before it knows them: one memory
@@ -817,18 +823,6 @@ __device__ __forceinline__ void reduce_tile(const ReduceArgs& a, ReduceCall& c, 
   }
   if (common) reduce_common_tile<IX>(a, c, tile, ntiles, width0, early, lds, sh_wave_total, sh_base);
   else reduce_wide_tile<IX>(a, c, sum_sink(a, c, ntiles, IX), tile, ntiles, lds + wave_id() * kWholeStage, sh_wave_total, sh_base);
-}
-
-template <bool IX>
-__global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage + kCopyOver];   // also holds an operand's payload
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[kTileWaves];
-  __shared__ u64 sh_base[kTileWaves];
-  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
-  ReduceCall c;
-  reduce_tile<IX>(a, c, lds, sh_tile, sh_wave_total, sh_base, survey);
-  give_answer(a.answer, a.ctl);
 }
 
 }  // namespace zc

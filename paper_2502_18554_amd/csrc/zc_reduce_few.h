@@ -251,9 +251,16 @@ __host__ constexpr int few_segments(int k, u64 tiles) {
   return tiles <= kFewTiles || (k <= 4 && tiles <= kFewTilesFull) ? 4 : 0;
 }
 
-template <bool IX, int SEGS, int AREAS>
-__device__ __forceinline__ void reduce_few_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kFewWaves * AREAS * kFewArea], SumParts<SEGS, kFewWaves / SEGS>& parts,
-                                                u32 (&sh_wave_total)[SEGS], u64 (&sh_base)[kFewWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
+template <bool IX, int SEGS, int AREAS, typename... A>
+__global__ __launch_bounds__(kFewThreads, AREAS > 2 ? 2 : 4) void reduce_few_kernel(ReduceArgs a, A... answer) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kFewWaves * AREAS * kFewArea];
+  __shared__ SumParts<SEGS, kFewWaves / SEGS> parts;
+  __shared__ u32 sh_wave_total[SEGS];
+  __shared__ u64 sh_base[kFewWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
+  const AnswerAtEnd<ReduceArgs, A...> at_end(a, answer...);
+
+  ReduceCall c;
   constexpr int PARTS = kFewWaves / SEGS;
   static_assert(AREAS * kFewArea >= kWholeStage + kCopyOver, "the output's words lie there too");
   u32 tile = 0, ntiles = 0, none = 0;
@@ -355,18 +362,6 @@ __device__ __forceinline__ void reduce_few_tile(const ReduceArgs& a, ReduceCall&
   const int lane = fresh_lane();
   const u32 b = seg * kWaveBlocks + u32(lane);
   place_sum_staged<kSumPlanes>(a, c, sink, sum.acc, sgn, w, sum.outlier, b < c.h.nb, b, tile, ntiles, word, wl, sh_wave_total, sh_base, wave, lane);
-}
-
-template <bool IX, int SEGS, int AREAS>
-__global__ __launch_bounds__(kFewThreads, AREAS > 2 ? 2 : 4) void reduce_few_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kFewWaves * AREAS * kFewArea];
-  __shared__ SumParts<SEGS, kFewWaves / SEGS> parts;
-  __shared__ u32 sh_wave_total[SEGS];
-  __shared__ u64 sh_base[kFewWaves];
-  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
-  ReduceCall c;
-  reduce_few_tile<IX, SEGS, AREAS>(a, c, lds, parts, sh_wave_total, sh_base, survey);
-  give_answer(a.answer, a.ctl);
 }
 
 }  // namespace zc

@@ -536,9 +536,16 @@ __host__ constexpr int few_op_segments(int k, u64 tiles) {
 }
 
 // SEGS: segments of a tile.  Their operands are divided among PARTS = 4 / SEGS waves each, whose extremes meet in LDS: see zc_reduce_few.h.
-template <bool IX, int OP, int SEGS>
-__device__ __forceinline__ void reduce_op_tile(const ReduceArgs& a, ReduceCall& c, u32 (&lds)[kTileWaves * kExtremeStage], u32& sh_tile,
-                                               u32 (&sh_wave_total)[SEGS], u64 (&sh_base)[kTileWaves], PlainSurvey<IX ? 1 : ZC_MAX_K>& survey) {
+template <bool IX, int OP, int SEGS = kTileWaves, typename... A>
+__global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a, A... answer) {
+  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kExtremeStage];
+  __shared__ u32 sh_tile;
+  __shared__ u32 sh_wave_total[SEGS];
+  __shared__ u64 sh_base[kTileWaves];
+  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
+  const AnswerAtEnd<ReduceArgs, A...> at_end(a, answer...);
+
+  ReduceCall c;
   constexpr int PARTS = kTileWaves / SEGS;
   u32 width0 = 0, tile = 0, ntiles = 0;
   if (!open_reduce<IX, SEGS, PARTS == 1>(a, c, width0, false, tile, ntiles, &sh_tile, &survey)) return;
@@ -626,18 +633,6 @@ __device__ __forceinline__ void reduce_op_tile(const ReduceArgs& a, ReduceCall& 
   }
   store_tables<kAccessOnce>(sink, b, pl.w, eb.outlier);     // (at the very end: a store under way is waited for by every poll of the look-back)
   finish_stream<SEGS>(sink, pl, tile, ntiles, tb);
-}
-
-template <bool IX, int OP, int SEGS = kTileWaves>
-__global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a) {
-  __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kExtremeStage];
-  __shared__ u32 sh_tile;
-  __shared__ u32 sh_wave_total[SEGS];
-  __shared__ u64 sh_base[kTileWaves];
-  __shared__ PlainSurvey<IX ? 1 : ZC_MAX_K> survey;
-  ReduceCall c;
-  reduce_op_tile<IX, OP, SEGS>(a, c, lds, sh_tile, sh_wave_total, sh_base, survey);
-  give_answer(a.answer, a.ctl);
 }
 
 }  // namespace zc

@@ -85,4 +85,20 @@ __device__ __forceinline__ void give_answer(const Answer& an, const Control* ctl
   if (lane == 0) __hip_atomic_store(&an.to->seq, an.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// The same for a kernel that has an instance for the calls that it answers, with an argument more (A = Answer), and one for all others (no A), in which this
+// is nothing: what ends the kernel, wherever it returns.  The kernels that reduce are such: with one instance, whose arguments said whether somebody waits, a Sum
+// of one buffer of 2^20 values took 8.3 us, now 8.1, of 16 of them 12.9 and 12.6, and a ring round of 2^24 values by ticket 40.1 and 38.3.  (The
+// compression and the decompression measure the same either way.)
+template <typename Args, typename... A>
+struct AnswerAtEnd {
+  __device__ __forceinline__ AnswerAtEnd(const Args&) {}
+};
+template <typename Args>
+struct AnswerAtEnd<Args, Answer> {
+  const Args& a;
+  const Answer& answer;
+  __device__ __forceinline__ AnswerAtEnd(const Args& args, const Answer& an) : a(args), answer(an) {}
+  __device__ __forceinline__ ~AnswerAtEnd() { give_answer(answer, a.ctl); }
+};
+
 }  // namespace zc

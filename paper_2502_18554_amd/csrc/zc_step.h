@@ -54,7 +54,6 @@ struct StepArgs {
   // of the output, end_tile = 0 meaning all of them; a later part (adopt) belongs to the call whose
   // tag the first part left in the control block.
   u32 first_tile, end_tile, adopt;
-  Answer answer;
 };
 
 // LDS of one wave: 64 rows (blocks) of 16 local values + 4 words of padding (an odd number of
@@ -660,15 +659,17 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, u32 (&lds)[kTileWav
   finish_stream<kTileWaves>(sink, pl, tile, ntiles, tb);
 }
 
-template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5>
-__global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a) {
+template <bool IX, bool SELF, int OP, bool TICKETS, int GROUPS = 5, typename... A>
+__global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a, A... answer) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kStepStage + kCopyOver];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[kTileWaves];
   __shared__ u64 sh_base[kTileWaves];
   __shared__ PlainSurvey<1> survey;
-  step_tile<IX, SELF, OP, TICKETS, GROUPS>(a, lds, sh_tile, sh_wave_total, sh_base, survey);
-  give_answer(a.answer, a.ctl);
+  const AnswerAtEnd<StepArgs, A...> at_end(a, answer...);
+  // (The arguments where they lie, see kernel_args, but for plain streams by workgroup id.)
+  if constexpr (IX || TICKETS) step_tile<IX, SELF, OP, TICKETS, GROUPS>(kernel_args<StepArgs>(), lds, sh_tile, sh_wave_total, sh_base, survey);
+  else step_tile<IX, SELF, OP, TICKETS, GROUPS>(a, lds, sh_tile, sh_wave_total, sh_base, survey);
 }
 
 }  // namespace zc
