@@ -289,9 +289,11 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
 //   sinusoids at 1e-4   1000 values 5.6 5.1 | 2^20: 6.6 5.4 | 2 000 003: 7.0 6.3 | 3 000 000: 7.1 6.8 | 5 000 000: 9.4 8.2 | 6 500 000: 9.5 9.7
 //   a field at 1e-4     1000 values 6.0 5.3 | 2^20: 6.8 5.8 | 2 000 003: 7.2 6.5 | 3 400 000: 7.6 7.8 | 5 000 000: 10.3 9.0 | 6 500 000: 10.5 10.7
 //   hard data           1000 values 5.7 4.6 | 2^20: 8.8 7.4 | 2 000 003: 9.1 7.7 | 3 000 000: 9.2 9.0 | 5 000 000: 11.7 10.2 | 8 000 000: 13.2 12.9
+// With ZC_CHAINS_COHERENT, whose look-back takes longer the more tiles there are, only the former: a field at 1e-4, 2 090 000 values 10.0 9.7 | 4 300 000: 12.0 12.4 |
+// 6 200 000: 13.7 14.4; hard data 11.9 11.2 | 13.8 14.1 | 15.7 16.2.
 __host__ inline bool packs_small_tiles(const CompressArgs& a) {
   const u64 tiles = num_tiles(a.nb);
-  return !a.ticketed && (tiles <= 256 || (tiles > 512 && tiles <= 768));
+  return !a.ticketed && (tiles <= 256 || (tiles > 512 && tiles <= 768 && !a.coherent));
 }
 
 template <bool TICKETS, int WAVES>

@@ -46,6 +46,16 @@ def test_compress_and_reduce_with_coherent_chains(zcref):
         assert st == st_ref == ZC_OK and step.tobytes() == step_ref.tobytes(), u.first_diff(step, step_ref)
 
 
+@pytest.mark.parametrize("tiles", [255, 256, 257, 513, 768, 769])
+def test_compression_with_coherent_chains(zcref, tiles):
+    """Both sides of the sizes at which the compressor's tiles are of four waves, here and without coherent chains."""
+    u = gpuutil
+    x = synth.sinusoids(tiles * TILE - 4097, seed=tiles).numpy()
+    st_ref, ref = zcref.compress(x, 1e-3)[:2]
+    st, s, total = u.gpu_compress(x, 1e-3)
+    assert st == st_ref == ZC_OK and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
+
+
 def test_wide_tiles_with_coherent_chains(zcref):
     """Blocks wider than 15 bits take the kernels' other paths, which look back the same way."""
     u = gpuutil
