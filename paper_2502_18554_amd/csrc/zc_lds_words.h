@@ -27,7 +27,6 @@ struct LaneOperands {
   u32 bytes;                     // indexed streams: whole 16-byte pieces to bring
   u64 tails;                     // indexed streams, bit s: there is more to bring (see fetch_payload_end)
 };
-constexpr u32 kNoWords = 0x3fffffffu;     // more than any widths add up to
 
 // most: words of the longest segment, and three.
 template <bool IX>

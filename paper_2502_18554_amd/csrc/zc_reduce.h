@@ -247,19 +247,35 @@ __device__ inline u32 payload_room(u64 bytes, const ReduceCall& c) {
 constexpr int kStageLoads = 4;
 constexpr u32 kMostStaged = 256u * kStageLoads + 64u;
 
-// Where operand s has the wave's segment.  An indexed stream (ix) says so by itself, and how long the segment is, so that its
-// payload can be asked for before its widths are there; of a plain one only the start is known.  Everything here is the same in every lane.
-__device__ inline OperandPlace open_operand(int s, u64 bytes, const ReduceCall& c, bool ix) {
-  OperandPlace p;
-  const u32 seg_off = lane_value(c.places, s), room = payload_room(bytes, c);
-  const u32 mis = seg_off & 3u;
-  p.src0 = seg_off - mis;
-  p.room = seg_off <= room ? room - p.src0 : 0u;         // (the start is inside on a validated stream)
-  p.span = 0;
-  if (ix) {
-    const u32 words = lane_value(c.ends, s) - seg_off;
-    if (mis <= p.room && words <= p.room - mis && words <= kMostStaged - 3u) p.span = mis + words;      // (else place_operand finds that the widths say something else)
+// Lane s: words of operand s from the 16-byte boundary at or below the wave's segment on: up to the end of the caller's buffer, and of an indexed stream (IX),
+// which says so by itself, up to the segment's end, so that its payload can be asked for before its widths are there.
+// (An index that says what cannot be, of at most `most` words and three, has nothing asked for, and kNoWords for the widths to contradict.)
+constexpr u32 kNoWords = 0x3fffffffu;     // more than any widths add up to
+struct LaneSegments {
+  u32 room, span;
+};
+template <bool IX>
+__device__ inline LaneSegments lane_segments(const ReduceCall& c, u32 most = kMostStaged) {
+  const u32 mis = c.places & 3u, room = payload_room(c.bytes, c), words = c.ends - c.places;
+  LaneSegments l;
+  l.room = c.places <= room ? room - (c.places - mis) : 0u;         // (the start is inside on a validated stream)
+  l.span = 0;
+  if (IX) {
+    const bool inside = mis <= l.room && words <= l.room - mis && words <= most - 3u;
+    l.span = inside ? mis + words : kNoWords;
+    if (!inside) l.room = 0;
   }
+  return l;
+}
+
+// Where operand s has the wave's segment; of a plain stream only the start is known.  Everything here is the same in every lane.
+// (Out of lanes, where the words of all operands have been worked out at once: with that done for each operand as it came, Sum of 64 x 2^20 values by ticket
+// 77.4 us, now 69.4, of 16 x 2^20 in a workspace for more 24.0 and 22.1, of 8 x 2^26 149.6 and 146.9.)
+__device__ inline OperandPlace open_operand(int s, const ReduceCall& c, const LaneSegments& l) {
+  OperandPlace p;
+  p.src0 = lane_value(c.places, s) & ~3u;
+  p.room = lane_value(l.room, s);
+  p.span = lane_value(l.span, s);
   p.w = p.pick = p.wcap = 0;
   return p;
 }
@@ -269,24 +285,16 @@ __device__ inline OperandPlace open_operand(int s, u64 bytes, const ReduceCall& 
 // what the index says, and no block may be wider than w_max (15 where the stream promised narrow
 // blocks, or where the caller has seen that there is no other).
 __device__ inline void place_operand(OperandPlace& p, int s, u32 width, const ReduceCall& c, bool ix, u32& err, u32 w_max = 15) {
-  const u32 w = width > w_max ? 0u : width;    // plain streams: cannot happen here; keeps every LDS access in range
-  const u32 words = psize_words(w);
+  const u32 words = psize_words(width);
   const u32 incl = wave_inclusive_sum(words);
-  const u32 wave_total = lane_value(incl, 63);
-  const u32 seg_off = lane_value(c.places, s);
-  const u32 mis = seg_off & 3u;
-  // true on a validated stream
-  bool inside = mis <= p.room && wave_total <= p.room - mis;
-  if (ix) {
-    inside = p.span == mis + wave_total;
-    if (__any(width > w_max) || lane_value(c.ends, s) - seg_off != wave_total) {
-      err |= status_bit(ZC_ERR_FORMAT);
-      inside = false;
-    }
-  }
-  p.span = inside ? mis + wave_total : 0u;     // <= 3 + 64 * (1 + w_max)
+  const u32 mis = lane_value(c.places, s) & 3u;
+  const u32 span = mis + lane_value(incl, 63);           // (at most 3 + 64 x 256)
+  // true on a validated stream (plain ones: cannot happen here; keeps every LDS access in range)
+  const bool inside = !__any(width > w_max) && (ix ? span == p.span : span <= p.room);
+  if (ix && !inside) err |= status_bit(ZC_ERR_FORMAT);
+  p.span = inside ? span : 0u;                 // <= 3 + 64 * (1 + w_max)
   p.pick = mis + (incl - words);
-  p.w = inside ? w : 0u;
+  p.w = inside ? width : 0u;
   p.wcap = w_max > 15 && __any(p.w > 15) ? 24u : __any(p.w > 12) ? 16u : __any(p.w > 8) ? 12u : __any(p.w > 4) ? 8u : __any(p.w != 0) ? 4u : 0u;
 }
 
@@ -459,6 +467,7 @@ __device__ __forceinline__ void sum_operands(const ReduceArgs& a, const ReduceCa
                                              bool early, u32* wl, u32 (&acc)[kSumPlanes], u32& top, i64& outlier, u32& err) {
   const u32 w_max = c.wide_streams ? 31u : 15u;
   const u32 seg = share.seg;
+  const LaneSegments segments = lane_segments<IX>(c);
   // What travels together: an operand's payload and first codes, and of an indexed one, whose segment is found without them,
   // the widths; a plain one's widths a step ahead of the others.
   OperandPlace next;
@@ -471,7 +480,7 @@ __device__ __forceinline__ void sum_operands(const ReduceArgs& a, const ReduceCa
   {
     const int lane = fresh_lane();
     const u32 b = seg * kWaveBlocks + u32(lane);
-    next = open_operand(0, at0.bytes, c, IX);
+    next = open_operand(0, c, segments);
     if (IX) {
       width_next = load_operand_width(at0.base, c, b);
     } else {
@@ -506,7 +515,7 @@ __device__ __forceinline__ void sum_operands(const ReduceArgs& a, const ReduceCa
     outlier += i64(outlier_next);
     if (IX) place_operand(cur, s, width, c, IX, err, w_max);
     if (s + 1 < a.k) {
-      next = open_operand(s + 1, ahead1.bytes, c, IX);
+      next = open_operand(s + 1, c, segments);
       if (IX) {
         width_next = load_operand_width(ahead1.base, c, b);
       } else {
@@ -779,7 +788,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
 // per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
 // but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
-// 80 registers and 28 bytes of scratch (plain streams: 96 and 36), which the common path touches behind its
+// 80 registers and 32 bytes of scratch (plain streams: 96 and 44), which the common path touches behind its
 // operand loop only: what the placement needs waits there.
 template <bool IX, typename... A>
 __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a, A... answer) {

@@ -308,6 +308,38 @@ def test_reduces_by_waves_that_share_operands(zcref, stream_variant, k, tiles, w
         assert u.gpu_reduce(refs[:-1] + [broken], n, op=op)[0] == ZC_ERR_FORMAT
 
 
+# The same operands where the kernels for few tiles are not taken: a workspace for many more values (the tiles are told by the streams' sizes
+# then, which allow more than there are), and by ticket.  Blocks of all classes of widths, and an operand that is not in order.
+@pytest.mark.parametrize("way", ["large_workspace", "tickets"])
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("k,tiles", [(1, 1), (2, 1), (2, 70), (4, 9), (5, 65), (8, 129), (12, 17), (16, 60), (64, 3)])
+def test_reduces_of_few_tiles_by_the_other_kernels(zcref, stream_variant, k, tiles, wide, way):
+    u = gpuutil
+    n = tiles * TILE - 2049 - 31
+    g = np.random.default_rng(9 * k + tiles)
+    rough = np.repeat(10.0 ** g.uniform(-3, 1 if not wide else 3, (n + 2047) // 2048), 2048)[:n].astype(np.float32)
+    base = _values(n, 64) + rough * g.standard_normal(n).astype(np.float32)
+    refs = ([zcref.compress(np.roll(base, 4096 * i), 6e-3)[1] for i in range(min(k, 4))] * 16)[:k]
+    nb, at = (n + 31) // 32, int(g.integers(0, (n + 31) // 32))
+    broken = refs[-1].copy()
+    if stream_variant == "indexed":
+        entry = 32 + 4 * (1 + at // 64)
+        broken[entry:entry + 4] = np.frombuffer(np.uint32(int.from_bytes(broken[entry:entry + 4].tobytes(), "little") + int(g.integers(1, 1 << 31))).tobytes(), np.uint8)
+    else:
+        broken[u.widths_begin(nb) + at] = (int(broken[u.widths_begin(nb) + at]) + 1) % 31
+    assert zcref.reduce(refs[:-1] + [broken])[0] == ZC_ERR_FORMAT
+    ws = u.workspace(1 << 27 if way == "large_workspace" else n, k)
+    u.set_tickets(way == "tickets")
+    try:
+        for op in (None, 1, 2):
+            st_ref, want = zcref.reduce(refs, op=op or 0)[:2]
+            st, got, _ = u.gpu_reduce(refs, n, op=op, ws=ws)
+            assert st == st_ref == ZC_OK and got.tobytes() == want.tobytes(), (op, u.first_diff(got, want))
+            assert u.gpu_reduce(refs[:-1] + [broken], n, op=op, ws=ws)[0] == ZC_ERR_FORMAT
+    finally:
+        u.set_tickets(False)
+
+
 # calls of one workgroup that somebody waits for: the main kernel itself gives the answer, also to a call that fails
 @pytest.mark.parametrize("n", [1, 31, 2049, 8192])
 def test_calls_of_one_workgroup_answer_themselves(zcref, n):
