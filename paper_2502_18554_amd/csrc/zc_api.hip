@@ -122,7 +122,7 @@ class CallAnswer {
     if (slot_) seq_ = g_reports.next_seq();
   }
   bool by_kernel() const { return slot_ != nullptr; }
-  Answer arg() const { return {slot_, seq_}; }
+  Answer arg(const u64* more = nullptr) const { return {slot_, seq_, more}; }
   // The launches are enqueued (or not).  See finish.
   int collect(bool launched, const void* d_ws, size_t* result, hipStream_t stream, bool wanted, bool may_pin = true, const u64* const* more = nullptr,
               u32 count = 0, u64* more_out = nullptr) {
@@ -320,6 +320,10 @@ template <bool AVERAGE>
 void (*pick_decompress_kernel(bool ix, bool self))(DecompressArgs) {
   return ix ? decompress_kernel<true, false, AVERAGE> : self ? decompress_kernel<false, true, AVERAGE> : decompress_kernel<false, false, AVERAGE>;
 }
+template <bool AVERAGE>
+void (*answering_decompress_kernel(bool ix))(DecompressArgs, Answer) {
+  return ix ? decompress_kernel<true, false, AVERAGE, Answer> : decompress_kernel<false, true, AVERAGE, Answer>;
+}
 }  // namespace
 
 extern "C" {
@@ -454,11 +458,13 @@ static int decompress_one(const void* d_in, size_t in_bytes, size_t first_value,
   da.first_value = first_value;
   da.count = count;
   da.nonce = call_nonce();
-  CallAnswer answer(n_out && !ranged, grid, stream);
-  da.answer = answer.arg();
+  CallAnswer answer(n_out && !ranged && (ix || self), grid, stream);
   if (ranged) {
     void (*kernel)(DecompressArgs) = ix ? decompress_range_kernel<true, false> : self ? decompress_range_kernel<false, true> : decompress_range_kernel<false, false>;
     hipLaunchKernelGGL(kernel, dim3(u32(grid)), dim3(kTileThreads), 0, stream, da);
+  } else if (answer.by_kernel()) {
+    launch_main(ZC_KERNEL_DECOMPRESS, average ? answering_decompress_kernel<true>(ix) : answering_decompress_kernel<false>(ix), dim3(1), dim3(kTileThreads),
+                stream, da, answer.arg());
   } else {
     void (*kernel)(DecompressArgs) = average ? pick_decompress_kernel<true>(ix, self) : pick_decompress_kernel<false>(ix, self);
     launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(grid)), dim3(kTileThreads), stream, da);
@@ -519,15 +525,19 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   const bool self = !ix && index_plain_streams(da.in, k, tiles_in, tiles, l, stream);
   da.ctl = l.ctl;
   da.nonce = call_nonce();
-  void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false, false> : self ? decompress_many_kernel<false, true, false>
-                                         : k > kManyByWave ? decompress_many_kernel<false, false, true> : decompress_many_kernel<false, false, false>;
-  CallAnswer answer(n_out != nullptr, tiles * u64(k), stream);
-  da.answer = answer.arg();
-  launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(tiles), u32(k)), dim3(kTileThreads), stream, da);
   // every header that passes validation holds its stream's n: fetch them along with the status
   const u64* heads[ZC_MAX_K];
   u64 ns[ZC_MAX_K];
   for (int i = 0; i < k; ++i) heads[i] = reinterpret_cast<const u64*>(static_cast<const u8*>(d_chunks[i]) + 8);
+  CallAnswer answer(n_out && (ix || self), tiles * u64(k), stream);      // (one stream then)
+  if (answer.by_kernel()) {
+    launch_main(ZC_KERNEL_DECOMPRESS, ix ? decompress_many_kernel<true, false, false, Answer> : decompress_many_kernel<false, true, false, Answer>, dim3(1),
+                dim3(kTileThreads), stream, da, answer.arg(heads[0]));
+  } else {
+    void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false, false> : self ? decompress_many_kernel<false, true, false>
+                                         : k > kManyByWave ? decompress_many_kernel<false, false, true> : decompress_many_kernel<false, false, false>;
+    launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(tiles), u32(k)), dim3(kTileThreads), stream, da);
+  }
   const int st = answer.collect(launch_ok(), d_ws, nullptr, stream, n_out != nullptr, true, heads, u32(k), ns);
   if (!n_out) return st;
   if (st == ZC_ERR_HIP || st == ZC_ERR_ARG || st == ZC_ERR_FORMAT) return st;

@@ -27,7 +27,6 @@ struct DecompressArgs {
   u64 first_value;   // decompress_range_kernel only: the part [first_value, first_value + count) of the
   u64 count;         // stream, first_value a multiple of the values of a segment
   u64 nonce;         // drawn by the host per call, goes into the call's tag (see launch_tag)
-  Answer answer;
 };
 
 // The sign and plane words of the lane's block (width w, 0 for a block that does not exist) out
@@ -229,7 +228,7 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
                                        const StreamIndex& index, Control* ctl, u64 nonce, u32* lds, PlainSurvey<K>* survey,
                                        bool average = false, u64 first_value = 0, u64 count = ~u64(0)) {
   const StreamRef in = streams[s];
-  const DecompressArgs a{in, out_values, out_cap_elems, index, ctl, first_value, count, nonce, {}};
+  const DecompressArgs a{in, out_values, out_cap_elems, index, ctl, first_value, count, nonce};
   constexpr bool many = K > 1;
 
   // Everything that can be asked for before the header is known goes out at once: the header, the segment's position and
@@ -359,12 +358,12 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
   }
 }
 
-template <bool IX, bool SELF, bool AVERAGE>
-__global__ __launch_bounds__(kTileThreads, 5) void decompress_kernel(DecompressArgs a) {
+template <bool IX, bool SELF, bool AVERAGE, typename... A>
+__global__ __launch_bounds__(kTileThreads, 5) void decompress_kernel(DecompressArgs a, A... answer) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
   __shared__ PlainSurvey<1> survey;
+  const AnswerAtEnd<DecompressArgs, A...> at_end(a, answer...);
   decompress_tile<IX, SELF, 1>(&a.in, 1, 0, a.out, a.out_cap_elems, a.index, a.ctl, a.nonce, lds, &survey, AVERAGE);
-  give_answer(a.answer, a.ctl);
 }
 
 // A part of a stream (see decompress_tile).
@@ -386,16 +385,15 @@ struct DecompressManyArgs {
   StreamIndex index;
   Control* ctl;
   u64 nonce;
-  Answer answer;
 };
 
-template <bool IX, bool SELF, bool ROWS>
-__global__ __launch_bounds__(kTileThreads, 5) void decompress_many_kernel(DecompressManyArgs a) {
+template <bool IX, bool SELF, bool ROWS, typename... A>
+__global__ __launch_bounds__(kTileThreads, 5) void decompress_many_kernel(DecompressManyArgs a, A... answer) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
   __shared__ PlainSurvey<ZC_MAX_K> survey;
+  const AnswerAtEnd<DecompressManyArgs, A...> at_end(a, answer...);
   const int s = blockIdx.y;
   decompress_tile<IX, SELF, ZC_MAX_K, ROWS>(a.in, a.k, s, a.out[s], a.out_cap_elems[s], a.index, a.ctl, a.nonce, lds, &survey);
-  give_answer(a.answer, a.ctl, a.in, a.k);
 }
 
 }  // namespace zc
