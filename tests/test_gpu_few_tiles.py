@@ -340,7 +340,8 @@ def test_reduces_of_few_tiles_by_the_other_kernels(zcref, stream_variant, k, til
         u.set_tickets(False)
 
 
-# calls of one workgroup that somebody waits for: the main kernel itself gives the answer, also to a call that fails
+# calls of one workgroup that somebody waits for: the main kernel itself gives the answer, also to a call that fails (the reduces here are of one workgroup
+# for the smallest streams only, see the test below)
 @pytest.mark.parametrize("n", [1, 31, 2049, 8192])
 def test_calls_of_one_workgroup_answer_themselves(zcref, n):
     u = gpuutil
@@ -366,6 +367,76 @@ def test_calls_of_one_workgroup_answer_themselves(zcref, n):
             want = zcref.reduce([ref], op=op or 0)[1]
             st, s, total = u.gpu_reduce([ref], n, op=op)
             assert st == ZC_OK and total == want.size and s.tobytes() == want.tobytes()
+
+
+# reduces of one workgroup, which takes streams whose sizes allow no second tile, and ring rounds and compressions by ticket: they answer
+# themselves too, whatever the answer
+@pytest.mark.parametrize("tickets", [False, True])
+@pytest.mark.parametrize("k", [1, 2, 3, 4])
+def test_reduces_of_one_workgroup_answer_themselves(zcref, stream_variant, k, tickets):
+    u = gpuutil
+    u.set_tickets(tickets)
+    try:
+        for n in (1, 31, 700):
+            xs = [synth.sinusoids(n, seed=i).numpy() for i in range(k)]
+            refs = [zcref.compress(x, 1e-1)[1] for x in xs]
+            assert all(r.size <= 32 + 5 * 256 for r in refs)
+            for _ in range(2):
+                for op in (None, 1, 2):
+                    want = zcref.reduce(refs, op=op or 0)[1]
+                    st, s, total = u.gpu_reduce(refs, n, op=op)
+                    assert st == ZC_OK and total == want.size and s.tobytes() == want.tobytes(), (n, op)
+                    assert u.gpu_reduce(refs, n, op=op, out_cap=want.size - 4)[0] == ZC_ERR_CAPACITY
+                    cut = refs[:-1] + [refs[-1][:refs[-1].size - 1]]
+                    assert u.gpu_reduce(cut, n, op=op)[0] == ZC_ERR_FORMAT
+                want = zcref.reduce_step(refs[0], xs[-1])[1]
+                st, s, total = u.gpu_reduce_step(refs[0], xs[-1])
+                assert st == ZC_OK and total == want.size and s.tobytes() == want.tobytes(), n
+                st, s, total = u.gpu_compress(xs[0], 1e-1)
+                assert st == ZC_OK and total == refs[0].size and s.tobytes() == refs[0].tobytes(), n
+                st, y, got = u.gpu_decompress(refs[0], n, average=True)
+                assert st == ZC_OK and got == n and np.array_equal(y.view(np.uint32), zcref.decompress(refs[0])[1].view(np.uint32))
+    finally:
+        u.set_tickets(False)
+
+
+# What a call has written is there when it returns: read at once on another stream, which nothing orders behind the call's (the call's own is
+# not waited for before the end).  Calls of one workgroup, which answer themselves, and of more.
+@pytest.mark.parametrize("n", [31, 5120, 8192, 100003, 1 << 20])
+def test_outputs_are_there_when_a_waited_call_returns(zcref, n):
+    u, zc = gpuutil, gpuutil.zc
+    xs = [synth.sinusoids(n, seed=i).numpy() for i in range(2)]
+    refs = [zcref.compress(x, 1e-1)[1] for x in xs]
+    d_xs, d_refs, sizes = [u.to_dev(x) for x in xs], [u.to_dev(r) for r in refs], [r.size for r in refs]
+    ws, d_out = u.workspace(n, 2), torch.empty(zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
+    copy, d_y, copy_y = torch.empty_like(d_out), torch.empty(n, device=u.DEV), torch.empty(n, device=u.DEV)
+    wants = [refs[0], zcref.reduce(refs)[1], zcref.reduce(refs, op=1)[1], zcref.reduce_step(refs[0], xs[1])[1]]
+    want_y = zcref.decompress(refs[0])[1].view(np.uint32)
+    mine, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    calls = [lambda: zc.zc_compress(d_xs[0], n, 1e-1, d_out, ws, stream=mine),
+             lambda: zc.zc_reduce_compressed(d_refs, sizes, d_out, ws, stream=mine),
+             lambda: zc.zc_reduce_compressed_op(d_refs, sizes, 1, d_out, ws, stream=mine),
+             lambda: zc.zc_reduce_step(d_refs[0], sizes[0], d_xs[1], n, d_out, ws, stream=mine)]
+    for _ in range(5):
+        for call, want in zip(calls, wants):
+            d_out.fill_(0xA5)
+            torch.cuda.synchronize()
+            st, total = call()
+            with torch.cuda.stream(other):
+                copy.copy_(d_out)
+            other.synchronize()
+            assert st == ZC_OK and total == want.size and copy[:total].cpu().numpy().tobytes() == want.tobytes()
+        for call in (lambda: zc.zc_decompress(d_refs[0], sizes[0], d_y, ws, stream=mine),
+                     lambda: zc.zc_decompress_many([d_refs[0]], [sizes[0]], [d_y], ws, stream=mine)):
+            d_y.fill_(float("nan"))
+            torch.cuda.synchronize()
+            st, got = call()
+            with torch.cuda.stream(other):
+                copy_y.copy_(d_y)
+            other.synchronize()
+            assert st == ZC_OK and got in (n, [n]) and np.array_equal(copy_y.cpu().numpy().view(np.uint32), want_y)
+    torch.cuda.synchronize()
 
 
 # both sides of the sizes between which the compressor's tiles are of four waves, with narrow and with wider blocks

@@ -56,6 +56,26 @@ def test_compression_with_coherent_chains(zcref, tiles):
     assert st == st_ref == ZC_OK and total == ref.size and s.tobytes() == ref.tobytes(), u.first_diff(s, ref)
 
 
+# Sums by tiles of two segments (5 and 8 operands), of one (12 and 16, but for 400 tiles) and of four; Max and Min by tiles of one (up to 128 tiles), of two (8 x 200 and
+# 12 x 400) and of four (4 x 600 and 2 x 300)
+@pytest.mark.parametrize("k,tiles,wide", [(5, 30, False), (5, 9, True), (8, 200, False), (8, 60, True), (12, 40, False), (12, 3, True), (16, 128, False), (16, 20, True),
+                                          (4, 9, True), (4, 64, False), (4, 600, False), (2, 300, True), (12, 400, False)])
+def test_reduces_by_waves_that_share_operands_with_coherent_chains(zcref, k, tiles, wide):
+    """Chains over descriptors that lie closer, and waves that only take part in the look-back's barriers."""
+    u = gpuutil
+    n = tiles * TILE - 2049 - 31
+    g = np.random.default_rng(k + 100 * tiles)
+    x = synth.sinusoids(n, seed=k).numpy()
+    x[37] = 900.0
+    rough = np.repeat(10.0 ** g.uniform(-3, 1 if not wide else 3, (n + 2047) // 2048), 2048)[:n].astype(np.float32)
+    x += rough * g.standard_normal(n).astype(np.float32)
+    refs = ([zcref.compress(np.roll(x, 4096 * i), 6e-3)[1] for i in range(min(k, 4))] * 4)[:k]
+    for op in (None, 1, 2):
+        st_ref, want = zcref.reduce(refs, op=op or 0)[:2]
+        st, got, _ = u.gpu_reduce(refs, n, op=op)
+        assert st == st_ref == ZC_OK and got.tobytes() == want.tobytes(), (op, u.first_diff(got, want))
+
+
 def test_wide_tiles_with_coherent_chains(zcref):
     """Blocks wider than 15 bits take the kernels' other paths, which look back the same way."""
     u = gpuutil
