@@ -10,7 +10,6 @@
 namespace zc {
 
 typedef __attribute__((address_space(3))) u32 LdsWord;
-__device__ inline u32 lds_address(const u32* p) { return u32(reinterpret_cast<uintptr_t>((const LdsWord*)p)); }
 
 // Nothing moves across this line.
 __device__ __forceinline__ void lds_words_line() {
@@ -83,28 +82,6 @@ __device__ __forceinline__ void fetch_payload_end(const LaneOperands& o, int s, 
 template <int N>
 __device__ __forceinline__ void wait_all_but() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Words FIRST .. FIRST + 7 of what lies in LDS from byte address `at` on.  Instructions of our own: ordinary reads would wait for every load to LDS that is
-// under way, not only for those to their area.
-template <int FIRST, int ROOM>
-__device__ __forceinline__ void read_lds_words(u32 at, u32 (&t)[ROOM]) {
-  static_assert(FIRST + 8 <= ROOM);
-  u64 v[4];
-  asm volatile(
-      "ds_read2_b32 %0, %4 offset0:%5 offset1:%6\n\t"
-      "ds_read2_b32 %1, %4 offset0:%7 offset1:%8\n\t"
-      "ds_read2_b32 %2, %4 offset0:%9 offset1:%10\n\t"
-      "ds_read2_b32 %3, %4 offset0:%11 offset1:%12\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-      : "v"(at), "n"(FIRST), "n"(FIRST + 1), "n"(FIRST + 2), "n"(FIRST + 3), "n"(FIRST + 4), "n"(FIRST + 5), "n"(FIRST + 6), "n"(FIRST + 7)
-      : "memory");
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    t[FIRST + 2 * i] = u32(v[i]);
-    t[FIRST + 2 * i + 1] = u32(v[i] >> 32);
-  }
 }
 
 }  // namespace zc

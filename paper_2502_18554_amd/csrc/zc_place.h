@@ -333,7 +333,7 @@ template <int NW, typename WordFn>
 __device__ inline void stage_words_downward(WordFn word, u32 w, u32 off, u32* wl, u32 aside) {
   volatile u32* const at = wl + (w ? off : aside);
   [&]<int... I>(std::integer_sequence<int, I...>) {
-    ((at[NW - 1 - I] = word(std::integral_constant<int, NW - 1 - I>{})), ...);
+    (void(at[NW - 1 - I] = word(std::integral_constant<int, NW - 1 - I>{})), ...);
   }(std::make_integer_sequence<int, NW>{});
 }
 

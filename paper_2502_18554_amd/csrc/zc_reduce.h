@@ -428,7 +428,6 @@ __device__ inline u32 sign_plane(const u32 (&acc)[kSumPlanes], u32 top) {
 // What a wave knows about its share of a tile.
 struct ReduceShare {
   u32 seg;                  // the segment (a stream has at most 2^26 blocks, so byte offsets into tables fit 32 bits)
-  bool live;                // it exists
   int first = 0, count = 0; // Max and Min, whose waves may share a segment's operands (see reduce_op_kernel): the wave's first one, and how many
 };
 
@@ -672,7 +671,7 @@ __device__ inline void reduce_common_tile(const ReduceArgs& a, const ReduceCall&
   const int wave = wave_id();
   u32* const wl = lds + wave * kWholeStage;
   const u32 seg = tile * kTileWaves + u32(wave);
-  const ReduceShare share{seg, seg < num_segments(c.h.nb)};
+  const ReduceShare share{seg};
   u32 acc[kSumPlanes], top, sgn, w, err = 0;
   i64 outlier;
   sum_operands<IX>(a, c, share, width0, early, wl, acc, top, outlier, err);
@@ -720,7 +719,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
   // (a later part of a reduce done in parts belongs to the call its first part opened)
   c.tag = call_tag(a.ctl, c.ltag, a.adopt != 0);
   c.places = 0;
-  if (!IX) c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg / kTileWaves, wave, ask, v, *survey, kTileWaves, int(seg % kTileWaves));
+  if (!IX) c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg / kTileWaves, wave, ask, v, *survey, int(seg % kTileWaves));
   c.base = in.base;
   c.bytes = in.bytes;
   c.h = v.h0;
@@ -764,7 +763,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
     seg = tile * u32(SEGS) + u32(wave % SEGS);
     if (!IX && tile < end_tile) {            // (the verdict stands: once more, for the place of this tile)
       ask = ask_plain_streams<ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg, wave);
-      c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg / kTileWaves, wave, ask, v, *survey, kTileWaves, int(seg % kTileWaves));
+      c.places = judge_plain_streams<IX ? 1 : ZC_MAX_K, true>(a.in, a.k, a.index, a.self != 0, seg / kTileWaves, wave, ask, v, *survey, int(seg % kTileWaves));
     }
     if (IX) in = ask_headers<IX>(any, a.k, tile < end_tile ? seg : 0u);
   }
@@ -788,8 +787,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
 // per compute unit, so that reduce_wide_tile, which has its segments' places to add up there, spills less: nothing
 // but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
-// 80 registers and 32 bytes of scratch (plain streams: 96 and 44), which the common path touches behind its
-// operand loop only: what the placement needs waits there.
+// 80 registers and 32 bytes of scratch (plain streams: 96 and 44), which the common path's operand loop does not touch.
 template <bool IX, typename... A>
 __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(ReduceArgs a, A... answer) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWholeStage + kCopyOver];   // also holds an operand's payload

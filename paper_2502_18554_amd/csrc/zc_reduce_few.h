@@ -34,7 +34,6 @@ namespace zc {
 // LDS of one operand's payload of a wave: what load_operand_payload can bring in of the longest segment, and the reads behind its last word.
 constexpr u32 kFewArea = kMostStaged + 32;         // words
 static_assert(kFewArea % 4 == 0 && kFewArea >= kMostStaged + u32(kSumPlanes) + 8, "16-byte pieces, and the reads behind the last sign word");
-constexpr int kFewWords = kSumPlanes + 8;          // a sign word and planes, read eight at a time
 
 // acc += another wave's sum of the same blocks, `theirs` planes of it (in LDS, 64 words a plane); planes [0, top) are valid before and after.
 template <int C>
@@ -67,7 +66,6 @@ __device__ inline void store_partial(const u32 (&acc)[kSumPlanes], u32* planes, 
     store_partial<C + 1>(acc, planes, top);
   }
 }
-
 
 // What the waves of a workgroup tell each other.
 template <int SEGS, int PARTS>

@@ -127,6 +127,29 @@ static_assert(kOperandArea >= 1027 + 16 && kOperandArea % 4 == 0, "an operand's 
 constexpr u32 kExtremeStage = 2 * kOperandArea;
 static_assert(kExtremeStage >= u32(kWaveStage) && kExtremeStage >= 64 * 32, "the output is staged in the same place, and a wave's extremes");
 
+__device__ inline u32 lds_address(const u32* p) { return u32(reinterpret_cast<uintptr_t>((const LdsWord*)p)); }
+// Words FIRST .. FIRST + 7 of what lies in LDS from byte address `at` on.  Instructions of our own: ordinary reads would wait for every load to LDS that is
+// under way, not only for those to their area.
+template <int FIRST, int ROOM>
+__device__ __forceinline__ void read_lds_words(u32 at, u32 (&t)[ROOM]) {
+  static_assert(FIRST + 8 <= ROOM);
+  u64 v[4];
+  asm volatile(
+      "ds_read2_b32 %0, %4 offset0:%5 offset1:%6\n\t"
+      "ds_read2_b32 %1, %4 offset0:%7 offset1:%8\n\t"
+      "ds_read2_b32 %2, %4 offset0:%9 offset1:%10\n\t"
+      "ds_read2_b32 %3, %4 offset0:%11 offset1:%12\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+      : "v"(at), "n"(FIRST), "n"(FIRST + 1), "n"(FIRST + 2), "n"(FIRST + 3), "n"(FIRST + 4), "n"(FIRST + 5), "n"(FIRST + 6), "n"(FIRST + 7)
+      : "memory");
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    t[FIRST + 2 * i] = u32(v[i]);
+    t[FIRST + 2 * i + 1] = u32(v[i] >> 32);
+  }
+}
+
 // What a wave knows about an operand's blocks once their widths are there.
 struct PipeOperand {
   u32 w, pick;              // the lane's block: its width, and where its sign word lies in the operand's area
@@ -266,7 +289,7 @@ __device__ inline void meet_far_codes(u32 (&acc)[16], u32 (&f)[16], i32 ahead) {
 // The common path: the extremes of as many operands as it can take (returned, uniform).  If that is not all, the next
 // one is decoded: f = its codes modulo 2^16, `from` what the first of them starts from.
 template <bool IX, int OP, int PARTS>
-__device__ __forceinline__ int extreme_packed(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
+__device__ __forceinline__ int extreme_packed(const ReduceCall& c, const ReduceShare& share, u32* wl,
                                               OperandPipe<IX, PARTS>& pipe, u32 (&acc)[16], u32 (&f)[16], u32& from, i32& base, u32& err) {
   base = pipe.first;
   // (every code is within reach of some operand's first code, that of its base, and so inside the format's limits: no
@@ -395,7 +418,7 @@ __device__ __forceinline__ void close_any(i32 (&acc)[32], bool active, ExtremeBl
 
 // The operands from s on, none of them with wide blocks, in 32 bits.  f: the deltas of operand s.
 template <bool IX, int OP, int PARTS>
-__device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
+__device__ __forceinline__ void extreme_rest(const ReduceCall& c, const ReduceShare& share, u32* wl,
                                              OperandPipe<IX, PARTS>& pipe, i32 (&acc)[32], u32 (&f)[16], int s, u32& err) {
 #pragma nounroll
   for (;;) {
@@ -413,13 +436,13 @@ __device__ __forceinline__ void extreme_rest(const ReduceArgs& a, const ReduceCa
 
 // Operands without wide blocks.  True: they are in `out` (the common path has taken them all), false: in acc.
 template <bool IX, int OP, int PARTS>
-__device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const ReduceCall& c, const ReduceShare& share, u32* wl,
+__device__ __forceinline__ bool extreme_narrow(const ReduceCall& c, const ReduceShare& share, u32* wl,
                                                ExtremeBlock& out, i32 (&acc)[32], u32& err) {
   OperandPipe<IX, PARTS> pipe;
   pipe.open(c, share, wl, err);
   u32 pairs[16], f[16], from = 0;
   i32 base;
-  const int s = extreme_packed<IX, OP, PARTS>(a, c, share, wl, pipe, pairs, f, from, base, err);
+  const int s = extreme_packed<IX, OP, PARTS>(c, share, wl, pipe, pairs, f, from, base, err);
   if (s == share.count) {
     pipe.close();
     if constexpr (PARTS == 1) {
@@ -440,7 +463,7 @@ __device__ __forceinline__ bool extreme_narrow(const ReduceArgs& a, const Reduce
     const i32 code = base + i32(i16x2_t(as_pair(pairs[j & 15]))[j >> 4]) - kCodeBias<OP>;
     acc[j] = s ? code : OP == ZC_OP_MAX ? i32(0x80000000u) : i32(0x7fffffff);
   }
-  extreme_rest<IX, OP, PARTS>(a, c, share, wl, pipe, acc, f, s, err);
+  extreme_rest<IX, OP, PARTS>(c, share, wl, pipe, acc, f, s, err);
   pipe.close();
   return false;
 }
@@ -553,7 +576,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   const int wave = wave_id() % SEGS, part = PARTS > 1 ? wave_id() / SEGS : 0;
   u32* const wl = lds + wave_id() * kExtremeStage;
   const u32 seg = uniform(tile * u32(SEGS) + u32(wave));
-  const ReduceShare share{seg, seg < num_segments(h.nb), part, (a.k - part + PARTS - 1) / PARTS};
+  const ReduceShare share{seg, part, (a.k - part + PARTS - 1) / PARTS};
   u32 err = 0;
   if (c.ends_bad) err |= status_bit(ZC_ERR_FORMAT);
 
@@ -561,7 +584,7 @@ __global__ __launch_bounds__(kTileThreads, 4) void reduce_op_kernel(ReduceArgs a
   i32 codes[32];
   bool closed = false;
   if (c.wide_streams) extreme_any<IX, OP, PARTS>(a, c, share, wl, codes, err);
-  else closed = extreme_narrow<IX, OP, PARTS>(a, c, share, wl, eb, codes, err);
+  else closed = extreme_narrow<IX, OP, PARTS>(c, share, wl, eb, codes, err);
   PayloadSink sink{a.out, a.out_cap, h.nb, a.ctl, a.desc, IX, a.coherent != 0, looks_direct(ntiles, kDirectTiles, a.coherent != 0, 0u), 0u, c.tag};
   if constexpr (PARTS > 1) {
     sink.apart = kDescApartFine;

@@ -510,16 +510,16 @@ __device__ inline u32 lanes_to_rows(u32 v) {
 
 // The lists of spans of a call in rows, for `sh`: four streams a wave and round.  blocks: lane s: of stream s (none from stream k on).
 template <int K>
-__device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 blocks, u32 tile, int wave, u32 waves, const SurveyLoads& ask, PlainSurvey<K>& sh) {
+__device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 blocks, u32 tile, int wave, const SurveyLoads& ask, PlainSurvey<K>& sh) {
   const u32 lane = u32(lane_id());
   uint4 next = ask.v[0];
   u32 s = row_stream(k, wave);
   u32 nspans = (u32(__builtin_amdgcn_ds_bpermute(int(4u * s), int(blocks))) + kSpanBlocks - 1) / kSpanBlocks;
 #pragma nounroll
-  for (u32 s0 = 4u * u32(wave); s0 < u32(k); s0 += 4u * waves) {
+  for (u32 s0 = 4u * u32(wave); s0 < u32(k); s0 += 4u * kTileWaves) {
     const uint4 first = next;
     const u32 here = s, spans_here = nspans;
-    s = (s + 4u * waves) & 63u;           // (asked for ahead of time; beyond the last stream nothing comes of it)
+    s = (s + 4u * kTileWaves) & 63u;           // (asked for ahead of time; beyond the last stream nothing comes of it)
     nspans = (u32(__builtin_amdgcn_ds_bpermute(int(4u * s), int(blocks))) + kSpanBlocks - 1) / kSpanBlocks;
     next = load_spans(index, s, nspans, 4u * (lane & 15u));
     const RowOfSpans r = sum_row_of_spans(index, here, spans_here, tile, first);
@@ -531,11 +531,11 @@ __device__ inline void sum_spans_by_rows(const StreamIndex& index, int k, u32 bl
   }
 }
 
-// Called by all `waves` waves of a workgroup; at most one barrier.  `v`: the verdict on the headers, completed here (err,
+// Called by all waves of a workgroup of kTileWaves waves; at most one barrier.  `v`: the verdict on the headers, completed here (err,
 // wide).  Returns, in lane s, the payload word offset of the wave's segment, kTileWaves * tile + in_tile, in stream s.
 template <int K, bool ROWS>
 __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int k, const StreamIndex& index, bool self, u32 tile, int wave,
-                                          const SurveyLoads& ask, StreamsVerdict& v, PlainSurvey<K>& sh, u32 waves = kTileWaves, int in_tile = wave_id() % kTileWaves) {
+                                          const SurveyLoads& ask, StreamsVerdict& v, PlainSurvey<K>& sh, int in_tile = wave_id() % kTileWaves) {
   const int lane = lane_id();
   const u32 parts = survey_parts(k, self);
   const bool mine = lane < k;
@@ -557,9 +557,9 @@ __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int
   } else {
     SurveyLoads loads = ask;
     const bool rows = ROWS && !self;
-    if (rows) sum_spans_by_rows(index, k, fits ? u32(v.mine.nb) : 0u, tile, wave, waves, ask, sh);
+    if (rows) sum_spans_by_rows(index, k, fits ? u32(v.mine.nb) : 0u, tile, wave, ask, sh);
 #pragma nounroll
-    for (u32 u = u32(wave); !rows && u < u32(k) * parts; u += waves) {
+    for (u32 u = u32(wave); !rows && u < u32(k) * parts; u += kTileWaves) {
       const u32 s = u / parts, p = u % parts;
       const u32 nb = lane_value(u32(fits), int(s)) ? lane_value(u32(v.mine.nb), int(s)) : 0u;
       u32 before = 0, total = 0, seen = 0;
