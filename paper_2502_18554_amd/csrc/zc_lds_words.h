@@ -1,4 +1,4 @@
-// Payloads of compressed operands on their way from memory straight to LDS, and the words read from there, shared by the
+// Payloads of compressed operands on their way from memory straight to LDS, shared by the
 // reduce kernels that keep several operands under way at once.
 #pragma once
 

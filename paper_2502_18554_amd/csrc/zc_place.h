@@ -322,13 +322,15 @@ __device__ inline void stage_wave_words(WordFn word, const Placement& pl, u32* w
 }
 
 // The same with one store a word and no condition, for a wave whose blocks have at most NW words each, where the instructions count (ring rounds of
-// 2^24 values with blocks of at most 7 bits 25.9 -> 24.7 us; compression of 2^20 such values by small tiles 5.9 -> 5.4).  With 16 words, of which a block has ten, the
-// stores themselves take longer than the conditions (compression of 2^20: this part of a tile 0.52 -> 0.84 us), and so they do in the kernels that are bound by memory (compression of 512^3
-// values 118.0 -> 120.2, Sum of 4 x 2^24 28.4 -> 28.8).  The words go from the last plane down
+// 2^24 values with blocks of at most 7 bits 25.9 -> 24.7 us; compression of 2^20 such values by small tiles 5.9 -> 5.4).  The words go from the last plane down
 // to the sign word: what a block of fewer planes writes behind its own words is another block's place, in which that block has a plane of a
-// lower number (its place begins no sooner than this one's ends), and so is overwritten later (a wave's LDS accesses are carried
-// out in their order; volatile keeps the compiler's hands off it).  A block without words, whose place is that of the next one, writes to
+// lower number (its place begins no sooner than this one's ends), and so is overwritten later (volatile keeps the compiler's hands off their order).
+// A block without words, whose place is that of the next one, writes to
 // `aside`, which has room for NW words, as there must be behind the wave's last word.
+// What these are compiled into: volatile accesses through an ordinary pointer are flat stores, coherent with the host, and each is followed by a wait for
+// all of the wave's memory accesses.  Through a pointer that is said to be to LDS (LdsWord) they are eight LDS writes without a wait
+// between them, and yet no faster: compression of 2^20 sinusoid values 5.57 us as it is, 5.69 so; ring rounds of 2^24 24.5 and 24.4, by ticket 37.6 and
+// 37.5.  (16 words, of which a block has ten, were tried with the waits only: compression of 512^3 values 118.0 -> 120.2, Sum of 4 x 2^24 28.4 -> 28.8.)
 template <int NW, typename WordFn>
 __device__ inline void stage_words_downward(WordFn word, u32 w, u32 off, u32* wl, u32 aside) {
   volatile u32* const at = wl + (w ? off : aside);

@@ -222,8 +222,7 @@ struct OperandPlace {
 };
 
 // (A wave's loads of its share of an operand are buffer loads, see bytes_from.  With conditions and addresses per lane an
-// operand took 420 instructions: Sum of 8 x 1024 values 15.8 us, now 13.9, of 4 x 4 194 301 hard ones 15.5, now 14.5,
-// of 8 x 2^26 161.6, now 157.0.)
+// operand took 420 instructions: Sum of 8 x 2^26 values 161.6 us, then 157.0; of 8 x 1024, when those still came here, 15.8, then 13.9.)
 // The first code of the lane's block (b; 0 if there is no such block).
 __device__ inline i32 load_operand_outlier(const u8* base, const ReduceCall& c, u32 b) {
   return i32(__builtin_amdgcn_raw_buffer_load_b32(bytes_from(base + c.firsts, 4u * c.nb), int(4u * b), 0, 0));
@@ -474,7 +473,7 @@ __device__ __forceinline__ void sum_operands(const ReduceArgs& a, const ReduceCa
   i32 outlier_next;
   u32 width_next = 0;
   // Where operands s, s + 1 and s + 2 are, asked for a step before it is needed (a scalar load on the spot is waited for,
-  // with all LDS reads under way, three times an operand: Sum of 8 x 1024 values 12.4 us, now 12.0).
+  // with all LDS reads under way, three times an operand: Sum of 8 x 1024 values, when those still came here, 12.4 us, then 12.0).
   StreamRef at0 = a.in[0], at1 = a.in[min(1, a.k - 1)], at2 = a.in[min(2, a.k - 1)];
   {
     const int lane = fresh_lane();
@@ -808,9 +807,8 @@ __global__ __launch_bounds__(kTileThreads, IX ? 6 : 5) void reduce_kernel(Reduce
   u32 tile = 0, ntiles = 0;
   if (!open_reduce<IX>(a, c, width0, early, tile, ntiles, &sh_tile, &survey)) return;
   // The segment number stays a scalar: in a vector register, with all the addresses that follow from it, it made the
-  // kernel spill in the operand loops.  (Plain streams of nothing but wide blocks, 4 x 4 194 301 values: 43.7 us, now
-  // 41.0; 16 x 100 003 hard values 33.6 and 32.2; 8 x 2^24 smooth ones 53.6 and 52.9.)  What the waves ask for two
-  // operands ahead is still asked for by vector loads (opaque_zero): scalar ones share their counter with the LDS reads.
+  // kernel spill in the operand loops.  (8 x 2^24 smooth values of plain streams 53.6 us, then 52.9; of nothing but wide blocks, 4 x 4 194 301, which go
+  // to zc_reduce_few.h now, 43.7 and 41.0.)
   tile = uniform(tile);
   // A tile leaves the common path only if one of its waves has to.  (A call with a block wider than 15 bits in
   // some operand used to send every tile through reduce_wide_tile: 8 x 2^24 values of hard data 84 us, now 50;

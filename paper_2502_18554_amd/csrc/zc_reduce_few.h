@@ -13,14 +13,15 @@
 //  - a segment's operands are divided among PARTS waves, each on a SIMD of its own, whose sums meet in LDS.  The tile is then SEGS
 //    segments, SEGS x PARTS = 4 waves a workgroup; there are more of them, closer descriptors (kDescApartFine), and all waves of the
 //    workgroup take part in the direct look-back.
-// us per call with reduce_kernel and with this (power-law fields at 1e-4 of their range):
+// us per call with reduce_kernel, as it was when this was made, and with this (power-law fields at 1e-4 of their range):
 //   tiles     1              13             128            245            512            1024
-//   2 x    7.1  6.8       8.6  8.0       9.3  8.7       9.5  9.1      10.8 10.2      15.0 13.8
-//   4 x    8.6  7.2      10.4  8.6      11.1  9.5      11.3  9.8      12.9 11.4      20.3 17.8
-//   8 x   12.1  7.7      14.1  9.1      14.9 10.6      15.4 12.2      17.9 15.8
-//  16 x   20.3  8.7      22.3 10.4      24.1 13.4      23.8 16.1      29.3 25.6
-//  64 x   70   17                       83   30        77   49       100   87
-// 4 x 4 194 301 of hard data 14.3 and 11.8, 4 x 1000 of it 10.4 and 8.0.
+//   2 x    7.1  6.1       8.6  7.4       9.3  8.2       9.5  8.4      10.8  9.9      15.0 13.1
+//   4 x    8.6  6.8      10.4  8.0      11.1  9.0      11.3  9.4      12.9 11.5      20.3 17.1
+//   8 x   12.1  7.2      14.1  8.6      14.9 10.1      15.4 11.6      17.9 16.0
+//  16 x   20.3  7.9      22.3  9.7      24.1 12.6      23.8 15.1      29.3 24.2
+//  64 x   70   16.2                     83   23.0      77   36.6     100   71.5
+// 4 x 4 194 301 of hard data 14.3 and 11.8, 4 x 1000 of it 10.4 and 8.0.  (reduce_kernel now, in a workspace for more tiles, see few_segments: 128 tiles of 2, 4, 8, 16 and
+// 64 operands 8.9 10.6 14.2 21.8 69; 512 tiles 12.4 13.3 17.5 27.4 87; 1024 tiles of 2 and 4 22.5 24.8.)
 #pragma once
 
 #include "zc_common.h"
