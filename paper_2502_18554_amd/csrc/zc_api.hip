@@ -122,7 +122,7 @@ class CallAnswer {
     if (slot_) seq_ = g_reports.next_seq();
   }
   bool by_kernel() const { return slot_ != nullptr; }
-  Answer arg(const u64* more = nullptr) const { return {slot_, seq_, more}; }
+  Answer arg() const { return {slot_, seq_}; }
   // The launches are enqueued (or not).  See finish.
   int collect(bool launched, const void* d_ws, size_t* result, hipStream_t stream, bool wanted, bool may_pin = true, const u64* const* more = nullptr,
               u32 count = 0, u64* more_out = nullptr) {
@@ -317,12 +317,12 @@ void (*answering_sum_kernel(bool ix, int segs))(ReduceArgs, Answer) {
   return ix ? reduce_kernel<true, Answer> : reduce_kernel<false, Answer>;
 }
 template <bool AVERAGE>
-void (*pick_decompress_kernel(bool ix, bool self))(DecompressArgs) {
-  return ix ? decompress_kernel<true, false, AVERAGE> : self ? decompress_kernel<false, true, AVERAGE> : decompress_kernel<false, false, AVERAGE>;
+void (*pick_decompress_kernel(bool ix))(DecompressArgs) {
+  return ix ? decompress_kernel<true, false, AVERAGE> : decompress_kernel<false, true, AVERAGE>;
 }
 template <bool AVERAGE>
-void (*answering_decompress_kernel(bool ix))(DecompressArgs, Answer) {
-  return ix ? decompress_kernel<true, false, AVERAGE, Answer> : decompress_kernel<false, true, AVERAGE, Answer>;
+void (*answering_decompress_kernel(bool ix, bool self))(DecompressArgs, Answer) {
+  return ix ? decompress_kernel<true, false, AVERAGE, Answer> : self ? decompress_kernel<false, true, AVERAGE, Answer> : decompress_kernel<false, false, AVERAGE, Answer>;
 }
 }  // namespace
 
@@ -458,16 +458,15 @@ static int decompress_one(const void* d_in, size_t in_bytes, size_t first_value,
   da.first_value = first_value;
   da.count = count;
   da.nonce = call_nonce();
-  CallAnswer answer(n_out && !ranged && (ix || self), grid, stream);
+  CallAnswer answer(n_out && !ranged, grid, stream);
   if (ranged) {
     void (*kernel)(DecompressArgs) = ix ? decompress_range_kernel<true, false> : self ? decompress_range_kernel<false, true> : decompress_range_kernel<false, false>;
     hipLaunchKernelGGL(kernel, dim3(u32(grid)), dim3(kTileThreads), 0, stream, da);
-  } else if (answer.by_kernel()) {
-    launch_main(ZC_KERNEL_DECOMPRESS, average ? answering_decompress_kernel<true>(ix) : answering_decompress_kernel<false>(ix), dim3(1), dim3(kTileThreads),
-                stream, da, answer.arg());
+  } else if (answer.by_kernel() || !(ix || self)) {      // (see AnswerAtEnd)
+    launch_main(ZC_KERNEL_DECOMPRESS, average ? answering_decompress_kernel<true>(ix, self) : answering_decompress_kernel<false>(ix, self), dim3(u32(grid)),
+                dim3(kTileThreads), stream, da, answer.arg());
   } else {
-    void (*kernel)(DecompressArgs) = average ? pick_decompress_kernel<true>(ix, self) : pick_decompress_kernel<false>(ix, self);
-    launch_main(ZC_KERNEL_DECOMPRESS, kernel, dim3(u32(grid)), dim3(kTileThreads), stream, da);
+    launch_main(ZC_KERNEL_DECOMPRESS, average ? pick_decompress_kernel<true>(ix) : pick_decompress_kernel<false>(ix), dim3(u32(grid)), dim3(kTileThreads), stream, da);
   }
   return answer.collect(launch_ok(), d_ws, n_out, stream, n_out != nullptr);
 }
@@ -532,7 +531,7 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   CallAnswer answer(n_out && (ix || self), tiles * u64(k), stream);      // (one stream then)
   if (answer.by_kernel()) {
     launch_main(ZC_KERNEL_DECOMPRESS, ix ? decompress_many_kernel<true, false, false, Answer> : decompress_many_kernel<false, true, false, Answer>, dim3(1),
-                dim3(kTileThreads), stream, da, answer.arg(heads[0]));
+                dim3(kTileThreads), stream, da, answer.arg());
   } else {
     void (*kernel)(DecompressManyArgs) = ix ? decompress_many_kernel<true, false, false> : self ? decompress_many_kernel<false, true, false>
                                          : k > kManyByWave ? decompress_many_kernel<false, false, true> : decompress_many_kernel<false, false, false>;

@@ -33,7 +33,6 @@ struct ReportArgs {
 struct Answer {
   ReportSlot* to;           // null: nobody waits, or by a kernel of its own
   u64 seq;
-  const u64* more;          // null, or a further word that the caller wants
 };
 
 template <int N>
@@ -69,7 +68,8 @@ inline bool report_words(ReportSlots& slots, const u64* const* from, u32 count, 
 }
 
 // The end of a main kernel, called by all its threads.
-__device__ __forceinline__ void give_answer(const Answer& an, const Control* ctl) {
+// heads, k: the streams whose n (the second word of a header) follow the call's own words.
+__device__ __forceinline__ void give_answer(const Answer& an, const Control* ctl, const StreamRef* heads = nullptr, int k = 0) {
   if (!an.to) return;       // uniform
   // Every wave waits for its own stores and atomics first: a barrier orders LDS, and whether the compiler puts a wait for memory in front
   // of it differs from kernel to kernel; the words read below, and the output that the caller may read next, need it.
@@ -77,17 +77,21 @@ __device__ __forceinline__ void give_answer(const Answer& an, const Control* ctl
   __syncthreads();
   if (wave_id() != 0) return;
   const int lane = lane_id();
-  const u64* const from = lane == 0 ? &ctl->status : lane == 1 ? &ctl->call_tag : lane == 2 ? &ctl->result : an.more;
-  if (lane < 4 && from)
-    __hip_atomic_store(&an.to->words[lane], __hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  const u64* const own = lane == 0 ? &ctl->status : lane == 1 ? &ctl->call_tag : &ctl->result;
+  if (lane < 3)
+    __hip_atomic_store(&an.to->words[lane], __hip_atomic_load(own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (lane < k)
+    __hip_atomic_store(&an.to->words[3 + lane], reinterpret_cast<const u64*>(heads[lane].base)[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __threadfence_system();
   if (lane == 0) __hip_atomic_store(&an.to->seq, an.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The same for a kernel that has an instance for the calls that it answers, with an argument more (A = Answer), and one for all others (no A), in which this
-// is nothing: what ends the kernel, wherever it returns.  All but the compression's are such.  With one instance, whose arguments said whether somebody
+// is nothing: what ends the kernel, wherever it returns.  With one instance, whose arguments said whether somebody
 // waits, a Sum of one buffer of 2^20 values took 8.3 us, now 8.1, of 16 of them 12.9 and 12.6, a ring round of 2^24 values by ticket 40.1 and
-// 38.3, and a decompression of 2^20 values 4.47 and 4.40.  (The compression of 3 to 4 million values takes 2 % longer with two instances.)
+// 38.3, and a decompression of 2^24 values 14.9 and 14.8.  (One instance for all calls have the compression, which takes 2 % longer on 3 to 4 million values with
+// two, and the decompression of plain streams that are indexed ahead, which is level.  A compression and decompression of 20 000 003 values, plain, takes 46.9 us;
+// with eight bytes more in Answer 47.5.)
 template <typename Args, typename... A>
 struct AnswerAtEnd {
   __device__ __forceinline__ AnswerAtEnd(const Args&) {}
@@ -97,7 +101,10 @@ struct AnswerAtEnd<Args, Answer> {
   const Args& a;
   const Answer& answer;
   __device__ __forceinline__ AnswerAtEnd(const Args& args, const Answer& an) : a(args), answer(an) {}
-  __device__ __forceinline__ ~AnswerAtEnd() { give_answer(answer, a.ctl); }
+  __device__ __forceinline__ ~AnswerAtEnd() {
+    if constexpr (requires { a.out_cap_elems[0]; }) give_answer(answer, a.ctl, a.in, a.k);      // (streams decompressed by one call)
+    else give_answer(answer, a.ctl);
+  }
 };
 
 }  // namespace zc
