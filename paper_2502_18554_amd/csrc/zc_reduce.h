@@ -729,6 +729,8 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
   c.nsum = v.nsum;
   c.wide_streams = v.wide;
   if (v.err) {
+    // (a workspace too small for some stream is told ahead of what else is wrong, as judge_plain_streams does)
+    if (IX && !a.n_least && __any(v.mine.ok && v.mine.n > a.n_most)) v.err |= status_bit(ZC_ERR_ARG);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
       if (!a.adopt) a.ctl->result = 0;
       raise_status(a.ctl, c.tag, v.err);

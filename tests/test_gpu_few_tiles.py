@@ -259,6 +259,8 @@ def test_a_reduce_in_too_small_a_workspace_is_refused(zcref, k, tickets):
     n = 40 * TILE - 2049
     ref = zcref.compress(_values(n, 91), 1e-3)[1]
     d_refs, sizes = [u.to_dev(ref)] * k, [ref.size] * k
+    other = zcref.compress(_values(n - 4096, 92), 1e-3)[1]
+    d_other = u.to_dev(other)
     d_out = torch.empty(u.zc.zc_compress_bound(n), dtype=torch.uint8, device=u.DEV)
     u.set_tickets(tickets)
     try:
@@ -267,6 +269,9 @@ def test_a_reduce_in_too_small_a_workspace_is_refused(zcref, k, tickets):
             for op in (0, 1, 2):
                 ws.fill_(0x5A)
                 assert u.zc.zc_reduce_compressed_op(d_refs, sizes, op, d_out, ws) == (ZC_ERR_ARG, 0), (small, op)
+                if k > 1:                                # ahead of anything else that is wrong
+                    for d_last, last in ((d_other, other), (u.to_dev(ref[:-1]), ref[:-1])):
+                        assert u.zc.zc_reduce_compressed_op(d_refs[:-1] + [d_last], sizes[:-1] + [last.size], op, d_out, ws) == (ZC_ERR_ARG, 0)
         for op in (0, 1, 2):
             want = zcref.reduce([ref] * k, op=op)[1]
             st, total = u.zc.zc_reduce_compressed_op(d_refs, sizes, op, d_out, u.workspace(n, k))
