@@ -108,28 +108,28 @@ __device__ inline u32 load_segment_end(const u8* base, u32 seg, u32 zero = 0) {
   return *reinterpret_cast<const u32*>(at_bytes(base, kHeaderBytes + 4u + 4u * seg + zero));
 }
 
-// Payload words of the four blocks whose width bytes are packed in x, added to `sum`.  Sum of (1 + w) over the non-zero
-// bytes = byte sum + number of non-zero bytes.
-__device__ inline u32 psize_words4(u32 x, u32 sum) {
-  const u32 nonzero = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;   // top bit of every non-zero byte
-  return __builtin_amdgcn_sad_u8(x, 0u, sum + u32(__builtin_popcount(nonzero)));
+// 16 width bytes from block b0 on of a table of nb, without those behind nb.
+__device__ inline uint4 clip_widths16(const uint4& v, u32 b0, u32 nb) {
+  const u32 live = nb > b0 ? nb - b0 : 0u;
+  u32 x[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) x[j] &= live >= 4u * j + 4 ? 0xFFFFFFFFu : (live > 4u * j ? (1u << (8 * (live - 4u * j))) - 1u : 0u);
+  return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
-// The same for 16 blocks from block b0 on of a table of nb (`seen`: OR of the width bytes; bytes behind nb do not count).
-__device__ inline u32 psize_words16(const uint4& v, u32 b0, u32 nb, u32& seen) {
-  u32 x[4] = {v.x, v.y, v.z, v.w};
-  if (b0 + 16 > nb) {
-    const u32 live = nb > b0 ? nb - b0 : 0u;           // 0..15 bytes exist
-#pragma unroll
-    for (int j = 0; j < 4; ++j) x[j] &= live >= 4u * j + 4 ? 0xFFFFFFFFu : (live > 4u * j ? (1u << (8 * (live - 4u * j))) - 1u : 0u);
-  }
-  u32 sum = 0;
+// Payload words of 16 blocks: the sum of (1 + w) over the non-zero bytes (`seen`: OR of the width bytes).  A masked sum of differences
+// leaves out the bytes that are zero: from 32 it is 32 for every other one, less the sum of the bytes.  (With a byte above 31 the result is
+// wrong; it makes the stream malformed, whatever it is.)
+__device__ inline u32 psize_words16(const uint4& v, u32& seen) {
+  const u32 x[4] = {v.x, v.y, v.z, v.w};
+  u32 sum = 0, rest = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     seen |= x[j];
-    sum = psize_words4(x[j], sum);
+    sum = __builtin_amdgcn_sad_u8(x[j], 0u, sum);
+    rest = __builtin_amdgcn_msad_u8(0x20202020u, x[j], rest);
   }
-  return sum;
+  return sum + ((sum + rest) >> 5);
 }
 constexpr u32 kBadWidths = 0xE0E0E0E0u;                // bits of a width byte above 31 ...
 constexpr u32 kWideWidths = 0xF0F0F0F0u;               // ... and above 15
@@ -165,7 +165,8 @@ __global__ __launch_bounds__(256) void stream_index_kernel(ScanArgs a) {
 #pragma unroll
   for (int i = 0; i < kIndexGroups; ++i) {
     const u64 b0 = (group0 + u64(i)) * kIndexGroupBlocks + u64(threadIdx.x) * 16;
-    sum[i] = psize_words16(v[i], u32(b0), u32(h.nb), seen);
+    if (b0 + 16 > h.nb) v[i] = clip_widths16(v[i], u32(b0), u32(h.nb));
+    sum[i] = psize_words16(v[i], seen);
     incl[i] = wave_inclusive_sum(sum[i]);
     if (lane == 63) sh_wave[i][wave] = incl[i];
   }
@@ -350,16 +351,17 @@ struct PlainSurvey {
 };
 
 // Tiles of all k streams of a call together up to which every workgroup sums their tables itself: the work grows with the
-// square of the tiles, the launch it saves does not.  us per call, with the launch ahead and without (power-law fields, 1e-3):
-//   decompress   1 tile 8.9 5.0 | 256: 8.8 7.8 | 320: 9.3 9.3 | 384: 9.3 10.1;   ring round   256: 11.0 10.2 | 320: 12.7 12.6 | 384: 13.3 13.6
-//   3 buffers    255: 9.8 9.6 | 384: 10.1 12.1;   8 buffers   256: 10.9 8.9 | 384: 11.0 11.0 | 512: 11.1 12.5
-//   16 buffers   384: 13.5 12.0 | 512: 13.4 13.6;   64 buffers   512: 28.5 25.3
+// square of the tiles, the launch it saves does not.  What bounds it is round trips to the L2, so several loads of a table are under way at once (with two of them
+// decompress took 6.0 us for 2^20 values, now 5.6, and 7.6 for 2 000 003, now 6.75; a ring round 8.4, 8.0 and 10.2, 9.2; Max of 2 x 2^20 11.2, 10.3; 12 buffers of
+// 200 000 11.2, 9.9).  us per call, with the launch ahead and without (power-law fields, 1e-3):
+//   decompress   1 tile 9.2 4.6 | 245: 9.2 6.8 | 367: 9.4 8.4 | 512: 9.7 9.4 | 611: 10.3 11.7;   ring round   367: 12.7 11.6 | 512: 13.1 12.8
+//   4 buffers    264: 10.3 7.3 | 392: 10.4 9.4 | 512: 10.5 10.2 | 588: 11.7 12.8;   16 buffers   400: 12.3 11.3 | 464: 13.9 11.8
+//   32 buffers   416: 15.7 13.7 | 512: 15.1 12.8;   64 buffers   448: 19.1 17.8 | 512: 17.7 17.4
 // The tables are summed one stream after the other, and what a launch ahead leaves to do is done for many at once in the
 // reduces (see below), so that there the launch pays earlier with many streams:
-//   Sum of 2     256: 12.3 11.5 | 320: 12.7 12.4;   of 8   256: 17.0 16.1 | 320: 17.7 17.5;   of 12   192: 20.2 19.0 | 288: 20.7 20.4
-//   Sum of 16    128: 23.9 23.2 | 256: 23.8 23.5 | 320: 23.8 24.7;   of 24   192: 31.2 30.4 | 288: 31.3 32.3
-//   Sum of 32    32: 37.9 38.4 | 256: 38.5 39.4;   of 64   64: 68.4 74.2
-__host__ constexpr u64 self_tiles(int k, bool reduce) { return reduce ? (k <= 12 ? 320 : k <= 16 ? 256 : k <= 24 ? 192 : 0) : k < 16 ? 320 : 512; }
+//   Max of 2     368: 12.7 11.7 | 490: 12.8 12.9;   Sum of 4   392: 12.4 11.2 | 512: 12.5 11.9 | 588: 12.8 12.6;   of 8   392: 13.3 12.2 | 512: 13.3 12.7
+//   Sum of 12    300: 14.0 12.4 | 396: 13.8 13.9;   of 16   256: 13.4 12.0 | 352: 13.6 13.5;   of 24   192: 14.7 14.4;   of 32   32: 16.0 16.9
+__host__ constexpr u64 self_tiles(int k, bool reduce) { return reduce ? (k <= 8 ? 480 : k <= 16 ? 320 : k <= 24 ? 192 : 0) : 512; }
 
 // The host does not know the tiles, only what the output or the workspace has room for and the bytes, which are at most
 // kMostTables times what the tables of so many tiles need (133 bytes a block where its tables take 5).  With more bytes than
@@ -388,14 +390,15 @@ typedef u32 u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 struct SurveyLoads {
   uint4 v[kSurveyLoads];
 };
-__device__ inline SurveyLoads load_widths(const StreamRef& in, u32 b0, u32 stride) {
-  SurveyLoads l;
+// The rest of a table of nb blocks, once nb is known, BATCH loads under way at once.
+template <int BATCH>
+__device__ inline void load_widths(const StreamRef& in, u32 nb, u32 b0, u32 stride, uint4 (&v)[BATCH]) {
+  const __amdgpu_buffer_rsrc_t table = bytes_from(in.base + kHeaderBytes, u32(pad16(nb)));
 #pragma unroll
-  for (int i = 0; i < kSurveyLoads; ++i) {
-    const u64 at = u64(kHeaderBytes) + b0 + u32(i) * stride + 16u * u32(lane_id());
-    l.v[i] = *reinterpret_cast<const uint4*>(at_bytes(in.base, at + 16 <= in.bytes ? u32(at) : 0u));
+  for (int i = 0; i < BATCH; ++i) {
+    const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(table, int(b0 + u32(i) * stride + 16u * u32(lane_id())), 0, 0);
+    v[i] = make_uint4(t.x, t.y, t.z, t.w);
   }
-  return l;
 }
 
 // Asked for before the headers are known.  self: the wave's first part of a table.  Else: [0] the first spans of stream
@@ -555,7 +558,6 @@ __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int
     total = rows_to_lanes(r.total);
     seen = rows_to_lanes(r.seen);
   } else {
-    SurveyLoads loads = ask;
     const bool rows = ROWS && !self;
     if (rows) sum_spans_by_rows(index, k, fits ? u32(v.mine.nb) : 0u, tile, wave, ask, sh);
 #pragma nounroll
@@ -565,28 +567,35 @@ __device__ __forceinline__ u32 judge_plain_streams(const StreamRef* streams, int
       u32 before = 0, total = 0, seen = 0;
       if (self) {
         const u32 first = tile * kTileBlocks, step = 1024u * parts;
-        if (u != u32(wave)) loads = load_widths(streams[s], 1024u * p, step);
-#pragma nounroll
-        for (u32 b0 = 1024u * p; b0 < nb; b0 += step * kSurveyLoads) {
-#pragma unroll
-          for (int i = 0; i < kSurveyLoads; ++i) {
-            const u32 c0 = b0 + step * u32(i);
-            if (c0 < nb) {                                 // uniform
-              const u32 b = c0 + 16u * u32(lane);
-              const u32 sum = psize_words16(loads.v[i], b, nb, seen);
-              total += sum;
-              before += b < first ? sum : 0u;
-              if (first - c0 < 1024u) {                    // uniform: the tile is one row of 16 lanes here
-                u32 incl = sum;
-                incl += dpp_row_shr_or_zero<1>(incl);
-                incl += dpp_row_shr_or_zero<2>(incl);
-                incl += dpp_row_shr_or_zero<4>(incl);
-                incl += dpp_row_shr_or_zero<8>(incl);
-                if (u32(lane) >> 4 == (first - c0) >> 8 && (lane & 3) == 0) sh.in_tile[4 * s + ((u32(lane) >> 2) & 3u)] = incl - sum;
-              }
-            }
+        // the blocks from c0 + 16 * lane on
+        auto count = [&](uint4 x, u32 c0) {
+          if (c0 + 1024u > nb) x = clip_widths16(x, c0 + 16u * u32(lane), nb);      // uniform
+          const u32 sum = psize_words16(x, seen);
+          total += sum;
+          if (c0 < first) before += c0 + 16u * u32(lane) < first ? sum : 0u;      // uniform
+          if (first - c0 < 1024u) {                        // uniform: the tile is one row of 16 lanes here
+            u32 incl = sum;
+            incl += dpp_row_shr_or_zero<1>(incl);
+            incl += dpp_row_shr_or_zero<2>(incl);
+            incl += dpp_row_shr_or_zero<4>(incl);
+            incl += dpp_row_shr_or_zero<8>(incl);
+            if (u32(lane) >> 4 == (first - c0) >> 8 && (lane & 3) == 0) sh.in_tile[4 * s + ((u32(lane) >> 2) & 3u)] = incl - sum;
           }
-          if (b0 + step * kSurveyLoads < nb) loads = load_widths(streams[s], b0 + step * kSurveyLoads, step);
+        };
+        u32 b0 = 1024u * p;
+        constexpr int kBatch = K == 1 ? 8 : 4;             // (many streams have small tables)
+        if (u == u32(wave)) {                              // uniform
+#pragma unroll
+          for (int i = 0; i < kSurveyLoads; ++i, b0 += step)
+            if (b0 < nb) count(ask.v[i], b0);              // uniform
+        }
+#pragma nounroll
+        for (; b0 < nb; b0 += step * kBatch) {
+          uint4 x[kBatch];
+          load_widths(streams[s], nb, b0, step, x);
+#pragma unroll
+          for (int i = 0; i < kBatch; ++i)
+            if (b0 + step * u32(i) < nb) count(x[i], b0 + step * u32(i));      // uniform
         }
       } else {
         sum_spans(index, s, nb, tile, u == u32(wave), ask, before, total, seen);
