@@ -369,6 +369,16 @@ __device__ __forceinline__ const Args& kernel_args() {
   return *(const Args*)(Constant*)__builtin_amdgcn_kernarg_segment_ptr();
 }
 
+// The same, in a way that keeps the compiler from seeing that these are the values it has: for a path that is hardly ever taken, so that what only that path needs is
+// loaded there instead of waiting for it in scalar registers.
+template <typename Args>
+__device__ __forceinline__ const Args& kernel_args_again() {
+  typedef const __attribute__((address_space(4))) Args Constant;
+  Constant* p = (Constant*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const Args*)p;
+}
+
 // Sum over the 64 lanes (result uniform).
 __device__ inline u32 wave_sum_u32(u32 v) {
   v += dpp_mov<kDppQuadSwap1>(v);

@@ -144,25 +144,15 @@ __device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u3
 // pushed out.  In both halves without tickets it needs fewer, but then has 20 bytes of scratch set aside, which
 // zc_compress_noalloc is not to need; in none it needs twice as many.  2^26 values by ticket 80.7 us with none, 80.0 with one,
 // 78.1 with both; without tickets 66.8, 65.6, 65.2.)
-// FEW: see compress_kernel.
-template <bool TICKETS, bool FEW>
+template <bool TICKETS>
 __device__ __forceinline__ void block_codes(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                    i32 (&q)[32], u32& err) {
   // Some value of this wave outside the screened domain: the checked arithmetic for all of it.
-  bool outside;
-  if constexpr (FEW) {
-    float most = 0.0f;
+  // (By maxima 16 instructions; by comparisons 64, and their results take scalar registers: 512^3 values 118.0 us, then 116.9.)
+  float most = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) most = most_of(most_of(most, x[i].x, x[i].y), x[i].z, x[i].w);
-    outside = needs_checks(most, a);
-  } else {
-    u32 flagged = 0;            // (no short-circuit: the four compares of a load are independent)
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      flagged |= u32(needs_checks(x[i].x, a)) | u32(needs_checks(x[i].y, a)) | u32(needs_checks(x[i].z, a)) |
-                 u32(needs_checks(x[i].w, a));
-    outside = flagged != 0;
-  }
+  for (int i = 0; i < 8; ++i) most = most_of(most_of(most, x[i].x, x[i].y), x[i].z, x[i].w);
+  const bool outside = needs_checks(most, a);
   const bool checked = __any(outside);
 
   // Loads 0..3 hold blocks 0..31, loads 4..7 blocks 32..63.  Either half goes through LDS as 32 rows
@@ -222,11 +212,11 @@ struct BlockFields {
   i32 outlier;
 };
 
-template <bool TICKETS, bool FEW>
+template <bool TICKETS>
 __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8], u64 wblock0, u32 have, int lane, u32* wl,
                                     BlockFields& bf, u32& err) {
   i32 q[32];
-  block_codes<TICKETS, FEW>(a, x, wblock0, have, lane, wl, q, err);
+  block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, err);
   bf.outlier = q[0];
   i32 top = 0, bottom = 0;              // largest and smallest delta (d0 = 0 is one of them)
 #pragma unroll
@@ -244,13 +234,66 @@ __device__ inline void block_fields(const CompressArgs& a, const float4 (&x)[8],
   bf.any = any;
 }
 
-// A wave that holds a block wider than 15 bits: the 16-bit fields are of no use then, and its 32 deltas do not
-// fit the registers beside everything else.  Once the wave's place is known it fetches and quantises its values
-// again, turns them into sign and plane words and stores those.  Only that wave does, and no tile waits for it:
-// of the hard-data configuration 2 % of the waves, but 16 % of the tiles, hold such a block.  (A tile with one
-// used to store its blocks two at a time, a plane word being the ballot of one bit of 32 lanes; 2^28 hard
-// values, compressed and decompressed: 674 us, now 455.)
-template <bool TICKETS, bool FEW>
+// Sign and plane words of two blocks (a and b, which may be the same), one per half of the wave, as ballots of their deltas: lane j of a half holds delta j.  w, at:
+// widths of the blocks, and where their words go, `to` + at, which has room for `room` words.
+__device__ __forceinline__ void store_block_ballots(i32 nd, u32 w_a, u32 w_b, u32 at_a, u32 at_b, u32* to, u64 room, u32 lane) {
+  const u32 half = lane >> 5, j = lane & 31u;
+  const u32 nmag = u32(nd < 0 ? -nd : nd);
+  const u32 w = half ? w_b : w_a, dst = half ? at_b : at_a;
+  const u64 sign = __ballot(nd < 0);
+  if (j == 0 && w && dst < room) to[dst] = half ? u32(sign >> 32) : u32(sign);
+  const u32 top = w_a > w_b ? w_a : w_b;
+#pragma nounroll
+  for (u32 p = 0; p < top; ++p) {
+    const u64 plane = __ballot(((nmag >> p) & 1u) != 0);
+    if (j == 0 && p < w && dst + 1 + p < room) to[dst + 1 + p] = half ? u32(plane >> 32) : u32(plane);
+  }
+}
+
+// The value of `v` in lane `src` (any lane, chosen per lane).
+__device__ inline u32 from_lane(u32 v, u32 src) { return u32(__builtin_amdgcn_ds_bpermute(int((src & 63u) << 2), int(v))); }
+
+// A block wider than 15 bits: the 16-bit fields are of no use then, and 32 deltas of 32 bits do not fit the registers beside
+// everything else.  Its values are fetched and quantised again, and its words staged beside those of the wave's other blocks while the look-back is under way: 32 lanes a
+// block, two blocks a step.  There are few of them as a rule: of the hard-data configuration one block in 3000, one wave in 50, one tile in 6.
+// (The whole wave used to go over its values again, behind the look-back, see store_wide_wave, and its tile stayed that much longer.  us for 2^28 such values 228.6, now
+// 208.0; 2^26: 64.0 58.2; 20 000 003: 25.5 22.3; 2^23: 13.4 11.4; 2^20: 7.4 6.4.  Data without wide blocks: level.)
+__device__ __forceinline__ void stage_wide_blocks(const Placement& pl, u64 wblock0, u64 wide, u32* wl) {
+  CompressArgs a;
+  {
+    const CompressArgs& again = kernel_args_again<CompressArgs>();
+    a.in = again.in;
+    a.n = again.n;
+    a.inv = again.inv;
+    a.step = again.step;
+    a.eb = again.eb;
+    a.screen = again.screen;
+  }
+  const u32 lane = u32(fresh_lane()), half = lane >> 5, j = lane & 31u;
+#pragma nounroll
+  while (wide) {
+    const u32 blk_a = u32(__builtin_ctzll(wide));
+    wide &= wide - 1;
+    const u32 blk_b = wide ? u32(__builtin_ctzll(wide)) : blk_a;       // (an odd one out is done twice)
+    wide &= wide - 1;
+    const u64 v0 = (wblock0 + (half ? blk_b : blk_a)) * kBlockValues;
+    const u64 left = a.n > v0 ? a.n - v0 : 0;
+    const u32 cnt = left < 32 ? u32(left) : 32u;         // values of this block that exist
+    u32 ignored = 0;                                     // errors were raised on the first pass
+    i32 q = 0;
+    if (j < cnt) q = quantize_value(a.in[v0 + j], a, ignored);
+    const i32 last = i32(from_lane(u32(q), 32u * half + (cnt ? cnt - 1u : 0u)));
+    if (j >= cnt) q = last;                              // the last block repeats its last code
+    const i32 before = i32(from_lane(u32(q), lane + 63u));             // lane - 1 (lane 0 gets lane 63: unused)
+    store_block_ballots(j ? q - before : 0, lane_value(pl.w, int(blk_a)), lane_value(pl.w, int(blk_b)), lane_value(pl.off_in_wave, int(blk_a)),
+                        lane_value(pl.off_in_wave, int(blk_b)), wl, kWaveStage, lane);
+  }
+}
+
+// A wave whose words are more than its staging area is made for: most of its blocks are wide then.  Once the wave's place is known it fetches and quantises all its values
+// again, turns them into sign and plane words and stores those.  Only that wave does, and no tile waits for it.
+// (2^28 hard values, compressed and decompressed, when a tile with a wide block stored all its blocks by ballots: 674 us, then 455.)
+template <bool TICKETS>
 __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const PayloadSink& sink, const Placement& pl, u64 base,
                                                 u64 wblock0, u32 have, int lane, u32* wl) {
   asm volatile("" : "+v"(lane));               // (or the compiler keeps what it has loaded and quantised before, in scratch)
@@ -259,7 +302,7 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
     float4 x[8];
     u32 ignored = 0;                           // errors were raised on the first pass
     load_raw(a, wblock0, lane, have, x);
-    block_codes<TICKETS, FEW>(a, x, wblock0, have, lane, wl, q, ignored);
+    block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, ignored);
   }
 #pragma unroll
   for (int j = 31; j >= 1; --j) q[j] -= q[j - 1];
@@ -284,7 +327,7 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
 // a multiple of 16384 values (20 000 003 values, compress and decompress: 59.0 us, now 51.9).
 // WAVES: kPackWaves, or kTileWaves where that shortens the call (packs_small_tiles): with few tiles two waves of a workgroup of eight
 // share a SIMD, which one alone keeps busy, while other compute units have nothing to do, and between one and one and a half workgroups of eight per compute unit
-// three of four waves share it more evenly.  There it is the instructions that count, so these kernels also screen with maxima (16 instructions for 64),
+// three of four waves share it more evenly.  There it is the instructions that count, so these kernels also
 // copy out by ranges and stage narrow blocks without conditions (stage_words_downward).  us, tiles of eight waves and of four:
 //   sinusoids at 1e-4   1000 values 5.6 5.1 | 2^20: 6.6 5.4 | 2 000 003: 7.0 6.3 | 3 000 000: 7.1 6.8 | 5 000 000: 9.4 8.2 | 6 500 000: 9.5 9.7
 //   a field at 1e-4     1000 values 6.0 5.3 | 2^20: 6.8 5.8 | 2 000 003: 7.2 6.5 | 3 400 000: 7.6 7.8 | 5 000 000: 10.3 9.0 | 6 500 000: 10.5 10.7
@@ -341,7 +384,7 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
     }
 
     BlockFields bf;
-    block_fields<TICKETS, FEW>(a, x, wblock0, have, lane, wl, bf, err);
+    block_fields<TICKETS>(a, x, wblock0, have, lane, wl, bf, err);
     Placement pl;
     pl.w = (active && bf.any) ? 32u - u32(__builtin_clz(bf.any)) : 0u;
     pl.wmax = wave_max_u32(pl.w);
@@ -362,9 +405,9 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
     if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
 
     // ---- fields -> sign + plane words, then the back half ----
-    const bool narrow = pl.wmax <= 15;         // uniform
+    const bool staged = pl.wave_total <= 64u * 16u;      // uniform (always, without wide blocks)
     const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
-      if (!narrow) return;
+      if (!staged) return;
       constexpr u32 kAside = 64 * 16 + 16;
       static_assert(kAside + 16 <= u32(kWaveStage));
       u32 pw[16];          // pw[0] = sign, pw[1 + p] = plane p
@@ -386,11 +429,13 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
 #pragma unroll
         for (int p = 0; p < 15; ++p) pw[1 + p] = bf.f[p];
       }
+      // (what a lane writes for a wide block, 16 words, is overwritten by the block's own)
       stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, pl, wl);
+      if (pl.wmax > 15) stage_wide_blocks(pl, wblock0, __ballot(pl.w > 15), wl);      // uniform
     });
     if (lane == 0) write_index_entry(sink, tile * u32(WAVES) + u32(wave), tb.words + pl.wave_off);
-    if (narrow) copy_staged_wave<16, FEW>(sink, pl, tb.words, wl, lane);
-    else store_wide_wave<TICKETS, FEW>(a, sink, pl, tb.words, wblock0, have, lane, wl);
+    if (staged) copy_staged_wave<16, FEW>(sink, pl, tb.words, wl, lane);
+    else store_wide_wave<TICKETS>(a, sink, pl, tb.words, wblock0, have, lane, wl);
     finish_stream<WAVES>(sink, pl, tile, ntiles, tb);
     if (active && tables_fit) {                // (not store_tables: see copy_staged_words)
       const u64 b = wblock0 + u64(lane);

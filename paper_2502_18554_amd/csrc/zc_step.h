@@ -215,9 +215,6 @@ __device__ inline u32 half_max(u32 v) {
   return lane_id() < 32 ? (a > b ? a : b) : (c > d ? c : d);
 }
 
-// The value of `v` in lane `src` (any lane, chosen per lane).
-__device__ inline u32 from_lane(u32 v, u32 src) { return u32(__builtin_amdgcn_ds_bpermute(int((src & 63u) << 2), int(v))); }
-
 // What the other path needs to know about the received segment, one lane per block.
 struct SlowInput {
   const u32* payload;   // the received stream's payload
@@ -266,18 +263,8 @@ __device__ inline void step_blocks_slow(const StepArgs& a, const ParsedHeader& h
   const u32 half = u32(lane) >> 5, j = u32(lane) & 31u;
   // sign and plane words of two blocks, one per half of the wave, as ballots of their deltas
   auto store_block = [&](i32 nd, u32 blk_a, u32 blk_b) {
-    const u32 nmag = u32(nd < 0 ? -nd : nd);
-    const u32 wo_a = lane_value(w_out, int(blk_a)), wo_b = lane_value(w_out, int(blk_b));
-    const u32 wo_mine = half ? wo_b : wo_a;
-    const u32 dst = half ? lane_value(off_out, int(blk_b)) : lane_value(off_out, int(blk_a));
-    const u64 sign = __ballot(nd < 0);
-    if (j == 0 && wo_mine && dst < room) to[dst] = half ? u32(sign >> 32) : u32(sign);
-    const u32 wo_top = wo_a > wo_b ? wo_a : wo_b;
-#pragma nounroll
-    for (u32 p = 0; p < wo_top; ++p) {
-      const u64 plane = __ballot(((nmag >> p) & 1u) != 0);
-      if (j == 0 && p < wo_mine && dst + 1 + p < room) to[dst + 1 + p] = half ? u32(plane >> 32) : u32(plane);
-    }
+    store_block_ballots(nd, lane_value(w_out, int(blk_a)), lane_value(w_out, int(blk_b)), lane_value(off_out, int(blk_a)), lane_value(off_out, int(blk_b)), to,
+                        room, u32(lane));
   };
   if constexpr (KEEP && PASS != kMeasure) {
     if (kept.blocks) {                         // uniform
