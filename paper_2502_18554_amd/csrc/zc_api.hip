@@ -92,12 +92,11 @@ u32 index_grid(u64 tiles) { return u32(((tiles + 15) / 16 + kIndexGroups - 1) / 
 
 ReportSlots g_reports;
 
-// Status, tag and size of a call, and `count` further words.
+// Status and size of a call, and `count` further words.
 int read_answer(const u64* host, size_t* result, u32 count, u64* more_out) {
-  if (result) *result = size_t(host[2]);
-  for (u32 i = 0; i < count; ++i) more_out[i] = host[3 + i];
-  // status bits count only under the tag of the last call
-  return status_from_bits((host[0] >> 32) == (host[1] >> 32) ? u32(host[0]) : 0u);
+  if (result) *result = size_t(host[1]);
+  for (u32 i = 0; i < count; ++i) more_out[i] = host[2 + i];
+  return status_from_bits(u32(host[0]));
 }
 
 // Waits for the call and fetches its status and size; `more` further words (the streams' n) travel along.
@@ -105,24 +104,37 @@ int read_answer(const u64* host, size_t* result, u32 count, u64* more_out) {
 int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = true, const u64* const* more = nullptr, u32 count = 0,
            u64* more_out = nullptr) {
   const Control* const ctl = static_cast<const Control*>(d_ws);
+  u64 host[kReportWords + 1];
+  // (An error of an earlier call still to be told could not be told from a failed launch: then a slot would be given back that is still written to.)
+  if (hipGetLastError() != hipSuccess) return ZC_ERR_HIP;
+  if (ReportSlot* const slot = stream_runs(stream) ? g_reports.take(may_pin) : nullptr) {
+    clear_answer(slot, 2 + count);
+    if (!(count <= 1 ? launch_call_report<1>(slot, ctl, more, count, stream) : launch_call_report<ZC_MAX_K>(slot, ctl, more, count, stream))) {
+      g_reports.give_back(slot);
+      return ZC_ERR_HIP;
+    }
+    return await_answer(g_reports, slot, 2 + count, host, stream) ? read_answer(host, result, count, more_out) : ZC_ERR_HIP;
+  }
+  // no slot, or the stream is being captured, which copy_words knows how to say
   const u64* from[kReportWords] = {&ctl->status, &ctl->call_tag, &ctl->result};
-  u64 host[kReportWords];
   for (u32 i = 0; i < count; ++i) from[3 + i] = more[i];
-  if (!report_words(g_reports, from, 3 + count, host, may_pin, stream)) return ZC_ERR_HIP;
-  return read_answer(host, result, count, more_out);
+  if (!copy_words(from, 3 + count, host, stream)) return ZC_ERR_HIP;
+  host[1] = (host[0] >> 32) == (host[1] >> 32) ? u64(u32(host[0])) : 0u;      // status bits count only under the tag of the last call
+  return read_answer(host + 1, result, count, more_out);
 }
 
 // The answer to a call whose main kernel gives it itself, if it may: somebody waits, the launch is one workgroup and the stream runs.
 // (With an error of an earlier call still to be told, a failed launch could not be told from it, and the slot not be given back.)
 class CallAnswer {
  public:
-  CallAnswer(bool wanted, u64 groups, hipStream_t stream, bool may_pin = true) {
+  // more: values of n that are to travel along.
+  CallAnswer(bool wanted, u64 groups, hipStream_t stream, bool may_pin = true, u32 more = 0) {
     if (!wanted || groups != 1 || hipPeekAtLastError() != hipSuccess || !stream_runs(stream)) return;
     slot_ = g_reports.take(may_pin);
-    if (slot_) seq_ = g_reports.next_seq();
+    if (slot_) clear_answer(slot_, 2 + more);
   }
   bool by_kernel() const { return slot_ != nullptr; }
-  Answer arg() const { return {slot_, seq_}; }
+  Answer arg() const { return {slot_}; }
   // The launches are enqueued (or not).  See finish.
   int collect(bool launched, const void* d_ws, size_t* result, hipStream_t stream, bool wanted, bool may_pin = true, const u64* const* more = nullptr,
               u32 count = 0, u64* more_out = nullptr) {
@@ -133,13 +145,12 @@ class CallAnswer {
     if (!wanted) return ZC_OK;
     if (!slot_) return finish(d_ws, result, stream, may_pin, more, count, more_out);
     u64 host[kReportWords];
-    if (!await_words(g_reports, slot_, seq_, 3 + count, host, stream)) return ZC_ERR_HIP;
+    if (!await_answer(g_reports, slot_, 2 + count, host, stream)) return ZC_ERR_HIP;
     return read_answer(host, result, count, more_out);
   }
 
  private:
   ReportSlot* slot_ = nullptr;
-  u64 seq_ = 0;
 };
 
 // Plain input streams of up to `tiles` tiles, most likely no more than `likely`: whether the main kernel is to sum their
@@ -528,7 +539,7 @@ int zc_decompress_many(const void* const* d_chunks, const size_t* chunk_bytes, i
   const u64* heads[ZC_MAX_K];
   u64 ns[ZC_MAX_K];
   for (int i = 0; i < k; ++i) heads[i] = reinterpret_cast<const u64*>(static_cast<const u8*>(d_chunks[i]) + 8);
-  CallAnswer answer(n_out && (ix || self), tiles * u64(k), stream);      // (one stream then)
+  CallAnswer answer(n_out && (ix || self), tiles * u64(k), stream, true, u32(k));      // (one stream then)
   if (answer.by_kernel()) {
     launch_main(ZC_KERNEL_DECOMPRESS, ix ? decompress_many_kernel<true, false, false, Answer> : decompress_many_kernel<false, true, false, Answer>, dim3(1),
                 dim3(kTileThreads), stream, da, answer.arg());

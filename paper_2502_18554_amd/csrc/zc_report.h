@@ -1,11 +1,12 @@
-// How a synchronous call gets its few result words (status, tag, size) back to the host.
+// How a synchronous call gets its few result words (status and size, or a handful of sums) back to the host.
 //
 // What bounds it: nothing but latency.  A copy to ordinary host memory goes through the runtime's staging
 // buffer and is followed by a wait for the stream: 22 us from launch to answer for a kernel that does nothing,
 // 15 us with pinned memory, 11 us for that kernel and the wait alone.  Here a kernel of one wave, ordered
-// behind the call's kernels on their stream, reads the words and stores them, and then a number that only
-// this request has, into pinned host memory that the calling thread polls: 9 us.  (A compress and a
-// decompress call of 5120 values, each waited for: 57.3 us, then 27.9; 22.8 now that one workgroup answers for itself, see below.)
+// behind the call's kernels on their stream, reads the words and stores them into pinned host memory that the calling thread polls: 9 us with a number behind
+// them that says they are there, which the kernel can store only when they have arrived (0.8 us later), and 8.5 with that said by a bit of every word.  (A compress and a
+// decompress call of 5120 values, each waited for: 57.3 us, then 27.9; 23.1 when one workgroup answered for itself, see below, now 22.9.
+// A waited ring round of 262 177 values 17.2, now 16.4.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,8 +33,43 @@ struct ReportArgs {
 // done 19.0 us where the kernel above takes 16.5, 512 of them 88.
 struct Answer {
   ReportSlot* to;           // null: nobody waits, or by a kernel of its own
-  u64 seq;
 };
+
+// A call's answer as its words go over: status (bits count only under the tag of the last call) and size, and then values of n.
+__device__ __forceinline__ u64 answer_word(const Control* ctl, u32 i) {
+  const u64 w = __hip_atomic_load(i ? &ctl->result : &ctl->status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const u64 tag = __hip_atomic_load(&ctl->call_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return i ? w : (w >> 32) == (tag >> 32) ? u64(u32(w)) : 0ull;
+}
+__device__ __forceinline__ void store_answer_word(ReportSlot* to, u32 i, u64 w) {
+  __hip_atomic_store(&to->words[i], w | kAnswered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// N: room for that many values of n (1, or all: the arguments travel with every launch).
+template <int N>
+struct CallReportArgs {
+  const Control* ctl;
+  ReportSlot* to;
+  u32 count;
+  const u64* more[N];
+};
+template <int N>
+__global__ __launch_bounds__(128) void call_report_kernel(CallReportArgs<N> a) {
+  static_assert(N + 2 <= 128, "a thread per word");
+  if (threadIdx.x < 2) store_answer_word(a.to, threadIdx.x, answer_word(a.ctl, threadIdx.x));
+  else if (threadIdx.x < 2 + a.count) store_answer_word(a.to, threadIdx.x, *a.more[threadIdx.x - 2]);
+}
+
+template <int N>
+inline bool launch_call_report(ReportSlot* slot, const Control* ctl, const u64* const* more, u32 count, hipStream_t stream) {
+  CallReportArgs<N> a;
+  a.ctl = ctl;
+  a.to = slot;
+  a.count = count;
+  for (u32 i = 0; i < count; ++i) a.more[i] = more[i];
+  hipLaunchKernelGGL(call_report_kernel<N>, dim3(1), dim3(N + 2 <= 64 ? 64 : 128), 0, stream, a);
+  return hipGetLastError() == hipSuccess;
+}
 
 template <int N>
 __global__ __launch_bounds__(128) void report_kernel(ReportArgs<N> a) {
@@ -77,13 +113,11 @@ __device__ __forceinline__ void give_answer(const Answer& an, const Control* ctl
   __syncthreads();
   if (wave_id() != 0) return;
   const int lane = lane_id();
-  const u64* const own = lane == 0 ? &ctl->status : lane == 1 ? &ctl->call_tag : &ctl->result;
-  if (lane < 3)
-    __hip_atomic_store(&an.to->words[lane], __hip_atomic_load(own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  if (lane < k)
-    __hip_atomic_store(&an.to->words[3 + lane], reinterpret_cast<const u64*>(heads[lane].base)[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  const u64 own = answer_word(ctl, lane == 0 ? 0u : 1u);
+  const u64 n = lane < k ? reinterpret_cast<const u64*>(heads[lane].base)[1] : 0ull;
   __threadfence_system();
-  if (lane == 0) __hip_atomic_store(&an.to->seq, an.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (lane < 2) store_answer_word(an.to, u32(lane), own);
+  if (lane < k) store_answer_word(an.to, u32(2 + lane), n);
 }
 
 // The same for a kernel that has an instance for the calls that it answers, with an argument more (A = Answer), and one for all others (no A), in which this

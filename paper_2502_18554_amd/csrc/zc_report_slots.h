@@ -69,6 +69,36 @@ inline bool stream_runs(hipStream_t stream) {
   return known && capture == hipStreamCaptureStatusNone;
 }
 
+// A call's answer: every word of it says by its highest bit that it is there (none of them needs that bit: a status, a size, counts of values), so that
+// nothing has to be waited for between them and a last word.  The caller clears the slot's words before it is asked for, and has them all before it is
+// given back.
+constexpr uint64_t kAnswered = uint64_t(1) << 63;
+
+inline void clear_answer(ReportSlot* slot, uint32_t count) {
+  for (uint32_t i = 0; i < count; ++i) __atomic_store_n(&slot->words[i], uint64_t(0), __ATOMIC_RELAXED);
+  __atomic_thread_fence(__ATOMIC_RELEASE);
+}
+
+// Waits for the `count` words of an answer, which something enqueued on `stream` stores in `slot`, and gives the slot back.
+inline bool await_answer(ReportSlots& slots, ReportSlot* slot, uint32_t count, uint64_t* to, hipStream_t stream) {
+  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(500);      // (see await_words)
+  uint32_t have = 0;
+  auto answered = [&] {
+    while (have < count && (__atomic_load_n(&slot->words[have], __ATOMIC_ACQUIRE) & kAnswered) != 0) ++have;
+    return have == count;
+  };
+  bool there = false;
+  for (uint32_t polls = 1; !(there = answered()); ++polls) {
+    __builtin_ia32_pause();
+    if ((polls & 63u) == 0 && std::chrono::steady_clock::now() > until) break;
+  }
+  if (!there) there = hipStreamSynchronize(stream) == hipSuccess && answered();
+  if (!there) return false;      // (with its slot: what was enqueued may still write there, if the GPU comes to it)
+  for (uint32_t i = 0; i < count; ++i) to[i] = __atomic_load_n(&slot->words[i], __ATOMIC_RELAXED) & ~kAnswered;
+  slots.give_back(slot);
+  return true;
+}
+
 // Waits for the answer to request `seq`, which something enqueued on `stream` stores in `slot`, and gives the slot back.
 inline bool await_words(ReportSlots& slots, ReportSlot* slot, uint64_t seq, uint32_t count, uint64_t* to, hipStream_t stream) {
   // Polled for the length of a large call, then left to the runtime, which also knows when no answer can come.
@@ -86,11 +116,8 @@ inline bool await_words(ReportSlots& slots, ReportSlot* slot, uint64_t seq, uint
   return true;
 }
 
-// The words at from[0 .. count) as they are when everything enqueued on `stream` so far has run.  `make`: see take.
-// launch(slot, seq): enqueues on `stream` what stores the words, and then seq, in the slot; false: nothing was enqueued.
-template <typename LaunchFn>
-inline bool report_words(ReportSlots& slots, const uint64_t* const* from, uint32_t count, uint64_t* to, bool make, hipStream_t stream,
-                         LaunchFn launch) {
+// The words at from[0 .. count) as they are when everything enqueued on `stream` so far has run, by copies.
+inline bool copy_words(const uint64_t* const* from, uint32_t count, uint64_t* to, hipStream_t stream) {
   // A stream that is being captured runs nothing, so there is no answer to wait for: the wait for the stream says so (and
   // ends the capture, as it does in any synchronous call).
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -100,14 +127,23 @@ inline bool report_words(ReportSlots& slots, const uint64_t* const* from, uint32
     (void)hipStreamSynchronize(stream);
     return false;
   }
-  ReportSlot* const slot = known ? slots.take(make) : nullptr;
-  if (!slot) {
-    for (uint32_t i = 0, run; i < count; i += run) {
-      for (run = 1; i + run < count && from[i + run] == from[i] + run;) ++run;
-      if (hipMemcpyAsync(to + i, from[i], run * sizeof(uint64_t), hipMemcpyDeviceToHost, stream) != hipSuccess) return false;
-    }
-    return hipStreamSynchronize(stream) == hipSuccess;
+  for (uint32_t i = 0, run; i < count; i += run) {
+    for (run = 1; i + run < count && from[i + run] == from[i] + run;) ++run;
+    if (hipMemcpyAsync(to + i, from[i], run * sizeof(uint64_t), hipMemcpyDeviceToHost, stream) != hipSuccess) return false;
   }
+  return hipStreamSynchronize(stream) == hipSuccess;
+}
+
+// The same by something that stores the words in a slot, if there is one.  `make`: see take.
+// launch(slot, seq): enqueues on `stream` what stores the words, and then seq, in the slot; false: nothing was enqueued.
+template <typename LaunchFn>
+inline bool report_words(ReportSlots& slots, const uint64_t* const* from, uint32_t count, uint64_t* to, bool make, hipStream_t stream,
+                         LaunchFn launch) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool known = hipStreamIsCapturing(stream, &capture) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  ReportSlot* const slot = known && capture == hipStreamCaptureStatusNone ? slots.take(make) : nullptr;
+  if (!slot) return copy_words(from, count, to, stream);
   const uint64_t seq = slots.next_seq();
   if (!launch(slot, seq)) {
     slots.give_back(slot);
