@@ -1,10 +1,11 @@
-"""ctypes binding of libzc.so: argument marshalling only.
+"""Binding of libzc.so by ctypes, and by native code for the calls that a program makes often: argument marshalling only.
 
 Buffers are torch tensors on the GPU (PyTorch is used for device memory and streams only);
 the functions have the names and argument order of include/zc.h.  There is no CPU fallback:
 if the HIP library has not been built, loading it raises.
 """
 import ctypes as C
+import importlib.util
 import os
 from array import array
 
@@ -28,6 +29,7 @@ EXPORTS = [
 ]
 
 _lib = None
+_native = None       # csrc/zc_calls.cpp: the same calls for arguments of the plainest form (NotImplemented for others), once libzc.so is loaded
 
 
 class ZcError(RuntimeError):
@@ -79,11 +81,26 @@ def lib():
         L.zc_profile_enable.argtypes = [C.c_int]
         L.zc_profile_collect.argtypes = [C.POINTER(C.c_float), C.POINTER(C.c_int), C.c_int]
         _lib = L
+        _load_native(L)
     return _lib
 
 
-# Small calls are bound by what happens here (a chunk of a few thousand values runs for 5 us): addresses go to
-# ctypes as plain integers, the current stream's handle is read without building a Stream object around it, and
+def _load_native(L):
+    global _native
+    path = os.path.join(_HERE, "_zc_calls.so")
+    stream_of = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if not os.path.exists(path) or stream_of is None:
+        return
+    spec = importlib.util.spec_from_file_location("_zc_calls", path)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    calls = (L.zc_compress_ex, L.zc_decompress_ex, L.zc_reduce_compressed_op, L.zc_reduce_step_op, L.zc_decompress_many)
+    native.setup(*(C.cast(f, C.c_void_p).value for f in calls), torch._C._cuda_getDevice, stream_of)
+    _native = native
+
+
+# Small calls are bound by what happens here (a chunk of a few thousand values runs for 4 us).  Where ctypes takes a call, addresses go to
+# it as plain integers, the current stream's handle is read without building a Stream object around it, and
 # the result words exist only where a call waits for them.
 def _stream(stream=None):
     if stream is not None:
@@ -136,6 +153,10 @@ def _size(t):
 def zc_compress(d_in, n, abs_eb, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
     """Returns (status, total_bytes); total_bytes is None in the asynchronous form.  flags 0 goes through
     zc_compress, anything else through zc_compress_ex."""
+    if _native:
+        r = _native.compress(d_in, n, abs_eb, d_out, d_ws, sync, stream, out_cap, flags)
+        if r is not NotImplemented:
+            return r
     nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     args = [_p(d_in), n, abs_eb, _p(d_out), cap, C.byref(nbytes) if sync else None, _p(d_ws), _size(d_ws), _stream(stream)]
@@ -167,6 +188,10 @@ def zc_compress_part(d_in, n, abs_eb, first_value, count, d_out, d_ws, sync=True
 def zc_decompress(d_in, in_bytes, d_out, d_ws, sync=True, stream=None, out_cap_elems=None, flags=0):
     """Returns (status, n); n is None in the asynchronous form.  flags 0 goes through zc_decompress,
     anything else through zc_decompress_ex."""
+    if _native:
+        r = _native.decompress(d_in, in_bytes, d_out, d_ws, sync, stream, out_cap_elems, flags)
+        if r is not NotImplemented:
+            return r
     n = C.c_size_t(0)
     cap = (d_out.numel() if d_out is not None else 0) if out_cap_elems is None else out_cap_elems
     args = [_p(d_in), in_bytes, _p(d_out), cap, C.byref(n) if sync else None, _p(d_ws), _size(d_ws), _stream(stream)]
@@ -196,6 +221,10 @@ def zc_decompress_range(d_in, in_bytes, first_value, count, d_out, d_ws, sync=Tr
 def zc_reduce_compressed(d_chunks, chunk_bytes, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
     """d_chunks: list of device tensors holding the k operand streams.  Returns (status, total_bytes).
     flags 0 goes through zc_reduce_compressed, anything else through zc_reduce_compressed_ex."""
+    if _native:
+        r = _native.reduce(d_chunks, chunk_bytes, ZC_OP_SUM, d_out, d_ws, sync, stream, out_cap, flags)
+        if r is not NotImplemented:
+            return r
     k = len(d_chunks)
     lists, at = _lists(k, [t.data_ptr() for t in d_chunks], chunk_bytes)
     nbytes = C.c_size_t(0) if sync else None
@@ -207,6 +236,10 @@ def zc_reduce_compressed(d_chunks, chunk_bytes, d_out, d_ws, sync=True, stream=N
 
 def zc_reduce_compressed_op(d_chunks, chunk_bytes, op, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
     """zc_reduce_compressed for Sum, Max or Min (ZC_OP_*).  Returns (status, total_bytes)."""
+    if _native:
+        r = _native.reduce(d_chunks, chunk_bytes, op, d_out, d_ws, sync, stream, out_cap, flags)
+        if r is not NotImplemented:
+            return r
     k = len(d_chunks)
     lists, at = _lists(k, [t.data_ptr() for t in d_chunks], chunk_bytes)
     nbytes = C.c_size_t(0) if sync else None
@@ -241,6 +274,10 @@ def zc_reduce_step_part(d_chunk, chunk_bytes, d_local, n_local, op, first_value,
 
 def zc_decompress_many(d_chunks, chunk_bytes, d_outs, d_ws, sync=True, stream=None, out_cap_elems=None, flags=0):
     """d_chunks / d_outs: lists of k device tensors.  Returns (status, [n of every stream]) (None when not sync)."""
+    if _native:
+        r = _native.many(d_chunks, chunk_bytes, d_outs, d_ws, sync, stream, out_cap_elems, flags)
+        if r is not NotImplemented:
+            return r
     k = len(d_chunks)
     lists, at = _lists(k, [t.data_ptr() for t in d_chunks], chunk_bytes, [t.data_ptr() for t in d_outs],
                        [t.numel() for t in d_outs] if out_cap_elems is None else out_cap_elems)
@@ -256,7 +293,7 @@ ZC_OP_SUM, ZC_OP_MAX, ZC_OP_MIN = 0, 1, 2
 def zc_reduce_step(d_chunk, chunk_bytes, d_local, n_local, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
     """One ring round: received stream + local fp32 values -> stream of the sums.  Returns (status, total_bytes).
     flags 0 goes through zc_reduce_step, anything else through zc_reduce_step_op."""
-    if flags:
+    if flags or _native:
         return zc_reduce_step_op(d_chunk, chunk_bytes, d_local, n_local, ZC_OP_SUM, d_out, d_ws, sync, stream, out_cap, flags)
     nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
@@ -268,6 +305,10 @@ def zc_reduce_step(d_chunk, chunk_bytes, d_local, n_local, d_out, d_ws, sync=Tru
 def zc_reduce_step_op(d_chunk, chunk_bytes, d_local, n_local, op, d_out, d_ws, sync=True, stream=None, out_cap=None,
                       flags=0):
     """zc_reduce_step for Sum, Max or Min.  Returns (status, total_bytes)."""
+    if _native:
+        r = _native.step(d_chunk, chunk_bytes, d_local, n_local, op, d_out, d_ws, sync, stream, out_cap, flags)
+        if r is not NotImplemented:
+            return r
     nbytes = C.c_size_t(0) if sync else None
     cap = _size(d_out) if out_cap is None else out_cap
     st = lib().zc_reduce_step_op(_p(d_chunk), int(chunk_bytes), _p(d_local), int(n_local), int(op), _p(d_out), cap,

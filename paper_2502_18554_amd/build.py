@@ -1,11 +1,13 @@
-"""Build the HIP library (csrc/*.hip -> libzc.so) for gfx950 with hipcc, in-tree."""
+"""Build the HIP library (csrc/*.hip -> libzc.so) for gfx950 with hipcc, and the native calls of the binding (_zc_calls.so), in-tree."""
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libzc.so")
 SOURCES = ["zc_api.hip"]
+CALLS = os.path.join(HERE, "_zc_calls.so")
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-shared",
@@ -19,6 +21,11 @@ def build(verbose=False, extra=()):
     cmd = ["hipcc", *FLAGS, *extra, *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB]
     if verbose:
         print(" ".join(cmd))
+    calls = ["g++", "-O2", "-std=c++17", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"],
+             os.path.join(CSRC, "zc_calls.cpp"), "-o", CALLS]
+    if verbose:
+        print(" ".join(calls))
+    subprocess.run(calls, check=True)
     subprocess.run(cmd, check=True)
     return LIB
 
