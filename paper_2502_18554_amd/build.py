@@ -13,6 +13,7 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-shared",
     "-ffp-contract=off",                                     # quantisation is defined by separate roundings
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",            # a kernel's leading scalar arguments are in registers when a wave starts
     "-Wall", "-Wno-unused-function",
 ]
 

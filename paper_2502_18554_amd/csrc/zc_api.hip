@@ -262,10 +262,10 @@ void launch_compress(CompressArgs& ca, u32 first_tile, u32 end_tile, bool timed,
     hipLaunchKernelGGL(empty_stream_kernel, dim3(1), dim3(64), 0, stream, ea);
     return;
   }
-  void (*kernel)(CompressArgs, u32, u32) = ca.ticketed ? compress_kernel<true> : compress_kernel<false>;
-  if (timed && packs_small_tiles(ca)) launch_main(ZC_KERNEL_COMPRESS, compress_kernel<false, kTileWaves>, dim3(end_tile), dim3(kTileThreads), stream, ca, first_tile, end_tile);
-  else if (timed) launch_main(ZC_KERNEL_COMPRESS, kernel, dim3(end_tile - first_tile), dim3(kPackThreads), stream, ca, first_tile, end_tile);
-  else hipLaunchKernelGGL(kernel, dim3(end_tile - first_tile), dim3(kPackThreads), 0, stream, ca, first_tile, end_tile);
+  void (*kernel)(const float*, u64, u32, u32, CompressArgs) = ca.ticketed ? compress_kernel<true> : compress_kernel<false>;
+  if (timed && packs_small_tiles(ca)) launch_main(ZC_KERNEL_COMPRESS, compress_kernel<false, kTileWaves>, dim3(end_tile), dim3(kTileThreads), stream, ca.in, ca.n, first_tile, end_tile, ca);
+  else if (timed) launch_main(ZC_KERNEL_COMPRESS, kernel, dim3(end_tile - first_tile), dim3(kPackThreads), stream, ca.in, ca.n, first_tile, end_tile, ca);
+  else hipLaunchKernelGGL(kernel, dim3(end_tile - first_tile), dim3(kPackThreads), 0, stream, ca.in, ca.n, first_tile, end_tile, ca);
 }
 
 // Workspace of zc_compress_noalloc: a device array of the library itself, one copy per GPU,
@@ -292,6 +292,8 @@ void* scratch_of_current_device() {
 }  // namespace
 
 namespace {
+template <typename... A>
+using DecompressKernel = void(const u8*, u64, DecompressArgs, A...);
 template <int OP>
 void (*pick_step_kernel(bool ix, bool self, bool tickets, u64 tiles))(StepArgs) {
   if (ix && tiles >= kStepMany) return tickets ? step_kernel<true, false, OP, true, 6> : step_kernel<true, false, OP, false, 6>;
@@ -328,11 +330,11 @@ void (*answering_sum_kernel(bool ix, int segs))(ReduceArgs, Answer) {
   return ix ? reduce_kernel<true, Answer> : reduce_kernel<false, Answer>;
 }
 template <bool AVERAGE>
-void (*pick_decompress_kernel(bool ix))(DecompressArgs) {
+DecompressKernel<>* pick_decompress_kernel(bool ix) {
   return ix ? decompress_kernel<true, false, AVERAGE> : decompress_kernel<false, true, AVERAGE>;
 }
 template <bool AVERAGE>
-void (*answering_decompress_kernel(bool ix, bool self))(DecompressArgs, Answer) {
+DecompressKernel<Answer>* answering_decompress_kernel(bool ix, bool self) {
   return ix ? decompress_kernel<true, false, AVERAGE, Answer> : self ? decompress_kernel<false, true, AVERAGE, Answer> : decompress_kernel<false, false, AVERAGE, Answer>;
 }
 }  // namespace
@@ -475,9 +477,9 @@ static int decompress_one(const void* d_in, size_t in_bytes, size_t first_value,
     hipLaunchKernelGGL(kernel, dim3(u32(grid)), dim3(kTileThreads), 0, stream, da);
   } else if (answer.by_kernel() || !(ix || self)) {      // (see AnswerAtEnd)
     launch_main(ZC_KERNEL_DECOMPRESS, average ? answering_decompress_kernel<true>(ix, self) : answering_decompress_kernel<false>(ix, self), dim3(u32(grid)),
-                dim3(kTileThreads), stream, da, answer.arg());
+                dim3(kTileThreads), stream, da.in.base, da.in.bytes, da, answer.arg());
   } else {
-    launch_main(ZC_KERNEL_DECOMPRESS, average ? pick_decompress_kernel<true>(ix) : pick_decompress_kernel<false>(ix), dim3(u32(grid)), dim3(kTileThreads), stream, da);
+    launch_main(ZC_KERNEL_DECOMPRESS, average ? pick_decompress_kernel<true>(ix) : pick_decompress_kernel<false>(ix), dim3(u32(grid)), dim3(kTileThreads), stream, da.in.base, da.in.bytes, da);
   }
   return answer.collect(launch_ok(), d_ws, n_out, stream, n_out != nullptr);
 }

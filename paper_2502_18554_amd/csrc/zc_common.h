@@ -359,22 +359,25 @@ __device__ inline T* at_bytes(T* uniform_base, u32 byte_offset) {
   return reinterpret_cast<T*>(reinterpret_cast<Byte*>(uniform_base) + byte_offset);
 }
 
-// The first argument of the running kernel, a struct, where it lies in memory, so that its fields are loaded where they are used.  (Fields of
+// An argument of the running kernel, a struct, where it lies in memory, so that its fields are loaded where they are used.  (Fields of
 // a parameter that is handed on by reference are all loaded at the kernel's start, and wait in scalar registers, or spilled.  Which is better was measured: ring rounds
 // of 2^24 values by ticket 40.1 us from a parameter, 38.3 from here; of plain streams of 2^22 13.7 and 13.9; the compression of 2^24 values 19.1 and 27.9, for
 // it uses its fields in many places.)
-template <typename Args>
+// AT: bytes in front of it.
+template <typename Args, int AT>
 __device__ __forceinline__ const Args& kernel_args() {
   typedef const __attribute__((address_space(4))) Args Constant;
-  return *(const Args*)(Constant*)__builtin_amdgcn_kernarg_segment_ptr();
+  typedef const __attribute__((address_space(4))) char Byte;
+  return *(const Args*)(Constant*)((Byte*)__builtin_amdgcn_kernarg_segment_ptr() + AT);
 }
 
 // The same, in a way that keeps the compiler from seeing that these are the values it has: for a path that is hardly ever taken, so that what only that path needs is
 // loaded there instead of waiting for it in scalar registers.
-template <typename Args>
+template <typename Args, int AT>
 __device__ __forceinline__ const Args& kernel_args_again() {
   typedef const __attribute__((address_space(4))) Args Constant;
-  Constant* p = (Constant*)__builtin_amdgcn_kernarg_segment_ptr();
+  typedef const __attribute__((address_space(4))) char Byte;
+  Constant* p = (Constant*)((Byte*)__builtin_amdgcn_kernarg_segment_ptr() + AT);
   asm volatile("" : "+s"(p));
   return *(const Args*)p;
 }

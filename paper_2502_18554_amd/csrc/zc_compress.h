@@ -48,6 +48,15 @@ struct CompressArgs {
   Answer answer;
 };
 
+// What a workgroup's first loads need comes ahead of the other arguments, one by one: such arguments are in scalar registers when a wave starts (the compiler is told so,
+// see build.py), and others are asked for and waited for.  (The compression of 2^22 values of a field 7.41 us, then 6.94; 2^24: 19.2 18.7; 512^3: 116.9 116.0; the
+// decompression of 2^23 8.0, then 7.9.  Not for the ring round, which needs nine registers for them: 2^22 values 9.26 and 9.09, but 2^24 25.1 and 26.0.)
+struct CompressInput {
+  const float* in;
+  u64 n;
+};
+constexpr int kCompressArgsAt = 24;          // bytes of arguments in front of CompressArgs
+
 // Round-to-nearest-even of r for |r| < 2^31 as the low word of r + 1.5 * 2^52.
 __device__ inline i32 rint_small(double r) {
   double t = __dadd_rn(r, 6755399441055744.0);
@@ -125,9 +134,9 @@ __device__ inline u32 share_values(u64 n, u64 v0) {
 // and no launch of its own: what lies beyond reads as zero without an access.  (The one to three values of an
 // incomplete last piece: see block_codes.)  The range check covers the vector offset and the instruction's own; a
 // scalar offset is not part of it, so there is none: the second four loads have a vector offset of their own.
-__device__ inline void load_raw(const CompressArgs& a, u64 wblock0, int lane, u32 have, float4 (&x)[8]) {
+__device__ inline void load_raw(const float* in, u64 wblock0, int lane, u32 have, float4 (&x)[8]) {
   const __amdgpu_buffer_rsrc_t share =
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.in + wblock0 * kBlockValues), 0, int(4u * (have & ~3u)), kRawBuffer);
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(in + wblock0 * kBlockValues), 0, int(4u * (have & ~3u)), kRawBuffer);
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const u32x4_t t = __builtin_amdgcn_raw_buffer_load_b128(share, 16 * lane + 1024 * i, 0, kAccessOnce);
@@ -261,7 +270,7 @@ __device__ inline u32 from_lane(u32 v, u32 src) { return u32(__builtin_amdgcn_ds
 __device__ __forceinline__ void stage_wide_blocks(const Placement& pl, u64 wblock0, u64 wide, u32* wl) {
   CompressArgs a;
   {
-    const CompressArgs& again = kernel_args_again<CompressArgs>();
+    const CompressArgs& again = kernel_args_again<CompressArgs, kCompressArgsAt>();
     a.in = again.in;
     a.n = again.n;
     a.inv = again.inv;
@@ -301,7 +310,7 @@ __device__ __forceinline__ void store_wide_wave(const CompressArgs& a, const Pay
   {
     float4 x[8];
     u32 ignored = 0;                           // errors were raised on the first pass
-    load_raw(a, wblock0, lane, have, x);
+    load_raw(a.in, wblock0, lane, have, x);
     block_codes<TICKETS>(a, x, wblock0, have, lane, wl, q, ignored);
   }
 #pragma unroll
@@ -340,7 +349,7 @@ __host__ inline bool packs_small_tiles(const CompressArgs& a) {
 }
 
 template <bool TICKETS, int WAVES>
-__device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_tile, u32 end_tile, u32 (&lds)[WAVES * kWaveStage], u32& sh_tile,
+__device__ __forceinline__ void compress_tile(const CompressInput& first, const CompressArgs& a, u32 first_tile, u32 end_tile, u32 (&lds)[WAVES * kWaveStage], u32& sh_tile,
                                              u32 (&sh_wave_total)[WAVES], u64 (&sh_base)[WAVES]) {
   constexpr int kBlocks = WAVES * kWaveBlocks;
   constexpr bool FEW = WAVES != kPackWaves;
@@ -351,8 +360,8 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
   float4 x[8];
   if (!TICKETS) {
     const u64 wblock0 = u64(tile) * kBlocks + u64(wave) * kWaveBlocks;
-    have = share_values(a.n, wblock0 * kBlockValues);
-    load_raw(a, wblock0, lane, have, x);
+    have = share_values(first.n, wblock0 * kBlockValues);
+    load_raw(first.in, wblock0, lane, have, x);
   }
   const u32 ntiles = (u32(a.nb) + kBlocks - 1) / kBlocks;
   u32* const wl = lds + wave * kWaveStage;
@@ -380,7 +389,7 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
     const bool active = u32(wblock0) + u32(lane) < u32(a.nb);      // (a stream has at most 2^26 blocks)
     if (TICKETS) {
       have = share_values(a.n, wblock0 * kBlockValues);
-      load_raw(a, wblock0, lane, have, x);
+      load_raw(a.in, wblock0, lane, have, x);
     }
 
     BlockFields bf;
@@ -447,12 +456,12 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, u32 first_t
 }
 
 template <bool TICKETS, int WAVES = kPackWaves>
-__global__ __launch_bounds__(64 * WAVES, WAVES == kPackWaves ? 8 : 4) void compress_kernel(CompressArgs a, u32 first_tile, u32 end_tile) {
+__global__ __launch_bounds__(64 * WAVES, WAVES == kPackWaves ? 8 : 4) void compress_kernel(const float* in, u64 n, u32 first_tile, u32 end_tile, CompressArgs a) {
   __shared__ __attribute__((aligned(16))) u32 lds[WAVES * kWaveStage];
   __shared__ u32 sh_tile;
   __shared__ u32 sh_wave_total[WAVES];
   __shared__ u64 sh_base[WAVES];
-  compress_tile<TICKETS, WAVES>(a, first_tile, end_tile, lds, sh_tile, sh_wave_total, sh_base);
+  compress_tile<TICKETS, WAVES>({in, n}, a, first_tile, end_tile, lds, sh_tile, sh_wave_total, sh_base);
   give_answer(a.answer, a.ctl);
 }
 

@@ -359,11 +359,12 @@ __device__ __forceinline__ void decompress_tile(const StreamRef* streams, int k,
 }
 
 template <bool IX, bool SELF, bool AVERAGE, typename... A>
-__global__ __launch_bounds__(kTileThreads, 5) void decompress_kernel(DecompressArgs a, A... answer) {
+__global__ __launch_bounds__(kTileThreads, 5) void decompress_kernel(const u8* base, u64 bytes, DecompressArgs a, A... answer) {
   __shared__ __attribute__((aligned(16))) u32 lds[kTileWaves * kWaveStage];
   __shared__ PlainSurvey<1> survey;
   const AnswerAtEnd<DecompressArgs, A...> at_end(a, answer...);
-  decompress_tile<IX, SELF, 1>(&a.in, 1, 0, a.out, a.out_cap_elems, a.index, a.ctl, a.nonce, lds, &survey, AVERAGE);
+  const StreamRef in{base, bytes};           // (what the first loads need, see CompressInput)
+  decompress_tile<IX, SELF, 1>(&in, 1, 0, a.out, a.out_cap_elems, a.index, a.ctl, a.nonce, lds, &survey, AVERAGE);
 }
 
 // A part of a stream (see decompress_tile).

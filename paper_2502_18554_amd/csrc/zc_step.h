@@ -655,7 +655,7 @@ __global__ __launch_bounds__(kTileThreads, GROUPS) void step_kernel(StepArgs a, 
   __shared__ PlainSurvey<1> survey;
   const AnswerAtEnd<StepArgs, A...> at_end(a, answer...);
   // (The arguments where they lie, see kernel_args, but for plain streams by workgroup id.)
-  if constexpr (IX || TICKETS) step_tile<IX, SELF, OP, TICKETS, GROUPS>(kernel_args<StepArgs>(), lds, sh_tile, sh_wave_total, sh_base, survey);
+  if constexpr (IX || TICKETS) step_tile<IX, SELF, OP, TICKETS, GROUPS>(kernel_args<StepArgs, 0>(), lds, sh_tile, sh_wave_total, sh_base, survey);
   else step_tile<IX, SELF, OP, TICKETS, GROUPS>(a, lds, sh_tile, sh_wave_total, sh_base, survey);
 }
 
