@@ -307,12 +307,13 @@ void (*pick_op_kernel(bool ix, int segs))(ReduceArgs) {
   if (segs == 2) return ix ? reduce_op_kernel<true, OP, 2> : reduce_op_kernel<false, OP, 2>;
   return ix ? reduce_op_kernel<true, OP> : reduce_op_kernel<false, OP>;
 }
-// segs: 0: not by reduce_few_kernel.
-void (*pick_sum_kernel(bool ix, int segs, u64 likely))(ReduceArgs) {
+// segs: 0: not by reduce_few_kernel.  large: see sum_large_tiles.
+void (*pick_sum_kernel(bool ix, int segs, u64 likely, bool large))(ReduceArgs) {
   if (segs == 1) return ix ? reduce_few_kernel<true, 1, 4> : reduce_few_kernel<false, 1, 4>;
   if (segs == 2) return ix ? reduce_few_kernel<true, 2, 4> : reduce_few_kernel<false, 2, 4>;
   if (segs && likely <= kFewTiles) return ix ? reduce_few_kernel<true, 4, 4> : reduce_few_kernel<false, 4, 4>;
   if (segs) return reduce_few_kernel<true, 4, 2>;
+  if (large) return reduce_kernel<true, kLargeWaves>;
   return ix ? reduce_kernel<true> : reduce_kernel<false>;
 }
 // The same for calls of one workgroup that answer themselves.  (That is one tile of four segments: no tickets, and none of the Sums, Maxima and Minima whose
@@ -327,7 +328,7 @@ void (*answering_op_kernel(bool ix))(ReduceArgs, Answer) {
 }
 void (*answering_sum_kernel(bool ix, int segs))(ReduceArgs, Answer) {
   if (segs) return ix ? reduce_few_kernel<true, 4, 4, Answer> : reduce_few_kernel<false, 4, 4, Answer>;
-  return ix ? reduce_kernel<true, Answer> : reduce_kernel<false, Answer>;
+  return ix ? reduce_kernel<true, kTileWaves, Answer> : reduce_kernel<false, kTileWaves, Answer>;
 }
 template <bool AVERAGE>
 DecompressKernel<>* pick_decompress_kernel(bool ix) {
@@ -625,13 +626,15 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   else if (!ranged && !ra.ticketed) segs = few_segments(k, likely);
   if (op == ZC_OP_SUM && likely > kFewTiles && !ix) segs = 0;
   if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
+  const bool large = op == ZC_OP_SUM && !segs && ix && !ranged && !ra.ticketed && sum_large_tiles(k, likely);
+  if (large) tiles = (tiles + 1) / 2;
   CallAnswer answer(out_bytes && !ranged, tiles, stream);
   if (answer.by_kernel()) {
     void (*kernel)(ReduceArgs, Answer) = op == ZC_OP_SUM ? answering_sum_kernel(ix, segs) : op == ZC_OP_MAX ? answering_op_kernel<ZC_OP_MAX>(ix) : answering_op_kernel<ZC_OP_MIN>(ix);
     launch_main(ZC_KERNEL_REDUCE, kernel, dim3(1), dim3(kTileThreads), stream, ra, answer.arg());
   } else {
-    void (*kernel)(ReduceArgs) = op == ZC_OP_SUM ? pick_sum_kernel(ix, segs, likely) : op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs) : pick_op_kernel<ZC_OP_MIN>(ix, segs);
-    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(kTileThreads), stream, ra);
+    void (*kernel)(ReduceArgs) = op == ZC_OP_SUM ? pick_sum_kernel(ix, segs, likely, large) : op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs) : pick_op_kernel<ZC_OP_MIN>(ix, segs);
+    launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(large ? 64 * kLargeWaves : kTileThreads), stream, ra);
   }
   return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr);
 }
