@@ -302,7 +302,8 @@ void (*pick_step_kernel(bool ix, bool self, bool tickets, u64 tiles))(StepArgs) 
   return tickets ? step_kernel<false, false, OP, true> : step_kernel<false, false, OP, false>;
 }
 template <int OP>
-void (*pick_op_kernel(bool ix, int segs))(ReduceArgs) {
+void (*pick_op_kernel(bool ix, int segs, bool large))(ReduceArgs) {
+  if (large) return reduce_op_kernel<true, OP, kLargeWaves>;
   if (segs == 1) return ix ? reduce_op_kernel<true, OP, 1> : reduce_op_kernel<false, OP, 1>;
   if (segs == 2) return ix ? reduce_op_kernel<true, OP, 2> : reduce_op_kernel<false, OP, 2>;
   return ix ? reduce_op_kernel<true, OP> : reduce_op_kernel<false, OP>;
@@ -626,14 +627,14 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   else if (!ranged && !ra.ticketed) segs = few_segments(k, likely);
   if (op == ZC_OP_SUM && likely > kFewTiles && !ix) segs = 0;
   if (segs) tiles = tiles * u64(kTileWaves) / u64(segs);
-  const bool large = op == ZC_OP_SUM && !segs && ix && !ranged && !ra.ticketed && sum_large_tiles(k, likely);
+  const bool large = ix && !ranged && !ra.ticketed && (op == ZC_OP_SUM ? !segs && sum_large_tiles(k, likely) : op_large_tiles(k, likely));
   if (large) tiles = (tiles + 1) / 2;
   CallAnswer answer(out_bytes && !ranged, tiles, stream);
   if (answer.by_kernel()) {
     void (*kernel)(ReduceArgs, Answer) = op == ZC_OP_SUM ? answering_sum_kernel(ix, segs) : op == ZC_OP_MAX ? answering_op_kernel<ZC_OP_MAX>(ix) : answering_op_kernel<ZC_OP_MIN>(ix);
     launch_main(ZC_KERNEL_REDUCE, kernel, dim3(1), dim3(kTileThreads), stream, ra, answer.arg());
   } else {
-    void (*kernel)(ReduceArgs) = op == ZC_OP_SUM ? pick_sum_kernel(ix, segs, likely, large) : op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs) : pick_op_kernel<ZC_OP_MIN>(ix, segs);
+    void (*kernel)(ReduceArgs) = op == ZC_OP_SUM ? pick_sum_kernel(ix, segs, likely, large) : op == ZC_OP_MAX ? pick_op_kernel<ZC_OP_MAX>(ix, segs, large) : pick_op_kernel<ZC_OP_MIN>(ix, segs, large);
     launch_main(ZC_KERNEL_REDUCE, kernel, dim3(u32(tiles)), dim3(large ? 64 * kLargeWaves : kTileThreads), stream, ra);
   }
   return answer.collect(launch_ok(), d_ws, out_bytes, stream, out_bytes != nullptr);

@@ -1,4 +1,4 @@
-"""Sums of few operands by tiles of eight segments: the limits of the rule that picks them, and last tiles of one segment, of four and of
+"""Reduces by tiles of eight segments: the limits of the rule that picks them, and last tiles of one segment, of four and of
 five, with wide blocks and without, against the reference codec."""
 import numpy as np
 import pytest
@@ -34,3 +34,23 @@ def test_sum_by_large_tiles(zcref, k, segments, wide):
     st, r, _ = u.gpu_reduce(refs, n)
     assert st == st_ref == ZC_OK and r.tobytes() == ref.tobytes(), u.first_diff(r, ref)
 
+
+# Max and Min: both sides of 768 tiles, of 1024 and of 1400, and beyond 4096 with two operands
+@pytest.mark.parametrize("k,op,segments", [(2, 1, 768 * 4), (2, 2, 768 * 4 + 1), (3, 1, 1024 * 4), (3, 2, 1024 * 4 + 5), (2, 1, 1024 * 4 + 4), (4, 1, 1400 * 4 + 1),
+                                           (2, 2, 4096 * 4 + 5)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_extremes_by_large_tiles(zcref, k, op, segments, wide):
+    n = segments * SEG - 33
+    base = synth.sinusoids(n, seed=12).numpy()
+    eb = synth.abs_bound(torch.from_numpy(base), 1e-3)
+    refs = []
+    for i in range(k):
+        x = np.roll(base, 977 * i) if i else base.copy()
+        if wide:
+            x[np.random.default_rng(i).integers(0, n, 40)] = 900.0 if i else -900.0
+            if i == 0:
+                x[5 * SEG:6 * SEG:2] = 900.0
+        refs.append(zcref.compress(x, eb)[1])
+    st_ref, ref = zcref.reduce(refs, op=op)[:2]
+    st, r, _ = u.gpu_reduce(refs, n, op=op)
+    assert st == st_ref == ZC_OK and r.tobytes() == ref.tobytes(), u.first_diff(r, ref)
