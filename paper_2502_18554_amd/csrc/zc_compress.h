@@ -262,6 +262,17 @@ __device__ __forceinline__ void store_block_ballots(i32 nd, u32 w_a, u32 w_b, u3
 // The value of `v` in lane `src` (any lane, chosen per lane).
 __device__ inline u32 from_lane(u32 v, u32 src) { return u32(__builtin_amdgcn_ds_bpermute(int((src & 63u) << 2), int(v))); }
 
+// Blocks wider than 15 bits of a wave up to which they are staged one by one (see stage_wide_blocks): two of them a step, and every step waits for its values, where a wave
+// that goes over all its values again (store_wide_wave) loads them once.  A tile of four waves has its look-back to fill with that, one step; where eight waves share a SIMD
+// and the values are in flight for other waves, three steps still pay.  us, every wave with so many blocks of 16 bits among narrow ones: all staged | none | by this rule
+//            1                   2                   3                   4                   6                   8                    32
+//   2^20     6.9   7.9   7.0     6.9   8.1   7.0     8.4   8.1   7.9     8.4   8.1   7.9     9.8   8.1   7.9    11.2   8.1   8.0    27.8   8.5   8.3
+//   2^23    11.6  16.7  11.6    11.5  16.7  11.6    13.5  16.8  13.4    13.6  16.8  13.5    15.6  16.8  15.3    17.4  16.9  15.6    40.0  17.6  16.5
+//   2^26    62.7 100.8  62.7    63.3 100.6  62.9    71.5 100.7  71.1    71.9 101.2  71.5    81.3 101.6  81.0    91.5 101.5 100.4     222   107   106
+// (one wave in ten with such blocks, 2^26: 58.2 69.1 58.0 | 57.9 69.7 57.9 | 61.2 70.0 60.8 | 61.1 70.1 61.2 | 66.0 69.7 65.3 | 71.1 69.9 67.8 | 138 71 69)
+template <int WAVES>
+constexpr int kStagedWide = WAVES == kPackWaves ? 6 : 2;
+
 // A block wider than 15 bits: the 16-bit fields are of no use then, and 32 deltas of 32 bits do not fit the registers beside
 // everything else.  Its values are fetched and quantised again, and its words staged beside those of the wave's other blocks while the look-back is under way: 32 lanes a
 // block, two blocks a step.  There are few of them as a rule: of the hard-data configuration one block in 3000, one wave in 50, one tile in 6.
@@ -299,7 +310,7 @@ __device__ __forceinline__ void stage_wide_blocks(const Placement& pl, u64 wbloc
   }
 }
 
-// A wave whose words are more than its staging area is made for: most of its blocks are wide then.  Once the wave's place is known it fetches and quantises all its values
+// A wave with more wide blocks than that, or with more words than its staging area is made for.  Once the wave's place is known it fetches and quantises all its values
 // again, turns them into sign and plane words and stores those.  Only that wave does, and no tile waits for it.
 // (2^28 hard values, compressed and decompressed, when a tile with a wide block stored all its blocks by ballots: 674 us, then 455.)
 template <bool TICKETS>
@@ -414,7 +425,8 @@ __device__ __forceinline__ void compress_tile(const CompressInput& first, const 
     if (threadIdx.x == 0) publish_tile_size(sink, tile, pl.tile_total, pl.tile_wide);
 
     // ---- fields -> sign + plane words, then the back half ----
-    const bool staged = pl.wave_total <= 64u * 16u;      // uniform (always, without wide blocks)
+    // uniform (always, without wide blocks)
+    const bool staged = pl.wmax <= 15 || (pl.wave_total <= 64u * 16u && __builtin_popcountll(__ballot(pl.w > 15)) <= kStagedWide<WAVES>);
     const TileBase tb = resolve_tile_base(sink, pl, tile, sh_base, wave, lane, [&] {
       if (!staged) return;
       constexpr u32 kAside = 64 * 16 + 16;

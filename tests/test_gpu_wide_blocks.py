@@ -33,6 +33,20 @@ def test_wide_blocks(zcref, n, which):
     _compare(zcref, x)
 
 
+# both sides of the limits from which a wave with wide blocks goes over all its values again: two of them in small tiles, six in large ones
+@pytest.mark.parametrize("n", [9 * 8192 - 31, 300 * 8192 - 2048 - 1])
+@pytest.mark.parametrize("count", [1, 2, 3, 6, 7, 8])
+def test_number_of_wide_blocks(zcref, n, count):
+    rng = np.random.default_rng(n + count)
+    x = (np.sin(np.arange(n) / 300.0) + rng.normal(0, 1e-3, n)).astype(np.float32)
+    for wave in range(0, (n + 2047) // 2048, 2):   # every other wave, the ragged last one among them
+        for b in rng.choice(62, count, replace=False):
+            at = wave * 2048 + 32 * int(b) + int(rng.integers(0, 32))
+            if at < n:
+                x[at] = rng.choice((-1, 1)) * rng.uniform(100, 900)
+    _compare(zcref, x)
+
+
 # a wave of constant blocks but for `wide` of 30 planes, 31 words each: 1023 words, 1054, and the whole wave
 @pytest.mark.parametrize("wide", [1, 32, 33, 34, 64])
 def test_words_of_a_wave(zcref, wide):
