@@ -104,23 +104,12 @@ int read_answer(const u64* host, size_t* result, u32 count, u64* more_out) {
 int finish(const void* d_ws, size_t* result, hipStream_t stream, bool may_pin = true, const u64* const* more = nullptr, u32 count = 0,
            u64* more_out = nullptr) {
   const Control* const ctl = static_cast<const Control*>(d_ws);
-  u64 host[kReportWords + 1];
-  // (An error of an earlier call still to be told could not be told from a failed launch: then a slot would be given back that is still written to.)
-  if (hipGetLastError() != hipSuccess) return ZC_ERR_HIP;
-  if (ReportSlot* const slot = stream_runs(stream) ? g_reports.take(may_pin) : nullptr) {
-    clear_answer(slot, 2 + count);
-    if (!(count <= 1 ? launch_call_report<1>(slot, ctl, more, count, stream) : launch_call_report<ZC_MAX_K>(slot, ctl, more, count, stream))) {
-      g_reports.give_back(slot);
-      return ZC_ERR_HIP;
-    }
-    return await_answer(g_reports, slot, 2 + count, host, stream) ? read_answer(host, result, count, more_out) : ZC_ERR_HIP;
-  }
-  // no slot, or the stream is being captured, which copy_words knows how to say
-  const u64* from[kReportWords] = {&ctl->status, &ctl->call_tag, &ctl->result};
-  for (u32 i = 0; i < count; ++i) from[3 + i] = more[i];
-  if (!copy_words(from, 3 + count, host, stream)) return ZC_ERR_HIP;
-  host[1] = (host[0] >> 32) == (host[1] >> 32) ? u64(u32(host[0])) : 0u;      // status bits count only under the tag of the last call
-  return read_answer(host + 1, result, count, more_out);
+  const u64* const own[3] = {&ctl->status, &ctl->call_tag, &ctl->result};
+  u64 host[kReportWords];
+  const bool told = fetch_answer(g_reports, own, more, count, host, may_pin, stream, [&](ReportSlot* slot) {
+    return count <= 1 ? launch_call_report<1>(slot, ctl, more, count, stream) : launch_call_report<ZC_MAX_K>(slot, ctl, more, count, stream);
+  });
+  return told ? read_answer(host, result, count, more_out) : ZC_ERR_HIP;
 }
 
 // The answer to a call whose main kernel gives it itself, if it may: somebody waits, the launch is one workgroup and the stream runs.

@@ -13,7 +13,7 @@
 
 namespace zc {
 
-constexpr int kReportWords = 4 + ZC_MAX_K;      // status, tag and size of a call (or the four quality sums), and k values of n
+constexpr int kReportWords = 4 + ZC_MAX_K;      // most words that a request is for: status, tag and size of a call, and k values of n
 
 // A request's place in pinned memory.
 struct ReportSlot {
@@ -69,8 +69,8 @@ inline bool stream_runs(hipStream_t stream) {
   return known && capture == hipStreamCaptureStatusNone;
 }
 
-// A call's answer: every word of it says by its highest bit that it is there (none of them needs that bit: a status, a size, counts of values), so that
-// nothing has to be waited for between them and a last word.  The caller clears the slot's words before it is asked for, and has them all before it is
+// A call's answer: every word of it says by its highest bit that it is there (none of them needs that bit: a status, a size, and n of streams whose headers were all
+// accepted, for with a malformed one among them a call answers FORMAT and no n is handed on), so that nothing has to be waited for between them and a last word.  The caller clears the slot's words before it is asked for, and has them all before it is
 // given back.
 constexpr uint64_t kAnswered = uint64_t(1) << 63;
 
@@ -134,7 +134,32 @@ inline bool copy_words(const uint64_t* const* from, uint32_t count, uint64_t* to
   return hipStreamSynchronize(stream) == hipSuccess;
 }
 
-// The same by something that stores the words in a slot, if there is one.  `make`: see take.
+// A call's answer when everything enqueued on `stream` so far has run: its status and size, and then the `count` words at `more`, by something that stores them in a slot,
+// or, where there is none, by copies.  own: the call's status, tag and size.  `make`: see take.
+// launch(slot): enqueues on `stream` what stores the words in the slot; false: nothing was enqueued.
+template <typename LaunchFn>
+inline bool fetch_answer(ReportSlots& slots, const uint64_t* const (&own)[3], const uint64_t* const* more, uint32_t count, uint64_t* to, bool make,
+                         hipStream_t stream, LaunchFn launch) {
+  if (ReportSlot* const slot = stream_runs(stream) ? slots.take(make) : nullptr) {
+    clear_answer(slot, 2 + count);
+    // (An error of an earlier call still to be told could not be told from a failed launch: then the slot would be given back that is still written to.)
+    if (hipGetLastError() != hipSuccess || !launch(slot)) {
+      slots.give_back(slot);
+      return false;
+    }
+    return await_answer(slots, slot, 2 + count, to, stream);
+  }
+  // no slot, or the stream is being captured, which copy_words knows how to say
+  const uint64_t* from[kReportWords] = {own[0], own[1], own[2]};
+  uint64_t words[kReportWords];
+  for (uint32_t i = 0; i < count; ++i) from[3 + i] = more[i];
+  if (!copy_words(from, 3 + count, words, stream)) return false;
+  to[0] = (words[0] >> 32) == (words[1] >> 32) ? uint64_t(uint32_t(words[0])) : 0u;      // status bits count only under the tag of the last call
+  for (uint32_t i = 0; i < 1 + count; ++i) to[1 + i] = words[2 + i];
+  return true;
+}
+
+// Words by something that stores them in a slot, if there is one, or by copies.  `make`: see take.
 // launch(slot, seq): enqueues on `stream` what stores the words, and then seq, in the slot; false: nothing was enqueued.
 template <typename LaunchFn>
 inline bool report_words(ReportSlots& slots, const uint64_t* const* from, uint32_t count, uint64_t* to, bool make, hipStream_t stream,

@@ -8,7 +8,8 @@
 
 static int pins_to_refuse = 0, pins = 0, copies = 0, syncs = 0;
 static hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-static hipError_t capture_query = hipSuccess;
+static hipError_t capture_query = hipSuccess, pending = hipSuccess, sync_result = hipSuccess;
+static void (*at_sync)() = nullptr;       // what the GPU does while the host waits for the stream
 extern "C" {
 hipError_t hipHostMalloc(void** p, size_t size, unsigned int) {
   ++pins;
@@ -16,9 +17,14 @@ hipError_t hipHostMalloc(void** p, size_t size, unsigned int) {
   *p = std::calloc(1, size);
   return hipSuccess;
 }
-hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipGetLastError(void) {
+  const hipError_t e = pending;
+  return pending = hipSuccess, e;
+}
 hipError_t hipStreamSynchronize(hipStream_t) {
   ++syncs;
+  if (at_sync) at_sync();
+  if (sync_result != hipSuccess) return sync_result;
   return capturing == hipStreamCaptureStatusNone ? hipSuccess : hipErrorStreamCaptureUnsupported;
 }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { return *s = capturing, capture_query; }
@@ -107,6 +113,124 @@ int main() {
     CHECK(zc::report_words(slots, from, 5, to, false, nullptr, runs) && pins == before && to[0] == 11);
     CHECK(answered(slots));
     CHECK(zc::report_words(slots, from, 5, to, false, nullptr, runs) && pins == before + 1);
+  }
+
+  // The answers of codec calls: status bits under the call's tag, the size, and n of the streams.
+  const uint64_t status = (uint64_t(7) << 32) | 6, tag = uint64_t(7) << 32, other_tag = uint64_t(8) << 32, size = 4711, ns[3] = {1, 0, uint64_t(1) << 31};
+  const uint64_t* const own[3] = {&status, &tag, &size};
+  const uint64_t* const more[3] = {ns, ns + 1, ns + 2};
+  const uint64_t want[5] = {6, 4711, 1, 0, uint64_t(1) << 31};
+  auto store = [](zc::ReportSlot* s, int i, uint64_t w) { __atomic_store_n(&s->words[i], w | zc::kAnswered, __ATOMIC_RELEASE); };
+  auto right = [&](int count) { return std::memcmp(to, want, sizeof(uint64_t) * count) == 0; };
+  auto answers = [&](zc::ReportSlot* s) {
+    ++launches;
+    for (int i : {3, 0, 4, 2, 1}) store(s, i, want[i]);      // in any order
+    return true;
+  };
+  auto no_answer = [&](zc::ReportSlot*) { return ++launches, false; };
+  // the next call is answered through a slot, and with the right words
+  auto told = [&](zc::ReportSlots& slots) {
+    std::memset(to, 0xff, sizeof(to));
+    const int before = launches, copies_before = copies;
+    return zc::fetch_answer(slots, own, more, 3, to, true, nullptr, answers) && launches == before + 1 && copies == copies_before && right(5);
+  };
+
+  std::printf("an answer has none of the marks its words come with\n");
+  {
+    zc::ReportSlots slots;
+    CHECK(told(slots));
+    CHECK(told(slots));       // (through the same place, which still holds the marked words of the answer before)
+  }
+  std::printf("an answer is waited for to its last word, whichever that is\n");
+  {
+    zc::ReportSlots slots;
+    for (int late = 0; late < 5; ++late) {
+      CHECK(told(slots));     // (whose words are still there)
+      static zc::ReportSlot* slot;
+      static int which;
+      static uint64_t word;
+      which = late, word = want[late];
+      const int syncs_before = syncs;
+      at_sync = [] { __atomic_store_n(&slot->words[which], word | zc::kAnswered, __ATOMIC_RELEASE); };
+      std::memset(to, 0xff, sizeof(to));
+      CHECK(zc::fetch_answer(slots, own, more, 3, to, true, nullptr, [&](zc::ReportSlot* s) {
+        slot = s;
+        for (int i = 0; i < 5; ++i)
+          if (i != late) store(s, i, want[i]);
+        return true;
+      }));
+      at_sync = nullptr;
+      CHECK(syncs == syncs_before + 1 && right(5));
+    }
+  }
+  std::printf("an answer that does not come is no answer, and its place is not given to another\n");
+  {
+    zc::ReportSlots slots;
+    zc::ReportSlot* lost = nullptr;
+    auto all_but_the_size = [&](zc::ReportSlot* s) {
+      lost = s;
+      for (int i : {0, 2, 3, 4}) store(s, i, want[i]);
+      return true;
+    };
+    CHECK(!zc::fetch_answer(slots, own, more, 3, to, true, nullptr, all_but_the_size));
+    zc::ReportSlot* held[32] = {};
+    int got = 0;
+    while (got < 32 && (held[got] = slots.take(true)) != nullptr) CHECK(held[got++] != lost);
+    CHECK(got == 31);
+  }
+  std::printf("a stream that fails has no answer\n");
+  {
+    zc::ReportSlots slots;
+    sync_result = hipErrorUnknown;
+    CHECK(!zc::fetch_answer(slots, own, more, 3, to, true, nullptr, [](zc::ReportSlot*) { return true; }));
+    sync_result = hipSuccess;
+    CHECK(told(slots));
+  }
+  std::printf("an answer's launch that fails gives its place back\n");
+  {
+    zc::ReportSlots slots;
+    for (int i = 0; i < 100; ++i) CHECK(!zc::fetch_answer(slots, own, more, 3, to, true, nullptr, no_answer));
+    CHECK(told(slots));
+  }
+  std::printf("an error still to be told is told ahead of a launch, and costs no place\n");
+  {
+    zc::ReportSlots slots;
+    const int before = launches;
+    for (int i = 0; i < 100; ++i) {
+      pending = hipErrorInvalidValue;
+      CHECK(!zc::fetch_answer(slots, own, more, 3, to, true, nullptr, answers) && pending == hipSuccess);
+    }
+    CHECK(launches == before && told(slots));
+  }
+  std::printf("an answer by copies, which is no launch, does not mind such an error\n");
+  {
+    zc::ReportSlots slots;
+    for (int i = 0; i < 32; ++i) CHECK(slots.take(true) != nullptr);
+    const int before = launches;
+    for (const hipError_t e : {hipSuccess, hipErrorInvalidValue}) {
+      pending = e;
+      std::memset(to, 0xff, sizeof(to));
+      CHECK(zc::fetch_answer(slots, own, more, 3, to, true, nullptr, answers) && launches == before && right(5));
+    }
+    pending = hipSuccess;
+    const uint64_t* const of_another[3] = {&status, &other_tag, &size};      // status bits of an earlier call
+    CHECK(zc::fetch_answer(slots, of_another, more, 3, to, true, nullptr, answers) && to[0] == 0 && to[1] == 4711);
+  }
+  std::printf("a call on a stream that is being captured has no answer, and costs no place\n");
+  {
+    zc::ReportSlots slots;
+    capturing = hipStreamCaptureStatusActive;
+    const int before = launches;
+    for (int i = 0; i < 100; ++i) CHECK(!zc::fetch_answer(slots, own, more, 3, to, true, nullptr, answers));
+    capturing = hipStreamCaptureStatusNone;
+    CHECK(launches == before && told(slots));
+  }
+  std::printf("a caller who rules out allocations gets an answer by copies\n");
+  {
+    zc::ReportSlots slots;
+    const int before = launches, pins_before = pins;
+    std::memset(to, 0xff, sizeof(to));
+    CHECK(zc::fetch_answer(slots, own, nullptr, 0, to, false, nullptr, answers) && launches == before && pins == pins_before && right(2));
   }
   std::printf("ok\n");
   return 0;
