@@ -17,16 +17,7 @@
 
 namespace zc {
 
-// N: room for that many words (4, or all: the arguments travel with every launch).
-template <int N>
-struct ReportArgs {
-  const u64* from[N];
-  u32 count;
-  ReportSlot* to;
-  u64 seq;
-};
-
-// The same without that kernel, for a call of one workgroup: it stores the words itself when it is done (a compress and a decompress
+// Without that kernel, for a call of one workgroup: it stores the words itself when it is done (a compress and a decompress
 // call of 5120 values, each waited for, 25.9 us with two launches of the kernel above, 23.4 without).  What it has written has to be
 // where the next reader finds it by then, whatever stream that runs on, so it is released to the system first, as the end of a kernel
 // does.  With more workgroups each of them would have to do so, and they take turns at it: 33 of them and a count of those that are
@@ -71,35 +62,35 @@ inline bool launch_call_report(ReportSlot* slot, const Control* ctl, const u64* 
   return hipGetLastError() == hipSuccess;
 }
 
-template <int N>
-__global__ __launch_bounds__(128) void report_kernel(ReportArgs<N> a) {
-  static_assert(N <= 128, "a thread per word");
+// Words of any value, the four sums of zc_quality: a number behind them says that they are there.
+constexpr int kSumWords = 4;
+struct ReportArgs {
+  const u64* from[kSumWords];
+  u32 count;
+  ReportSlot* to;
+  u64 seq;
+};
+__global__ __launch_bounds__(64) void report_kernel(ReportArgs a) {
   if (threadIdx.x < a.count)
     __hip_atomic_store(&a.to->words[threadIdx.x], *a.from[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   // (what the call has written was released at its kernel's end, and these words go past the caches: all that is missing is that they have
-  // arrived before the number goes out.  A fence and a releasing store in this place made an answer 0.6 us later by itself; a waited ring round of 262 177 values is level
-  // either way.)
+  // arrived before the number goes out.  A fence and a releasing store in this place made an answer 0.6 us later by itself.)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) __hip_atomic_store(&a.to->seq, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <int N>
-inline bool launch_report(ReportSlot* slot, u64 seq, const u64* const* from, u32 count, hipStream_t stream) {
-  ReportArgs<N> a;
-  for (u32 i = 0; i < count; ++i) a.from[i] = from[i];
-  a.count = count;
-  a.to = slot;
-  a.seq = seq;
-  hipLaunchKernelGGL(report_kernel<N>, dim3(1), dim3(N <= 64 ? 64 : 128), 0, stream, a);
-  return hipGetLastError() == hipSuccess;
-}
-
-// The words at from[0 .. count) as they are when everything enqueued on `stream` so far has run.  `make`: the slots may be
+// The words at from[0 .. count), at most kSumWords, as they are when everything enqueued on `stream` so far has run.  `make`: the slots may be
 // pinned now.
 inline bool report_words(ReportSlots& slots, const u64* const* from, u32 count, u64* to, bool make, hipStream_t stream) {
   return report_words(slots, from, count, to, make, stream, [&](ReportSlot* slot, u64 seq) {
-    return count <= 4 ? launch_report<4>(slot, seq, from, count, stream) : launch_report<kReportWords>(slot, seq, from, count, stream);
+    ReportArgs a;
+    for (u32 i = 0; i < count; ++i) a.from[i] = from[i];
+    a.count = count;
+    a.to = slot;
+    a.seq = seq;
+    hipLaunchKernelGGL(report_kernel, dim3(1), dim3(64), 0, stream, a);
+    return hipGetLastError() == hipSuccess;
   });
 }
 
