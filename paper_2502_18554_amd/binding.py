@@ -7,6 +7,7 @@ if the HIP library has not been built, loading it raises.
 import ctypes as C
 import importlib.util
 import os
+import sysconfig
 from array import array
 
 import torch
@@ -87,13 +88,16 @@ def lib():
 
 def _load_native(L):
     global _native
-    path = os.path.join(_HERE, "_zc_calls.so")
+    path = os.path.join(_HERE, "_zc_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # (the one that was built for this Python)
     stream_of = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if not os.path.exists(path) or stream_of is None:
         return
-    spec = importlib.util.spec_from_file_location("_zc_calls", path)
-    native = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(native)
+    try:
+        spec = importlib.util.spec_from_file_location("_zc_calls", path)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+    except ImportError:              # one that does not load: ctypes takes all calls
+        return
     calls = (L.zc_compress_ex, L.zc_decompress_ex, L.zc_reduce_compressed_op, L.zc_reduce_step_op, L.zc_decompress_many)
     native.setup(*(C.cast(f, C.c_void_p).value for f in calls), torch._C._cuda_getDevice, stream_of)
     _native = native

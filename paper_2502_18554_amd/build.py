@@ -1,4 +1,4 @@
-"""Build the HIP library (csrc/*.hip -> libzc.so) for gfx950 with hipcc, and the native calls of the binding (_zc_calls.so), in-tree."""
+"""Build the HIP library (csrc/*.hip -> libzc.so) for gfx950 with hipcc, and the native calls of the binding for this Python, in-tree."""
 import os
 import subprocess
 import sysconfig
@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libzc.so")
 SOURCES = ["zc_api.hip"]
-CALLS = os.path.join(HERE, "_zc_calls.so")
+CALLS = os.path.join(HERE, "_zc_calls" + sysconfig.get_config_var("EXT_SUFFIX"))      # (named for this Python: another one leaves it alone)
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-shared",

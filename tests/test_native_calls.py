@@ -1,6 +1,7 @@
 """The binding's native calls against its own way through ctypes: the same arguments reach the library and the same results come back,
 whatever form they are given in; with the library's calls replaced, so that this needs no GPU."""
 import ctypes as C
+import sysconfig
 
 import numpy as np
 import pytest
@@ -145,3 +146,18 @@ def test_what_neither_takes(seen):
     with pytest.raises(IndexError):
         b.zc_reduce_compressed([X], [1, 2], Y, W)
     assert not seen
+
+
+def test_native_calls_of_another_python(monkeypatch, tmp_path):
+    """Native calls that were built for another Python are not looked at, and with some that do not load all calls go through ctypes, the first one
+    as the later ones."""
+    L = b.lib()
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert "-" in suffix                                   # (it names the Python)
+    monkeypatch.setattr(b, "_HERE", str(tmp_path))
+    monkeypatch.setattr(b, "_native", None)
+    for name in ("_zc_calls.so", "_zc_calls" + suffix.replace("cpython-3", "cpython-4"), "_zc_calls" + suffix):
+        (tmp_path / name).write_bytes(b"built elsewhere")
+        monkeypatch.setattr(b, "_lib", None)
+        assert b.lib() is not None and b._native is None
+        assert b.zc_strerror(0) == L.zc_strerror(0).decode()
