@@ -161,3 +161,19 @@ def test_native_calls_of_another_python(monkeypatch, tmp_path):
         monkeypatch.setattr(b, "_lib", None)
         assert b.lib() is not None and b._native is None
         assert b.zc_strerror(0) == L.zc_strerror(0).decode()
+
+
+def test_build_without_python_headers(monkeypatch, tmp_path):
+    """The library is built ahead of the native calls, and also where those cannot be."""
+    from paper_2502_18554_amd import build
+    ran = []
+    calls = tmp_path / "_zc_calls.so"
+    monkeypatch.setattr(build, "CALLS", str(calls))
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, check: ran.append(cmd[0]))
+    build.build()
+    assert ran == ["hipcc", "g++"]
+    ran.clear()
+    calls.write_bytes(b"of other sources")
+    monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build() == build.LIB
+    assert ran == ["hipcc"] and not calls.exists()
