@@ -136,6 +136,32 @@ def test_both_ways_are_alike(seen, monkeypatch, call, options):
     assert len(seen) == 2 and seen[0] == seen[1]
 
 
+# what the native calls leave to ctypes: by number in CALLS (numpy's numbers and arrays, a list that is too short), and a stream by name
+DECLINED = {7, 10, 11}
+
+
+@pytest.mark.parametrize("call", range(len(CALLS)))
+@pytest.mark.parametrize("options", [{}, {"sync": False}, {"sync": 1, "flags": 3}, {"stream": STREAM}, {"sync": False, "flags": 1}])
+def test_which_way_a_call_goes(seen, monkeypatch, call, options):
+    """The plain forms are answered by the native calls, the others are declined ahead of any call of the library."""
+    native, answers = b._native, []
+
+    class Listening:
+        def __getattr__(self, name):
+            def listen(*args):
+                before = len(seen)
+                r = getattr(native, name)(*args)
+                answers.append(r)
+                assert len(seen) == before + (r is not NotImplemented)
+                return r
+            return listen
+
+    monkeypatch.setattr(b, "_native", Listening())
+    assert CALLS[call](**options)[0] == 6
+    assert len(answers) == 1 and len(seen) == 1
+    assert (answers[0] is NotImplemented) == ("stream" in options or call in DECLINED)
+
+
 def test_what_neither_takes(seen):
     with pytest.raises(AttributeError):
         b.zc_compress(X, 10, 0.25, Y, None)
