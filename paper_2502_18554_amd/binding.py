@@ -155,8 +155,8 @@ def _size(t):
 
 
 def zc_compress(d_in, n, abs_eb, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
-    """Returns (status, total_bytes); total_bytes is None in the asynchronous form.  flags 0 goes through
-    zc_compress, anything else through zc_compress_ex."""
+    """zc_compress, or zc_compress_ex with flags, which is the same with flags 0.
+    Returns (status, total_bytes); total_bytes is None in the asynchronous form."""
     if _native:
         r = _native.compress(d_in, n, abs_eb, d_out, d_ws, sync, stream, out_cap, flags)
         if r is not NotImplemented:
@@ -190,8 +190,8 @@ def zc_compress_part(d_in, n, abs_eb, first_value, count, d_out, d_ws, sync=True
 
 
 def zc_decompress(d_in, in_bytes, d_out, d_ws, sync=True, stream=None, out_cap_elems=None, flags=0):
-    """Returns (status, n); n is None in the asynchronous form.  flags 0 goes through zc_decompress,
-    anything else through zc_decompress_ex."""
+    """zc_decompress, or zc_decompress_ex with flags, which is the same with flags 0.
+    Returns (status, n); n is None in the asynchronous form."""
     if _native:
         r = _native.decompress(d_in, in_bytes, d_out, d_ws, sync, stream, out_cap_elems, flags)
         if r is not NotImplemented:
@@ -223,8 +223,8 @@ def zc_decompress_range(d_in, in_bytes, first_value, count, d_out, d_ws, sync=Tr
 
 
 def zc_reduce_compressed(d_chunks, chunk_bytes, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
-    """d_chunks: list of device tensors holding the k operand streams.  Returns (status, total_bytes).
-    flags 0 goes through zc_reduce_compressed, anything else through zc_reduce_compressed_ex."""
+    """zc_reduce_compressed, or zc_reduce_compressed_ex with flags: zc_reduce_compressed_op of a Sum is the same.
+    d_chunks: list of device tensors holding the k operand streams.  Returns (status, total_bytes)."""
     if _native:
         r = _native.reduce(d_chunks, chunk_bytes, ZC_OP_SUM, d_out, d_ws, sync, stream, out_cap, flags)
         if r is not NotImplemented:
@@ -295,8 +295,8 @@ ZC_OP_SUM, ZC_OP_MAX, ZC_OP_MIN = 0, 1, 2
 
 
 def zc_reduce_step(d_chunk, chunk_bytes, d_local, n_local, d_out, d_ws, sync=True, stream=None, out_cap=None, flags=0):
-    """One ring round: received stream + local fp32 values -> stream of the sums.  Returns (status, total_bytes).
-    flags 0 goes through zc_reduce_step, anything else through zc_reduce_step_op."""
+    """One ring round: received stream + local fp32 values -> stream of the sums: zc_reduce_step, or with flags zc_reduce_step_op of a Sum, which is
+    the same with flags 0.  Returns (status, total_bytes)."""
     if flags or _native:
         return zc_reduce_step_op(d_chunk, chunk_bytes, d_local, n_local, ZC_OP_SUM, d_out, d_ws, sync, stream, out_cap, flags)
     nbytes = C.c_size_t(0) if sync else None
