@@ -26,6 +26,7 @@
 #pragma once
 
 #include "zc_common.h"
+#include "zc_large_tiles.h"
 #include "zc_place.h"
 #include "zc_report.h"
 #include "zc_scan.h"
@@ -789,23 +790,7 @@ __device__ inline bool open_reduce(const ReduceArgs& a, ReduceCall& c, u32& widt
 // but wide blocks, 4 x 4 194 301 values, 47 us with six and 41 with five; narrow ones, 8 x 2^24, 61.4 and 61.7.
 // The kernel of its own that plain streams with wide blocks had before was a launch of 3 us on every call.)
 // 80 registers and 32 bytes of scratch (plain streams: 96 and 44), which the common path's operand loop does not touch.
-// WAVES: segments of a tile, a wave each.  Where a tile has little to do, for it has few operands, half as many of them, of twice the size, look back sooner (a wave
-// spends a third of its life on that, and the chains are half as long); with many operands a large tile's waves end too far apart.  Three such
-// workgroups fit a compute unit where six of the others do, 768 and 1536 at the same time, so that which is better also depends on how full the last round is.
-// us with tiles of four segments and of eight (fields; hard data), tiles of four:
-//   2 x    733: 10.8 11.3 | 794: 11.6 11.2 | 1024: 12.9 11.7 | 1465: 18.1 15.3 | 1587: 19.1 19.4 | 1893: 22.9 20.2 | 2048: 24.1 21.5 | 8192: 71.5 67.5;   hard data   2048: 26.8 23.5
-//   4 x    611: 12.1 13.3 | 794: 14.3 13.4 | 1024: 15.5 13.8 | 1465: 20.5 18.8 | 1709: 27.2 27.8 | 2048: 28.6 27.0 | 8192: 85.8 83.9;   hard data   8192: 101.5 99.6
-//   6 x    550: 17.6 16.7 | 794: 19.6 17.4 | 1099: 23.2 24.4 | 1465: 27.7 26.8 | 1709: 34.0 35.4 | 2442: 44.0 43.4
-//   8 x    611: 20.3 19.5 | 1024: 25.5 22.3 | 1099: 27.2 30.8 | 1709: 41.0 42.5 | 2048: 45.9 45.7 | 8192: 146.9 147.9;   hard data   611: 21.7 22.2 | 1024: 25.3 23.1
-//  12 x    525: 21.0 20.7 | 794: 23.6 22.4;   16 x   525: 29.5 30.7 | 794: 35.9 33.9 | 1024: 41.8 41.4;   hard data   525: 32.0 33.7 | 1024: 37.3 37.3
-// (tiles: what the host knows of them, see few_segments; up to 611 tiles of up to four operands reduce_few_kernel was the one that it was measured against.)
-constexpr int kLargeWaves = 8;
-__host__ constexpr bool sum_large_tiles(int k, u64 tiles) {
-  if (k < 2) return false;
-  if (tiles <= 1024) return k <= 12 && tiles > (k <= 4 ? 768u : 640u);
-  if (tiles <= 1536) return k <= 4 || (k <= 7 && tiles > 1400);
-  return k <= 3 ? tiles > 1700 : k <= 7 && tiles > 1900;
-}
+// WAVES: segments of a tile, a wave each: see zc_large_tiles.h.
 template <bool IX, int WAVES = kTileWaves, typename... A>
 __global__ __launch_bounds__(64 * WAVES, IX ? 6 : 5) void reduce_kernel(ReduceArgs a, A... answer) {
   __shared__ __attribute__((aligned(16))) u32 lds[WAVES * kWholeStage + kCopyOver];   // also holds an operand's payload

@@ -242,8 +242,8 @@ constexpr int kFewWaves = 4, kFewThreads = 64 * kFewWaves;
 // 1024 tiles, 8 operands 26.3 and 26.4; 2048 tiles, 2 operands 26.5 and 28.0).  Fewer segments a tile, us:
 //   of four, two, one    128 tiles   4 operands 9.5 9.6 11.2 | 5: 11.2 10.1 11.5 | 8: 12.3 10.6 11.8 | 12: 15.7 12.7 12.7 | 16: 18.6 13.9 13.4
 //                        245 tiles   4: 9.8 11.0 20.2 | 5: 11.6 11.3 20.5 | 16: 19.4 16.1 25.2 | 64: 60 49 59;   512 tiles   16: 25.6 32.9
-// (From 769 tiles on reduce_kernel with large tiles is faster for few operands, see sum_large_tiles; this was the faster one up to 1024 before.)
-constexpr u64 kFewTiles = 512, kFewTilesFull = 768;
+// (From 769 tiles on reduce_kernel with large tiles is faster, where a call may have those, see zc_large_tiles.h.)
+constexpr u64 kFewTiles = 512, kFewTilesFull = 1024;
 __host__ constexpr int few_segments(int k, u64 tiles) {
   if (k < 2) return 0;
   if (k >= 12 && tiles <= kFewTiles / 4) return 1;

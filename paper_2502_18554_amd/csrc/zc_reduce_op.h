@@ -558,18 +558,7 @@ __host__ constexpr int few_op_segments(int k, u64 tiles) {
   return (tiles <= 256 ? k >= 8 : tiles <= 512 && k >= 12) ? 2 : 4;
 }
 
-// Whether they run with tiles of eight segments, a wave each, of which two workgroups fit a compute unit where four of the others do (see sum_large_tiles): 512 and 1024 at the same time, so that
-// it depends on how full the last round is.  us with tiles of four segments and of eight (fields; hard data), tiles of four:
-//   2 x    611: 11.8 12.6 | 794: 13.5 12.7 | 1099: 19.1 18.6 | 1465: 23.9 19.2 | 2048: 29.1 24.0 | 2442: 33.5 32.3 | 8192: 93.9 89.0
-//   4 x    611: 14.6 16.0 | 794: 16.8 16.0 | 1099: 22.6 23.3 | 1465: 28.0 24.1 | 2048: 34.7 30.9 | 8192: 114.6 112.0;   hard data   1024: 22.2 21.0 | 2048: 41.0 39.0 | 8192: 139.6 140.4
-//   8 x    525: 23.3 26.5 | 794: 28.2 27.4 | 1024: 29.6 28.3 | 1099: 36.6 39.4 | 1465: 43.3 41.5 | 2048: 55.1 54.0;   16 x   525: 38.9 44.1 | 1024: 50.9 48.7
-__host__ constexpr bool op_large_tiles(int k, u64 tiles) {
-  if (k < 2 || tiles <= 768) return false;
-  if (tiles <= 1024 || k == 2) return true;
-  return tiles > 1400 && (k == 3 || (k <= 8 && tiles <= 4096));
-}
-
-// SEGS: segments of a tile.  Their operands are divided among PARTS = 4 / SEGS waves each (one from four segments on), whose extremes meet in LDS: see zc_reduce_few.h.
+// SEGS: segments of a tile (eight: see zc_large_tiles.h).  Their operands are divided among PARTS = 4 / SEGS waves each (one from four segments on), whose extremes meet in LDS: see zc_reduce_few.h.
 template <bool IX, int OP, int SEGS = kTileWaves, typename... A>
 __global__ __launch_bounds__(SEGS > kTileWaves ? 64 * SEGS : kTileThreads, 4) void reduce_op_kernel(ReduceArgs a, A... answer) {
   constexpr int WAVES = SEGS > kTileWaves ? SEGS : kTileWaves;

@@ -1,0 +1,25 @@
+// Which reduces run with tiles of eight segments (csrc/zc_large_tiles.h): the calls that they were measured to be slower for have none.
+#include <cstdio>
+
+#include "../../paper_2502_18554_amd/csrc/zc_large_tiles.h"
+
+struct Call {
+  int k;
+  uint64_t tiles;
+  bool large;
+};
+
+int main() {
+  int wrong = 0;
+  const Call sums[] = {{1, 900, false}, {2, 900, false}, {2, 901, true}, {3, 784, false}, {3, 785, true}, {5, 640, false}, {5, 641, true}, {8, 720, false}, {8, 785, true}, {13, 900, false}, {4, 1500, true}, {5, 1400, false},
+                       {7, 1401, true}, {8, 1500, false}, {2, 1537, false}, {2, 1700, false}, {2, 1701, true}, {3, 1700, false}, {3, 1781, true}, {4, 1709, false}, {4, 1851, true},
+                       {6, 1709, false}, {6, 2048, true}, {6, 2442, false}, {5, 3072, true}, {5, 3073, false}, {7, 4096, false}, {6, 8192, false}, {4, 8192, true}, {2, 1 << 18, true}};
+  const Call extremes[] = {{1, 900, false}, {2, 769, false}, {8, 784, false}, {2, 785, true}, {64, 1024, true}, {2, 1030, false}, {3, 1030, false}, {8, 1099, false}, {2, 1201, true}, {4, 1301, true},
+                           {8, 1401, true}, {9, 1500, false}, {2, 1600, true}, {3, 1600, false}, {8, 1600, false}, {3, 1751, true}, {4, 1800, false}, {4, 1851, true}, {8, 1931, true},
+                           {8, 2048, true}, {2, 2049, false}, {2, 2401, true}, {3, 2049, false}, {8, 2056, false}, {4, 2056, false}, {5, 4096, false}, {3, 4300, false}, {3, 8192, true}, {4, 8192, false}};
+  for (const Call& c : sums)
+    if (zc::sum_large_tiles(c.k, c.tiles) != c.large) ++wrong, std::printf("sum of %d, %llu tiles\n", c.k, (unsigned long long)c.tiles);
+  for (const Call& c : extremes)
+    if (zc::op_large_tiles(c.k, c.tiles) != c.large) ++wrong, std::printf("extreme of %d, %llu tiles\n", c.k, (unsigned long long)c.tiles);
+  return wrong != 0;
+}

@@ -174,6 +174,15 @@ def test_answers_of_synchronous_calls(tmp_path):
     assert run.returncode == 0, run.stdout
 
 
+def test_calls_by_large_tiles(tmp_path):
+    """The rules that pick tiles of eight segments, at the limits and where such tiles are slower."""
+    src = os.path.join(ROOT, "tests", "host", "large_tiles_host.cpp")
+    exe = str(tmp_path / "large_tiles_host")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", src, "-o", exe], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert run.returncode == 0, run.stdout
+
+
 def test_calls_from_two_threads_share_no_setting(libzc):
     """The library keeps no settings: two host threads that want different stream variants and tile
     hand-outs say so in their calls and never see each other's choice.  (Without a GPU only the
