@@ -611,7 +611,7 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     ra.n_least = ra.n_most = n;
     tiles = ra.end_tile - ra.first_tile;
   }
-  const bool large = ix && !ranged && !ra.ticketed && (op == ZC_OP_SUM ? sum_large_tiles(k, likely) : op_large_tiles(k, likely));
+  const bool large = ix && !ranged && !ra.ticketed && room_for_tiles(out_cap, likely) && (op == ZC_OP_SUM ? sum_large_tiles(k, likely) : op_large_tiles(k, likely));
   int segs = 0;
   if (op != ZC_OP_SUM) segs = ranged || ra.ticketed ? kTileWaves : few_op_segments(k, likely);
   else if (!ranged && !ra.ticketed && !large) segs = few_segments(k, likely);

@@ -43,4 +43,9 @@ constexpr bool op_large_tiles(int k, uint64_t tiles) {
   return (k == 2 && tiles > 2400) || (k == 3 && tiles > 4400);
 }
 
+// Tiles are what the workspace and the operands' bytes allow; with a larger workspace than a call needs they are far fewer, and tiles of eight, of which then not every
+// compute unit has one, are up to 20 % slower (Max of 8 x 2^20 values in a workspace for 1000 tiles 15.1 us by tiles of four, 18.2).  So the output must have room for as many too: for their values at 4 bytes each, or a stream of them at its longest, which is a little
+// more.  (In a workspace and an output that are both larger the loss remains.)
+constexpr bool room_for_tiles(uint64_t out_cap, uint64_t tiles) { return tiles == 0 || out_cap / (4 * 4 * 64 * 32) >= tiles - 1; }
+
 }  // namespace zc

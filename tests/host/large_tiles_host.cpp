@@ -1,5 +1,6 @@
 // Which reduces run with tiles of eight segments (csrc/zc_large_tiles.h): the calls that they were measured to be slower for have none.
 #include <cstdio>
+#include <initializer_list>
 
 #include "../../paper_2502_18554_amd/csrc/zc_large_tiles.h"
 
@@ -21,5 +22,14 @@ int main() {
     if (zc::sum_large_tiles(c.k, c.tiles) != c.large) ++wrong, std::printf("sum of %d, %llu tiles\n", c.k, (unsigned long long)c.tiles);
   for (const Call& c : extremes)
     if (zc::op_large_tiles(c.k, c.tiles) != c.large) ++wrong, std::printf("extreme of %d, %llu tiles\n", c.k, (unsigned long long)c.tiles);
+
+  // n values: tiles as the workspace tells them, and the output's room (bytes of values, or of the longest stream)
+  for (const uint64_t n : {1ull, 8191ull, 8192ull, 8193ull, 4194301ull, 20000003ull, 67108864ull, 2147483648ull}) {
+    const uint64_t tiles = (n + 8191) / 8192, blocks = (n + 31) / 32;
+    const bool holds = zc::room_for_tiles(4 * n, tiles) && zc::room_for_tiles(32 + 133 * blocks, tiles) && zc::room_for_tiles(uint64_t(1) << 40, tiles) &&
+                       (tiles < 40 || !zc::room_for_tiles(32 + 133 * blocks, tiles + tiles / 16));
+    if (!holds) ++wrong, std::printf("room for %llu values\n", (unsigned long long)n);
+  }
+  if (zc::room_for_tiles(32 + 133ull * 131072, 3600)) ++wrong, std::printf("4 194 304 values in a workspace for many more\n");
   return wrong != 0;
 }

@@ -1,5 +1,6 @@
 """Reduces by tiles of eight segments, which only indexed streams have: the limits of the rule that picks them, and last tiles of one segment, of four and of
-five, with wide blocks and without, with both ways to read the chains, against the reference codec; what is wrong in the upper half of a tile."""
+five, with wide blocks and without, with both ways to read the chains, against the reference codec; what is wrong in the upper half of a tile; and calls of
+which the host takes there to be more tiles than there are."""
 import numpy as np
 import pytest
 import torch
@@ -97,3 +98,18 @@ def test_range_in_large_tiles(zcref, seg):
     q[seg * SEG + 40:(seg + 1) * SEG] = 2 ** 29 + 5
     beyond = zcref.encode_codes(q, 1e-3)[1]
     assert u.gpu_reduce([beyond, beyond], n)[0] == ZC_ERR_RANGE == zcref.reduce([beyond, beyond])[0]
+
+
+# A workspace and an output made for many more values: tiles of eight then reduce streams of any size, down to one of a few values.
+@pytest.mark.parametrize("n", [33, 2049, 5 * 8192 + 1, 130 * 8192 - 1, 525 * 8192 - 777])
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("made_for", [900 * 8192, 3000 * 8192])
+def test_few_tiles_in_a_large_workspace(zcref, n, wide, made_for):
+    refs = _operands(zcref, 3, n, 14, wide and n > 6 * SEG)
+    room = 32 + 5 * (made_for // 32)               # streams whose sizes allow as many tiles, as far as the host knows
+    padded = [np.concatenate([r, np.zeros(max(0, room - r.size), np.uint8)]) for r in refs]
+    ws = u.workspace(made_for, 3)
+    for op in (0, 1, 2):
+        st_ref, ref = zcref.reduce(refs, op=op)[:2]
+        st, r, _ = u.gpu_reduce(padded, made_for, op=op or None, ws=ws)
+        assert st == st_ref == ZC_OK and r.tobytes() == ref.tobytes(), (op, u.first_diff(r, ref))
