@@ -116,7 +116,8 @@ size_t zc_compress_bound_ex(size_t n, unsigned flags);
  * have faster kernels, chosen by the smaller of what the operands' sizes and the workspace allow, so that
  * a call that is given just zc_workspace_bytes(n, k) bytes (ws_bytes; the buffer may be larger) can be
  * up to twice as fast: the Sum of 16 x 2^20 values 12.5 us so, 22.1 with a workspace for 2^27.
- * (From 640 tiles on an output that has no room for as many tells them that the workspace is larger.) */
+ * (From 640 tiles on an output that has no room for as many, or operands of hardly any bytes, tell them that the
+ * workspace is larger.) */
 size_t zc_workspace_bytes(size_t n_max, int k_max);
 
 /* fZ-light compression (Section 3.3).  d_in: n binary32 values, 16-byte aligned.

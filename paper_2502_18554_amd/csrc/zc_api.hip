@@ -565,11 +565,12 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   const WorkspaceLayout l = workspace_layout(d_ws, ws_bytes, k);
   if (l.tiles_cap < 1) return ZC_ERR_ARG;
   // the output's tiles need a look-back descriptor each, whatever the variant
-  u64 tiles = l.tiles_cap, tiles_in = 1;
+  u64 tiles = l.tiles_cap, tiles_in = 1, least_bytes = ~u64(0);
   for (int i = 0; i < k; ++i) {
     const u64 t = num_tiles(blocks_bound(chunk_bytes[i]));
     if (t < tiles) tiles = t;
     if (t > tiles_in) tiles_in = t;
+    if (chunk_bytes[i] < least_bytes) least_bytes = chunk_bytes[i];
   }
   if (tiles > kMaxTiles) tiles = kMaxTiles;
   if (tiles < 1) tiles = 1;
@@ -611,7 +612,7 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
     ra.n_least = ra.n_most = n;
     tiles = ra.end_tile - ra.first_tile;
   }
-  const bool large = ix && !ranged && !ra.ticketed && room_for_tiles(out_cap, likely) && (op == ZC_OP_SUM ? sum_large_tiles(k, likely) : op_large_tiles(k, likely));
+  const bool large = ix && !ranged && !ra.ticketed && tiles_are_there(out_cap, least_bytes, likely) && (op == ZC_OP_SUM ? sum_large_tiles(k, likely) : op_large_tiles(k, likely));
   int segs = 0;
   if (op != ZC_OP_SUM) segs = ranged || ra.ticketed ? kTileWaves : few_op_segments(k, likely);
   else if (!ranged && !ra.ticketed && !large) segs = few_segments(k, likely);

@@ -44,8 +44,14 @@ constexpr bool op_large_tiles(int k, uint64_t tiles) {
 }
 
 // Tiles are what the workspace and the operands' bytes allow; with a larger workspace than a call needs they are far fewer, and tiles of eight, of which then not every
-// compute unit has one, are up to 20 % slower (Max of 8 x 2^20 values in a workspace for 1000 tiles 15.1 us by tiles of four, 18.2).  So the output must have room for as many too: for their values at 4 bytes each, or a stream of them at its longest, which is a little
-// more.  (In a workspace and an output that are both larger the loss remains.)
-constexpr bool room_for_tiles(uint64_t out_cap, uint64_t tiles) { return tiles == 0 || out_cap / (4 * 4 * 64 * 32) >= tiles - 1; }
+// compute unit has one, are up to 20 % slower (Max of 8 x 2^20 values in a workspace for 1000 tiles 15.1 us by tiles of four, 18.2).  So the output must have room for as
+// many too, for their values at 4 bytes each, or a stream of them at its longest, which is a little more; and the shortest operand must have twice the bytes that as many blocks
+// take at least (a field at 1e-2 of its range has four times as many, sinusoids twice; streams of hardly anything but constant blocks, up to 20 % slower for that, have fewer).  Where all of
+// these are larger than the call, which for a field at 1e-4 is up to five times, the loss remains: only the GPU knows better, and kernels that could take
+// either tile when they know are 8 to 15 % slower for all calls (more registers spilled; Sum of 4 x 2^26 values 95.3 us, 102.4).
+constexpr bool tiles_are_there(uint64_t out_cap, uint64_t least_bytes, uint64_t tiles) {
+  constexpr uint64_t kBlocks = 4 * 64;         // of a tile
+  return tiles == 0 || (out_cap / (4 * 32 * kBlocks) >= tiles - 1 && least_bytes / (2 * 5 * kBlocks) >= tiles - 1);
+}
 
 }  // namespace zc

@@ -23,13 +23,15 @@ int main() {
   for (const Call& c : extremes)
     if (zc::op_large_tiles(c.k, c.tiles) != c.large) ++wrong, std::printf("extreme of %d, %llu tiles\n", c.k, (unsigned long long)c.tiles);
 
-  // n values: tiles as the workspace tells them, and the output's room (bytes of values, or of the longest stream)
+  // n values: tiles as the workspace tells them, the output's room (bytes of values, or of the longest stream) and the shortest operand's bytes
+  const uint64_t plenty = uint64_t(1) << 40;
   for (const uint64_t n : {1ull, 8191ull, 8192ull, 8193ull, 4194301ull, 20000003ull, 67108864ull, 2147483648ull}) {
-    const uint64_t tiles = (n + 8191) / 8192, blocks = (n + 31) / 32;
-    const bool holds = zc::room_for_tiles(4 * n, tiles) && zc::room_for_tiles(32 + 133 * blocks, tiles) && zc::room_for_tiles(uint64_t(1) << 40, tiles) &&
-                       (tiles < 40 || !zc::room_for_tiles(32 + 133 * blocks, tiles + tiles / 16));
-    if (!holds) ++wrong, std::printf("room for %llu values\n", (unsigned long long)n);
+    const uint64_t tiles = (n + 8191) / 8192, blocks = (n + 31) / 32, longest = 32 + 133 * blocks;
+    const bool holds = zc::tiles_are_there(4 * n, 11 * blocks, tiles) && zc::tiles_are_there(longest, longest, tiles) && zc::tiles_are_there(plenty, plenty, tiles) &&
+                       (tiles < 40 || (!zc::tiles_are_there(longest, plenty, tiles + tiles / 16) && !zc::tiles_are_there(plenty, 11 * blocks, tiles + tiles / 4)));
+    if (!holds) ++wrong, std::printf("tiles of %llu values\n", (unsigned long long)n);
   }
-  if (zc::room_for_tiles(32 + 133ull * 131072, 3600)) ++wrong, std::printf("4 194 304 values in a workspace for many more\n");
+  // 4 194 304 values in a workspace for many more; with an output for as many, and 34 bytes a block
+  if (zc::tiles_are_there(32 + 133ull * 131072, plenty, 3600) || zc::tiles_are_there(plenty, 34ull * 131072, 3600)) ++wrong, std::printf("larger workspaces\n");
   return wrong != 0;
 }

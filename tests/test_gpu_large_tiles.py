@@ -106,7 +106,7 @@ def test_range_in_large_tiles(zcref, seg):
 @pytest.mark.parametrize("made_for", [900 * 8192, 3000 * 8192])
 def test_few_tiles_in_a_large_workspace(zcref, n, wide, made_for):
     refs = _operands(zcref, 3, n, 14, wide and n > 6 * SEG)
-    room = 32 + 5 * (made_for // 32)               # streams whose sizes allow as many tiles, as far as the host knows
+    room = 32 + 10 * (made_for // 32)              # streams whose sizes speak for as many tiles, as far as the host knows
     padded = [np.concatenate([r, np.zeros(max(0, room - r.size), np.uint8)]) for r in refs]
     ws = u.workspace(made_for, 3)
     for op in (0, 1, 2):
