@@ -382,6 +382,14 @@ __device__ __forceinline__ const Args& kernel_args_again() {
   return *(const Args*)p;
 }
 
+// AT for a kernel of this type: its parameters one behind the other, each aligned as its type is.  (What hands out an AT is checked against this.)
+template <typename Args, typename... Params>
+constexpr int kernel_args_at(void (*)(Params...)) {
+  int at = 0, found = -1;
+  ((at = (at + int(alignof(Params)) - 1) / int(alignof(Params)) * int(alignof(Params)), found = std::is_same_v<Params, Args> ? at : found, at += int(sizeof(Params))), ...);
+  return found;
+}
+
 // Sum over the 64 lanes (result uniform).
 __device__ inline u32 wave_sum_u32(u32 v) {
   v += dpp_mov<kDppQuadSwap1>(v);

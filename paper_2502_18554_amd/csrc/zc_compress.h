@@ -55,7 +55,7 @@ struct CompressInput {
   const float* in;
   u64 n;
 };
-constexpr int kCompressArgsAt = 24;          // bytes of arguments in front of CompressArgs
+constexpr int kCompressArgsAt = 24;          // bytes of arguments in front of CompressArgs (checked behind the kernel)
 
 // Round-to-nearest-even of r for |r| < 2^31 as the low word of r + 1.5 * 2^52.
 __device__ inline i32 rint_small(double r) {
@@ -476,6 +476,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == kPackWaves ? 8 : 4) void compr
   compress_tile<TICKETS, WAVES>({in, n}, a, first_tile, end_tile, lds, sh_tile, sh_wave_total, sh_base);
   give_answer(a.answer, a.ctl);
 }
+static_assert(kernel_args_at<CompressArgs>(decltype(&compress_kernel<false>){}) == kCompressArgsAt);
 
 // The stream of no values: a header (and the one closing entry of an indexed stream's index).
 struct EmptyStreamArgs {
