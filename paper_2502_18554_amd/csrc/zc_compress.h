@@ -450,9 +450,12 @@ __device__ __forceinline__ void compress_tile(const CompressInput& first, const 
 #pragma unroll
         for (int p = 0; p < 15; ++p) pw[1 + p] = bf.f[p];
       }
-      // (what a lane writes for a wide block, 16 words, is overwritten by the block's own)
+      // (what a lane writes for a wide block, 16 words, is overwritten by the block's own, which other lanes write)
       stage_wave_words<16>([&](auto i) { return pw[decltype(i)::value]; }, pl, wl);
-      if (pl.wmax > 15) stage_wide_blocks(pl, wblock0, __ballot(pl.w > 15), wl);      // uniform
+      if (pl.wmax > 15) {                        // uniform
+        wave_lds_sync();
+        stage_wide_blocks(pl, wblock0, __ballot(pl.w > 15), wl);
+      }
     });
     if (lane == 0) write_index_entry(sink, tile * u32(WAVES) + u32(wave), tb.words + pl.wave_off);
     if (staged) copy_staged_wave<16, FEW>(sink, pl, tb.words, wl, lane);
