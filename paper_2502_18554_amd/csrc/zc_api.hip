@@ -146,8 +146,9 @@ class CallAnswer {
 // width tables itself (see judge_plain_streams); if not, their positions are computed ahead of it.  Either way is right
 // whatever the streams hold.
 bool index_plain_streams(const StreamRef* streams, int k, u64 tiles, u64 likely, const WorkspaceLayout& l, hipStream_t stream,
-                         bool reduce = false) {
-  if (likely * u64(k) <= self_tiles(k, reduce) && tiles * u64(k) <= kMostTables * self_tiles(k, reduce)) return true;
+                         bool reduce = false, bool tickets = false) {
+  const u64 most = self_tiles(k, reduce, tickets);
+  if (likely * u64(k) <= most && tiles * u64(k) <= kMostTables * most) return true;
   ScanArgs sa;
   for (int i = 0; i < k; ++i) sa.streams[i] = streams[i];
   sa.k = k;
@@ -586,7 +587,7 @@ static int reduce_impl(const void* const* d_chunks, const size_t* chunk_bytes, i
   // many there are, and with a larger one a call that could do without the launch ahead may get it all the same)
   const u64 made_for = l.tiles_cap > kWsSpareTiles ? l.tiles_cap - kWsSpareTiles : 1;
   const u64 likely = tiles < made_for ? tiles : made_for;
-  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, likely, l, stream, true);
+  ra.self = ix ? 0u : index_plain_streams(ra.in, k, tiles_in, likely, l, stream, true, (flags & ZC_TILES_BY_TICKET) != 0);
   ra.out = static_cast<u8*>(d_out);
   ra.out_cap = out_cap;
   ra.ctl = l.ctl;
@@ -680,7 +681,7 @@ static int step_impl(const void* d_chunk, size_t chunk_bytes, const float* d_loc
   StepArgs ta;
   ta.in.base = static_cast<const u8*>(d_chunk);
   ta.in.bytes = chunk_bytes;
-  const bool self = !ix && index_plain_streams(&ta.in, 1, tiles_of_stream(chunk_bytes, l, false), tiles, l, stream);
+  const bool self = !ix && index_plain_streams(&ta.in, 1, tiles_of_stream(chunk_bytes, l, false), tiles, l, stream, false, (flags & ZC_TILES_BY_TICKET) != 0);
   ta.local = d_local;
   ta.n_local = n_local;
   ta.index = l.index;

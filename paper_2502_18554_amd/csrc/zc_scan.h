@@ -361,7 +361,15 @@ struct PlainSurvey {
 // reduces (see below), so that there the launch pays earlier with many streams:
 //   Max of 2     368: 12.7 11.7 | 490: 12.8 12.9;   Sum of 4   392: 12.4 11.2 | 512: 12.5 11.9 | 588: 12.8 12.6;   of 8   392: 13.3 12.2 | 512: 13.3 12.7
 //   Sum of 12    300: 14.0 12.4 | 396: 13.8 13.9;   of 16   256: 13.4 12.0 | 352: 13.6 13.5;   of 24   192: 14.7 14.4;   of 32   32: 16.0 16.9
-__host__ constexpr u64 self_tiles(int k, bool reduce) { return reduce ? (k <= 8 ? 480 : k <= 16 ? 320 : k <= 24 ? 192 : 0) : 512; }
+// Where tiles are handed out by tickets a workgroup does it twice in a call that writes (the verdict ahead of its ticket, the place behind it), and it pays less far; with the
+// launch ahead and without:
+//   ring round   320: 18.8 16.3 | 340: 22.2 23.0 | 400: 16.0 17.2 | 512: 16.1 18.8; hard data   320: 22.5 19.9 | 340: 23.4 24.1 | 512: 20.5 22.8
+//   Sum of 4     340: 22.6 21.0 | 480: 23.3 22.7;   Max of 8   320: 24.2 21.7 | 400: 22.9 23.1 | 480: 22.7 24.0;   Sum of 16   256: 29.5 27.5 | 288: 26.0 28.7 | 320: 26.4 29.0
+__host__ constexpr u64 self_tiles(int k, bool reduce, bool tickets) {
+  if (!reduce) return tickets ? 320 : 512;
+  if (tickets && k > 4) return k <= 12 ? 320 : k <= 16 ? 256 : k <= 24 ? 192 : 0;
+  return k <= 8 ? 480 : k <= 16 ? 320 : k <= 24 ? 192 : 0;
+}
 
 // The host does not know the tiles, only what the output or the workspace has room for and the bytes, which are at most
 // kMostTables times what the tables of so many tiles need (133 bytes a block where its tables take 5).  With more bytes than

@@ -49,6 +49,27 @@ def test_tables(zcref, nb):
             assert st == st_ref and (st != ZC_OK or r.tobytes() == ref.tobytes()), (k, op)
 
 
+# The limits where tiles are handed out by tickets: 320 tiles of a ring round, 480 of up to four streams, 320, 256 and 192 of more.
+@pytest.mark.parametrize("k,tiles", [(1, 320), (1, 321), (2, 240), (2, 241), (8, 40), (8, 41), (16, 16), (16, 17), (24, 8), (24, 9)])
+def test_tables_by_tickets(zcref, k, tiles):
+    nb = tiles * 256
+    n = nb * 32 - 5
+    s = [_stream(zcref, nb, 9 * nb + i) for i in range(k)]
+    u.set_tickets(True)
+    try:
+        if k == 1:
+            local = np.zeros(n, np.float32)
+            st_ref, ref = zcref.reduce_step(s[0], local)[:2]
+            st, r, _ = u.gpu_reduce_step(s[0], local)
+            assert st == st_ref and r.tobytes() == ref.tobytes(), u.first_diff(r, ref)
+        for op in (None, 1):
+            st_ref, ref = zcref.reduce(s, op=op or 0)[:2]
+            st, r, _ = u.gpu_reduce(s, n, op=op)
+            assert st == st_ref == ZC_OK and r.tobytes() == ref.tobytes(), u.first_diff(r, ref)
+    finally:
+        u.set_tickets(False)
+
+
 @pytest.mark.parametrize("byte", [32, 33, 0x7F, 0x80, 0x81, 0xE0, 0xFF])
 def test_bytes_that_are_no_width(zcref, byte):
     nb = 10 * PIECE + 37
