@@ -3,8 +3,8 @@
 // What bounds a small call is the host: a compression of a few thousand values runs for 3 to 4 us, and its caller spent 1.3 us on
 // marshalling by ctypes and 3 on the launch.  Here the marshalling is 0.5 us (a chunk of 5120 values compressed and decompressed, each waited for, 22.7 us,
 // then 20.5; 16 buffers of 5120 values decompressed by one call 8.2, then 6.4; a waited ring round of 262 177 values 16.4, then 15.0).
-// Nothing is decided here: whatever is not of the plainest form (a stream by name, sizes that are no Python integers, lists of other
-// kinds or lengths) is answered with NotImplemented, and binding.py takes the call its own way.
+// Nothing is decided here: whatever is not of a plain form (lists of other kinds or lengths, negative numbers) is answered with NotImplemented, ahead of
+// anything that takes time, and binding.py takes the call its own way, 0.1 us later.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -23,10 +23,10 @@ struct Calls {
   decltype(&zc_decompress_many) many;
 } g_calls;
 PyObject *g_device, *g_raw_stream;             // torch's own: the current device, and the current stream's handle on a device
-PyObject *g_data_ptr, *g_nbytes, *g_numel;     // names
+PyObject *g_data_ptr, *g_nbytes, *g_numel, *g_cuda_stream;     // names
 
-// Every reader below returns false where the object is not of the plainest form (nothing raised), or with an exception set.
-bool whole(PyObject* o, uint64_t& v) {
+// Every reader below returns false where the object is not of a plain form (nothing raised), or with an exception set.
+bool exact(PyObject* o, uint64_t& v) {
   if (!PyLong_CheckExact(o)) return false;
   v = PyLong_AsUnsignedLongLong(o);
   if (v == ~uint64_t(0) && PyErr_Occurred()) {
@@ -34,6 +34,24 @@ bool whole(PyObject* o, uint64_t& v) {
     return false;
   }
   return true;
+}
+
+// Other whole numbers too (numpy's, enumerations), which may run code of their own.
+bool whole(PyObject* o, uint64_t& v) {
+  if (PyLong_CheckExact(o)) return exact(o, v);
+  if (!PyIndex_Check(o)) return false;
+  PyObject* const i = PyNumber_Index(o);
+  if (!i) return false;
+  const bool ok = exact(i, v);
+  Py_DECREF(i);
+  return ok;
+}
+
+bool real(PyObject* o, double& v) {
+  v = PyFloat_AsDouble(o);
+  if (v != -1.0 || !PyErr_Occurred()) return true;
+  PyErr_Clear();
+  return false;
 }
 
 bool small(PyObject* o, int& v) {
@@ -46,7 +64,7 @@ bool small(PyObject* o, int& v) {
 bool of_method(PyObject* tensor, PyObject* name, uint64_t& v) {
   PyObject* r = PyObject_CallMethodNoArgs(tensor, name);
   if (!r) return false;
-  const bool ok = whole(r, v);
+  const bool ok = exact(r, v);
   Py_DECREF(r);
   return ok;
 }
@@ -58,31 +76,38 @@ bool address(PyObject* tensor, void*& p) {
   return true;
 }
 
-bool bytes_of(PyObject* tensor, uint64_t& v) {
-  PyObject* r = PyObject_GetAttr(tensor, g_nbytes);
+bool of_attribute(PyObject* o, PyObject* name, uint64_t& v) {
+  PyObject* r = PyObject_GetAttr(o, name);
   if (!r) return false;
-  const bool ok = whole(r, v);
+  const bool ok = exact(r, v);
   Py_DECREF(r);
   return ok;
 }
+bool bytes_of(PyObject* tensor, uint64_t& v) { return of_attribute(tensor, g_nbytes, v); }
 
-// A capacity: as given, or the tensor's own (bytes, or elements).
-bool capacity(PyObject* given, PyObject* tensor, bool elements, uint64_t& v) {
-  if (given != Py_None) return whole(given, v);
+// A capacity: as given (read ahead of all else), or the tensor's own (bytes, or elements).
+bool given_capacity(PyObject* given, uint64_t& v) { return given == Py_None || whole(given, v); }
+bool own_capacity(PyObject* given, PyObject* tensor, bool elements, uint64_t& v) {
+  if (given != Py_None) return true;
   if (!elements) return bytes_of(tensor, v);
   v = 0;
   return tensor == Py_None || of_method(tensor, g_numel, v);
 }
 
-bool current_stream(PyObject* given, void*& stream) {
-  if (given != Py_None) return false;
+// The stream as given, or the current one.
+bool stream_of(PyObject* given, void*& stream) {
+  uint64_t v = 0;
+  if (given != Py_None) {
+    if (!of_attribute(given, g_cuda_stream, v)) return false;
+    stream = reinterpret_cast<void*>(v);
+    return true;
+  }
   PyObject* device = PyObject_CallNoArgs(g_device);
   if (!device) return false;
   PyObject* r = PyObject_CallOneArg(g_raw_stream, device);
   Py_DECREF(device);
   if (!r) return false;
-  uint64_t v = 0;
-  const bool ok = whole(r, v);
+  const bool ok = exact(r, v);
   Py_DECREF(r);
   stream = reinterpret_cast<void*>(v);
   return ok;
@@ -131,7 +156,7 @@ bool counts(PyObject* list, Py_ssize_t k, size_t* to) {
   if (!items) return false;
   for (Py_ssize_t i = 0; i < k; ++i) {
     uint64_t v;
-    if (!whole(items[i], v)) return false;
+    if (!exact(items[i], v)) return false;      // (nothing runs that could change the list)
     to[i] = size_t(v);
   }
   return true;
@@ -142,12 +167,13 @@ PyObject* compress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   void *in, *out, *ws, *stream;
   uint64_t n, cap, ws_bytes;
   int flags;
-  if (n_args != 9 || !whole(a[1], n) || !PyFloat_CheckExact(a[2]) || !small(a[8], flags) || !address(a[0], in) || !address(a[3], out) ||
-      !capacity(a[7], a[3], false, cap) || !address(a[4], ws) || !bytes_of(a[4], ws_bytes) || !current_stream(a[6], stream))
+  double eb64;
+  if (n_args != 9 || !whole(a[1], n) || !real(a[2], eb64) || !small(a[8], flags) || !given_capacity(a[7], cap) || !address(a[0], in) || !address(a[3], out) ||
+      !own_capacity(a[7], a[3], false, cap) || !address(a[4], ws) || !bytes_of(a[4], ws_bytes) || !stream_of(a[6], stream))
     return not_this_way();
   const int sync = PyObject_IsTrue(a[5]);
   if (sync < 0) return nullptr;
-  const float eb = float(PyFloat_AS_DOUBLE(a[2]));
+  const float eb = float(eb64);
   size_t size = 0;
   int st;
   Py_BEGIN_ALLOW_THREADS
@@ -161,8 +187,8 @@ PyObject* decompress(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   void *in, *out, *ws, *stream;
   uint64_t in_bytes, cap, ws_bytes;
   int flags;
-  if (n_args != 8 || !whole(a[1], in_bytes) || !small(a[7], flags) || !address(a[0], in) || !address(a[2], out) ||
-      !capacity(a[6], a[2], true, cap) || !address(a[3], ws) || !bytes_of(a[3], ws_bytes) || !current_stream(a[5], stream))
+  if (n_args != 8 || !whole(a[1], in_bytes) || !small(a[7], flags) || !given_capacity(a[6], cap) || !address(a[0], in) || !address(a[2], out) ||
+      !own_capacity(a[6], a[2], true, cap) || !address(a[3], ws) || !bytes_of(a[3], ws_bytes) || !stream_of(a[5], stream))
     return not_this_way();
   const int sync = PyObject_IsTrue(a[4]);
   if (sync < 0) return nullptr;
@@ -179,9 +205,9 @@ PyObject* step(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   void *in, *local, *out, *ws, *stream;
   uint64_t in_bytes, n, cap, ws_bytes;
   int op, flags;
-  if (n_args != 11 || !whole(a[1], in_bytes) || !whole(a[3], n) || !small(a[4], op) || !small(a[10], flags) || !address(a[0], in) ||
-      !address(a[2], local) || !address(a[5], out) || !capacity(a[9], a[5], false, cap) || !address(a[6], ws) || !bytes_of(a[6], ws_bytes) ||
-      !current_stream(a[8], stream))
+  if (n_args != 11 || !whole(a[1], in_bytes) || !whole(a[3], n) || !small(a[4], op) || !small(a[10], flags) || !given_capacity(a[9], cap) ||
+      !address(a[0], in) || !address(a[2], local) || !address(a[5], out) || !own_capacity(a[9], a[5], false, cap) || !address(a[6], ws) || !bytes_of(a[6], ws_bytes) ||
+      !stream_of(a[8], stream))
     return not_this_way();
   const int sync = PyObject_IsTrue(a[7]);
   if (sync < 0) return nullptr;
@@ -202,8 +228,8 @@ PyObject* reduce(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   size_t sizes[ZC_MAX_K];
   if (n_args != 9 || !(PyList_CheckExact(a[0]) || PyTuple_CheckExact(a[0]))) return not_this_way();
   const Py_ssize_t k = PySequence_Fast_GET_SIZE(a[0]);
-  if (k < 1 || k > ZC_MAX_K || !small(a[2], op) || !small(a[8], flags) || !counts(a[1], k, sizes) || !addresses(a[0], k, chunks) ||
-      !address(a[3], out) || !capacity(a[7], a[3], false, cap) || !address(a[4], ws) || !bytes_of(a[4], ws_bytes) || !current_stream(a[6], stream))
+  if (k < 1 || k > ZC_MAX_K || !small(a[2], op) || !small(a[8], flags) || !given_capacity(a[7], cap) || !counts(a[1], k, sizes) || !addresses(a[0], k, chunks) ||
+      !address(a[3], out) || !own_capacity(a[7], a[3], false, cap) || !address(a[4], ws) || !bytes_of(a[4], ws_bytes) || !stream_of(a[6], stream))
     return not_this_way();
   const int sync = PyObject_IsTrue(a[5]);
   if (sync < 0) return nullptr;
@@ -224,11 +250,10 @@ PyObject* many(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   size_t sizes[ZC_MAX_K], caps[ZC_MAX_K], ns[ZC_MAX_K] = {};
   if (n_args != 8 || !(PyList_CheckExact(a[0]) || PyTuple_CheckExact(a[0]))) return not_this_way();
   const Py_ssize_t k = PySequence_Fast_GET_SIZE(a[0]);
-  if (k < 1 || k > ZC_MAX_K || !small(a[7], flags) || !counts(a[1], k, sizes) || !addresses(a[0], k, chunks) || !addresses(a[2], k, outs))
+  if (k < 1 || k > ZC_MAX_K || !small(a[7], flags) || !counts(a[1], k, sizes) || (a[6] != Py_None && !counts(a[6], k, caps)) || !addresses(a[0], k, chunks) ||
+      !addresses(a[2], k, outs))
     return not_this_way();
-  if (a[6] != Py_None) {
-    if (!counts(a[6], k, caps)) return not_this_way();
-  } else {
+  if (a[6] == Py_None) {
     for (Py_ssize_t i = 0; i < k; ++i) {
       PyObject** const items = entries(a[2], k);
       if (!items) return not_this_way();
@@ -240,7 +265,7 @@ PyObject* many(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
       caps[i] = size_t(v);
     }
   }
-  if (!address(a[3], ws) || !bytes_of(a[3], ws_bytes) || !current_stream(a[5], stream)) return not_this_way();
+  if (!address(a[3], ws) || !bytes_of(a[3], ws_bytes) || !stream_of(a[5], stream)) return not_this_way();
   const int sync = PyObject_IsTrue(a[4]);
   if (sync < 0) return nullptr;
   int st;
@@ -301,6 +326,7 @@ PyMODINIT_FUNC PyInit__zc_calls() {
   g_data_ptr = PyUnicode_InternFromString("data_ptr");
   g_nbytes = PyUnicode_InternFromString("nbytes");
   g_numel = PyUnicode_InternFromString("numel");
-  if (!g_data_ptr || !g_nbytes || !g_numel) return nullptr;
+  g_cuda_stream = PyUnicode_InternFromString("cuda_stream");
+  if (!g_data_ptr || !g_nbytes || !g_numel || !g_cuda_stream) return nullptr;
   return PyModule_Create(&g_module);
 }

@@ -1,5 +1,5 @@
 """The entry points without flags (zc_compress, zc_decompress, zc_reduce_compressed, zc_reduce_compressed_ex, zc_reduce_step) called as C functions, waited for and not:
-the same streams and values as their forms with flags, and the reference codec's.  (The binding reaches them only in calls that name a stream.)"""
+the same streams and values as their forms with flags, and the reference codec's.  (The binding reaches them only where its native calls decline.)"""
 import ctypes as C
 
 import numpy as np

@@ -123,6 +123,10 @@ CALLS = [
     lambda **o: b.zc_decompress_many([X, Z], [11, 12], [Y, W], W, **o),
     lambda **o: b.zc_decompress_many([X], [11], [Y], W, out_cap_elems=[9], **o),
     lambda **o: b.zc_decompress_many([X] * 64, [11] * 64, [Y] * 64, W, **o),
+    lambda **o: b.zc_decompress_many([X], [np.int64(11)], [Y], W, **o),
+    lambda **o: b.zc_compress(X, np.int32(10), np.float32(0.25), Y, W, **o),
+    lambda **o: b.zc_compress(X, 10, 1, Y, W, out_cap=np.int64(7), **o),
+    lambda **o: b.zc_decompress(X, np.uint64(33), Y, W, out_cap_elems=np.int64(3), **o),
 ]
 
 
@@ -136,8 +140,8 @@ def test_both_ways_are_alike(seen, monkeypatch, call, options):
     assert len(seen) == 2 and seen[0] == seen[1]
 
 
-# what the native calls leave to ctypes: by number in CALLS (numpy's numbers and arrays, a list that is too short), and a stream by name
-DECLINED = {7, 10, 11}
+# what the native calls leave to ctypes: by number in CALLS (an array of sizes, a list that is too short, numpy's numbers in a list)
+DECLINED = {10, 11, 15}
 
 
 @pytest.mark.parametrize("call", range(len(CALLS)))
@@ -159,7 +163,7 @@ def test_which_way_a_call_goes(seen, monkeypatch, call, options):
     monkeypatch.setattr(b, "_native", Listening())
     assert CALLS[call](**options)[0] == 6
     assert len(answers) == 1 and len(seen) == 1
-    assert (answers[0] is NotImplemented) == ("stream" in options or call in DECLINED)
+    assert (answers[0] is NotImplemented) == (call in DECLINED)
 
 
 def test_what_neither_takes(seen):
@@ -169,6 +173,10 @@ def test_what_neither_takes(seen):
         b.zc_decompress(7, 10, Y, W)
     with pytest.raises((TypeError, C.ArgumentError)):
         b.zc_compress(X, 10.0, 0.25, Y, W)
+    with pytest.raises((TypeError, C.ArgumentError)):
+        b.zc_compress(X, 10, "0.25", Y, W)
+    with pytest.raises(AttributeError):
+        b.zc_compress(X, 10, 0.25, Y, W, stream=7)
     with pytest.raises(IndexError):
         b.zc_reduce_compressed([X], [1, 2], Y, W)
     assert not seen
